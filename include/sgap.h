@@ -49,7 +49,7 @@
  *     +0, whatever C held before.  A row's result may be -0 or +0 where the
  *     exact sum is zero.
  *   - Placement (speed only, never results): any 4-byte aligned addresses are
- *     accepted (16-byte aligned B and C allow 16-byte loads).  Where rows of B
+ *     accepted.  Where rows of B
  *     are gathered at random out of memory, the operands of one matrix are
  *     served faster out of ONE allocation, packed one after the other, than
  *     out of five allocations that each start on a large page boundary
@@ -82,7 +82,9 @@ typedef enum {
  *   operations.
  *     row-split schedule   : the group_size lanes share one row
  *       ({<1/g row, c col>, r} with g = r = group_size, Section 6.2); a plain
- *       tree sum, one writeback lane, plain store.
+ *       tree sum, one writeback lane, plain store.  (A row of many thousand
+ *       entries is shared by all groups of its workgroup instead of holding
+ *       one of them up; it still has one plain store.)
  *     nnz-balanced schedule: lane = one stored entry ({<1 nnz, c col>, r},
  *       Section 6.2); the group performs a SEGMENTED reduction keyed by row
  *       (Fig. 1c), one writeback lane per run of equal rows.
@@ -130,9 +132,9 @@ int sgap_get_schedule(void);
  *               SGAP_REDUCE_PARALLEL; units per lane for SGAP_REDUCE_SERIAL)
  *   strategy    an sgap_strategy
  *   stream      hipStream_t or NULL
- * The number of dense columns per lane (the paper's c) is chosen from N and
- * the pointer alignment: 4 (one 16-byte load) if N % 4 == 0 and B, C are
- * 16-byte aligned, else 2, else 1 (Section 7.2, coarsening rule).
+ * The number of dense columns per lane (the paper's c, Section 7.2) is 4 (one
+ * 16-byte load at any 4-byte aligned address) for N >= 4, 2 for N = 2 and 3,
+ * and 1 for N = 1.
  * The nnz-balanced schedule reads rowptr[M] on the device and runs a
  * fixed-size grid, so this call never synchronises with the host.
  */
@@ -202,8 +204,8 @@ int sgap_spmm_csr_gr(int64_t M, int64_t K, int64_t N,
  *   persistent      1: the row-split schedule launches only as many workgroups
  *                   as the chip holds at once and each loops over work items.
  *   nnz_tile        stored entries per tile of the nnz-balanced serial strategy:
- *                   256, 512, 1024 or 2048 (the two small ones need N % 4 == 0
- *                   and 16-byte aligned B and C, else the automatic choice is kept).
+ *                   256, 512, 1024 or 2048 (the two small ones need N >= 4, else
+ *                   the automatic choice is kept).
  *   wave_rows       lane layout of the row-split serial strategy: 1 = one wavefront
  *                   owns group_size consecutive rows (at most 63) and all its 64
  *                   lanes hold column chunks of c = 4, 2 or 1 columns, so that a
@@ -553,14 +555,14 @@ int sgap_version(void);
  *                        over work items; 0 (default): one workgroup per item.
  *   SGAP_TUNE_NNZ_TILE   stored entries per tile of the nnz-balanced serial
  *                        strategy: 256, 512, 1024 or 2048 (the two small ones
- *                        need N % 4 == 0 and 16-byte aligned B and C, else
+ *                        need N >= 4, else
  *                        the automatic choice is kept); 0 = automatic, from
  *                        nnz and the size of the chip.
  *   SGAP_TUNE_SDDMM_ROW_CACHE  1 (default): sgap_sddmm_csr's parallel strategy
  *                        hands a group consecutive stored entries and keeps
  *                        the current row of X1 in registers when
- *                        J <= 16 * group_size and the operands are 16-byte
- *                        aligned; 0: every entry loads both of its rows.
+ *                        4 <= J <= 16 * group_size; 0: every entry loads
+ *                        both of its rows.
  * Knobs 6 and 7 (long rows by column windows) of earlier versions are gone:
  * that path needs working memory and is chosen per call, see sgap_config;
  * their numbers are refused with SGAP_ERR_INVALID_ARG.

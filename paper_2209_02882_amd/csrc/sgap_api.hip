@@ -180,13 +180,13 @@ struct LaunchDebugSegReduce {
 
 hipError_t launch_debug_group_reduce(const float* in, float* out, int g, int r, int lc, hipStream_t s)
 {
-    if (!dispatch_group(g, lc, 1, LaunchDebugReduce{in, out, r, s})) return hipErrorInvalidValue;
+    if (!dispatch_group(g, lc, 4, LaunchDebugReduce{in, out, r, s})) return hipErrorInvalidValue;
     return hipGetLastError();
 }
 hipError_t launch_debug_group_seg_reduce(const float* in, const int32_t* span, float* out, int g, int lc,
                                          hipStream_t s)
 {
-    if (!dispatch_group(g, lc, 1, LaunchDebugSegReduce{in, span, out, s})) return hipErrorInvalidValue;
+    if (!dispatch_group(g, lc, 4, LaunchDebugSegReduce{in, span, out, s})) return hipErrorInvalidValue;
     return hipGetLastError();
 }
 // mode 0: copy src -> dst; 1: read src only (dst is a one-float sink); 2: write dst only
@@ -247,6 +247,7 @@ int pow2_ceil_capped(int64_t v, int cap)
 
 constexpr int kXcds = 8;            // accelerator dies, each with its own L2
 constexpr int64_t kMaxEntries = 2147483647LL - 65535;  // 32-bit positions with room for a tile past the end
+constexpr int kSmallGrid = 4;       // workgroups per compute unit below which row-split parallel stacks no rows on a group
 constexpr int kAutoTileCols = 128;  // 512 bytes of a B row per work item
 constexpr int kAutoWindowKb = 3072;   // KiB of B per column window of the long-rows path: most of a die's 4 MiB L2
 constexpr int kAutoLongRows = 8192;   // capacity of the list of long rows when the caller names none
@@ -311,7 +312,8 @@ int check_config(const sgap_config& c)
     return SGAP_OK;
 }
 
-int widest_vec(int64_t N, const void* p, const void* q)
+// Columns per lane of the kernels that need aligned accesses (a wavefront per row, long rows by column windows).
+int aligned_vec(int64_t N, const void* p, const void* q)
 {
     const uintptr_t align_bits = reinterpret_cast<uintptr_t>(p) | reinterpret_cast<uintptr_t>(q);
     if (N % 4 == 0 && (align_bits & 15) == 0) return 4;
@@ -349,10 +351,10 @@ int spmm_impl(int64_t M, int64_t K, int64_t N, const int32_t* rowptr, const int3
     if (nnz_hint > 0 && (!colidx || !vals))
         return fail(SGAP_ERR_INVALID_ARG, "colidx and vals must not be null when A has entries");
 
-    // columns per lane (coarsening c): widest vector the shape and alignment allow
-    const int vec = widest_vec(N, B, C);
+    const int vec = lane_columns(N);  // columns per lane (coarsening c)
     const int64_t chunks = (N + vec - 1) / vec;
-    const bool windows = windows_apply(c, vec) && K > 0;
+    const int avec = aligned_vec(N, B, C);
+    const bool windows = windows_apply(c, avec) && K > 0;
     if (windows) {
         const int64_t need = spmm_panels_workspace_bytes(K, N, window_bytes_of(c), long_rows_of(c));
         if (!workspace || workspace_bytes < need)
@@ -396,6 +398,11 @@ int spmm_impl(int64_t M, int64_t K, int64_t N, const int32_t* rowptr, const int3
             rows_per_slot = (int)(432.0 / (avg_row * slots) + 0.5);
             if (rows_per_slot < 1) rows_per_slot = 1;
             if (rows_per_slot > 1024 / slots) rows_per_slot = 1024 / slots > 0 ? 1024 / slots : 1;
+            // a small matrix: spread over the chip before groups get a second row (1,024 rows of 10 entries, N = 32,
+            // G = 8: 256 workgroups instead of 24)
+            const int64_t col_tiles = (N + tile_cols - 1) / tile_cols;
+            const int64_t spread = M * col_tiles / ((int64_t)slots * cus * kSmallGrid);
+            if (rows_per_slot > spread) rows_per_slot = spread > 1 ? (int)spread : 1;
         }
         // Serial strategy in the widest lane layout: one wavefront per group_size consecutive rows (at most 63),
         // all 64 lanes on column chunks of 1, 2 or 4 columns (the widest that fills most of the lanes).  On request
@@ -404,7 +411,7 @@ int spmm_impl(int64_t M, int64_t K, int64_t N, const int32_t* rowptr, const int3
         // entries the narrower layout, with more rows in flight per workgroup, is faster (stencil27 at N = 256:
         // 1.27 against 1.52 ms) and 8-byte loads cost as much as 16-byte ones (N = 128: 0.62 against 0.94 ms).
         const bool wave_wanted = c.wave_rows == 1 ? N >= 48 : c.wave_rows == 0 && windows && N >= 192;
-        const int wave_vec = wave_wanted && !par && reduce_size == 0 ? (N > 128 ? vec : N > 64 ? (vec < 2 ? vec : 2) : 1) : 0;
+        const int wave_vec = wave_wanted && !par && reduce_size == 0 ? (N > 128 ? avec : N > 64 ? (avec < 2 ? avec : 2) : 1) : 0;
         const int wave_rows_count = group_size > 63 ? 63 : group_size;
         if (reduce_size != 0) {
             // every row receives atomic adds
@@ -478,7 +485,7 @@ int tune_impl(int64_t M, int64_t K, int64_t N, const int32_t* rowptr, const int3
     auto rate = [&](const sgap_config& c) {
         if (status != SGAP_OK) return;
         // a window size the caller's workspace does not cover is not a candidate
-        if (windows_apply(c, widest_vec(N, B, C)) && K > 0 &&
+        if (windows_apply(c, aligned_vec(N, B, C)) && K > 0 &&
             (!workspace || workspace_bytes < sgap::spmm_panels_workspace_bytes(K, N, window_bytes_of(c), long_rows_of(c))))
             return;
         sgap_tuned_point pt;
@@ -505,7 +512,7 @@ int tune_impl(int64_t M, int64_t K, int64_t N, const int32_t* rowptr, const int3
         // long rows by column windows, if the caller brought working memory for the default list and window
         sgap_config probe = config_from_globals(SGAP_SCHED_ROW_SPLIT, SGAP_REDUCE_SERIAL, 1, 0);
         probe.long_row_min = 1024;
-        const int vec = widest_vec(N, B, C);
+        const int vec = aligned_vec(N, B, C);
         if (workspace && K > 0 && windows_apply(probe, vec) &&
             workspace_bytes >= sgap::spmm_panels_workspace_bytes(K, N, window_bytes_of(probe), long_rows_of(probe)) &&
             (reinterpret_cast<uintptr_t>(workspace) & 255) == 0) {
@@ -681,10 +688,7 @@ static int sddmm_impl(int64_t M, int64_t K, int64_t J, const int32_t* rowptr, co
     }
     if (J > 0 && (!X1 || !X2T)) return fail(SGAP_ERR_INVALID_ARG, "X1 and X2T must not be null when J > 0");
 
-    const uintptr_t align_bits = reinterpret_cast<uintptr_t>(X1) | reinterpret_cast<uintptr_t>(X2T);
-    int vec = 1;
-    if (J % 4 == 0 && (align_bits & 15) == 0) vec = 4;
-    else if (J % 2 == 0 && (align_bits & 7) == 0) vec = 2;
+    const int vec = lane_columns(J);
 
     SpmmArgs a;
     a.M = M; a.K = K; a.N = J;
@@ -699,7 +703,7 @@ static int sddmm_impl(int64_t M, int64_t K, int64_t J, const int32_t* rowptr, co
     mark(ev0);
     const bool par = strategy == SGAP_REDUCE_PARALLEL;
     hipError_t err;
-    if (long_row_min > 0 && vec == 4 && J >= 32 && J <= 256 && K > 0) {
+    if (long_row_min > 0 && aligned_vec(J, X1, X2T) == 4 && J >= 32 && J <= 256 && K > 0) {
         const int64_t window_bytes = (int64_t)(window_kb > 0 ? window_kb : 2048) * 1024;
         const int64_t cap = max_long_rows > 0 ? max_long_rows : kAutoLongRows;
         if (!workspace || workspace_bytes < sddmm_panels_workspace_bytes(K, J, window_bytes, cap) ||
@@ -785,11 +789,7 @@ int sgap_mttkrp_csf_ex(int64_t I, int64_t K, int64_t L, int64_t J, const int32_t
     if (K > 0 && L > 0 && (!X1 || !X2)) return fail(SGAP_ERR_INVALID_ARG, "X1 and X2 must not be null");
     // (fidx, eptr, eidx and vals are read only for fibers that fptr announces)
 
-    const uintptr_t align_bits =
-        reinterpret_cast<uintptr_t>(X1) | reinterpret_cast<uintptr_t>(X2) | reinterpret_cast<uintptr_t>(Y);
-    int vec = 1;
-    if (J % 4 == 0 && (align_bits & 15) == 0) vec = 4;
-    else if (J % 2 == 0 && (align_bits & 7) == 0) vec = 2;
+    const int vec = lane_columns(J);
     const bool par = strategy == SGAP_REDUCE_PARALLEL;
     const int g = par ? group_size : 1;
     const int lc = pow2_ceil_capped((J + vec - 1) / vec, 64 / g);

@@ -75,16 +75,22 @@ struct Vec {
     }
 };
 
-// VEC consecutive floats starting at an address aligned to VEC*4 bytes.
+// Two and four floats as one access that asks for no more than 4-byte alignment: the vector memory path of this
+// chip takes such addresses, so that the columns per lane need not divide the row length (N = 37: ten 16-byte loads
+// per row of B instead of thirty-seven 4-byte ones).
+typedef float native_f4 __attribute__((ext_vector_type(4), aligned(4)));
+typedef float native_f2 __attribute__((ext_vector_type(2), aligned(4)));
+
+// VEC consecutive floats (any 4-byte aligned address).
 template <int VEC>
 __device__ __forceinline__ Vec<VEC> load_vec(const float* __restrict__ p)
 {
     Vec<VEC> r;
     if constexpr (VEC == 4) {
-        const float4 t = *reinterpret_cast<const float4*>(p);
+        const native_f4 t = *reinterpret_cast<const native_f4*>(p);
         r.v[0] = t.x; r.v[1] = t.y; r.v[2] = t.z; r.v[3] = t.w;
     } else if constexpr (VEC == 2) {
-        const float2 t = *reinterpret_cast<const float2*>(p);
+        const native_f2 t = *reinterpret_cast<const native_f2*>(p);
         r.v[0] = t.x; r.v[1] = t.y;
     } else {
         r.v[0] = *p;
@@ -96,9 +102,11 @@ template <int VEC>
 __device__ __forceinline__ void store_vec(float* __restrict__ p, const Vec<VEC>& r)
 {
     if constexpr (VEC == 4) {
-        *reinterpret_cast<float4*>(p) = make_float4(r.v[0], r.v[1], r.v[2], r.v[3]);
+        native_f4 t = {r.v[0], r.v[1], r.v[2], r.v[3]};
+        *reinterpret_cast<native_f4*>(p) = t;
     } else if constexpr (VEC == 2) {
-        *reinterpret_cast<float2*>(p) = make_float2(r.v[0], r.v[1]);
+        native_f2 t = {r.v[0], r.v[1]};
+        *reinterpret_cast<native_f2*>(p) = t;
     } else {
         *p = r.v[0];
     }
@@ -112,9 +120,6 @@ __device__ __forceinline__ T load_stream(const T* __restrict__ p)
     return __builtin_nontemporal_load(p);
 }
 
-typedef float native_f4 __attribute__((ext_vector_type(4)));
-typedef float native_f2 __attribute__((ext_vector_type(2)));
-
 template <int VEC>
 __device__ __forceinline__ void store_vec_stream(float* __restrict__ p, const Vec<VEC>& r)
 {
@@ -126,6 +131,43 @@ __device__ __forceinline__ void store_vec_stream(float* __restrict__ p, const Ve
         __builtin_nontemporal_store(t, reinterpret_cast<native_f2*>(p));
     } else {
         __builtin_nontemporal_store(r.v[0], p);
+    }
+}
+
+// The columns of a lane whose chunk starts at column k < N: k .. k + VEC, or, where fewer than VEC columns are left,
+// the last VEC columns of the row (N >= VEC): no lane reads past a row, and the columns it shares with the lane in
+// front of it come out the same in both, so that a plain store of all VEC of them is right whichever lands last.
+// Where sums are ADDED somewhere the lane first brings its own columns to the front (from_last_columns).
+// RAGGED = false: N is known to be a multiple of VEC (kernels whose registers are all spoken for come in both forms).
+template <int VEC, bool RAGGED = true>
+__device__ __forceinline__ int64_t lane_first_col(int64_t k, int64_t N)
+{
+    if constexpr (VEC == 1 || !RAGGED) return k;
+    else return k + VEC <= N ? k : N - VEC;
+}
+template <int VEC, bool RAGGED = true>
+__device__ __forceinline__ uint32_t lane_first_col(uint32_t k, uint32_t N)
+{
+    if constexpr (VEC == 1 || !RAGGED) return k;
+    else return k + VEC <= N ? k : N - VEC;
+}
+
+// Columns of this lane's chunk that the lane in front of it holds as well: k - lane_first_col(k, N), 0 .. VEC-1.
+// Afterwards v[i] belongs to column k + i; what lies past the end of the row is zero.
+template <int VEC, bool RAGGED = true>
+__device__ __forceinline__ void from_last_columns(Vec<VEC>& x, int shared)
+{
+    if constexpr (VEC > 1 && RAGGED) {
+        if (shared <= 0) return;
+        Vec<VEC> y;
+#pragma unroll
+        for (int i = 0; i < VEC; ++i) {
+            y.v[i] = 0.0f;
+#pragma unroll
+            for (int j = i + 1; j < VEC; ++j)
+                if (j - i == shared) y.v[i] = x.v[j];
+        }
+        x = y;
     }
 }
 
@@ -157,14 +199,6 @@ struct BRow {
 inline bool offsets_fit_32(const SpmmArgs& a)
 {
     return a.K <= (1 << 24) && a.N * 4 < (1 << 24) && a.K * a.N * 4 <= 0xffffffffLL;
-}
-
-// Cross-group merge: hardware fp32 atomic add (no return value needed).
-template <int VEC>
-__device__ __forceinline__ void atomic_add_vec(float* __restrict__ p, const Vec<VEC>& r)
-{
-#pragma unroll
-    for (int i = 0; i < VEC; ++i) unsafeAtomicAdd(p + i, r.v[i]);
 }
 
 // How an nnz-balanced kernel cuts the stored entries: tile = positions per LDS
@@ -253,17 +287,24 @@ hipError_t launch_reorder_rows(int64_t M, int64_t K, const int32_t* rowptr, cons
                                bool by_length, int32_t* perm, int32_t* rowptr_out, int32_t* colidx_out,
                                float* vals_out, void* workspace, int compute_units, hipStream_t s);
 
+// Columns per lane for rows of N dense columns: four wherever a row has four, since a 16-byte access costs the
+// vector memory path as much as a 4-byte one and needs no more than 4-byte alignment.
+inline int lane_columns(int64_t N) { return N >= 4 ? 4 : N >= 2 ? 2 : 1; }
+
 // Generic (g, lc, vec) -> template instance dispatch.  F is a functor with
 //   template <int G, int LC, int VEC> void operator()() const
+// Rows of one column take one lane, rows of two or three at most two (lane_columns), so the narrow instances exist
+// for those lane counts only.
 template <int G, int LC, typename F>
 inline bool dispatch_vec(int vec, F&& f)
 {
     switch (vec) {
         case 4: f.template operator()<G, LC, 4>(); return true;
-        case 2: f.template operator()<G, LC, 2>(); return true;
-        case 1: f.template operator()<G, LC, 1>(); return true;
-        default: return false;
+        case 2: if constexpr (LC <= 2) { f.template operator()<G, LC, 2>(); return true; } break;
+        case 1: if constexpr (LC == 1) { f.template operator()<G, LC, 1>(); return true; } break;
+        default: break;
     }
+    return false;
 }
 
 template <int G, typename F>

@@ -169,8 +169,9 @@ __global__ __launch_bounds__(kBlock) void mttkrp_kernel(MttkrpArgs a, int rows_p
     for (int64_t k0 = 0; k0 < a.J; k0 += (int64_t)LC * VEC) {
         const int64_t k = k0 + (int64_t)chunk * VEC;
         const bool k_ok = k < a.J;
-        const BRow<OFF32> x2row(a.X2, a.J, k_ok ? k : 0);
-        const GlobalRows<VEC, OFF32> x2rows(a.X2, a.J, k_ok ? k : 0);
+        const int64_t k_lane = k_ok ? lane_first_col<VEC>(k, a.J) : 0;  // the VEC columns this lane holds
+        const BRow<OFF32> x2row(a.X2, a.J, k_lane);
+        const GlobalRows<VEC, OFF32> x2rows(a.X2, a.J, k_lane);
         for (int r = 0; r < rows_per_slot; ++r) {
             // the lanes of a slot share `row`, so whole slots leave together
             const int64_t row = row_first + (interleave ? slot + (int64_t)r * SLOTS : (int64_t)slot * rows_per_slot + r);
@@ -185,7 +186,7 @@ __global__ __launch_bounds__(kBlock) void mttkrp_kernel(MttkrpArgs a, int rows_p
                     x1.zero();
                     t.zero();
                     if (k_ok) {
-                        x1 = load_vec<VEC>(a.X1 + (int64_t)s_fk[f] * a.J + k);
+                        x1 = load_vec<VEC>(a.X1 + (int64_t)s_fk[f] * a.J + k_lane);
                         const uint32_t q0 = (uint32_t)(s_ep[f] - e0), q1 = (uint32_t)(s_ep[f + 1] - e0);
                         if (q0 < q1) gather_fma<VEC, 1>(t, s_A, q0, q1, x2rows);
                     }
@@ -193,13 +194,13 @@ __global__ __launch_bounds__(kBlock) void mttkrp_kernel(MttkrpArgs a, int rows_p
                     for (int i = 0; i < VEC; ++i) acc.v[i] = __builtin_fmaf(x1.v[i], t.v[i], acc.v[i]);
                 }
             } else {
-                mttkrp_slice_direct<G, LC, VEC, OFF32>(a, acc, a.fptr[row], a.fptr[row + 1], member, chunk, k, k_ok,
+                mttkrp_slice_direct<G, LC, VEC, OFF32>(a, acc, a.fptr[row], a.fptr[row + 1], member, chunk, k_lane, k_ok,
                                                        x2row);
             }
             // members without fibers contributed +0; the lanes of a slot meet here
 #pragma unroll
             for (int i = 0; i < VEC; ++i) acc.v[i] = group_tree_sum<G, LC>(acc.v[i]);
-            if (member == 0 && k_ok) store_vec_stream<VEC>(a.Y + row * a.J + k, acc);
+            if (member == 0 && k_ok) store_vec_stream<VEC>(a.Y + row * a.J + k_lane, acc);
         }
     }
 }

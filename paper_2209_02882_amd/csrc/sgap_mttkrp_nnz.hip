@@ -140,6 +140,7 @@ __global__ __launch_bounds__(kBlock) void mttkrp_nnz_kernel(MttkrpArgs a, int gr
             for (int64_t k0 = 0; k0 < a.J; k0 += (int64_t)LC * VEC) {
                 const int64_t k = k0 + (int64_t)chunk * VEC;
                 const bool k_ok = k < a.J;
+                const int64_t k_lane = k_ok ? lane_first_col<VEC>(k, a.J) : 0;  // the VEC columns this lane holds
                 for (int step = 0; step < STEPS; ++step) {
                     const int q = (step * kWavesPerBlock + wave) * ENTRIES_PER_WAVE + entry_lane;
                     if ((step * kWavesPerBlock + wave) * ENTRIES_PER_WAVE >= cnt) break;  // the whole wavefront
@@ -149,7 +150,7 @@ __global__ __launch_bounds__(kBlock) void mttkrp_nnz_kernel(MttkrpArgs a, int gr
                     Vec<VEC> x;
                     x.zero();
                     if (valid && k_ok) {
-                        x = load_vec<VEC>(a.X2 + (int64_t)r.l * a.J + k);
+                        x = load_vec<VEC>(a.X2 + (int64_t)r.l * a.J + k_lane);
 #pragma unroll
                         for (int v = 0; v < VEC; ++v) x.v[v] *= r.val;
                     }
@@ -164,7 +165,7 @@ __global__ __launch_bounds__(kBlock) void mttkrp_nnz_kernel(MttkrpArgs a, int gr
                     Vec<VEC> y;
                     y.zero();
                     if (valid && start_f && k_ok) {
-                        const Vec<VEC> x1 = load_vec<VEC>(a.X1 + (int64_t)r.k * a.J + k);
+                        const Vec<VEC> x1 = load_vec<VEC>(a.X1 + (int64_t)r.k * a.J + k_lane);
 #pragma unroll
                         for (int v = 0; v < VEC; ++v) y.v[v] = x1.v[v] * x.v[v];
                     }
@@ -180,9 +181,11 @@ __global__ __launch_bounds__(kBlock) void mttkrp_nnz_kernel(MttkrpArgs a, int gr
                         if (valid && start_s && k_ok) {
                             if (inside)
                                 write_out<LC, VEC>(out, r.i, k, true, y);
-                            else
+                            else {
+                                from_last_columns<VEC>(y, (int)(k - k_lane));
                                 merge_add<VEC, false>(mb, s_slot[q], chunk * VEC, y,
                                                       chunk == 0 && ((fl & kMtFirstSlice) || q == 0), r.i, true);
+                            }
                         }
                     } else {
                         if (valid && start_s && k_ok) write_out<LC, VEC>(out, r.i, k, false, y);
@@ -202,6 +205,7 @@ __global__ __launch_bounds__(kBlock) void mttkrp_nnz_kernel(MttkrpArgs a, int gr
             for (int64_t k0 = 0; k0 < a.J; k0 += (int64_t)LC * VEC) {
                 const int64_t k = k0 + (int64_t)chunk * VEC;
                 const bool k_ok = k < a.J;
+                const int64_t k_lane = k_ok ? lane_first_col<VEC>(k, a.J) : 0;  // the VEC columns this lane holds
                 for (int blk = entry_lane * group; k_ok && blk < cnt; blk += ENTRY_LANES * group) {
                     const int end = blk + group < cnt ? blk + group : cnt;
                     Vec<VEC> fiber_sum, slice_sum;
@@ -223,8 +227,8 @@ __global__ __launch_bounds__(kBlock) void mttkrp_nnz_kernel(MttkrpArgs a, int gr
                         for (int u = 0; u < D; ++u) {
                             x2[u].zero();
                             x1[u].zero();
-                            if (q0 + u < end) x2[u] = load_vec<VEC>(a.X2 + (int64_t)r[u].l * a.J + k);
-                            if (close[u] & kMtFirstFiber) x1[u] = load_vec<VEC>(a.X1 + (int64_t)r[u].k * a.J + k);
+                            if (q0 + u < end) x2[u] = load_vec<VEC>(a.X2 + (int64_t)r[u].l * a.J + k_lane);
+                            if (close[u] & kMtFirstFiber) x1[u] = load_vec<VEC>(a.X1 + (int64_t)r[u].k * a.J + k_lane);
                         }
 #pragma unroll
                         for (int u = 0; u < D; ++u) {
@@ -241,9 +245,11 @@ __global__ __launch_bounds__(kBlock) void mttkrp_nnz_kernel(MttkrpArgs a, int gr
                                 const bool from_start = (s_flag[run_begin] & kMtFirstSlice) != 0;
                                 if (from_start && q0 + u + 1 < end)
                                     write_out<LC, VEC>(out, r[u].i, k, true, slice_sum);
-                                else
+                                else {
+                                    from_last_columns<VEC>(slice_sum, (int)(k - k_lane));
                                     merge_add<VEC, (LC >= 8)>(mb, s_slot[q0 + u], chunk * VEC, slice_sum,
                                                               chunk == 0 && (from_start || run_begin == 0), r[u].i, true);
+                                }
                             } else {
                                 write_out<LC, VEC>(out, r[u].i, k, false, slice_sum);  // the entry's LC chunk lanes together
                             }

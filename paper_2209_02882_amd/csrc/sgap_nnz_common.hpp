@@ -243,13 +243,13 @@ __device__ __forceinline__ void find_tile_rows(const SpmmArgs& a, const TileDeal
 // one over consecutive words, so where the pass is complete (all LC lanes are
 // here) the sums change hands first: in round q lane c adds column q*LC + c,
 // which chunk lane (q*LC + c) / VEC holds.
-template <int LC, int VEC>
-__device__ __forceinline__ void write_out(const SpmmArgs& a, int32_t row, int64_t k, bool plain,
-                                          const Vec<VEC>& x)
+// k = the chunk's first column, x = the sums of the VEC columns from lane_first_col(k, N) on.
+template <int LC, int VEC, bool RAGGED = true>
+__device__ __forceinline__ void write_out(const SpmmArgs& a, int32_t row, int64_t k, bool plain, Vec<VEC> x)
 {
-    float* __restrict__ dst = a.C + (int64_t)row * a.N + k;
+    const int64_t k_lane = lane_first_col<VEC, RAGGED>(k, a.N);
     if (plain) {
-        store_vec<VEC>(dst, x);
+        store_vec<VEC>(a.C + (int64_t)row * a.N + k_lane, x);
         return;
     }
     if constexpr (LC >= VEC && VEC > 1) {
@@ -270,7 +270,10 @@ __device__ __forceinline__ void write_out(const SpmmArgs& a, int32_t row, int64_
             return;
         }
     }
-    atomic_add_vec<VEC>(dst, x);
+    from_last_columns<VEC, RAGGED>(x, (int)(k - k_lane));
+#pragma unroll
+    for (int i = 0; i < VEC; ++i)
+        if (!RAGGED || k + i < a.N) unsafeAtomicAdd(a.C + (int64_t)row * a.N + k + i, x.v[i]);
 }
 
 // LDS accumulators of tile mode.  Slot s < nslots-1 belongs to the row whose
@@ -337,7 +340,7 @@ __device__ __forceinline__ void merge_add(const MergeBuf& mb, int32_t slot, int 
 // thread = slot_lane*LC + chunk, the same column mapping as the compute phase.
 // The LC lanes of a slot sit in one wavefront, so the owner lane's reset of
 // slot_row cannot overtake the other lanes' reads.
-template <int LC, int VEC>
+template <int LC, int VEC, bool RAGGED = true>
 __device__ __forceinline__ void merge_write_out(const SpmmArgs& a, const MergeBuf& mb, int64_t k, bool k_ok)
 {
     constexpr int SLOT_LANES = kBlock / LC;
@@ -365,7 +368,15 @@ __device__ __forceinline__ void merge_write_out(const SpmmArgs& a, const MergeBu
                 x.v[i] = src[i];
                 src[i] = 0.0f;
             }
-            if (k_ok) store_vec_stream<VEC>(a.C + (int64_t)row * a.N + k, x);
+            if (k_ok) {
+                if (!RAGGED || k + VEC <= a.N) {
+                    store_vec_stream<VEC>(a.C + (int64_t)row * a.N + k, x);
+                } else {
+#pragma unroll
+                    for (int i = 0; i < VEC; ++i)
+                        if (k + i < a.N) a.C[(int64_t)row * a.N + k + i] = x.v[i];
+                }
+            }
         }
         if (chunk == 0) mb.slot_row[s] = -1;
     }

@@ -25,7 +25,8 @@ __global__ __launch_bounds__(kBlock) void zero_rows_kernel(SpmmArgs a, int lcz, 
     Vec<VEC> z;
     z.zero();
     float* __restrict__ dst = a.C + row * a.N;
-    for (int64_t k = (int64_t)chunk * VEC; k < a.N; k += (int64_t)lcz * VEC) store_vec<VEC>(dst + k, z);
+    for (int64_t k = (int64_t)chunk * VEC; k < a.N; k += (int64_t)lcz * VEC)
+        store_vec<VEC>(dst + lane_first_col<VEC>(k, a.N), z);
 }
 
 NnzPlan plan_nnz_parallel(int group, int lc, int vec)

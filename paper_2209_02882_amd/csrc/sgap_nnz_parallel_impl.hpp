@@ -91,7 +91,7 @@ __device__ __forceinline__ void build_records(const int32_t (&col)[kParEpt], con
 // entry by its column chunk; the G members of a group then run a segmented
 // sum keyed by row and the first lane of every run writes.  Lanes outside the
 // chunk contribute +0.  Ends with a barrier.
-template <int G, int LC, int VEC, bool OFF32, bool MERGE>
+template <int G, int LC, int VEC, bool OFF32, bool MERGE, bool RAGGED>
 __device__ __forceinline__ void parallel_chunk(const SpmmArgs& a, const MergeBuf& mb,
                                                const TileEntry* __restrict__ s_tile)
 {
@@ -107,9 +107,10 @@ __device__ __forceinline__ void parallel_chunk(const SpmmArgs& a, const MergeBuf
     const int64_t N = a.N;
 
     for (int64_t k0 = 0; k0 < N; k0 += (int64_t)LC * VEC) {
-        const int64_t k = k0 + (int64_t)chunk * VEC;
-        const bool k_ok = k < N;
-        const BRow<OFF32> Brow(a.B, N, k);
+        const uint32_t k = (uint32_t)k0 + chunk * VEC;  // N < 2^31
+        const bool k_ok = k < (uint32_t)N;
+        const uint32_t k_lane = k_ok ? lane_first_col<VEC, RAGGED>(k, (uint32_t)N) : 0;  // the VEC columns this lane holds
+        const BRow<OFF32> Brow(a.B, N, k_lane);
         for (int step = 0; step < STEPS; step += kParDepth) {
             TileEntry e[kParDepth];
             Vec<VEC> x[kParDepth];
@@ -135,20 +136,21 @@ __device__ __forceinline__ void parallel_chunk(const SpmmArgs& a, const MergeBuf
                     if constexpr (MERGE) {
                         if ((meta & kMetaRowStart) && left <= G - 1 - member) {
                             // the run is the whole row
-                            store_vec_stream<VEC>(a.C + (int64_t)e[u].row * N + k, x[u]);
+                            store_vec_stream<VEC>(a.C + (int64_t)e[u].row * N + k_lane, x[u]);
                         } else {
+                            from_last_columns<VEC, RAGGED>(x[u], (int)((uint32_t)k0 + chunk * VEC - k_lane));
                             merge_add<VEC, kParMergeCas>(mb, meta >> kMetaSlotShift, chunk * VEC, x[u],
                                            chunk == 0 && (meta & kMetaOwner), e[u].row, (meta & kMetaOutside) != 0);
                         }
                     } else {
-                        write_out<LC, VEC>(a, e[u].row, k, (meta & kMetaPlain) != 0, x[u]);
+                        write_out<LC, VEC, RAGGED>(a, e[u].row, k, (meta & kMetaPlain) != 0, x[u]);
                     }
                 }
             }
         }
         if constexpr (MERGE) {
             __syncthreads();  // all partial sums of this pass are in LDS
-            merge_write_out<LC, VEC>(a, mb, k, k_ok);
+            merge_write_out<LC, VEC, RAGGED>(a, mb, k, k_ok);
         }
         __syncthreads();  // slots clear / records fully consumed
     }
@@ -160,7 +162,7 @@ __device__ __forceinline__ void parallel_chunk(const SpmmArgs& a, const MergeBuf
 // Tiles are handed out by TileDeal; the loads that bring in the next tile (entries
 // and rowptr window) are issued before the current tile is multiplied out.
 // MERGE selects tile mode of the merge rule.
-template <int G, int LC, int VEC, bool OFF32, bool MERGE>
+template <int G, int LC, int VEC, bool OFF32, bool MERGE, bool RAGGED>
 __global__ __launch_bounds__(kBlock) void nnz_parallel_kernel(SpmmArgs a)
 {
     extern __shared__ __align__(16) unsigned char s_raw[];
@@ -241,7 +243,7 @@ __global__ __launch_bounds__(kBlock) void nnz_parallel_kernel(SpmmArgs a)
                 __syncthreads();
                 // start bringing in the next tile of this batch
                 if (j + 1 < j1) fetch_tile(deal.tile(j + 1), s_tile_row[j + 1 - j0]);
-                parallel_chunk<G, LC, VEC, OFF32, MERGE>(a, mb, s_tile);
+                parallel_chunk<G, LC, VEC, OFF32, MERGE, RAGGED>(a, mb, s_tile);
             } else {
                 // long runs of rows without entries: a window of the rows with entries only, so that the tile
                 // still goes in one piece (sgap_nnz_common.hpp).  The rows are staged in the record area, which is
@@ -256,7 +258,7 @@ __global__ __launch_bounds__(kBlock) void nnz_parallel_kernel(SpmmArgs a)
                               s_tile, s_row);
                 __syncthreads();
                 if (j + 1 < j1) fetch_tile(deal.tile(j + 1), s_tile_row[j + 1 - j0]);
-                parallel_chunk<G, LC, VEC, OFF32, MERGE>(a, mb, s_tile);
+                parallel_chunk<G, LC, VEC, OFF32, MERGE, RAGGED>(a, mb, s_tile);
             }
         }
     }
@@ -273,24 +275,31 @@ struct Launch {
     hipStream_t s;
 
     template <int G, int LC, int VEC, bool OFF32, bool MERGE>
+    void pick_columns() const
+    {
+        if (VEC > 1 && a.N % VEC != 0) go<G, LC, VEC, OFF32, MERGE, (VEC > 1)>();
+        else go<G, LC, VEC, OFF32, MERGE, false>();
+    }
+
+    template <int G, int LC, int VEC, bool OFF32, bool MERGE, bool RAGGED>
     void go() const
     {
         constexpr int nslots = kParTile / G + 1;
         constexpr int smem = kParTile * (int)sizeof(TileEntry) + (MERGE ? nslots * (LC * VEC * 4 + 8) : 0);
         static int asked = 0;
-        ensure_dynamic_lds(nnz_parallel_kernel<G, LC, VEC, OFF32, MERGE>, smem, asked);
-        static const int per_cu = resident_per_cu(nnz_parallel_kernel<G, LC, VEC, OFF32, MERGE>, smem);
+        ensure_dynamic_lds(nnz_parallel_kernel<G, LC, VEC, OFF32, MERGE, RAGGED>, smem, asked);
+        static const int per_cu = resident_per_cu(nnz_parallel_kernel<G, LC, VEC, OFF32, MERGE, RAGGED>, smem);
         const int grid = persistent_grid(per_cu, compute_units, nnz_hint, kParTile);
-        hipLaunchKernelGGL((nnz_parallel_kernel<G, LC, VEC, OFF32, MERGE>), dim3(grid), dim3(kBlock), smem, s, a);
+        hipLaunchKernelGGL((nnz_parallel_kernel<G, LC, VEC, OFF32, MERGE, RAGGED>), dim3(grid), dim3(kBlock), smem, s, a);
     }
 
     template <int G, int LC, int VEC>
     void operator()() const
     {
         if (off32) {
-            if (merge) go<G, LC, VEC, true, true>(); else go<G, LC, VEC, true, false>();
+            if (merge) pick_columns<G, LC, VEC, true, true>(); else pick_columns<G, LC, VEC, true, false>();
         } else {
-            if (merge) go<G, LC, VEC, false, true>(); else go<G, LC, VEC, false, false>();
+            if (merge) pick_columns<G, LC, VEC, false, true>(); else pick_columns<G, LC, VEC, false, false>();
         }
     }
 };

@@ -27,7 +27,7 @@ namespace sgap {
 // relative to row_lb: window index wi stands for row row_lb + wi, or, when
 // s_row is given (a window of the rows WITH entries only), for row s_row[wi].
 // MERGE selects tile mode of the merge rule; in that mode the function ends with a barrier.
-template <int LC, int VEC, bool OFF32, bool MERGE>
+template <int LC, int VEC, bool OFF32, bool MERGE, bool RAGGED>
 __device__ __forceinline__ void serial_chunk(const SpmmArgs& a, const MergeBuf& mb, const StagedEntry* __restrict__ s_A,
                                              const int32_t* __restrict__ s_win, const RowWindow& w, int32_t row_lb,
                                              int32_t tile_start, int32_t base, int32_t end,
@@ -49,9 +49,10 @@ __device__ __forceinline__ void serial_chunk(const SpmmArgs& a, const MergeBuf& 
     const int per_step = ENTRY_LANES * G;  // positions the workgroup covers per step
 
     for (int64_t k0 = 0; k0 < N; k0 += (int64_t)LC * VEC) {
-        const int64_t k = k0 + (int64_t)chunk * VEC;
-        const bool k_ok = k < N;
-        const BRow<OFF32> Brow(a.B, N, k);
+        const uint32_t k = (uint32_t)k0 + chunk * VEC;  // N < 2^31
+        const bool k_ok = k < (uint32_t)N;
+        const uint32_t k_lane = k_ok ? lane_first_col<VEC, RAGGED>(k, (uint32_t)N) : 0;  // the VEC columns this lane holds
+        const BRow<OFF32> Brow(a.B, N, k_lane);
         for (int32_t blk = tile_start + entry_lane * G; k_ok && blk < end; blk += per_step) {
             // this lane's aligned block of G positions, clipped to the chunk
             const int32_t blk_begin = blk > base ? blk : base;
@@ -102,18 +103,19 @@ __device__ __forceinline__ void serial_chunk(const SpmmArgs& a, const MergeBuf& 
                     if constexpr (MERGE) {
                         if (run_begin == row_begin && p + 1 == row_end) {
                             // the run is the whole row
-                            store_vec_stream<VEC>(a.C + (int64_t)row * N + k, acc);
+                            store_vec_stream<VEC>(a.C + (int64_t)row * N + k_lane, acc);
                         } else {
                             const int32_t first_in_chunk = row_begin > base ? row_begin : base;
                             const int32_t slot =
                                 row_begin < base ? mb.nslots - 1 : (row_begin - tile_start) >> a.log2_group;
+                            from_last_columns<VEC, RAGGED>(acc, (int)((uint32_t)k0 + chunk * VEC - k_lane));
                             merge_add<VEC, kCasMerge>(mb, slot, chunk * VEC, acc, chunk == 0 && run_begin == first_in_chunk, row,
                                            row_begin < base || row_end > end);
                         }
                     } else {
                         // the whole row lies inside this aligned block: nobody else adds to it
                         const bool plain = row_begin >= blk && row_end <= blk + G;
-                        write_out<LC, VEC>(a, row, k, plain, acc);
+                        write_out<LC, VEC, RAGGED>(a, row, k, plain, acc);
                     }
                     acc.zero();
                     if (p + 1 < blk_end) {
@@ -134,15 +136,15 @@ __device__ __forceinline__ void serial_chunk(const SpmmArgs& a, const MergeBuf& 
         }
         if constexpr (MERGE) {
             __syncthreads();  // all partial sums of this pass are in LDS
-            merge_write_out<LC, VEC>(a, mb, k, k_ok);
+            merge_write_out<LC, VEC, RAGGED>(a, mb, k, k_ok);
             __syncthreads();  // slots are clear again
         }
     }
 }
 
 // EPT = tile / kBlock stored entries per thread held in registers between tiles.
-template <int LC, int VEC, bool OFF32, bool MERGE, int EPT>
-__global__ __launch_bounds__(kBlock) void nnz_serial_kernel(SpmmArgs a)
+template <int LC, int VEC, bool OFF32, bool MERGE, int EPT, bool RAGGED>
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) void nnz_serial_kernel(SpmmArgs a)
 {
     constexpr int TILE = EPT * kBlock;
     constexpr int WPT = kWindowCap / kBlock + 1;  // rowptr window entries per thread (last one: thread 0 only)
@@ -239,7 +241,7 @@ __global__ __launch_bounds__(kBlock) void nnz_serial_kernel(SpmmArgs a)
                 __syncthreads();  // everyone has read the plain window
                 w.n_last = load_compact_window(a, row_lb, tile_end, s_win, s_row, s_scan) - 1;
             }
-            serial_chunk<LC, VEC, OFF32, MERGE>(a, mb, s_A, s_win, w, 0, tile_start, tile_start, tile_end, s_row);
+            serial_chunk<LC, VEC, OFF32, MERGE, RAGGED>(a, mb, s_A, s_win, w, 0, tile_start, tile_start, tile_end, s_row);
             // tile and window fully consumed before they are overwritten (tile mode ends with a barrier of its own)
             if constexpr (!MERGE) __syncthreads();
         }
@@ -258,6 +260,13 @@ struct Launch {
     hipStream_t s;
 
     template <int LC, int VEC, bool OFF32, bool MERGE, int EPT>
+    void pick_columns() const
+    {
+        if (VEC > 1 && a.N % VEC != 0) go<LC, VEC, OFF32, MERGE, EPT, (VEC > 1)>();
+        else go<LC, VEC, OFF32, MERGE, EPT, false>();
+    }
+
+    template <int LC, int VEC, bool OFF32, bool MERGE, int EPT, bool RAGGED>
     void go() const
     {
         const int nslots = tile / a.group + 1;
@@ -265,10 +274,10 @@ struct Launch {
         static int cached[7];  // [log2 group] resident workgroups per CU of this instance, 0 = not asked yet
         int& per_cu = cached[a.log2_group];
         static int asked = 0;  // most dynamic LDS this instance has been allowed so far
-        ensure_dynamic_lds(nnz_serial_kernel<LC, VEC, OFF32, MERGE, EPT>, smem, asked);
-        if (per_cu == 0) per_cu = resident_per_cu(nnz_serial_kernel<LC, VEC, OFF32, MERGE, EPT>, smem);
+        ensure_dynamic_lds(nnz_serial_kernel<LC, VEC, OFF32, MERGE, EPT, RAGGED>, smem, asked);
+        if (per_cu == 0) per_cu = resident_per_cu(nnz_serial_kernel<LC, VEC, OFF32, MERGE, EPT, RAGGED>, smem);
         const int grid = persistent_grid(per_cu, compute_units, nnz_hint, tile);
-        hipLaunchKernelGGL((nnz_serial_kernel<LC, VEC, OFF32, MERGE, EPT>), dim3(grid), dim3(kBlock), smem, s, a);
+        hipLaunchKernelGGL((nnz_serial_kernel<LC, VEC, OFF32, MERGE, EPT, RAGGED>), dim3(grid), dim3(kBlock), smem, s, a);
     }
 
     template <int LC, int VEC, bool OFF32, bool MERGE>
@@ -276,11 +285,11 @@ struct Launch {
     {
         // the small tiles exist for 16-byte lanes only (plan_nnz_serial)
         if constexpr (VEC == 4) {
-            if (tile == 256) return go<LC, VEC, OFF32, MERGE, 1>();
-            if (tile == 512) return go<LC, VEC, OFF32, MERGE, 2>();
+            if (tile == 256) return pick_columns<LC, VEC, OFF32, MERGE, 1>();
+            if (tile == 512) return pick_columns<LC, VEC, OFF32, MERGE, 2>();
         }
-        if (tile == 1024) go<LC, VEC, OFF32, MERGE, 4>();
-        else go<LC, VEC, OFF32, MERGE, 8>();
+        if (tile == 1024) pick_columns<LC, VEC, OFF32, MERGE, 4>();
+        else pick_columns<LC, VEC, OFF32, MERGE, 8>();
     }
 
     template <int LC, int VEC>
@@ -297,12 +306,11 @@ struct Launch {
     template <int LC>
     hipError_t run(int vec) const
     {
-        switch (vec) {
-            case 4: pick_mode<LC, 4>(); break;
-            case 2: pick_mode<LC, 2>(); break;
-            case 1: pick_mode<LC, 1>(); break;
-            default: return hipErrorInvalidValue;
-        }
+        // the narrow vectors are for rows of one to three columns (lane_columns)
+        if (vec == 4) pick_mode<LC, 4>();
+        else if (LC <= 2 && vec == 2) pick_mode<LC <= 2 ? LC : 1, 2>();
+        else if (LC == 1 && vec == 1) pick_mode<1, 1>();
+        else return hipErrorInvalidValue;
         return hipGetLastError();
     }
 };

@@ -10,20 +10,96 @@ namespace sgap {
 
 constexpr int kStageCap = 2048;  // (column, value) pairs per LDS chunk: 16 KB
 constexpr int kRowCap = 1024;    // rowptr entries kept in LDS per row block (+1)
+constexpr int kShareMin = 256;   // the shortest row that a whole workgroup takes together
 constexpr int kRowSplitMaxBlock = 512;  // threads per workgroup: 128, 256 or 512, chosen at launch
+
+// One row by the whole workgroup: lc chunk lanes (the power of two that covers the columns, at most a wavefront) and
+// block / lc members, each of which takes every (block / lc)-th stored entry with kGatherDepth rows of B in flight; members
+// of a wavefront are summed with shuffles, the wavefronts' sums through LDS in a fixed order, and the row has one
+// plain store as ever.  For the rows whose length would keep the one group that owns them busy long after the rest of
+// the chip is done (see share_rows_from).  s_A and s_part may be the same memory.  Block-uniform; barriers inside.
+template <int VEC, bool OFF32>
+__device__ __forceinline__ void shared_row(const SpmmArgs& a, int64_t row, uint32_t p_begin, uint32_t p_end,
+                                           int64_t k_begin, int64_t k_end, StagedEntry* __restrict__ s_A, int block)
+{
+    constexpr int D = kGatherDepth;
+    const int64_t N = a.N;
+    int lc = 1;
+    while (lc < kWave && (int64_t)lc * VEC < k_end - k_begin) lc *= 2;
+    const uint32_t members = (uint32_t)(block / lc);
+    const uint32_t member = (uint32_t)threadIdx.x / lc;
+    const int chunk = threadIdx.x % lc;
+    const int lane = threadIdx.x % kWave;
+    const int wave = threadIdx.x / kWave;
+    float* s_part = reinterpret_cast<float*>(s_A);  // block/64 wavefronts x lc*VEC columns
+    for (int64_t k0 = k_begin; k0 < k_end; k0 += (int64_t)lc * VEC) {
+        const int64_t k = k0 + (int64_t)chunk * VEC;
+        const bool k_ok = k < k_end;
+        const int64_t first = k_ok ? lane_first_col<VEC>(k, N) : 0;
+        const GlobalRows<VEC, OFF32> B(a.B, N, first);
+        Vec<VEC> acc;
+        acc.zero();
+        for (uint32_t base = p_begin; base < p_end; base += kStageCap) {
+            const uint32_t cnt = p_end - base < (uint32_t)kStageCap ? p_end - base : (uint32_t)kStageCap;
+            __syncthreads();
+            stage_entries(a, base, cnt, s_A, block);
+            __syncthreads();
+            for (uint32_t q = member; k_ok && q < cnt; q += D * members) {
+                StagedEntry e[D];
+                Vec<VEC> b[D];
+#pragma unroll
+                for (int u = 0; u < D; ++u) {
+                    e[u].col = 0;
+                    e[u].val = 0.0f;
+                    if (q + u * members < cnt) e[u] = s_A[q + u * members];
+                }
+#pragma unroll
+                for (int u = 0; u < D; ++u) {
+                    b[u].zero();
+                    if (q + u * members < cnt) b[u] = B.load(e[u].col);
+                }
+#pragma unroll
+                for (int u = 0; u < D; ++u) acc.fma(e[u].val, b[u]);
+            }
+        }
+        for (int d = kWave / 2; d >= lc; d /= 2) {
+#pragma unroll
+            for (int i = 0; i < VEC; ++i) acc.v[i] += __shfl_down(acc.v[i], d, kWave);
+        }
+        __syncthreads();  // the last entries are consumed
+        if (lane < lc) {
+#pragma unroll
+            for (int i = 0; i < VEC; ++i) s_part[(wave * lc + lane) * VEC + i] = acc.v[i];
+        }
+        __syncthreads();
+        if (wave == 0 && lane < lc && k_ok) {
+            for (int w = 1; w < block / kWave; ++w) {
+#pragma unroll
+                for (int i = 0; i < VEC; ++i) acc.v[i] += s_part[(w * lc + lane) * VEC + i];
+            }
+            store_vec_stream<VEC>(a.C + row * N + first, acc);
+        }
+    }
+}
 
 // PARTIAL: the G members of a row reduce in sub-groups of `reduce_members`
 // (a power of two below G) and the first member of every sub-group adds its
 // sum to C with atomics; C must hold zeros before the launch.
 // SKIP: leave the rows described by `skip` alone.
+// share_from (G > 1, whole-group reductions): rows of at least that many stored entries are left out of the walk and
+// produced by the whole workgroup afterwards (shared_row).
 // The workgroup size (the paper's blockSz, Section 7.2) is the launch's: SLOTS = blockDim.x / (G*LC)
 // groups work side by side on the rows of a row block.
 template <int G, int LC, int VEC, bool OFF32, bool PARTIAL, bool SKIP = false>
 __global__ __launch_bounds__(kRowSplitMaxBlock) void row_split_kernel(SpmmArgs a, TileSched ts, int rows_per_slot,
-                                                                      int interleave, int reduce_members, RowSkip skip)
+                                                                      int interleave, int reduce_members,
+                                                                      int32_t share_from, RowSkip skip)
 {
     __shared__ StagedEntry s_A[kStageCap];
     __shared__ int32_t s_rp[kRowCap + 1];
+    constexpr bool SHARE = G > 1 && !PARTIAL;
+    __shared__ uint16_t s_shared[SHARE ? kRowCap : 1];  // this block's shared rows
+    __shared__ int32_t s_shared_n;
     constexpr int SPAN = G * LC;
     const int block = blockDim.x;
     const int SLOTS = block / SPAN;
@@ -59,13 +135,34 @@ __global__ __launch_bounds__(kRowSplitMaxBlock) void row_split_kernel(SpmmArgs a
         if (my_last > block_rows) my_last = block_rows;
 
         __syncthreads();  // everyone is done with the previous item's LDS contents
+        uint32_t nz_first, nz_last;
         if (rp_in_lds) {
             for (int i = threadIdx.x; i <= block_rows; i += block)
                 s_rp[i] = a.rowptr[row_first + i];
+            if constexpr (SHARE) {
+                if (threadIdx.x == 0) s_shared_n = 0;
+            }
             __syncthreads();
+            nz_first = (uint32_t)__builtin_amdgcn_readfirstlane(s_rp[0]);  // the same in all lanes: scalar registers
+            nz_last = (uint32_t)__builtin_amdgcn_readfirstlane(s_rp[block_rows]);
+        } else {
+            nz_first = (uint32_t)a.rowptr[row_first];
+            nz_last = (uint32_t)a.rowptr[row_last];
         }
-        const uint32_t nz_first = (uint32_t)a.rowptr[row_first];
-        const uint32_t nz_last = (uint32_t)a.rowptr[row_last];
+        // (block-uniform; the entries of a shared row are not walked here, so a block that holds nothing else
+        // passes over them without looking)
+        const bool share_on = SHARE && rp_in_lds && nz_last - nz_first >= (uint32_t)share_from;
+        if constexpr (SHARE) {
+            if (share_on) {
+                for (int i = threadIdx.x; i < block_rows; i += block) {
+                    const int32_t len = s_rp[i + 1] - s_rp[i];
+                    bool shared = len >= share_from;
+                    if constexpr (SKIP) shared = shared && !(skip_on && len >= skip.min_len);
+                    if (shared) s_shared[atomicAdd(&s_shared_n, 1)] = (uint16_t)i;
+                }
+            }
+        }
+        const bool one_chunk = nz_last - nz_first <= (uint32_t)kStageCap;
 
         const int64_t k_tile_end =
             (int64_t)(col_tile + 1) * ts.tile_cols < N ? (int64_t)(col_tile + 1) * ts.tile_cols : N;
@@ -73,16 +170,20 @@ __global__ __launch_bounds__(kRowSplitMaxBlock) void row_split_kernel(SpmmArgs a
         for (int64_t k0 = (int64_t)col_tile * ts.tile_cols; k0 < k_tile_end; k0 += (int64_t)LC * VEC) {
             const int32_t k = (int32_t)k0 + chunk * VEC;  // N < 2^31
             const bool k_ok = k < k_tile_end;
-            const GlobalRows<VEC, OFF32> Brow(a.B, N, k);
+            const int32_t k_lane = k_ok ? (int32_t)lane_first_col<VEC>((uint32_t)k, (uint32_t)N) : 0;  // the VEC columns this lane holds
+            const GlobalRows<VEC, OFF32> Brow(a.B, N, k_lane);
 
             int32_t row = my_first;
             Vec<VEC> acc;
             acc.zero();
             for (uint32_t base = nz_first;; base += kStageCap) {  // runs at least once: empty rows get stored
                 const uint32_t cnt = nz_last - base < (uint32_t)kStageCap ? nz_last - base : (uint32_t)kStageCap;
-                if (base != nz_first || k0 != (int64_t)col_tile * ts.tile_cols) __syncthreads();
-                stage_entries(a, base, cnt, s_A, block);
-                __syncthreads();
+                const bool staged = one_chunk && k0 != (int64_t)col_tile * ts.tile_cols;  // by the pass before
+                if (!staged) {
+                    if (base != nz_first || k0 != (int64_t)col_tile * ts.tile_cols) __syncthreads();
+                    stage_entries(a, base, cnt, s_A, block);
+                    __syncthreads();
+                }
                 // rows of this slot that have entries in the chunk (or are empty)
                 while (row < my_last) {
                     uint32_t p_begin, p_end;
@@ -97,6 +198,7 @@ __global__ __launch_bounds__(kRowSplitMaxBlock) void row_split_kernel(SpmmArgs a
                     const uint32_t hi = p_end < base + cnt ? p_end : base + cnt;
                     bool skipped = false;
                     if constexpr (SKIP) skipped = skip_on && p_end - p_begin >= (uint32_t)skip.min_len;
+                    if constexpr (SHARE) skipped = skipped || (share_on && p_end - p_begin >= (uint32_t)share_from);
                     if (!skipped && k_ok && lo < hi) {
                         // first position >= lo that belongs to this member
                         const uint32_t first = lo + ((member - (lo - p_begin)) & (G - 1));
@@ -109,6 +211,7 @@ __global__ __launch_bounds__(kRowSplitMaxBlock) void row_split_kernel(SpmmArgs a
 #pragma unroll
                         for (int i = 0; i < VEC; ++i)
                             acc.v[i] = group_partial_sum<G, LC>(acc.v[i], reduce_members * LC);
+                        from_last_columns<VEC>(acc, k - k_lane);
                         // a sub-group whose first member has no entry of the row holds +0
                         const bool adds = (member & (reduce_members - 1)) == 0 && (uint32_t)member < p_end - p_begin;
                         if constexpr (LC >= VEC) {
@@ -130,17 +233,32 @@ __global__ __launch_bounds__(kRowSplitMaxBlock) void row_split_kernel(SpmmArgs a
                                     unsafeAtomicAdd(a.C + (row_first + row) * N + k0 + col, mine);
                             }
                         } else {
-                            if (adds && k_ok) atomic_add_vec<VEC>(a.C + (row_first + row) * N + k, acc);
+                            if (adds && k_ok) {
+#pragma unroll
+                                for (int i = 0; i < VEC; ++i)
+                                    if (k + i < k_tile_end) unsafeAtomicAdd(a.C + (row_first + row) * N + k + i, acc.v[i]);
+                            }
                         }
                     } else {
 #pragma unroll
                         for (int i = 0; i < VEC; ++i) acc.v[i] = group_tree_sum<G, LC>(acc.v[i]);
-                        if (member == 0 && k_ok && !skipped) store_vec_stream<VEC>(a.C + (row_first + row) * N + k, acc);
+                        if (member == 0 && k_ok && !skipped) store_vec_stream<VEC>(a.C + (row_first + row) * N + k_lane, acc);
                     }
                     acc.zero();
                     row += row_step;
                 }
                 if (base + cnt >= nz_last) break;
+            }
+        }
+        if constexpr (SHARE) {
+            if (share_on) {
+                const int n = s_shared_n;  // written before the barriers of the walk
+                for (int i = 0; i < n; ++i) {
+                    const int row = __builtin_amdgcn_readfirstlane(s_shared[i]);
+                    shared_row<VEC, OFF32>(a, row_first + row, (uint32_t)__builtin_amdgcn_readfirstlane(s_rp[row]),
+                                           (uint32_t)__builtin_amdgcn_readfirstlane(s_rp[row + 1]),
+                                           (int64_t)col_tile * ts.tile_cols, k_tile_end, s_A, block);
+                }
             }
         }
     }
@@ -167,6 +285,15 @@ struct Launch {
         return n;
     }
 
+    // A group's rounds of loads on a row of len entries are len / (G * kGatherDepth) for each pass over the columns,
+    // each of them a round trip to memory with a handful of loads in flight.  From about sixteen rounds on, the whole
+    // workgroup takes the row instead; never a row that is only a few steps of the workgroup long.
+    static int32_t share_rows_from(int g, int passes)
+    {
+        const int len = 16 * g * kGatherDepth / passes;
+        return len < kShareMin ? kShareMin : len;
+    }
+
     template <int G, int LC, int VEC>
     void operator()() const
     {
@@ -184,16 +311,18 @@ struct Launch {
         ts.items = ts.row_blocks * ts.col_tiles;
         ts.xcds = xcds;
         ts.items_per_xcd = (ts.items + xcds - 1) / xcds;
+        const int passes = (int)(((int64_t)tile_cols + LC * VEC - 1) / (LC * VEC));
+        const int32_t share_from = share_rows_from(G, passes);
         int64_t wgs_per_xcd = max_grid / xcds > 0 ? max_grid / xcds : 1;
         if (wgs_per_xcd * xcds > 0x7ffffff0LL) wgs_per_xcd = 0x7ffffff0LL / xcds;
         if (wgs_per_xcd > ts.items_per_xcd) wgs_per_xcd = ts.items_per_xcd;
         const unsigned grid = (unsigned)(wgs_per_xcd * xcds);
         if (off32)
             hipLaunchKernelGGL((row_split_kernel<G, LC, VEC, true, PARTIAL, SKIP>), dim3(grid), dim3(block), 0, s, a,
-                               ts, rows_per_slot, interleave, reduce_members, skip);
+                               ts, rows_per_slot, interleave, reduce_members, share_from, skip);
         else
             hipLaunchKernelGGL((row_split_kernel<G, LC, VEC, false, PARTIAL, SKIP>), dim3(grid), dim3(block), 0, s, a,
-                               ts, rows_per_slot, interleave, reduce_members, skip);
+                               ts, rows_per_slot, interleave, reduce_members, share_from, skip);
     }
 };
 

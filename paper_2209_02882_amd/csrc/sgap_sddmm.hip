@@ -18,6 +18,8 @@
 // (chunks of neighbouring tiles per die, see TileDeal), the rows of a tile's entries come from a bisection of rowptr
 // for the tile's first entry and an LDS window of rowptr for the rest (the
 // same pieces as the nnz-balanced SpMM kernels).
+#include <type_traits>
+
 #include "sgap_common.hpp"
 #include "sgap_lane_ops.hpp"
 #include "sgap_nnz_common.hpp"
@@ -40,6 +42,20 @@ __device__ __forceinline__ float dot_vec(const Vec<VEC>& x, const Vec<VEC>& y, f
 #pragma unroll
     for (int i = 0; i < VEC; ++i) acc = __builtin_fmaf(x.v[i], y.v[i], acc);
     return acc;
+}
+
+// The VEC columns from lane_first_col(c, J) on with those in front of c set to zero: they are the lane's in front.
+template <int VEC, bool RAGGED>
+__device__ __forceinline__ Vec<VEC> load_own(const float* __restrict__ row, int64_t c, int64_t J)
+{
+    const int64_t first = lane_first_col<VEC, RAGGED>(c, J);
+    Vec<VEC> x = load_vec<VEC>(row + first);
+    if constexpr (VEC > 1 && RAGGED) {
+#pragma unroll
+        for (int i = 0; i < VEC - 1; ++i)
+            if (first + i < c) x.v[i] = 0.0f;
+    }
+    return x;
 }
 
 // Copy the tile's columns and values into LDS and look up the row of every
@@ -77,7 +93,7 @@ __device__ __forceinline__ void stage_tile(const SpmmArgs& a, int32_t tile_start
 // per_lane = 0: parallel strategy, G lanes per entry.  per_lane > 0 (G = 1):
 // serial strategy, per_lane consecutive entries per lane.
 // SKIP: leave the entries of the rows described by s.skip alone.
-template <int G, int VEC, bool SKIP = false>
+template <int G, int VEC, bool RAGGED, bool SKIP = false>
 __global__ __launch_bounds__(kBlock) void sddmm_kernel(SddmmArgs s, int per_lane)
 {
     __shared__ int32_t s_col[kSddmmTile];
@@ -146,8 +162,8 @@ __global__ __launch_bounds__(kBlock) void sddmm_kernel(SddmmArgs s, int per_lane
                             x1[u].zero();
                             x2[u].zero();
                             if (ok[u]) {
-                                x1[u] = load_vec<VEC>(x1p[u] + c);
-                                x2[u] = load_vec<VEC>(x2p[u] + c);
+                                x1[u] = load_own<VEC, RAGGED>(x1p[u], c, J);
+                                x2[u] = load_own<VEC, RAGGED>(x2p[u], c, J);
                             }
                         }
 #pragma unroll
@@ -183,7 +199,7 @@ __global__ __launch_bounds__(kBlock) void sddmm_kernel(SddmmArgs s, int per_lane
 #pragma unroll
                             for (int u = 0; u < U; ++u) acc = dot_vec<VEC>(x1[u], x2[u], acc);
                         }
-                        for (; c < J; c += VEC) acc = dot_vec<VEC>(load_vec<VEC>(x1p + c), load_vec<VEC>(x2p + c), acc);
+                        for (; c < J; c += VEC) acc = dot_vec<VEC>(load_own<VEC, RAGGED>(x1p, c, J), load_own<VEC, RAGGED>(x2p, c, J), acc);
                         s.out[tile_start + e] = s_val[e] * acc;
                     }
                 }
@@ -202,7 +218,7 @@ __global__ __launch_bounds__(kBlock) void sddmm_kernel(SddmmArgs s, int per_lane
 // as a whole still moves through neighbouring entries, whose rows of X2T tend
 // to be neighbours or the same (L1 hits).  The loads of a batch (rows of X2T,
 // and rows of X1 where the row changes inside the batch) are issued together.
-template <int G, int S>
+template <int G, int S, bool RAGGED>
 __global__ __launch_bounds__(kBlock) void sddmm_rowcache_kernel(SddmmArgs s)
 {
     constexpr int VEC = 4;
@@ -266,8 +282,8 @@ __global__ __launch_bounds__(kBlock) void sddmm_rowcache_kernel(SddmmArgs s)
                         const int64_t c = (int64_t)(st * G + member) * VEC;
                         x2[u][st].zero();
                         x1[u][st].zero();
-                        if (ok[u] && c_ok[st]) x2[u][st] = load_vec<VEC>(X2T + (int64_t)col[u] * J + c);
-                        if (fresh[u] && c_ok[st]) x1[u][st] = load_vec<VEC>(s.X1 + (int64_t)row[u] * J + c);
+                        if (ok[u] && c_ok[st]) x2[u][st] = load_own<VEC, RAGGED>(X2T + (int64_t)col[u] * J, c, J);
+                        if (fresh[u] && c_ok[st]) x1[u][st] = load_own<VEC, RAGGED>(s.X1 + (int64_t)row[u] * J, c, J);
                     }
                 }
                 float acc[U];
@@ -297,12 +313,12 @@ __global__ __launch_bounds__(kBlock) void sddmm_rowcache_kernel(SddmmArgs s)
 
 namespace {
 
-template <int G, int S>
+template <int G, int S, bool RAGGED>
 void launch_rowcache(const SddmmArgs& s, int compute_units, int64_t nnz_hint, hipStream_t stream)
 {
-    static const int per_cu = resident_per_cu(sddmm_rowcache_kernel<G, S>, 0);
+    static const int per_cu = resident_per_cu(sddmm_rowcache_kernel<G, S, RAGGED>, 0);
     const int grid = persistent_grid(per_cu, compute_units, nnz_hint, kSddmmTile);
-    hipLaunchKernelGGL((sddmm_rowcache_kernel<G, S>), dim3(grid), dim3(kBlock), 0, stream, s);
+    hipLaunchKernelGGL((sddmm_rowcache_kernel<G, S, RAGGED>), dim3(grid), dim3(kBlock), 0, stream, s);
 }
 
 // steps of G*4 columns that cover J: 1, 2 or 4 pick the row-cache kernel, 0 = more than 4
@@ -310,36 +326,45 @@ template <int G>
 bool try_rowcache(const SddmmArgs& s, int64_t J, int compute_units, int64_t nnz_hint, hipStream_t stream)
 {
     const int64_t steps = (J + G * 4 - 1) / (G * 4);
-    if (steps <= 1) launch_rowcache<G, 1>(s, compute_units, nnz_hint, stream);
-    else if (steps <= 2) launch_rowcache<G, 2>(s, compute_units, nnz_hint, stream);
-    else if (steps <= 4) launch_rowcache<G, 4>(s, compute_units, nnz_hint, stream);
+    const bool ragged = J % 4 != 0;
+    auto pick = [&](auto s_const) {
+        constexpr int S = decltype(s_const)::value;
+        if (ragged) launch_rowcache<G, S, true>(s, compute_units, nnz_hint, stream);
+        else launch_rowcache<G, S, false>(s, compute_units, nnz_hint, stream);
+    };
+    if (steps <= 1) pick(std::integral_constant<int, 1>{});
+    else if (steps <= 2) pick(std::integral_constant<int, 2>{});
+    else if (steps <= 4) pick(std::integral_constant<int, 4>{});
     else return false;
     return true;
 }
 
-template <int G, int VEC>
+template <int G, int VEC, bool RAGGED>
 void launch_one(const SddmmArgs& s, int per_lane, int compute_units, int64_t nnz_hint, hipStream_t stream)
 {
-    static const int per_cu = resident_per_cu(sddmm_kernel<G, VEC>, 0);
+    static const int per_cu = resident_per_cu(sddmm_kernel<G, VEC, RAGGED>, 0);
     const int grid = persistent_grid(per_cu, compute_units, nnz_hint, kSddmmTile);
-    hipLaunchKernelGGL((sddmm_kernel<G, VEC>), dim3(grid), dim3(kBlock), 0, stream, s, per_lane);
+    hipLaunchKernelGGL((sddmm_kernel<G, VEC, RAGGED>), dim3(grid), dim3(kBlock), 0, stream, s, per_lane);
 }
 
 template <int G>
 void launch_skip(const SddmmArgs& s, int per_lane, int compute_units, int64_t nnz_hint, hipStream_t stream)
 {
-    static const int per_cu = resident_per_cu(sddmm_kernel<G, 4, true>, 0);
+    static const int per_cu = resident_per_cu(sddmm_kernel<G, 4, false, true>, 0);
     const int grid = persistent_grid(per_cu, compute_units, nnz_hint, kSddmmTile);
-    hipLaunchKernelGGL((sddmm_kernel<G, 4, true>), dim3(grid), dim3(kBlock), 0, stream, s, per_lane);
+    hipLaunchKernelGGL((sddmm_kernel<G, 4, false, true>), dim3(grid), dim3(kBlock), 0, stream, s, per_lane);
 }
 
 template <int G>
 bool launch_vec(const SddmmArgs& s, int vec, int per_lane, int compute_units, int64_t nnz_hint, hipStream_t stream)
 {
     switch (vec) {
-        case 4: launch_one<G, 4>(s, per_lane, compute_units, nnz_hint, stream); return true;
-        case 2: launch_one<G, 2>(s, per_lane, compute_units, nnz_hint, stream); return true;
-        case 1: launch_one<G, 1>(s, per_lane, compute_units, nnz_hint, stream); return true;
+        case 4:
+            if (s.a.N % 4 != 0) launch_one<G, 4, true>(s, per_lane, compute_units, nnz_hint, stream);
+            else launch_one<G, 4, false>(s, per_lane, compute_units, nnz_hint, stream);
+            return true;
+        case 2: launch_one<G, 2, true>(s, per_lane, compute_units, nnz_hint, stream); return true;
+        case 1: launch_one<G, 1, false>(s, per_lane, compute_units, nnz_hint, stream); return true;
         default: return false;
     }
 }
