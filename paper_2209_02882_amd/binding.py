@@ -1,4 +1,8 @@
-"""ctypes binding of libsgap.so: argument marshalling only.
+"""Binding of libsgap.so: argument marshalling only.
+
+The compute calls go through a small native module (csrc/sgap_python.cpp), which reads the tensors and calls the
+library in a few hundred nanoseconds; whatever it does not take (another type, a wrong length, a stream of the
+caller's) goes through ctypes and the checks below, which say what is wrong.
 
 Function names mirror the C ABI in include/sgap.h.  Tensors are torch CUDA
 tensors (used purely as device memory); every computation happens in the HIP
@@ -69,6 +73,7 @@ EXPORTS = {
 }
 
 _lib = None
+_native = None
 
 
 class SgapError(RuntimeError):
@@ -92,6 +97,21 @@ def load():
             fn.argtypes = args
         _lib = lib
     return _lib
+
+
+def _load_native():
+    """The native module (once).  Raises if it has not been built: there is no other quick way."""
+    global _native
+    if _native is None:
+        import torch  # noqa: F401  (its libraries have to be there first)
+
+        load()
+        try:
+            from . import _native as module
+        except ImportError as e:
+            raise RuntimeError("the native module is missing: build it with `python -m paper_2209_02882_amd.build`") from e
+        _native = module
+    return _native
 
 
 def _check(status: int):
@@ -159,6 +179,11 @@ def sgap_spmm_csr_ex(M, K, N, rowptr, colidx, vals, B, C, group_size, strategy, 
                      nnz_hint=None, stream=None) -> None:
     """C = A_csr * B with an explicit schedule.  nnz_hint defaults to the
     length of colidx, which the host knows without touching the device."""
+    st = (_native or _load_native()).spmm_csr_ex(M, K, N, rowptr, colidx, vals, B, C, group_size, strategy, schedule, nnz_hint, stream)
+    if st == 0:
+        return
+    if st > 0:
+        _check(st)
     ptrs = _spmm_args(M, K, N, rowptr, colidx, vals, B, C)
     if nnz_hint is None:
         nnz_hint = colidx.numel()
@@ -220,6 +245,11 @@ def sgap_spmm_csr_cfg(M, K, N, rowptr, colidx, vals, B, C, config: Config, nnz_h
                       stream=None) -> None:
     """C = A_csr * B at the point and with the tiling `config` names; `workspace` is a CUDA uint8 tensor of
     at least sgap_spmm_csr_workspace_size bytes when the configuration sets long rows apart."""
+    st = (_native or _load_native()).spmm_csr_cfg(M, K, N, rowptr, colidx, vals, B, C, config, nnz_hint, workspace, stream)
+    if st == 0:
+        return
+    if st > 0:
+        _check(st)
     ptrs = _spmm_args(M, K, N, rowptr, colidx, vals, B, C)
     if nnz_hint is None:
         nnz_hint = colidx.numel()
@@ -258,6 +288,11 @@ def sgap_spmm_csr_gr(M, K, N, rowptr, colidx, vals, B, C, group_size, reduce_siz
 def sgap_sddmm_csr(M, K, J, rowptr, colidx, vals, X1, X2T, out_vals, group_size, strategy, nnz_hint=None,
                    stream=None) -> None:
     """out_vals[p] = vals[p] * <X1[row(p), :], X2T[colidx[p], :]> (see include/sgap.h)."""
+    st = (_native or _load_native()).sddmm_csr(M, K, J, rowptr, colidx, vals, X1, X2T, out_vals, group_size, strategy, nnz_hint, stream)
+    if st == 0:
+        return
+    if st > 0:
+        _check(st)
     import torch
 
     if rowptr.numel() != M + 1:
@@ -286,6 +321,12 @@ def sgap_sddmm_csr_windows(M, K, J, rowptr, colidx, vals, X1, X2T, out_vals, gro
                            window_kb=0, max_long_rows=0, workspace=None, nnz_hint=None, stream=None) -> None:
     """sgap_sddmm_csr with the stored entries of rows of at least long_row_min entries taken by column
     windows of X2T (see include/sgap.h)."""
+    st = (_native or _load_native()).sddmm_csr_windows(M, K, J, rowptr, colidx, vals, X1, X2T, out_vals, group_size, strategy, nnz_hint,
+                                                        long_row_min, window_kb, max_long_rows, workspace, stream)
+    if st == 0:
+        return
+    if st > 0:
+        _check(st)
     import torch
 
     if rowptr.numel() != M + 1:
@@ -308,6 +349,11 @@ def sgap_sddmm_csr_windows(M, K, J, rowptr, colidx, vals, X1, X2T, out_vals, gro
 def sgap_ttm_csf(F, K, L, eptr, eidx, vals, X1, Yf, group_size, strategy, schedule, nnz_hint=None,
                  stream=None) -> None:
     """Yf[f, :] = sum over the entries p of fiber f of vals[p] * X1[eidx[p], :] (see include/sgap.h)."""
+    st = (_native or _load_native()).spmm_csr_ex(F, K, L, eptr, eidx, vals, X1, Yf, group_size, strategy, schedule, nnz_hint, stream)
+    if st == 0:
+        return
+    if st > 0:
+        _check(st)
     ptrs = _spmm_args(F, K, L, eptr, eidx, vals, X1, Yf)
     if nnz_hint is None:
         nnz_hint = eidx.numel()
@@ -338,6 +384,12 @@ def sgap_mttkrp_csf_ex(I, K, L, J, fptr, fidx, eptr, eidx, vals, X1, X2, Y, grou
                        nnz_hint=None, stream=None) -> None:
     """sgap_mttkrp_csf with a choice of schedule: slices (row-split) or stored entries (nnz-balanced) as the
     unit of work.  nnz_hint defaults to the length of vals."""
+    st = (_native or _load_native()).mttkrp_csf_ex(I, K, L, J, fptr, fidx, eptr, eidx, vals, X1, X2, Y, group_size, strategy, schedule,
+                                                    nnz_hint, stream)
+    if st == 0:
+        return
+    if st > 0:
+        _check(st)
     import torch
 
     if fptr.numel() != I + 1:

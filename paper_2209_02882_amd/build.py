@@ -43,6 +43,30 @@ def build_library(jobs: int = 8) -> str:
     return LIB
 
 
+NATIVE = os.path.join(HERE, "_native.so")
+
+
+def build_native() -> str:
+    """Compile the module behind binding.py's calls (csrc/sgap_python.cpp, host code) against torch's headers; it
+    finds libsgap.so beside itself and torch's libraries already loaded."""
+    import sysconfig
+
+    import torch
+
+    inc = os.path.join(os.path.dirname(torch.__file__), "include")
+    lib = os.path.join(os.path.dirname(torch.__file__), "lib")
+    rocm = os.environ.get("ROCM_PATH", "/opt/rocm")
+    cmd = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-fvisibility=hidden", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
+           f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}", "-w",
+           "-I" + inc, "-I" + os.path.join(inc, "torch", "csrc", "api", "include"), "-I" + os.path.join(rocm, "include"),
+           "-I" + sysconfig.get_paths()["include"], os.path.join(CSRC, "sgap_python.cpp"), "-o", NATIVE,
+           "-L" + HERE, "-l:libsgap.so", "-Wl,-rpath,$ORIGIN", "-L" + lib, "-ltorch_python", "-ltorch_cpu", "-lc10", "-lc10_hip"]
+    r = subprocess.run(cmd, capture_output=True, text=True)
+    if r.returncode != 0:
+        raise RuntimeError(f"g++ failed for sgap_python.cpp:\n{r.stderr}")
+    return NATIVE
+
+
 MICROBENCH = os.path.join(HERE, "microbench")
 
 
@@ -66,5 +90,6 @@ if __name__ == "__main__":
     import sys
 
     print(build_library())
+    print(build_native())
     if "--microbench" in sys.argv[1:]:
         print("\n".join(build_microbenchmarks()))
