@@ -383,13 +383,18 @@ int spmm_impl(int64_t M, int64_t K, int64_t N, const int32_t* rowptr, const int3
         const int xcds = c.xcd_remap == 0 ? 1 : kXcds;
         const int cus = compute_units();
         const int block = c.block_size > 0 ? c.block_size : kBlock;
-        const int g = par ? group_size : 1;  // lanes per row
+        int g = par ? group_size : 1;  // members per row
         const double avg_row = nnz_hint > 0 ? (double)nnz_hint / (double)M : 16.0;
         // Column tile: how many columns of B/C one work item covers.
         int64_t tile_cols = c.tile_cols > 0 ? c.tile_cols : kAutoTileCols;
         if (tile_cols > N) tile_cols = N;
         tile_cols = (tile_cols + vec - 1) / vec * vec;
-        const int lc = pow2_ceil_capped(tile_cols / vec, 64 / g);
+        // A row has the 64 lanes of a wavefront at most.  Columns come first: a group whose members leave too few chunk
+        // lanes for the tile gives members up, so that a row is gathered in one pass with all its loads in flight (N =
+        // 37, G = 16: one pass of 4 members x 16 chunk lanes in place of three of 16 x 4).  Not where the caller named
+        // a reduction narrower than the group: the sub-groups are what is asked for then.
+        const int lc = pow2_ceil_capped(tile_cols / vec, reduce_size == 0 ? 64 : 64 / g);
+        if (reduce_size == 0 && g * lc > 64) g = 64 / lc;
         int rows_per_slot = par ? c.rows_per_group : group_size;
         if (rows_per_slot <= 0) {
             // rows a group works through per item: enough stored entries per
