@@ -94,12 +94,13 @@ __device__ __forceinline__ RowWindow load_row_window(const SpmmArgs& a, int32_t&
     return w;
 }
 
-// Cut the plain window of a tile (s_win[r] = rowptr[row_lb + r], r <= kWindowCap, with s_win[kWindowCap] >=
+// Cut the plain window of a tile (s_win[r] = rowptr[row_lb + r], r <= CAP, with s_win[CAP] >=
 // tile_end, and row_lb the row of the tile's first position) down, in place, to the rows with entries that start
 // below tile_end: on return s_win[0 .. n] holds their first positions (and the end of the last), s_row[0 .. n)
 // their rows; n is returned.  A kept row moves to a slot at or in front of its own, every round reads its kBlock
 // slots before any is written, and a slot that a later round still reads is only ever overwritten with the value
 // it holds (the next row with entries starts where this one ends).  Block-uniform; two barriers per kBlock rows.
+template <int CAP = kWindowCap>
 __device__ __forceinline__ int32_t compact_window(int32_t* __restrict__ s_win, int32_t* __restrict__ s_row,
                                                   int32_t row_lb, int32_t tile_end, int32_t* __restrict__ s_wave)
 {
@@ -108,7 +109,7 @@ __device__ __forceinline__ int32_t compact_window(int32_t* __restrict__ s_win, i
     for (int32_t r0 = 0;; r0 += kBlock) {
         const int32_t r = r0 + tid;
         int32_t lo = 0x7fffffff, hi = 0x7fffffff;
-        if (r < kWindowCap) {
+        if (r < CAP) {
             lo = s_win[r];
             hi = s_win[r + 1];
         }

@@ -208,129 +208,279 @@ __global__ __launch_bounds__(kBlock) void sddmm_kernel(SddmmArgs s, int per_lane
     }
 }
 
-// Parallel strategy when the G lanes of a group cover a dense row in S <= 4
-// steps of 4 columns each (J <= S*G*4, 16-byte aligned operands).
-// A group takes its stored entries in batches of U CONSECUTIVE ones, which
-// mostly belong to one row of A, and keeps that row's chunk of X1 in
-// registers: a row of X1 is loaded when the row changes, not once per entry,
-// which takes up to half of the volume off the vector memory path.  The
-// batches of a round are dealt to the groups in order, so that the workgroup
-// as a whole still moves through neighbouring entries, whose rows of X2T tend
-// to be neighbours or the same (L1 hits).  The loads of a batch (rows of X2T,
-// and rows of X1 where the row changes inside the batch) are issued together.
-template <int G, int S, bool RAGGED>
-__global__ __launch_bounds__(kBlock) void sddmm_rowcache_kernel(SddmmArgs s)
+// Parallel strategy when the G lanes of a group cover a dense row in S <= 4 steps of 4 columns each (J <= S*G*4).
+// Every wavefront walks a quarter of the tile, (64/G)*U consecutive entries at a time, U consecutive ones per group.
+// What bounds the kernel is the vector memory path that brings in one row of X2T per entry, so everything else is kept
+// off it and off the vector units:
+//   - the rows of X1 that the tile touches are copied to LDS once (x1_rows of them fit; a tile of short rows, whose
+//     rows change with nearly every entry, reads them from memory), and read from there when a group's row changes;
+//   - the row of an entry comes from the window of rows with entries (compact_window): a thread bisects it for the
+//     first of its EPT entries and steps along for the others;
+//   - one multiply-add forms the address of a row of X2T, its S steps differ by a constant offset;
+//   - the next tile's entries and row pointers are requested before this one is multiplied out.
+// stencil27, J = 128, G = 8: 1,031 us with tiles of 1,024 entries, rows of X1 read from memory per batch and a
+// bisection per entry; 825 us now, at 2.3 instead of 4.7 GB moved (the tile: see try_tile).  What is left is the L1:
+// a workgroup takes the rows one after the other, so that only consecutive columns hit, and asks the L2 for twice the
+// lines that SpMM's row-split kernel does with eight rows in step.  A kernel with the rows in step ran 740 us here but
+// took two to three times as long on R-MAT, whose heavy rows sit together.
+// EDGE: J is not S*G*4 (lanes without columns, or a ragged last chunk).
+template <int G, int S, bool EDGE, int EPT>
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) void sddmm_tile_kernel(SddmmArgs s, int x1_rows)
 {
     constexpr int VEC = 4;
-    constexpr int SLOTS = kBlock / G;
-    constexpr int EPS = kSddmmTile / SLOTS;  // entries per group and tile
-    constexpr int U = 8 / S < EPS ? 8 / S : EPS;  // entries per batch: U*S <= 8 loads per operand in flight
-    __shared__ int32_t s_col[kSddmmTile];
-    __shared__ float s_val[kSddmmTile];
-    __shared__ int32_t s_row[kSddmmTile];
-    __shared__ int32_t s_win[kWindowCap + 1];
+    constexpr int GROUPS = kWave / G;
+    constexpr int TILE = EPT * kBlock;
+    constexpr int WAVE_RUN = TILE / kWavesPerBlock;
+    constexpr int U0 = 8 / S;  // entries per group and batch: 8 loads in flight per lane
+    constexpr int U = U0 * GROUPS > WAVE_RUN ? WAVE_RUN / GROUPS : U0;
+    constexpr int PITCH = S * G * VEC;  // floats of one row of X1 in LDS, zeros behind column J
+    constexpr int WPT = EPT + 1;  // row pointers per thread: a window of TILE rows
+    extern __shared__ __align__(16) float s_x1[];
+    __shared__ __align__(16) int32_t s_col[TILE];
+    __shared__ __align__(16) float s_val[TILE];
+    __shared__ __align__(16) uint16_t s_idx[TILE];  // window index of the entry's row
+    __shared__ int32_t s_win[TILE + 1];
+    __shared__ int32_t s_row[TILE];
+    __shared__ int32_t s_scan[kWavesPerBlock];
     __shared__ int32_t s_tile_row[kTileRowBatch];
 
     const SpmmArgs& a = s.a;
     const int tid = threadIdx.x;
-    const int slot = tid / G;
-    const int member = tid % G;
-    const int64_t J = a.N;
-    const float* __restrict__ X2T = a.B;
+    const int lane = tid % kWave;
+    const int wave = tid / kWave;
+    const int grp = lane / G;
+    const int member = lane % G;
+    const int32_t J = (int32_t)a.N;
+    const uint32_t row_bytes = (uint32_t)J * 4u;
+    const int32_t M = (int32_t)a.M;
     const int32_t nnz = a.rowptr[a.M];
-    const int64_t tiles = ((int64_t)nnz + kSddmmTile - 1) / kSddmmTile;
+    const int64_t tiles = ((int64_t)nnz + TILE - 1) / TILE;
     const TileDeal deal(tiles, blockIdx.x, gridDim.x);
     const int64_t my_tiles = deal.mine;
     if (my_tiles == 0) return;
-    // this lane's columns: (st*G + member)*4, st < S
+    TileWalk ahead(deal);  // the tile that is fetched next
+
+    // this lane's columns in step st: (st*G + member)*4 ..; c_first = the first column it loads
     bool c_ok[S];
+    int32_t c_first[S];
 #pragma unroll
-    for (int st = 0; st < S; ++st) c_ok[st] = (int64_t)(st * G + member) * VEC < J;
+    for (int st = 0; st < S; ++st) {
+        const int32_t c = (st * G + member) * VEC;
+        c_ok[st] = !EDGE || c < J;
+        c_first[st] = EDGE ? (c_ok[st] ? (int32_t)lane_first_col<VEC>((uint32_t)c, (uint32_t)J) : 0) : c;
+    }
+    // the lane's chunk of a row of X1 or X2T (the columns it shares with the lane in front of it as zeros)
+    auto load_chunk = [&](const float* base, int32_t row, int st) {
+        const char* p = reinterpret_cast<const char*>(base + (EDGE ? c_first[st] : member * VEC)) + (uint64_t)(uint32_t)row * row_bytes;
+        Vec<VEC> x;
+        if constexpr (EDGE) {
+            x.zero();
+            if (c_ok[st]) x = load_vec<VEC>(reinterpret_cast<const float*>(p));
+#pragma unroll
+            for (int i = 0; i < VEC - 1; ++i)
+                if (c_first[st] + i < (st * G + member) * VEC) x.v[i] = 0.0f;
+        } else {
+            x = load_vec<VEC>(reinterpret_cast<const float*>(p) + st * G * VEC);
+        }
+        return x;
+    };
+
+    int32_t nx_col[EPT];
+    float nx_val[EPT];
+    int32_t nx_win[WPT];
+    auto fetch_tile = [&](int32_t row_lb) {  // the tile `ahead` stands at
+        const int32_t start = (int32_t)(ahead.tile() * TILE);
+#pragma unroll
+        for (int i = 0; i < EPT; ++i) {
+            const int32_t p = start + tid + i * kBlock;
+            nx_col[i] = 0;  // (positions past the end gather row 0 of X2T, and nothing of them is written)
+            nx_val[i] = 0.0f;
+            if (p < nnz) {
+                nx_col[i] = load_stream(a.colidx + p);
+                nx_val[i] = load_stream(a.vals + p);
+            }
+        }
+#pragma unroll
+        for (int i = 0; i < WPT; ++i) {
+            const int w = tid + i * kBlock;
+            const int64_t r = (int64_t)row_lb + w;
+            nx_win[i] = w <= TILE ? a.rowptr[r <= M ? r : M] : 0;
+        }
+    };
 
     for (int64_t j0 = 0; j0 < my_tiles; j0 += kTileRowBatch) {
-        find_tile_rows(a, deal, j0, kSddmmTile, s_tile_row);
+        find_tile_rows(a, deal, j0, TILE, s_tile_row);
         const int64_t j1 = j0 + kTileRowBatch < my_tiles ? j0 + kTileRowBatch : my_tiles;
+        fetch_tile(s_tile_row[0]);
         for (int64_t j = j0; j < j1; ++j) {
-            const int64_t t = deal.tile(j);
-            const int32_t tile_start = (int32_t)(t * kSddmmTile);
-            const int32_t tile_end = nnz - tile_start < kSddmmTile ? nnz : tile_start + kSddmmTile;
+            const int32_t tile_start = (int32_t)(ahead.tile() * TILE);
+            ahead.next();
+            const int32_t tile_end = nnz - tile_start < TILE ? nnz : tile_start + TILE;
             const int cnt = tile_end - tile_start;
             const int32_t row_lb = s_tile_row[j - j0];
-
-            stage_tile(a, tile_start, tile_end, row_lb, s_col, s_val, s_row, s_win);
-
-            int32_t cur_row = -1;
-            Vec<VEC> x1c[S];  // the chunk of X1[cur_row] this lane owns
+            // install the tile that was fetched ahead (the barrier at the end of the loop: the last one is consumed)
 #pragma unroll
-            for (int st = 0; st < S; ++st) x1c[st].zero();
-            for (int i0 = 0; i0 < EPS; i0 += U) {  // same trip count in every lane
-                int32_t row[U], col[U];
-                bool ok[U], fresh[U];
+            for (int i = 0; i < EPT; ++i) {
+                s_col[tid + i * kBlock] = nx_col[i];
+                s_val[tid + i * kBlock] = nx_val[i];
+            }
 #pragma unroll
-                for (int u = 0; u < U; ++u) {
-                    const int e = (i0 / U * SLOTS + slot) * U + u;
-                    ok[u] = e < cnt;
-                    row[u] = ok[u] ? s_row[e] : (u ? row[u - 1] : cur_row);
-                    col[u] = ok[u] ? s_col[e] : 0;
-                    fresh[u] = ok[u] && row[u] != (u ? row[u - 1] : cur_row);
-                }
-                Vec<VEC> x1[U][S], x2[U][S];
+            for (int i = 0; i < WPT; ++i)
+                if (tid + i * kBlock <= TILE) s_win[tid + i * kBlock] = nx_win[i];
+            __syncthreads();
+            if (j + 1 < j1) fetch_tile(s_tile_row[j + 1 - j0]);
+            int32_t n;  // rows with entries in the tile: first positions in s_win, numbers in s_row
+            if (s_win[TILE] >= tile_end) {
+                n = compact_window<TILE>(s_win, s_row, row_lb, tile_end, s_scan);
+            } else {
+                __syncthreads();  // everyone has read the plain window
+                n = load_compact_window(a, row_lb, tile_end, s_win, s_row, s_scan);
+            }
+            const bool x1_in_lds = n <= x1_rows;
+            if (x1_in_lds) {
+                for (int i = tid; i < n * (PITCH / VEC); i += kBlock) {
+                    const int r = i / (PITCH / VEC);
+                    const int32_t c = i % (PITCH / VEC) * VEC;
+                    Vec<VEC> x;
+                    if constexpr (EDGE) {
+                        x.zero();
+                        if (c < J) {
+                            const int32_t first = (int32_t)lane_first_col<VEC>((uint32_t)c, (uint32_t)J);
+                            x = load_vec<VEC>(s.X1 + (int64_t)s_row[r] * J + first);
 #pragma unroll
-                for (int u = 0; u < U; ++u) {
-#pragma unroll
-                    for (int st = 0; st < S; ++st) {
-                        const int64_t c = (int64_t)(st * G + member) * VEC;
-                        x2[u][st].zero();
-                        x1[u][st].zero();
-                        if (ok[u] && c_ok[st]) x2[u][st] = load_own<VEC, RAGGED>(X2T + (int64_t)col[u] * J, c, J);
-                        if (fresh[u] && c_ok[st]) x1[u][st] = load_own<VEC, RAGGED>(s.X1 + (int64_t)row[u] * J, c, J);
+                            for (int v = 0; v < VEC - 1; ++v)
+                                if (first + v < c) x.v[v] = 0.0f;
+                        }
+                    } else {
+                        x = load_vec<VEC>(s.X1 + (int64_t)s_row[r] * J + c);
                     }
+                    *reinterpret_cast<float4*>(s_x1 + i * VEC) = make_float4(x.v[0], x.v[1], x.v[2], x.v[3]);
                 }
-                float acc[U];
+            }
+            {
+                int32_t wi = last_row_at_or_before(s_win, 0, n - 1, tile_start + tid * EPT);
 #pragma unroll
-                for (int u = 0; u < U; ++u) {
-                    acc[u] = 0.0f;
-#pragma unroll
-                    for (int st = 0; st < S; ++st) {
-                        if (fresh[u]) x1c[st] = x1[u][st];
-                        acc[u] = dot_vec<VEC>(x1c[st], x2[u][st], acc[u]);
-                    }
-                }
-                cur_row = row[U - 1];
-#pragma unroll
-                for (int u = 0; u < U; ++u) acc[u] = group_tree_sum<G, 1>(acc[u]);
-#pragma unroll
-                for (int u = 0; u < U; ++u) {
-                    const int e = (i0 / U * SLOTS + slot) * U + u;
-                    if (member == 0 && ok[u]) s_val[e] *= acc[u];  // this group is the entry's only reader
+                for (int i = 0; i < EPT; ++i) {
+                    // (every row of the window has entries: at most one step per position; the last row's end is the window's)
+                    if (wi + 1 < n && s_win[wi + 1] <= tile_start + tid * EPT + i) ++wi;
+                    s_idx[tid * EPT + i] = (uint16_t)wi;
                 }
             }
             __syncthreads();
-            for (int i = tid; i < cnt; i += kBlock) s.out[tile_start + i] = s_val[i];
+
+            // One batch of B entries per group from slot b on; LDS_X1: the rows of X1 come from LDS, where a group reads
+            // one when its row changes (cur); else every entry's row is requested along with its row of X2T.
+            int32_t cur = -1;
+            Vec<VEC> x1c[S];  // the chunk of X1's row `cur` this lane owns
+#pragma unroll
+            for (int st = 0; st < S; ++st) x1c[st].zero();
+            auto batch = [&](int b, auto b_const, auto lds_const) {
+                constexpr int B = decltype(b_const)::value;
+                constexpr bool LDS_X1 = decltype(lds_const)::value;
+                const int e = b + grp * B;
+                float acc[B];
+                Vec<VEC> x2[B][S];
+#pragma unroll
+                for (int u = 0; u < B; ++u) {
+                    acc[u] = 0.0f;
+#pragma unroll
+                    for (int st = 0; st < S; ++st) x2[u][st] = load_chunk(a.B, s_col[e + u], st);
+                }
+                if constexpr (LDS_X1) {
+#pragma unroll
+                    for (int u = 0; u < B; ++u) {
+                        const int32_t idx = s_idx[e + u];
+                        if (idx != cur) {
+#pragma unroll
+                            for (int st = 0; st < S; ++st) {
+                                const float4 t = *reinterpret_cast<const float4*>(s_x1 + idx * PITCH + (st * G + member) * VEC);
+                                x1c[st].v[0] = t.x; x1c[st].v[1] = t.y; x1c[st].v[2] = t.z; x1c[st].v[3] = t.w;
+                            }
+                            cur = idx;
+                        }
+#pragma unroll
+                        for (int st = 0; st < S; ++st) acc[u] = dot_vec<VEC>(x1c[st], x2[u][st], acc[u]);
+                    }
+                } else {
+                    Vec<VEC> x1[B][S];
+#pragma unroll
+                    for (int u = 0; u < B; ++u) {
+                        const int32_t row = s_row[s_idx[e + u]];
+#pragma unroll
+                        for (int st = 0; st < S; ++st) x1[u][st] = load_chunk(s.X1, row, st);
+                    }
+#pragma unroll
+                    for (int u = 0; u < B; ++u) {
+#pragma unroll
+                        for (int st = 0; st < S; ++st) acc[u] = dot_vec<VEC>(x1[u][st], x2[u][st], acc[u]);
+                    }
+                }
+#pragma unroll
+                for (int u = 0; u < B; ++u) acc[u] = group_tree_sum<G, 1>(acc[u]);
+                if (member == 0) {
+                    // the group's outputs are consecutive, and so are the groups'
+#pragma unroll
+                    for (int u = 0; u < B; ++u) acc[u] *= s_val[e + u];
+                    if (B % VEC == 0 && e + B <= cnt) {
+#pragma unroll
+                        for (int u = 0; u + VEC <= B; u += VEC) {
+                            const Vec<VEC> o = {acc[u], acc[u + 1], acc[u + 2], acc[u + 3]};
+                            store_vec_stream<VEC>(s.out + tile_start + e + u, o);
+                        }
+                    } else {
+#pragma unroll
+                        for (int u = 0; u < B; ++u)
+                            if (e + u < cnt) s.out[tile_start + e + u] = acc[u];
+                    }
+                }
+            };
+            const int run_end = (wave + 1) * WAVE_RUN < cnt ? (wave + 1) * WAVE_RUN : cnt;
+            if (x1_in_lds) {
+                for (int b = wave * WAVE_RUN; b < run_end; b += GROUPS * U)
+                    batch(b, std::integral_constant<int, U>{}, std::true_type{});
+            } else {
+                constexpr int H = U < 2 ? 1 : U / 2;
+                for (int b = wave * WAVE_RUN; b < run_end; b += GROUPS * H)
+                    batch(b, std::integral_constant<int, H>{}, std::false_type{});
+            }
+            __syncthreads();  // the tile is consumed
         }
     }
 }
 
 namespace {
 
-template <int G, int S, bool RAGGED>
-void launch_rowcache(const SddmmArgs& s, int compute_units, int64_t nnz_hint, hipStream_t stream)
+constexpr int kX1LdsBytes = 10 * 1024;  // rows of X1 in LDS per 256 entries of a tile: 20 of 512 bytes
+
+template <int G, int S, bool EDGE, int EPT>
+void launch_tile(const SddmmArgs& s, int compute_units, int64_t nnz_hint, hipStream_t stream)
 {
-    static const int per_cu = resident_per_cu(sddmm_rowcache_kernel<G, S, RAGGED>, 0);
-    const int grid = persistent_grid(per_cu, compute_units, nnz_hint, kSddmmTile);
-    hipLaunchKernelGGL((sddmm_rowcache_kernel<G, S, RAGGED>), dim3(grid), dim3(kBlock), 0, stream, s);
+    constexpr int x1_rows = EPT * kX1LdsBytes / (S * G * 16);
+    constexpr int x1_bytes = x1_rows * S * G * 16;
+    static const int per_cu = resident_per_cu(sddmm_tile_kernel<G, S, EDGE, EPT>, x1_bytes);
+    const int grid = persistent_grid(per_cu, compute_units, nnz_hint, EPT * kBlock);
+    hipLaunchKernelGGL((sddmm_tile_kernel<G, S, EDGE, EPT>), dim3(grid), dim3(kBlock), x1_bytes, stream, s, x1_rows);
 }
 
-// steps of G*4 columns that cover J: 1, 2 or 4 pick the row-cache kernel, 0 = more than 4
+// Steps of G*4 columns that cover J: 1, 2 or 4 pick sddmm_tile_kernel, 0 = more than 4.
+// Tile: the entries that all resident workgroups work on at a time decide whether neighbouring rows find each other's
+// rows of X2T in the die's L2: 256 entries for wide rows (stencil27, J = 128: 825 us, 512 entries 958, 1,024 entries
+// 1,038), twice that for rows of up to 64 columns, where the work per tile weighs more (57 x 60 x 62 stencil, J = 34:
+// 92 us against 107; R-MAT alike).
 template <int G>
-bool try_rowcache(const SddmmArgs& s, int64_t J, int compute_units, int64_t nnz_hint, hipStream_t stream)
+bool try_tile(const SddmmArgs& s, int64_t J, int compute_units, int64_t nnz_hint, hipStream_t stream)
 {
     const int64_t steps = (J + G * 4 - 1) / (G * 4);
-    const bool ragged = J % 4 != 0;
     auto pick = [&](auto s_const) {
         constexpr int S = decltype(s_const)::value;
-        if (ragged) launch_rowcache<G, S, true>(s, compute_units, nnz_hint, stream);
-        else launch_rowcache<G, S, false>(s, compute_units, nnz_hint, stream);
+        const bool edge = J != S * G * 4;
+        if (J <= 64) {
+            if (edge) launch_tile<G, S, true, 2>(s, compute_units, nnz_hint, stream);
+            else launch_tile<G, S, false, 2>(s, compute_units, nnz_hint, stream);
+        } else {
+            if (edge) launch_tile<G, S, true, 1>(s, compute_units, nnz_hint, stream);
+            else launch_tile<G, S, false, 1>(s, compute_units, nnz_hint, stream);
+        }
     };
     if (steps <= 1) pick(std::integral_constant<int, 1>{});
     else if (steps <= 2) pick(std::integral_constant<int, 2>{});
@@ -390,13 +540,13 @@ hipError_t launch_sddmm(const SpmmArgs& a, const float* X1, float* out, int g, i
         ok = launch_vec<1>(s, vec, per_lane, compute_units, nnz_hint, stream);
     } else if (vec == 4 && row_cache && a.N > 0) {
         switch (g) {
-            case 1: ok = try_rowcache<1>(s, a.N, compute_units, nnz_hint, stream); break;
-            case 2: ok = try_rowcache<2>(s, a.N, compute_units, nnz_hint, stream); break;
-            case 4: ok = try_rowcache<4>(s, a.N, compute_units, nnz_hint, stream); break;
-            case 8: ok = try_rowcache<8>(s, a.N, compute_units, nnz_hint, stream); break;
-            case 16: ok = try_rowcache<16>(s, a.N, compute_units, nnz_hint, stream); break;
-            case 32: ok = try_rowcache<32>(s, a.N, compute_units, nnz_hint, stream); break;
-            case 64: ok = try_rowcache<64>(s, a.N, compute_units, nnz_hint, stream); break;
+            case 1: ok = try_tile<1>(s, a.N, compute_units, nnz_hint, stream); break;
+            case 2: ok = try_tile<2>(s, a.N, compute_units, nnz_hint, stream); break;
+            case 4: ok = try_tile<4>(s, a.N, compute_units, nnz_hint, stream); break;
+            case 8: ok = try_tile<8>(s, a.N, compute_units, nnz_hint, stream); break;
+            case 16: ok = try_tile<16>(s, a.N, compute_units, nnz_hint, stream); break;
+            case 32: ok = try_tile<32>(s, a.N, compute_units, nnz_hint, stream); break;
+            case 64: ok = try_tile<64>(s, a.N, compute_units, nnz_hint, stream); break;
             default: break;
         }
         if (!ok) return launch_sddmm(a, X1, out, g, per_lane, vec, false, compute_units, nnz_hint, stream);

@@ -56,4 +56,28 @@ struct TileDeal {
     }
 };
 
+// A workgroup's tiles one after the other: deal.tile(0), deal.tile(1), ... without a division per tile (a 64-bit
+// division is a hundred instructions, which a tile of a few hundred entries feels).
+struct TileWalk {
+    uint32_t chunk, blk, rem, blk_step, rem_step, die, dies;
+    SGAP_HOST_DEVICE explicit TileWalk(const TileDeal& d)
+        : chunk((uint32_t)d.chunk), die((uint32_t)d.die), dies((uint32_t)d.dies)
+    {
+        blk = (uint32_t)d.wg / chunk;
+        rem = (uint32_t)d.wg % chunk;
+        blk_step = (uint32_t)d.wgs / chunk;
+        rem_step = (uint32_t)d.wgs % chunk;
+    }
+    SGAP_HOST_DEVICE uint32_t tile() const { return (die + dies * blk) * chunk + rem; }  // below 2^31 / 256
+    SGAP_HOST_DEVICE void next()
+    {
+        blk += blk_step;
+        rem += rem_step;
+        if (rem >= chunk) {
+            rem -= chunk;
+            ++blk;
+        }
+    }
+};
+
 }  // namespace sgap
