@@ -265,9 +265,10 @@ hipError_t launch_sddmm(const SpmmArgs& a, const float* X1, float* out, int g, i
 hipError_t launch_sddmm_panels(const SpmmArgs& a, const float* X1, float* out, int g, int per_lane, int xcds,
                                int compute_units, int64_t nnz_hint, int32_t min_len, int64_t window_bytes,
                                void* workspace, int64_t cap, hipStream_t stream);
-// the plain SDDMM kernel (no row cache) that leaves the entries of the rows described by `skip` alone
-hipError_t launch_sddmm_skip(const SpmmArgs& a, const float* X1, float* out, int g, int per_lane, int compute_units,
-                             int64_t nnz_hint, const RowSkip& skip, hipStream_t stream);
+// the plain SDDMM kernel on the rows of at least from_len entries that are not described by `skip` (on every row if
+// there are more of those than skip.max_rows)
+hipError_t launch_sddmm_rest(const SpmmArgs& a, const float* X1, float* out, int g, int per_lane, int compute_units,
+                             int64_t nnz_hint, const RowSkip& skip, int32_t from_len, hipStream_t stream);
 // MTTKRP on compressed sparse fibers: g lanes per slice (1 for the serial
 // strategy), rows_per_slot slices per group (consecutive, or interleaved with
 // the other groups' slices), lc chunk lanes of vec columns each.

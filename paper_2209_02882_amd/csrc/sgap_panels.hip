@@ -26,6 +26,7 @@
 // rows than the list holds, this path does nothing and the row-split kernel
 // takes every row.
 #include "sgap_common.hpp"
+#include "sgap_dot8.hpp"
 #include "sgap_lane_ops.hpp"
 #include "sgap_row_split_impl.hpp"
 #include "sgap_uniform.hpp"
@@ -727,10 +728,8 @@ hipError_t launch_row_split_panels(const SpmmArgs& a, int g, int lc, int vec, in
 // entries [p0, p1) of a long row, by one wavefront of G members x LC chunk lanes
 // (LC >= 8, J <= LC*4: a lane owns four columns).  The members split the entries
 // eight at a time; a member's LC lanes hold partial dot products of its eight
-// entries and sum them in log2(LC) exchange steps, the first three of which halve
-// the number of values a lane carries (8, 4, 2, 1), so that the eight sums cost
-// ten exchanges instead of 8 * log2(LC).  Afterwards lane c of a member holds the
-// sum of entry c >> (log2(LC) - 3), and the lanes whose low bits are zero write.
+// entries and sum them with dot8_reduce, after which lane c of a member holds the sum
+// of entry dot8_number(c).
 template <int G, int LC>
 __device__ __forceinline__ void panel_sddmm_item(const SpmmArgs& a, const float* __restrict__ X1,
                                                  float* __restrict__ out, int32_t p0, int32_t p1, int64_t row, int lane)
@@ -775,42 +774,15 @@ __device__ __forceinline__ void panel_sddmm_item(const SpmmArgs& a, const float*
 #pragma unroll
                 for (int v = 0; v < VEC; ++v) part[u] = __builtin_fmaf(x1.v[v], x2[u].v[v], part[u]);
             }
-            // 8 -> 4 -> 2 -> 1 values: the upper half of each pair of lane halves keeps the upper half of the values
-            float four[4], two[2], one;
-            {
-                const bool up = (chunk & (LC / 2)) != 0;
-#pragma unroll
-                for (int u = 0; u < 4; ++u) {
-                    const float keep = up ? part[u + 4] : part[u];
-                    const float send = up ? part[u] : part[u + 4];
-                    four[u] = keep + __shfl_xor(send, LC / 2, LC);
-                }
-            }
-            {
-                const bool up = (chunk & (LC / 4)) != 0;
-#pragma unroll
-                for (int u = 0; u < 2; ++u) {
-                    const float keep = up ? four[u + 2] : four[u];
-                    const float send = up ? four[u] : four[u + 2];
-                    two[u] = keep + __shfl_xor(send, LC / 4, LC);
-                }
-            }
-            {
-                const bool up = (chunk & (LC / 8)) != 0;
-                const float keep = up ? two[1] : two[0];
-                const float send = up ? two[0] : two[1];
-                one = keep + __shfl_xor(send, LC / 8, LC);
-            }
-#pragma unroll
-            for (int m = LC / 16; m >= 1; m /= 2) one += __shfl_xor(one, m, LC);
+            dot8_reduce<LC>(part);
             // this lane's entry of the batch, and its value
-            const int u_mine = chunk / (LC / 8);
+            const int u_mine = dot8_number<LC>(chunk);
             float val_mine = val[0];
 #pragma unroll
             for (int u = 1; u < V; ++u)
                 if (u == u_mine) val_mine = val[u];
             const int j = j0 + u_mine * G + member;
-            if (chunk % (LC / 8) == 0 && j < cnt) out[base + j] = val_mine * one;
+            if (dot8_writer<LC>(chunk) && j < cnt) out[base + j] = val_mine * part[0];
         }
     }
 }
@@ -818,11 +790,12 @@ __device__ __forceinline__ void panel_sddmm_item(const SpmmArgs& a, const float*
 template <int G, int LC>
 __global__ __launch_bounds__(kBlock) void panel_sddmm_kernel(SpmmArgs a, const float* __restrict__ X1,
                                                              float* __restrict__ out, PanelView scr, int windows,
-                                                             int xcds)
+                                                             int xcds, uint32_t below)
 {
+    // below: the kernel runs only for lists of fewer rows (longer lists are panel_sddmm_owner_kernel's)
     __shared__ uint32_t s_claim;
     const uint32_t n = scr.head->count;
-    if (n == 0 || n > scr.cap) return;
+    if (n == 0 || n > scr.cap || n >= below) return;
     const int lane = threadIdx.x % kWave;
     const int wave = threadIdx.x / kWave;
     const int per_row = windows + 1;
@@ -847,11 +820,195 @@ __global__ __launch_bounds__(kBlock) void panel_sddmm_kernel(SpmmArgs a, const f
     }
 }
 
+// Up to eight entries j .. j + cnt - 1 of a chunk (one wavefront, 64 lanes on J <= 256 columns): their dot products with
+// the row of X1 whose columns the lanes hold, times their values, to out[0 .. cnt).  PART: fewer than eight, perhaps.
+// EDGE: lanes past the last column exist (they load columns that exist, and add nothing).
+template <bool OFF32, bool EDGE, bool PART>
+__device__ __forceinline__ void wave_dot8(const UniformRows<4, OFF32>& rows, const Vec<4>& x1, const EntryChunk& ch, int j,
+                                          int cnt, int lane, bool k_ok, float* __restrict__ out)
+{
+    int32_t c[8];
+    Vec<4> b[8];
+    float part[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) c[u] = __builtin_amdgcn_readlane(ch.col, (j + u) & (kWave - 1));
+#pragma unroll
+    for (int u = 0; u < 8; ++u) {
+        if constexpr (PART) {
+            b[u].zero();
+            if (u < cnt) b[u] = rows.load(c[u]);
+        } else {
+            b[u] = rows.load(c[u]);
+        }
+    }
+#pragma unroll
+    for (int u = 0; u < 8; ++u) {
+        part[u] = x1.v[0] * b[u].v[0];
+#pragma unroll
+        for (int i = 1; i < 4; ++i) part[u] = __builtin_fmaf(x1.v[i], b[u].v[i], part[u]);
+        if (EDGE && !k_ok) part[u] = 0.0f;
+    }
+    dot8_reduce<kWave>(part);
+    const int u = dot8_number<kWave>(lane);
+    const float val = __int_as_float(__shfl(ch.val, (j + u) & (kWave - 1), kWave));
+    if (dot8_writer<kWave>(lane) && (!PART || u < cnt)) out[u] = val * part[0];
+}
+
+// SDDMM with owner wavefronts, as panel_owner_kernel has them for SpMM (same deal of the rows, same walk through the
+// windows, same barrier per window): for dense rows of 129 to 256 columns and lists long enough.  What a wavefront keeps
+// of its ten rows is their rows of X1 instead of their sums, and every entry is written when it is done: no atomics.
+template <bool OFF32, bool EDGE>
+__global__ __launch_bounds__(kOwnerBlock) void panel_sddmm_owner_kernel(const int32_t* __restrict__ colidx,
+                                                                        const float* __restrict__ vals,
+                                                                        const float* __restrict__ X1,
+                                                                        const float* __restrict__ X2T,
+                                                                        float* __restrict__ out, PanelView scr, int64_t K,
+                                                                        int64_t J, int windows, int32_t window_rows,
+                                                                        int xcds, uint32_t min_rows)
+{
+    constexpr int R = kOwnerRows;
+    const uint32_t n = scr.head->count;
+    if (n < min_rows || n > scr.cap) return;
+    const int lane = threadIdx.x % kWave;
+    const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    const uint32_t xcd = blockIdx.x % xcds;
+    const uint32_t waves = (gridDim.x / xcds) * kOwnerWaves;  // wavefronts of this die
+    const uint32_t me = (blockIdx.x / xcds) * kOwnerWaves + wave;
+    const uint32_t rounds = (n + waves - 1) / waves;
+    const int per_row = windows + 1;
+    const int w_begin = panel_share_begin((int)xcd, windows, xcds);
+    const int w_end = panel_share_begin((int)xcd + 1, windows, xcds);
+    const int64_t k = (int64_t)lane * 4;
+    const bool k_ok = !EDGE || k < J;
+    const UniformRows<4, OFF32> rows(X2T, K, J, k_ok ? k : 0);
+    for (uint32_t r0 = 0; r0 < rounds; r0 += R) {
+        // positions per row slot as in panel_owner_kernel
+        int32_t my_pos = 0;
+        int32_t my_row = -1;
+        {
+            const uint32_t round = r0 + (uint32_t)(lane % R);
+            const uint32_t q = round * waves + ((round & 1u) ? waves - 1u - me : me);
+            if (lane < 3 * R && round < rounds && q < n) {
+                const int32_t i = scr.order[q];
+                my_pos = scr.ptr[(int64_t)i * per_row + (lane >= R && lane < 2 * R ? w_end : w_begin)];
+                my_row = scr.rows[i];
+            }
+        }
+        Vec<4> x1[R];
+        EntryChunk held[R];
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            const int32_t row = __builtin_amdgcn_readlane(my_row, r);
+            x1[r].zero();
+            if (row >= 0) x1[r] = load_vec<4>(X1 + (int64_t)row * J + (k_ok ? k : 0));
+            held[r] = load_chunk(colidx, vals, __builtin_amdgcn_readlane(my_pos, r),
+                                 __builtin_amdgcn_readlane(my_pos, R + r), lane);
+        }
+        for (int w = w_begin; w < w_end; ++w) {
+            const bool last = w + 1 == w_end;  // of the share: takes all that is left
+            const int64_t limit64 = (int64_t)(w + 1) * window_rows;
+            const int32_t limit = limit64 > 0x7fffffffLL ? 0x7fffffff : (int32_t)limit64;
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+                int32_t p = __builtin_amdgcn_readlane(my_pos, r);
+                const int32_t end = __builtin_amdgcn_readlane(my_pos, R + r);
+                int32_t base = __builtin_amdgcn_readlane(my_pos, 2 * R + r);
+                for (;;) {
+                    const int from = p - base;
+                    int to = end - base < kWave ? end - base : kWave;
+                    if (to < from) to = from;
+                    const bool whole = to == kWave && base + kWave < end;  // the row goes on behind them
+                    if (!last) {
+                        const unsigned long long beyond = __ballot(lane >= from && lane < to && held[r].col >= limit);
+                        if (beyond) to = __ffsll((long long)beyond) - 1;
+                    }
+                    const bool refill = whole && to == kWave;
+                    EntryChunk ahead = held[r];
+                    if (refill) ahead = load_chunk(colidx, vals, base + kWave, end, lane);
+                    int j = from;
+                    for (; j + 8 <= to; j += 8)
+                        wave_dot8<OFF32, EDGE, false>(rows, x1[r], held[r], j, 8, lane, k_ok, out + base + j);
+                    if (j < to) wave_dot8<OFF32, EDGE, true>(rows, x1[r], held[r], j, to - j, lane, k_ok, out + base + j);
+                    p = base + to;
+                    if (!refill) break;
+                    held[r] = ahead;
+                    base += kWave;
+                }
+                if (lane == r) my_pos = p;
+                if (lane == 2 * R + r) my_pos = base;
+            }
+            __syncthreads();  // the compute unit's wavefronts take the next window together
+        }
+    }
+}
+
+// The rows of fewer than `below` entries while the long rows have a place in the list (else the kernel does nothing):
+// LC chunk lanes hold a row of X1 in registers and take the row's entries eight at a time; 64 / LC rows per wavefront
+// side by side, rows_per_member one after the other.  Bound by the random reads of X2T (skewed, J = 256: 2.2 M entries).
+template <int LC>
+__global__ __launch_bounds__(kBlock) void sddmm_short_rows_kernel(SpmmArgs a, const float* __restrict__ X1,
+                                                                  float* __restrict__ out, RowSkip skip, int32_t below,
+                                                                  int rows_per_member, int64_t blocks_per_xcd)
+{
+    if (*skip.count > skip.max_rows) return;
+    constexpr int MEMBERS = kBlock / LC;
+    const int member = threadIdx.x / LC;
+    const int chunk = threadIdx.x % LC;
+    const int lane0 = threadIdx.x % kWave / LC * LC;  // first lane of this member
+    const int64_t J = a.N;
+    const int64_t k = (int64_t)chunk * 4;
+    const bool k_ok = k < J;
+    const int64_t block = (int64_t)(blockIdx.x % 8) * blocks_per_xcd + blockIdx.x / 8;
+    const int64_t row0 = (block * MEMBERS + member) * rows_per_member;
+    // (members past the last row stay: the sums are made by the whole wavefront together)
+    auto pointer = [&](int i) { return a.rowptr[row0 + i < a.M ? row0 + i : a.M]; };
+    int32_t begin = pointer(0), end = pointer(1);
+    for (int i = 0; i < rows_per_member; ++i) {
+        const int32_t next_end = pointer(i + 2 <= rows_per_member ? i + 2 : rows_per_member);
+        const int32_t stop = end - begin < below ? end : begin;
+        if (__any(begin < stop)) {
+            Vec<4> x1;
+            x1.zero();
+            if (k_ok && begin < stop) x1 = load_vec<4>(X1 + (row0 + i) * J + k);
+            for (int32_t p = begin; __any(p < stop); p += 8) {
+                // lanes 0 .. 7 of a member hold its eight entries
+                int32_t my_col = 0, my_val = 0;
+                if (chunk < 8 && p + chunk < stop) {
+                    my_col = load_stream(a.colidx + p + chunk);
+                    my_val = __float_as_int(load_stream(a.vals + p + chunk));
+                }
+                Vec<4> b[8];
+                float part[8];
+#pragma unroll
+                for (int u = 0; u < 8; ++u) {
+                    const int32_t col = __shfl(my_col, lane0 + u, kWave);
+                    b[u].zero();
+                    if (k_ok && p + u < stop) b[u] = load_vec<4>(a.B + (int64_t)col * J + k);
+                }
+#pragma unroll
+                for (int u = 0; u < 8; ++u) {
+                    part[u] = x1.v[0] * b[u].v[0];
+#pragma unroll
+                    for (int v = 1; v < 4; ++v) part[u] = __builtin_fmaf(x1.v[v], b[u].v[v], part[u]);
+                }
+                dot8_reduce<LC>(part);
+                const int u = dot8_number<LC>(chunk);
+                const float val = __int_as_float(__shfl(my_val, lane0 + u, kWave));
+                if (dot8_writer<LC>(chunk) && p + u < stop) out[p + u] = val * part[0];
+            }
+        }
+        begin = end;
+        end = next_end;
+    }
+}
+
 namespace {
+
+constexpr int32_t kShortRow = 1024;  // rows of fewer entries are a member's of sddmm_short_rows_kernel
 
 template <int G, int LC>
 void launch_sddmm_long_rows(const SpmmArgs& a, const float* X1, float* out, const PanelView& scr, int windows, int xcds,
-                            int compute_units, hipStream_t s)
+                            uint32_t below, int compute_units, hipStream_t s)
 {
     static const int per_cu = [] {
         int n = 0;
@@ -862,7 +1019,7 @@ void launch_sddmm_long_rows(const SpmmArgs& a, const float* X1, float* out, cons
     int grid = per_cu * compute_units;
     grid -= grid % xcds;
     if (grid < xcds) grid = xcds;
-    hipLaunchKernelGGL((panel_sddmm_kernel<G, LC>), dim3(grid), dim3(kBlock), 0, s, a, X1, out, scr, windows, xcds);
+    hipLaunchKernelGGL((panel_sddmm_kernel<G, LC>), dim3(grid), dim3(kBlock), 0, s, a, X1, out, scr, windows, xcds, below);
 }
 
 }  // namespace
@@ -881,19 +1038,56 @@ hipError_t launch_sddmm_panels(const SpmmArgs& a, const float* X1, float* out, i
     plan_panels(a.K, a.N, window_bytes, &windows, &window_rows);
     if ((int64_t)windows * cap > 0xffffffffLL) return hipErrorInvalidValue;
     const PanelView scr = panel_view(workspace, cap, windows);
-    launch_panel_preparation(a, scr, windows, window_rows, min_len, false, false, 1, compute_units, s);
     int wave_lc = 8;
     while (wave_lc < kWave && (int64_t)wave_lc * 4 < a.N) wave_lc *= 2;
-    switch (wave_lc) {
-        case 8: launch_sddmm_long_rows<8, 8>(a, X1, out, scr, windows, xcds, compute_units, s); break;
-        case 16: launch_sddmm_long_rows<4, 16>(a, X1, out, scr, windows, xcds, compute_units, s); break;
-        case 32: launch_sddmm_long_rows<2, 32>(a, X1, out, scr, windows, xcds, compute_units, s); break;
-        default: launch_sddmm_long_rows<1, 64>(a, X1, out, scr, windows, xcds, compute_units, s); break;
+    const bool owners = wave_lc == kWave;
+    launch_panel_preparation(a, scr, windows, window_rows, min_len, false, owners, owners ? xcds : 1, compute_units, s);
+    uint32_t below = 0xffffffffu;
+    if (owners) {
+        below = owner_min_rows(xcds, compute_units);
+        int grid = compute_units;
+        grid -= grid % xcds;
+        if (grid < xcds) grid = xcds;
+        auto go = [&](auto kernel) {
+            hipLaunchKernelGGL(kernel, dim3(grid), dim3(kOwnerBlock), 0, s, a.colidx, a.vals, X1, a.B, out, scr, a.K, a.N,
+                               windows, window_rows, xcds, below);
+        };
+        const bool edge = a.N != kWave * 4;
+        if (offsets_fit_32(a)) {
+            if (edge) go(panel_sddmm_owner_kernel<true, true>); else go(panel_sddmm_owner_kernel<true, false>);
+        } else {
+            if (edge) go(panel_sddmm_owner_kernel<false, true>); else go(panel_sddmm_owner_kernel<false, false>);
+        }
     }
-    const hipError_t err = hipGetLastError();
+    switch (wave_lc) {
+        case 8: launch_sddmm_long_rows<8, 8>(a, X1, out, scr, windows, xcds, below, compute_units, s); break;
+        case 16: launch_sddmm_long_rows<4, 16>(a, X1, out, scr, windows, xcds, below, compute_units, s); break;
+        case 32: launch_sddmm_long_rows<2, 32>(a, X1, out, scr, windows, xcds, below, compute_units, s); break;
+        default: launch_sddmm_long_rows<1, 64>(a, X1, out, scr, windows, xcds, below, compute_units, s); break;
+    }
+    hipError_t err = hipGetLastError();
     if (err != hipSuccess) return err;
-    return launch_sddmm_skip(a, X1, out, g, per_lane, compute_units, nnz_hint,
-                             RowSkip{&scr.head->count, scr.cap, min_len}, s);
+    const RowSkip skip{&scr.head->count, scr.cap, min_len};
+    const int32_t short_below = min_len < kShortRow ? min_len : kShortRow;
+    {
+        const int members = kBlock / wave_lc;
+        const int rows_per_member = 4;
+        const int64_t blocks = (a.M + (int64_t)members * rows_per_member - 1) / ((int64_t)members * rows_per_member);
+        const int64_t blocks_per_xcd = (blocks + 7) / 8;
+        if (blocks_per_xcd * 8 > 0x7fffffffLL) return hipErrorInvalidValue;
+        const dim3 grid((unsigned)(blocks_per_xcd * 8)), block(kBlock);
+        auto go = [&](auto kernel) {
+            hipLaunchKernelGGL(kernel, grid, block, 0, s, a, X1, out, skip, short_below, rows_per_member, blocks_per_xcd);
+        };
+        switch (wave_lc) {
+            case 8: go(sddmm_short_rows_kernel<8>); break;
+            case 16: go(sddmm_short_rows_kernel<16>); break;
+            case 32: go(sddmm_short_rows_kernel<32>); break;
+            default: go(sddmm_short_rows_kernel<64>); break;
+        }
+    }
+    // what neither has: rows in between, and every row of a matrix with more long rows than the list holds
+    return launch_sddmm_rest(a, X1, out, g, per_lane, compute_units, nnz_hint, skip, short_below, s);
 }
 
 }  // namespace sgap

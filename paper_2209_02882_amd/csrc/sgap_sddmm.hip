@@ -33,7 +33,8 @@ struct SddmmArgs {
     SpmmArgs a;       // M, K, N = J, rowptr, colidx, vals; B = X2T; C unused
     const float* __restrict__ X1;
     float* __restrict__ out;
-    RowSkip skip;     // entries of these rows are left alone (kernels instantiated with SKIP only)
+    RowSkip skip;     // entries of these rows are left alone (kernels instantiated with SKIP only),
+    int32_t from_len; // and of rows shorter than this, while the list of those rows holds
 };
 
 template <int VEC>
@@ -62,12 +63,12 @@ __device__ __forceinline__ Vec<VEC> load_own(const float* __restrict__ row, int6
 // entry through the rowptr window (cut at row boundaries where long runs of
 // empty rows overflow it).  row_lb = a row at or before the tile's first
 // entry.  Block-uniform; the LDS arrays are ready on return.
-// skip_len > 0: entries of rows of at least skip_len stored entries get the
-// one's complement of their row (a negative number) instead.
+// skip_len > 0: entries of rows of at least skip_len or fewer than from_len stored
+// entries get the one's complement of their row (a negative number) instead.
 __device__ __forceinline__ void stage_tile(const SpmmArgs& a, int32_t tile_start, int32_t tile_end, int32_t row_lb,
                                            int32_t* __restrict__ s_col, float* __restrict__ s_val,
                                            int32_t* __restrict__ s_row, int32_t* __restrict__ s_win,
-                                           int32_t skip_len = 0)
+                                           int32_t skip_len = 0, int32_t from_len = 0)
 {
     const int tid = threadIdx.x;
     const int cnt = tile_end - tile_start;
@@ -81,7 +82,8 @@ __device__ __forceinline__ void stage_tile(const SpmmArgs& a, int32_t tile_start
         const RowWindow w = load_row_window(a, row_lb, base, tile_end - base, s_win);
         for (int i = tid; i < w.cnt; i += kBlock) {
             const int32_t wi = last_row_at_or_before(s_win, w.n_first, w.n_last, base + i);
-            const bool skipped = skip_len > 0 && s_win[wi + 1] - s_win[wi] >= skip_len;
+            const int32_t len = s_win[wi + 1] - s_win[wi];
+            const bool skipped = skip_len > 0 && (len >= skip_len || len < from_len);
             s_row[base - tile_start + i] = skipped ? ~(row_lb + wi) : row_lb + wi;
         }
         row_lb += w.n_last;
@@ -115,7 +117,10 @@ __global__ __launch_bounds__(kBlock) void sddmm_kernel(SddmmArgs s, int per_lane
     const int64_t my_tiles = deal.mine;
     if (my_tiles == 0) return;
     int32_t skip_len = 0;
-    if constexpr (SKIP) skip_len = *s.skip.count <= s.skip.max_rows ? s.skip.min_len : 0;
+    if constexpr (SKIP) {
+        skip_len = *s.skip.count <= s.skip.max_rows ? s.skip.min_len : 0;
+        if (skip_len > 0 && s.from_len >= skip_len) return;  // other kernels have every row
+    }
 
     for (int64_t j0 = 0; j0 < my_tiles; j0 += kTileRowBatch) {
         find_tile_rows(a, deal, j0, kSddmmTile, s_tile_row);
@@ -134,7 +139,7 @@ __global__ __launch_bounds__(kBlock) void sddmm_kernel(SddmmArgs s, int per_lane
                     a.rowptr[row_lb + 1] - a.rowptr[row_lb] >= skip_len)
                     continue;
             }
-            stage_tile(a, tile_start, tile_end, row_lb, s_col, s_val, s_row, s_win, skip_len);
+            stage_tile(a, tile_start, tile_end, row_lb, s_col, s_val, s_row, s_win, skip_len, s.from_len);
 
             if (per_lane == 0) {
                 // U entries per group at a time, so that 2*U rows are in flight
@@ -535,6 +540,7 @@ hipError_t launch_sddmm(const SpmmArgs& a, const float* X1, float* out, int g, i
     s.X1 = X1;
     s.out = out;
     s.skip = RowSkip{nullptr, 0, 0};
+    s.from_len = 0;
     bool ok = false;
     if (per_lane > 0) {
         ok = launch_vec<1>(s, vec, per_lane, compute_units, nnz_hint, stream);
@@ -566,16 +572,17 @@ hipError_t launch_sddmm(const SpmmArgs& a, const float* X1, float* out, int g, i
     return hipGetLastError();
 }
 
-// The plain kernel (16-byte loads: J % 4 == 0, aligned operands) with the
-// entries of the rows described by `skip` left alone.
-hipError_t launch_sddmm_skip(const SpmmArgs& a, const float* X1, float* out, int g, int per_lane, int compute_units,
-                             int64_t nnz_hint, const RowSkip& skip, hipStream_t stream)
+// The plain kernel (16-byte loads: J % 4 == 0, aligned operands) on the rows of at least from_len entries
+// that are not described by `skip`; on every row if that list is too long to hold.
+hipError_t launch_sddmm_rest(const SpmmArgs& a, const float* X1, float* out, int g, int per_lane, int compute_units,
+                             int64_t nnz_hint, const RowSkip& skip, int32_t from_len, hipStream_t stream)
 {
     SddmmArgs s;
     s.a = a;
     s.X1 = X1;
     s.out = out;
     s.skip = skip;
+    s.from_len = from_len;
     switch (per_lane > 0 ? 1 : g) {
         case 1: launch_skip<1>(s, per_lane, compute_units, nnz_hint, stream); break;
         case 2: launch_skip<2>(s, per_lane, compute_units, nnz_hint, stream); break;
