@@ -439,9 +439,10 @@ int sgap_mttkrp_csf(int64_t I, int64_t K, int64_t L, int64_t J,
  *                            busy).  parallel: G lanes hold G consecutive
  *                            entries and run two segmented sums, keyed by
  *                            fiber and then, over the fiber sums times their
- *                            rows of X1, by slice.  serial: a lane walks G
- *                            consecutive entries and closes fibers into the
- *                            slice's sum and slices into Y where they end.
+ *                            rows of X1, by slice.  serial: a lane walks
+ *                            consecutive entries, as many as divide a tile
+ *                            evenly over the lanes whatever G is, and closes
+ *                            slices into Y where they end.
  *                            Y is set to zero first and every run's sum is
  *                            added with fp32 atomics: results agree from run
  *                            to run within rounding only.

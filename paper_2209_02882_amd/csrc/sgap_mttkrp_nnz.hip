@@ -9,9 +9,7 @@
 //             members of a group run a segmented sum keyed by fiber; the first lane of every fiber run
 //             multiplies by its chunk of the row of X1; a second segmented sum, keyed by slice, runs over
 //             those products (the other lanes pass +0); the first lane of every slice run adds into Y.
-//   serial    {<g nnz, c col>, 1}: a lane walks G consecutive entries, closes a fiber's sum into the
-//             slice's sum where the fiber (or its share) ends, and adds the slice's sum into Y where the
-//             slice (or its share) ends: the conditional flush, twice.
+// (The serial strategy has a kernel of its own: sgap_mttkrp_serial.hip.)
 // Lane layout as everywhere: thread = (slot*G + member)*LC + chunk.  Several groups may hold parts of one
 // slice, so sums are ADDED into Y (the "Atomics" output strategy of Section 6.2) and Y is set to zero
 // beforehand.  Where the accumulators fit (tile mode of the SpMM kernels' merge rule: one slot per aligned
@@ -49,7 +47,7 @@ __device__ __forceinline__ int run_span(unsigned long long starts, int entry_lan
     return following < room ? following : room;
 }
 
-template <int G, int LC, int VEC, bool PAR, bool MERGE>
+template <int G, int LC, int VEC, bool MERGE>
 __global__ __launch_bounds__(kBlock) void mttkrp_nnz_kernel(MttkrpArgs a, int group, int log2_group)
 {
     extern __shared__ __align__(16) unsigned char s_raw[];
@@ -128,7 +126,7 @@ __global__ __launch_bounds__(kBlock) void mttkrp_nnz_kernel(MttkrpArgs a, int gr
         }
         __syncthreads();
 
-        if constexpr (PAR) {
+        {
             constexpr int ENTRIES_PER_WAVE = kWave / LC;
             constexpr int ENTRIES_PER_STEP = ENTRIES_PER_WAVE * kWavesPerBlock;
             constexpr int STEPS = kMtTile / ENTRIES_PER_STEP;
@@ -197,73 +195,6 @@ __global__ __launch_bounds__(kBlock) void mttkrp_nnz_kernel(MttkrpArgs a, int gr
                     __syncthreads();  // slots are clear again
                 }
             }
-        } else {
-            constexpr int D = 4;  // rows of X2 in flight per lane
-            constexpr int ENTRY_LANES = kBlock / LC;
-            const int entry_lane = tid / LC;
-            const int chunk = tid % LC;
-            for (int64_t k0 = 0; k0 < a.J; k0 += (int64_t)LC * VEC) {
-                const int64_t k = k0 + (int64_t)chunk * VEC;
-                const bool k_ok = k < a.J;
-                const int64_t k_lane = k_ok ? lane_first_col<VEC>(k, a.J) : 0;  // the VEC columns this lane holds
-                for (int blk = entry_lane * group; k_ok && blk < cnt; blk += ENTRY_LANES * group) {
-                    const int end = blk + group < cnt ? blk + group : cnt;
-                    Vec<VEC> fiber_sum, slice_sum;
-                    fiber_sum.zero();
-                    slice_sum.zero();
-                    int run_begin = blk;  // first entry of the slice run that slice_sum belongs to
-                    for (int q0 = blk; q0 < end; q0 += D) {
-                        MtRecord r[D];
-                        Vec<VEC> x2[D], x1[D];
-                        int close[D];  // what ends with entry q0 + u: kMtFirstFiber a fiber's share, kMtFirstSlice a slice's
-#pragma unroll
-                        for (int u = 0; u < D; ++u) {
-                            const int q = q0 + u;
-                            r[u] = s_rec[q < end ? q : blk];
-                            close[u] = q + 1 >= end ? (kMtFirstFiber | kMtFirstSlice) : s_flag[q + 1];
-                            if (q >= end) close[u] = 0;
-                        }
-#pragma unroll
-                        for (int u = 0; u < D; ++u) {
-                            x2[u].zero();
-                            x1[u].zero();
-                            if (q0 + u < end) x2[u] = load_vec<VEC>(a.X2 + (int64_t)r[u].l * a.J + k_lane);
-                            if (close[u] & kMtFirstFiber) x1[u] = load_vec<VEC>(a.X1 + (int64_t)r[u].k * a.J + k_lane);
-                        }
-#pragma unroll
-                        for (int u = 0; u < D; ++u) {
-                            if (q0 + u >= end) continue;
-                            fiber_sum.fma(r[u].val, x2[u]);
-                            if (!(close[u] & kMtFirstFiber)) continue;
-#pragma unroll
-                            for (int v = 0; v < VEC; ++v)
-                                slice_sum.v[v] = __builtin_fmaf(x1[u].v[v], fiber_sum.v[v], slice_sum.v[v]);
-                            fiber_sum.zero();
-                            if (!(close[u] & kMtFirstSlice)) continue;
-                            if constexpr (MERGE) {
-                                // a slice that starts and ends inside this lane's block has no other writer
-                                const bool from_start = (s_flag[run_begin] & kMtFirstSlice) != 0;
-                                if (from_start && q0 + u + 1 < end)
-                                    write_out<LC, VEC>(out, r[u].i, k, true, slice_sum);
-                                else {
-                                    from_last_columns<VEC>(slice_sum, (int)(k - k_lane));
-                                    merge_add<VEC, (LC >= 8)>(mb, s_slot[q0 + u], chunk * VEC, slice_sum,
-                                                              chunk == 0 && (from_start || run_begin == 0), r[u].i, true);
-                                }
-                            } else {
-                                write_out<LC, VEC>(out, r[u].i, k, false, slice_sum);  // the entry's LC chunk lanes together
-                            }
-                            slice_sum.zero();
-                            run_begin = q0 + u + 1;
-                        }
-                    }
-                }
-                if constexpr (MERGE) {
-                    __syncthreads();  // all sums of this pass are in LDS
-                    merge_write_out<LC, VEC>(out, mb, k, k_ok);
-                    __syncthreads();  // slots are clear again
-                }
-            }
         }
     }
 }
@@ -275,11 +206,11 @@ struct LaunchMttkrpNnz {
     int group, compute_units;
     int64_t nnz_hint;
     hipStream_t s;
-    template <int G, int LC, int VEC, bool PAR, bool MERGE>
+    template <int G, int LC, int VEC, bool MERGE>
     void launch(int smem, int log2_group) const
     {
         int per_cu = 0;
-        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, mttkrp_nnz_kernel<G, LC, VEC, PAR, MERGE>, kBlock,
+        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, mttkrp_nnz_kernel<G, LC, VEC, MERGE>, kBlock,
                                                          smem) != hipSuccess || per_cu < 1)
             per_cu = 1;
         int64_t grid = (int64_t)per_cu * compute_units;
@@ -287,11 +218,11 @@ struct LaunchMttkrpNnz {
             const int64_t tiles = (nnz_hint + kMtTile - 1) / kMtTile;
             if (tiles < grid) grid = tiles > 0 ? tiles : 1;
         }
-        hipLaunchKernelGGL((mttkrp_nnz_kernel<G, LC, VEC, PAR, MERGE>), dim3((unsigned)grid), dim3(kBlock), smem, s, a,
+        hipLaunchKernelGGL((mttkrp_nnz_kernel<G, LC, VEC, MERGE>), dim3((unsigned)grid), dim3(kBlock), smem, s, a,
                            group, log2_group);
     }
-    template <int G, int LC, int VEC, bool PAR>
-    void go() const
+    template <int G, int LC, int VEC>
+    void operator()() const
     {
         int log2_group = 0;
         while ((1 << log2_group) < group) ++log2_group;
@@ -302,24 +233,15 @@ struct LaunchMttkrpNnz {
         if (smem <= kMost) {
             if (smem > 48 * 1024) {
                 static const hipError_t asked = hipFuncSetAttribute(
-                    reinterpret_cast<const void*>(mttkrp_nnz_kernel<G, LC, VEC, PAR, true>),
+                    reinterpret_cast<const void*>(mttkrp_nnz_kernel<G, LC, VEC, true>),
                     hipFuncAttributeMaxDynamicSharedMemorySize, kMost);
                 (void)asked;
             }
-            launch<G, LC, VEC, PAR, true>(smem, log2_group);
+            launch<G, LC, VEC, true>(smem, log2_group);
         } else {
-            launch<G, LC, VEC, PAR, false>(0, log2_group);
+            launch<G, LC, VEC, false>(0, log2_group);
         }
     }
-};
-
-struct LaunchMttkrpNnzPar : LaunchMttkrpNnz {
-    template <int G, int LC, int VEC>
-    void operator()() const { go<G, LC, VEC, true>(); }
-};
-struct LaunchMttkrpNnzSer : LaunchMttkrpNnz {
-    template <int G, int LC, int VEC>
-    void operator()() const { go<G, LC, VEC, false>(); }
 };
 
 }  // namespace
@@ -327,9 +249,8 @@ struct LaunchMttkrpNnzSer : LaunchMttkrpNnz {
 hipError_t launch_mttkrp_nnz(const MttkrpArgs& a, int g, bool parallel, int lc, int vec, int compute_units,
                              int64_t nnz_hint, hipStream_t s)
 {
-    bool ok;
-    if (parallel) ok = dispatch_group(g, lc, vec, LaunchMttkrpNnzPar{{a, g, compute_units, nnz_hint, s}});
-    else ok = dispatch_group(1, lc, vec, LaunchMttkrpNnzSer{{a, g, compute_units, nnz_hint, s}});
+    if (!parallel) return launch_mttkrp_serial(a, lc, vec, compute_units, nnz_hint, s);
+    const bool ok = dispatch_group(g, lc, vec, LaunchMttkrpNnz{a, g, compute_units, nnz_hint, s});
     if (!ok) return hipErrorInvalidValue;
     return hipGetLastError();
 }
