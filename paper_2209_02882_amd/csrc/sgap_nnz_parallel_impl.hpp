@@ -34,57 +34,60 @@ constexpr int kMetaPlain = 1 << 12;      // direct mode: row lies inside one ali
 constexpr int kMetaSlotShift = 16;       // tile mode: LDS accumulator slot of the row
 
 constexpr int kParEpt = kParTile / kBlock;     // stored entries per thread held in registers between tiles
+static_assert(kParEpt == 4, "a thread's entries come with one 16-byte load each of columns and values");
 constexpr int kParWpt = kWindowCap / kBlock + 1;
+typedef int32_t native_i4 __attribute__((ext_vector_type(4), aligned(4)));
 // LDS merge through the hardware's fp32 atomic: the run heads of one row meet on
 // one address within a wavefront (measured against the compare-and-swap loop:
 // rmat N=4 G=16 0.47 vs 0.62 ms, powerlaw 0.135 vs 0.162 ms)
 constexpr bool kParMergeCas = false;
 constexpr int kParDepth = 4;                   // steps issued together
 
-// Build the LDS records of the chunk [base, end) of the tile that starts at
-// tile_start from the entries a thread holds in registers (thread t holds
-// positions tile_start + t + i*kBlock).  LDS slot s holds position
-// tile_start + s; slots outside the chunk are marked invalid.  The rows of the
-// chunk are s_win[w.n_first .. w.n_last + 1] relative to row_lb, or, when s_row is
-// given (a window of the rows with entries only), the rows s_row[wi]; s_row may
-// then lie inside s_tile: every thread has read its rows before any record is
-// written (a barrier in between, so the call is block-uniform in that case).
+// Build the LDS records of the tile [tile_start, end) from the entries a thread holds in registers: thread t holds the
+// kParEpt consecutive positions from tile_start + t * kParEpt on.  LDS slot s holds position tile_start + s; slots
+// behind the tile's last entry are marked invalid.  The rows with entries of the tile are s_row[wi], wi < n, and start
+// at s_win[wi] (s_win[n]: where the last one ends); a thread bisects them for its first position and steps along for
+// the others (a bisection of all row pointers for every entry was half of the kernel's vector instructions).  s_row may
+// lie inside s_tile: every thread has read its rows before any record is written.  Block-uniform; a barrier inside.
 __device__ __forceinline__ void build_records(const int32_t (&col)[kParEpt], const float (&val)[kParEpt],
-                                              int32_t tile_start, int32_t base, int32_t end, const RowWindow& w,
-                                              int32_t row_lb, int log2_group, int nslots,
-                                              const int32_t* __restrict__ s_win, TileEntry* s_tile,
-                                              const int32_t* s_row = nullptr)
+                                              int32_t tile_start, int32_t end, int32_t n, int log2_group, int nslots,
+                                              const int32_t* __restrict__ s_win, TileEntry* s_tile, const int32_t* s_row)
 {
     TileEntry rec[kParEpt];
+    const int q0 = threadIdx.x * kParEpt;
+    int32_t wi = last_row_at_or_before(s_win, 0, n - 1, tile_start + q0);
+    int32_t p_begin = s_win[wi], p_end = s_win[wi + 1], row = s_row[wi];
 #pragma unroll
     for (int i = 0; i < kParEpt; ++i) {
-        const int q = threadIdx.x + i * kBlock;
-        const int32_t p = tile_start + q;
+        const int32_t p = tile_start + q0 + i;
         TileEntry e;
         e.col = 0; e.val = 0.0f; e.row = 0; e.meta = 0;
-        if (p >= base && p < end) {
-            const int32_t wi = last_row_at_or_before(s_win, w.n_first, w.n_last, p);
-            const int32_t p_begin = s_win[wi];
-            const int32_t p_end = s_win[wi + 1];
+        if (p < end) {
+            if (p >= p_end) {  // the next row (every row of the window has entries)
+                ++wi;
+                p_begin = p_end;
+                p_end = s_win[wi + 1];
+                row = s_row[wi];
+            }
             const int32_t left = p_end - 1 - p;
             int32_t meta = kMetaValid | (left < kMetaLeftMask ? left : kMetaLeftMask);
             if (p == p_begin) meta |= kMetaRowStart;
-            if (p == base) meta |= kMetaChunkStart;
-            if (p == (p_begin > base ? p_begin : base)) meta |= kMetaOwner;
-            if (p_begin < base || p_end > end) meta |= kMetaOutside;
+            if (p == tile_start) meta |= kMetaChunkStart;
+            if (p == (p_begin > tile_start ? p_begin : tile_start)) meta |= kMetaOwner;
+            if (p_begin < tile_start || p_end > end) meta |= kMetaOutside;
             if ((p_begin >> log2_group) == ((p_end - 1) >> log2_group)) meta |= kMetaPlain;
-            const int32_t slot = p_begin < base ? nslots - 1 : (p_begin - tile_start) >> log2_group;
+            const int32_t slot = p_begin < tile_start ? nslots - 1 : (p_begin - tile_start) >> log2_group;
             meta |= slot << kMetaSlotShift;
             e.col = col[i];
             e.val = val[i];
-            e.row = s_row ? s_row[wi] : row_lb + wi;
+            e.row = row;
             e.meta = meta;
         }
         rec[i] = e;
     }
-    if (s_row) __syncthreads();
+    __syncthreads();
 #pragma unroll
-    for (int i = 0; i < kParEpt; ++i) s_tile[threadIdx.x + i * kBlock] = rec[i];
+    for (int i = 0; i < kParEpt; ++i) s_tile[q0 + i] = rec[i];
 }
 
 // Multiply out the records staged in s_tile: a lane multiplies ONE stored
@@ -196,15 +199,24 @@ __global__ __launch_bounds__(kBlock) void nnz_parallel_kernel(SpmmArgs a)
     float nx_val[kParEpt];
     int32_t nx_win[kParWpt];
     auto fetch_tile = [&](int64_t t, int32_t row_lb) {
-        const int32_t start = (int32_t)(t * kParTile);
+        const int32_t start = (int32_t)(t * kParTile) + tid * kParEpt;
 #pragma unroll
         for (int i = 0; i < kParEpt; ++i) {
-            const int32_t p = start + tid + i * kBlock;
             nx_col[i] = 0;
             nx_val[i] = 0.0f;
-            if (p < nnz) {
-                nx_col[i] = load_stream(a.colidx + p);
-                nx_val[i] = load_stream(a.vals + p);
+        }
+        if (start + kParEpt <= nnz) {
+            const native_i4 c = __builtin_nontemporal_load(reinterpret_cast<const native_i4*>(a.colidx + start));
+            const native_f4 v = __builtin_nontemporal_load(reinterpret_cast<const native_f4*>(a.vals + start));
+            nx_col[0] = c.x; nx_col[1] = c.y; nx_col[2] = c.z; nx_col[3] = c.w;
+            nx_val[0] = v.x; nx_val[1] = v.y; nx_val[2] = v.z; nx_val[3] = v.w;
+        } else {
+#pragma unroll
+            for (int i = 0; i < kParEpt; ++i) {
+                if (start + i < nnz) {
+                    nx_col[i] = load_stream(a.colidx + start + i);
+                    nx_val[i] = load_stream(a.vals + start + i);
+                }
             }
         }
 #pragma unroll
@@ -232,34 +244,21 @@ __global__ __launch_bounds__(kBlock) void nnz_parallel_kernel(SpmmArgs a)
                 if (tid + i * kBlock <= kWindowCap) s_win[tid + i * kBlock] = nx_win[i];
             __syncthreads();
 
+            // The tile's rows with entries, staged in the record area, which is free until build_records fills it (no
+            // static LDS to spare beside the largest merge slots).  One piece whatever the runs of rows without entries.
+            int32_t* s_row = reinterpret_cast<int32_t*>(s_tile);
+            int32_t n;
             if (s_win[kWindowCap] >= tile_end) {
-                // the window covers every row of the tile: one chunk
-                RowWindow w;
-                w.cnt = tile_end - tile_start;
-                w.n_first = first_above(s_win, kWindowCap + 1, tile_start) - 1;
-                w.n_last = first_above(s_win, kWindowCap + 1, tile_end - 1) - 1;
-                build_records(nx_col, nx_val, tile_start, tile_start, tile_end, w, row_lb, a.log2_group, mb.nslots,
-                              s_win, s_tile);
-                __syncthreads();
-                // start bringing in the next tile of this batch
-                if (j + 1 < j1) fetch_tile(deal.tile(j + 1), s_tile_row[j + 1 - j0]);
-                parallel_chunk<G, LC, VEC, OFF32, MERGE, RAGGED>(a, mb, s_tile);
+                n = compact_window(s_win, s_row, row_lb, tile_end, s_scan);
             } else {
-                // long runs of rows without entries: a window of the rows with entries only, so that the tile
-                // still goes in one piece (sgap_nnz_common.hpp).  The rows are staged in the record area, which is
-                // free until build_records fills it (no static LDS to spare beside the largest merge slots).
-                int32_t* s_row = reinterpret_cast<int32_t*>(s_tile);
                 __syncthreads();  // everyone has read the plain window
-                RowWindow w;
-                w.cnt = tile_end - tile_start;
-                w.n_first = 0;
-                w.n_last = load_compact_window(a, row_lb, tile_end, s_win, s_row, s_scan) - 1;
-                build_records(nx_col, nx_val, tile_start, tile_start, tile_end, w, 0, a.log2_group, mb.nslots, s_win,
-                              s_tile, s_row);
-                __syncthreads();
-                if (j + 1 < j1) fetch_tile(deal.tile(j + 1), s_tile_row[j + 1 - j0]);
-                parallel_chunk<G, LC, VEC, OFF32, MERGE, RAGGED>(a, mb, s_tile);
+                n = load_compact_window(a, row_lb, tile_end, s_win, s_row, s_scan);
             }
+            build_records(nx_col, nx_val, tile_start, tile_end, n, a.log2_group, mb.nslots, s_win, s_tile, s_row);
+            __syncthreads();
+            // start bringing in the next tile of this batch
+            if (j + 1 < j1) fetch_tile(deal.tile(j + 1), s_tile_row[j + 1 - j0]);
+            parallel_chunk<G, LC, VEC, OFF32, MERGE, RAGGED>(a, mb, s_tile);
         }
     }
 }
