@@ -9,24 +9,37 @@ namespace sgap {
 // Rows that will receive global atomic adds (their positions straddle an
 // aligned merge block of 2^merge_log2 positions) and rows without stored
 // entries are set to +0; merge_log2 < 0: every row is.
-// thread = (row_lane, chunk); chunk lanes stride over the row's columns.
+// A lane looks at one row (the row pointers are read once, in order), and the wavefront then clears the rows that
+// want it, lcz lanes to a row.  A wavefront has rows_per_wave rows: 64, or eight where that leaves the chip idle.  Bound by
+// the writes: R-MAT with 2^21 rows of which 922,500 have no entries, N = 32: 33 us
+// with eight lanes looking at every row.
 template <int VEC>
-__global__ __launch_bounds__(kBlock) void zero_rows_kernel(SpmmArgs a, int lcz, int merge_log2)
+__global__ __launch_bounds__(kBlock) void zero_rows_kernel(SpmmArgs a, int log2_lcz, int merge_log2, int rows_per_wave)
 {
-    const int chunk = threadIdx.x % lcz;
-    const int row_lane = threadIdx.x / lcz;
-    const int rows_per_block = kBlock / lcz;
-    const int64_t row = (int64_t)blockIdx.x * rows_per_block + row_lane;
-    if (row >= a.M) return;
-    const int32_t p_begin = a.rowptr[row];
-    const int32_t p_end = a.rowptr[row + 1];
-    const bool plain = merge_log2 >= 0 && p_end > p_begin && (p_begin >> merge_log2) == ((p_end - 1) >> merge_log2);
-    if (plain) return;
+    __shared__ uint8_t s_list[kWavesPerBlock][kWave];
+    const int lane = threadIdx.x % kWave;
+    uint8_t* list = s_list[threadIdx.x / kWave];
+    const int64_t row0 = ((int64_t)blockIdx.x * kWavesPerBlock + threadIdx.x / kWave) * rows_per_wave;
+    const int64_t row = row0 + lane;
+    bool wanted = lane < rows_per_wave && row < a.M;
+    if (wanted && merge_log2 >= 0) {
+        const int32_t p_begin = a.rowptr[row];
+        const int32_t p_end = a.rowptr[row + 1];
+        wanted = !(p_end > p_begin && (p_begin >> merge_log2) == ((p_end - 1) >> merge_log2));
+    }
+    const unsigned long long mask = __ballot(wanted);
+    if (mask == 0) return;
+    if (wanted) list[__popcll(mask & ((1ull << lane) - 1ull))] = (uint8_t)lane;
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    const int n = __popcll(mask);
+    const int chunk = lane & ((1 << log2_lcz) - 1);
     Vec<VEC> z;
     z.zero();
-    float* __restrict__ dst = a.C + row * a.N;
-    for (int64_t k = (int64_t)chunk * VEC; k < a.N; k += (int64_t)lcz * VEC)
-        store_vec<VEC>(dst + lane_first_col<VEC>(k, a.N), z);
+    for (int i = lane >> log2_lcz; i < n; i += kWave >> log2_lcz) {
+        float* __restrict__ dst = a.C + (row0 + list[i]) * a.N;
+        for (int64_t k = (int64_t)chunk * VEC; k < a.N; k += (int64_t)VEC << log2_lcz)
+            store_vec<VEC>(dst + lane_first_col<VEC>(k, a.N), z);
+    }
 }
 
 NnzPlan plan_nnz_parallel(int group, int lc, int vec)
@@ -78,15 +91,16 @@ hipError_t launch_nnz_parallel(const SpmmArgs& a, int lc, int vec, int compute_u
 
 hipError_t launch_nnz_zero_rows(const SpmmArgs& a, int vec, int merge_log2, hipStream_t s)
 {
-    int64_t chunks = (a.N + vec - 1) / vec;
-    int lcz = 1;
-    while (lcz < 64 && lcz < chunks) lcz *= 2;
-    const int rows_per_block = kBlock / lcz;
-    const int64_t grid = (a.M + rows_per_block - 1) / rows_per_block;
+    const int64_t chunks = (a.N + vec - 1) / vec;
+    int log2_lcz = 0;
+    while (log2_lcz < 6 && (1 << log2_lcz) < chunks) ++log2_lcz;
+    const int rows_per_wave = a.M < (1 << 17) && log2_lcz >= 2 ? 8 : kWave;  // (2^17 rows: two workgroups per compute unit)
+    const int64_t rows_per_block = (int64_t)kWavesPerBlock * rows_per_wave;
+    const dim3 grid((unsigned)((a.M + rows_per_block - 1) / rows_per_block)), block(kBlock);
     switch (vec) {
-        case 4: hipLaunchKernelGGL((zero_rows_kernel<4>), dim3((unsigned)grid), dim3(kBlock), 0, s, a, lcz, merge_log2); break;
-        case 2: hipLaunchKernelGGL((zero_rows_kernel<2>), dim3((unsigned)grid), dim3(kBlock), 0, s, a, lcz, merge_log2); break;
-        case 1: hipLaunchKernelGGL((zero_rows_kernel<1>), dim3((unsigned)grid), dim3(kBlock), 0, s, a, lcz, merge_log2); break;
+        case 4: hipLaunchKernelGGL((zero_rows_kernel<4>), grid, block, 0, s, a, log2_lcz, merge_log2, rows_per_wave); break;
+        case 2: hipLaunchKernelGGL((zero_rows_kernel<2>), grid, block, 0, s, a, log2_lcz, merge_log2, rows_per_wave); break;
+        case 1: hipLaunchKernelGGL((zero_rows_kernel<1>), grid, block, 0, s, a, log2_lcz, merge_log2, rows_per_wave); break;
         default: return hipErrorInvalidValue;
     }
     return hipGetLastError();
