@@ -206,11 +206,14 @@ inline bool offsets_fit_32(const SpmmArgs& a)
 // block the zeroing pass must assume (tile in tile mode, group otherwise),
 // lc = chunk lanes per stored entry the kernel is to run with (the plan may
 // narrow the layout it was asked about so that the accumulators fit the LDS).
+// share = consecutive entries a lane walks (the serial strategy: the group size, or less where the tile has no more for
+// a lane).
 struct NnzPlan {
     int tile;
     bool merge;
     int merge_log2;
     int lc;
+    int share;
 };
 NnzPlan plan_nnz_serial(int group, int lc, int vec, int64_t nnz_hint, int compute_units, int forced_tile);
 NnzPlan plan_nnz_parallel(int group, int lc, int vec);

@@ -51,6 +51,7 @@ NnzPlan plan_nnz_parallel(int group, int lc, int vec)
     const int nslots = p.tile / group + 1;
     p.merge = nslots * (lc * vec * 4 + 8) <= kMergeLdsBudget;
     p.lc = lc;
+    p.share = group;
     // Most of the LDS, and if need be narrower passes: for G = 1 (else a global atomic add per stored entry:
     // stencil27 32 ms against 20 ms, rmat 43 against 10) and for narrow passes (rmat, N = 32, G = 2 and 4:
     // 23 and 10 ms against 6.0 and 3.4).  Wider passes of G >= 2 do better with their few global atomics per

@@ -19,16 +19,14 @@ NnzPlan plan_nnz_serial(int group, int lc, int vec, int64_t nnz_hint, int comput
     // tile size by the share of the chip that is busy over the rounds of
     // tiles, the last of which is only partly filled, and take the largest
     // tile that keeps 85 % busy, else the best one.
-    // No tile below half a step of the workgroup (a step gives every entry lane
-    // `group` positions; below half a step most lanes idle, which costs more
-    // than it gains: powerlaw at N=16, G=32: 0.069 against 0.032 ms), nor below 256.
-    const int step = (kBlock / lc) * group;
-    const int min_tile = step / 2 >= p.tile ? p.tile : (step / 2 > 256 ? step / 2 : 256);
+    // A tile of fewer positions than a step of the workgroup (every entry lane `group` positions) is divided evenly:
+    // a lane's share is then smaller than the group size, but never below eight entries (one batch of loads), nor the
+    // tile below 256.
+    const int lanes_share = 8 * (kBlock / lc);
+    const int min_tile = lanes_share > p.tile ? p.tile : lanes_share > 256 ? lanes_share : 256;
     if (forced_tile >= 1024 || (forced_tile > 0 && vec == 4)) {
         p.tile = forced_tile;
-    } else if (nnz_hint > 0 && vec == 4 && lc >= 8) {
-        // (narrower passes do too little per entry to pay for more, smaller tiles:
-        // powerlaw at N=16 runs 0.032 ms with the full tile, 0.044 ms with the balanced one)
+    } else if (nnz_hint > 0 && vec == 4) {
         const double resident = 4.0 * compute_units;
         int best_tile = p.tile;
         double best_busy = 0.0;
@@ -66,8 +64,10 @@ NnzPlan plan_nnz_serial(int group, int lc, int vec, int64_t nnz_hint, int comput
             p.merge = true;
         }
     }
+    const int most = p.tile / (kBlock / p.lc) > 1 ? p.tile / (kBlock / p.lc) : 1;
+    p.share = group < most ? group : most;
     int lg = 0;
-    while ((1 << lg) < (p.merge ? p.tile : group)) ++lg;
+    while ((1 << lg) < (p.merge ? p.tile : p.share)) ++lg;
     p.merge_log2 = lg;
     return p;
 }

@@ -22,6 +22,10 @@
 
 namespace sgap {
 
+// LDS place of the tile's entry number q: the entry lanes of a wavefront read at strides of `group` entries, a power of
+// two, and without the gaps would meet on a few of the banks (R-MAT, G = 32: half of the LDS cycles were conflicts).
+__host__ __device__ constexpr int staged_place(int q) { return q + (q >> 5); }
+
 // Multiply out the chunk [base, end) of the tile staged in s_A (slot s holds
 // position tile_start + s), whose rows are s_win[w.n_first .. w.n_last + 1]
 // relative to row_lb: window index wi stands for row row_lb + wi, or, when
@@ -71,10 +75,12 @@ __device__ __forceinline__ void serial_chunk(const SpmmArgs& a, const MergeBuf& 
             for (int32_t p0 = blk_begin; p0 < blk_end; p0 += kDepth) {
                 StagedEntry e[kDepth];
                 Vec<VEC> b[kDepth];
+                // (a batch starts at a multiple of eight, or is a share of fewer: no gap inside it)
+                const StagedEntry* __restrict__ here = s_A + staged_place(p0 - tile_start);
                 if (p0 + kDepth < row_end && p0 + kDepth < blk_end) {
                     // no row or block ends inside this batch: nothing to decide per entry
 #pragma unroll
-                    for (int u = 0; u < kDepth; ++u) e[u] = s_A[p0 + u - tile_start];
+                    for (int u = 0; u < kDepth; ++u) e[u] = here[u];
 #pragma unroll
                     for (int u = 0; u < kDepth; ++u) b[u] = load_vec<VEC>(Brow.at(e[u].col));
 #pragma unroll
@@ -85,7 +91,7 @@ __device__ __forceinline__ void serial_chunk(const SpmmArgs& a, const MergeBuf& 
                 for (int u = 0; u < kDepth; ++u) {
                     e[u].col = 0;
                     e[u].val = 0.0f;
-                    if (p0 + u < blk_end) e[u] = s_A[p0 + u - tile_start];
+                    if (p0 + u < blk_end) e[u] = here[u];
                 }
 #pragma unroll
                 for (int u = 0; u < kDepth; ++u) {
@@ -157,11 +163,12 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
     __shared__ int32_t s_tile_row[kTileRowBatch];
     constexpr int WIDTH = LC * VEC;
 
+    constexpr int PLACES = staged_place(TILE);
     StagedEntry* s_A = reinterpret_cast<StagedEntry*>(s_raw);
     MergeBuf mb;
     mb.nslots = TILE / a.group + 1;
     mb.width = WIDTH;
-    mb.accum = reinterpret_cast<float*>(s_raw + (size_t)TILE * sizeof(StagedEntry));
+    mb.accum = reinterpret_cast<float*>(s_raw + (size_t)PLACES * sizeof(StagedEntry));
     mb.slot_row = reinterpret_cast<int32_t*>(mb.accum + (MERGE ? mb.nslots * WIDTH : 0));
     mb.slot_atomic = mb.slot_row + mb.nslots;
 
@@ -171,6 +178,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
     const TileDeal deal(tiles, blockIdx.x, gridDim.x);
     const int64_t my_tiles = deal.mine;
     if (my_tiles == 0) return;
+    TileWalk ahead(deal);  // the tile that is fetched next
     const int tid = threadIdx.x;
 
     if constexpr (MERGE) merge_reset(mb);  // made visible by the barriers below
@@ -179,8 +187,8 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
     int32_t nx_col[EPT];
     float nx_val[EPT];
     int32_t nx_win[WPT];
-    auto fetch_tile = [&](int64_t t, int32_t row_lb) {
-        const int32_t start = (int32_t)(t * TILE);
+    auto fetch_tile = [&](int32_t row_lb) {  // the tile `ahead` stands at
+        const int32_t start = (int32_t)(ahead.tile() * TILE);
 #pragma unroll
         for (int i = 0; i < EPT; ++i) {
             const int32_t p = start + tid + i * kBlock;
@@ -202,11 +210,11 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
     for (int64_t j0 = 0; j0 < my_tiles; j0 += kTileRowBatch) {
         find_tile_rows(a, deal, j0, TILE, s_tile_row);
         const int64_t j1 = j0 + kTileRowBatch < my_tiles ? j0 + kTileRowBatch : my_tiles;
-        fetch_tile(deal.tile(j0), s_tile_row[0]);
+        fetch_tile(s_tile_row[0]);
 
         for (int64_t j = j0; j < j1; ++j) {
-            const int64_t t = deal.tile(j);
-            const int32_t tile_start = (int32_t)(t * TILE);
+            const int32_t tile_start = (int32_t)(ahead.tile() * TILE);
+            ahead.next();
             const int32_t tile_end = nnz - tile_start < TILE ? nnz : tile_start + TILE;
             int32_t row_lb = s_tile_row[j - j0];
 
@@ -216,14 +224,14 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
                 StagedEntry e;
                 e.col = nx_col[i];
                 e.val = nx_val[i];
-                s_A[tid + i * kBlock] = e;
+                s_A[staged_place(tid + i * kBlock)] = e;
             }
 #pragma unroll
             for (int i = 0; i < WPT; ++i)
                 if (tid + i * kBlock <= kWindowCap) s_win[tid + i * kBlock] = nx_win[i];
             __syncthreads();
             // start bringing in the next tile of this batch
-            if (j + 1 < j1) fetch_tile(deal.tile(j + 1), s_tile_row[j + 1 - j0]);
+            if (j + 1 < j1) fetch_tile(s_tile_row[j + 1 - j0]);
 
             // The rows WITH entries of the tile, their first positions in s_win and their numbers in s_row: rows
             // without entries (44 % of the rows of an R-MAT matrix, in runs of 3.5 on average) would cost a search
@@ -270,7 +278,7 @@ struct Launch {
     void go() const
     {
         const int nslots = tile / a.group + 1;
-        const int smem = tile * (int)sizeof(StagedEntry) + (MERGE ? nslots * (LC * VEC * 4 + 8) : 0);
+        const int smem = staged_place(tile) * (int)sizeof(StagedEntry) + (MERGE ? nslots * (LC * VEC * 4 + 8) : 0);
         static int cached[7];  // [log2 group] resident workgroups per CU of this instance, 0 = not asked yet
         int& per_cu = cached[a.log2_group];
         static int asked = 0;  // most dynamic LDS this instance has been allowed so far
