@@ -72,21 +72,13 @@ __device__ __forceinline__ void gather_tail(Vec<VEC>& acc, const StagedEntry* __
     for (int j = 0; j < U; ++j) acc.fma(e[j].val, b[j]);
 }
 
-// Gathered rows of B a lane keeps in flight.  Six, not eight: the row-split
-// kernel then needs 78 instead of 90 vector registers and a SIMD holds six
-// wavefronts instead of five, which is worth more on the 27-entry rows of the
-// stencil workload (0.66 -> 0.615 ms) than the deeper batch.
-constexpr int kGatherDepth = 6;
-
 // acc += sum over LDS slots q = q0, q0+STRIDE, ... < q1 of val[q] * B[col[q], k..k+VEC)
-// Full batches of kGatherDepth, then the remaining entries as one more round
-// of predicated loads, so that a row costs ceil(len/kGatherDepth) memory round
-// trips.
-template <int VEC, int STRIDE, typename SRC>
+// Full batches of D, then the remaining entries as one more round of predicated loads, so that a row costs
+// ceil(len/D) memory round trips.
+template <int VEC, int STRIDE, int D, typename SRC>
 __device__ __forceinline__ void gather_fma(Vec<VEC>& acc, const StagedEntry* __restrict__ s_A, uint32_t q0,
                                            uint32_t q1, const SRC& B)
 {
-    constexpr int D = kGatherDepth;
     uint32_t q = q0;
     for (; q + (D - 1) * STRIDE < q1; q += D * STRIDE) gather_batch<VEC, STRIDE, D>(acc, s_A, q, B);
     if (q >= q1) return;

@@ -32,6 +32,7 @@
 
 namespace sgap {
 
+constexpr int kMttkrpStagedDepth = 6;  // ... when they come from LDS
 constexpr int kMttkrpDepth = 4;  // gathered rows of X2 in flight per lane when entries come straight from memory
 
 // LDS copies of a block of slices: its slice pointers, its fibers (second index
@@ -188,7 +189,7 @@ __global__ __launch_bounds__(kBlock) void mttkrp_kernel(MttkrpArgs a, int rows_p
                     if (k_ok) {
                         x1 = load_vec<VEC>(a.X1 + (int64_t)s_fk[f] * a.J + k_lane);
                         const uint32_t q0 = (uint32_t)(s_ep[f] - e0), q1 = (uint32_t)(s_ep[f + 1] - e0);
-                        if (q0 < q1) gather_fma<VEC, 1>(t, s_A, q0, q1, x2rows);
+                        if (q0 < q1) gather_fma<VEC, 1, kMttkrpStagedDepth>(t, s_A, q0, q1, x2rows);
                     }
 #pragma unroll
                     for (int i = 0; i < VEC; ++i) acc.v[i] = __builtin_fmaf(x1.v[i], t.v[i], acc.v[i]);

@@ -8,21 +8,30 @@
 
 namespace sgap {
 
+// Rows of B a lane keeps in flight, chosen with the columns' layout (DEPTH of the kernel):
+//   6  one lane per row: 70 vector registers, seven wavefronts per SIMD (stencil27, N = 128: 593 us; with eight in flight
+//      and five wavefronts 641, with four 619);
+//   4  one lane per row and rows of a dozen entries or fewer: more wavefronts beat deeper batches that are mostly masked
+//      (fibers of 1 to 16 entries, 32 columns, two rows per lane: 231 us, 234 with six, 262 with eight);
+//   8  several lanes per row: few wavefronts have long rows left, and those are done the sooner (power law, N = 37, G = 16:
+//      77 us with six, 73 with eight).
+constexpr int kDepthRows = 6, kDepthShort = 4, kDepthGroups = 8;
+constexpr double kShortRowMean = 12.0;
 constexpr int kStageCap = 2048;  // (column, value) pairs per LDS chunk: 16 KB
 constexpr int kRowCap = 1024;    // rowptr entries kept in LDS per row block (+1)
 constexpr int kShareMin = 256;   // the shortest row that a whole workgroup takes together
 constexpr int kRowSplitMaxBlock = 512;  // threads per workgroup: 128, 256 or 512, chosen at launch
 
 // One row by the whole workgroup: lc chunk lanes (the power of two that covers the columns, at most a wavefront) and
-// block / lc members, each of which takes every (block / lc)-th stored entry with kGatherDepth rows of B in flight; members
+// block / lc members, each of which takes every (block / lc)-th stored entry with DEPTH rows of B in flight; members
 // of a wavefront are summed with shuffles, the wavefronts' sums through LDS in a fixed order, and the row has one
 // plain store as ever.  For the rows whose length would keep the one group that owns them busy long after the rest of
 // the chip is done (see share_rows_from).  s_A and s_part may be the same memory.  Block-uniform; barriers inside.
-template <int VEC, bool OFF32>
+template <int VEC, bool OFF32, int DEPTH>
 __device__ __forceinline__ void shared_row(const SpmmArgs& a, int64_t row, uint32_t p_begin, uint32_t p_end,
                                            int64_t k_begin, int64_t k_end, StagedEntry* __restrict__ s_A, int block)
 {
-    constexpr int D = kGatherDepth;
+    constexpr int D = DEPTH;
     const int64_t N = a.N;
     int lc = 1;
     while (lc < kWave && (int64_t)lc * VEC < k_end - k_begin) lc *= 2;
@@ -90,7 +99,7 @@ __device__ __forceinline__ void shared_row(const SpmmArgs& a, int64_t row, uint3
 // produced by the whole workgroup afterwards (shared_row).
 // The workgroup size (the paper's blockSz, Section 7.2) is the launch's: SLOTS = blockDim.x / (G*LC)
 // groups work side by side on the rows of a row block.
-template <int G, int LC, int VEC, bool OFF32, bool PARTIAL, bool SKIP = false>
+template <int G, int LC, int VEC, bool OFF32, bool PARTIAL, bool SKIP, int DEPTH>
 __global__ __launch_bounds__(kRowSplitMaxBlock) void row_split_kernel(SpmmArgs a, TileSched ts, int rows_per_slot,
                                                                       int interleave, int reduce_members,
                                                                       int32_t share_from, RowSkip skip)
@@ -202,7 +211,7 @@ __global__ __launch_bounds__(kRowSplitMaxBlock) void row_split_kernel(SpmmArgs a
                     if (!skipped && k_ok && lo < hi) {
                         // first position >= lo that belongs to this member
                         const uint32_t first = lo + ((member - (lo - p_begin)) & (G - 1));
-                        if (first < hi) gather_fma<VEC, G>(acc, s_A, first - base, hi - base, Brow);
+                        if (first < hi) gather_fma<VEC, G, DEPTH>(acc, s_A, first - base, hi - base, Brow);
                     }
                     if (p_end > base + cnt) break;  // the row continues in the next chunk
                     // members without entries contributed +0 (zero extension);
@@ -255,7 +264,7 @@ __global__ __launch_bounds__(kRowSplitMaxBlock) void row_split_kernel(SpmmArgs a
                 const int n = s_shared_n;  // written before the barriers of the walk
                 for (int i = 0; i < n; ++i) {
                     const int row = __builtin_amdgcn_readfirstlane(s_shared[i]);
-                    shared_row<VEC, OFF32>(a, row_first + row, (uint32_t)__builtin_amdgcn_readfirstlane(s_rp[row]),
+                    shared_row<VEC, OFF32, DEPTH>(a, row_first + row, (uint32_t)__builtin_amdgcn_readfirstlane(s_rp[row]),
                                            (uint32_t)__builtin_amdgcn_readfirstlane(s_rp[row + 1]),
                                            (int64_t)col_tile * ts.tile_cols, k_tile_end, s_A, block);
                 }
@@ -274,6 +283,7 @@ struct Launch {
     int reduce_members;
     int block;  // threads per workgroup: 128, 256 or 512 (at least G*LC)
     hipStream_t s;
+    bool short_rows;  // rows of kShortRowMean entries or fewer in the mean
     RowSkip skip = {nullptr, 0, 0};
 
     // workgroups of this instance that one compute unit can hold at once
@@ -285,23 +295,32 @@ struct Launch {
         return n;
     }
 
-    // A group's rounds of loads on a row of len entries are len / (G * kGatherDepth) for each pass over the columns,
+    // A group's rounds of loads on a row of len entries are about len / (G * 6) for each pass over the columns,
     // each of them a round trip to memory with a handful of loads in flight.  From about sixteen rounds on, the whole
     // workgroup takes the row instead; never a row that is only a few steps of the workgroup long.
     static int32_t share_rows_from(int g, int passes)
     {
-        const int len = 16 * g * kGatherDepth / passes;
+        const int len = 16 * g * 6 / passes;
         return len < kShareMin ? kShareMin : len;
     }
 
     template <int G, int LC, int VEC>
     void operator()() const
     {
+        if constexpr (G > 1) go<G, LC, VEC, kDepthGroups>();
+        else if constexpr (SKIP) go<G, LC, VEC, kDepthRows>();
+        else if (short_rows) go<G, LC, VEC, kDepthShort>();
+        else go<G, LC, VEC, kDepthRows>();
+    }
+
+    template <int G, int LC, int VEC, int DEPTH>
+    void go() const
+    {
         // a persistent grid must be resident all at once (asked of the runtime only for such launches)
         int max_grid = 0x7fffffff;
         if (persistent)
-            max_grid = compute_units * (off32 ? resident_per_cu(row_split_kernel<G, LC, VEC, true, PARTIAL, SKIP>, block)
-                                              : resident_per_cu(row_split_kernel<G, LC, VEC, false, PARTIAL, SKIP>, block));
+            max_grid = compute_units * (off32 ? resident_per_cu(row_split_kernel<G, LC, VEC, true, PARTIAL, SKIP, DEPTH>, block)
+                                              : resident_per_cu(row_split_kernel<G, LC, VEC, false, PARTIAL, SKIP, DEPTH>, block));
         const int slots = block / (G * LC);
         const int64_t rows_per_block = (int64_t)slots * rows_per_slot;
         TileSched ts;
@@ -318,10 +337,10 @@ struct Launch {
         if (wgs_per_xcd > ts.items_per_xcd) wgs_per_xcd = ts.items_per_xcd;
         const unsigned grid = (unsigned)(wgs_per_xcd * xcds);
         if (off32)
-            hipLaunchKernelGGL((row_split_kernel<G, LC, VEC, true, PARTIAL, SKIP>), dim3(grid), dim3(block), 0, s, a,
+            hipLaunchKernelGGL((row_split_kernel<G, LC, VEC, true, PARTIAL, SKIP, DEPTH>), dim3(grid), dim3(block), 0, s, a,
                                ts, rows_per_slot, interleave, reduce_members, share_from, skip);
         else
-            hipLaunchKernelGGL((row_split_kernel<G, LC, VEC, false, PARTIAL, SKIP>), dim3(grid), dim3(block), 0, s, a,
+            hipLaunchKernelGGL((row_split_kernel<G, LC, VEC, false, PARTIAL, SKIP, DEPTH>), dim3(grid), dim3(block), 0, s, a,
                                ts, rows_per_slot, interleave, reduce_members, share_from, skip);
     }
 };
