@@ -11,16 +11,27 @@ struct StagedEntry {
     float val;
 };
 
-// Coalesced streaming copy of stored entries [base, base+cnt) into LDS.
-// The caller synchronises.
+// Coalesced streaming copy of stored entries [base, base+cnt) into LDS, U per
+// thread requested before the first is put down (one at a time, each round of the
+// workgroup waited for memory: 544 entries of a block of fibers took three round
+// trips, a chunk of 2,048 entries of a long row eight).  The caller synchronises.
+template <int U>
 __device__ __forceinline__ void stage_entries(const SpmmArgs& a, uint32_t base, uint32_t cnt,
                                               StagedEntry* __restrict__ s_A, uint32_t block = kBlock)
 {
-    for (uint32_t q = threadIdx.x; q < cnt; q += block) {
-        StagedEntry e;
-        e.col = load_stream(a.colidx + base + q);
-        e.val = load_stream(a.vals + base + q);
-        s_A[q] = e;
+    for (uint32_t q0 = threadIdx.x; q0 < cnt; q0 += U * block) {
+        StagedEntry e[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const uint32_t q = q0 + u * block;
+            if (q < cnt) {
+                e[u].col = load_stream(a.colidx + base + q);
+                e[u].val = load_stream(a.vals + base + q);
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+            if (q0 + u * block < cnt) s_A[q0 + u * block] = e[u];
     }
 }
 
