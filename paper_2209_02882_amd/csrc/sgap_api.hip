@@ -434,7 +434,7 @@ int spmm_impl(int64_t M, int64_t K, int64_t N, const int32_t* rowptr, const int3
             // the parallel strategy interleaves its groups' rows; the serial strategy's lanes
             // own consecutive rows by definition
             err = launch_row_split(a, g, lc, vec, rows_per_slot, par, (int)tile_cols, xcds, cus, c.persistent != 0,
-                                   block, avg_row, s);
+                                   block, nnz_hint, avg_row, s);
         }
     } else {
         const int lc = pow2_ceil_capped(chunks, par ? 64 / group_size : 64);

@@ -227,7 +227,8 @@ NnzPlan plan_nnz_parallel(int group, int lc, int vec);
 // workgroup per item); block = threads per workgroup (128, 256 or 512).
 // mean_row: stored entries per row as far as the host knows.
 hipError_t launch_row_split(const SpmmArgs& a, int g, int lc, int vec, int rows_per_slot, bool interleave,
-                            int tile_cols, int xcds, int compute_units, bool persistent, int block, double mean_row,
+                            int tile_cols, int xcds, int compute_units, bool persistent, int block, int64_t nnz_hint,
+                            double mean_row,
                             hipStream_t s);
 // the same with g lanes per row reducing in sub-groups of r < g lanes whose sums
 // are merged with atomics; C must have been zeroed (launch_nnz_zero_rows, -1)

@@ -691,7 +691,7 @@ hipError_t launch_row_split_panels(const SpmmArgs& a, int g, int lc, int vec, in
     // the claiming kernel numbers its items (column tile, window, long row) with 32 bits
     if ((a.N + window_cols - 1) / window_cols * windows * cap > 0xffffffffLL)
         return launch_row_split(a, g, lc, vec, rows_per_slot, interleave, tile_cols, xcds, compute_units, persistent,
-                                block, 16.0, s);
+                                block, -1, 16.0, s);
     const PanelView scr = panel_view(workspace, cap, windows);
     // a wavefront per row with all 64 lanes on column chunks: worth it from 128 columns on
     const bool owners = wave_lc == kPanelTileLanes && a.N >= 128;
@@ -717,7 +717,7 @@ hipError_t launch_row_split_panels(const SpmmArgs& a, int g, int lc, int vec, in
     // serial strategy with one wavefront per rows_per_slot rows (sgap_wave_rows.hip)
     if (wave_vec > 0) return launch_wave_rows(a, wave_vec, rows_per_slot, xcds, &skip, s);
     row_split_detail::Launch<false, true> f{a, rows_per_slot, interleave ? 1 : 0, tile_cols, xcds, compute_units,
-                                            offsets_fit_32(a), persistent, 0, block, s, false, skip};
+                                            offsets_fit_32(a), persistent, 0, block, s, -1, false, skip};
     if (!dispatch_group(g, lc, vec, f)) return hipErrorInvalidValue;
     return hipGetLastError();
 }

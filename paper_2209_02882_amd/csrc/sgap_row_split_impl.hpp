@@ -95,20 +95,24 @@ __device__ __forceinline__ void shared_row(const SpmmArgs& a, int64_t row, uint3
 // (a power of two below G) and the first member of every sub-group adds its
 // sum to C with atomics; C must hold zeros before the launch.
 // SKIP: leave the rows described by `skip` alone.
-// share_from (G > 1, whole-group reductions): rows of at least that many stored entries are left out of the walk and
-// produced by the whole workgroup afterwards (shared_row).
+// share_from (G > 1, whole-group reductions): rows of at least that many stored entries are left out of the walk; the
+// first `finders` workgroups of the grid look for them, each in an equal stretch of the rows, and produce them one after
+// the other with all their lanes (shared_row).  They start first, so that the longest rows are done while the others
+// are walked: a workgroup that came across one during its walk ended some 40 us behind the rest.  A row of 27,000
+// entries is what binds a power law then; eight finders per compute unit (as many as are resident) leave few rows in
+// sequence: 65,536 rows, N = 37, G = 8: 73 us in the walk, 70.7 with one finder per compute unit, 58.4 with two, 47.5
+// with four or eight; 114,150 rows, N = 34: 100.5, 100.4, 90.2, 82.8 and 72.5 with eight.
 // The workgroup size (the paper's blockSz, Section 7.2) is the launch's: SLOTS = blockDim.x / (G*LC)
 // groups work side by side on the rows of a row block.
 template <int G, int LC, int VEC, bool OFF32, bool PARTIAL, bool SKIP, int DEPTH>
 __global__ __launch_bounds__(kRowSplitMaxBlock) void row_split_kernel(SpmmArgs a, TileSched ts, int rows_per_slot,
                                                                       int interleave, int reduce_members,
-                                                                      int32_t share_from, RowSkip skip)
+                                                                      int32_t share_from, int finders, RowSkip skip)
 {
     __shared__ StagedEntry s_A[kStageCap];
     __shared__ int32_t s_rp[kRowCap + 1];
     constexpr bool SHARE = G > 1 && !PARTIAL;
-    __shared__ uint16_t s_shared[SHARE ? kRowCap : 1];  // this block's shared rows
-    __shared__ int32_t s_shared_n;
+    __shared__ int32_t s_found;
     // entries per thread in flight to LDS: single lanes' row blocks have one or two for each thread, and the registers of
     // four would cost the instance a wavefront per SIMD (stencil of 1,048,576 rows, N = 128: 602 us against 593)
     constexpr int STAGED = G == 1 && DEPTH == kDepthRows ? 1 : 4;
@@ -125,10 +129,37 @@ __global__ __launch_bounds__(kRowSplitMaxBlock) void row_split_kernel(SpmmArgs a
     bool skip_on = false;
     if constexpr (SKIP) skip_on = *skip.count <= skip.max_rows;
 
+    if constexpr (SHARE) {
+        if ((int)blockIdx.x < finders) {
+            const int64_t per = (a.M + finders - 1) / finders;
+            const int64_t first = per * blockIdx.x, last = first + per < a.M ? first + per : a.M;
+            for (int64_t r0 = first; r0 < last; r0 += block) {
+                __syncthreads();  // the last rows found are done with
+                if (threadIdx.x == 0) s_found = 0;
+                __syncthreads();
+                const int64_t r = r0 + threadIdx.x;
+                if (r < last) {
+                    const int32_t len = a.rowptr[r + 1] - a.rowptr[r];
+                    bool shared = len >= share_from;
+                    if constexpr (SKIP) shared = shared && !(skip_on && len >= skip.min_len);
+                    if (shared) s_rp[atomicAdd(&s_found, 1)] = (int32_t)r;
+                }
+                __syncthreads();
+                const int n = s_found;
+                for (int i = 0; i < n; ++i) {
+                    const int32_t row = __builtin_amdgcn_readfirstlane(s_rp[i]);
+                    shared_row<VEC, OFF32, DEPTH>(a, row, (uint32_t)a.rowptr[row], (uint32_t)a.rowptr[row + 1], 0, N, s_A, block);
+                }
+            }
+            return;
+        }
+    }
+
     // persistent walk over this die's run of work items
-    const int64_t xcd = blockIdx.x % ts.xcds;
-    const int64_t wg_in_xcd = blockIdx.x / ts.xcds;
-    const int64_t wgs_per_xcd = gridDim.x / ts.xcds;
+    const int64_t wg = blockIdx.x - finders;
+    const int64_t xcd = wg % ts.xcds;
+    const int64_t wg_in_xcd = wg / ts.xcds;
+    const int64_t wgs_per_xcd = (gridDim.x - finders) / ts.xcds;
     for (int64_t it = wg_in_xcd; it < ts.items_per_xcd; it += wgs_per_xcd) {
         const int64_t item = xcd * ts.items_per_xcd + it;
         if (item >= ts.items) break;
@@ -151,28 +182,12 @@ __global__ __launch_bounds__(kRowSplitMaxBlock) void row_split_kernel(SpmmArgs a
         if (rp_in_lds) {
             for (int i = threadIdx.x; i <= block_rows; i += block)
                 s_rp[i] = a.rowptr[row_first + i];
-            if constexpr (SHARE) {
-                if (threadIdx.x == 0) s_shared_n = 0;
-            }
             __syncthreads();
             nz_first = (uint32_t)__builtin_amdgcn_readfirstlane(s_rp[0]);  // the same in all lanes: scalar registers
             nz_last = (uint32_t)__builtin_amdgcn_readfirstlane(s_rp[block_rows]);
         } else {
             nz_first = (uint32_t)a.rowptr[row_first];
             nz_last = (uint32_t)a.rowptr[row_last];
-        }
-        // (block-uniform; the entries of a shared row are not walked here, so a block that holds nothing else
-        // passes over them without looking)
-        const bool share_on = SHARE && rp_in_lds && nz_last - nz_first >= (uint32_t)share_from;
-        if constexpr (SHARE) {
-            if (share_on) {
-                for (int i = threadIdx.x; i < block_rows; i += block) {
-                    const int32_t len = s_rp[i + 1] - s_rp[i];
-                    bool shared = len >= share_from;
-                    if constexpr (SKIP) shared = shared && !(skip_on && len >= skip.min_len);
-                    if (shared) s_shared[atomicAdd(&s_shared_n, 1)] = (uint16_t)i;
-                }
-            }
         }
         const bool one_chunk = nz_last - nz_first <= (uint32_t)kStageCap;
 
@@ -210,7 +225,7 @@ __global__ __launch_bounds__(kRowSplitMaxBlock) void row_split_kernel(SpmmArgs a
                     const uint32_t hi = p_end < base + cnt ? p_end : base + cnt;
                     bool skipped = false;
                     if constexpr (SKIP) skipped = skip_on && p_end - p_begin >= (uint32_t)skip.min_len;
-                    if constexpr (SHARE) skipped = skipped || (share_on && p_end - p_begin >= (uint32_t)share_from);
+                    if constexpr (SHARE) skipped = skipped || p_end - p_begin >= (uint32_t)share_from;
                     if (!skipped && k_ok && lo < hi) {
                         // first position >= lo that belongs to this member
                         const uint32_t first = lo + ((member - (lo - p_begin)) & (G - 1));
@@ -262,17 +277,6 @@ __global__ __launch_bounds__(kRowSplitMaxBlock) void row_split_kernel(SpmmArgs a
                 if (base + cnt >= nz_last) break;
             }
         }
-        if constexpr (SHARE) {
-            if (share_on) {
-                const int n = s_shared_n;  // written before the barriers of the walk
-                for (int i = 0; i < n; ++i) {
-                    const int row = __builtin_amdgcn_readfirstlane(s_shared[i]);
-                    shared_row<VEC, OFF32, DEPTH>(a, row_first + row, (uint32_t)__builtin_amdgcn_readfirstlane(s_rp[row]),
-                                           (uint32_t)__builtin_amdgcn_readfirstlane(s_rp[row + 1]),
-                                           (int64_t)col_tile * ts.tile_cols, k_tile_end, s_A, block);
-                }
-            }
-        }
     }
 }
 
@@ -286,6 +290,7 @@ struct Launch {
     int reduce_members;
     int block;  // threads per workgroup: 128, 256 or 512 (at least G*LC)
     hipStream_t s;
+    int64_t nnz_hint;  // stored entries, -1 = unknown
     bool short_rows;  // rows of kShortRowMean entries or fewer in the mean
     RowSkip skip = {nullptr, 0, 0};
 
@@ -334,17 +339,24 @@ struct Launch {
         ts.xcds = xcds;
         ts.items_per_xcd = (ts.items + xcds - 1) / xcds;
         const int passes = (int)(((int64_t)tile_cols + LC * VEC - 1) / (LC * VEC));
+        // rows that whole workgroups take, and the workgroups that look for them (whole rounds of the dies)
         const int32_t share_from = share_rows_from(G, passes);
+        int finders = 0;
+        if (G > 1 && !PARTIAL && (nnz_hint < 0 || nnz_hint >= share_from)) {
+            const int64_t most = 8LL * compute_units;  // and no fewer than 64 rows each: a wavefront's look
+            finders = (int)((a.M + 63) / 64 < most ? (a.M + 63) / 64 : most);
+            finders = (finders + xcds - 1) / xcds * xcds;
+        }
         int64_t wgs_per_xcd = max_grid / xcds > 0 ? max_grid / xcds : 1;
         if (wgs_per_xcd * xcds > 0x7ffffff0LL) wgs_per_xcd = 0x7ffffff0LL / xcds;
         if (wgs_per_xcd > ts.items_per_xcd) wgs_per_xcd = ts.items_per_xcd;
-        const unsigned grid = (unsigned)(wgs_per_xcd * xcds);
+        const unsigned grid = (unsigned)(wgs_per_xcd * xcds + finders);
         if (off32)
             hipLaunchKernelGGL((row_split_kernel<G, LC, VEC, true, PARTIAL, SKIP, DEPTH>), dim3(grid), dim3(block), 0, s, a,
-                               ts, rows_per_slot, interleave, reduce_members, share_from, skip);
+                               ts, rows_per_slot, interleave, reduce_members, share_from, finders, skip);
         else
             hipLaunchKernelGGL((row_split_kernel<G, LC, VEC, false, PARTIAL, SKIP, DEPTH>), dim3(grid), dim3(block), 0, s, a,
-                               ts, rows_per_slot, interleave, reduce_members, share_from, skip);
+                               ts, rows_per_slot, interleave, reduce_members, share_from, finders, skip);
     }
 };
 

@@ -12,7 +12,7 @@ hipError_t launch_row_split_partial(const SpmmArgs& a, int g, int r, int lc, int
 {
     if (r < 1 || r >= g || (r & (r - 1)) != 0) return hipErrorInvalidValue;
     row_split_detail::Launch<true> f{a, rows_per_slot, 1, tile_cols, xcds, compute_units,
-                                     offsets_fit_32(a), persistent, r, block, s, false};
+                                     offsets_fit_32(a), persistent, r, block, s, -1, false};
     if (!dispatch_group(g, lc, vec, f)) return hipErrorInvalidValue;
     return hipGetLastError();
 }

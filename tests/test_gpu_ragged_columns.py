@@ -43,3 +43,17 @@ def test_ragged_columns_of_sddmm(J):
     for st in ("parallel", "serial"):
         for g in binding.GROUP_SIZES:
             assert np.array_equal(dp.run_sddmm(X1d, g, st).cpu().numpy().astype(np.float64), ref), (g, st)
+
+
+# long rows looked for over several rounds of a workgroup, next to each other and at both ends
+@pytest.mark.parametrize("M,block", [(64, 128), (65, 256), (16385, 256), (400_000, 128), (400_000, 512)])
+def test_long_rows_found_in_large_matrices(M, block):
+    lengths = np.random.default_rng(M).integers(0, 3, M)
+    where = np.array([0, 1, 2, 63, 64, M // 2, M // 2 + 1, M - 200, M - 1]) % M
+    lengths[where] = [900, 256, 768, 1536, 255, 2500, 300, 1000, 767]
+    p, _ = problem(M, 3000, 5, lengths, seed=M)
+    ref, _ = oracle.spmm_csr(p.M, p.K, p.N, p.rowptr, p.colidx, p.vals, p.B, nthreads=8, bound=False)
+    dp = DeviceProblem(p)
+    for g in (2, 8, 32):
+        got = dp.run_cfg(binding.make_config(g, "parallel", "row_split", block_size=block)).cpu().numpy()
+        assert np.array_equal(got.astype(np.float64), ref), g
