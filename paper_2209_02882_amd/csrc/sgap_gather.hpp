@@ -11,12 +11,12 @@ struct StagedEntry {
     float val;
 };
 
-// Coalesced streaming copy of stored entries [base, base+cnt) into LDS, U per
+// Coalesced streaming copy of cnt stored entries into LDS, U per
 // thread requested before the first is put down (one at a time, each round of the
 // workgroup waited for memory: 544 entries of a block of fibers took three round
 // trips, a chunk of 2,048 entries of a long row eight).  The caller synchronises.
 template <int U>
-__device__ __forceinline__ void stage_entries(const SpmmArgs& a, uint32_t base, uint32_t cnt,
+__device__ __forceinline__ void stage_entries(const int32_t* __restrict__ idx, const float* __restrict__ vals, uint32_t cnt,
                                               StagedEntry* __restrict__ s_A, uint32_t block = kBlock)
 {
     for (uint32_t q0 = threadIdx.x; q0 < cnt; q0 += U * block) {
@@ -25,8 +25,8 @@ __device__ __forceinline__ void stage_entries(const SpmmArgs& a, uint32_t base, 
         for (int u = 0; u < U; ++u) {
             const uint32_t q = q0 + u * block;
             if (q < cnt) {
-                e[u].col = load_stream(a.colidx + base + q);
-                e[u].val = load_stream(a.vals + base + q);
+                e[u].col = load_stream(idx + q);
+                e[u].val = load_stream(vals + q);
             }
         }
 #pragma unroll

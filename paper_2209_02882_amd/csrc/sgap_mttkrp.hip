@@ -147,6 +147,7 @@ __global__ __launch_bounds__(kBlock) void mttkrp_kernel(MttkrpArgs a, int rows_p
         f0 = s_fp[0];
         const int32_t fibers = s_fp[block_rows] - f0;
         if (fibers >= 0 && fibers <= kMtFibers) {
+#pragma unroll 2
             for (int i = threadIdx.x; i <= fibers; i += kBlock) {
                 s_ep[i] = a.eptr[f0 + i];
                 if (i < fibers) s_fk[i] = a.fidx[f0 + i];
@@ -155,12 +156,7 @@ __global__ __launch_bounds__(kBlock) void mttkrp_kernel(MttkrpArgs a, int rows_p
             e0 = s_ep[0];
             const int32_t entries = s_ep[fibers] - e0;
             if (entries >= 0 && entries <= kMtEntries) {
-                for (int i = threadIdx.x; i < entries; i += kBlock) {
-                    StagedEntry e;
-                    e.col = load_stream(a.eidx + e0 + i);
-                    e.val = load_stream(a.vals + e0 + i);
-                    s_A[i] = e;
-                }
+                stage_entries<4>(a.eidx + e0, a.vals + e0, (uint32_t)entries, s_A);
                 __syncthreads();
                 staged = true;
             }

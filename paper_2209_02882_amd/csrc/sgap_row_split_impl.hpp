@@ -51,7 +51,7 @@ __device__ __forceinline__ void shared_row(const SpmmArgs& a, int64_t row, uint3
         for (uint32_t base = p_begin; base < p_end; base += kStageCap) {
             const uint32_t cnt = p_end - base < (uint32_t)kStageCap ? p_end - base : (uint32_t)kStageCap;
             __syncthreads();
-            stage_entries<8>(a, base, cnt, s_A, block);
+            stage_entries<8>(a.colidx + base, a.vals + base, cnt, s_A, block);
             __syncthreads();
             for (uint32_t q = member; k_ok && q < cnt; q += D * members) {
                 StagedEntry e[D];
@@ -208,7 +208,7 @@ __global__ __launch_bounds__(kRowSplitMaxBlock) void row_split_kernel(SpmmArgs a
                 const bool staged = one_chunk && k0 != (int64_t)col_tile * ts.tile_cols;  // by the pass before
                 if (!staged) {
                     if (base != nz_first || k0 != (int64_t)col_tile * ts.tile_cols) __syncthreads();
-                    stage_entries<STAGED>(a, base, cnt, s_A, block);
+                    stage_entries<STAGED>(a.colidx + base, a.vals + base, cnt, s_A, block);
                     __syncthreads();
                 }
                 // rows of this slot that have entries in the chunk (or are empty)
