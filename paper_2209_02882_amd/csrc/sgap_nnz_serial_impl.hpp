@@ -27,16 +27,15 @@ namespace sgap {
 __host__ __device__ constexpr int staged_place(int q) { return q + (q >> 5); }
 
 // Multiply out the chunk [base, end) of the tile staged in s_A (slot s holds
-// position tile_start + s), whose rows WITH entries begin at s_win[w.n_first ..
-// w.n_last] (the last one ends at s_win[w.n_last + 1]) and have the numbers s_row.
-// The next row's number and end are requested when a row is taken up: where rows
-// hold a few entries a flush would otherwise wait for LDS twice.
-// Both arrays have one place behind the last, read but not used.
+// position tile_start + s), whose rows are s_win[w.n_first .. w.n_last + 1]
+// relative to row_lb: window index wi stands for row row_lb + wi, or, when
+// s_row is given (a window of the rows WITH entries only), for row s_row[wi].
 // MERGE selects tile mode of the merge rule; in that mode the function ends with a barrier.
 template <int LC, int VEC, bool OFF32, bool MERGE, bool RAGGED>
 __device__ __forceinline__ void serial_chunk(const SpmmArgs& a, const MergeBuf& mb, const StagedEntry* __restrict__ s_A,
-                                             const int32_t* __restrict__ s_win, const int32_t* __restrict__ s_row,
-                                             const RowWindow& w, int32_t tile_start, int32_t base, int32_t end)
+                                             const int32_t* __restrict__ s_win, const RowWindow& w, int32_t row_lb,
+                                             int32_t tile_start, int32_t base, int32_t end,
+                                             const int32_t* __restrict__ s_row = nullptr)
 {
     constexpr int kDepth = 8;  // gathered rows of B in flight per lane
     // How partial sums are added into the LDS slots.  With many chunk lanes per
@@ -45,7 +44,7 @@ __device__ __forceinline__ void serial_chunk(const SpmmArgs& a, const MergeBuf& 
     // wavefront holds up to 64 entry lanes, whole rows of which meet on one
     // slot, and the loop would retry once per lane: the hardware atomic wins
     // (rmat at N=4, one entry per lane: 1.6 ms against 23 ms).
-    constexpr bool kCasMerge = false;
+    constexpr bool kCasMerge = LC >= 8;
     constexpr int ENTRY_LANES = kBlock / LC;
     const int entry_lane = threadIdx.x / LC;
     const int chunk = threadIdx.x % LC;
@@ -67,8 +66,6 @@ __device__ __forceinline__ void serial_chunk(const SpmmArgs& a, const MergeBuf& 
             int32_t wi = last_row_at_or_before(s_win, w.n_first, w.n_last, blk_begin);
             int32_t row_begin = s_win[wi];
             int32_t row_end = s_win[wi + 1];
-            int32_t row = s_row[wi];
-            int32_t next_end = s_win[wi + 2], next_row = s_row[wi + 1];
             int32_t run_begin = blk_begin;
             Vec<VEC> acc;
             acc.zero();
@@ -107,7 +104,8 @@ __device__ __forceinline__ void serial_chunk(const SpmmArgs& a, const MergeBuf& 
                     if (p >= blk_end) continue;
                     acc.fma(e[u].val, b[u]);
                     if (p + 1 != row_end && p + 1 != blk_end) continue;
-                    // flush the run [run_begin, p] of `row`
+                    // flush the run [run_begin, p] of the row at window index wi
+                    const int32_t row = s_row ? s_row[wi] : row_lb + wi;
                     if constexpr (MERGE) {
                         if (run_begin == row_begin && p + 1 == row_end) {
                             // the run is the whole row
@@ -127,13 +125,16 @@ __device__ __forceinline__ void serial_chunk(const SpmmArgs& a, const MergeBuf& 
                     }
                     acc.zero();
                     if (p + 1 < blk_end) {
-                        // there is a next row: it holds position p + 1
+                        // next row with stored entries (there is one at or before the
+                        // chunk's last row): the very next slot in a window of rows with
+                        // entries only, else bisect over the rows without entries
                         ++wi;
                         row_begin = row_end;
-                        row_end = next_end;
-                        row = next_row;
-                        next_end = s_win[wi + 2];
-                        next_row = s_row[wi + 1];
+                        row_end = s_win[wi + 1];
+                        if (row_end <= p + 1) {
+                            wi = last_row_at_or_before(s_win, wi + 1, w.n_last, p + 1);
+                            row_end = s_win[wi + 1];
+                        }
                         run_begin = p + 1;  // = row_begin
                     }
                 }
@@ -156,8 +157,8 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
     extern __shared__ __align__(16) unsigned char s_raw[];
     // (the window of rows with entries holds up to one row per position of the tile)
     constexpr int WIN = TILE > kWindowCap ? TILE : kWindowCap;
-    __shared__ int32_t s_win[WIN + 2];
-    __shared__ int32_t s_row[WIN + 1];
+    __shared__ int32_t s_win[WIN + 1];
+    __shared__ int32_t s_row[WIN];
     __shared__ int32_t s_scan[kWavesPerBlock];
     __shared__ int32_t s_tile_row[kTileRowBatch];
     constexpr int WIDTH = LC * VEC;
@@ -248,7 +249,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
                 __syncthreads();  // everyone has read the plain window
                 w.n_last = load_compact_window(a, row_lb, tile_end, s_win, s_row, s_scan) - 1;
             }
-            serial_chunk<LC, VEC, OFF32, MERGE, RAGGED>(a, mb, s_A, s_win, s_row, w, tile_start, tile_start, tile_end);
+            serial_chunk<LC, VEC, OFF32, MERGE, RAGGED>(a, mb, s_A, s_win, w, 0, tile_start, tile_start, tile_end, s_row);
             // tile and window fully consumed before they are overwritten (tile mode ends with a barrier of its own)
             if constexpr (!MERGE) __syncthreads();
         }
