@@ -26,16 +26,13 @@ namespace sgap {
 // two, and without the gaps would meet on a few of the banks (R-MAT, G = 32: half of the LDS cycles were conflicts).
 __host__ __device__ constexpr int staged_place(int q) { return q + (q >> 5); }
 
-// Multiply out the chunk [base, end) of the tile staged in s_A (slot s holds
-// position tile_start + s), whose rows are s_win[w.n_first .. w.n_last + 1]
-// relative to row_lb: window index wi stands for row row_lb + wi, or, when
-// s_row is given (a window of the rows WITH entries only), for row s_row[wi].
+// Multiply out the tile [tile_start, end) staged in s_A (staged_place says where); its rows WITH entries begin at
+// s_win[0 .. n_last] (the last one ends at s_win[n_last + 1]) and have the numbers s_row[0 .. n_last].
 // MERGE selects tile mode of the merge rule; in that mode the function ends with a barrier.
 template <int LC, int VEC, bool OFF32, bool MERGE, bool RAGGED>
 __device__ __forceinline__ void serial_chunk(const SpmmArgs& a, const MergeBuf& mb, const StagedEntry* __restrict__ s_A,
-                                             const int32_t* __restrict__ s_win, const RowWindow& w, int32_t row_lb,
-                                             int32_t tile_start, int32_t base, int32_t end,
-                                             const int32_t* __restrict__ s_row = nullptr)
+                                             const int32_t* __restrict__ s_win, const int32_t* __restrict__ s_row,
+                                             int32_t n_last, int32_t tile_start, int32_t end)
 {
     constexpr int kDepth = 8;  // gathered rows of B in flight per lane
     // How partial sums are added into the LDS slots.  With many chunk lanes per
@@ -58,21 +55,19 @@ __device__ __forceinline__ void serial_chunk(const SpmmArgs& a, const MergeBuf& 
         const uint32_t k_lane = k_ok ? lane_first_col<VEC, RAGGED>(k, (uint32_t)N) : 0;  // the VEC columns this lane holds
         const BRow<OFF32> Brow(a.B, N, k_lane);
         for (int32_t blk = tile_start + entry_lane * G; k_ok && blk < end; blk += per_step) {
-            // this lane's aligned block of G positions, clipped to the chunk
-            const int32_t blk_begin = blk > base ? blk : base;
+            // this lane's aligned block of G positions
             const int32_t blk_end = blk + G < end ? blk + G : end;
-            if (blk_begin >= blk_end) continue;
-            // window index of the row that holds blk_begin
-            int32_t wi = last_row_at_or_before(s_win, w.n_first, w.n_last, blk_begin);
+            // window index of the row that holds its first
+            int32_t wi = last_row_at_or_before(s_win, 0, n_last, blk);
             int32_t row_begin = s_win[wi];
             int32_t row_end = s_win[wi + 1];
-            int32_t run_begin = blk_begin;
+            int32_t run_begin = blk;
             Vec<VEC> acc;
             acc.zero();
             // Entries are fetched kDepth at a time regardless of row ends, so
             // that kDepth rows of B are in flight, and then consumed in order;
             // the register is flushed where a row or the block ends.
-            for (int32_t p0 = blk_begin; p0 < blk_end; p0 += kDepth) {
+            for (int32_t p0 = blk; p0 < blk_end; p0 += kDepth) {
                 StagedEntry e[kDepth];
                 Vec<VEC> b[kDepth];
                 // (a batch starts at a multiple of eight, or is a share of fewer: no gap inside it)
@@ -105,18 +100,18 @@ __device__ __forceinline__ void serial_chunk(const SpmmArgs& a, const MergeBuf& 
                     acc.fma(e[u].val, b[u]);
                     if (p + 1 != row_end && p + 1 != blk_end) continue;
                     // flush the run [run_begin, p] of the row at window index wi
-                    const int32_t row = s_row ? s_row[wi] : row_lb + wi;
+                    const int32_t row = s_row[wi];
                     if constexpr (MERGE) {
                         if (run_begin == row_begin && p + 1 == row_end) {
                             // the run is the whole row
                             store_vec_stream<VEC>(a.C + (int64_t)row * N + k_lane, acc);
                         } else {
-                            const int32_t first_in_chunk = row_begin > base ? row_begin : base;
+                            const int32_t first_here = row_begin > tile_start ? row_begin : tile_start;
                             const int32_t slot =
-                                row_begin < base ? mb.nslots - 1 : (row_begin - tile_start) >> a.log2_group;
+                                row_begin < tile_start ? mb.nslots - 1 : (row_begin - tile_start) >> a.log2_group;
                             from_last_columns<VEC, RAGGED>(acc, (int)((uint32_t)k0 + chunk * VEC - k_lane));
-                            merge_add<VEC, kCasMerge>(mb, slot, chunk * VEC, acc, chunk == 0 && run_begin == first_in_chunk, row,
-                                           row_begin < base || row_end > end);
+                            merge_add<VEC, kCasMerge>(mb, slot, chunk * VEC, acc, chunk == 0 && run_begin == first_here, row,
+                                           row_begin < tile_start || row_end > end);
                         }
                     } else {
                         // the whole row lies inside this aligned block: nobody else adds to it
@@ -125,16 +120,12 @@ __device__ __forceinline__ void serial_chunk(const SpmmArgs& a, const MergeBuf& 
                     }
                     acc.zero();
                     if (p + 1 < blk_end) {
-                        // next row with stored entries (there is one at or before the
-                        // chunk's last row): the very next slot in a window of rows with
-                        // entries only, else bisect over the rows without entries
-                        ++wi;
+                        // on to the row that holds position p + 1 (every row of the window has entries: one step, but
+                        // with a loop here the compiler keeps the eight flushes of a batch apart; merged, they held 15
+                        // registers more where the merge has no loop of its own: 137 for LC = 4, a wavefront fewer)
                         row_begin = row_end;
-                        row_end = s_win[wi + 1];
-                        if (row_end <= p + 1) {
-                            wi = last_row_at_or_before(s_win, wi + 1, w.n_last, p + 1);
-                            row_end = s_win[wi + 1];
-                        }
+                        do row_end = s_win[++wi + 1];
+                        while (row_end <= p + 1);
                         run_begin = p + 1;  // = row_begin
                     }
                 }
@@ -149,8 +140,12 @@ __device__ __forceinline__ void serial_chunk(const SpmmArgs& a, const MergeBuf& 
 }
 
 // EPT = tile / kBlock stored entries per thread held in registers between tiles.
+// Registers: up to 1,024 entries every instance stays within 128 (115 to 123 in tile mode with 32-bit offsets: four
+// wavefronts per SIMD) and none spills.  What is computed from the thread's number for the tile's way in and out (LDS
+// places, positions) would be hoisted out of the loop over tiles and be held while a tile is multiplied out, so it is
+// computed from an opaque copy of the number.
 template <int LC, int VEC, bool OFF32, bool MERGE, int EPT, bool RAGGED>
-__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) void nnz_serial_kernel(SpmmArgs a)
+__global__ __launch_bounds__(kBlock) void nnz_serial_kernel(SpmmArgs a)
 {
     constexpr int TILE = EPT * kBlock;
     constexpr int WPT = kWindowCap / kBlock + 1;  // rowptr window entries per thread (last one: thread 0 only)
@@ -179,7 +174,6 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
     const int64_t my_tiles = deal.mine;
     if (my_tiles == 0) return;
     TileWalk ahead(deal);  // the tile that is fetched next
-    const int tid = threadIdx.x;
 
     if constexpr (MERGE) merge_reset(mb);  // made visible by the barriers below
 
@@ -189,6 +183,8 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
     int32_t nx_win[WPT];
     auto fetch_tile = [&](int32_t row_lb) {  // the tile `ahead` stands at
         const int32_t start = (int32_t)(ahead.tile() * TILE);
+        int tid = threadIdx.x;
+        asm volatile("" : "+v"(tid));
 #pragma unroll
         for (int i = 0; i < EPT; ++i) {
             const int32_t p = start + tid + i * kBlock;
@@ -213,10 +209,12 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
         fetch_tile(s_tile_row[0]);
 
         for (int64_t j = j0; j < j1; ++j) {
+            int tid = threadIdx.x;
+            asm volatile("" : "+v"(tid));
             const int32_t tile_start = (int32_t)(ahead.tile() * TILE);
             ahead.next();
             const int32_t tile_end = nnz - tile_start < TILE ? nnz : tile_start + TILE;
-            int32_t row_lb = s_tile_row[j - j0];
+            const int32_t row_lb = s_tile_row[j - j0];
 
             // install the tile that was fetched ahead
 #pragma unroll
@@ -238,18 +236,17 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
             // of the window at the end of the row in front of them, and cutting a tile whose rows do not fit the
             // plain window costs a window load and several barriers per cut (R-MAT's sparse end: up to nine cuts
             // per tile).  One path for all tiles also keeps the kernel's code (serial_chunk is long) small.
-            RowWindow w;
-            w.cnt = tile_end - tile_start;
-            w.n_first = 0;
+            int32_t n;
             if (s_win[kWindowCap] >= tile_end) {
                 // the plain window covers every row of the tile: cut it down where it stands
-                w.n_last = compact_window(s_win, s_row, row_lb, tile_end, s_scan) - 1;
+                n = compact_window(s_win, s_row, row_lb, tile_end, s_scan);
             } else {
                 // long runs of rows without entries: read on in rowptr
                 __syncthreads();  // everyone has read the plain window
-                w.n_last = load_compact_window(a, row_lb, tile_end, s_win, s_row, s_scan) - 1;
+                n = load_compact_window(a, row_lb, tile_end, s_win, s_row, s_scan);
             }
-            serial_chunk<LC, VEC, OFF32, MERGE, RAGGED>(a, mb, s_A, s_win, w, 0, tile_start, tile_start, tile_end, s_row);
+            serial_chunk<LC, VEC, OFF32, MERGE, RAGGED>(a, mb, s_A, s_win, s_row, __builtin_amdgcn_readfirstlane(n) - 1,
+                                                        tile_start, tile_end);
             // tile and window fully consumed before they are overwritten (tile mode ends with a barrier of its own)
             if constexpr (!MERGE) __syncthreads();
         }

@@ -1,0 +1,51 @@
+"""What the compiler gave the kernels of the built library, read from the code objects' own metadata: no kernel keeps
+vector registers in memory.  (A spill inside a loop over tiles costs more than the loads it stands beside, and a build
+says nothing about it.)  No GPU."""
+import struct
+
+import pytest
+
+from paper_2209_02882_amd import binding
+
+msgpack = pytest.importorskip("msgpack")  # the metadata's encoding
+EM_AMDGPU, SHT_NOTE, NT_AMDGPU_METADATA = 224, 7, 32
+
+
+def notes(elf):
+    """(type, description) of every note of an ELF64 image that starts at elf[0]."""
+    section_table, = struct.unpack_from("<Q", elf, 40)
+    sections, = struct.unpack_from("<H", elf, 60)
+    for i in range(sections):
+        kind, = struct.unpack_from("<I", elf, section_table + 64 * i + 4)
+        if kind != SHT_NOTE:
+            continue
+        at, size = struct.unpack_from("<QQ", elf, section_table + 64 * i + 24)
+        end = at + size
+        while at < end:
+            name, desc, note = struct.unpack_from("<III", elf, at)
+            at += 12 + (name + 3) // 4 * 4
+            yield note, elf[at:at + desc]
+            at += (desc + 3) // 4 * 4
+
+
+@pytest.fixture(scope="module")
+def kernels():
+    """Metadata of every kernel: the code objects lie one after the other inside the library."""
+    data = memoryview(open(binding.LIB_PATH, "rb").read())
+    raw, found, at = data.obj, [], 0
+    while (at := raw.find(b"\x7fELF\x02", at)) >= 0:
+        if len(raw) - at > 64 and struct.unpack_from("<H", data, at + 18)[0] == EM_AMDGPU:
+            for note, desc in notes(data[at:]):
+                if note == NT_AMDGPU_METADATA:
+                    found += msgpack.unpackb(desc, strict_map_key=False)["amdhsa.kernels"]
+        at += 4
+    assert len(found) > 1000
+    return found
+
+
+@pytest.mark.parametrize("family", ["nnz_serial_kernel"])
+def test_no_vector_register_is_spilled(kernels, family):
+    mine = [k for k in kernels if family in k[".name"]]
+    assert mine
+    spilled = {k[".name"]: k[".vgpr_spill_count"] for k in mine if k[".vgpr_spill_count"] or k[".private_segment_fixed_size"]}
+    assert not spilled
