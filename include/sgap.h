@@ -148,8 +148,10 @@ int sgap_spmm_csr(int64_t M, int64_t K, int64_t N,
  * optional host-side count of stored entries.
  *   schedule    an sgap_schedule
  *   nnz_hint    rowptr[M] if the caller knows it, else -1.  Only used to size
- *               the nnz-balanced grid (a hint larger than the truth is safe;
- *               a smaller one is also safe, only slower).
+ *               grids and tiles and to choose between launches of the same
+ *               result (rows per group, whether rows can be so long that
+ *               workgroups look for them): a hint larger than the truth is
+ *               safe; a smaller one is also safe, only slower.
  */
 int sgap_spmm_csr_ex(int64_t M, int64_t K, int64_t N,
                      const int32_t* rowptr, const int32_t* colidx, const float* vals,

@@ -60,6 +60,14 @@ struct TileSched {
     int32_t xcds;           // 8, or 1 to switch the remapping off
 };
 
+// The workgroups of a row-split launch.  The first `finders` look for the rows of at least share_from stored entries and
+// produce them with all their lanes; the others walk the work items and pass over such rows.
+struct RowSplitGrid {
+    int32_t share_from;  // 0x7fffffff, which no row reaches, exactly where nobody looks for such rows
+    int32_t finders;
+    uint32_t grid;
+};
+
 template <int VEC>
 struct Vec {
     float v[VEC];
@@ -217,6 +225,10 @@ struct NnzPlan {
 };
 NnzPlan plan_nnz_serial(int group, int lc, int vec, int64_t nnz_hint, int compute_units, int forced_tile);
 NnzPlan plan_nnz_parallel(int group, int lc, int vec);
+// g = lanes per row of a whole-group reduction (1: no rows are shared), passes = passes of a group over its columns,
+// resident = workgroups that fit the chip at once for a persistent launch (0: a workgroup per item).
+RowSplitGrid plan_row_split_grid(int g, int passes, int64_t M, int64_t items, int xcds, int compute_units,
+                                 int64_t nnz_hint, int resident);
 // ---- host-side launchers, one per kernel family (defined in the .hip files)
 // lc = chunk lanes per row (power of two), vec = columns per lane (1, 2, 4).
 // g = lanes per row (1 for the serial strategy), rows_per_slot = rows a group

@@ -27,6 +27,49 @@
 
 namespace sgap {
 
+namespace {
+
+constexpr int kShareMin = 256;    // the shortest row that a whole workgroup takes together
+constexpr int kFinderRows = 64;   // a finder looks at no fewer rows: a wavefront's look
+constexpr int kFindersPerCu = 8;  // as many workgroups as are resident
+
+// A group's rounds of loads on a row of len entries are about len / (g * kDepthGroups) for each pass over the columns,
+// each of them a round trip to memory with a handful of loads in flight.  From a dozen rounds on, the whole workgroup
+// takes the row instead; never a row that is only a few steps of the workgroup long.
+int32_t share_rows_from(int g, int passes)
+{
+    const int len = 12 * g * kDepthGroups / passes;
+    return len < kShareMin ? kShareMin : len;
+}
+
+}  // namespace
+
+// Finders cost a look at every row pointer, so there are none where the caller's count of entries says that no row can
+// be long enough.  That count may be too small: the walk then takes every row, whatever its length (share_from).
+// Finders per compute unit, G = 8: the longest rows of a power law (4,096 entries) bind it otherwise.  65,536 rows,
+// N = 37: 73 us without finders, 70.7 with one, 58.4 with two, 47.5 with four or eight; 114,150 rows, N = 34: 100.5
+// without, 100.4, 90.2 and 82.8 with one, two and four, 72.5 with eight.
+RowSplitGrid plan_row_split_grid(int g, int passes, int64_t M, int64_t items, int xcds, int compute_units,
+                                 int64_t nnz_hint, int resident)
+{
+    RowSplitGrid p = {0x7fffffff, 0, 0};
+    const int64_t items_per_xcd = (items + xcds - 1) / xcds;
+    int64_t wgs_per_xcd = resident > 0 ? (resident / xcds > 0 ? resident / xcds : 1) : items_per_xcd;
+    if (wgs_per_xcd > items_per_xcd) wgs_per_xcd = items_per_xcd;
+    if (wgs_per_xcd * xcds > 0x7ffffff0LL) wgs_per_xcd = 0x7ffffff0LL / xcds;
+    const int64_t walkers = wgs_per_xcd * xcds;
+    const int32_t share_from = share_rows_from(g, passes);
+    if (g > 1 && (nnz_hint < 0 || nnz_hint >= share_from)) {
+        const int64_t most = (int64_t)kFindersPerCu * compute_units;
+        int64_t finders = (M + kFinderRows - 1) / kFinderRows < most ? (M + kFinderRows - 1) / kFinderRows : most;
+        finders = (finders + xcds - 1) / xcds * xcds;  // whole rounds of the dies
+        p.share_from = share_from;
+        p.finders = (int32_t)finders;
+    }
+    p.grid = (uint32_t)(walkers + p.finders);
+    return p;
+}
+
 hipError_t launch_row_split(const SpmmArgs& a, int g, int lc, int vec, int rows_per_slot, bool interleave,
                             int tile_cols, int xcds, int compute_units, bool persistent, int block, int64_t nnz_hint, double mean_row,
                             hipStream_t s)

@@ -19,14 +19,13 @@ constexpr int kDepthRows = 6, kDepthShort = 4, kDepthGroups = 8;
 constexpr double kShortRowMean = 12.0;
 constexpr int kStageCap = 2048;  // (column, value) pairs per LDS chunk: 16 KB
 constexpr int kRowCap = 1024;    // rowptr entries kept in LDS per row block (+1)
-constexpr int kShareMin = 256;   // the shortest row that a whole workgroup takes together
 constexpr int kRowSplitMaxBlock = 512;  // threads per workgroup: 128, 256 or 512, chosen at launch
 
 // One row by the whole workgroup: lc chunk lanes (the power of two that covers the columns, at most a wavefront) and
 // block / lc members, each of which takes every (block / lc)-th stored entry with DEPTH rows of B in flight; members
 // of a wavefront are summed with shuffles, the wavefronts' sums through LDS in a fixed order, and the row has one
 // plain store as ever.  For the rows whose length would keep the one group that owns them busy long after the rest of
-// the chip is done (see share_rows_from).  s_A and s_part may be the same memory.  Block-uniform; barriers inside.
+// the chip is done (see plan_row_split_grid).  s_A and s_part may be the same memory.  Block-uniform; barriers inside.
 template <int VEC, bool OFF32, int DEPTH>
 __device__ __forceinline__ void shared_row(const SpmmArgs& a, int64_t row, uint32_t p_begin, uint32_t p_end,
                                            int64_t k_begin, int64_t k_end, StagedEntry* __restrict__ s_A, int block)
@@ -95,19 +94,16 @@ __device__ __forceinline__ void shared_row(const SpmmArgs& a, int64_t row, uint3
 // (a power of two below G) and the first member of every sub-group adds its
 // sum to C with atomics; C must hold zeros before the launch.
 // SKIP: leave the rows described by `skip` alone.
-// share_from (G > 1, whole-group reductions): rows of at least that many stored entries are left out of the walk; the
-// first `finders` workgroups of the grid look for them, each in an equal stretch of the rows, and produce them one after
-// the other with all their lanes (shared_row).  They start first, so that the longest rows are done while the others
-// are walked: a workgroup that came across one during its walk ended some 40 us behind the rest.  A row of 27,000
-// entries is what binds a power law then; eight finders per compute unit (as many as are resident) leave few rows in
-// sequence: 65,536 rows, N = 37, G = 8: 73 us in the walk, 70.7 with one finder per compute unit, 58.4 with two, 47.5
-// with four or eight; 114,150 rows, N = 34: 100.5, 100.4, 90.2, 82.8 and 72.5 with eight.
+// grid (plan_row_split_grid; G > 1, whole-group reductions): rows of at least share_from stored entries are left out of
+// the walk; the first `finders` workgroups of the grid look for them, each in an equal stretch of the rows, and produce
+// them one after the other with all their lanes (shared_row).  They start first, so that the longest rows are done while
+// the others are walked: a workgroup that came across one during its walk ended some 40 us behind the rest.
 // The workgroup size (the paper's blockSz, Section 7.2) is the launch's: SLOTS = blockDim.x / (G*LC)
 // groups work side by side on the rows of a row block.
 template <int G, int LC, int VEC, bool OFF32, bool PARTIAL, bool SKIP, int DEPTH>
 __global__ __launch_bounds__(kRowSplitMaxBlock) void row_split_kernel(SpmmArgs a, TileSched ts, int rows_per_slot,
                                                                       int interleave, int reduce_members,
-                                                                      int32_t share_from, int finders, RowSkip skip)
+                                                                      RowSplitGrid plan, RowSkip skip)
 {
     __shared__ StagedEntry s_A[kStageCap];
     __shared__ int32_t s_rp[kRowCap + 1];
@@ -130,8 +126,8 @@ __global__ __launch_bounds__(kRowSplitMaxBlock) void row_split_kernel(SpmmArgs a
     if constexpr (SKIP) skip_on = *skip.count <= skip.max_rows;
 
     if constexpr (SHARE) {
-        if ((int)blockIdx.x < finders) {
-            const int64_t per = (a.M + finders - 1) / finders;
+        if ((int)blockIdx.x < plan.finders) {
+            const int64_t per = (a.M + plan.finders - 1) / plan.finders;
             const int64_t first = per * blockIdx.x, last = first + per < a.M ? first + per : a.M;
             for (int64_t r0 = first; r0 < last; r0 += block) {
                 __syncthreads();  // the last rows found are done with
@@ -140,7 +136,7 @@ __global__ __launch_bounds__(kRowSplitMaxBlock) void row_split_kernel(SpmmArgs a
                 const int64_t r = r0 + threadIdx.x;
                 if (r < last) {
                     const int32_t len = a.rowptr[r + 1] - a.rowptr[r];
-                    bool shared = len >= share_from;
+                    bool shared = len >= plan.share_from;
                     if constexpr (SKIP) shared = shared && !(skip_on && len >= skip.min_len);
                     if (shared) s_rp[atomicAdd(&s_found, 1)] = (int32_t)r;
                 }
@@ -156,10 +152,10 @@ __global__ __launch_bounds__(kRowSplitMaxBlock) void row_split_kernel(SpmmArgs a
     }
 
     // persistent walk over this die's run of work items
-    const int64_t wg = blockIdx.x - finders;
+    const int64_t wg = blockIdx.x - plan.finders;
     const int64_t xcd = wg % ts.xcds;
     const int64_t wg_in_xcd = wg / ts.xcds;
-    const int64_t wgs_per_xcd = (gridDim.x - finders) / ts.xcds;
+    const int64_t wgs_per_xcd = (gridDim.x - plan.finders) / ts.xcds;
     for (int64_t it = wg_in_xcd; it < ts.items_per_xcd; it += wgs_per_xcd) {
         const int64_t item = xcd * ts.items_per_xcd + it;
         if (item >= ts.items) break;
@@ -225,7 +221,7 @@ __global__ __launch_bounds__(kRowSplitMaxBlock) void row_split_kernel(SpmmArgs a
                     const uint32_t hi = p_end < base + cnt ? p_end : base + cnt;
                     bool skipped = false;
                     if constexpr (SKIP) skipped = skip_on && p_end - p_begin >= (uint32_t)skip.min_len;
-                    if constexpr (SHARE) skipped = skipped || p_end - p_begin >= (uint32_t)share_from;
+                    if constexpr (SHARE) skipped = skipped || p_end - p_begin >= (uint32_t)plan.share_from;
                     if (!skipped && k_ok && lo < hi) {
                         // first position >= lo that belongs to this member
                         const uint32_t first = lo + ((member - (lo - p_begin)) & (G - 1));
@@ -303,15 +299,6 @@ struct Launch {
         return n;
     }
 
-    // A group's rounds of loads on a row of len entries are about len / (G * 6) for each pass over the columns,
-    // each of them a round trip to memory with a handful of loads in flight.  From about sixteen rounds on, the whole
-    // workgroup takes the row instead; never a row that is only a few steps of the workgroup long.
-    static int32_t share_rows_from(int g, int passes)
-    {
-        const int len = 16 * g * 6 / passes;
-        return len < kShareMin ? kShareMin : len;
-    }
-
     template <int G, int LC, int VEC>
     void operator()() const
     {
@@ -325,9 +312,9 @@ struct Launch {
     void go() const
     {
         // a persistent grid must be resident all at once (asked of the runtime only for such launches)
-        int max_grid = 0x7fffffff;
+        int resident = 0;
         if (persistent)
-            max_grid = compute_units * (off32 ? resident_per_cu(row_split_kernel<G, LC, VEC, true, PARTIAL, SKIP, DEPTH>, block)
+            resident = compute_units * (off32 ? resident_per_cu(row_split_kernel<G, LC, VEC, true, PARTIAL, SKIP, DEPTH>, block)
                                               : resident_per_cu(row_split_kernel<G, LC, VEC, false, PARTIAL, SKIP, DEPTH>, block));
         const int slots = block / (G * LC);
         const int64_t rows_per_block = (int64_t)slots * rows_per_slot;
@@ -339,24 +326,15 @@ struct Launch {
         ts.xcds = xcds;
         ts.items_per_xcd = (ts.items + xcds - 1) / xcds;
         const int passes = (int)(((int64_t)tile_cols + LC * VEC - 1) / (LC * VEC));
-        // rows that whole workgroups take, and the workgroups that look for them (whole rounds of the dies)
-        const int32_t share_from = share_rows_from(G, passes);
-        int finders = 0;
-        if (G > 1 && !PARTIAL && (nnz_hint < 0 || nnz_hint >= share_from)) {
-            const int64_t most = 8LL * compute_units;  // and no fewer than 64 rows each: a wavefront's look
-            finders = (int)((a.M + 63) / 64 < most ? (a.M + 63) / 64 : most);
-            finders = (finders + xcds - 1) / xcds * xcds;
-        }
-        int64_t wgs_per_xcd = max_grid / xcds > 0 ? max_grid / xcds : 1;
-        if (wgs_per_xcd * xcds > 0x7ffffff0LL) wgs_per_xcd = 0x7ffffff0LL / xcds;
-        if (wgs_per_xcd > ts.items_per_xcd) wgs_per_xcd = ts.items_per_xcd;
-        const unsigned grid = (unsigned)(wgs_per_xcd * xcds + finders);
+        const RowSplitGrid plan =
+            plan_row_split_grid(PARTIAL ? 1 : G, passes, a.M, ts.items, xcds, compute_units, nnz_hint, resident);
+        const uint32_t grid = plan.grid;
         if (off32)
             hipLaunchKernelGGL((row_split_kernel<G, LC, VEC, true, PARTIAL, SKIP, DEPTH>), dim3(grid), dim3(block), 0, s, a,
-                               ts, rows_per_slot, interleave, reduce_members, share_from, finders, skip);
+                               ts, rows_per_slot, interleave, reduce_members, plan, skip);
         else
             hipLaunchKernelGGL((row_split_kernel<G, LC, VEC, false, PARTIAL, SKIP, DEPTH>), dim3(grid), dim3(block), 0, s, a,
-                               ts, rows_per_slot, interleave, reduce_members, share_from, finders, skip);
+                               ts, rows_per_slot, interleave, reduce_members, plan, skip);
     }
 };
 
