@@ -204,7 +204,9 @@ int sgap_spmm_csr_gr(int64_t M, int64_t K, int64_t N,
  *                   so that its L2 keeps the rows of B it gathers; 0: plain
  *                   round-robin order.
  *   persistent      1: the row-split schedule launches only as many workgroups
- *                   as the chip holds at once and each loops over work items.
+ *                   as the chip holds at once and each loops over work items
+ *                   (in the parallel strategy after it has looked through its
+ *                   share of the rows for long ones).
  *   nnz_tile        stored entries per tile of the nnz-balanced serial strategy:
  *                   256, 512, 1024 or 2048 (the two small ones need N >= 4, else
  *                   the automatic choice is kept).

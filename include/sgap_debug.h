@@ -51,7 +51,7 @@ int sgap_debug_group_seg_reduce(const float* in, const int32_t* span, float* out
                                 int group_size, int lanes_per_row, void* stream);
 
 /*
- * Host-side pieces of the nnz-balanced schedule, exported for tests; no GPU
+ * Host-side pieces of the schedules, exported for tests; no GPU
  * is touched.
  *   sgap_debug_tile_deal: which tiles of stored entries workgroup `block` of a
  *     persistent grid of `grid` workgroups takes when the matrix has `tiles`
@@ -65,11 +65,21 @@ int sgap_debug_group_seg_reduce(const float* in, const int32_t* span, float* out
  *     strategy with lanes_per_row chunk lanes of cols_per_lane columns each on
  *     a chip of compute_units; forced_tile as sgap_config.nnz_tile.  Host
  *     pointers; lanes_used may be null.
+ *   sgap_debug_plan_row_split: the grid of a row-split launch with
+ *     lanes_per_row lanes per row and `passes` passes over its columns, for M
+ *     rows in `items` work items: the first `finders` of `grid` workgroups
+ *     look for the rows of at least share_from stored entries and produce them
+ *     whole; the workgroups from walk_from on walk the items and leave such
+ *     rows out.  resident: workgroups that the chip holds at once, for a
+ *     persistent grid (0: a workgroup per item).  Host pointers.
  */
 int64_t sgap_debug_tile_deal(int64_t tiles, int grid, int block, int64_t* out_tiles, int64_t capacity);
 int sgap_debug_plan_nnz_serial(int group_size, int lanes_per_row, int cols_per_lane, int64_t nnz_hint,
                                int compute_units, int forced_tile, int* tile, int* merge_on_chip,
                                int* lanes_used);
+int sgap_debug_plan_row_split(int lanes_per_row, int passes, int64_t M, int64_t items, int dies, int compute_units,
+                              int64_t nnz_hint, int resident, int64_t* share_from, int64_t* finders,
+                              int64_t* walk_from, int64_t* grid);
 
 /*
  * Streaming kernels over n fp32 elements (16-byte aligned device buffers):

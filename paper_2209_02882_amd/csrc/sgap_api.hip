@@ -993,6 +993,22 @@ int sgap_debug_plan_nnz_serial(int group_size, int lanes_per_row, int cols_per_l
     return SGAP_OK;
 }
 
+int sgap_debug_plan_row_split(int lanes_per_row, int passes, int64_t M, int64_t items, int dies, int compute_units_,
+                              int64_t nnz_hint, int resident, int64_t* share_from, int64_t* finders, int64_t* walk_from,
+                              int64_t* grid)
+{
+    if (!is_pow2_group(lanes_per_row) || passes < 1 || M < 1 || items < 1 || dies < 1 || compute_units_ < 1 ||
+        nnz_hint < -1 || resident < 0 || !share_from || !finders || !walk_from || !grid)
+        return fail(SGAP_ERR_INVALID_ARG, "bad plan arguments");
+    const sgap::RowSplitGrid p =
+        sgap::plan_row_split_grid(lanes_per_row, passes, M, items, dies, compute_units_, nnz_hint, resident);
+    *share_from = p.share_from;
+    *finders = p.finders;
+    *walk_from = p.walk_from;
+    *grid = p.grid;
+    return SGAP_OK;
+}
+
 int64_t sgap_reorder_rows_workspace_size(int64_t M)
 {
     if (M < 0) {

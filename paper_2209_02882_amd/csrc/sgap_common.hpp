@@ -61,10 +61,11 @@ struct TileSched {
 };
 
 // The workgroups of a row-split launch.  The first `finders` look for the rows of at least share_from stored entries and
-// produce them with all their lanes; the others walk the work items and pass over such rows.
+// produce them with all their lanes; those from number walk_from on walk the work items and pass over such rows.
 struct RowSplitGrid {
     int32_t share_from;  // 0x7fffffff, which no row reaches, exactly where nobody looks for such rows
     int32_t finders;
+    int32_t walk_from;   // = finders; 0 on a persistent grid, whose workgroups look for rows first and then walk
     uint32_t grid;
 };
 

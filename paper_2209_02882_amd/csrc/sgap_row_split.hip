@@ -52,7 +52,7 @@ int32_t share_rows_from(int g, int passes)
 RowSplitGrid plan_row_split_grid(int g, int passes, int64_t M, int64_t items, int xcds, int compute_units,
                                  int64_t nnz_hint, int resident)
 {
-    RowSplitGrid p = {0x7fffffff, 0, 0};
+    RowSplitGrid p = {0x7fffffff, 0, 0, 0};
     const int64_t items_per_xcd = (items + xcds - 1) / xcds;
     int64_t wgs_per_xcd = resident > 0 ? (resident / xcds > 0 ? resident / xcds : 1) : items_per_xcd;
     if (wgs_per_xcd > items_per_xcd) wgs_per_xcd = items_per_xcd;
@@ -62,11 +62,17 @@ RowSplitGrid plan_row_split_grid(int g, int passes, int64_t M, int64_t items, in
     if (g > 1 && (nnz_hint < 0 || nnz_hint >= share_from)) {
         const int64_t most = (int64_t)kFindersPerCu * compute_units;
         int64_t finders = (M + kFinderRows - 1) / kFinderRows < most ? (M + kFinderRows - 1) / kFinderRows : most;
-        finders = (finders + xcds - 1) / xcds * xcds;  // whole rounds of the dies
+        if (resident > 0) {
+            // a persistent grid is resident all at once: its own workgroups are the finders
+            if (finders > walkers) finders = walkers;
+        } else {
+            finders = (finders + xcds - 1) / xcds * xcds;  // whole rounds of the dies
+            p.walk_from = (int32_t)finders;
+        }
         p.share_from = share_from;
         p.finders = (int32_t)finders;
     }
-    p.grid = (uint32_t)(walkers + p.finders);
+    p.grid = (uint32_t)(walkers + p.walk_from);
     return p;
 }
 

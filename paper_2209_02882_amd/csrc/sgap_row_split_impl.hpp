@@ -147,15 +147,15 @@ __global__ __launch_bounds__(kRowSplitMaxBlock) void row_split_kernel(SpmmArgs a
                     shared_row<VEC, OFF32, DEPTH>(a, row, (uint32_t)a.rowptr[row], (uint32_t)a.rowptr[row + 1], 0, N, s_A, block);
                 }
             }
-            return;
+            if ((int)blockIdx.x < plan.walk_from) return;
         }
     }
 
     // persistent walk over this die's run of work items
-    const int64_t wg = blockIdx.x - plan.finders;
+    const int64_t wg = blockIdx.x - plan.walk_from;
     const int64_t xcd = wg % ts.xcds;
     const int64_t wg_in_xcd = wg / ts.xcds;
-    const int64_t wgs_per_xcd = (gridDim.x - plan.finders) / ts.xcds;
+    const int64_t wgs_per_xcd = (gridDim.x - plan.walk_from) / ts.xcds;
     for (int64_t it = wg_in_xcd; it < ts.items_per_xcd; it += wgs_per_xcd) {
         const int64_t item = xcd * ts.items_per_xcd + it;
         if (item >= ts.items) break;
