@@ -8,15 +8,18 @@
 // plainly, the others are combined per tile in LDS, and only slices that reach beyond the tile use global atomics.
 //
 // What bounds it is the gathers of rows of X2 (a factor that does not fit a die's L2 comes from the Infinity Cache); what
-// kept it from that was its own control flow: a fiber holds a handful of entries, and with a second sum per fiber the
-// eight entry lanes of a wavefront close a fiber at two of three steps, each in a branch of its own.  So:
-//   - a tile's fibers (a thread each) find their slice and bring their row of X1 into LDS, once per tile; an entry's
-//     product is (v * X1[k,:]) * X2[l,:] with the row of X1 out of LDS, and nothing happens where a fiber ends;
-//   - where a slice ends is marked in the entry's fiber number, so that a step without such an end has no branch;
+// kept it from that was its own control flow: a fiber holds a handful of entries, and the eight entry lanes of a wavefront
+// close a fiber at two of three steps.  So a step does little beside its gather and multiply-add:
+//   - a tile's fibers (a thread each) find their slice and bring their row of X1 into LDS, once per tile, from where
+//     t[f,:] is scaled when the fiber ends;
+//   - where a fiber and where a slice ends is marked in the entry's fiber number;
 //   - the next tile's entries, fiber pointers and slice pointers are requested before this tile is multiplied out.
 // A tile with more fibers than LDS has rows for is cut into pieces of that many fibers, each merged by itself.
-// 262,144 slices, one in a thousand with 2,000 to 20,000 fibers, J = 32, G = 32: 871 us with a 16-byte record per entry
-// (two bisections and three loads each) and two searches per tile, 657 with fibers looked up once and a sum per fiber.
+// 262,144 slices, one in a thousand with 2,000 to 20,000 fibers, J = 32, G = 32: 873 us with a 16-byte record per entry
+// (two bisections and three loads each) and two searches per tile, 540 now.  (v * X1[k,:]) * X2[l,:] added up entry by
+// entry, with nothing to do where a fiber ends, takes as long; it rounds once more per entry and adds in one long chain
+// (mean error 1.82e-8 of the sum of absolute values against 1.56e-8), and v * X1[k,:] may leave the range of the numbers
+// where no t[f,:] does.
 #include "sgap_gather.hpp"
 #include "sgap_nnz_common.hpp"
 
@@ -28,7 +31,9 @@ constexpr int kMsBatch = 64;             // tiles whose first fibers and slices 
 constexpr int kMsFibers = kBlock - 1;    // fibers of a piece at most: a thread each, and a pointer more
 constexpr int kMsSlices = kBlock - 1;    // slices whose pointers a tile keeps (a fiber beyond them bisects the pointers)
 constexpr int kMsX1Bytes = 35 * 512;     // rows of X1 in LDS: 140 of 128 bytes (four workgroups per compute unit)
-constexpr uint16_t kMsEnds = 1 << 15;    // the slice ends with this entry
+constexpr uint16_t kMsEnds = 1 << 15;       // the slice ends with this entry
+constexpr uint16_t kMsFiberEnds = 1 << 14;  // the fiber does
+constexpr int kMsFiberMask = kMsFiberEnds - 1;
 
 // LDS place of a tile's entry: the entry lanes of a wavefront read at strides of g entries, which without the padding
 // all fall on the same banks.
@@ -44,7 +49,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
     constexpr int PITCH = LC * VEC;
     extern __shared__ __align__(16) unsigned char s_raw[];
     __shared__ StagedEntry s_A[kMsTile + (kMsTile >> 5)];
-    __shared__ __align__(16) uint16_t s_fiber[kMsTile];  // an entry's fiber, counted from the piece's first, and kMsEnds
+    __shared__ __align__(16) uint16_t s_fiber[kMsTile];  // an entry's fiber, counted from the piece's first, and the two marks
     __shared__ int32_t s_fwin[kMsFibers + 1];  // first positions of the piece's fibers
     __shared__ int32_t s_k[kMsFibers];         // their rows of X1
     __shared__ int32_t s_i[kMsFibers];         // their slices
@@ -181,7 +186,8 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
                     for (int i = 0; i < kMsEpt; ++i) {
                         if (p + i < base || p + i >= end) continue;
                         while (s_fwin[w + 1] <= p + i) ++w;  // ends: some fiber of the piece holds the entry
-                        s_fiber[tid * kMsEpt + i] = (uint16_t)(w | (s_end[w] == p + i + 1 ? kMsEnds : 0));
+                        s_fiber[tid * kMsEpt + i] = (uint16_t)(
+                            w | (s_fwin[w + 1] == p + i + 1 ? kMsFiberEnds : 0) | (s_end[w] == p + i + 1 ? kMsEnds : 0));
                     }
                 }
                 __syncthreads();
@@ -203,11 +209,12 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
                     const int32_t blk_end = blk + GROUP < end ? blk + GROUP : end;
                     if (k_ok && blk_begin < blk_end) {
                         int32_t run_begin = blk_begin;  // where the slice's run in this share begins
-                        Vec<VEC> sum;
+                        Vec<VEC> sum, t;  // of the slice's fibers, of the fiber's entries
                         sum.zero();
+                        t.zero();
                         // the run that ends with entry p leaves the registers
                         auto flush = [&](int32_t p, int fiber) {
-                            const int w = fiber & (kMsEnds - 1);
+                            const int w = fiber & kMsFiberMask;
                             const bool ends = (fiber & kMsEnds) != 0;
                             const int32_t row = s_i[w], begin = s_begin[w];
                             if (ends && begin == run_begin) {
@@ -257,19 +264,23 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
 #pragma unroll
                             for (int u = 0; u < D; ++u) {
                                 if (!full && !mine(u)) continue;
-                                const float* x = my_x1 + (fiber[u] & (kMsEnds - 1)) * PITCH;
-                                if constexpr (VEC == 4) {
-                                    const float4 t = *reinterpret_cast<const float4*>(x);
-                                    sum.v[0] = __builtin_fmaf(e[u].val * t.x, b[u].v[0], sum.v[0]);
-                                    sum.v[1] = __builtin_fmaf(e[u].val * t.y, b[u].v[1], sum.v[1]);
-                                    sum.v[2] = __builtin_fmaf(e[u].val * t.z, b[u].v[2], sum.v[2]);
-                                    sum.v[3] = __builtin_fmaf(e[u].val * t.w, b[u].v[3], sum.v[3]);
-                                } else {
+                                t.fma(e[u].val, b[u]);
+                                const bool last = p0 + u + 1 == blk_end;
+                                if ((fiber[u] & kMsFiberEnds) || last) {
+                                    const float* x = my_x1 + (fiber[u] & kMsFiberMask) * PITCH;
+                                    if constexpr (VEC == 4) {
+                                        const float4 f = *reinterpret_cast<const float4*>(x);
+                                        sum.v[0] = __builtin_fmaf(f.x, t.v[0], sum.v[0]);
+                                        sum.v[1] = __builtin_fmaf(f.y, t.v[1], sum.v[1]);
+                                        sum.v[2] = __builtin_fmaf(f.z, t.v[2], sum.v[2]);
+                                        sum.v[3] = __builtin_fmaf(f.w, t.v[3], sum.v[3]);
+                                    } else {
 #pragma unroll
-                                    for (int v = 0; v < VEC; ++v) sum.v[v] = __builtin_fmaf(e[u].val * x[v], b[u].v[v], sum.v[v]);
+                                        for (int v = 0; v < VEC; ++v) sum.v[v] = __builtin_fmaf(x[v], t.v[v], sum.v[v]);
+                                    }
+                                    t.zero();
+                                    if ((fiber[u] & kMsEnds) || last) flush(p0 + u, fiber[u]);
                                 }
-                                if ((fiber[u] & kMsEnds) || p0 + u + 1 == blk_end) flush(p0 + u, fiber[u]);
-
                             }
                         }
                     }
