@@ -1,8 +1,10 @@
 """Binding of libsgap.so: argument marshalling only.
 
-The compute calls go through a small native module (csrc/sgap_python.cpp), which reads the tensors and calls the
-library in a few hundred nanoseconds; whatever it does not take (another type, a wrong length, a stream of the
-caller's) goes through ctypes and the checks below, which say what is wrong.
+sgap_spmm_csr_ex, sgap_spmm_csr_cfg, sgap_sddmm_csr, sgap_sddmm_csr_windows, sgap_ttm_csf and sgap_mttkrp_csf_ex go
+through a small native module (csrc/sgap_python.cpp), which reads the tensors and calls the library in a few hundred
+nanoseconds; what it does not take (another type, a wrong length, a number that is no int) goes through ctypes and the
+checks below, which say what is wrong.  The other calls, and all of them where that module has not been built, go
+through ctypes: about 8 us of host time each.
 
 Function names mirror the C ABI in include/sgap.h.  Tensors are torch CUDA
 tensors (used purely as device memory); every computation happens in the HIP
@@ -100,8 +102,15 @@ def load():
     return _lib
 
 
+class _TakesNothing:
+    """In the native module's place where that is missing: every call is left to ctypes."""
+
+    def __getattr__(self, name):
+        return lambda *args: -1
+
+
 def _load_native():
-    """The native module (once).  Raises if it has not been built: there is no other quick way."""
+    """The native module (once); without it the calls work all the same, and a warning says that they are slow."""
     global _native
     if _native is None:
         import torch  # noqa: F401  (its libraries have to be there first)
@@ -110,7 +119,11 @@ def _load_native():
         try:
             from . import _native as module
         except ImportError as e:
-            raise RuntimeError("the native module is missing: build it with `python -m paper_2209_02882_amd.build`") from e
+            import warnings
+
+            warnings.warn(f"calls go through ctypes, about 8 us each: the native module cannot be loaded ({e}); build it "
+                          "with `python -m paper_2209_02882_amd.build`", RuntimeWarning, stacklevel=3)
+            module = _TakesNothing()
         _native = module
     return _native
 
