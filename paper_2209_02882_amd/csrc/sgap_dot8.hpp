@@ -58,30 +58,26 @@ __device__ __forceinline__ float last_steps(float v)
 template <int S, int V>
 __device__ __forceinline__ void dot8_steps(float (&v)[8])
 {
-    if constexpr (V > 1 && S >= 1) {
+    if constexpr (V > 1) {
 #pragma unroll
         for (int i = 0; i < V / 2; ++i) v[i] = pair_step<S>(v[i], v[i + V / 2]);
         dot8_steps<S / 2, V / 2>(v);
-    } else if constexpr (V == 1) {
+    } else {
         v[0] = last_steps<S>(v[0]);
     }
 }
 
-// Sums left per lane after dot8_reduce: one from eight lanes on, else two (LC = 4).
-template <int LC>
-constexpr int dot8_left() { return LC >= 8 ? 1 : 8 / LC; }
-
-// Afterwards v[j], j < dot8_left<LC>(), is complete in the lanes with dot8_writer() and belongs to the sum number
-// dot8_number() + j of the eight.  All lanes of the wavefront call together.
+// Afterwards v[0] is complete in the lanes with dot8_writer() and belongs to the sum number dot8_number() of the eight.
+// All lanes of the wavefront call together.
 template <int LC>
 __device__ __forceinline__ void dot8_reduce(float (&v)[8])
 {
-    static_assert(LC >= 4 && LC <= 64, "4 to 64 lanes");
+    static_assert(LC >= 8 && LC <= 64, "8 to 64 lanes");
     dot8_steps<LC / 2, 8>(v);
 }
 template <int LC>
-__device__ __forceinline__ bool dot8_writer(int chunk) { return LC <= 8 || chunk % (LC / 8) == 0; }
+__device__ __forceinline__ bool dot8_writer(int chunk) { return chunk % (LC / 8) == 0; }
 template <int LC>
-__device__ __forceinline__ int dot8_number(int chunk) { return LC >= 8 ? chunk / (LC / 8) : chunk * (8 / LC); }
+__device__ __forceinline__ int dot8_number(int chunk) { return chunk / (LC / 8); }
 
 }  // namespace sgap
