@@ -857,6 +857,9 @@ __device__ __forceinline__ void wave_dot8(const UniformRows<4, OFF32>& rows, con
 // SDDMM with owner wavefronts, as panel_owner_kernel has them for SpMM (same deal of the rows, same walk through the
 // windows, same barrier per window): for dense rows of 129 to 256 columns and lists long enough.  What a wavefront keeps
 // of its ten rows is their rows of X1 instead of their sums, and every entry is written when it is done: no atomics.
+// Registers: ten rows of X1, their entries and a batch of eight gathers fill the 128 that a workgroup of 1,024 threads
+// has.  The instance for J = 256 keeps two of them in memory; the form that does not (the lane's place among the eight
+// sums computed anew for each batch, 125 registers) takes 2,743 us on the skewed matrix where this one takes 2,726.
 template <bool OFF32, bool EDGE>
 __global__ __launch_bounds__(kOwnerBlock) void panel_sddmm_owner_kernel(const int32_t* __restrict__ colidx,
                                                                         const float* __restrict__ vals,

@@ -228,7 +228,9 @@ __global__ __launch_bounds__(kBlock) void sddmm_kernel(SddmmArgs s, int per_lane
 // a workgroup takes the rows one after the other, so that only consecutive columns hit, and asks the L2 for twice the
 // lines that SpMM's row-split kernel does with eight rows in step.  A kernel with the rows in step ran 740 us here but
 // took two to three times as long on R-MAT, whose heavy rows sit together.
-// EDGE: J is not S*G*4 (lanes without columns, or a ragged last chunk).
+// EDGE: J is not S*G*4 (lanes without columns, or a ragged last chunk).  Those instances with S = 4 and 512 entries keep
+// two registers in memory; computed anew per tile, what they hold costs more (R-MAT of 2^19 rows, J = 35, G = 4: 165.9
+// us against 164.8).
 template <int G, int S, bool EDGE, int EPT>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) void sddmm_tile_kernel(SddmmArgs s, int x1_rows)
 {

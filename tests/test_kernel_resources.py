@@ -43,9 +43,11 @@ def kernels():
     return found
 
 
-@pytest.mark.parametrize("family", ["nnz_serial_kernel"])
-def test_no_vector_register_is_spilled(kernels, family):
-    mine = [k for k in kernels if family in k[".name"]]
-    assert mine
-    spilled = {k[".name"]: k[".vgpr_spill_count"] for k in mine if k[".vgpr_spill_count"] or k[".private_segment_fixed_size"]}
-    assert not spilled
+# instances with two registers in memory, faster than the forms without (beside the kernels in sgap_panels.hip and
+# sgap_sddmm.hip)
+KNOWN = {"panel_sddmm_owner_kernelILb1ELb0E": 2, **{f"sddmm_tile_kernelILi{g}ELi4ELb1ELi2E": 2 for g in (2, 4, 8, 16, 32)}}
+
+
+def test_no_vector_register_is_spilled(kernels):
+    spilled = {k[".name"]: k[".vgpr_spill_count"] for k in kernels if k[".vgpr_spill_count"] or k[".private_segment_fixed_size"]}
+    assert not {name: n for name, n in spilled.items() if n > max([0] + [KNOWN[part] for part in KNOWN if part in name])}
