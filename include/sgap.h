@@ -82,9 +82,16 @@ typedef enum {
  *   operations.
  *     row-split schedule   : the group_size lanes share one row
  *       ({<1/g row, c col>, r} with g = r = group_size, Section 6.2); a plain
- *       tree sum, one writeback lane, plain store.  (A row of many thousand
- *       entries is shared by all groups of its workgroup instead of holding
- *       one of them up; it still has one plain store.)
+ *       tree sum, one writeback lane, plain store.  A row has a wavefront's 64
+ *       lanes at most, and its columns come first: a tile of T columns (128
+ *       unless tile_cols says otherwise, N if that is less) takes L = T/4 of
+ *       them, rounded up to a power of two, and the group has
+ *       g = min(group_size, 64/L) members.  So at N >= 128 every group_size
+ *       from 2 on names the same launch, with two members; a narrower
+ *       tile_cols admits more.  A row of at least 96*g entries (or fewer where
+ *       a tile takes several passes, never below 256) is taken by a whole
+ *       workgroup instead of holding one group up; it still has one plain
+ *       store.
  *     nnz-balanced schedule: lane = one stored entry ({<1 nnz, c col>, r},
  *       Section 6.2); the group performs a SEGMENTED reduction keyed by row
  *       (Fig. 1c), one writeback lane per run of equal rows.
@@ -94,7 +101,9 @@ typedef enum {
  *     row-split schedule   : lane = group_size consecutive rows
  *       ({<g row, c col>, 1}, Section 6.1), plain stores.
  *     nnz-balanced schedule: lane = group_size consecutive stored entries
- *       ({<g nnz, c col>, 1}, Section 6.1).
+ *       ({<g nnz, c col>, 1}, Section 6.1), or fewer where that many per lane
+ *       are more than a tile has (a tile of 1,024 entries at N = 64 has 64 for
+ *       each of 16 lanes; small matrices get smaller tiles).
  *
  * In the nnz-balanced schedule a row whose stored entries all lie inside one
  * aligned block of positions (group_size positions, or a whole tile of about a
@@ -169,7 +178,8 @@ int sgap_spmm_csr_ex(int64_t M, int64_t K, int64_t N,
  * lane adds its own sum: the group is parallelised with the "Atomics" output
  * strategy alone, as in the schedule printed in Section 6.2).  r = g is
  * sgap_spmm_csr_ex with the parallel strategy and the row-split schedule:
- * plain stores, no atomics.  For r < g the library zeroes C first, and the
+ * plain stores, no atomics, and as many members as that has; for r < g the g
+ * lanes are kept and wide rows take more passes.  For r < g the library zeroes C first, and the
  * order of the atomic adds, hence the fp32 rounding, varies between runs.
  * Other arguments, ownership and errors as for sgap_spmm_csr_ex.
  */
@@ -468,7 +478,8 @@ int sgap_mttkrp_csf_ex(int64_t I, int64_t K, int64_t L, int64_t J, const int32_t
  * fastest.  Each point runs once, timed, as a warm-up and,
  * unless that run was more than 4 times slower than the best point so far,
  * `reps` more times (reps >= 1); its time is the minimum over its timed runs and
- * includes the row-zeroing pass of the nnz-balanced schedule.
+ * includes the row-zeroing pass of the nnz-balanced schedule.  Points that name
+ * the same launch (see SGAP_REDUCE_PARALLEL) are each timed.
  *   table  host, NULL or room for SGAP_NUM_POINTS entries, filled in the order
  *          schedule (row-split first), strategy (parallel first), group size
  *          ascending.

@@ -32,8 +32,8 @@
 
 namespace sgap {
 
-constexpr int kMttkrpStagedDepth = 6;  // ... when they come from LDS
 constexpr int kMttkrpDepth = 4;  // gathered rows of X2 in flight per lane when entries come straight from memory
+constexpr int kMttkrpStagedDepth = 6;  // ... when they come from LDS
 
 // LDS copies of a block of slices: its slice pointers, its fibers (second index
 // and entry pointer) and its entries.  A block that does not fit is worked
