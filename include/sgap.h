@@ -576,8 +576,8 @@ int sgap_version(void);
  *                        nnz and the size of the chip.
  *   SGAP_TUNE_SDDMM_ROW_CACHE  1 (default): sgap_sddmm_csr's parallel strategy
  *                        hands a group consecutive stored entries and keeps
- *                        the current row of X1 in registers when
- *                        4 <= J <= 16 * group_size; 0: every entry loads
+ *                        the rows of X1 that a tile of entries touches in LDS
+ *                        when 4 <= J <= 16 * group_size; 0: every entry loads
  *                        both of its rows.
  * Knobs 6 and 7 (long rows by column windows) of earlier versions are gone:
  * that path needs working memory and is chosen per call, see sgap_config;

@@ -216,7 +216,7 @@ thread_local char t_last_error[256] = "";
 int g_tile_cols = 0;
 int g_xcd_remap = -1;  // -1 auto (on), 0 off, 1 on
 int g_rows_per_slot = 0;
-int g_sddmm_row_cache = 1;  // SDDMM parallel: keep rows of X1 in registers where the shape allows
+int g_sddmm_row_cache = 1;  // SDDMM parallel: keep rows of X1 in LDS where the shape allows
 int g_nnz_tile = 0;    // nnz-balanced serial: forced tile size, 0 = automatic
 int g_persistent = 0;  // row-split: one workgroup per item keeps the rows in flight on a die close together
 

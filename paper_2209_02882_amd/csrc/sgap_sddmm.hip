@@ -14,10 +14,12 @@
 // Every output has exactly one writer: no atomics, no zeroing.
 //
 // The unit of work is a stored entry, so the schedule is nnz-balanced by
-// construction: tiles of 1024 entries are dealt to persistent workgroups
+// construction: tiles of 256 to 1,024 entries are dealt to persistent workgroups
 // (chunks of neighbouring tiles per die, see TileDeal), the rows of a tile's entries come from a bisection of rowptr
 // for the tile's first entry and an LDS window of rowptr for the rest (the
-// same pieces as the nnz-balanced SpMM kernels).
+// same pieces as the nnz-balanced SpMM kernels).  sddmm_tile_kernel has the
+// parallel strategy wherever four steps of its lanes cover a dense row,
+// sddmm_kernel has the rest.
 #include <type_traits>
 
 #include "sgap_common.hpp"
@@ -530,10 +532,9 @@ bool launch_vec(const SddmmArgs& s, int vec, int per_lane, int compute_units, in
 
 // a: M, K, N = J, rowptr, colidx, vals, B = X2T (C unused).  g = lanes per
 // stored entry (parallel strategy, per_lane = 0) or 1 with per_lane = entries
-// per lane (serial strategy).  vec = columns per lane and load (4, 2 or 1;
-// J % vec == 0 and matching alignment of X1 and X2T).
-// row_cache: let the parallel strategy keep rows of X1 in registers where the
-// shape allows it.
+// per lane (serial strategy).  vec = columns per lane and load (lane_columns(J)).
+// row_cache: let the parallel strategy keep the rows of X1 that a tile touches
+// in LDS where the shape allows it.
 hipError_t launch_sddmm(const SpmmArgs& a, const float* X1, float* out, int g, int per_lane, int vec, bool row_cache,
                         int compute_units, int64_t nnz_hint, hipStream_t stream)
 {
