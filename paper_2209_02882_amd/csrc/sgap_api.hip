@@ -1009,6 +1009,25 @@ int sgap_debug_plan_row_split(int lanes_per_row, int passes, int64_t M, int64_t 
     return SGAP_OK;
 }
 
+int64_t sgap_debug_finder_rows(int64_t M, int finders, int finder, int64_t* out_rows, int64_t capacity)
+{
+    if (M < 1 || M > 2147483646LL || finders < 1 || finder < 0 || finder >= finders || capacity < 0 ||
+        (capacity > 0 && !out_rows)) {
+        fail(SGAP_ERR_INVALID_ARG, "bad finder arguments");
+        return -1;
+    }
+    const sgap::FinderDeal deal(M);
+    int64_t n = 0;
+    const uint32_t last = deal.first_place((uint32_t)finder + 1, (uint32_t)finders);
+    for (uint32_t p = deal.first_place((uint32_t)finder, (uint32_t)finders); p < last; ++p)
+        for (uint32_t r = 0; r < sgap::FinderDeal::kUnit; ++r)
+            if (deal.row(p, r) < M) {
+                if (n < capacity) out_rows[n] = deal.row(p, r);
+                ++n;
+            }
+    return n;
+}
+
 int64_t sgap_reorder_rows_workspace_size(int64_t M)
 {
     if (M < 0) {

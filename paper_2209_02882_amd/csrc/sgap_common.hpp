@@ -5,6 +5,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "sgap_tile_deal.hpp"
+
 namespace sgap {
 
 constexpr int kWave = 64;          // wavefront size on gfx950
@@ -65,6 +67,7 @@ struct TileSched {
 struct RowSplitGrid {
     int32_t share_from;  // 0x7fffffff, which no row reaches, exactly where nobody looks for such rows
     int32_t finders;
+    FinderDeal deal;     // which rows each of them looks through
     int32_t walk_from;   // = finders; 0 on a persistent grid, whose workgroups look for rows first and then walk
     uint32_t grid;
 };

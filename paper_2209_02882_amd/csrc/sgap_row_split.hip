@@ -30,7 +30,8 @@ namespace sgap {
 namespace {
 
 constexpr int kShareMin = 256;    // the shortest row that a whole workgroup takes together
-constexpr int kFinderRows = 64;   // a finder looks at no fewer rows: a wavefront's look
+constexpr int kFinderRows = 64;   // a finder looks at no fewer rows (32 cost matrices without long rows: 10,000 rows of 16
+                                  // entries, N = 32, G = 8 6.3 -> 6.7 us)
 constexpr int kFindersPerCu = 8;  // as many workgroups as are resident
 
 // A group's rounds of loads on a row of len entries are about len / (g * kDepthGroups) for each pass over the columns,
@@ -48,11 +49,12 @@ int32_t share_rows_from(int g, int passes)
 // be long enough.  That count may be too small: the walk then takes every row, whatever its length (share_from).
 // Finders per compute unit, G = 8: the longest rows of a power law (4,096 entries) bind it otherwise.  65,536 rows,
 // N = 37: 73 us without finders, 70.7 with one, 58.4 with two, 47.5 with four or eight; 114,150 rows, N = 34: 100.5
-// without, 100.4, 90.2 and 82.8 with one, two and four, 72.5 with eight.
+// without, 100.4, 90.2 and 82.8 with one, two and four, 72.5 with eight (a stretch of rows for each; FinderDeal says
+// what dealing them out changed).
 RowSplitGrid plan_row_split_grid(int g, int passes, int64_t M, int64_t items, int xcds, int compute_units,
                                  int64_t nnz_hint, int resident)
 {
-    RowSplitGrid p = {0x7fffffff, 0, 0, 0};
+    RowSplitGrid p = {0x7fffffff, 0, FinderDeal(M), 0, 0};
     const int64_t items_per_xcd = (items + xcds - 1) / xcds;
     int64_t wgs_per_xcd = resident > 0 ? (resident / xcds > 0 ? resident / xcds : 1) : items_per_xcd;
     if (wgs_per_xcd > items_per_xcd) wgs_per_xcd = items_per_xcd;

@@ -95,8 +95,8 @@ __device__ __forceinline__ void shared_row(const SpmmArgs& a, int64_t row, uint3
 // sum to C with atomics; C must hold zeros before the launch.
 // SKIP: leave the rows described by `skip` alone.
 // grid (plan_row_split_grid; G > 1, whole-group reductions): rows of at least share_from stored entries are left out of
-// the walk; the first `finders` workgroups of the grid look for them, each in an equal stretch of the rows, and produce
-// them one after the other with all their lanes (shared_row).  They start first, so that the longest rows are done while
+// the walk; the first `finders` workgroups of the grid look for them, each in its share of the rows (FinderDeal), and
+// produce them one after the other with all their lanes (shared_row).  They start first, so that the longest rows are done while
 // the others are walked: a workgroup that came across one during its walk ended some 40 us behind the rest.
 // The workgroup size (the paper's blockSz, Section 7.2) is the launch's: SLOTS = blockDim.x / (G*LC)
 // groups work side by side on the rows of a row block.
@@ -127,14 +127,16 @@ __global__ __launch_bounds__(kRowSplitMaxBlock) void row_split_kernel(SpmmArgs a
 
     if constexpr (SHARE) {
         if ((int)blockIdx.x < plan.finders) {
-            const int64_t per = (a.M + plan.finders - 1) / plan.finders;
-            const int64_t first = per * blockIdx.x, last = first + per < a.M ? first + per : a.M;
-            for (int64_t r0 = first; r0 < last; r0 += block) {
+            constexpr uint32_t UNIT = FinderDeal::kUnit;
+            const uint32_t last = plan.deal.first_place(blockIdx.x + 1, plan.finders);
+            for (uint32_t first = plan.deal.first_place(blockIdx.x, plan.finders); first < last; first += kRowCap / UNIT) {
+                const uint32_t look = (last - first < kRowCap / UNIT ? last - first : kRowCap / UNIT) * UNIT;
                 __syncthreads();  // the last rows found are done with
                 if (threadIdx.x == 0) s_found = 0;
                 __syncthreads();
-                const int64_t r = r0 + threadIdx.x;
-                if (r < last) {
+                for (uint32_t q = threadIdx.x; q < look; q += block) {
+                    const int64_t r = plan.deal.row(first + q / UNIT, q % UNIT);
+                    if (r >= a.M) continue;
                     const int32_t len = a.rowptr[r + 1] - a.rowptr[r];
                     bool shared = len >= plan.share_from;
                     if constexpr (SKIP) shared = shared && !(skip_on && len >= skip.min_len);

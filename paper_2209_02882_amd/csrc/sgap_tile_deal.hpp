@@ -80,4 +80,34 @@ struct TileWalk {
     }
 };
 
+// Which rows a workgroup looks through for long ones.  Units of four neighbouring rows (a 16-byte piece of rowptr) are
+// dealt so that neighbours, and units a power of two apart, go to workgroups far from each other: long rows often sit
+// together (the first rows of an R-MAT matrix, those with few one bits in their number), and the workgroup that finds
+// them produces them one after the other.  Unit u has place u * g mod 2^k, g the odd number nearest to the golden section
+// of 2^k, and workgroup i takes the i-th stretch of places; step is the inverse of g.  R-MAT with 2^21 rows, row-split
+// parallel, G = 16, N = 4, 16 and 32: 5.0, 6.9 and 9.6 ms with a stretch of rows for each workgroup, 1.5, 1.4 and 1.6 so.
+struct FinderDeal {
+    static constexpr uint32_t kUnit = 4;
+    uint32_t units, mask, step;
+    FinderDeal() = default;
+    explicit FinderDeal(int64_t M)
+    {
+        units = (uint32_t)((M + kUnit - 1) / kUnit);  // below 2^29
+        uint64_t places = 1;
+        while (places < units) places *= 2;
+        mask = (uint32_t)(places - 1);
+        const uint32_t g = (uint32_t)((double)places * 0.6180339887498949) | 1u;
+        step = g;  // right in three bits; every round doubles them
+        for (int i = 0; i < 4; ++i) step *= 2u - g * step;
+    }
+    // first place of workgroup i of n (of workgroup n: behind the last place)
+    SGAP_HOST_DEVICE uint32_t first_place(uint32_t i, uint32_t n) const
+    {
+        const uint64_t p = (uint64_t)(mask / n + 1) * i;
+        return p <= mask ? (uint32_t)p : mask + 1;
+    }
+    // row number r < kUnit of the unit at a place (M or beyond: no such row)
+    SGAP_HOST_DEVICE int64_t row(uint32_t place, uint32_t r) const { return (int64_t)((place * step) & mask) * kUnit + r; }
+};
+
 }  // namespace sgap

@@ -2,6 +2,7 @@
 logic, no GPU."""
 import ctypes
 
+import numpy as np
 import pytest
 
 from paper_2209_02882_amd import binding
@@ -38,8 +39,41 @@ def test_rows_are_left_out_only_where_somebody_looks_for_them(M, items, dies):
                         assert walk_from == finders and grid - walk_from >= items
 
 
+def finder_rows(M, finders, i):
+    lib = binding.load()
+    n = lib.sgap_debug_finder_rows(M, finders, i, None, 0)
+    rows = np.empty(max(n, 1), np.int64)
+    assert lib.sgap_debug_finder_rows(M, finders, i, rows.ctypes.data, n) == n
+    return rows[:n]
+
+
+@pytest.mark.parametrize("M,finders", [(1, 1), (1, 8), (3, 8), (64, 8), (65, 8), (1000, 16), (50_021, 784), (65_536, 1024),
+                                       (1_000_000, 2048), (2_097_152, 2048), (300_001, 7)])
+def test_every_row_is_looked_at_by_one_finder_and_long_rows_fall_apart(M, finders):
+    owner = np.full(M, -1)
+    for i in range(finders):
+        rows = finder_rows(M, finders, i)
+        assert (owner[rows] == -1).all() and np.unique(rows).size == rows.size
+        owner[rows] = i
+    assert (owner >= 0).all()
+    if finders < 64:
+        return
+    # neighbouring rows in bulk, and the longest rows of an R-MAT matrix: those with few one bits in their number
+    for long_rows in (np.arange(finders), np.arange(M - finders, M)):
+        assert np.bincount(owner[long_rows]).max() <= 16  # four units of four rows (equal stretches: 64 and more)
+    bits = np.zeros(M, np.int64)
+    for b in range(M.bit_length()):
+        bits += np.arange(M) >> b & 1
+    for few in (1, 2, 3):
+        long_rows = np.flatnonzero(bits <= few)
+        assert np.bincount(owner[long_rows]).max() <= 16 + 4 * long_rows.size / finders
+
+
 def test_bad_arguments():
     lib = binding.load()
+    assert lib.sgap_debug_finder_rows(0, 1, 0, None, 0) == -1
+    assert lib.sgap_debug_finder_rows(10, 4, 4, None, 0) == -1
+    assert lib.sgap_debug_finder_rows(10, 4, 0, None, 5) == -1
     x = ctypes.byref(ctypes.c_int64())
     assert lib.sgap_debug_plan_row_split(3, 1, 1, 1, 8, 256, -1, 0, x, x, x, x) == binding.SGAP_ERR_INVALID_ARG
     assert lib.sgap_debug_plan_row_split(8, 1, 1, 1, 8, 256, -2, 0, x, x, x, x) == binding.SGAP_ERR_INVALID_ARG
