@@ -13,8 +13,10 @@ namespace sgap {
 //      and five wavefronts 641, with four 619);
 //   4  one lane per row and rows of a dozen entries or fewer: more wavefronts beat deeper batches that are mostly masked
 //      (fibers of 1 to 16 entries, 32 columns, two rows per lane: 231 us, 234 with six, 262 with eight);
-//   8  several lanes per row: few wavefronts have long rows left, and those are done the sooner (power law, N = 37, G = 16:
-//      77 us with six, 73 with eight).
+//   8  several lanes per row: rows that a workgroup takes together are done the sooner (power law, N = 37, G = 16: 77 us
+//      with six, 73 with eight, before those had workgroups of their own).  For the other rows it depends: stencil27,
+//      N = 16, G = 8 203 us against 233 with six, N = 128 700 against 712, but N = 4, G = 16 164 against 145, and fibers
+//      of 1 to 16 entries, 32 columns, two lanes 339 against 300.
 constexpr int kDepthRows = 6, kDepthShort = 4, kDepthGroups = 8;
 constexpr double kShortRowMean = 12.0;
 constexpr int kStageCap = 2048;  // (column, value) pairs per LDS chunk: 16 KB
