@@ -69,11 +69,11 @@ int sgap_debug_group_seg_reduce(const float* in, const int32_t* span, float* out
  *     lanes_per_row lanes per row and `passes` passes over its columns, for M
  *     rows in `items` work items: the first `finders` of `grid` workgroups
  *     look for the rows of at least share_from stored entries and produce them
- *     whole; the workgroups from walk_from on walk the items and leave such
- *     rows out.  resident: workgroups that the chip holds at once, for a
+ *     whole, `team` of them looking through the same rows; the workgroups from
+ *     walk_from on walk the items and leave such rows out.  resident: workgroups that the chip holds at once, for a
  *     persistent grid (0: a workgroup per item).  Host pointers.
- *   sgap_debug_finder_rows: the rows of M that workgroup number `finder` of
- *     `finders` looks through.  Writes up to `capacity` of them into out_rows
+ *   sgap_debug_finder_rows: the rows of M that team number `team` of `teams`
+ *     looks through.  Writes up to `capacity` of them into out_rows
  *     (host) and returns how many there are, or -1 on bad arguments.
  */
 int64_t sgap_debug_tile_deal(int64_t tiles, int grid, int block, int64_t* out_tiles, int64_t capacity);
@@ -82,8 +82,8 @@ int sgap_debug_plan_nnz_serial(int group_size, int lanes_per_row, int cols_per_l
                                int* lanes_used);
 int sgap_debug_plan_row_split(int lanes_per_row, int passes, int64_t M, int64_t items, int dies, int compute_units,
                               int64_t nnz_hint, int resident, int64_t* share_from, int64_t* finders,
-                              int64_t* walk_from, int64_t* grid);
-int64_t sgap_debug_finder_rows(int64_t M, int finders, int finder, int64_t* out_rows, int64_t capacity);
+                              int64_t* team, int64_t* walk_from, int64_t* grid);
+int64_t sgap_debug_finder_rows(int64_t M, int teams, int team, int64_t* out_rows, int64_t capacity);
 
 /*
  * Streaming kernels over n fp32 elements (16-byte aligned device buffers):

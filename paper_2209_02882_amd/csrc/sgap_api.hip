@@ -994,32 +994,33 @@ int sgap_debug_plan_nnz_serial(int group_size, int lanes_per_row, int cols_per_l
 }
 
 int sgap_debug_plan_row_split(int lanes_per_row, int passes, int64_t M, int64_t items, int dies, int compute_units_,
-                              int64_t nnz_hint, int resident, int64_t* share_from, int64_t* finders, int64_t* walk_from,
-                              int64_t* grid)
+                              int64_t nnz_hint, int resident, int64_t* share_from, int64_t* finders, int64_t* team,
+                              int64_t* walk_from, int64_t* grid)
 {
     if (!is_pow2_group(lanes_per_row) || passes < 1 || M < 1 || items < 1 || dies < 1 || compute_units_ < 1 ||
-        nnz_hint < -1 || resident < 0 || !share_from || !finders || !walk_from || !grid)
+        nnz_hint < -1 || resident < 0 || !share_from || !finders || !team || !walk_from || !grid)
         return fail(SGAP_ERR_INVALID_ARG, "bad plan arguments");
     const sgap::RowSplitGrid p =
         sgap::plan_row_split_grid(lanes_per_row, passes, M, items, dies, compute_units_, nnz_hint, resident);
     *share_from = p.share_from;
     *finders = p.finders;
+    *team = 1LL << p.log2_team;
     *walk_from = p.walk_from;
     *grid = p.grid;
     return SGAP_OK;
 }
 
-int64_t sgap_debug_finder_rows(int64_t M, int finders, int finder, int64_t* out_rows, int64_t capacity)
+int64_t sgap_debug_finder_rows(int64_t M, int teams, int team, int64_t* out_rows, int64_t capacity)
 {
-    if (M < 1 || M > 2147483646LL || finders < 1 || finder < 0 || finder >= finders || capacity < 0 ||
+    if (M < 1 || M > 2147483646LL || teams < 1 || team < 0 || team >= teams || capacity < 0 ||
         (capacity > 0 && !out_rows)) {
         fail(SGAP_ERR_INVALID_ARG, "bad finder arguments");
         return -1;
     }
     const sgap::FinderDeal deal(M);
     int64_t n = 0;
-    const uint32_t last = deal.first_place((uint32_t)finder + 1, (uint32_t)finders);
-    for (uint32_t p = deal.first_place((uint32_t)finder, (uint32_t)finders); p < last; ++p)
+    const uint32_t last = deal.first_place((uint32_t)team + 1, (uint32_t)teams);
+    for (uint32_t p = deal.first_place((uint32_t)team, (uint32_t)teams); p < last; ++p)
         for (uint32_t r = 0; r < sgap::FinderDeal::kUnit; ++r)
             if (deal.row(p, r) < M) {
                 if (n < capacity) out_rows[n] = deal.row(p, r);

@@ -67,7 +67,8 @@ struct TileSched {
 struct RowSplitGrid {
     int32_t share_from;  // 0x7fffffff, which no row reaches, exactly where nobody looks for such rows
     int32_t finders;
-    FinderDeal deal;     // which rows each of them looks through
+    int32_t log2_team;   // 2^log2_team of them look through the same rows and take the long ones in turn
+    FinderDeal deal;     // which rows a team looks through
     int32_t walk_from;   // = finders; 0 on a persistent grid, whose workgroups look for rows first and then walk
     uint32_t grid;
 };

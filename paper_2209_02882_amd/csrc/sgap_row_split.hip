@@ -33,6 +33,8 @@ constexpr int kShareMin = 256;    // the shortest row that a whole workgroup tak
 constexpr int kFinderRows = 64;   // a finder looks at no fewer rows (32 cost matrices without long rows: 10,000 rows of 16
                                   // entries, N = 32, G = 8 6.3 -> 6.7 us)
 constexpr int kFindersPerCu = 8;  // as many workgroups as are resident
+constexpr int kTeamRows = 256;    // a team of two looks through no more rows: a look of its workgroups' threads
+constexpr int kTeamsPerCu = 4;    // no teams where there are more finders: they come in rounds then
 
 // A group's rounds of loads on a row of len entries are about len / (g * kDepthGroups) for each pass over the columns,
 // each of them a round trip to memory with a handful of loads in flight.  From a dozen rounds on, the whole workgroup
@@ -50,11 +52,15 @@ int32_t share_rows_from(int g, int passes)
 // Finders per compute unit, G = 8: the longest rows of a power law (4,096 entries) bind it otherwise.  65,536 rows,
 // N = 37: 73 us without finders, 70.7 with one, 58.4 with two, 47.5 with four or eight; 114,150 rows, N = 34: 100.5
 // without, 100.4, 90.2 and 82.8 with one, two and four, 72.5 with eight (a stretch of rows for each; FinderDeal says
-// what dealing them out changed).
+// what dealing them out changed).  Where there are few finders two look through the same rows and take the long ones in
+// turn, so that two of the longest seldom wait for each other.  Power laws, ten matrices each, in the mean: 9,437 rows,
+// N = 45 26.6 -> 23.1 us, 20,000 rows, N = 16 13.2 -> 11.4, 50,021 rows, N = 37 43.8 -> 40.3.  Teams of four gain 3 %
+// more at best and cost 60,000 rows without long ones 18.7 -> 19.1; teams where finders come in rounds lose (150,000
+// rows, N = 37: 92.2 -> 98.0).
 RowSplitGrid plan_row_split_grid(int g, int passes, int64_t M, int64_t items, int xcds, int compute_units,
                                  int64_t nnz_hint, int resident)
 {
-    RowSplitGrid p = {0x7fffffff, 0, FinderDeal(M), 0, 0};
+    RowSplitGrid p = {0x7fffffff, 0, 0, FinderDeal(M), 0, 0};
     const int64_t items_per_xcd = (items + xcds - 1) / xcds;
     int64_t wgs_per_xcd = resident > 0 ? (resident / xcds > 0 ? resident / xcds : 1) : items_per_xcd;
     if (wgs_per_xcd > items_per_xcd) wgs_per_xcd = items_per_xcd;
@@ -64,11 +70,16 @@ RowSplitGrid plan_row_split_grid(int g, int passes, int64_t M, int64_t items, in
     if (g > 1 && (nnz_hint < 0 || nnz_hint >= share_from)) {
         const int64_t most = (int64_t)kFindersPerCu * compute_units;
         int64_t finders = (M + kFinderRows - 1) / kFinderRows < most ? (M + kFinderRows - 1) / kFinderRows : most;
+        if (resident > 0 && finders > walkers) finders = walkers;
+        const int64_t rows_each = (M + finders - 1) / finders;
+        if (2 * rows_each <= kTeamRows && finders >= 2 && finders <= (int64_t)kTeamsPerCu * compute_units) p.log2_team = 1;
+        const int64_t team = 1LL << p.log2_team;
         if (resident > 0) {
             // a persistent grid is resident all at once: its own workgroups are the finders
-            if (finders > walkers) finders = walkers;
+            finders = finders / team * team;
         } else {
-            finders = (finders + xcds - 1) / xcds * xcds;  // whole rounds of the dies
+            const int64_t whole = team > xcds ? team : xcds;  // whole teams, whole rounds of the dies
+            finders = (finders + whole - 1) / whole * whole;
             p.walk_from = (int32_t)finders;
         }
         p.share_from = share_from;

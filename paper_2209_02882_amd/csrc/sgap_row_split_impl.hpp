@@ -97,8 +97,8 @@ __device__ __forceinline__ void shared_row(const SpmmArgs& a, int64_t row, uint3
 // sum to C with atomics; C must hold zeros before the launch.
 // SKIP: leave the rows described by `skip` alone.
 // grid (plan_row_split_grid; G > 1, whole-group reductions): rows of at least share_from stored entries are left out of
-// the walk; the first `finders` workgroups of the grid look for them, each in its share of the rows (FinderDeal), and
-// produce them one after the other with all their lanes (shared_row).  They start first, so that the longest rows are done while
+// the walk; the first `finders` workgroups of the grid look for them, a team of them in each share of the rows
+// (FinderDeal), and produce them in turn, one after the other with all their lanes (shared_row).  They start first, so that the longest rows are done while
 // the others are walked: a workgroup that came across one during its walk ended some 40 us behind the rest.
 // The workgroup size (the paper's blockSz, Section 7.2) is the launch's: SLOTS = blockDim.x / (G*LC)
 // groups work side by side on the rows of a row block.
@@ -110,7 +110,7 @@ __global__ __launch_bounds__(kRowSplitMaxBlock) void row_split_kernel(SpmmArgs a
     __shared__ StagedEntry s_A[kStageCap];
     __shared__ int32_t s_rp[kRowCap + 1];
     constexpr bool SHARE = G > 1 && !PARTIAL;
-    __shared__ int32_t s_found;
+    __shared__ unsigned long long s_mask[kRowSplitMaxBlock / kWave];
     // entries per thread in flight to LDS: single lanes' row blocks have one or two for each thread, and the registers of
     // four would cost the instance a wavefront per SIMD (stencil of 1,048,576 rows, N = 128: 602 us against 593)
     constexpr int STAGED = G == 1 && DEPTH == kDepthRows ? 1 : 4;
@@ -130,22 +130,36 @@ __global__ __launch_bounds__(kRowSplitMaxBlock) void row_split_kernel(SpmmArgs a
     if constexpr (SHARE) {
         if ((int)blockIdx.x < plan.finders) {
             constexpr uint32_t UNIT = FinderDeal::kUnit;
-            const uint32_t last = plan.deal.first_place(blockIdx.x + 1, plan.finders);
-            for (uint32_t first = plan.deal.first_place(blockIdx.x, plan.finders); first < last; first += kRowCap / UNIT) {
+            const uint32_t team = blockIdx.x >> plan.log2_team, teams = (uint32_t)plan.finders >> plan.log2_team;
+            const uint32_t mine = blockIdx.x & ((1u << plan.log2_team) - 1u);  // of the rows found, this one's turns
+            const int lane = threadIdx.x % kWave, wave = threadIdx.x / kWave;
+            const uint32_t last = plan.deal.first_place(team + 1, teams);
+            for (uint32_t first = plan.deal.first_place(team, teams); first < last; first += kRowCap / UNIT) {
                 const uint32_t look = (last - first < kRowCap / UNIT ? last - first : kRowCap / UNIT) * UNIT;
-                __syncthreads();  // the last rows found are done with
-                if (threadIdx.x == 0) s_found = 0;
-                __syncthreads();
-                for (uint32_t q = threadIdx.x; q < look; q += block) {
+                uint32_t found = 0;  // the same in all members of the team, and in the same order
+                for (uint32_t q0 = 0; q0 < look; q0 += block) {
+                    const uint32_t q = q0 + threadIdx.x;
                     const int64_t r = plan.deal.row(first + q / UNIT, q % UNIT);
-                    if (r >= a.M) continue;
-                    const int32_t len = a.rowptr[r + 1] - a.rowptr[r];
-                    bool shared = len >= plan.share_from;
-                    if constexpr (SKIP) shared = shared && !(skip_on && len >= skip.min_len);
-                    if (shared) s_rp[atomicAdd(&s_found, 1)] = (int32_t)r;
+                    bool shared = q < look && r < a.M;
+                    if (shared) {
+                        const int32_t len = a.rowptr[r + 1] - a.rowptr[r];
+                        shared = len >= plan.share_from;
+                        if constexpr (SKIP) shared = shared && !(skip_on && len >= skip.min_len);
+                    }
+                    const unsigned long long mask = __ballot(shared);
+                    __syncthreads();  // the last rows found, or the last masks, are done with
+                    if (lane == 0) s_mask[wave] = mask;
+                    __syncthreads();
+                    uint32_t rank = found + (uint32_t)__popcll(mask & ((1ull << lane) - 1ull));
+                    for (int w = 0; w < block / kWave; ++w) {
+                        const uint32_t c = (uint32_t)__popcll(s_mask[w]);
+                        if (w < wave) rank += c;
+                        found += c;
+                    }
+                    if (shared && (rank & ((1u << plan.log2_team) - 1u)) == mine) s_rp[rank >> plan.log2_team] = (int32_t)r;
                 }
                 __syncthreads();
-                const int n = s_found;
+                const int n = (int)((found + (1u << plan.log2_team) - 1u - mine) >> plan.log2_team);
                 for (int i = 0; i < n; ++i) {
                     const int32_t row = __builtin_amdgcn_readfirstlane(s_rp[i]);
                     shared_row<VEC, OFF32, DEPTH>(a, row, (uint32_t)a.rowptr[row], (uint32_t)a.rowptr[row + 1], 0, N, s_A, block);

@@ -80,11 +80,11 @@ struct TileWalk {
     }
 };
 
-// Which rows a workgroup looks through for long ones.  Units of four neighbouring rows (a 16-byte piece of rowptr) are
+// Which rows a team of workgroups looks through for long ones.  Units of four neighbouring rows (a 16-byte piece of rowptr) are
 // dealt so that neighbours, and units a power of two apart, go to workgroups far from each other: long rows often sit
-// together (the first rows of an R-MAT matrix, those with few one bits in their number), and the workgroup that finds
-// them produces them one after the other.  Unit u has place u * g mod 2^k, g the odd number nearest to the golden section
-// of 2^k, and workgroup i takes the i-th stretch of places; step is the inverse of g.  R-MAT with 2^21 rows, row-split
+// together (the first rows of an R-MAT matrix, those with few one bits in their number), and the workgroups that find
+// them produce them one after the other.  Unit u has place u * g mod 2^k, g the odd number nearest to the golden section
+// of 2^k, and team i takes the i-th stretch of places; step is the inverse of g.  R-MAT with 2^21 rows, row-split
 // parallel, G = 16, N = 4, 16 and 32: 5.0, 6.9 and 9.6 ms with a stretch of rows for each workgroup, 1.5, 1.4 and 1.6 so.
 struct FinderDeal {
     static constexpr uint32_t kUnit = 4;
@@ -100,7 +100,7 @@ struct FinderDeal {
         step = g;  // right in three bits; every round doubles them
         for (int i = 0; i < 4; ++i) step *= 2u - g * step;
     }
-    // first place of workgroup i of n (of workgroup n: behind the last place)
+    // first place of team i of n (of team n: behind the last place)
     SGAP_HOST_DEVICE uint32_t first_place(uint32_t i, uint32_t n) const
     {
         const uint64_t p = (uint64_t)(mask / n + 1) * i;

@@ -11,7 +11,7 @@ NEVER = 2**31 - 1
 
 
 def plan(g, passes, M, items, nnz_hint, resident=0, dies=8, cus=256):
-    out = [ctypes.c_int64() for _ in range(4)]
+    out = [ctypes.c_int64() for _ in range(5)]
     assert binding.load().sgap_debug_plan_row_split(g, passes, M, items, dies, cus, nnz_hint, resident,
                                                     *(ctypes.byref(x) for x in out)) == 0
     return tuple(x.value for x in out)
@@ -24,12 +24,15 @@ def test_rows_are_left_out_only_where_somebody_looks_for_them(M, items, dies):
         for passes in (1, 2, 75):
             for hint in (-1, 0, 1, 100, 255, 256, 5000, 2**31 - 65536):
                 for resident in (0, 1, 7, 8, 1000, 2048):
-                    share_from, finders, walk_from, grid = plan(g, passes, M, items, hint, resident, dies)
+                    share_from, finders, team, walk_from, grid = plan(g, passes, M, items, hint, resident, dies)
                     assert (finders == 0) == (share_from == NEVER)
                     if g == 1 or 0 <= hint < max(256, 96 * g // passes):
                         assert finders == 0
                     else:
                         assert share_from == max(256, 96 * g // passes) and finders > 0
+                    assert team in (1, 2) and finders % team == 0
+                    if team > 1:
+                        assert 2 * -(-M // finders) <= 256 and finders <= 4 * 256 + dies
                     # every die has workgroups that walk, and the same number of them
                     assert 0 <= walk_from < grid and (grid - walk_from) % dies == 0 and walk_from % dies == 0
                     if resident:
@@ -75,6 +78,6 @@ def test_bad_arguments():
     assert lib.sgap_debug_finder_rows(10, 4, 4, None, 0) == -1
     assert lib.sgap_debug_finder_rows(10, 4, 0, None, 5) == -1
     x = ctypes.byref(ctypes.c_int64())
-    assert lib.sgap_debug_plan_row_split(3, 1, 1, 1, 8, 256, -1, 0, x, x, x, x) == binding.SGAP_ERR_INVALID_ARG
-    assert lib.sgap_debug_plan_row_split(8, 1, 1, 1, 8, 256, -2, 0, x, x, x, x) == binding.SGAP_ERR_INVALID_ARG
-    assert lib.sgap_debug_plan_row_split(8, 1, 1, 1, 8, 256, -1, 0, x, x, x, None) == binding.SGAP_ERR_INVALID_ARG
+    assert lib.sgap_debug_plan_row_split(3, 1, 1, 1, 8, 256, -1, 0, x, x, x, x, x) == binding.SGAP_ERR_INVALID_ARG
+    assert lib.sgap_debug_plan_row_split(8, 1, 1, 1, 8, 256, -2, 0, x, x, x, x, x) == binding.SGAP_ERR_INVALID_ARG
+    assert lib.sgap_debug_plan_row_split(8, 1, 1, 1, 8, 256, -1, 0, x, x, x, x, None) == binding.SGAP_ERR_INVALID_ARG
