@@ -239,7 +239,11 @@ int sgap_spmm_csr_gr(int64_t M, int64_t K, int64_t N,
  *                   it when long rows hold most entries and B is far larger than
  *                   the L2s.  Needs a workspace (below).  0 = off.
  *   window_kb       KiB of B per column window (at most 511 windows are made);
- *                   automatic: 3072.
+ *                   automatic: 3072.  Lists of at least 256 long rows that hold
+ *                   a fair share of the columns are multiplied out of windows in
+ *                   LDS instead, from 64 columns of B on, where that is the
+ *                   faster; a window of at most 154 KiB (of 64 columns of B)
+ *                   asks for that form wherever it applies.
  *   max_long_rows   capacity of the list of long rows, at most 1,048,576;
  *                   automatic: 8192.  The rows are found on the device; when a
  *                   matrix has more long rows than this, the call produces every

@@ -18,6 +18,9 @@
 // (the rows were zeroed before), which is what the "Atomics" output strategy of
 // Section 6.2 does for a row that several groups produce.
 //
+// Where the list is long enough and its rows are dense enough the windows are far smaller and lie in LDS
+// (sgap_panels_lds.hpp), which delivers them four times as fast as the L2.
+//
 // The row-split kernel then produces all other rows and leaves the long ones
 // alone (`RowSkip`).  Everything is decided on the device, so the call stays
 // asynchronous: the list of long rows and the window pointers live in a
@@ -25,9 +28,12 @@
 // panel_workspace_bytes for a list of `cap` rows).  When the matrix has more long
 // rows than the list holds, this path does nothing and the row-split kernel
 // takes every row.
+#include <algorithm>
+
 #include "sgap_common.hpp"
 #include "sgap_dot8.hpp"
 #include "sgap_lane_ops.hpp"
+#include "sgap_panels_lds.hpp"
 #include "sgap_row_split_impl.hpp"
 #include "sgap_uniform.hpp"
 
@@ -35,24 +41,7 @@ namespace sgap {
 
 constexpr int kPanelMaxWindows = 511;  // column windows at most
 constexpr int kPanelDies = 8;          // dies of the chip (the window count is made a multiple of it)
-constexpr int kRankMaxRows = 8192;     // lists up to this length are sorted by row length (their lengths fit in LDS)
 constexpr int kSearchLanes = 4;        // lanes that look for one window pointer together
-
-// The workspace: a header, the list of long rows, the same list sorted by length, the rows' lengths, and the
-// window pointers.
-struct PanelHeader {
-    uint32_t count;     // long rows found (may exceed the list's capacity: then the path is off)
-    uint32_t next[15];  // per die: the next item nobody has taken yet
-    uint32_t pad[48];
-};
-struct PanelView {
-    PanelHeader* head;
-    int32_t* rows;   // [cap]
-    int32_t* order;  // [cap] the long rows from the longest to the shortest: order[q] indexes rows[]
-    int32_t* len;    // [cap] stored entries of rows[i]
-    int32_t* ptr;    // [cap * (windows + 1)]: ptr[i * (windows + 1) + w] = first entry of long row i with column >= w * window_rows
-    uint32_t cap;    // rows the list holds
-};
 
 int64_t panel_workspace_bytes(int64_t cap, int windows)
 {
@@ -81,6 +70,10 @@ PanelView panel_view(void* workspace, int64_t cap, int windows)
 __global__ void panel_reset_kernel(PanelView scr)
 {
     if (blockIdx.x == 0 && threadIdx.x < 16) (&scr.head->count)[threadIdx.x] = 0;  // count and next[]
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        scr.head->entries = 0;
+        scr.head->lds.on = 0;
+    }
 }
 
 // A workgroup looks at kFindRows rows per thread and adds to the list's counter once: a returning atomic on one
@@ -90,17 +83,23 @@ constexpr int kFindRows = 8;
 __global__ __launch_bounds__(kBlock) void panel_find_rows_kernel(SpmmArgs a, PanelView scr, int32_t min_len)
 {
     __shared__ uint32_t s_wave[kWavesPerBlock];
+    __shared__ unsigned long long s_entries[kWavesPerBlock];
     __shared__ uint32_t s_base;
     const int lane = threadIdx.x % kWave;
     const int wave = threadIdx.x / kWave;
     const int64_t row0 = (int64_t)blockIdx.x * (kBlock * kFindRows) + threadIdx.x;
+    if (row0 == 0) scr.head->nnz = (uint32_t)a.rowptr[a.M];
     uint32_t mine = 0;  // bit j: row row0 + j * kBlock is long
     int32_t len[kFindRows];
+    unsigned long long entries = 0;
 #pragma unroll
     for (int j = 0; j < kFindRows; ++j) {
         const int64_t row = row0 + (int64_t)j * kBlock;
         len[j] = row < a.M ? a.rowptr[row + 1] - a.rowptr[row] : 0;
-        if (row < a.M && len[j] >= min_len) mine |= 1u << j;
+        if (row < a.M && len[j] >= min_len) {
+            mine |= 1u << j;
+            entries += (unsigned long long)len[j];
+        }
     }
     const uint32_t cnt = (uint32_t)__popc(mine);
     uint32_t incl = cnt;  // long rows of this and the lower lanes of the wavefront
@@ -108,8 +107,12 @@ __global__ __launch_bounds__(kBlock) void panel_find_rows_kernel(SpmmArgs a, Pan
     for (int d = 1; d < kWave; d *= 2) {
         const uint32_t t = (uint32_t)__shfl_up((int)incl, d, kWave);
         if (lane >= d) incl += t;
+        entries += __shfl_xor(entries, d, kWave);
     }
-    if (lane == kWave - 1) s_wave[wave] = incl;
+    if (lane == kWave - 1) {
+        s_wave[wave] = incl;
+        s_entries[wave] = entries;
+    }
     __syncthreads();
     if (threadIdx.x == 0) {
         uint32_t total = 0;
@@ -117,8 +120,13 @@ __global__ __launch_bounds__(kBlock) void panel_find_rows_kernel(SpmmArgs a, Pan
             const uint32_t c = s_wave[w];
             s_wave[w] = total;
             total += c;
+            entries += w > 0 ? s_entries[w] : 0ull;
         }
-        s_base = total ? atomicAdd(&scr.head->count, total) : 0u;
+        s_base = 0;
+        if (total) {
+            s_base = atomicAdd(&scr.head->count, total);
+            atomicAdd(&scr.head->entries, entries);
+        }
     }
     __syncthreads();
     uint32_t i = s_base + s_wave[wave] + incl - cnt;
@@ -144,10 +152,17 @@ __device__ __forceinline__ int panel_share_begin(int xcd, int windows, int xcds)
 template <int VEC>
 __device__ __forceinline__ void panel_pointers_body(const SpmmArgs& a, const PanelView& scr, int windows,
                                                     int32_t window_rows, int zero_rows, uint32_t few_from, int xcds,
-                                                    bool ranked, uint32_t block, uint32_t blocks)
+                                                    const LdsArgs& lds, bool ranked, uint32_t block, uint32_t blocks)
 {
     const uint32_t n = scr.head->count;
     if (n == 0 || n > scr.cap) return;
+    const LdsPlan plan = lds_plan(scr.head, lds, a.K, a.N);
+    if (block == 0 && threadIdx.x == 0) scr.head->lds = plan;
+    if (plan.on) {  // panel_lds_kernel's shares are pieces of its own
+        windows = (int)(plan.per_die * lds.dies);
+        window_rows = plan.share_cols;
+        few_from = 0xffffffffu;
+    }
     const int64_t threads = (int64_t)blocks * kBlock;
     const int64_t tid = (int64_t)block * kBlock + threadIdx.x;
     const int per_row = windows + 1;
@@ -324,7 +339,7 @@ __global__ __launch_bounds__(kBlock) void panel_long_rows_kernel(SpmmArgs a, Pan
     static_assert(G * LC == kWave, "one wavefront per item");
     __shared__ uint32_t s_claim;
     const uint32_t n = scr.head->count;
-    if (n == 0 || n > scr.cap || n >= below) return;
+    if (n == 0 || n > scr.cap || n >= below || scr.head->lds.on) return;
     const int lane = threadIdx.x % kWave;
     const int wave = threadIdx.x / kWave;
     const int per_row = windows + 1;
@@ -404,12 +419,12 @@ __device__ __forceinline__ void panel_rank_body(const PanelView& scr, int32_t* s
 template <int VEC>
 __global__ __launch_bounds__(kBlock) void panel_pointers_kernel(SpmmArgs a, PanelView scr, int windows,
                                                                 int32_t window_rows, int zero_rows, uint32_t few_from,
-                                                                int xcds, uint32_t pointer_blocks)
+                                                                int xcds, LdsArgs lds, uint32_t pointer_blocks)
 {
     __shared__ int32_t s_len[kRankMaxRows];
     const bool ranked = gridDim.x > pointer_blocks;
     if (blockIdx.x < pointer_blocks)
-        panel_pointers_body<VEC>(a, scr, windows, window_rows, zero_rows, few_from, xcds, ranked, blockIdx.x,
+        panel_pointers_body<VEC>(a, scr, windows, window_rows, zero_rows, few_from, xcds, lds, ranked, blockIdx.x,
                                  pointer_blocks);
     else
         panel_rank_body(scr, s_len, blockIdx.x - pointer_blocks);
@@ -417,6 +432,7 @@ __global__ __launch_bounds__(kBlock) void panel_pointers_kernel(SpmmArgs a, Pane
 
 constexpr int kOwnerBlock = 1024;  // one workgroup of 16 wavefronts per compute unit
 constexpr int kOwnerWaves = kOwnerBlock / kWave;
+static_assert(kOwnerBlock == kLdsBlock, "panel_lds_rows runs in the owners' workgroups");
 constexpr int kOwnerRows = 10;  // long rows a wavefront owns at a time
 constexpr int kOwnerDepth = 8;  // gathered rows of B in flight per lane
 
@@ -437,6 +453,7 @@ constexpr int kOwnerDepth = 8;  // gathered rows of B in flight per lane
 // Nothing here relies on sorted columns: an entry is taken in the first window of the share at which it is at
 // the front of what is left and lies in front of the window's end, at the latest in the share's last window,
 // which takes all that is left.
+// (One launch for these and for panel_lds_rows, which never run both: an idle kernel is 5 us.)
 // Runs only when the list holds at least min_rows rows; with fewer, most wavefronts would own nothing and
 // panel_long_rows_kernel (which then runs instead) keeps the whole chip busy.
 template <int VEC, bool OFF32>
@@ -444,13 +461,19 @@ __global__ __launch_bounds__(kOwnerBlock) void panel_owner_kernel(const int32_t*
                                                                   const float* __restrict__ vals,
                                                                   const float* __restrict__ B, float* __restrict__ C,
                                                                   PanelView scr, int64_t K, int64_t N, int windows,
-                                                                  int32_t window_rows, int xcds, uint32_t min_rows)
+                                                                  int32_t window_rows, int xcds, uint32_t min_rows,
+                                                                  LdsArgs lds)
 {
     constexpr int R = kOwnerRows;
+    __shared__ LdsShared s_lds;
     const uint32_t n = scr.head->count;
-    if (n < min_rows || n > scr.cap) return;
-    const int lane = threadIdx.x % kWave;
     const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    if (scr.head->lds.on) {  // the windows lie in LDS
+        panel_lds_rows(colidx, vals, B, C, scr, K, N, lds, wave, s_lds);
+        return;
+    }
+    if (n < min_rows || n > scr.cap) return;
+    const int lane = LdsThread().lane;  // (threadIdx.x would be kept throughout the other branch)
     const uint32_t xcd = blockIdx.x % xcds;
     const uint32_t waves = (gridDim.x / xcds) * kOwnerWaves;  // wavefronts of this die
     const uint32_t me = (blockIdx.x / xcds) * kOwnerWaves + wave;
@@ -541,6 +564,17 @@ __global__ __launch_bounds__(kOwnerBlock) void panel_owner_kernel(const int32_t*
     }
 }
 
+// panel_lds_rows by itself, where no owner wavefronts are launched (N <= 128).
+__global__ __launch_bounds__(kLdsBlock) void panel_lds_kernel(const int32_t* __restrict__ colidx,
+                                                              const float* __restrict__ vals, const float* __restrict__ B,
+                                                              float* __restrict__ C, PanelView scr, int64_t K, int64_t N,
+                                                              LdsArgs lds)
+{
+    __shared__ LdsShared s_lds;
+    const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    if (scr.head->lds.on) panel_lds_rows(colidx, vals, B, C, scr, K, N, lds, wave, s_lds);
+}
+
 namespace {
 
 template <int G, int LC, int VEC>
@@ -579,7 +613,7 @@ uint32_t owner_min_rows(int xcds, int compute_units)
 
 template <int VEC>
 void launch_owner_rows(const SpmmArgs& a, const PanelView& scr, int windows, int32_t window_rows, int xcds,
-                       int compute_units, hipStream_t s)
+                       int compute_units, const LdsArgs& lds, hipStream_t s)
 {
     const bool off32 = offsets_fit_32(a);
     // one workgroup per compute unit (nothing depends on their all being resident: there is no waiting between them)
@@ -589,10 +623,10 @@ void launch_owner_rows(const SpmmArgs& a, const PanelView& scr, int windows, int
     const uint32_t min_rows = owner_min_rows(xcds, compute_units);
     if (off32)
         hipLaunchKernelGGL((panel_owner_kernel<VEC, true>), dim3(grid), dim3(kOwnerBlock), 0, s, a.colidx, a.vals, a.B,
-                           a.C, scr, a.K, a.N, windows, window_rows, xcds, min_rows);
+                           a.C, scr, a.K, a.N, windows, window_rows, xcds, min_rows, lds);
     else
         hipLaunchKernelGGL((panel_owner_kernel<VEC, false>), dim3(grid), dim3(kOwnerBlock), 0, s, a.colidx, a.vals, a.B,
-                           a.C, scr, a.K, a.N, windows, window_rows, xcds, min_rows);
+                           a.C, scr, a.K, a.N, windows, window_rows, xcds, min_rows, lds);
 }
 
 // Column windows of about window_bytes of B each, at most kPanelMaxWindows.
@@ -625,9 +659,9 @@ void plan_panels(int64_t K, int64_t N, int64_t window_bytes, int* windows, int32
 // it needs the pointers of its xcds shares only).
 void launch_panel_preparation(const SpmmArgs& a, const PanelView& scr, int windows, int32_t window_rows,
                               int32_t min_len, bool zero_rows, bool owners, int xcds, int compute_units,
-                              hipStream_t s)
+                              const LdsArgs& lds, hipStream_t s)
 {
-    const bool rank_rows = owners;
+    const bool rank_rows = owners || lds.min_rows != 0xffffffffu;
     const uint32_t few_from = owners ? owner_min_rows(xcds, compute_units) : 0xffffffffu;
     hipLaunchKernelGGL(panel_reset_kernel, dim3(1), dim3(kWave), 0, s, scr);
     constexpr int64_t rows_per_block = (int64_t)kBlock * kFindRows;
@@ -640,7 +674,7 @@ void launch_panel_preparation(const SpmmArgs& a, const PanelView& scr, int windo
         rank_blocks = (rows + kBlock / kRankLanes - 1) / (kBlock / kRankLanes);
     }
     hipLaunchKernelGGL((panel_pointers_kernel<4>), dim3(pointer_blocks + rank_blocks), dim3(kBlock), 0, s, a, scr, windows,
-                       window_rows, zero_rows ? 1 : 0, few_from, xcds, pointer_blocks);
+                       window_rows, zero_rows ? 1 : 0, few_from, xcds, lds, pointer_blocks);
 }
 
 // Lane layout of the SpMM window kernels: chunk lanes for the columns of a tile (at most kPanelTileLanes * 4
@@ -695,10 +729,16 @@ hipError_t launch_row_split_panels(const SpmmArgs& a, int g, int lc, int vec, in
     const PanelView scr = panel_view(workspace, cap, windows);
     // a wavefront per row with all 64 lanes on column chunks: worth it from 128 columns on
     const bool owners = wave_lc == kPanelTileLanes && a.N >= 128;
-    launch_panel_preparation(a, scr, windows, window_rows, min_len, true, owners, xcds, compute_units, s);
+    const uint32_t lds_workgroups = (uint32_t)(compute_units / xcds > 0 ? compute_units / xcds : 1);
+    const LdsArgs lds{a.N >= kLdsMinCols ? kLdsMinRows : 0xffffffffu, (uint32_t)xcds, lds_workgroups, cap * (windows + 1),
+                      window_bytes <= kLdsWindow * kLdsRowBytes ? (int32_t)std::max<int64_t>(1, window_bytes / kLdsRowBytes) : 0};
+    launch_panel_preparation(a, scr, windows, window_rows, min_len, true, owners, xcds, compute_units, lds, s);
+    if (!owners && lds.min_rows != 0xffffffffu)
+        hipLaunchKernelGGL(panel_lds_kernel, dim3(lds_workgroups * (uint32_t)xcds), dim3(kLdsBlock), 0, s, a.colidx, a.vals, a.B,
+                           a.C, scr, a.K, a.N, lds);
     uint32_t below = 0xffffffffu;
     if (owners) {
-        launch_owner_rows<4>(a, scr, windows, window_rows, xcds, compute_units, s);
+        launch_owner_rows<4>(a, scr, windows, window_rows, xcds, compute_units, lds, s);
         below = owner_min_rows(xcds, compute_units);
     }
     switch (wave_lc) {
@@ -1044,7 +1084,7 @@ hipError_t launch_sddmm_panels(const SpmmArgs& a, const float* X1, float* out, i
     int wave_lc = 8;
     while (wave_lc < kWave && (int64_t)wave_lc * 4 < a.N) wave_lc *= 2;
     const bool owners = wave_lc == kWave;
-    launch_panel_preparation(a, scr, windows, window_rows, min_len, false, owners, owners ? xcds : 1, compute_units, s);
+    launch_panel_preparation(a, scr, windows, window_rows, min_len, false, owners, owners ? xcds : 1, compute_units, LdsArgs{0xffffffffu, 1, 1, 0, 0}, s);
     uint32_t below = 0xffffffffu;
     if (owners) {
         below = owner_min_rows(xcds, compute_units);

@@ -1,0 +1,514 @@
+// Long rows by column windows that a compute unit holds in LDS (the preparation, and the forms that gather through the
+// L2 instead, are in sgap_panels.hip).
+//
+// A form that gathers a row of B per stored entry is bound by the vector memory path, 64 bytes per clock and compute
+// unit (skewed matrix, 500,000 rows, N = 256: 57.6 GB in 2.2 ms, 26 TB/s).  LDS has four times that (a 16-byte read of a
+// wavefront takes 4.6 clocks), and long rows that hold a fair share of all columns have a few entries in any run of some
+// hundred of them: so a workgroup that owns a whole compute unit brings 64 columns of a run of rows of B (a window) into
+// LDS, multiplies out what its long rows have there, and goes on to the next window, the sums of its rows in registers.
+//   team   16 lanes x 4 columns hold one long row's 64 columns; a wavefront is four teams, side by side on four rows of
+//          about the same length (neighbours in the list sorted by length)
+//   slot   a team owns up to kLdsSlots rows, one after the other in every window: 16 wavefronts x 4 teams x 20 slots =
+//          1,280 rows per workgroup, 80 registers of sums per lane
+//   job    (share of the columns, 64 columns of B, 1,280 long rows); a die's workgroups work on the same share
+//          together, so that A and B come out of HBM once (1.25 GB fetched there, of 0.97 GB)
+// Four entries of four rows cost a wavefront one addition (the address), one 16-byte LDS read and four multiply-adds; a
+// pair is handed round its team by DPP (row_newbcast), at no cost.  That makes the vector instructions the bound: 530 M on
+// the skewed matrix, 2.07 M clocks of a SIMD of 2.5 M in all (1.28 ms; the whole call 2.54 ms before, 1.62 now).  Half of
+// them are multiply-adds that A asks for; a sixth is what the four rows of a wavefront differ by in a window (the more
+// entries a row has there, the less: hence windows as large as LDS allows), a quarter what a slot costs by itself, and
+// the rest fills up pairs.  The remaining clocks are the windows' way into LDS (10 %) and waiting for the slowest
+// wavefront (8 %).  Windows in two halves by turns would hide the former at the price of half the entries per slot.
+//
+// Nothing relies on sorted columns or columns without repetition: where what a row has in a window is not one run of its
+// entries, or more than a slot takes at once, the rest is gathered from memory.
+#pragma once
+#include <type_traits>
+
+#include "sgap_common.hpp"
+#include "sgap_panel_view.hpp"
+
+namespace sgap {
+
+constexpr int kLdsBlock = 1024;
+constexpr int kLdsWaves = kLdsBlock / kWave;
+constexpr int kLdsTeam = 16;                       // lanes of a team, 4 columns each
+constexpr int kLdsTeams = kWave / kLdsTeam;        // teams of a wavefront
+constexpr int kLdsCols = kLdsTeam * 4;             // columns of a job
+constexpr int kLdsSlots = 20;                      // rows a team owns
+constexpr int kLdsWindow = 616;                    // rows of B in LDS (and one of zeros): 157,952 of 163,840 bytes
+constexpr int kLdsRowBytes = kLdsCols * 4;
+constexpr uint32_t kLdsMaxNnz = 1u << 29;          // byte offsets of entries have 31 bits
+constexpr uint32_t kLdsMinRows = 256;
+constexpr int kLdsMinCols = 64;                    // columns of B from which on the kernel runs
+constexpr int kLdsNoLoads = 0x0F70;                // s_waitcnt vmcnt(0)
+static_assert(kLdsSlots <= 2 * kLdsTeam, "positions of the slots lie in two registers of a team");
+
+// What the host knows of it.
+struct LdsArgs {
+    uint32_t min_rows;    // the kernel runs for lists of at least so many rows
+    uint32_t dies;
+    uint32_t workgroups;  // of a die
+    int64_t ptr_room;     // pointers there is room for
+    int32_t window;       // columns of a window at most, as the caller asks for them (the kernel runs then); 0: he does not
+};
+
+// How the list's rows are laid over the workgroups.  Their number is not known on the host: the workgroups of
+// panel_pointers_kernel each work it out (all lanes of a wavefront together), one leaves it in the header.
+__device__ __forceinline__ LdsPlan lds_plan(const PanelHeader* head, const LdsArgs& args, int64_t K, int64_t N)
+{
+    LdsPlan p;
+    const uint32_t n = head->count;
+    p.on = 0;
+    if (n < args.min_rows) return p;
+    const unsigned long long entries = head->entries;
+    const uint32_t dies = args.dies;
+    p.tiles = (uint32_t)((N + kLdsCols - 1) / kLdsCols);
+    p.tile_cols = (uint32_t)((N / 4 + p.tiles - 1) / p.tiles) * 4;
+    const uint32_t quads = (n + kLdsTeams - 1) / kLdsTeams;
+    const uint32_t least = (quads + kLdsWaves * kLdsSlots - 1) / (kLdsWaves * kLdsSlots);
+    const float per_col = (float)entries / ((float)n * (float)K);  // entries of a long row per column
+    // Lane l: l + 1 shares per die, with the fewest groups of rows and up to three more.  Clocks of a job, roughly (500,000
+    // rows, 5,000 of them long with 11,000 entries in the mean, N = 256: 2.77 M by this, 2.6 M measured): a wavefront's
+    // pass over a slot in a window, the window on its way into LDS, the sums added into C at the end; and the search for
+    // the shares' ends before.
+    p.window = args.window > 0 ? args.window : (int32_t)fmaxf(1.0f, fminf((float)kLdsWindow, 16.0f / per_col));
+    const uint32_t lane = threadIdx.x % kWave;
+    unsigned long long best = ~0ull;
+    for (uint32_t more = 0; more < 4; ++more) {
+        const uint32_t groups = least + more;
+        const uint32_t slots = (quads + kLdsWaves * groups - 1) / (kLdsWaves * groups);
+        const int64_t shares = (int64_t)(lane + 1) * dies;
+        const int64_t share_cols = (K + shares - 1) / shares;
+        const uint32_t windows = (uint32_t)((share_cols + p.window - 1) / p.window);
+        const uint32_t rounds = (p.tiles * groups * (lane + 1) + args.workgroups - 1) / args.workgroups;
+        const float slot = 600.0f + 128.0f * per_col * (float)share_cols / (float)windows;
+        const float cost = (float)rounds * ((float)windows * ((float)slots * slot + 5000.0f) + (float)slots * 7400.0f)
+                           + 0.3f * (float)n * (float)shares;
+        const bool fits = (shares + 1) * n <= args.ptr_room;
+        const unsigned long long key = (unsigned long long)__float_as_uint(cost) << 32 | more << 8 | lane;
+        if (fits && key < best) best = key;
+    }
+#pragma unroll
+    for (int m = 1; m < kWave; m *= 2) {
+        const unsigned long long other = __shfl_xor(best, m, kWave);
+        if (other < best) best = other;
+    }
+    const uint32_t chosen = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)best);
+    p.groups = least + (chosen >> 8 & 3);
+    p.slots = (quads + kLdsWaves * p.groups - 1) / (kLdsWaves * p.groups);
+    p.per_die = (chosen & 63) + 1;
+    p.share_cols = (int32_t)((K + (int64_t)p.per_die * dies - 1) / ((int64_t)p.per_die * dies));
+    // The kernels that gather every entry's row of B through the L2 take the clocks that its bytes need at 43 (owner
+    // wavefronts, N > 128) and 29 (claiming wavefronts) bytes per clock and compute unit, the latter more where there are
+    // too few rows to go round.  Measured around the line, us for the whole call, this kernel against those:
+    //   rows (1 % long)  mean long row  N = 64        N = 128       N = 256
+    //   500,000          5,500          584 /   632   806 / 1,050   1,291 / 1,559
+    //   500,000          2,750          517 /   434   697 /   721   1,136 / 1,057
+    //   120,000          1,320          136 /   110   177 /   157     272 /   203
+    //    60,000          4,125          127 /   256   150 /   185     210 /   213
+    //    26,000          1,650                         85 /   173
+    float gather = (float)entries * (float)N * 4.0f / ((float)(dies * args.workgroups) * (N > 128 ? 43.0f : 29.0f));
+    if (N <= 128) gather *= fmaxf(1.0f, 1200.0f / (float)n);
+    const bool faster = args.window > 0 || __uint_as_float((uint32_t)(best >> 32)) < gather;
+    p.on = best != ~0ull && faster && head->nnz < kLdsMaxNnz && K <= (1 << 24);
+    return p;
+}
+
+// The value that lane J of a lane's team holds.
+template <int J>
+__device__ __forceinline__ int32_t team_bcast(int32_t v)
+{
+    return __builtin_amdgcn_update_dpp(0, v, 0x150 + J, 0xF, 0xF, true);
+}
+// The value that the lane D above holds (zero past the end of the team).
+template <int D>
+__device__ __forceinline__ int32_t team_shift(int32_t v)
+{
+    return __builtin_amdgcn_update_dpp(0, v, 0x100 + D, 0xF, 0xF, true);
+}
+
+// Two neighbouring stored entries.
+struct LdsEntries {
+    int32_t col[2], val[2];  // the bits of the values
+};
+
+// The stored entries by their byte offsets in colidx and vals: 32 bits, and what lies past the last entry reads as zero.
+struct LdsMatrix {
+    __amdgpu_buffer_rsrc_t cols, vals;
+    __device__ __forceinline__ LdsMatrix(const int32_t* colidx, const float* values, uint32_t nnz)
+        : cols(__builtin_amdgcn_make_buffer_rsrc(const_cast<int32_t*>(colidx), 0, (int)(nnz * 4), 0x00020000)),
+          vals(__builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(values), 0, (int)(nnz * 4), 0x00020000))
+    {
+    }
+    __device__ __forceinline__ LdsEntries load(uint32_t at) const
+    {
+        typedef uint32_t raw_u2 __attribute__((ext_vector_type(2)));
+        const raw_u2 c = __builtin_amdgcn_raw_buffer_load_b64(cols, (int)at, 0, 0);
+        const raw_u2 v = __builtin_amdgcn_raw_buffer_load_b64(vals, (int)at, 0, 0);
+        return {{(int32_t)c.x, (int32_t)c.y}, {(int32_t)v.x, (int32_t)v.y}};
+    }
+};
+
+// f(0), f(1), ... f(R - 1), each with its number as a type.
+template <int R, int I = 0, typename F>
+__device__ __forceinline__ void lds_each(F&& f)
+{
+    if constexpr (I < R) {
+        f(std::integral_constant<int, I>{});
+        lds_each<R, I + 1>(f);
+    }
+}
+
+// acc += (lane J of the team's val[0]) * b[0] + (its val[1]) * b[1], two fused multiply-adds per column; FIRST: acc = that.
+// The compiler does not fold the DPP move into a fused multiply-add by itself.  (The no-op is the two wait states between
+// a write of val and its DPP read, which the compiler does not see inside this text.)
+template <int J, bool FIRST>
+__device__ __forceinline__ void team_fma(Vec<4>& acc, const int32_t (&val)[2], const Vec<4> (&b)[2])
+{
+    if constexpr (FIRST) {
+        asm volatile("s_nop 1\n\t"
+                     "v_mul_f32_dpp %0, %4, %6 row_newbcast:%14 row_mask:0xf bank_mask:0xf\n\t"
+                     "v_mul_f32_dpp %1, %4, %7 row_newbcast:%14 row_mask:0xf bank_mask:0xf\n\t"
+                     "v_mul_f32_dpp %2, %4, %8 row_newbcast:%14 row_mask:0xf bank_mask:0xf\n\t"
+                     "v_mul_f32_dpp %3, %4, %9 row_newbcast:%14 row_mask:0xf bank_mask:0xf\n\t"
+                     "v_fmac_f32_dpp %0, %5, %10 row_newbcast:%14 row_mask:0xf bank_mask:0xf\n\t"
+                     "v_fmac_f32_dpp %1, %5, %11 row_newbcast:%14 row_mask:0xf bank_mask:0xf\n\t"
+                     "v_fmac_f32_dpp %2, %5, %12 row_newbcast:%14 row_mask:0xf bank_mask:0xf\n\t"
+                     "v_fmac_f32_dpp %3, %5, %13 row_newbcast:%14 row_mask:0xf bank_mask:0xf"
+                     : "=&v"(acc.v[0]), "=&v"(acc.v[1]), "=&v"(acc.v[2]), "=&v"(acc.v[3])
+                     : "v"(val[0]), "v"(val[1]), "v"(b[0].v[0]), "v"(b[0].v[1]), "v"(b[0].v[2]), "v"(b[0].v[3]),
+                       "v"(b[1].v[0]), "v"(b[1].v[1]), "v"(b[1].v[2]), "v"(b[1].v[3]), "n"(J));
+    } else {
+        asm volatile("s_nop 1\n\t"
+                     "v_fmac_f32_dpp %0, %4, %6 row_newbcast:%14 row_mask:0xf bank_mask:0xf\n\t"
+                     "v_fmac_f32_dpp %1, %4, %7 row_newbcast:%14 row_mask:0xf bank_mask:0xf\n\t"
+                     "v_fmac_f32_dpp %2, %4, %8 row_newbcast:%14 row_mask:0xf bank_mask:0xf\n\t"
+                     "v_fmac_f32_dpp %3, %4, %9 row_newbcast:%14 row_mask:0xf bank_mask:0xf\n\t"
+                     "v_fmac_f32_dpp %0, %5, %10 row_newbcast:%14 row_mask:0xf bank_mask:0xf\n\t"
+                     "v_fmac_f32_dpp %1, %5, %11 row_newbcast:%14 row_mask:0xf bank_mask:0xf\n\t"
+                     "v_fmac_f32_dpp %2, %5, %12 row_newbcast:%14 row_mask:0xf bank_mask:0xf\n\t"
+                     "v_fmac_f32_dpp %3, %5, %13 row_newbcast:%14 row_mask:0xf bank_mask:0xf"
+                     : "+&v"(acc.v[0]), "+&v"(acc.v[1]), "+&v"(acc.v[2]), "+&v"(acc.v[3])
+                     : "v"(val[0]), "v"(val[1]), "v"(b[0].v[0]), "v"(b[0].v[1]), "v"(b[0].v[2]), "v"(b[0].v[3]),
+                       "v"(b[1].v[0]), "v"(b[1].v[1]), "v"(b[1].v[2]), "v"(b[1].v[3]), "n"(J));
+    }
+}
+
+typedef float lds_f4 __attribute__((ext_vector_type(4)));
+typedef const __attribute__((address_space(3))) char* lds_bytes;
+
+// Two rows of the window for each of the four teams: those whose byte offsets in LDS lane J of the team has.
+template <int J>
+__device__ __forceinline__ void lds_read(Vec<4> (&b)[2], lds_bytes mine, const int32_t (&off)[2])
+{
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+        const lds_f4 t = *(const __attribute__((address_space(3))) lds_f4*)(mine + team_bcast<J>(off[i]));
+        b[i].v[0] = t.x; b[i].v[1] = t.y; b[i].v[2] = t.z; b[i].v[3] = t.w;
+    }
+}
+
+// This thread's place, worked out anew where it is asked for: what the phases between the windows make of it would
+// otherwise be kept in registers throughout, of which there are none to spare.
+struct LdsThread {
+    int lane, team, member;
+    __device__ __forceinline__ LdsThread()
+    {
+        uint32_t all = ~0u;
+        asm volatile("" : "+s"(all));
+        lane = (int)__builtin_amdgcn_mbcnt_hi(all, __builtin_amdgcn_mbcnt_lo(all, 0));
+        team = lane / kLdsTeam;
+        member = lane % kLdsTeam;
+    }
+};
+
+// First column of this lane in the tile that begins at tile_k; a lane past the last column gets columns that exist (its
+// sums are thrown away).
+__device__ __forceinline__ int64_t lds_columns(int32_t tile_k, const LdsThread& t, int64_t N)
+{
+    return tile_k + t.member * 4 + 4 <= N ? tile_k + t.member * 4 : N - 4;
+}
+
+struct LdsLanes {
+    uint32_t member8;  // eight times the lane's number in its team: byte offset of its two entries
+    int shift;         // first lane of the team in its half of the wavefront
+    bool high;         // the upper half
+};
+
+__device__ __forceinline__ uint32_t team_field(unsigned long long mask, const LdsLanes& l)
+{
+    const uint32_t half = l.high ? (uint32_t)(mask >> 32) : (uint32_t)mask;
+    return __builtin_amdgcn_ubfe(half, l.shift, kLdsTeam);
+}
+
+// The window a workgroup is at: columns [first, first + cols), as byte offsets of rows in LDS (of less than 2^24 columns).
+struct LdsWindow {
+    uint32_t minus_first;  // -first * kLdsRowBytes
+    uint32_t bytes;        // cols * kLdsRowBytes
+};
+
+// What one slot has in the window, into acc; returns the bytes of entries taken.  over: minus the bytes of entries to the end
+// of the slot's share.  Of the sixteen times two entries at the slot's position the first ones that lie in the window are taken.
+// `open` is set where that may not be all of them: where a team has more than 32, and where one in the window lies behind
+// one that does not (columns that are not sorted; nothing is taken then).
+__device__ __forceinline__ uint32_t lds_slot(lds_bytes mine, Vec<4>& acc, const LdsEntries& e, int32_t over, const LdsWindow& w,
+                                             const LdsLanes& l, bool& open)
+{
+    constexpr unsigned long long kNotFirst = 0xFFFEFFFEFFFEFFFEull, kLast = 0x8000800080008000ull;
+    static_assert(kLdsRowBytes == 256, "the shift");
+    int32_t off[2], val[2];
+    unsigned long long taken[2];
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+        const uint32_t at = ((uint32_t)e.col[i] << 8) + w.minus_first;
+        const bool there = over < -(int32_t)l.member8 - 4 * i;
+        taken[i] = __ballot(at < w.bytes) & __ballot(there);
+        const bool in = at < w.bytes && there;
+        off[i] = in ? (int32_t)at : kLdsWindow * kLdsRowBytes;
+        val[i] = in ? e.val[i] : 0;
+    }
+    const unsigned long long gaps = (taken[1] & ~taken[0]) | (taken[0] & ~(taken[1] << 1) & kNotFirst);
+    open = gaps != 0 || (taken[1] & kLast) != 0;
+    if (gaps != 0) return 0;
+    const uint32_t both = (uint32_t)taken[0] | (uint32_t)(taken[0] >> 32);
+    uint32_t pairs = (uint32_t)__popc((both | both >> 16) & 0xFFFFu);  // of the team with the most
+    // sixteen entries at a time, by twos, the next two rows read before these are multiplied.  The window's sums are made
+    // by themselves and then added to the row's: a row of n entries, m of them in a window, has rounding errors as of
+    // m + n / m additions in a row instead of n (one long sum was less exact than the gathering forms' many short ones).
+    Vec<4> sum;
+    for (;;) {
+        Vec<4> b[2][2];
+        lds_read<0>(b[0], mine, off);
+        lds_each<kLdsTeam / 2>([&](auto Q) {
+            constexpr int q = decltype(Q)::value;
+            if (q == 0 || pairs > q) {
+                if constexpr (q + 1 < kLdsTeam / 2) lds_read<q + 1>(b[(q + 1) % 2], mine, off);
+                team_fma<q, q == 0>(sum, val, b[q % 2]);
+            }
+        });
+#pragma unroll
+        for (int i = 0; i < 4; ++i) acc.v[i] += sum.v[i];
+        if (pairs <= kLdsTeam / 2) break;
+        pairs -= kLdsTeam / 2;
+        asm volatile("" : "+s"(pairs));  // (one copy of the sixteen: two for each of twenty slots do not fit the instruction cache)
+        off[0] = team_shift<kLdsTeam / 2>(off[0]);
+        off[1] = team_shift<kLdsTeam / 2>(off[1]);
+        val[0] = team_shift<kLdsTeam / 2>(val[0]);
+        val[1] = team_shift<kLdsTeam / 2>(val[1]);
+    }
+    return ((uint32_t)__popc(team_field(taken[0], l)) + (uint32_t)__popc(team_field(taken[1], l))) * 4;
+}
+
+// The rest of a slot: the entries in front of column c1 up to the first that is not, in any order of the columns, rows of
+// B from memory (B points to the lane's columns).  The sums are added to `row` (nullptr: the team has no row, or the lane
+// no columns).
+__device__ __forceinline__ uint32_t lds_rest(const LdsMatrix& matrix, const float* __restrict__ B, int64_t N,
+                                             float* __restrict__ row, uint32_t p, uint32_t end, int32_t c1, const LdsLanes& l)
+{
+    Vec<4> acc;
+    acc.zero();
+    for (;;) {
+        const LdsEntries e = matrix.load(p + l.member8);
+        const uint32_t rest = end - p;
+        // (the bits past a field's sixteenth are zero)
+        const uint32_t even = (uint32_t)__ffs((int)~team_field(__ballot(e.col[0] < c1 && l.member8 < rest), l)) - 1u;
+        const uint32_t odd = (uint32_t)__ffs((int)~team_field(__ballot(e.col[1] < c1 && l.member8 + 4 < rest), l)) - 1u;
+        const uint32_t taken = even <= odd ? 2 * even : 2 * odd + 1;
+#pragma unroll 1
+        for (uint32_t j = 0; __any(2 * j < taken); ++j) {
+            Vec<4> b[2];
+            float val[2];
+#pragma unroll
+            for (int i = 0; i < 2; ++i) {
+                const int32_t col = __shfl(e.col[i], (int)j, kLdsTeam);
+                val[i] = __int_as_float(__shfl(e.val[i], (int)j, kLdsTeam));
+                b[i].zero();
+                if (2 * j + i < taken) b[i] = load_vec<4>(B + (int64_t)col * N);
+                else val[i] = 0.0f;
+            }
+#pragma unroll
+            for (int i = 0; i < 2; ++i) acc.fma(val[i], b[i]);
+        }
+        p += taken * 4;
+        if (!__any(taken == 2 * kLdsTeam)) break;
+    }
+    if (row)
+        for (int i = 0; i < 4; ++i) unsafeAtomicAdd(row + i, acc.v[i]);
+    return p;
+}
+
+// The kernel's shared memory.
+struct LdsShared {
+    __attribute__((aligned(16))) float b[(kLdsWindow + 1) * kLdsCols];
+    uint32_t end[kLdsWaves * kLdsTeams * kLdsSlots];
+};
+static_assert(sizeof(LdsShared) <= 160 * 1024, "of a compute unit");
+
+// A workgroup of kLdsBlock threads that has its compute unit to itself.
+__device__ __forceinline__ void panel_lds_rows(const int32_t* __restrict__ colidx, const float* __restrict__ vals,
+                                               const float* __restrict__ B, float* __restrict__ C, const PanelView& scr,
+                                               int64_t K, int64_t N, const LdsArgs& args, uint32_t wave, LdsShared& shared)
+{
+    constexpr int R = kLdsSlots;
+    float* const s_b = shared.b;
+    uint32_t* const s_end = shared.end;
+    const uint32_t n = scr.head->count;
+    const LdsPlan plan = scr.head->lds;
+    const LdsMatrix matrix(colidx, vals, scr.head->nnz);
+    const uint32_t die = blockIdx.x % args.dies;
+    LdsLanes l;
+    lds_bytes mine;    // LDS address of this lane's columns in the window's first row
+    uint32_t* end_of;  // where the share of a slot's row ends, of the team's slots
+    {
+        const LdsThread t;
+        l.member8 = (uint32_t)t.member * 8;
+        l.shift = t.team % 2 * kLdsTeam;
+        l.high = t.team >= 2;
+        mine = (lds_bytes)s_b + t.member * 16;
+        end_of = s_end + (wave * kLdsTeams + t.team) * R;
+    }
+    static_assert(kLdsCols == kWave, "the row of zeros");
+    if (wave == 0) s_b[kLdsWindow * kLdsCols + LdsThread().lane] = 0.0f;
+
+    // a window has at most about two thirds of the 32 entries that a slot takes at once, of the longest row
+    int32_t most_cols = plan.window;
+    if (args.window == 0 && n <= (uint32_t)kRankMaxRows)
+        most_cols = (int32_t)fmaxf(1.0f, fminf((float)kLdsWindow, fmaxf(0.25f * (float)most_cols, 20.0f * (float)K / (float)scr.len[scr.order[0]])));
+    const uint32_t per_share = plan.tiles * plan.groups;
+    const uint32_t jobs = per_share * plan.per_die;
+    const uint32_t shares = plan.per_die * args.dies;
+    for (uint32_t job = blockIdx.x / args.dies; job < jobs; job += args.workgroups) {
+        const uint32_t share = die * plan.per_die + job / per_share;
+        const uint32_t tile = job % per_share % plan.tiles;
+        const uint32_t group = job % per_share / plan.tiles;
+        const int64_t share_begin = (int64_t)share * plan.share_cols;
+        if (share_begin >= K) continue;
+        const int32_t share_end = (int32_t)(K - share_begin < plan.share_cols ? K : share_begin + plan.share_cols);
+        const int32_t tile_k = (int32_t)(tile * plan.tile_cols);  // first column
+
+        auto list_place = [&](uint32_t slot, int team) {  // place of the team's row in the ranked list
+            const uint32_t units = kLdsWaves * plan.groups;
+            const uint32_t me = group * kLdsWaves + wave;
+            return (slot * units + (slot & 1 ? units - 1 - me : me)) * kLdsTeams + (uint32_t)team;
+        };
+        int32_t pos[2] = {0, 0};  // lane i of a team: where slots i and 16 + i stand, as byte offsets
+        {
+            const LdsThread t;
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                const uint32_t slot = (uint32_t)(h * kLdsTeam + t.member);
+                const uint32_t q = list_place(slot, t.team);
+                uint32_t end = 0;
+                if (slot < plan.slots && q < n) {
+                    const int64_t at = (int64_t)scr.order[q] * (shares + 1) + share;
+                    pos[h] = scr.ptr[at] * 4;
+                    end = (uint32_t)scr.ptr[at + 1] * 4;
+                }
+                if (slot < R) end_of[slot] = end;  // (read by this wavefront alone)
+            }
+        }
+        Vec<4> acc[R];
+#pragma unroll
+        for (int r = 0; r < R; ++r) acc[r].zero();
+
+        const int32_t count = (share_end - (int32_t)share_begin + most_cols - 1) / most_cols;  // windows
+        const int32_t width = (share_end - (int32_t)share_begin + count - 1) / count;
+        LdsEntries held[2];           // of the next two slots
+        uint32_t next_end = end_of[0];  // of the next slot
+        lds_each<2>([&](auto I) {
+            constexpr int i = decltype(I)::value;
+            held[i] = matrix.load((uint32_t)team_bcast<i>(pos[0]) + l.member8);
+        });
+        for (int32_t w = 0; w < count; ++w) {
+            const int32_t c0 = (int32_t)share_begin + w * width;
+            const int32_t cols = share_end - c0 < width ? share_end - c0 : width;
+            __syncthreads();  // everyone is done with the window before
+            const LdsThread t;
+            const int64_t k = lds_columns(tile_k, t, N);
+            for (int32_t i = (int32_t)wave * kLdsTeams; i < cols; i += kLdsWaves * kLdsTeams) {
+                const int32_t row = i + t.team < cols ? i + t.team : cols - 1;
+                const float* from = B + (int64_t)(c0 + row) * N + k;
+                __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)from,
+                                                 (__attribute__((address_space(3))) void*)(s_b + i * kLdsCols), 16, 0, 0);
+            }
+            __builtin_amdgcn_s_waitcnt(kLdsNoLoads);
+            __syncthreads();
+            LdsWindow window{0u - (uint32_t)c0 * kLdsRowBytes, (uint32_t)cols * kLdsRowBytes};
+            asm volatile("" : "+s"(window.minus_first));  // (else a subtraction and a shift, where one instruction does both)
+            uint32_t open = 0;  // slots with more to do
+            lds_each<R>([&](auto I) {
+                constexpr int r = decltype(I)::value, ahead = (r + 2) % R;
+                // A compute unit issues its oldest wavefronts first: with nothing said the youngest take twice as long and
+                // the others wait for them at the end of the window.  So a wavefront steps back as it gets on.
+                if constexpr (r % (R / 4) == 0) __builtin_amdgcn_s_setprio(3 - r / (R / 4));
+                const LdsEntries e = held[0];
+                held[0] = held[1];
+                const uint32_t end = next_end;
+                next_end = end_of[(r + 1) % R];
+                // (this way round: v_subrev with row_newbcast, which end - pos becomes, hands round the wrong operand)
+                const int32_t over = team_bcast<r % kLdsTeam>(pos[r / kLdsTeam]) - (int32_t)end;
+                bool slot_open;
+                const uint32_t taken = lds_slot(mine, acc[r], e, over, window, l, slot_open);
+                if (slot_open) open |= 1u << r;
+                open = (uint32_t)__builtin_amdgcn_readfirstlane((int)open);
+                asm volatile("" : "+s"(open));  // (now: the compiler would keep every slot's masks until the last)
+                pos[r / kLdsTeam] += __builtin_amdgcn_inverse_ballot_w64(0x0001000100010001ull << (r % kLdsTeam)) ? (int32_t)taken : 0;
+                held[1] = matrix.load((uint32_t)team_bcast<ahead % kLdsTeam>(pos[ahead / kLdsTeam]) + l.member8);
+            });
+            const bool final = w + 1 == count;  // of the share: takes all that is left (of rows that are not sorted)
+            if (final) {
+                const LdsThread t;
+#pragma unroll
+                for (int h = 0; h < 2; ++h) {
+                    const int slot = h * kLdsTeam + t.member;
+                    const unsigned long long some = __ballot(slot < R && (uint32_t)pos[h] < end_of[slot < R ? slot : 0]);
+                    open |= (uint32_t)((some | some >> 16 | some >> 32 | some >> 48) & 0xFFFFu) << (h * kLdsTeam);
+                }
+            }
+            if (open) {
+                const LdsThread t;
+                const int64_t k = lds_columns(tile_k, t, N);
+                const bool own = tile_k + t.member * 4 < N && t.member * 4 < (int)plan.tile_cols;
+                do {
+                    const uint32_t r = (uint32_t)__ffs((int)open) - 1u;
+                    open &= open - 1u;
+                    const bool upper = r >= kLdsTeam;
+                    const uint32_t p = (uint32_t)__shfl(upper ? pos[1] : pos[0], (int)(r % kLdsTeam), kLdsTeam);
+                    const uint32_t q = list_place(r, t.team);
+                    float* row = own && q < n ? C + (int64_t)scr.rows[scr.order[q]] * N + k : nullptr;
+                    const uint32_t after = lds_rest(matrix, B + k, N, row, p, end_of[r], final ? 0x7fffffff : c0 + cols, l);
+                    if (t.member == (int)(r % kLdsTeam)) (upper ? pos[1] : pos[0]) = (int32_t)after;
+                } while (open);
+                // (the first two slots may have been among them)
+                lds_each<2>([&](auto I) {
+                    constexpr int i = decltype(I)::value;
+                    held[i] = matrix.load((uint32_t)team_bcast<i>(pos[0]) + l.member8);
+                });
+            }
+        }
+        __syncthreads();  // everyone is done with the last window: its place serves the sums on their way out
+        // (a wavefront's sums change lanes, so that an atomic instruction covers consecutive words: lanes that are 16
+        // bytes apart keep the memory pipeline busy four times longer)
+        const LdsThread t;
+        float* out = s_b + wave * (kWave * 4);
+        lds_each<R>([&](auto I) {
+            constexpr int r = decltype(I)::value;
+            const uint32_t q = list_place(r, t.team);
+            *reinterpret_cast<float4*>(out + t.lane * 4) = make_float4(acc[r].v[0], acc[r].v[1], acc[r].v[2], acc[r].v[3]);
+            __builtin_amdgcn_wave_barrier();
+            if (q < n) {
+                float* row = C + (int64_t)scr.rows[scr.order[q]] * N + tile_k;
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const int col = i * kLdsTeam + t.member;
+                    const float sum = out[t.team * kLdsCols + col];
+                    if (col < (int)plan.tile_cols && tile_k + col < N) unsafeAtomicAdd(row + col, sum);
+                }
+            }
+            __builtin_amdgcn_wave_barrier();
+        });
+    }
+}
+
+}  // namespace sgap
