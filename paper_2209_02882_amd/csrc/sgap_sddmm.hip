@@ -226,28 +226,48 @@ __global__ __launch_bounds__(kBlock) void sddmm_kernel(SddmmArgs s, int per_lane
 //   - one multiply-add forms the address of a row of X2T, its S steps differ by a constant offset;
 //   - the next tile's entries and row pointers are requested before this one is multiplied out.
 // stencil27, J = 128, G = 8: 1,031 us with tiles of 1,024 entries, rows of X1 read from memory per batch and a
-// bisection per entry; 825 us now, at 2.3 instead of 4.7 GB moved (the tile: see try_tile).  What is left is the L1:
-// a workgroup takes the rows one after the other, so that only consecutive columns hit, and asks the L2 for twice the
-// lines that SpMM's row-split kernel does with eight rows in step.  A kernel with the rows in step ran 740 us here but
-// took two to three times as long on R-MAT, whose heavy rows sit together.
+// bisection per entry; 831 us with the above, at 2.3 instead of 4.7 GB moved (the tile: see try_tile).
+// IN_STEP: what was left then was the L1: a workgroup that takes the rows one after the other finds only consecutive
+// columns there, and asks the L2 for twice the lines that SpMM's row-split kernel does with eight rows in step.  So a
+// tile's entries change their order: the first ones of all its rows, then the second ones, and so on, the wavefronts
+// through it together.  No lane waits for a longer row (a kernel that gave every row its lanes took two to three times as
+// long on R-MAT, whose heavy rows sit together).  Four instead of eight loads in flight per lane, six wavefronts per SIMD
+// instead of four: 831 -> 675 us (stencil of 60 x 57 x 62: 160 -> 132; in step with eight loads in flight: 790).  Columns
+// without order: uniform, 5 entries a row 97 -> 94, R-MAT of 2^18 rows 186 -> 184; uniform, 30 a row 99 -> 102, power law
+// 123 -> 128.
 // EDGE: J is not S*G*4 (lanes without columns, or a ragged last chunk).  Those instances with S = 4 and 512 entries keep
 // two registers in memory; computed anew per tile, what they hold costs more (R-MAT of 2^19 rows, J = 35, G = 4: 165.9
 // us against 164.8).
+// Tiles of wide rows without lanes to spare.
+__host__ __device__ constexpr bool in_step(bool edge, int ept) { return !edge && ept == 1; }
+constexpr int kX1LdsBytes = 10 * 1024;  // rows of X1 in LDS per 256 entries of a tile: 20 of 512 bytes
+__host__ __device__ constexpr int x1_pitch(int columns, bool edge, int ept)
+{
+    return in_step(edge, ept) && columns % 64 == 0 ? columns + 32 : columns;
+}
+
 template <int G, int S, bool EDGE, int EPT>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) void sddmm_tile_kernel(SddmmArgs s, int x1_rows)
 {
     constexpr int VEC = 4;
+    constexpr bool IN_STEP = in_step(EDGE, EPT);
     constexpr int GROUPS = kWave / G;
     constexpr int TILE = EPT * kBlock;
     constexpr int WAVE_RUN = TILE / kWavesPerBlock;
-    constexpr int U0 = 8 / S;  // entries per group and batch: 8 loads in flight per lane
+    constexpr int U0 = (IN_STEP ? 4 : 8) / S;  // entries per group and batch: 4 or 8 loads in flight per lane
     constexpr int U = U0 * GROUPS > WAVE_RUN ? WAVE_RUN / GROUPS : U0;
-    constexpr int PITCH = S * G * VEC;  // floats of one row of X1 in LDS, zeros behind column J
+    // floats of one row of X1 in LDS, zeros behind column J; IN_STEP: groups read neighbouring rows at the same columns
+    // together, so neighbours begin in different halves of the banks
+    constexpr int PITCH = x1_pitch(S * G * VEC, EDGE, EPT);
+    constexpr int ROW_CHUNKS = S * G;
     constexpr int WPT = EPT + 1;  // row pointers per thread: a window of TILE rows
     extern __shared__ __align__(16) float s_x1[];
     __shared__ __align__(16) int32_t s_col[TILE];
     __shared__ __align__(16) float s_val[TILE];
     __shared__ __align__(16) uint16_t s_idx[TILE];  // window index of the entry's row
+    // IN_STEP: where an entry comes from in the tile, and the results in the tile's order
+    __shared__ uint16_t s_from[IN_STEP ? TILE : 1];
+    __shared__ float s_out[IN_STEP ? TILE : 1];
     __shared__ int32_t s_win[TILE + 1];
     __shared__ int32_t s_row[TILE];
     __shared__ int32_t s_scan[kWavesPerBlock];
@@ -328,10 +348,14 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
             const int cnt = tile_end - tile_start;
             const int32_t row_lb = s_tile_row[j - j0];
             // install the tile that was fetched ahead (the barrier at the end of the loop: the last one is consumed)
+            const int32_t my_col = nx_col[0];
+            const float my_val = nx_val[0];
+            if constexpr (!IN_STEP) {
 #pragma unroll
-            for (int i = 0; i < EPT; ++i) {
-                s_col[tid + i * kBlock] = nx_col[i];
-                s_val[tid + i * kBlock] = nx_val[i];
+                for (int i = 0; i < EPT; ++i) {
+                    s_col[tid + i * kBlock] = nx_col[i];
+                    s_val[tid + i * kBlock] = nx_val[i];
+                }
             }
 #pragma unroll
             for (int i = 0; i < WPT; ++i)
@@ -347,9 +371,9 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
             }
             const bool x1_in_lds = n <= x1_rows;
             if (x1_in_lds) {
-                for (int i = tid; i < n * (PITCH / VEC); i += kBlock) {
-                    const int r = i / (PITCH / VEC);
-                    const int32_t c = i % (PITCH / VEC) * VEC;
+                for (int i = tid; i < n * ROW_CHUNKS; i += kBlock) {
+                    const int r = i / ROW_CHUNKS;
+                    const int32_t c = i % ROW_CHUNKS * VEC;
                     Vec<VEC> x;
                     if constexpr (EDGE) {
                         x.zero();
@@ -363,10 +387,31 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
                     } else {
                         x = load_vec<VEC>(s.X1 + (int64_t)s_row[r] * J + c);
                     }
-                    *reinterpret_cast<float4*>(s_x1 + i * VEC) = make_float4(x.v[0], x.v[1], x.v[2], x.v[3]);
+                    *reinterpret_cast<float4*>(s_x1 + r * PITCH + c) = make_float4(x.v[0], x.v[1], x.v[2], x.v[3]);
                 }
             }
-            {
+            if constexpr (IN_STEP) {
+                // Entry number i of its row in the tile comes behind the entries number 0 .. i - 1 of every row and those
+                // number i of the rows in front: where rows have entries alike, neighbouring rows' come together.
+                const int32_t p = tile_start + tid;
+                const int32_t wi = last_row_at_or_before(s_win, 0, n - 1, p);
+                int32_t place = tid;
+                if (x1_in_lds && tid < cnt) {
+                    const int32_t number = p - (s_win[wi] > tile_start ? s_win[wi] : tile_start);
+                    int32_t begin = tile_start;  // of a row, in the tile
+                    place = 0;
+                    for (int32_t r = 0; r < n; ++r) {
+                        const int32_t end = s_win[r + 1] < tile_end ? s_win[r + 1] : tile_end;
+                        const int32_t limit = number + (r < wi ? 1 : 0);
+                        place += end - begin < limit ? end - begin : limit;
+                        begin = end;
+                    }
+                }
+                s_col[place] = my_col;
+                s_val[place] = my_val;
+                s_idx[place] = (uint16_t)wi;
+                s_from[place] = (uint16_t)tid;
+            } else {
                 int32_t wi = last_row_at_or_before(s_win, 0, n - 1, tile_start + tid * EPT);
 #pragma unroll
                 for (int i = 0; i < EPT; ++i) {
@@ -386,19 +431,21 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
             auto batch = [&](int b, auto b_const, auto lds_const) {
                 constexpr int B = decltype(b_const)::value;
                 constexpr bool LDS_X1 = decltype(lds_const)::value;
-                const int e = b + grp * B;
+                // (IN_STEP: neighbouring groups on neighbouring entries; else a group's entries, and so its results, together)
+                const int e = IN_STEP ? b + grp : b + grp * B;
+                constexpr int NEXT = IN_STEP ? GROUPS : 1;
                 float acc[B];
                 Vec<VEC> x2[B][S];
 #pragma unroll
                 for (int u = 0; u < B; ++u) {
                     acc[u] = 0.0f;
 #pragma unroll
-                    for (int st = 0; st < S; ++st) x2[u][st] = load_chunk(a.B, s_col[e + u], st);
+                    for (int st = 0; st < S; ++st) x2[u][st] = load_chunk(a.B, s_col[e + u * NEXT], st);
                 }
                 if constexpr (LDS_X1) {
 #pragma unroll
                     for (int u = 0; u < B; ++u) {
-                        const int32_t idx = s_idx[e + u];
+                        const int32_t idx = s_idx[e + u * NEXT];
                         if (idx != cur) {
 #pragma unroll
                             for (int st = 0; st < S; ++st) {
@@ -414,7 +461,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
                     Vec<VEC> x1[B][S];
 #pragma unroll
                     for (int u = 0; u < B; ++u) {
-                        const int32_t row = s_row[s_idx[e + u]];
+                        const int32_t row = s_row[s_idx[e + u * NEXT]];
 #pragma unroll
                         for (int st = 0; st < S; ++st) x1[u][st] = load_chunk(s.X1, row, st);
                     }
@@ -426,7 +473,12 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
                 }
 #pragma unroll
                 for (int u = 0; u < B; ++u) acc[u] = group_tree_sum<G, 1>(acc[u]);
-                if (member == 0) {
+                if constexpr (IN_STEP) {
+                    if (member == 0) {
+#pragma unroll
+                        for (int u = 0; u < B; ++u) s_out[s_from[e + u * NEXT]] = acc[u] * s_val[e + u * NEXT];
+                    }
+                } else if (member == 0) {
                     // the group's outputs are consecutive, and so are the groups'
 #pragma unroll
                     for (int u = 0; u < B; ++u) acc[u] *= s_val[e + u];
@@ -445,27 +497,34 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
             };
             const int run_end = (wave + 1) * WAVE_RUN < cnt ? (wave + 1) * WAVE_RUN : cnt;
             if (x1_in_lds) {
-                for (int b = wave * WAVE_RUN; b < run_end; b += GROUPS * U)
-                    batch(b, std::integral_constant<int, U>{}, std::true_type{});
+                if constexpr (IN_STEP) {
+                    for (int b = wave * GROUPS * U; b < cnt; b += kWavesPerBlock * GROUPS * U)
+                        batch(b, std::integral_constant<int, U>{}, std::true_type{});
+                } else {
+                    for (int b = wave * WAVE_RUN; b < run_end; b += GROUPS * U)
+                        batch(b, std::integral_constant<int, U>{}, std::true_type{});
+                }
             } else {
                 constexpr int H = U < 2 ? 1 : U / 2;
                 for (int b = wave * WAVE_RUN; b < run_end; b += GROUPS * H)
                     batch(b, std::integral_constant<int, H>{}, std::false_type{});
             }
             __syncthreads();  // the tile is consumed
+            if constexpr (IN_STEP) {
+                // (nobody writes here before the barriers of the next tile)
+                if (tid < cnt) __builtin_nontemporal_store(s_out[tid], s.out + tile_start + tid);
+            }
         }
     }
 }
 
 namespace {
 
-constexpr int kX1LdsBytes = 10 * 1024;  // rows of X1 in LDS per 256 entries of a tile: 20 of 512 bytes
-
 template <int G, int S, bool EDGE, int EPT>
 void launch_tile(const SddmmArgs& s, int compute_units, int64_t nnz_hint, hipStream_t stream)
 {
     constexpr int x1_rows = EPT * kX1LdsBytes / (S * G * 16);
-    constexpr int x1_bytes = x1_rows * S * G * 16;
+    constexpr int x1_bytes = x1_rows * x1_pitch(S * G * 4, EDGE, EPT) * 4;
     static const int per_cu = resident_per_cu(sddmm_tile_kernel<G, S, EDGE, EPT>, x1_bytes);
     const int grid = persistent_grid(per_cu, compute_units, nnz_hint, EPT * kBlock);
     hipLaunchKernelGGL((sddmm_tile_kernel<G, S, EDGE, EPT>), dim3(grid), dim3(kBlock), x1_bytes, stream, s, x1_rows);

@@ -125,3 +125,21 @@ def test_unaligned_operands_take_the_narrow_loads():
                                    binding.STRATEGIES[st])
             torch.cuda.synchronize()
             check(out, ref, bnd, False, f"shift {shift} g={g} {st}")
+
+
+# tiles of 256 entries whose entries change their order: one row in a tile, more rows than LDS has places for (20 of 128
+# columns), rows that begin and end inside a tile, none, a last tile of one entry
+@pytest.mark.parametrize("J,g", [(128, 8), (128, 16), (256, 16), (128, 32)])
+@pytest.mark.parametrize("lengths", ["alike", "one long", "short", "mixed", "with gaps"])
+def test_entries_of_a_tile_in_step(J, g, lengths):
+    rng = np.random.default_rng(J + g)
+    rows = {"alike": np.full(300, 27), "one long": np.array([3, 1500, 2, 255, 256, 257, 1]), "short": np.full(700, 3),
+            "mixed": rng.integers(1, 90, 200), "with gaps": np.where(rng.random(3000) < 0.1, rng.integers(1, 40, 3000), 0)}[lengths]
+    rows = np.append(rows, (1 - int(rows.sum())) % 256)  # one entry behind the last whole tile
+    M, K = rows.size, 2000
+    rowptr, colidx = wl.csr_from_lengths(rng, rows, K)
+    vals = wl.fill_values(rng, colidx.size, True)
+    p = wl.SpmmProblem("in step", M, K, J, rowptr, colidx, vals, wl.fill_values(rng, K * J, True).reshape(K, J))
+    X1 = wl.fill_values(rng, M * J, True).reshape(M, J)
+    ref, bnd = oracle.sddmm_csr(M, K, J, rowptr, colidx, vals, X1, p.B, nthreads=8)
+    check(DeviceProblem(p).run_sddmm(torch.from_numpy(X1).cuda(), g, "parallel"), ref, bnd, True, f"J={J} g={g} {lengths}")
