@@ -366,7 +366,8 @@ int sgap_sddmm_csr(int64_t M, int64_t K, int64_t J,
  * aligned; otherwise the call is sgap_sddmm_csr.  Every entry still has one
  * writer: no atomics, results reproducible.
  *   long_row_min, window_kb (automatic: 2048), max_long_rows
- *                    as in sgap_config
+ *                    as in sgap_config; the windows in LDS are of at most
+ *                    149 KiB here
  *   workspace, workspace_bytes
  *                    device memory, 256-byte aligned, of at least
  *                    sgap_sddmm_csr_workspace_size(K, J, window_kb,

@@ -34,6 +34,7 @@
 #include "sgap_dot8.hpp"
 #include "sgap_lane_ops.hpp"
 #include "sgap_panels_lds.hpp"
+#include "sgap_panels_lds_dots.hpp"
 #include "sgap_row_split_impl.hpp"
 #include "sgap_uniform.hpp"
 
@@ -731,7 +732,7 @@ hipError_t launch_row_split_panels(const SpmmArgs& a, int g, int lc, int vec, in
     const bool owners = wave_lc == kPanelTileLanes && a.N >= 128;
     const uint32_t lds_workgroups = (uint32_t)(compute_units / xcds > 0 ? compute_units / xcds : 1);
     const LdsArgs lds{a.N >= kLdsMinCols ? kLdsMinRows : 0xffffffffu, (uint32_t)xcds, lds_workgroups, cap * (windows + 1),
-                      window_bytes <= kLdsWindow * kLdsRowBytes ? (int32_t)std::max<int64_t>(1, window_bytes / kLdsRowBytes) : 0};
+                      window_bytes <= kLdsWindow * kLdsRowBytes ? (int32_t)std::max<int64_t>(1, window_bytes / kLdsRowBytes) : 0, false};
     launch_panel_preparation(a, scr, windows, window_rows, min_len, true, owners, xcds, compute_units, lds, s);
     if (!owners && lds.min_rows != 0xffffffffu)
         hipLaunchKernelGGL(panel_lds_kernel, dim3(lds_workgroups * (uint32_t)xcds), dim3(kLdsBlock), 0, s, a.colidx, a.vals, a.B,
@@ -835,7 +836,7 @@ __global__ __launch_bounds__(kBlock) void panel_sddmm_kernel(SpmmArgs a, const f
     // below: the kernel runs only for lists of fewer rows (longer lists are panel_sddmm_owner_kernel's)
     __shared__ uint32_t s_claim;
     const uint32_t n = scr.head->count;
-    if (n == 0 || n > scr.cap || n >= below) return;
+    if (n == 0 || n > scr.cap || n >= below || scr.head->lds.on) return;
     const int lane = threadIdx.x % kWave;
     const int wave = threadIdx.x / kWave;
     const int per_row = windows + 1;
@@ -911,7 +912,7 @@ __global__ __launch_bounds__(kOwnerBlock) void panel_sddmm_owner_kernel(const in
 {
     constexpr int R = kOwnerRows;
     const uint32_t n = scr.head->count;
-    if (n < min_rows || n > scr.cap) return;
+    if (n < min_rows || n > scr.cap || scr.head->lds.on) return;
     const int lane = threadIdx.x % kWave;
     const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
     const uint32_t xcd = blockIdx.x % xcds;
@@ -1045,6 +1046,17 @@ __global__ __launch_bounds__(kBlock) void sddmm_short_rows_kernel(SpmmArgs a, co
     }
 }
 
+__global__ __launch_bounds__(kLdsBlock) void panel_lds_dots_kernel(const int32_t* __restrict__ colidx,
+                                                                   const float* __restrict__ vals,
+                                                                   const float* __restrict__ X1,
+                                                                   const float* __restrict__ X2T, float* __restrict__ out,
+                                                                   PanelView scr, int64_t K, int64_t J, LdsArgs lds)
+{
+    __shared__ DotsShared s_dots;
+    const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    if (scr.head->lds.on) panel_lds_dots(colidx, vals, X1, X2T, out, scr, K, J, lds, wave, s_dots);
+}
+
 namespace {
 
 constexpr int32_t kShortRow = 1024;  // rows of fewer entries are a member's of sddmm_short_rows_kernel
@@ -1084,8 +1096,14 @@ hipError_t launch_sddmm_panels(const SpmmArgs& a, const float* X1, float* out, i
     int wave_lc = 8;
     while (wave_lc < kWave && (int64_t)wave_lc * 4 < a.N) wave_lc *= 2;
     const bool owners = wave_lc == kWave;
-    launch_panel_preparation(a, scr, windows, window_rows, min_len, false, owners, owners ? xcds : 1, compute_units, LdsArgs{0xffffffffu, 1, 1, 0, 0}, s);
+    const uint32_t lds_workgroups = (uint32_t)(compute_units / xcds > 0 ? compute_units / xcds : 1);
+    const LdsArgs lds{a.N >= kLdsMinCols ? kLdsMinRows : 0xffffffffu, (uint32_t)xcds, lds_workgroups, cap * (windows + 1),
+                      window_bytes <= kDotsWindow * kLdsRowBytes ? (int32_t)std::max<int64_t>(1, window_bytes / kLdsRowBytes) : 0, true};
+    launch_panel_preparation(a, scr, windows, window_rows, min_len, false, owners, owners ? xcds : 1, compute_units, lds, s);
     uint32_t below = 0xffffffffu;
+    if (lds.min_rows != 0xffffffffu)
+        hipLaunchKernelGGL(panel_lds_dots_kernel, dim3(lds_workgroups * (uint32_t)xcds), dim3(kLdsBlock), 0, s, a.colidx, a.vals, X1,
+                           a.B, out, scr, a.K, a.N, lds);
     if (owners) {
         below = owner_min_rows(xcds, compute_units);
         int grid = compute_units;

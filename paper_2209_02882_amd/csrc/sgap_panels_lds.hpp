@@ -51,6 +51,7 @@ struct LdsArgs {
     uint32_t workgroups;  // of a die
     int64_t ptr_room;     // pointers there is room for
     int32_t window;       // columns of a window at most, as the caller asks for them (the kernel runs then); 0: he does not
+    bool dots;            // SDDMM: a job has all columns of its rows
 };
 
 // How the list's rows are laid over the workgroups.  Their number is not known on the host: the workgroups of
@@ -71,7 +72,8 @@ __device__ __forceinline__ LdsPlan lds_plan(const PanelHeader* head, const LdsAr
     // Lane l: l + 1 shares per die, with the fewest groups of rows and up to three more.  Clocks of a job, roughly (500,000
     // rows, 5,000 of them long with 11,000 entries in the mean, N = 256: 2.77 M by this, 2.6 M measured): a wavefront's
     // pass over a slot in a window, the window on its way into LDS, the sums added into C at the end; and the search for
-    // the shares' ends before.
+    // the shares' ends before.  SDDMM passes once for every tile, and what looking up and writing its entries adds is
+    // about one pass more (the same matrix: 3.51 M by this, 3.49 M measured; 64 columns: 1.46 M and 1.40 M).
     p.window = args.window > 0 ? args.window : (int32_t)fmaxf(1.0f, fminf((float)kLdsWindow, 16.0f / per_col));
     const uint32_t lane = threadIdx.x % kWave;
     unsigned long long best = ~0ull;
@@ -81,10 +83,11 @@ __device__ __forceinline__ LdsPlan lds_plan(const PanelHeader* head, const LdsAr
         const int64_t shares = (int64_t)(lane + 1) * dies;
         const int64_t share_cols = (K + shares - 1) / shares;
         const uint32_t windows = (uint32_t)((share_cols + p.window - 1) / p.window);
-        const uint32_t rounds = (p.tiles * groups * (lane + 1) + args.workgroups - 1) / args.workgroups;
-        const float slot = 600.0f + 128.0f * per_col * (float)share_cols / (float)windows;
-        const float cost = (float)rounds * ((float)windows * ((float)slots * slot + 5000.0f) + (float)slots * 7400.0f)
-                           + 0.3f * (float)n * (float)shares;
+        const float in_window = per_col * (float)share_cols / (float)windows;  // entries of a row
+        const uint32_t rounds = ((args.dots ? 1 : p.tiles) * groups * (lane + 1) + args.workgroups - 1) / args.workgroups;
+        const float job = args.dots ? (float)(windows * (p.tiles + 1)) * ((float)slots * (700.0f + 117.0f * in_window) + 6000.0f)
+                                    : (float)windows * ((float)slots * (600.0f + 128.0f * in_window) + 5000.0f) + (float)slots * 7400.0f;
+        const float cost = (float)rounds * job + 0.3f * (float)n * (float)shares;
         const bool fits = (shares + 1) * n <= args.ptr_room;
         const unsigned long long key = (unsigned long long)__float_as_uint(cost) << 32 | more << 8 | lane;
         if (fits && key < best) best = key;
@@ -108,10 +111,26 @@ __device__ __forceinline__ LdsPlan lds_plan(const PanelHeader* head, const LdsAr
     //   120,000          1,320          136 /   110   177 /   157     272 /   203
     //    60,000          4,125          127 /   256   150 /   185     210 /   213
     //    26,000          1,650                         85 /   173
-    float gather = (float)entries * (float)N * 4.0f / ((float)(dies * args.workgroups) * (N > 128 ? 43.0f : 29.0f));
-    if (N <= 128) gather *= fmaxf(1.0f, 1200.0f / (float)n);
+    // SDDMM's gathering kernels reach 50 and 40 bytes per clock where there are rows enough, spend something on every long
+    // row's part of a panel of 2 MiB and the rest on filling and draining the chip (constants fitted to 55 calls; what the
+    // rule misses is within 10 %):
+    //   500,000          11,000         768 / 1,041   1,229 / 1,775   2,085 / 2,749
+    //   500,000          5,500          644 /   649     957 / 1,112   1,603 / 1,691
+    //   500,000          2,750          556 /   465     838 /   822   1,389 / 1,158
+    //   120,000          1,320          127 /   110     147 /   162     232 /   216
+    //    60,000          4,125           93 /   205     147 /   204     187 /   226
+    //    60,000          1,650           72 /   119     111 /   126     168 /   136
+    float gather = (float)entries * (float)N * 4.0f / (float)(dies * args.workgroups);
+    if (args.dots) {
+        const float pieces = (float)n * (float)K * (float)N * 4.0f / (float)(2 << 20);
+        gather = N > 128 ? gather / 50.0f * (1.0f + 400.0f / (float)n) + 0.15f * pieces - 27000.0f
+                         : gather / 40.0f * (1.0f + 800.0f / (float)n) + 0.6f * pieces + 40000.0f;
+    } else {
+        gather /= N > 128 ? 43.0f : 29.0f;
+        if (N <= 128) gather *= fmaxf(1.0f, 1200.0f / (float)n);
+    }
     const bool faster = args.window > 0 || __uint_as_float((uint32_t)(best >> 32)) < gather;
-    p.on = best != ~0ull && faster && head->nnz < kLdsMaxNnz && K <= (1 << 24);
+    p.on = best != ~0ull && faster && head->nnz < kLdsMaxNnz && K <= (1 << 24) && N < (1 << 30);
     return p;
 }
 
