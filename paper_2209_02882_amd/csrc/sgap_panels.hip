@@ -370,45 +370,47 @@ __global__ __launch_bounds__(kBlock) void panel_long_rows_kernel(SpmmArgs a, Pan
 }
 
 // order[] = the long rows sorted by length, longest first (ties by their place in rows[]).  Every row counts
-// the rows that come before it, sixteen lanes to a row, with all lengths in LDS; a list of more than
+// the rows that come before it, sixteen lanes to a row, with a piece of the lengths in LDS at a time; a list of more than
 // kRankMaxRows rows keeps the order in which the rows were found (panel_pointers_kernel wrote it): with so
 // many rows every wavefront owns several dozen and their lengths average out.
 constexpr int kRankLanes = 16;
-static_assert(kRankMaxRows % (kRankLanes * 4) == 0, "the padded list fits the LDS array");
+// 8 KB, so that the LDS does not keep the pointers' workgroups of the same launch off a compute unit (with all 8,192 lengths
+// there it held four: 5,000 rows, 325,000 pointers, 57 us; now 44).
+constexpr int kRankPiece = 2048;
+static_assert(kRankPiece % (kRankLanes * 4) == 0 && kRankPiece % kBlock == 0, "the padded piece fits the LDS array");
 __device__ __forceinline__ void panel_rank_body(const PanelView& scr, int32_t* s_len, uint32_t block)
 {
     const uint32_t n = scr.head->count;
     constexpr uint32_t rows_per_block = kBlock / kRankLanes;
     if (n == 0 || n > scr.cap || n > (uint32_t)kRankMaxRows || block * rows_per_block >= n) return;
-    // (padded to a multiple of the unrolled stride with lengths no row has: they come before nobody)
     constexpr uint32_t kStride = kRankLanes * 4;
-    const uint32_t n_pad = (n + kStride - 1) / kStride * kStride;  // <= kRankMaxRows, a multiple of kStride
-    constexpr int kAtOnce = 8;  // loads in flight per thread
-    for (uint32_t j0 = threadIdx.x; j0 < n_pad; j0 += kAtOnce * kBlock) {
+    constexpr int kAtOnce = kRankPiece / kBlock;  // loads in flight per thread
+    const uint32_t i = block * rows_per_block + threadIdx.x / kRankLanes;
+    const uint32_t part = threadIdx.x % kRankLanes;
+    const int32_t mine = i < n ? scr.len[i] : 0;
+    uint32_t before = 0;
+    for (uint32_t first = 0; first < n; first += kRankPiece) {
+        // (padded to a multiple of the unrolled stride with lengths no row has: they come before nobody)
+        const uint32_t here = n - first < (uint32_t)kRankPiece ? n - first : (uint32_t)kRankPiece;
+        const uint32_t padded = (here + kStride - 1) / kStride * kStride;
         int32_t len[kAtOnce];
 #pragma unroll
         for (int u = 0; u < kAtOnce; ++u) {
-            const uint32_t j = j0 + (uint32_t)u * kBlock;
-            len[u] = j < n ? scr.len[j] : -1;
+            const uint32_t j = threadIdx.x + (uint32_t)u * kBlock;
+            len[u] = j < here ? scr.len[first + j] : -1;
         }
+        if (first > 0) __syncthreads();  // everyone is done with the piece before
 #pragma unroll
-        for (int u = 0; u < kAtOnce; ++u) {
-            const uint32_t j = j0 + (uint32_t)u * kBlock;
-            if (j < n_pad) s_len[j] = len[u];
+        for (int u = 0; u < kAtOnce; ++u) s_len[threadIdx.x + (uint32_t)u * kBlock] = len[u];
+        __syncthreads();
+        for (uint32_t j0 = part; j0 < padded; j0 += kStride) {
+            int32_t other[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) other[u] = s_len[j0 + u * kRankLanes];
+#pragma unroll
+            for (int u = 0; u < 4; ++u)
+                before += (other[u] > mine || (other[u] == mine && first + j0 + u * kRankLanes < i)) ? 1u : 0u;
         }
-    }
-    __syncthreads();
-    const uint32_t i = block * rows_per_block + threadIdx.x / kRankLanes;
-    const uint32_t part = threadIdx.x % kRankLanes;
-    const int32_t mine = i < n ? s_len[i] : 0;
-    uint32_t before = 0;
-    for (uint32_t j0 = part; j0 < n_pad; j0 += kStride) {
-        int32_t other[4];
-#pragma unroll
-        for (int u = 0; u < 4; ++u) other[u] = s_len[j0 + u * kRankLanes];
-#pragma unroll
-        for (int u = 0; u < 4; ++u)
-            before += (other[u] > mine || (other[u] == mine && j0 + u * kRankLanes < i)) ? 1u : 0u;
     }
 #pragma unroll
     for (int m = kRankLanes / 2; m >= 1; m /= 2) before += (uint32_t)__shfl_xor((int)before, m, kRankLanes);
@@ -422,7 +424,7 @@ __global__ __launch_bounds__(kBlock) void panel_pointers_kernel(SpmmArgs a, Pane
                                                                 int32_t window_rows, int zero_rows, uint32_t few_from,
                                                                 int xcds, LdsArgs lds, uint32_t pointer_blocks)
 {
-    __shared__ int32_t s_len[kRankMaxRows];
+    __shared__ int32_t s_len[kRankPiece];
     const bool ranked = gridDim.x > pointer_blocks;
     if (blockIdx.x < pointer_blocks)
         panel_pointers_body<VEC>(a, scr, windows, window_rows, zero_rows, few_from, xcds, lds, ranked, blockIdx.x,
@@ -668,7 +670,9 @@ void launch_panel_preparation(const SpmmArgs& a, const PanelView& scr, int windo
     constexpr int64_t rows_per_block = (int64_t)kBlock * kFindRows;
     hipLaunchKernelGGL(panel_find_rows_kernel, dim3((unsigned)((a.M + rows_per_block - 1) / rows_per_block)), dim3(kBlock),
                        0, s, a, scr, min_len);
-    const uint32_t pointer_blocks = (uint32_t)compute_units * 4;
+    // (the search is bound by the lines that its probes fetch: 325,000 and 85,000 pointers take 47 and 26 us with four
+    // workgroups per compute unit, 44 and 26 with five, 42 and 28 with six, 56 and 33 with eight)
+    const uint32_t pointer_blocks = (uint32_t)compute_units * 5;
     uint32_t rank_blocks = 0;
     if (rank_rows) {
         const uint32_t rows = scr.cap < (uint32_t)kRankMaxRows ? scr.cap : (uint32_t)kRankMaxRows;

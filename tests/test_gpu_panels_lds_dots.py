@@ -40,7 +40,7 @@ def test_columns_and_windows(J, K):
         check(p, 40, f"J={J} K={K} {window_kb} KiB", window_kb=window_kb)
 
 
-@pytest.mark.parametrize("n_long,runs", [(255, 0), (256, 1), (257, 1), (1279, 1), (1281, 1), (2563, 1)])
+@pytest.mark.parametrize("n_long,runs", [(255, 0), (256, 1), (257, 1), (1279, 1), (1281, 1), (2048, 1), (2049, 1), (4161, 1)])
 def test_rows(n_long, runs):
     check(problem(n_long, 1500, 64, 160, seed=n_long), 30, f"{n_long} rows", runs=runs)
 
