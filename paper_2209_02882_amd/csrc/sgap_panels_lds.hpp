@@ -10,11 +10,12 @@
 //          about the same length (neighbours in the list sorted by length)
 //   slot   a team owns up to kLdsSlots rows, one after the other in every window: 16 wavefronts x 4 teams x 20 slots =
 //          1,280 rows per workgroup, 80 registers of sums per lane
-//   job    (share of the columns, 64 columns of B, 1,280 long rows); a die's workgroups work on the same share
-//          together, so that A and B come out of HBM once (1.25 GB fetched there, of 0.97 GB)
+//   job    (share of the columns, 64 columns of B, 1,280 long rows); a die's workgroups work on the same few
+//          shares together (3.8 GB fetched beyond the L2s, A once per 64 columns of B; the gathers fetched 1.2 GB there and
+//          57.6 GB out of the L2s)
 // Four entries of four rows cost a wavefront one addition (the address), one 16-byte LDS read and four multiply-adds; a
-// pair is handed round its team by DPP (row_newbcast), at no cost.  That makes the vector instructions the bound: 530 M on
-// the skewed matrix, 2.07 M clocks of a SIMD of 2.5 M in all (1.28 ms; the whole call 2.54 ms before, 1.62 now).  Half of
+// pair is handed round its team by DPP (row_newbcast), at no cost.  That makes the vector instructions the bound: 568 M on
+// the skewed matrix, 2.2 M clocks of a SIMD of 2.6 M in all (1.2 ms; the whole call 2.54 ms before, 1.61 now).  Half of
 // them are multiply-adds that A asks for; a sixth is what the four rows of a wavefront differ by in a window (the more
 // entries a row has there, the less: hence windows as large as LDS allows), a quarter what a slot costs by itself, and
 // the rest fills up pairs.  The remaining clocks are the windows' way into LDS (10 %) and waiting for the slowest
@@ -102,32 +103,32 @@ __device__ __forceinline__ LdsPlan lds_plan(const PanelHeader* head, const LdsAr
     p.slots = (quads + kLdsWaves * p.groups - 1) / (kLdsWaves * p.groups);
     p.per_die = (chosen & 63) + 1;
     p.share_cols = (int32_t)((K + (int64_t)p.per_die * dies - 1) / ((int64_t)p.per_die * dies));
-    // The kernels that gather every entry's row of B through the L2 take the clocks that its bytes need at 43 (owner
-    // wavefronts, N > 128) and 29 (claiming wavefronts) bytes per clock and compute unit, the latter more where there are
-    // too few rows to go round.  Measured around the line, us for the whole call, this kernel against those:
-    //   rows (1 % long)  mean long row  N = 64        N = 128       N = 256
-    //   500,000          5,500          584 /   632   806 / 1,050   1,291 / 1,559
-    //   500,000          2,750          517 /   434   697 /   721   1,136 / 1,057
-    //   120,000          1,320          136 /   110   177 /   157     272 /   203
-    //    60,000          4,125          127 /   256   150 /   185     210 /   213
-    //    26,000          1,650                         85 /   173
-    // SDDMM's gathering kernels reach 50 and 40 bytes per clock where there are rows enough, spend something on every long
-    // row's part of a panel of 2 MiB and the rest on filling and draining the chip (constants fitted to 55 calls; what the
-    // rule misses is within 10 %):
-    //   500,000          11,000         768 / 1,041   1,229 / 1,775   2,085 / 2,749
-    //   500,000          5,500          644 /   649     957 / 1,112   1,603 / 1,691
-    //   500,000          2,750          556 /   465     838 /   822   1,389 / 1,158
-    //   120,000          1,320          127 /   110     147 /   162     232 /   216
-    //    60,000          4,125           93 /   205     147 /   204     187 /   226
-    //    60,000          1,650           72 /   119     111 /   126     168 /   136
+    // The kernels that gather every entry's row of B through the L2.  Up to 128 columns: wavefronts that claim pieces, 29 bytes
+    // per clock and compute unit (SDDMM 40, and something for every long row's part of a panel of 2 MiB and for filling and
+    // draining the chip), more time where there are too few rows to go round.  Beyond: owner wavefronts, each with the same
+    // number of rows, rounded up, at 296 clocks per gathered row (the address units take as long for 132 columns as for 256).
+    // 160,000 clocks are what the model of the LDS kernel leaves out at its start; where the two are close the owners are kept.
+    // Measured around the line, us for the whole call, LDS against gathers (one row in a hundred is long):
+    //         rows      mean long row  N = 64        N = 128         N = 160       N = 208       N = 256
+    //   SpMM  500,000   5,500          584 /   632   806 / 1,050                                 1,291 / 1,559
+    //         500,000   2,750          517 /   434   697 /   721                                 1,136 / 1,057
+    //         120,000   8,250                                        437 / 514     452 / 511       432 /   546
+    //          88,000   6,050                                        314 / 299     329 / 285       316 /   304
+    //          60,000   4,125          127 /   256   150 /   185     261 / 259     344 / 320       330 /   337
+    //   SDDMM 500,000   5,500          644 /   649   957 / 1,112                                 1,603 / 1,691
+    //         500,000   2,750          556 /   465   838 /   822                                 1,389 / 1,158
+    //         120,000   8,250                                        311 / 471     408 / 547       399 /   582
+    //          88,000   6,050                                        281 / 265     344 / 308       346 /   325
+    //         120,000   1,320          127 /   110   147 /   162                                   232 /   216
+    const float pieces = (float)n * (float)K * (float)N * 4.0f / (float)(2 << 20);
     float gather = (float)entries * (float)N * 4.0f / (float)(dies * args.workgroups);
-    if (args.dots) {
-        const float pieces = (float)n * (float)K * (float)N * 4.0f / (float)(2 << 20);
-        gather = N > 128 ? gather / 50.0f * (1.0f + 400.0f / (float)n) + 0.15f * pieces - 27000.0f
-                         : gather / 40.0f * (1.0f + 800.0f / (float)n) + 0.6f * pieces + 40000.0f;
+    if (N > 128) {
+        const uint32_t owners = args.workgroups * kLdsWaves;
+        gather = 296.0f / (float)dies * (float)((n + owners - 1) / owners) * ((float)entries / (float)n) + 0.15f * pieces - 160000.0f;
+    } else if (args.dots) {
+        gather = gather / 40.0f * (1.0f + 800.0f / (float)n) + 0.6f * pieces + 40000.0f;
     } else {
-        gather /= N > 128 ? 43.0f : 29.0f;
-        if (N <= 128) gather *= fmaxf(1.0f, 1200.0f / (float)n);
+        gather = gather / 29.0f * fmaxf(1.0f, 1200.0f / (float)n);
     }
     const bool faster = args.window > 0 || __uint_as_float((uint32_t)(best >> 32)) < gather;
     p.on = best != ~0ull && faster && head->nnz < kLdsMaxNnz && K <= (1 << 24) && N < (1 << 30);
