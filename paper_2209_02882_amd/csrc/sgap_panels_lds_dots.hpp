@@ -82,7 +82,7 @@ struct DotsFound {
     unsigned long long taken[2];  // lanes whose entry i is one of the window's
     uint32_t most;                // entries of the team with the most
     bool full;                    // a team has taken all 32 and may have more
-    bool odd;                     // they are not the first ones (columns that are not sorted): none is taken
+    bool odd;                     // a team's are not the first ones (columns that are not sorted): it takes none
 };
 
 // over as for lds_slot.
@@ -95,12 +95,21 @@ __device__ __forceinline__ DotsFound dots_find(const uint32_t (&at)[2], int32_t 
         f.taken[i] = __ballot(at[i] < w.bytes) & __ballot(over < -(int32_t)(l.member8 / 2) - 4 * kLdsTeam * i);
     const unsigned long long gaps = ((f.taken[0] & ~(f.taken[0] << 1)) | (f.taken[1] & ~(f.taken[1] << 1))) & ~kFirst;
     const unsigned long long late = f.taken[1] & kFirst & ~(f.taken[0] >> (kLdsTeam - 1));
-    f.odd = (gaps | late) != 0;
-    f.full = !f.odd && (f.taken[1] >> (kLdsTeam - 1) & kFirst) != 0;
+    unsigned long long odd = gaps | late;
+    f.odd = odd != 0;
+    if (f.odd) {  // of those teams alone: how a row's sums are made does not depend on the rows beside it
+        odd = (odd | odd >> 8) & 0x00FF00FF00FF00FFull;
+        odd = (odd | odd >> 4) & 0x000F000F000F000Full;
+        odd = (odd | odd >> 2) & 0x0003000300030003ull;
+        odd = (odd | odd >> 1) & kFirst;
+        const unsigned long long lanes = (odd << kLdsTeam) - odd;
+        f.taken[0] &= ~lanes;
+        f.taken[1] &= ~lanes;
+    }
+    f.full = (f.taken[1] >> (kLdsTeam - 1) & kFirst) != 0;
     f.most = 0;
 #pragma unroll
     for (int i = 0; i < 2; ++i) {
-        if (f.odd) f.taken[i] = 0;
         const uint32_t both = (uint32_t)f.taken[i] | (uint32_t)(f.taken[i] >> 32);
         f.most += (uint32_t)__popc((both | both >> 16) & 0xFFFFu);
     }
@@ -363,7 +372,19 @@ __device__ __forceinline__ void panel_lds_dots(const int32_t* __restrict__ colid
                 open &= open - 1u;
                 const bool upper = r >= kLdsTeam;
                 const uint32_t p = (uint32_t)__shfl(upper ? pos[1] : pos[0], (int)(r % kLdsTeam), kLdsTeam);
-                const uint32_t after = dots_rest(matrix, vals, X1 + (int64_t)row_of[r] * J, X2T, out, J, p, end_of[r],
+                // The teams that have more to do here, each by its own row (else which entries come out of LDS, and with that
+                // the rounding, would depend on the rows beside it): those that took all 32, and those that took none of
+                // the window's.
+                const int32_t took = __shfl(upper ? taken[1] : taken[0], (int)(r % kLdsTeam), kLdsTeam);
+                bool more = final || took == 2 * kLdsTeam;
+#pragma unroll
+                for (int i = 0; i < 2; ++i) {
+                    const uint32_t at = p + member4 + 4 * kLdsTeam * i;
+                    const uint32_t col = __builtin_amdgcn_raw_buffer_load_b32(matrix.cols, (int)at, 0, 0);
+                    const bool here = at < end_of[r] && (col << 8) + window.minus_first < window.bytes;
+                    more |= team_field(__ballot(here && took == 0), l) != 0;
+                }
+                const uint32_t after = dots_rest(matrix, vals, X1 + (int64_t)row_of[r] * J, X2T, out, J, p, more ? end_of[r] : p,
                                                  final ? 0x7fffffff : c0 + cols, t.member);
                 if (t.member == (int)(r % kLdsTeam)) (upper ? pos[1] : pos[0]) = (int32_t)after;
             }

@@ -71,6 +71,27 @@ def test_unsorted_and_repeated_columns(n_long):
     check(p, 60, "unsorted, many windows", window_kb=16)
 
 
+# rows of one length, which the list holds in any order, a third of them without order of the columns
+@pytest.mark.parametrize("J", [68, 256])
+def test_the_rows_beside_a_row_do_not_change_its_results(J):
+    M, K, length = 600, 3000, 400
+    rng = np.random.default_rng(J)
+    cols = np.sort(rng.permuted(np.tile(np.arange(K, dtype=np.int32), (M, 1)), axis=1)[:, :length], axis=1)
+    cols[::3] = rng.permuted(cols[::3], axis=1)
+    vals, X1 = (wl.fill_values(rng, M * n, False).reshape(M, n) for n in (length, J))
+    rowptr = np.arange(M + 1, dtype=np.int32) * length
+
+    def run(order):
+        p = wl.SpmmProblem("order", M, K, J, rowptr, cols[order].ravel(), vals[order].ravel(), B)
+        X1d = torch.from_numpy(X1[order]).cuda()
+        return DeviceProblem(p).run_sddmm_windows(X1d, 8, "parallel", length, 149).cpu().numpy().reshape(M, length)
+
+    B = wl.fill_values(rng, K * J, False).reshape(K, J)
+    first = run(np.arange(M))
+    for order in (np.arange(M)[::-1], rng.permutation(M)):
+        assert np.array_equal(run(order), first[order])
+
+
 def test_infinite_and_nan_rows_reach_only_the_entries_that_name_them():
     p = problem(400, 3000, 68, 300, seed=5)
     p.B[11], p.B[1500], p.B[2999] = np.inf, np.nan, -np.inf
