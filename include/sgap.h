@@ -239,11 +239,12 @@ int sgap_spmm_csr_gr(int64_t M, int64_t K, int64_t N,
  *                   it when long rows hold most entries and B is far larger than
  *                   the L2s.  Needs a workspace (below).  0 = off.
  *   window_kb       KiB of B per column window (at most 511 windows are made);
- *                   automatic: 3072.  Lists of at least 256 long rows that hold
- *                   a fair share of the columns are multiplied out of windows in
- *                   LDS instead, from 64 columns of B on, where that is the
- *                   faster; a window of at most 154 KiB (of 64 columns of B)
- *                   asks for that form wherever it applies.
+ *                   automatic: 3072, except that lists of at least 256 long
+ *                   rows that hold a fair share of the columns are multiplied
+ *                   out of windows in LDS, from 64 columns of B on, where the
+ *                   library expects that to be the faster.  At most 154: windows
+ *                   in LDS (of that size for 64 columns of B) wherever they
+ *                   apply; more: never.
  *   max_long_rows   capacity of the list of long rows, at most 1,048,576;
  *                   automatic: 8192.  The rows are found on the device; when a
  *                   matrix has more long rows than this, the call produces every
@@ -366,8 +367,7 @@ int sgap_sddmm_csr(int64_t M, int64_t K, int64_t J,
  * aligned; otherwise the call is sgap_sddmm_csr.  Every entry still has one
  * writer: no atomics, results reproducible.
  *   long_row_min, window_kb (automatic: 2048), max_long_rows
- *                    as in sgap_config; the windows in LDS are of at most
- *                    149 KiB here
+ *                    as in sgap_config, with 149 in the place of 154
  *   workspace, workspace_bytes
  *                    device memory, 256-byte aligned, of at least
  *                    sgap_sddmm_csr_workspace_size(K, J, window_kb,

@@ -427,7 +427,7 @@ int spmm_impl(int64_t M, int64_t K, int64_t N, const int32_t* rowptr, const int3
         } else if (windows) {
             err = launch_row_split_panels(a, g, lc, vec, wave_vec > 0 ? wave_rows_count : rows_per_slot, par,
                                           (int)tile_cols, xcds, cus, c.persistent != 0, block, wave_vec, c.long_row_min,
-                                          window_bytes_of(c), workspace, long_rows_of(c), s);
+                                          window_bytes_of(c), c.window_kb > 0, workspace, long_rows_of(c), s);
         } else if (wave_vec > 0) {
             err = launch_wave_rows(a, wave_vec, wave_rows_count, xcds, nullptr, s);
         } else {
@@ -721,7 +721,7 @@ static int sddmm_impl(int64_t M, int64_t K, int64_t J, const int32_t* rowptr, co
         }
         err = launch_sddmm_panels(a, X1, out_vals, par ? group_size : 1, par ? 0 : group_size,
                                   g_xcd_remap == 0 ? 1 : kXcds, compute_units(), nnz_hint, long_row_min, window_bytes,
-                                  workspace, cap, s);
+                                  window_kb > 0, workspace, cap, s);
     } else
         err = launch_sddmm(a, X1, out_vals, par ? group_size : 1, par ? 0 : group_size, vec, g_sddmm_row_cache != 0,
                            compute_units(), nnz_hint, s);

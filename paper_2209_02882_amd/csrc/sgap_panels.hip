@@ -28,8 +28,6 @@
 // panel_workspace_bytes for a list of `cap` rows).  When the matrix has more long
 // rows than the list holds, this path does nothing and the row-split kernel
 // takes every row.
-#include <algorithm>
-
 #include "sgap_common.hpp"
 #include "sgap_dot8.hpp"
 #include "sgap_lane_ops.hpp"
@@ -656,6 +654,22 @@ void plan_panels(int64_t K, int64_t N, int64_t window_bytes, int* windows, int32
     *window_rows = (int32_t)rows;
 }
 
+// What the caller says about the windows: nothing, and the device chooses between windows in LDS and windows that the L2
+// holds; a size that fits in LDS, and they lie there; a larger one, and they do not.
+LdsArgs lds_args(int64_t N, int windows, int64_t window_bytes, bool asked, int xcds, int compute_units, int64_t cap, bool dots)
+{
+    const int64_t rows = window_bytes / kLdsRowBytes;
+    const bool fit = rows <= (dots ? kDotsWindow : kLdsWindow);
+    LdsArgs lds;
+    lds.min_rows = N >= kLdsMinCols && (fit || !asked) ? kLdsMinRows : 0xffffffffu;
+    lds.dies = (uint32_t)xcds;
+    lds.workgroups = (uint32_t)(compute_units / xcds > 0 ? compute_units / xcds : 1);
+    lds.ptr_room = cap * (windows + 1);
+    lds.window = asked && fit ? (int32_t)(rows > 0 ? rows : 1) : 0;
+    lds.dots = dots;
+    return lds;
+}
+
 // The preparation both operators share: list of the rows of at least min_len
 // entries, their window pointers, and (zero_rows) zeros in their rows of C.
 // owners: the list goes to panel_owner_kernel when it is long enough (the rows are ranked for it, and
@@ -718,8 +732,8 @@ int64_t sddmm_panels_workspace_bytes(int64_t K, int64_t J, int64_t window_bytes,
 // bytes.  lc and the other row-split arguments as for launch_row_split.
 hipError_t launch_row_split_panels(const SpmmArgs& a, int g, int lc, int vec, int rows_per_slot, bool interleave,
                                    int tile_cols, int xcds, int compute_units, bool persistent, int block,
-                                   int wave_vec, int32_t min_len, int64_t window_bytes, void* workspace, int64_t cap,
-                                   hipStream_t s)
+                                   int wave_vec, int32_t min_len, int64_t window_bytes, bool window_asked,
+                                   void* workspace, int64_t cap, hipStream_t s)
 {
     if (vec != 4 || min_len < 1 || xcds < 1 || !workspace || cap < 1) return hipErrorInvalidValue;
     int wave_lc = 1, windows = 1;
@@ -734,12 +748,10 @@ hipError_t launch_row_split_panels(const SpmmArgs& a, int g, int lc, int vec, in
     const PanelView scr = panel_view(workspace, cap, windows);
     // a wavefront per row with all 64 lanes on column chunks: worth it from 128 columns on
     const bool owners = wave_lc == kPanelTileLanes && a.N >= 128;
-    const uint32_t lds_workgroups = (uint32_t)(compute_units / xcds > 0 ? compute_units / xcds : 1);
-    const LdsArgs lds{a.N >= kLdsMinCols ? kLdsMinRows : 0xffffffffu, (uint32_t)xcds, lds_workgroups, cap * (windows + 1),
-                      window_bytes <= kLdsWindow * kLdsRowBytes ? (int32_t)std::max<int64_t>(1, window_bytes / kLdsRowBytes) : 0, false};
+    const LdsArgs lds = lds_args(a.N, windows, window_bytes, window_asked, xcds, compute_units, cap, false);
     launch_panel_preparation(a, scr, windows, window_rows, min_len, true, owners, xcds, compute_units, lds, s);
     if (!owners && lds.min_rows != 0xffffffffu)
-        hipLaunchKernelGGL(panel_lds_kernel, dim3(lds_workgroups * (uint32_t)xcds), dim3(kLdsBlock), 0, s, a.colidx, a.vals, a.B,
+        hipLaunchKernelGGL(panel_lds_kernel, dim3(lds.workgroups * lds.dies), dim3(kLdsBlock), 0, s, a.colidx, a.vals, a.B,
                            a.C, scr, a.K, a.N, lds);
     uint32_t below = 0xffffffffu;
     if (owners) {
@@ -1088,7 +1100,7 @@ void launch_sddmm_long_rows(const SpmmArgs& a, const float* X1, float* out, cons
 // sddmm_panels_workspace_bytes(K, J, window_bytes, cap) bytes.
 hipError_t launch_sddmm_panels(const SpmmArgs& a, const float* X1, float* out, int g, int per_lane, int xcds,
                                int compute_units, int64_t nnz_hint, int32_t min_len, int64_t window_bytes,
-                               void* workspace, int64_t cap, hipStream_t s)
+                               bool window_asked, void* workspace, int64_t cap, hipStream_t s)
 {
     if (a.N % 4 != 0 || a.N < 32 || a.N > 256 || min_len < 1 || xcds < 1 || !workspace || cap < 1)
         return hipErrorInvalidValue;
@@ -1100,13 +1112,11 @@ hipError_t launch_sddmm_panels(const SpmmArgs& a, const float* X1, float* out, i
     int wave_lc = 8;
     while (wave_lc < kWave && (int64_t)wave_lc * 4 < a.N) wave_lc *= 2;
     const bool owners = wave_lc == kWave;
-    const uint32_t lds_workgroups = (uint32_t)(compute_units / xcds > 0 ? compute_units / xcds : 1);
-    const LdsArgs lds{a.N >= kLdsMinCols ? kLdsMinRows : 0xffffffffu, (uint32_t)xcds, lds_workgroups, cap * (windows + 1),
-                      window_bytes <= kDotsWindow * kLdsRowBytes ? (int32_t)std::max<int64_t>(1, window_bytes / kLdsRowBytes) : 0, true};
+    const LdsArgs lds = lds_args(a.N, windows, window_bytes, window_asked, xcds, compute_units, cap, true);
     launch_panel_preparation(a, scr, windows, window_rows, min_len, false, owners, owners ? xcds : 1, compute_units, lds, s);
     uint32_t below = 0xffffffffu;
     if (lds.min_rows != 0xffffffffu)
-        hipLaunchKernelGGL(panel_lds_dots_kernel, dim3(lds_workgroups * (uint32_t)xcds), dim3(kLdsBlock), 0, s, a.colidx, a.vals, X1,
+        hipLaunchKernelGGL(panel_lds_dots_kernel, dim3(lds.workgroups * lds.dies), dim3(kLdsBlock), 0, s, a.colidx, a.vals, X1,
                            a.B, out, scr, a.K, a.N, lds);
     if (owners) {
         below = owner_min_rows(xcds, compute_units);

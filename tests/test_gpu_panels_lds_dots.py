@@ -108,6 +108,12 @@ def test_floats_where_the_rule_takes_it():
     check(problem(300, 26000, 128, 3000, seed=9, integer=False), 500, "floats", exact=False, window_kb=0)
 
 
+def test_the_size_of_the_windows_chooses_between_lds_and_the_l2():
+    p = problem(300, 26000, 128, 3000, seed=11)
+    for window_kb, runs in ((0, 1), (149, 1), (150, 0), (2048, 0)):
+        check(p, 500, f"{window_kb} KiB", window_kb=window_kb, runs=runs)
+
+
 def test_rows_too_thin_for_it():
     check(problem(700, 20000, 256, 200, seed=10), 40, "thin", window_kb=0, runs=0)
 
