@@ -240,9 +240,10 @@ int sgap_spmm_csr_gr(int64_t M, int64_t K, int64_t N,
  *                   the L2s.  Needs a workspace (below).  0 = off.
  *   window_kb       KiB of B per column window (at most 511 windows are made);
  *                   automatic: 3072, except that lists of at least 256 long
- *                   rows that hold a fair share of the columns are multiplied
- *                   out of windows in LDS, from 64 columns of B on, where the
- *                   library expects that to be the faster.  At most 154: windows
+ *                   rows that hold a fair share of the columns, in ascending
+ *                   order and spread over them, are multiplied out of windows in
+ *                   LDS, from 64 columns of B on, where the library expects that
+ *                   to be the faster (some places of every long row tell).  At most 154: windows
  *                   in LDS (of that size for 64 columns of B) wherever they
  *                   apply; more: never.
  *   max_long_rows   capacity of the list of long rows, at most 1,048,576;

@@ -24,7 +24,9 @@ struct PanelHeader {
     unsigned long long entries;  // stored entries of the rows found
     uint32_t nnz;                // of the matrix
     LdsPlan lds;
-    uint32_t pad[37];
+    uint32_t worst;            // the most of any row of those of:
+    unsigned long long apart;  // entries of the rows found that windows in LDS would not serve, estimated
+    uint32_t pad[34];
 };
 struct PanelView {
     PanelHeader* head;

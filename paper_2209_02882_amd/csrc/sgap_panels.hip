@@ -70,8 +70,9 @@ __global__ void panel_reset_kernel(PanelView scr)
 {
     if (blockIdx.x == 0 && threadIdx.x < 16) (&scr.head->count)[threadIdx.x] = 0;  // count and next[]
     if (blockIdx.x == 0 && threadIdx.x == 0) {
-        scr.head->entries = 0;
+        scr.head->entries = scr.head->apart = 0;
         scr.head->lds.on = 0;
+        scr.head->worst = 0;
     }
 }
 
@@ -79,22 +80,27 @@ __global__ void panel_reset_kernel(PanelView scr)
 // address takes about 0.1 us (they are carried out one after another, beyond the dies' L2s), and a matrix may have
 // thousands of long rows (skewed, 5,000 of them: 44 us with one update per wavefront that found a row).
 constexpr int kFindRows = 8;
-__global__ __launch_bounds__(kBlock) void panel_find_rows_kernel(SpmmArgs a, PanelView scr, int32_t min_len)
+// places: windows in LDS may come into question, which some places of every long row have a say in: a thread looks at one row
+// (by those who found them, some had two rows to look at and the kernel took 8.8 us instead of 7.4; without places 5.2),
+// the last wavefront asks for room in the list meanwhile.
+__global__ __launch_bounds__(kBlock) void panel_find_rows_kernel(SpmmArgs a, PanelView scr, int32_t min_len, bool places)
 {
     __shared__ uint32_t s_wave[kWavesPerBlock];
     __shared__ unsigned long long s_entries[kWavesPerBlock];
     __shared__ uint32_t s_base;
+    __shared__ int2 s_long[kBlock * kFindRows];  // first entry, entries
     const int lane = threadIdx.x % kWave;
     const int wave = threadIdx.x / kWave;
     const int64_t row0 = (int64_t)blockIdx.x * (kBlock * kFindRows) + threadIdx.x;
     if (row0 == 0) scr.head->nnz = (uint32_t)a.rowptr[a.M];
     uint32_t mine = 0;  // bit j: row row0 + j * kBlock is long
-    int32_t len[kFindRows];
+    int32_t begin[kFindRows], len[kFindRows];
     unsigned long long entries = 0;
 #pragma unroll
     for (int j = 0; j < kFindRows; ++j) {
         const int64_t row = row0 + (int64_t)j * kBlock;
-        len[j] = row < a.M ? a.rowptr[row + 1] - a.rowptr[row] : 0;
+        begin[j] = row < a.M ? a.rowptr[row] : 0;
+        len[j] = row < a.M ? a.rowptr[row + 1] - begin[j] : 0;
         if (row < a.M && len[j] >= min_len) {
             mine |= 1u << j;
             entries += (unsigned long long)len[j];
@@ -113,22 +119,44 @@ __global__ __launch_bounds__(kBlock) void panel_find_rows_kernel(SpmmArgs a, Pan
         s_entries[wave] = entries;
     }
     __syncthreads();
-    if (threadIdx.x == 0) {
-        uint32_t total = 0;
-        for (int w = 0; w < kWavesPerBlock; ++w) {
-            const uint32_t c = s_wave[w];
-            s_wave[w] = total;
-            total += c;
-            entries += w > 0 ? s_entries[w] : 0ull;
-        }
-        s_base = 0;
-        if (total) {
-            s_base = atomicAdd(&scr.head->count, total);
-            atomicAdd(&scr.head->entries, entries);
+    uint32_t at = incl - cnt, total = 0;  // this thread's first long row among the workgroup's
+#pragma unroll
+    for (int w = 0; w < kWavesPerBlock; ++w) {
+        at += w < wave ? s_wave[w] : 0u;
+        total += s_wave[w];
+    }
+    if (total == 0) return;
+    if (places) {
+        uint32_t i = at;
+#pragma unroll
+        for (int j = 0; j < kFindRows; ++j)
+            if (mine & (1u << j)) s_long[i++] = make_int2(begin[j], len[j]);
+        __syncthreads();
+    }
+    if (threadIdx.x == kBlock - 1) {
+        for (int w = 0; w < kWavesPerBlock - 1; ++w) entries += s_entries[w];
+        s_base = atomicAdd(&scr.head->count, total);
+        atomicAdd(&scr.head->entries, entries);
+    }
+    if (places) {
+        unsigned long long apart = 0;
+        uint32_t worst = 0;
+        for (uint32_t i = threadIdx.x; i < total; i += kBlock) apart += lds_apart(a.colidx + s_long[i].x, s_long[i].y, a.K, worst);
+        if (__any(apart != 0)) {
+#pragma unroll
+            for (int d = 1; d < kWave; d *= 2) {
+                apart += __shfl_xor(apart, d, kWave);
+                const uint32_t other = (uint32_t)__shfl_xor((int)worst, d, kWave);
+                worst = worst < other ? other : worst;
+            }
+            if (lane == 0) {
+                atomicAdd(&scr.head->apart, apart);
+                if (worst) atomicMax(&scr.head->worst, worst);
+            }
         }
     }
     __syncthreads();
-    uint32_t i = s_base + s_wave[wave] + incl - cnt;
+    uint32_t i = s_base + at;
 #pragma unroll
     for (int j = 0; j < kFindRows; ++j) {
         if (!(mine & (1u << j))) continue;
@@ -683,7 +711,7 @@ void launch_panel_preparation(const SpmmArgs& a, const PanelView& scr, int windo
     hipLaunchKernelGGL(panel_reset_kernel, dim3(1), dim3(kWave), 0, s, scr);
     constexpr int64_t rows_per_block = (int64_t)kBlock * kFindRows;
     hipLaunchKernelGGL(panel_find_rows_kernel, dim3((unsigned)((a.M + rows_per_block - 1) / rows_per_block)), dim3(kBlock),
-                       0, s, a, scr, min_len);
+                       0, s, a, scr, min_len, lds.min_rows != 0xffffffffu && lds.window == 0);
     // (the search is bound by the lines that its probes fetch: 325,000 and 85,000 pointers take 47 and 26 us with four
     // workgroups per compute unit, 44 and 26 with five, 42 and 28 with six, 56 and 33 with eight)
     const uint32_t pointer_blocks = (uint32_t)compute_units * 5;

@@ -45,6 +45,34 @@ constexpr int kLdsMinCols = 64;                    // columns of B from which on
 constexpr int kLdsNoLoads = 0x0F70;                // s_waitcnt vmcnt(0)
 static_assert(kLdsSlots <= 2 * kLdsTeam, "positions of the slots lie in two registers of a team");
 
+// Entries of a long row that windows in LDS would not serve, estimated from sixteen places of it: those that the window of
+// a slot has no room for, and all where the columns have no order.  The kernels gather them from memory, a few at a time.
+// (A window as the row by itself would have it: 16 entries wide in the mean.)  worst: raised to the row's, in entries
+// without order: crowded ones wait a sixteenth as long, and one place alone is crowded now and then where columns are random.
+__device__ __forceinline__ uint32_t lds_apart(const int32_t* __restrict__ cols, int32_t len, int64_t K, uint32_t& worst)
+{
+    constexpr int kPlaces = 16, kRoom = 2 * kLdsTeam;
+    const int32_t width = (int32_t)fminf((float)kLdsWindow, 16.0f * (float)K / (float)len);
+    int32_t here[kPlaces], there[kPlaces];
+#pragma unroll
+    for (int j = 0; j < kPlaces; ++j) {
+        const int32_t at = len / kPlaces * j;
+        here[j] = cols[at];
+        there[j] = cols[at + kRoom < len ? at + kRoom : len - 1];
+    }
+    uint32_t crowded = 0;
+    bool order = true;
+#pragma unroll
+    for (int j = 0; j < kPlaces; ++j) {
+        order = order && there[j] >= here[j] && (j == 0 || here[j] >= here[j - 1]);
+        crowded += len / kPlaces * j + kRoom < len && there[j] - here[j] < width ? 1u : 0u;
+    }
+    const uint32_t apart = order ? (uint32_t)((unsigned long long)len * crowded / kPlaces) : (uint32_t)len;
+    const uint32_t alone = order ? (crowded > 1 ? apart / 16 : 0u) : apart;
+    worst = worst < alone ? alone : worst;
+    return apart;
+}
+
 // What the host knows of it.
 struct LdsArgs {
     uint32_t min_rows;    // the kernel runs for lists of at least so many rows
@@ -130,7 +158,23 @@ __device__ __forceinline__ LdsPlan lds_plan(const PanelHeader* head, const LdsAr
     } else {
         gather = gather / 29.0f * fmaxf(1.0f, 1200.0f / (float)n);
     }
-    const bool faster = args.window > 0 || __uint_as_float((uint32_t)(best >> 32)) < gather;
+    // What windows would not serve.  A few rows of it cost four times what their share of all entries would (the other teams
+    // and wavefronts wait), and all wait for the team whose row has the most.  500,000 rows, 5,000 of them long, us, LDS
+    // against gathers (which are what the rule then takes, but for 0.02 %):
+    //   without order, share of the long rows   0.02 %        0.1 %           1 %             all
+    //     SpMM  N = 64                          765 / 1,050   3,260 / 1,224   6,843 / 1,392   19,578 /  2,730
+    //           N = 256                       1,642 / 2,536   4,181 / 3,176   8,234 / 3,764   48,440 / 16,519
+    //     SDDMM J = 64                          709 / 1,030   2,763 / 1,251   6,096 / 1,476   17,415 /  2,768
+    //           J = 256                       1,922 / 2,729   7,369 / 3,498  16,017 / 4,239   49,890 / 16,758
+    //   a quarter full over a run of columns    0.1 %         1 %             all
+    //     SpMM  N = 64                          981 / 1,052   1,238 / 1,079   5,620 / 1,119
+    //           N = 256                       2,666 / 3,156   3,566 / 3,499  16,398 / 5,562
+    //     SDDMM J = 64                          951 / 1,041   1,190 / 1,083   4,448 / 1,253
+    //           J = 256                       2,586 / 3,526   3,287 / 3,923  10,879 / 6,013
+    const float apart = fmaxf((float)head->apart / (float)(dies * args.workgroups) *
+                                  (args.dots ? 280.0f + 460.0f * (float)p.tiles : 440.0f + 410.0f * (float)p.tiles),
+                              (float)head->worst * (args.dots ? 200.0f + 200.0f * (float)p.tiles : 600.0f));
+    const bool faster = args.window > 0 || __uint_as_float((uint32_t)(best >> 32)) + apart < gather;
     p.on = best != ~0ull && faster && head->nnz < kLdsMaxNnz && K <= (1 << 24) && N < (1 << 30);
     return p;
 }

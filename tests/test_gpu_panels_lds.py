@@ -96,6 +96,35 @@ def test_the_size_of_the_windows_chooses_between_lds_and_the_l2():
         check(p, 500, f"{window_kb} KiB", window_kb=window_kb, runs=runs)
 
 
+def without_order(p, rows):
+    """p with the entries of these rows in any order."""
+    rng = np.random.default_rng(1)
+    for i in rows:
+        a, b = p.rowptr[i], p.rowptr[i + 1]
+        perm = rng.permutation(b - a)
+        p.colidx[a:b], p.vals[a:b] = p.colidx[a:b][perm], p.vals[a:b][perm]
+    return p
+
+
+def crowded(p, rows):
+    """p with the entries of these rows side by side, somewhere."""
+    rng = np.random.default_rng(1)
+    for i in rows:
+        a, b = p.rowptr[i], p.rowptr[i + 1]
+        p.colidx[a:b] = rng.integers(p.K - (b - a) + 1) + np.arange(b - a)
+    return p
+
+
+# the windows in LDS serve rows whose columns ascend and lie apart; the others, and lists with some of them, are gathered
+@pytest.mark.parametrize("shape", [without_order, crowded])
+def test_rows_that_windows_in_lds_would_not_serve(shape):
+    n_long, args = 1300, (1300, 9000, 128, 6000)
+    long = np.flatnonzero(np.diff(problem(*args, seed=12).rowptr) > 500)
+    assert long.size == n_long
+    for rows, runs in ((long, 0), (long[::20], 0), (long[:0], 1)):
+        check(shape(problem(*args, seed=12), rows), 500, f"{rows.size} rows", window_kb=0, runs=runs)
+
+
 def test_rows_too_thin_for_it():
     check(problem(700, 20000, 64, 200, seed=10), 40, "thin", window_kb=0, runs=0)
 

@@ -10,7 +10,7 @@ from paper_2209_02882_amd import binding
 from paper_2209_02882_amd import workloads as wl
 
 from gpu_util import TOL, DeviceProblem
-from test_gpu_panels_lds import LDS_RUNS, problem
+from test_gpu_panels_lds import LDS_RUNS, crowded, problem, without_order
 
 pytestmark = pytest.mark.gpu
 
@@ -112,6 +112,15 @@ def test_the_size_of_the_windows_chooses_between_lds_and_the_l2():
     p = problem(300, 26000, 128, 3000, seed=11)
     for window_kb, runs in ((0, 1), (149, 1), (150, 0), (2048, 0)):
         check(p, 500, f"{window_kb} KiB", window_kb=window_kb, runs=runs)
+
+
+@pytest.mark.parametrize("shape", [without_order, crowded])
+def test_rows_that_windows_in_lds_would_not_serve(shape):
+    args = (300, 26000, 128, 3000)
+    long = np.flatnonzero(np.diff(problem(*args, seed=12).rowptr) > 500)
+    assert long.size == 300
+    for rows, runs in ((long, 0), (long[::20], 0), (long[:0], 1)):
+        check(shape(problem(*args, seed=12), rows), 500, f"{rows.size} rows", window_kb=0, runs=runs)
 
 
 def test_rows_too_thin_for_it():
