@@ -75,6 +75,16 @@ int sgap_debug_group_seg_reduce(const float* in, const int32_t* span, float* out
  *   sgap_debug_finder_rows: the rows of M that team number `team` of `teams`
  *     looks through.  Writes up to `capacity` of them into out_rows
  *     (host) and returns how many there are, or -1 on bad arguments.
+ *   sgap_debug_plan_windows: the form that long rows by column windows take
+ *     (SpMM, or SDDMM with N for J) for a list of `rows` rows that hold
+ *     `entries` of nnz stored entries, the longest `longest`; apart of them,
+ *     at most worst of one row, are what windows in LDS would not serve.
+ *     window_kb and max_long_rows as in sgap_config.  *in_lds 1: windows in LDS
+ *     of `window` columns, the rows in `groups` groups, `shares` shares of the
+ *     columns per die; 0: gathers (then those are 0).  The clocks that the
+ *     library expects of both (0: the one in LDS does not come into question).
+ *     The device decides by the same functions; 32-bit word 19 of the
+ *     workspace says what it decided.
  */
 int64_t sgap_debug_tile_deal(int64_t tiles, int grid, int block, int64_t* out_tiles, int64_t capacity);
 int sgap_debug_plan_nnz_serial(int group_size, int lanes_per_row, int cols_per_lane, int64_t nnz_hint,
@@ -84,6 +94,10 @@ int sgap_debug_plan_row_split(int lanes_per_row, int passes, int64_t M, int64_t 
                               int64_t nnz_hint, int resident, int64_t* share_from, int64_t* finders,
                               int64_t* team, int64_t* walk_from, int64_t* grid);
 int64_t sgap_debug_finder_rows(int64_t M, int teams, int team, int64_t* out_rows, int64_t capacity);
+int sgap_debug_plan_windows(int sddmm, int64_t K, int64_t N, int64_t rows, int64_t entries, int64_t longest,
+                            int64_t nnz, int64_t apart, int64_t worst, int window_kb, int max_long_rows,
+                            int compute_units, int* in_lds, int* groups, int* shares, int* window,
+                            double* lds_clocks, double* gather_clocks);
 
 /*
  * Streaming kernels over n fp32 elements (16-byte aligned device buffers):

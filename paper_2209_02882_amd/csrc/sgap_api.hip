@@ -2,6 +2,7 @@
 // launches on the caller's stream.  See include/sgap.h for the contract.
 #include "../../include/sgap.h"
 #include "../../include/sgap_debug.h"
+#include "sgap_panel_view.hpp"
 
 #include <cstdio>
 #include <cstring>
@@ -250,6 +251,7 @@ constexpr int64_t kMaxEntries = 2147483647LL - 65535;  // 32-bit positions with 
 constexpr int kSmallGrid = 4;       // workgroups per compute unit below which row-split parallel stacks no rows on a group
 constexpr int kAutoTileCols = 128;  // 512 bytes of a B row per work item
 constexpr int kAutoWindowKb = 3072;   // KiB of B per column window of the long-rows path: most of a die's 4 MiB L2
+constexpr int kSddmmWindowKb = 2048;  // the same for SDDMM
 constexpr int kAutoLongRows = 8192;   // capacity of the list of long rows when the caller names none
 constexpr int kMaxLongRows = 1 << 20;
 
@@ -711,7 +713,7 @@ static int sddmm_impl(int64_t M, int64_t K, int64_t J, const int32_t* rowptr, co
     const bool par = strategy == SGAP_REDUCE_PARALLEL;
     hipError_t err;
     if (long_row_min > 0 && aligned_vec(J, X1, X2T) == 4 && J >= 32 && J <= 256 && K > 0) {
-        const int64_t window_bytes = (int64_t)(window_kb > 0 ? window_kb : 2048) * 1024;
+        const int64_t window_bytes = (int64_t)(window_kb > 0 ? window_kb : kSddmmWindowKb) * 1024;
         const int64_t cap = max_long_rows > 0 ? max_long_rows : kAutoLongRows;
         if (!workspace || workspace_bytes < sddmm_panels_workspace_bytes(K, J, window_bytes, cap) ||
             (reinterpret_cast<uintptr_t>(workspace) & 255)) {
@@ -757,7 +759,7 @@ int64_t sgap_sddmm_csr_workspace_size(int64_t K, int64_t J, int window_kb, int m
         return -1;
     }
     if (K == 0 || J % 4 != 0 || J < 32 || J > 256) return 0;  // the window path does not apply
-    return sgap::sddmm_panels_workspace_bytes(K, J, (int64_t)(window_kb > 0 ? window_kb : 2048) * 1024,
+    return sgap::sddmm_panels_workspace_bytes(K, J, (int64_t)(window_kb > 0 ? window_kb : kSddmmWindowKb) * 1024,
                                               max_long_rows > 0 ? max_long_rows : kAutoLongRows);
 }
 
@@ -1007,6 +1009,29 @@ int sgap_debug_plan_row_split(int lanes_per_row, int passes, int64_t M, int64_t 
     *team = 1LL << p.log2_team;
     *walk_from = p.walk_from;
     *grid = p.grid;
+    return SGAP_OK;
+}
+
+int sgap_debug_plan_windows(int sddmm, int64_t K, int64_t N, int64_t rows, int64_t entries, int64_t longest, int64_t nnz,
+                            int64_t apart, int64_t worst, int window_kb, int max_long_rows, int compute_units_, int* in_lds,
+                            int* groups, int* shares, int* window, double* lds_clocks, double* gather_clocks)
+{
+    if (K < 1 || K > 2147483647LL || N < 4 || N % 4 != 0 || N > 2147483647LL || rows < 1 || rows > kMaxLongRows || longest < 1 ||
+        entries < longest || nnz < entries || nnz > kMaxEntries || apart < 0 || worst < 0 || worst > longest || window_kb < 0 ||
+        window_kb > (1 << 20) || max_long_rows < 0 || max_long_rows > kMaxLongRows || compute_units_ < 1 || !in_lds || !groups ||
+        !shares || !window || !lds_clocks || !gather_clocks)
+        return fail(SGAP_ERR_INVALID_ARG, "bad plan arguments");
+    const sgap::LdsList list{(uint32_t)rows, (uint32_t)longest, (uint32_t)nnz, (uint32_t)worst, (unsigned long long)entries,
+                             (unsigned long long)apart};
+    const int64_t bytes = (int64_t)(window_kb > 0 ? window_kb : sddmm ? kSddmmWindowKb : kAutoWindowKb) * 1024;
+    const sgap::PanelForm form = sgap::plan_panel_form(sddmm != 0, K, N, list, bytes, window_kb > 0,
+                                                       max_long_rows > 0 ? max_long_rows : kAutoLongRows, kXcds, compute_units_);
+    *in_lds = form.lds.on ? 1 : 0;
+    *groups = form.lds.on ? (int)form.lds.groups : 0;
+    *shares = form.lds.on ? (int)form.lds.per_die : 0;
+    *window = form.lds.on ? form.lds.window : 0;
+    *lds_clocks = form.lds_clocks;
+    *gather_clocks = form.gather_clocks;
     return SGAP_OK;
 }
 

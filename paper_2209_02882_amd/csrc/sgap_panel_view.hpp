@@ -13,7 +13,7 @@ struct LdsPlan {
     uint32_t groups, slots;     // groups of rows, rows of a team
     uint32_t per_die;           // shares of the columns that a die takes
     int32_t share_cols;         // columns of a share
-    int32_t window;             // columns of a window at most
+    int32_t window;             // columns of a window
 };
 
 // The workspace: a header, the list of long rows, the same list sorted by length, the rows' lengths, and the
@@ -26,7 +26,8 @@ struct PanelHeader {
     LdsPlan lds;
     uint32_t worst;            // the most of any row of those of:
     unsigned long long apart;  // entries of the rows found that windows in LDS would not serve, estimated
-    uint32_t pad[34];
+    uint32_t longest;          // entries of the longest of the rows found
+    uint32_t pad[33];
 };
 struct PanelView {
     PanelHeader* head;
@@ -37,5 +38,19 @@ struct PanelView {
     uint32_t cap;    // rows the list holds
 };
 static_assert(sizeof(PanelHeader) == 256, "the workspace's size is part of the interface");
+
+// What the list of long rows is like.
+struct LdsList {
+    uint32_t count, longest, nnz, worst;  // nnz: of the matrix
+    unsigned long long entries, apart;
+};
+
+// The choice between windows in LDS and gathers, worked out on the host (the device makes it by the same functions).
+struct PanelForm {
+    LdsPlan lds;
+    float lds_clocks, gather_clocks;
+};
+PanelForm plan_panel_form(bool dots, int64_t K, int64_t N, const LdsList& list, int64_t window_bytes, bool window_asked,
+                          int64_t cap, int xcds, int compute_units);
 
 }  // namespace sgap

@@ -28,6 +28,8 @@
 // panel_workspace_bytes for a list of `cap` rows).  When the matrix has more long
 // rows than the list holds, this path does nothing and the row-split kernel
 // takes every row.
+#include <algorithm>
+
 #include "sgap_common.hpp"
 #include "sgap_dot8.hpp"
 #include "sgap_lane_ops.hpp"
@@ -72,38 +74,43 @@ __global__ void panel_reset_kernel(PanelView scr)
     if (blockIdx.x == 0 && threadIdx.x == 0) {
         scr.head->entries = scr.head->apart = 0;
         scr.head->lds.on = 0;
-        scr.head->worst = 0;
+        scr.head->worst = scr.head->longest = 0;
     }
 }
 
-// A workgroup looks at kFindRows rows per thread and adds to the list's counter once: a returning atomic on one
+// A workgroup looks at up to kFindRows rows per thread and adds to the list's counter once: a returning atomic on one
 // address takes about 0.1 us (they are carried out one after another, beyond the dies' L2s), and a matrix may have
 // thousands of long rows (skewed, 5,000 of them: 44 us with one update per wavefront that found a row).
 constexpr int kFindRows = 8;
 // places: windows in LDS may come into question, which some places of every long row have a say in: a thread looks at one row
-// (by those who found them, some had two rows to look at and the kernel took 8.8 us instead of 7.4; without places 5.2),
+// (by those who found them, some had two rows to look at: 60,000 rows, 600 of them long, 8.8 us instead of 7.4, without
+// places 5.2; 500,000 rows 13.4, without 8.2),
 // the last wavefront asks for room in the list meanwhile.
-__global__ __launch_bounds__(kBlock) void panel_find_rows_kernel(SpmmArgs a, PanelView scr, int32_t min_len, bool places)
+// each: rows per thread.
+__global__ __launch_bounds__(kBlock) void panel_find_rows_kernel(SpmmArgs a, PanelView scr, int32_t min_len, int each, bool places)
 {
-    __shared__ uint32_t s_wave[kWavesPerBlock];
+    __shared__ uint32_t s_wave[kWavesPerBlock], s_longest[kWavesPerBlock];
     __shared__ unsigned long long s_entries[kWavesPerBlock];
     __shared__ uint32_t s_base;
     __shared__ int2 s_long[kBlock * kFindRows];  // first entry, entries
     const int lane = threadIdx.x % kWave;
     const int wave = threadIdx.x / kWave;
-    const int64_t row0 = (int64_t)blockIdx.x * (kBlock * kFindRows) + threadIdx.x;
+    const int64_t row0 = (int64_t)blockIdx.x * (kBlock * each) + threadIdx.x;
+    const int64_t rows = row0 + (int64_t)each * kBlock < a.M ? row0 + (int64_t)each * kBlock : a.M;
     if (row0 == 0) scr.head->nnz = (uint32_t)a.rowptr[a.M];
     uint32_t mine = 0;  // bit j: row row0 + j * kBlock is long
     int32_t begin[kFindRows], len[kFindRows];
     unsigned long long entries = 0;
+    uint32_t longest = 0;
 #pragma unroll
     for (int j = 0; j < kFindRows; ++j) {
         const int64_t row = row0 + (int64_t)j * kBlock;
-        begin[j] = row < a.M ? a.rowptr[row] : 0;
-        len[j] = row < a.M ? a.rowptr[row + 1] - begin[j] : 0;
-        if (row < a.M && len[j] >= min_len) {
+        begin[j] = row < rows ? a.rowptr[row] : 0;
+        len[j] = row < rows ? a.rowptr[row + 1] - begin[j] : 0;
+        if (row < rows && len[j] >= min_len) {
             mine |= 1u << j;
             entries += (unsigned long long)len[j];
+            longest = (uint32_t)len[j] > longest ? (uint32_t)len[j] : longest;
         }
     }
     const uint32_t cnt = (uint32_t)__popc(mine);
@@ -113,9 +120,12 @@ __global__ __launch_bounds__(kBlock) void panel_find_rows_kernel(SpmmArgs a, Pan
         const uint32_t t = (uint32_t)__shfl_up((int)incl, d, kWave);
         if (lane >= d) incl += t;
         entries += __shfl_xor(entries, d, kWave);
+        const uint32_t other = (uint32_t)__shfl_xor((int)longest, d, kWave);
+        longest = longest < other ? other : longest;
     }
     if (lane == kWave - 1) {
         s_wave[wave] = incl;
+        s_longest[wave] = longest;
         s_entries[wave] = entries;
     }
     __syncthreads();
@@ -134,14 +144,23 @@ __global__ __launch_bounds__(kBlock) void panel_find_rows_kernel(SpmmArgs a, Pan
         __syncthreads();
     }
     if (threadIdx.x == kBlock - 1) {
-        for (int w = 0; w < kWavesPerBlock - 1; ++w) entries += s_entries[w];
+        for (int w = 0; w < kWavesPerBlock - 1; ++w) {
+            entries += s_entries[w];
+            longest = longest < s_longest[w] ? s_longest[w] : longest;
+        }
         s_base = atomicAdd(&scr.head->count, total);
         atomicAdd(&scr.head->entries, entries);
+        atomicMax(&scr.head->longest, longest);
     }
     if (places) {
         unsigned long long apart = 0;
         uint32_t worst = 0;
-        for (uint32_t i = threadIdx.x; i < total; i += kBlock) apart += lds_apart(a.colidx + s_long[i].x, s_long[i].y, a.K, worst);
+        // (where nearly all rows are long, as many as there are threads, spread over them)
+        const uint32_t looked = total < (uint32_t)kBlock ? total : (uint32_t)kBlock;
+        if (threadIdx.x < looked) {
+            const int2 row = s_long[threadIdx.x * total / looked];
+            apart = (unsigned long long)lds_apart(a.colidx + row.x, row.y, a.K, worst) * total / looked;
+        }
         if (__any(apart != 0)) {
 #pragma unroll
             for (int d = 1; d < kWave; d *= 2) {
@@ -183,7 +202,8 @@ __device__ __forceinline__ void panel_pointers_body(const SpmmArgs& a, const Pan
 {
     const uint32_t n = scr.head->count;
     if (n == 0 || n > scr.cap) return;
-    const LdsPlan plan = lds_plan(scr.head, lds, a.K, a.N);
+    const LdsList list{n, scr.head->longest, scr.head->nnz, scr.head->worst, scr.head->entries, scr.head->apart};
+    const LdsPlan plan = lds_plan(list, lds, a.K, a.N);
     if (block == 0 && threadIdx.x == 0) scr.head->lds = plan;
     if (plan.on) {  // panel_lds_kernel's shares are pieces of its own
         windows = (int)(plan.per_die * lds.dies);
@@ -693,6 +713,7 @@ LdsArgs lds_args(int64_t N, int windows, int64_t window_bytes, bool asked, int x
     lds.dies = (uint32_t)xcds;
     lds.workgroups = (uint32_t)(compute_units / xcds > 0 ? compute_units / xcds : 1);
     lds.ptr_room = cap * (windows + 1);
+    lds.gather_windows = (uint32_t)windows;
     lds.window = asked && fit ? (int32_t)(rows > 0 ? rows : 1) : 0;
     lds.dots = dots;
     return lds;
@@ -709,9 +730,12 @@ void launch_panel_preparation(const SpmmArgs& a, const PanelView& scr, int windo
     const bool rank_rows = owners || lds.min_rows != 0xffffffffu;
     const uint32_t few_from = owners ? owner_min_rows(xcds, compute_units) : 0xffffffffu;
     hipLaunchKernelGGL(panel_reset_kernel, dim3(1), dim3(kWave), 0, s, scr);
-    constexpr int64_t rows_per_block = (int64_t)kBlock * kFindRows;
+    // workgroups enough that the places of the long rows are looked at side by side, few enough for the list's counter (15,000
+    // rows, 3,000 of them long: 8 workgroups 23.8 us, 59 5.2)
+    const int64_t each = std::min<int64_t>(kFindRows, (a.M + 64 * kBlock - 1) / (64 * kBlock));
+    const int64_t rows_per_block = kBlock * each;
     hipLaunchKernelGGL(panel_find_rows_kernel, dim3((unsigned)((a.M + rows_per_block - 1) / rows_per_block)), dim3(kBlock),
-                       0, s, a, scr, min_len, lds.min_rows != 0xffffffffu && lds.window == 0);
+                       0, s, a, scr, min_len, (int)each, lds.min_rows != 0xffffffffu && lds.window == 0);
     // (the search is bound by the lines that its probes fetch: 325,000 and 85,000 pointers take 47 and 26 us with four
     // workgroups per compute unit, 44 and 26 with five, 42 and 28 with six, 56 and 33 with eight)
     const uint32_t pointer_blocks = (uint32_t)compute_units * 5;
@@ -752,6 +776,37 @@ int64_t sddmm_panels_workspace_bytes(int64_t K, int64_t J, int64_t window_bytes,
     int32_t window_rows = 1;
     plan_panels(K, J > 0 ? J : 1, window_bytes, &windows, &window_rows);
     return panel_workspace_bytes(cap, windows);
+}
+
+PanelForm plan_panel_form(bool dots, int64_t K, int64_t N, const LdsList& list, int64_t window_bytes, bool window_asked,
+                          int64_t cap, int xcds, int compute_units)
+{
+    int wave_lc = 1, windows = 1;
+    int64_t window_cols = N;
+    int32_t window_rows = 1;
+    if (!dots) spmm_panel_layout(N, &wave_lc, &window_cols);
+    plan_panels(K, window_cols, window_bytes, &windows, &window_rows);
+    const LdsArgs args = lds_args(N, windows, window_bytes, window_asked, xcds, compute_units, cap, dots);
+    PanelForm form;
+    form.lds.on = 0;
+    form.lds_clocks = form.gather_clocks = 0.0f;
+    if (list.count < args.min_rows) return form;
+    const LdsShape s = lds_shape(list, args, K, N);
+    uint32_t groups = s.least, per_die = 1;
+    float best = lds_cost(s, list, args, K, N, groups, per_die);
+    for (uint32_t g = s.least; g < s.least + kLdsMore; ++g)
+        for (uint32_t shares = 1; shares <= kLdsShares; ++shares) {
+            const float cost = lds_cost(s, list, args, K, N, g, shares);
+            if (cost < best) {
+                best = cost;
+                groups = g;
+                per_die = shares;
+            }
+        }
+    form.lds = lds_layout(s, list, args, K, N, groups, per_die, best);
+    form.lds_clocks = best + lds_apart_cost(s, list, args);
+    form.gather_clocks = gather_cost(list, args, N);
+    return form;
 }
 
 // Long rows (at least min_len entries) window by window, all other rows by the

@@ -38,6 +38,7 @@ constexpr int kLdsTeams = kWave / kLdsTeam;        // teams of a wavefront
 constexpr int kLdsCols = kLdsTeam * 4;             // columns of a job
 constexpr int kLdsSlots = 20;                      // rows a team owns
 constexpr int kLdsWindow = 616;                    // rows of B in LDS (and one of zeros): 157,952 of 163,840 bytes
+constexpr int kDotsWindow = 596;                   // of X2T, for SDDMM: the rows' numbers lie in LDS too
 constexpr int kLdsRowBytes = kLdsCols * 4;
 constexpr uint32_t kLdsMaxNnz = 1u << 29;          // byte offsets of entries have 31 bits
 constexpr uint32_t kLdsMinRows = 256;
@@ -79,47 +80,171 @@ struct LdsArgs {
     uint32_t dies;
     uint32_t workgroups;  // of a die
     int64_t ptr_room;     // pointers there is room for
+    uint32_t gather_windows;  // that the kernels which gather would have
     int32_t window;       // columns of a window at most, as the caller asks for them (the kernel runs then); 0: he does not
     bool dots;            // SDDMM: a job has all columns of its rows
 };
 
-// How the list's rows are laid over the workgroups.  Their number is not known on the host: the workgroups of
-// panel_pointers_kernel each work it out (all lanes of a wavefront together), one leaves it in the header.
-__device__ __forceinline__ LdsPlan lds_plan(const PanelHeader* head, const LdsArgs& args, int64_t K, int64_t N)
+// What all layouts of a list have in common.
+struct LdsShape {
+    uint32_t tiles, quads, least;  // column tiles; teams' rows by fours; groups of rows at least
+    int32_t window;                // columns of a window
+    float per_col;                 // entries of a long row per column
+};
+
+__host__ __device__ inline LdsShape lds_shape(const LdsList& list, const LdsArgs& args, int64_t K, int64_t N)
+{
+    LdsShape s;
+    s.tiles = ((uint32_t)N + kLdsCols - 1) / kLdsCols;
+    s.quads = (list.count + kLdsTeams - 1) / kLdsTeams;
+    s.least = (s.quads + kLdsWaves * kLdsSlots - 1) / (kLdsWaves * kLdsSlots);
+    s.per_col = (float)list.entries / ((float)list.count * (float)K);
+    // of the longest row about two thirds of the 32 entries that a slot takes at once, and of a row in the mean 4 at least
+    const int32_t room = args.dots ? kDotsWindow : kLdsWindow;
+    float window = 16.0f / s.per_col;
+    if (window > (float)room) window = (float)room;
+    const float longest = 20.0f * (float)K / (float)list.longest;
+    window = longest > 0.25f * window ? longest : 0.25f * window;
+    s.window = args.window > 0 ? args.window : window < 1.0f ? 1 : window > (float)room ? room : (int32_t)window;
+    return s;
+}
+
+// The choice between the windows in LDS and the kernels that gather through the L2 is made by the clocks that both are
+// expected to take: the three functions below, whose constants are fitted to the kernels' own times over 200 lists (8 % off in
+// the mean, 28 % at most).  A layout that the workspace has no room for takes for ever.
+// Measured, us for the whole call, LDS against gathers; one row in a hundred is long, columns at random:
+//       rows  mean long row   N = 64        N = 128        N = 160        N = 256        N = 384        N = 1,024
+//   SpMM
+//    500,000  11,000    768 / 1,052  1,021 / 1,728  1,700 / 2,449  1,618 / 2,538  2,569 / 4,692  6,590 / 10,392
+//    500,000   5,500    584 /   622    773 / 1,038  1,262 / 1,416  1,245 / 1,545  2,119 / 2,789  5,148 /  6,331
+//    500,000   2,750    499 /   431    672 /   728  1,090 /   918  1,110 / 1,045  1,907 / 1,869  4,492 /  4,398
+//    250,000   4,400    286 /   325    362 /   472    534 /   631    536 /   681    884 / 1,229  1,826 /  2,681
+//    120,000   8,250    232 /   302    302 /   442    424 /   514    396 /   537    563 / 1,010  1,166 /  2,316
+//    120,000   3,300    170 /   175    215 /   244    272 /   272    324 /   330    407 /   540    774 /  1,133
+//    120,000   1,320    124 /   109    159 /   157    218 /   175    240 /   196    352 /   352    644 /    720
+//     88,000   6,050    183 /   273    222 /   323    310 /   289    278 /   293    395 /   528    796 /  1,092
+//     60,000   4,125    156 /   257    183 /   210    232 /   230    276 /   293    342 /   466    539 /  1,037
+//     60,000   1,650     99 /   134    127 /   121    153 /   130    179 /   160    227 /   256    364 /    555
+//     30,000   2,060     92 /   214    104 /   199    126 /   131    146 /   148    166 /   220    266 /    451
+//   SDDMM     J = 64        J = 96         J = 128        J = 160        J = 256
+//    500,000  11,000    741 / 1,030  1,146 / 1,509  1,186 / 1,745  1,584 / 2,211  1,991 / 2,725
+//    500,000   5,500    593 /   635    902 /   941    940 / 1,094  1,224 / 1,320  1,545 / 1,668
+//    500,000   2,750    524 /   459    797 /   662    845 /   811  1,086 /   868  1,375 / 1,148
+//    250,000   4,400    234 /   294    313 /   407    347 /   463    449 /   572    584 /   714
+//    120,000   8,250    179 /   290    282 /   361    245 /   414    290 /   453    379 /   559
+//    120,000   3,300    183 /   227    239 /   260    227 /   292    262 /   301    318 /   354
+//    120,000   1,320     93 /   110    136 /   146    131 /   163    160 /   160    207 /   213
+//     88,000   6,050    131 /   192    168 /   250    175 /   291    220 /   253    269 /   308
+//     60,000   4,125    175 /   287    202 /   277    209 /   284    233 /   262    264 /   306
+//     60,000   1,650    102 /   151    118 /   153    124 /   158    141 /   143    165 /   166
+//     30,000   2,060    105 /   223    113 /   241    114 /   206    126 /   143    138 /   158
+// The rule takes the slower one where the two are close, at a loss of up to 8 % (SDDMM 88,000 x 6,050 at J = 208 and 256: 8
+// and 14 %); one row eight times as long as the others costs it up to 22 % (120,000 rows, N = 128).
+__host__ __device__ inline float lds_cost(const LdsShape& s, const LdsList& list, const LdsArgs& args, int64_t K, int64_t N,
+                                          uint32_t groups, uint32_t per_die)
+{
+    const uint32_t slots = (s.quads + kLdsWaves * groups - 1) / (kLdsWaves * groups);
+    const uint32_t shares = per_die * args.dies;
+    if ((int64_t)(shares + 1) * list.count > args.ptr_room) return __builtin_inff();
+    const uint32_t share_cols = ((uint32_t)K + shares - 1) / shares;
+    const uint32_t windows = (share_cols + (uint32_t)s.window - 1) / (uint32_t)s.window;
+    const float in_window = s.per_col * (float)share_cols / (float)windows;  // entries of a row
+    const uint32_t rounds = ((args.dots ? 1 : s.tiles) * groups * per_die + args.workgroups - 1) / args.workgroups;
+    const float tiles = (float)s.tiles, rows = (float)slots;
+    // Of a job: its windows on their way into LDS, a wavefront's passes over its slots, the sums added into C at the end.
+    // SDDMM passes once for every tile, and looking up and writing the entries is about half a pass more.
+    const float job = args.dots ? (float)windows * ((tiles + 0.45f) * (17600.0f + 815.0f * rows) + tiles * 106.0f * rows * in_window)
+                                : ((float)windows * (15800.0f + rows * (454.0f + 80.0f * in_window)) + 11000.0f * rows) *
+                                      (N % kLdsCols == 0 ? 0.97f : 1.14f);  // (a tile's rows of B begin amid cache lines)
+    // what the longest row has in a window beyond the 32 entries that a slot takes at once, where its window is as narrow as
+    // it gets: the fewer the rounds, the longer the others wait for it
+    const float share = (float)list.longest * (float)s.window / (float)K;
+    const float over = share > 32.0f && args.window == 0 ? (float)list.longest * (1.0f - 32.0f / share) * 32.0f / tiles : 0.0f;
+    const float pointers = (args.dots ? 0.17f : 0.4f) * (float)list.count * (float)shares;
+    return (args.dots ? 20000.0f : 43000.0f) + (float)rounds * job + over + pointers;
+}
+
+// Clocks of what the windows would not serve.  A few rows of it cost four times what their share of all entries would (the
+// other teams and wavefronts wait), and all wait for the team whose row has the most.  500,000 rows, 5,000 of them long, us, LDS
+// against gathers:
+//   without order, share of the long rows   0.02 %        0.1 %           1 %             all
+//     SpMM  N = 64                          765 / 1,050   3,260 / 1,224   6,843 / 1,392   19,578 /  2,730
+//           N = 256                       1,642 / 2,536   4,181 / 3,176   8,234 / 3,764   48,440 / 16,519
+//     SDDMM J = 64                          709 / 1,030   2,763 / 1,251   6,096 / 1,476   17,415 /  2,768
+//           J = 256                       1,922 / 2,729   7,369 / 3,498  16,017 / 4,239   49,890 / 16,758
+//   a quarter full over a run of columns    0.1 %         1 %             all
+//     SpMM  N = 64                          981 / 1,052   1,238 / 1,079   5,620 / 1,119
+//           N = 256                       2,666 / 3,156   3,566 / 3,499  16,398 / 5,562
+//     SDDMM J = 64                          951 / 1,041   1,190 / 1,083   4,448 / 1,253
+//           J = 256                       2,586 / 3,526   3,287 / 3,923  10,879 / 6,013
+__host__ __device__ inline float lds_apart_cost(const LdsShape& s, const LdsList& list, const LdsArgs& args)
+{
+    const float all = (float)list.apart / (float)(args.dies * args.workgroups) *
+                      (args.dots ? 280.0f + 460.0f * (float)s.tiles : 440.0f + 410.0f * (float)s.tiles);
+    const float one = (float)list.worst * (args.dots ? 200.0f + 200.0f * (float)s.tiles : 600.0f);
+    return all > one ? all : one;
+}
+
+// Clocks of the kernels that gather every entry's row of B through the L2.
+__host__ __device__ inline float gather_cost(const LdsList& list, const LdsArgs& args, int64_t N)
+{
+    const float n = (float)list.count, entries = (float)list.entries, windows = (float)args.gather_windows;
+    const float die_windows = (float)((args.gather_windows + args.dies - 1) / args.dies);  // of the die with the most
+    if (N > 128) {
+        // owner wavefronts: every die walks its windows once per 256 columns, as long as a wavefront needs for all its rows
+        // or for the longest
+        const float tiles = (float)((N + 255) / 256);
+        const uint32_t owners = args.workgroups * kLdsWaves;
+        const float rounds = (float)((list.count + owners - 1) / owners);
+        const float rows = rounds * entries / n;
+        const float most = rows > (float)list.longest ? rows : (float)list.longest;
+        const float row = 270.0f + 0.28f * (float)N / tiles;  // of B
+        return tiles * (23000.0f + row * most * die_windows / windows + 1800.0f * rounds * windows / (float)args.dies);
+    }
+    // wavefronts that claim pieces, sixteen to a workgroup: what the chip moves (columns filled up to 64 or 128), and what a
+    // workgroup's pieces take one after the other
+    const float columns = N <= 64 ? 64.0f : 128.0f;
+    const float bytes = entries * columns * 4.0f / (float)args.workgroups * die_windows / windows;
+    const float claims = n * die_windows / 16.0f / (7.0f * (float)args.workgroups);
+    const float piece = 4.0f * entries / (n * windows) * (claims > 1.0f ? claims : 1.0f);
+    const float pointers = (args.dots ? 0.17f : 0.4f) * n * windows;
+    return args.dots ? 96000.0f + 0.0194f * bytes + piece * (70.0f + 60.6f * columns / 64.0f) + pointers
+                     : 84000.0f + 0.0222f * bytes + piece * (38.5f + 52.3f * columns / 64.0f) + pointers;
+}
+
+constexpr uint32_t kLdsMore = 4, kLdsShares = kWave;  // layouts tried: the fewest groups of rows and up to three more, shares per die
+
+__host__ __device__ inline LdsPlan lds_layout(const LdsShape& s, const LdsList& list, const LdsArgs& args, int64_t K, int64_t N,
+                                              uint32_t groups, uint32_t per_die, float cost)
 {
     LdsPlan p;
-    const uint32_t n = head->count;
+    const bool faster = args.window > 0 || cost + lds_apart_cost(s, list, args) < gather_cost(list, args, N);
+    p.on = cost < __builtin_inff() && faster && list.nnz < kLdsMaxNnz && K <= (1 << 24) && N < (1 << 30);
+    p.tiles = s.tiles;
+    p.tile_cols = ((uint32_t)N / 4 + s.tiles - 1) / s.tiles * 4;
+    p.groups = groups;
+    p.slots = (s.quads + kLdsWaves * groups - 1) / (kLdsWaves * groups);
+    p.per_die = per_die;
+    p.share_cols = (int32_t)(((uint32_t)K + per_die * args.dies - 1) / (per_die * args.dies));
+    p.window = s.window;
+    return p;
+}
+
+// How the list's rows are laid over the workgroups.  Their number is not known on the host: the workgroups of
+// panel_pointers_kernel each work it out (all lanes of a wavefront together, one number of shares each), one leaves it in the
+// header.
+__device__ __forceinline__ LdsPlan lds_plan(const LdsList& list, const LdsArgs& args, int64_t K, int64_t N)
+{
+    LdsPlan p;
     p.on = 0;
-    if (n < args.min_rows) return p;
-    const unsigned long long entries = head->entries;
-    const uint32_t dies = args.dies;
-    p.tiles = (uint32_t)((N + kLdsCols - 1) / kLdsCols);
-    p.tile_cols = (uint32_t)((N / 4 + p.tiles - 1) / p.tiles) * 4;
-    const uint32_t quads = (n + kLdsTeams - 1) / kLdsTeams;
-    const uint32_t least = (quads + kLdsWaves * kLdsSlots - 1) / (kLdsWaves * kLdsSlots);
-    const float per_col = (float)entries / ((float)n * (float)K);  // entries of a long row per column
-    // Lane l: l + 1 shares per die, with the fewest groups of rows and up to three more.  Clocks of a job, roughly (500,000
-    // rows, 5,000 of them long with 11,000 entries in the mean, N = 256: 2.77 M by this, 2.6 M measured): a wavefront's
-    // pass over a slot in a window, the window on its way into LDS, the sums added into C at the end; and the search for
-    // the shares' ends before.  SDDMM passes once for every tile, and what looking up and writing its entries adds is
-    // about one pass more (the same matrix: 3.51 M by this, 3.49 M measured; 64 columns: 1.46 M and 1.40 M).
-    p.window = args.window > 0 ? args.window : (int32_t)fmaxf(1.0f, fminf((float)kLdsWindow, 16.0f / per_col));
+    if (list.count < args.min_rows) return p;
+    const LdsShape s = lds_shape(list, args, K, N);
     const uint32_t lane = threadIdx.x % kWave;
     unsigned long long best = ~0ull;
-    for (uint32_t more = 0; more < 4; ++more) {
-        const uint32_t groups = least + more;
-        const uint32_t slots = (quads + kLdsWaves * groups - 1) / (kLdsWaves * groups);
-        const int64_t shares = (int64_t)(lane + 1) * dies;
-        const int64_t share_cols = (K + shares - 1) / shares;
-        const uint32_t windows = (uint32_t)((share_cols + p.window - 1) / p.window);
-        const float in_window = per_col * (float)share_cols / (float)windows;  // entries of a row
-        const uint32_t rounds = ((args.dots ? 1 : p.tiles) * groups * (lane + 1) + args.workgroups - 1) / args.workgroups;
-        const float job = args.dots ? (float)(windows * (p.tiles + 1)) * ((float)slots * (700.0f + 117.0f * in_window) + 6000.0f)
-                                    : (float)windows * ((float)slots * (600.0f + 128.0f * in_window) + 5000.0f) + (float)slots * 7400.0f;
-        const float cost = (float)rounds * job + 0.3f * (float)n * (float)shares;
-        const bool fits = (shares + 1) * n <= args.ptr_room;
+    for (uint32_t more = 0; more < kLdsMore; ++more) {
+        const float cost = lds_cost(s, list, args, K, N, s.least + more, lane + 1);
         const unsigned long long key = (unsigned long long)__float_as_uint(cost) << 32 | more << 8 | lane;
-        if (fits && key < best) best = key;
+        if (key < best) best = key;
     }
 #pragma unroll
     for (int m = 1; m < kWave; m *= 2) {
@@ -127,56 +252,8 @@ __device__ __forceinline__ LdsPlan lds_plan(const PanelHeader* head, const LdsAr
         if (other < best) best = other;
     }
     const uint32_t chosen = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)best);
-    p.groups = least + (chosen >> 8 & 3);
-    p.slots = (quads + kLdsWaves * p.groups - 1) / (kLdsWaves * p.groups);
-    p.per_die = (chosen & 63) + 1;
-    p.share_cols = (int32_t)((K + (int64_t)p.per_die * dies - 1) / ((int64_t)p.per_die * dies));
-    // The kernels that gather every entry's row of B through the L2.  Up to 128 columns: wavefronts that claim pieces, 29 bytes
-    // per clock and compute unit (SDDMM 40, and something for every long row's part of a panel of 2 MiB and for filling and
-    // draining the chip), more time where there are too few rows to go round.  Beyond: owner wavefronts, each with the same
-    // number of rows, rounded up, at 296 clocks per gathered row (the address units take as long for 132 columns as for 256).
-    // 160,000 clocks are what the model of the LDS kernel leaves out at its start; where the two are close the owners are kept.
-    // Measured around the line, us for the whole call, LDS against gathers (one row in a hundred is long):
-    //         rows      mean long row  N = 64        N = 128         N = 160       N = 208       N = 256
-    //   SpMM  500,000   5,500          584 /   632   806 / 1,050                                 1,291 / 1,559
-    //         500,000   2,750          517 /   434   697 /   721                                 1,136 / 1,057
-    //         120,000   8,250                                        437 / 514     452 / 511       432 /   546
-    //          88,000   6,050                                        314 / 299     329 / 285       316 /   304
-    //          60,000   4,125          127 /   256   150 /   185     261 / 259     344 / 320       330 /   337
-    //   SDDMM 500,000   5,500          644 /   649   957 / 1,112                                 1,603 / 1,691
-    //         500,000   2,750          556 /   465   838 /   822                                 1,389 / 1,158
-    //         120,000   8,250                                        311 / 471     408 / 547       399 /   582
-    //          88,000   6,050                                        281 / 265     344 / 308       346 /   325
-    //         120,000   1,320          127 /   110   147 /   162                                   232 /   216
-    const float pieces = (float)n * (float)K * (float)N * 4.0f / (float)(2 << 20);
-    float gather = (float)entries * (float)N * 4.0f / (float)(dies * args.workgroups);
-    if (N > 128) {
-        const uint32_t owners = args.workgroups * kLdsWaves;
-        gather = 296.0f / (float)dies * (float)((n + owners - 1) / owners) * ((float)entries / (float)n) + 0.15f * pieces - 160000.0f;
-    } else if (args.dots) {
-        gather = gather / 40.0f * (1.0f + 800.0f / (float)n) + 0.6f * pieces + 40000.0f;
-    } else {
-        gather = gather / 29.0f * fmaxf(1.0f, 1200.0f / (float)n);
-    }
-    // What windows would not serve.  A few rows of it cost four times what their share of all entries would (the other teams
-    // and wavefronts wait), and all wait for the team whose row has the most.  500,000 rows, 5,000 of them long, us, LDS
-    // against gathers (which are what the rule then takes, but for 0.02 %):
-    //   without order, share of the long rows   0.02 %        0.1 %           1 %             all
-    //     SpMM  N = 64                          765 / 1,050   3,260 / 1,224   6,843 / 1,392   19,578 /  2,730
-    //           N = 256                       1,642 / 2,536   4,181 / 3,176   8,234 / 3,764   48,440 / 16,519
-    //     SDDMM J = 64                          709 / 1,030   2,763 / 1,251   6,096 / 1,476   17,415 /  2,768
-    //           J = 256                       1,922 / 2,729   7,369 / 3,498  16,017 / 4,239   49,890 / 16,758
-    //   a quarter full over a run of columns    0.1 %         1 %             all
-    //     SpMM  N = 64                          981 / 1,052   1,238 / 1,079   5,620 / 1,119
-    //           N = 256                       2,666 / 3,156   3,566 / 3,499  16,398 / 5,562
-    //     SDDMM J = 64                          951 / 1,041   1,190 / 1,083   4,448 / 1,253
-    //           J = 256                       2,586 / 3,526   3,287 / 3,923  10,879 / 6,013
-    const float apart = fmaxf((float)head->apart / (float)(dies * args.workgroups) *
-                                  (args.dots ? 280.0f + 460.0f * (float)p.tiles : 440.0f + 410.0f * (float)p.tiles),
-                              (float)head->worst * (args.dots ? 200.0f + 200.0f * (float)p.tiles : 600.0f));
-    const bool faster = args.window > 0 || __uint_as_float((uint32_t)(best >> 32)) + apart < gather;
-    p.on = best != ~0ull && faster && head->nnz < kLdsMaxNnz && K <= (1 << 24) && N < (1 << 30);
-    return p;
+    const float cost = __int_as_float(__builtin_amdgcn_readfirstlane((int)(uint32_t)(best >> 32)));
+    return lds_layout(s, list, args, K, N, s.least + (chosen >> 8), (chosen & 255) + 1, cost);
 }
 
 // The value that lane J of a lane's team holds.
@@ -435,10 +512,6 @@ __device__ __forceinline__ void panel_lds_rows(const int32_t* __restrict__ colid
     static_assert(kLdsCols == kWave, "the row of zeros");
     if (wave == 0) s_b[kLdsWindow * kLdsCols + LdsThread().lane] = 0.0f;
 
-    // a window has at most about two thirds of the 32 entries that a slot takes at once, of the longest row
-    int32_t most_cols = plan.window;
-    if (args.window == 0 && n <= (uint32_t)kRankMaxRows)
-        most_cols = (int32_t)fmaxf(1.0f, fminf((float)kLdsWindow, fmaxf(0.25f * (float)most_cols, 20.0f * (float)K / (float)scr.len[scr.order[0]])));
     const uint32_t per_share = plan.tiles * plan.groups;
     const uint32_t jobs = per_share * plan.per_die;
     const uint32_t shares = plan.per_die * args.dies;
@@ -476,7 +549,7 @@ __device__ __forceinline__ void panel_lds_rows(const int32_t* __restrict__ colid
 #pragma unroll
         for (int r = 0; r < R; ++r) acc[r].zero();
 
-        const int32_t count = (share_end - (int32_t)share_begin + most_cols - 1) / most_cols;  // windows
+        const int32_t count = (share_end - (int32_t)share_begin + plan.window - 1) / plan.window;  // windows
         const int32_t width = (share_end - (int32_t)share_begin + count - 1) / count;
         LdsEntries held[2];           // of the next two slots
         uint32_t next_end = end_of[0];  // of the next slot

@@ -21,8 +21,6 @@
 
 namespace sgap {
 
-constexpr int kDotsWindow = 596;  // rows of X2T in LDS (and one of zeros)
-
 struct DotsShared {
     __attribute__((aligned(16))) float b[(kDotsWindow + 1) * kLdsCols];
     uint32_t end[kLdsWaves * kLdsTeams * kLdsSlots];  // of the slots' shares, as byte offsets of entries
@@ -246,9 +244,6 @@ __device__ __forceinline__ void panel_lds_dots(const int32_t* __restrict__ colid
     const uint32_t member4 = l.member8 / 2;
     const int32_t entry = dots_entry((int)(l.member8 / 8));
     const uint32_t row_bytes = (uint32_t)J * 4;
-    int32_t most_cols = plan.window < kDotsWindow ? plan.window : kDotsWindow;
-    if (args.window == 0 && n <= (uint32_t)kRankMaxRows)
-        most_cols = (int32_t)fmaxf(1.0f, fminf((float)kDotsWindow, fmaxf(0.25f * (float)most_cols, 20.0f * (float)K / (float)scr.len[scr.order[0]])));
     const uint32_t jobs = plan.groups * plan.per_die;
     const uint32_t shares = plan.per_die * args.dies;
     for (uint32_t job = blockIdx.x / args.dies; job < jobs; job += args.workgroups) {
@@ -281,7 +276,7 @@ __device__ __forceinline__ void panel_lds_dots(const int32_t* __restrict__ colid
                 }
             }
         }
-        const int32_t count = (share_end - (int32_t)share_begin + most_cols - 1) / most_cols;  // windows
+        const int32_t count = (share_end - (int32_t)share_begin + plan.window - 1) / plan.window;  // windows
         const int32_t width = (share_end - (int32_t)share_begin + count - 1) / count;
         for (int32_t w = 0; w < count; ++w) {
             const int32_t c0 = (int32_t)share_begin + w * width;

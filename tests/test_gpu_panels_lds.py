@@ -8,6 +8,7 @@ from paper_2209_02882_amd import binding
 from paper_2209_02882_amd import workloads as wl
 
 from gpu_util import DeviceProblem, assert_close, full_reference
+from test_window_form import plan
 
 pytestmark = pytest.mark.gpu
 
@@ -90,6 +91,24 @@ def test_floats_where_the_rule_takes_it():
     check(problem(1300, 9000, 128, 6000, seed=9, integer=False), 500, "floats", exact=False, window_kb=0)
 
 
+# (which the tests of test_window_form.py rest on)
+@pytest.mark.parametrize("n_long,K,N,longest", [(260, 9000, 64, 3000), (1300, 9000, 128, 6000), (700, 20000, 160, 4000), (300, 5000, 260, 700)])
+def test_the_device_chooses_as_the_host_does(n_long, K, N, longest):
+    p = problem(n_long, K, N, longest, seed=n_long, shortest=longest // 3)
+    dp = DeviceProblem(p)
+    lengths = np.diff(p.rowptr)
+    long = lengths[lengths >= longest // 4]
+    cfg = binding.make_config(1, "serial", "row_split", long_row_min=longest // 4)
+    ws = dp.workspace_for(cfg)
+    dp.launch_cfg(dp.new_output(), cfg, ws)
+    head = ws[:256].view(torch.int32).cpu().tolist()
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    on, groups, shares, window, _, _ = plan("spmm", K, N, long.size, int(long.sum()), int(long.max()), int(p.rowptr[-1]),
+                                            head[28], head[27], cus=cus)
+    assert head[0] == long.size and head[16] == long.sum() and head[30] == long.max()
+    assert head[LDS_RUNS] == on and (not on or (head[22], head[24], head[26]) == (groups, shares, window))
+
+
 def test_the_size_of_the_windows_chooses_between_lds_and_the_l2():
     p = problem(1300, 9000, 128, 6000, seed=11)
     for window_kb, runs in ((0, 1), (154, 1), (155, 0), (3072, 0)):
@@ -121,7 +140,7 @@ def test_rows_that_windows_in_lds_would_not_serve(shape):
     n_long, args = 1300, (1300, 9000, 128, 6000)
     long = np.flatnonzero(np.diff(problem(*args, seed=12).rowptr) > 500)
     assert long.size == n_long
-    for rows, runs in ((long, 0), (long[::20], 0), (long[:0], 1)):
+    for rows, runs in ((long, 0), (long[::4], 0), (long[:0], 1)):
         check(shape(problem(*args, seed=12), rows), 500, f"{rows.size} rows", window_kb=0, runs=runs)
 
 
