@@ -704,12 +704,12 @@ void plan_panels(int64_t K, int64_t N, int64_t window_bytes, int* windows, int32
 
 // What the caller says about the windows: nothing, and the device chooses between windows in LDS and windows that the L2
 // holds; a size that fits in LDS, and they lie there; a larger one, and they do not.
-LdsArgs lds_args(int64_t N, int windows, int64_t window_bytes, bool asked, int xcds, int compute_units, int64_t cap, bool dots)
+LdsArgs lds_args(int64_t K, int64_t N, int windows, int64_t window_bytes, bool asked, int xcds, int compute_units, int64_t cap, bool dots)
 {
     const int64_t rows = window_bytes / kLdsRowBytes;
     const bool fit = rows <= (dots ? kDotsWindow : kLdsWindow);
     LdsArgs lds;
-    lds.min_rows = N >= kLdsMinCols && (fit || !asked) ? kLdsMinRows : 0xffffffffu;
+    lds.min_rows = N >= kLdsMinCols && (fit || !asked) && K <= kLdsMaxCols ? kLdsMinRows : 0xffffffffu;
     lds.dies = (uint32_t)xcds;
     lds.workgroups = (uint32_t)(compute_units / xcds > 0 ? compute_units / xcds : 1);
     lds.ptr_room = cap * (windows + 1);
@@ -786,7 +786,7 @@ PanelForm plan_panel_form(bool dots, int64_t K, int64_t N, const LdsList& list, 
     int32_t window_rows = 1;
     if (!dots) spmm_panel_layout(N, &wave_lc, &window_cols);
     plan_panels(K, window_cols, window_bytes, &windows, &window_rows);
-    const LdsArgs args = lds_args(N, windows, window_bytes, window_asked, xcds, compute_units, cap, dots);
+    const LdsArgs args = lds_args(K, N, windows, window_bytes, window_asked, xcds, compute_units, cap, dots);
     PanelForm form;
     form.lds.on = 0;
     form.lds_clocks = form.gather_clocks = 0.0f;
@@ -831,7 +831,7 @@ hipError_t launch_row_split_panels(const SpmmArgs& a, int g, int lc, int vec, in
     const PanelView scr = panel_view(workspace, cap, windows);
     // a wavefront per row with all 64 lanes on column chunks: worth it from 128 columns on
     const bool owners = wave_lc == kPanelTileLanes && a.N >= 128;
-    const LdsArgs lds = lds_args(a.N, windows, window_bytes, window_asked, xcds, compute_units, cap, false);
+    const LdsArgs lds = lds_args(a.K, a.N, windows, window_bytes, window_asked, xcds, compute_units, cap, false);
     launch_panel_preparation(a, scr, windows, window_rows, min_len, true, owners, xcds, compute_units, lds, s);
     if (!owners && lds.min_rows != 0xffffffffu)
         hipLaunchKernelGGL(panel_lds_kernel, dim3(lds.workgroups * lds.dies), dim3(kLdsBlock), 0, s, a.colidx, a.vals, a.B,
@@ -998,8 +998,9 @@ __device__ __forceinline__ void wave_dot8(const UniformRows<4, OFF32>& rows, con
 // windows, same barrier per window): for dense rows of 129 to 256 columns and lists long enough.  What a wavefront keeps
 // of its ten rows is their rows of X1 instead of their sums, and every entry is written when it is done: no atomics.
 // Registers: ten rows of X1, their entries and a batch of eight gathers fill the 128 that a workgroup of 1,024 threads
-// has.  The instance for J = 256 keeps two of them in memory; the form that does not (the lane's place among the eight
-// sums computed anew for each batch, 125 registers) takes 2,743 us on the skewed matrix where this one takes 2,726.
+// has.
+// (One launch for these and for panel_lds_dots, as for SpMM: 500,000 rows, J = 256, windows in LDS, 2,010 us with two and 1,983
+// with one; 60,000 rows 267 and 263.)
 template <bool OFF32, bool EDGE>
 __global__ __launch_bounds__(kOwnerBlock) void panel_sddmm_owner_kernel(const int32_t* __restrict__ colidx,
                                                                         const float* __restrict__ vals,
@@ -1007,13 +1008,18 @@ __global__ __launch_bounds__(kOwnerBlock) void panel_sddmm_owner_kernel(const in
                                                                         const float* __restrict__ X2T,
                                                                         float* __restrict__ out, PanelView scr, int64_t K,
                                                                         int64_t J, int windows, int32_t window_rows,
-                                                                        int xcds, uint32_t min_rows)
+                                                                        int xcds, uint32_t min_rows, LdsArgs lds)
 {
     constexpr int R = kOwnerRows;
+    __shared__ DotsShared s_dots;
     const uint32_t n = scr.head->count;
-    if (n < min_rows || n > scr.cap || scr.head->lds.on) return;
-    const int lane = threadIdx.x % kWave;
     const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    if (scr.head->lds.on) {  // the windows lie in LDS
+        panel_lds_dots(colidx, vals, X1, X2T, out, scr, K, J, lds, wave, s_dots);
+        return;
+    }
+    if (n < min_rows || n > scr.cap) return;
+    const int lane = LdsThread().lane;  // (threadIdx.x would be kept throughout the other branch)
     const uint32_t xcd = blockIdx.x % xcds;
     const uint32_t waves = (gridDim.x / xcds) * kOwnerWaves;  // wavefronts of this die
     const uint32_t me = (blockIdx.x / xcds) * kOwnerWaves + wave;
@@ -1029,8 +1035,11 @@ __global__ __launch_bounds__(kOwnerBlock) void panel_sddmm_owner_kernel(const in
         int32_t my_pos = 0;
         int32_t my_row = -1;
         {
+            const int lane = LdsThread().lane;  // (else the place in ptr is kept throughout)
             const uint32_t round = r0 + (uint32_t)(lane % R);
-            const uint32_t q = round * waves + ((round & 1u) ? waves - 1u - me : me);
+            uint32_t odd = waves - 1u - 2u * me;  // (and so are these in vector registers)
+            asm volatile("" : "+s"(odd));
+            const uint32_t q = round * waves + me + (round & 1u) * odd;
             if (lane < 3 * R && round < rounds && q < n) {
                 const int32_t i = scr.order[q];
                 my_pos = scr.ptr[(int64_t)i * per_row + (lane >= R && lane < 2 * R ? w_end : w_begin)];
@@ -1145,6 +1154,7 @@ __global__ __launch_bounds__(kBlock) void sddmm_short_rows_kernel(SpmmArgs a, co
     }
 }
 
+// panel_lds_dots by itself, where no owner wavefronts are launched (J <= 128).
 __global__ __launch_bounds__(kLdsBlock) void panel_lds_dots_kernel(const int32_t* __restrict__ colidx,
                                                                    const float* __restrict__ vals,
                                                                    const float* __restrict__ X1,
@@ -1195,10 +1205,10 @@ hipError_t launch_sddmm_panels(const SpmmArgs& a, const float* X1, float* out, i
     int wave_lc = 8;
     while (wave_lc < kWave && (int64_t)wave_lc * 4 < a.N) wave_lc *= 2;
     const bool owners = wave_lc == kWave;
-    const LdsArgs lds = lds_args(a.N, windows, window_bytes, window_asked, xcds, compute_units, cap, true);
+    const LdsArgs lds = lds_args(a.K, a.N, windows, window_bytes, window_asked, xcds, compute_units, cap, true);
     launch_panel_preparation(a, scr, windows, window_rows, min_len, false, owners, owners ? xcds : 1, compute_units, lds, s);
     uint32_t below = 0xffffffffu;
-    if (lds.min_rows != 0xffffffffu)
+    if (!owners && lds.min_rows != 0xffffffffu)
         hipLaunchKernelGGL(panel_lds_dots_kernel, dim3(lds.workgroups * lds.dies), dim3(kLdsBlock), 0, s, a.colidx, a.vals, X1,
                            a.B, out, scr, a.K, a.N, lds);
     if (owners) {
@@ -1208,7 +1218,7 @@ hipError_t launch_sddmm_panels(const SpmmArgs& a, const float* X1, float* out, i
         if (grid < xcds) grid = xcds;
         auto go = [&](auto kernel) {
             hipLaunchKernelGGL(kernel, dim3(grid), dim3(kOwnerBlock), 0, s, a.colidx, a.vals, X1, a.B, out, scr, a.K, a.N,
-                               windows, window_rows, xcds, below);
+                               windows, window_rows, xcds, below, lds);
         };
         const bool edge = a.N != kWave * 4;
         if (offsets_fit_32(a)) {

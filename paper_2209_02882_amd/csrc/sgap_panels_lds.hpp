@@ -41,6 +41,7 @@ constexpr int kLdsWindow = 616;                    // rows of B in LDS (and one 
 constexpr int kDotsWindow = 596;                   // of X2T, for SDDMM: the rows' numbers lie in LDS too
 constexpr int kLdsRowBytes = kLdsCols * 4;
 constexpr uint32_t kLdsMaxNnz = 1u << 29;          // byte offsets of entries have 31 bits
+constexpr int64_t kLdsMaxCols = 1 << 24;           // byte offsets of rows of 64 columns have 32 bits
 constexpr uint32_t kLdsMinRows = 256;
 constexpr int kLdsMinCols = 64;                    // columns of B from which on the kernel runs
 constexpr int kLdsNoLoads = 0x0F70;                // s_waitcnt vmcnt(0)
@@ -219,7 +220,7 @@ __host__ __device__ inline LdsPlan lds_layout(const LdsShape& s, const LdsList& 
 {
     LdsPlan p;
     const bool faster = args.window > 0 || cost + lds_apart_cost(s, list, args) < gather_cost(list, args, N);
-    p.on = cost < __builtin_inff() && faster && list.nnz < kLdsMaxNnz && K <= (1 << 24) && N < (1 << 30);
+    p.on = cost < __builtin_inff() && faster && list.nnz < kLdsMaxNnz && N < (1 << 30);
     p.tiles = s.tiles;
     p.tile_cols = ((uint32_t)N / 4 + s.tiles - 1) / s.tiles * 4;
     p.groups = groups;

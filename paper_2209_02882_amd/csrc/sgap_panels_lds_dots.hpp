@@ -171,7 +171,7 @@ __device__ __forceinline__ uint32_t dots_rest(const LdsMatrix& matrix, const flo
                                               const float* __restrict__ X2T, float* __restrict__ out, int64_t J, uint32_t p,
                                               uint32_t end, int32_t c1, const LdsLanes& l)
 {
-    const int member = (int)(l.member8 / 8);
+    const int member = LdsThread().member;
     for (;;) {
         const uint32_t at = p + l.member8 / 2;
         const int32_t col = (int32_t)__builtin_amdgcn_raw_buffer_load_b32(matrix.cols, (int)at, 0, 0);
@@ -189,7 +189,7 @@ __device__ __forceinline__ uint32_t dots_rest(const LdsMatrix& matrix, const flo
             }
             if (j < taken) {
 #pragma unroll 1
-                for (int64_t k = member * 4; k < J; k += kLdsCols) {
+                for (int32_t k = member * 4; k < (int32_t)J; k += kLdsCols) {
                     const Vec<4> a = load_vec<4>(X1_row + k);
                     Vec<4> b[4];
 #pragma unroll

@@ -43,9 +43,8 @@ def kernels():
     return found
 
 
-# instances with two registers in memory, faster than the forms without (beside the kernels in sgap_panels.hip and
-# sgap_sddmm.hip)
-KNOWN = {"panel_sddmm_owner_kernelILb1ELb0E": 2, **{f"sddmm_tile_kernelILi{g}ELi4ELb1ELi2E": 2 for g in (2, 4, 8, 16, 32)}}
+# instances with two registers in memory, faster than the forms without (beside the kernel in sgap_sddmm.hip)
+KNOWN = {f"sddmm_tile_kernelILi{g}ELi4ELb1ELi2E": 2 for g in (2, 4, 8, 16, 32)}
 
 
 def test_no_vector_register_is_spilled(kernels):
