@@ -97,10 +97,11 @@ def test_more_long_rows_than_the_list_holds_switches_the_path_off(panels):
             assert_close(panels.run(dp, *point), C_ref, BND, exact=True, what=f"list of {cap} rows {point}")
 
 
-def test_many_long_rows_of_wide_operands_take_several_passes(panels):
-    # 128 columns and more: every long row has one owner wavefront per die; 12,000 long rows are more than
+@pytest.mark.parametrize("N", [128, 132])
+def test_many_long_rows_of_wide_operands_take_several_passes(panels, N):
+    # from 129 columns on: every long row has one owner wavefront per die; 12,000 long rows are more than
     # the wavefronts of a die own in one pass, and more than are sorted by length
-    M, K, N = 12500, 3000, 128
+    M, K = 12500, 3000
     lengths = np.full(M, 40)
     lengths[::25] = 3
     p = csr_problem("many_long_wide", M, K, N, lengths, seed=4, integer=True)

@@ -1,5 +1,6 @@
-"""SDDMM with long rows by column windows where owner wavefronts take them (129 to 256 columns, lists of 256 rows and
-more), the short rows' kernel beside them, and the rows that fall to neither: exact on integer-valued inputs."""
+"""SDDMM with long rows by column windows (windows of 64 KiB lie in LDS; of 160 KiB owner wavefronts take them, from 129 columns
+on, in lists of 256 rows and more), the short rows' kernel beside them, and the rows that fall to neither: exact on
+integer-valued inputs."""
 import numpy as np
 import pytest
 import torch
@@ -13,7 +14,7 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("J", [32, 64, 100, 128, 132, 200, 252, 256])
-@pytest.mark.parametrize("min_len,window_kb,cap", [(150, 0, 0), (150, 64, 0), (1500, 256, 0), (40, 16, 255)])
+@pytest.mark.parametrize("min_len,window_kb,cap", [(150, 0, 0), (150, 64, 0), (150, 160, 0), (1500, 256, 0), (40, 16, 255)])
 def test_long_short_and_other_rows(J, min_len, window_kb, cap):
     rng = np.random.default_rng(J + min_len)
     M, K = 3000, 5000

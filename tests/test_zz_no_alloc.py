@@ -26,14 +26,16 @@ def run_static(dp, cfg):
     return C
 
 
-@pytest.mark.parametrize("N", [64, 256])  # the claiming kernel / the owner wavefronts
-def test_two_calls_in_a_row_the_second_smaller(N):
+# the claiming kernel, the owner wavefronts (the second's list is too short for them), windows in LDS (which lists from 256
+# rows on take; the second's is claimed)
+@pytest.mark.parametrize("N,window_kbs", [(64, (160, 192)), (256, (160, 192)), (64, (32, 64)), (256, (32, 64))])
+def test_two_calls_in_a_row_the_second_smaller(N, window_kbs):
     # first: 1,400 long rows over many windows; second: a smaller matrix with fewer long rows and fewer windows
     first = csr_problem("first", 4200, 9000, N, mixed_lengths(4200, 9000, 41, long_every=3, long_len=(150, 900)),
                         seed=41, integer=True)
     second = csr_problem("second", 900, 2000, N, mixed_lengths(900, 2000, 42, long_every=7, long_len=(120, 500)),
                          seed=42, integer=True)
-    for p, window_kb in ((first, 32), (second, 64)):
+    for p, window_kb in zip((first, second), window_kbs):
         dp = DeviceProblem(p)
         C_ref, BND = full_reference(p)
         for point in [(1, "serial", "row_split"), (8, "parallel", "row_split")]:
