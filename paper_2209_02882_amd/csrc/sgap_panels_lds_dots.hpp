@@ -80,7 +80,7 @@ struct DotsFound {
     unsigned long long taken[2];  // lanes whose entry i is one of the window's
     uint32_t most;                // entries of the team with the most
     bool full;                    // a team has taken all 32 and may have more
-    bool odd;                     // a team's are not the first ones (columns that are not sorted): it takes none
+    unsigned long long odd;       // lanes that show that a team's are not the first ones (columns that are not sorted)
 };
 
 // over as for lds_slot.
@@ -93,17 +93,7 @@ __device__ __forceinline__ DotsFound dots_find(const uint32_t (&at)[2], int32_t 
         f.taken[i] = __ballot(at[i] < w.bytes) & __ballot(over < -(int32_t)(l.member8 / 2) - 4 * kLdsTeam * i);
     const unsigned long long gaps = ((f.taken[0] & ~(f.taken[0] << 1)) | (f.taken[1] & ~(f.taken[1] << 1))) & ~kFirst;
     const unsigned long long late = f.taken[1] & kFirst & ~(f.taken[0] >> (kLdsTeam - 1));
-    unsigned long long odd = gaps | late;
-    f.odd = odd != 0;
-    if (f.odd) {  // of those teams alone: how a row's sums are made does not depend on the rows beside it
-        odd = (odd | odd >> 8) & 0x00FF00FF00FF00FFull;
-        odd = (odd | odd >> 4) & 0x000F000F000F000Full;
-        odd = (odd | odd >> 2) & 0x0003000300030003ull;
-        odd = (odd | odd >> 1) & kFirst;
-        const unsigned long long lanes = (odd << kLdsTeam) - odd;
-        f.taken[0] &= ~lanes;
-        f.taken[1] &= ~lanes;
-    }
+    f.odd = gaps | late;
     f.full = (f.taken[1] >> (kLdsTeam - 1) & kFirst) != 0;
     f.most = 0;
 #pragma unroll
@@ -340,9 +330,12 @@ __device__ __forceinline__ void panel_lds_dots(const int32_t* __restrict__ colid
                         const int32_t over = team_bcast<r % kLdsTeam>(pos[r / kLdsTeam]) - (int32_t)end;
                         const DotsFound f = dots_find(at, over, window, l);
                         most = __builtin_amdgcn_inverse_ballot_w64(1ull << r) ? (int32_t)f.most : most;
-                        const int32_t here = __popc(team_field(f.taken[0], l)) + __popc(team_field(f.taken[1], l));
+                        int32_t here = __popc(team_field(f.taken[0], l)) + __popc(team_field(f.taken[1], l));
+                        // (such a team takes none, and the others what they have: how a row's sums are made does not depend on
+                        // the rows beside it)
+                        if (f.odd && team_field(f.odd, l)) here = 0;
                         taken[r / kLdsTeam] = __builtin_amdgcn_inverse_ballot_w64(0x0001000100010001ull << (r % kLdsTeam)) ? here : taken[r / kLdsTeam];
-                        if (f.full || f.odd) open |= 1u << r;
+                        if (f.full || f.odd != 0) open |= 1u << r;
                         open = (uint32_t)__builtin_amdgcn_readfirstlane((int)open);
                         asm volatile("" : "+s"(open));
                     }
