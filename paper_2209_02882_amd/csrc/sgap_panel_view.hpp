@@ -4,7 +4,7 @@
 
 namespace sgap {
 
-constexpr int kRankMaxRows = 8192;     // lists up to this length are sorted by row length (their lengths fit in LDS)
+constexpr int kRankMaxRows = 8192;     // lists up to this length are sorted by row length (every row looks at every other)
 
 // How panel_lds_kernel's work is laid over the workgroups.
 struct LdsPlan {

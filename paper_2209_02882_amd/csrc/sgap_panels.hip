@@ -829,8 +829,8 @@ hipError_t launch_row_split_panels(const SpmmArgs& a, int g, int lc, int vec, in
         return launch_row_split(a, g, lc, vec, rows_per_slot, interleave, tile_cols, xcds, compute_units, persistent,
                                 block, -1, 16.0, s);
     const PanelView scr = panel_view(workspace, cap, windows);
-    // a wavefront per row with all 64 lanes on column chunks: worth it from 128 columns on
-    const bool owners = wave_lc == kPanelTileLanes && a.N >= 128;
+    // a wavefront per row with all 64 lanes on column chunks: from 129 columns on
+    const bool owners = wave_lc == kPanelTileLanes;
     const LdsArgs lds = lds_args(a.K, a.N, windows, window_bytes, window_asked, xcds, compute_units, cap, false);
     launch_panel_preparation(a, scr, windows, window_rows, min_len, true, owners, xcds, compute_units, lds, s);
     if (!owners && lds.min_rows != 0xffffffffu)

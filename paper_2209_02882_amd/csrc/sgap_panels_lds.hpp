@@ -15,14 +15,15 @@
 //          57.6 GB out of the L2s)
 // Four entries of four rows cost a wavefront one addition (the address), one 16-byte LDS read and four multiply-adds; a
 // pair is handed round its team by DPP (row_newbcast), at no cost.  That makes the vector instructions the bound: 568 M on
-// the skewed matrix, 2.2 M clocks of a SIMD of 2.6 M in all (1.2 ms; the whole call 2.54 ms before, 1.61 now).  Half of
+// the skewed matrix, 2.2 M clocks of a SIMD of 2.8 M in all (1.2 to 1.3 ms; the whole call 2.54 ms before, 1.62 now).  Half of
 // them are multiply-adds that A asks for; a sixth is what the four rows of a wavefront differ by in a window (the more
 // entries a row has there, the less: hence windows as large as LDS allows), a quarter what a slot costs by itself, and
 // the rest fills up pairs.  The remaining clocks are the windows' way into LDS (10 %) and waiting for the slowest
 // wavefront (8 %).  Windows in two halves by turns would hide the former at the price of half the entries per slot.
 //
 // Nothing relies on sorted columns or columns without repetition: where what a row has in a window is not one run of its
-// entries, or more than a slot takes at once, the rest is gathered from memory.
+// entries, or more than a slot takes at once, the rest is gathered from memory; where that would be much, the kernels that
+// gather all of it run (lds_apart, lds_layout).
 #pragma once
 #include <type_traits>
 

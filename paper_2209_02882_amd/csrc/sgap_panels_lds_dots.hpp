@@ -9,9 +9,9 @@
 // The first tile's pass looks up what belongs to the window (dots_find); the others know how many entries there are and let
 // the rest of their lanes add up what nobody asks for, in front of rows that exist.
 //
-// Bound by the vector instructions: on the skewed matrix (500,000 rows, 5,000 long ones with 55 M entries, J = 256) 690 M of
-// them, 2.7 M clocks of a SIMD of 3.4 M (1.6 ms; the owner wavefronts that gather through the L2 took 2.28 ms, the call
-// 2.73 ms and now 2.00 ms).  A third are the products that the entries ask for, as many what four rows differ by in a
+// Bound by the vector instructions: on the skewed matrix (500,000 rows, 5,000 long ones with 55 M entries, J = 256) 717 M of
+// them, 2.8 M clocks of a SIMD of 3.3 M (1.6 to 1.7 ms; the owner wavefronts that gather through the L2 took 2.28 ms, the call
+// 2.73 ms and now 1.98 ms).  A third are the products that the entries ask for, as many what four rows differ by in a
 // window and the adding up over lanes, a sixth the addresses, the rest what a slot costs.  7.7 GB come from beyond the L2s:
 // a row of X1 is read again in every window.  Looking entries up in every
 // tile and eight-entry sums of 18 instructions were 833 M (1.84 ms); the next window's first tile on its way while the

@@ -238,7 +238,10 @@ __global__ __launch_bounds__(kBlock) void sddmm_kernel(SddmmArgs s, int per_lane
 // EDGE: J is not S*G*4 (lanes without columns, or a ragged last chunk).  Those instances with S = 4 and 512 entries keep
 // two registers in memory; computed anew per tile, what they hold costs more (R-MAT of 2^19 rows, J = 35, G = 4: 165.9
 // us against 164.8).
-// Tiles of wide rows without lanes to spare.
+// In step: J above 64 that is one, two or four times G * 4, so that no lane is to spare (at the groups of 8 and 16 that is 128
+// alone, and 256 with 16).  Tiles of 512 entries, J up to 64, keep a wavefront's entries together, and so do the EDGE
+// instances: in step they measured 182 -> 171 us (stencil of 60 x 57 x 62, G = 8, J = 120), 176 -> 171 (100), 161 -> 165 (96),
+// 161 -> 162 (72), R-MAT of 2^18 rows 234 -> 221 (100), 184 -> 174 (96).
 __host__ __device__ constexpr bool in_step(bool edge, int ept) { return !edge && ept == 1; }
 constexpr int kX1LdsBytes = 10 * 1024;  // rows of X1 in LDS per 256 entries of a tile: 20 of 512 bytes
 __host__ __device__ constexpr int x1_pitch(int columns, bool edge, int ept)
