@@ -87,6 +87,17 @@ struct LdsArgs {
     bool dots;            // SDDMM: a job has all columns of its rows
 };
 
+// a / b of clocks, on the device by the reciprocal instruction (every workgroup works out the plan before it begins: 10.2 us
+// for panel_pointers_kernel on 300 rows with divisions and four layouts a lane, 7.8 with these and two).
+__host__ __device__ inline float lds_ratio(float a, float b)
+{
+#ifdef __HIP_DEVICE_COMPILE__
+    return a * __builtin_amdgcn_rcpf(b);
+#else
+    return a / b;
+#endif
+}
+
 // What all layouts of a list have in common.
 struct LdsShape {
     uint32_t tiles, quads, least;  // column tiles; teams' rows by fours; groups of rows at least
@@ -112,36 +123,36 @@ __host__ __device__ inline LdsShape lds_shape(const LdsList& list, const LdsArgs
 }
 
 // The choice between the windows in LDS and the kernels that gather through the L2 is made by the clocks that both are
-// expected to take: the three functions below, whose constants are fitted to the kernels' own times over 200 lists (8 % off in
-// the mean, 28 % at most).  A layout that the workspace has no room for takes for ever.
+// expected to take: the three functions below, whose constants are fitted to the kernels' own times over 350 lists (9 % off in
+// the mean, 28 % in the case of most).  A layout that the workspace has no room for takes for ever.
 // Measured, us for the whole call, LDS against gathers; one row in a hundred is long, columns at random:
-//       rows  mean long row   N = 64        N = 128        N = 160        N = 256        N = 384        N = 1,024
 //   SpMM
-//    500,000  11,000    768 / 1,052  1,021 / 1,728  1,700 / 2,449  1,618 / 2,538  2,569 / 4,692  6,590 / 10,392
-//    500,000   5,500    584 /   622    773 / 1,038  1,262 / 1,416  1,245 / 1,545  2,119 / 2,789  5,148 /  6,331
-//    500,000   2,750    499 /   431    672 /   728  1,090 /   918  1,110 / 1,045  1,907 / 1,869  4,492 /  4,398
-//    250,000   4,400    286 /   325    362 /   472    534 /   631    536 /   681    884 / 1,229  1,826 /  2,681
-//    120,000   8,250    232 /   302    302 /   442    424 /   514    396 /   537    563 / 1,010  1,166 /  2,316
-//    120,000   3,300    170 /   175    215 /   244    272 /   272    324 /   330    407 /   540    774 /  1,133
-//    120,000   1,320    124 /   109    159 /   157    218 /   175    240 /   196    352 /   352    644 /    720
-//     88,000   6,050    183 /   273    222 /   323    310 /   289    278 /   293    395 /   528    796 /  1,092
-//     60,000   4,125    156 /   257    183 /   210    232 /   230    276 /   293    342 /   466    539 /  1,037
-//     60,000   1,650     99 /   134    127 /   121    153 /   130    179 /   160    227 /   256    364 /    555
-//     30,000   2,060     92 /   214    104 /   199    126 /   131    146 /   148    166 /   220    266 /    451
-//   SDDMM     J = 64        J = 96         J = 128        J = 160        J = 256
-//    500,000  11,000    741 / 1,030  1,146 / 1,509  1,186 / 1,745  1,584 / 2,211  1,991 / 2,725
-//    500,000   5,500    593 /   635    902 /   941    940 / 1,094  1,224 / 1,320  1,545 / 1,668
-//    500,000   2,750    524 /   459    797 /   662    845 /   811  1,086 /   868  1,375 / 1,148
-//    250,000   4,400    234 /   294    313 /   407    347 /   463    449 /   572    584 /   714
-//    120,000   8,250    179 /   290    282 /   361    245 /   414    290 /   453    379 /   559
-//    120,000   3,300    183 /   227    239 /   260    227 /   292    262 /   301    318 /   354
-//    120,000   1,320     93 /   110    136 /   146    131 /   163    160 /   160    207 /   213
-//     88,000   6,050    131 /   192    168 /   250    175 /   291    220 /   253    269 /   308
-//     60,000   4,125    175 /   287    202 /   277    209 /   284    233 /   262    264 /   306
-//     60,000   1,650    102 /   151    118 /   153    124 /   158    141 /   143    165 /   166
-//     30,000   2,060    105 /   223    113 /   241    114 /   206    126 /   143    138 /   158
-// The rule takes the slower one where the two are close, at a loss of up to 8 % (SDDMM 88,000 x 6,050 at J = 208 and 256: 8
-// and 14 %); one row eight times as long as the others costs it up to 22 % (120,000 rows, N = 128).
+//       rows    mean  N = 64         N = 128        N = 160        N = 256        N = 384        N = 1,024
+//    500,000  11,000    773 / 1,054  1,020 / 1,733  1,699 / 2,421  1,622 / 2,528  2,566 / 4,645  6,573 / 10,272
+//    500,000   5,500    583 /   622    777 / 1,038  1,262 / 1,413  1,249 / 1,542  2,113 / 2,787  5,064 /  6,330
+//    500,000   2,750    499 /   432    670 /   732  1,087 /   918  1,103 / 1,042  1,907 / 1,872  4,511 /  4,375
+//    250,000   4,400    288 /   324    361 /   474    524 /   634    537 /   682    888 / 1,233  1,822 /  2,667
+//    120,000   8,250    230 /   304    301 /   447    418 /   514    398 /   541    561 / 1,010  1,170 /  2,315
+//    120,000   3,300    166 /   174    212 /   245    270 /   273    324 /   333    410 /   541    774 /  1,160
+//    120,000   1,320    123 /   110    161 /   158    218 /   176    240 /   198    356 /   351    644 /    732
+//     88,000   6,050    176 /   270    219 /   307    301 /   288    274 /   292    394 /   533    795 /  1,106
+//     60,000   4,125    153 /   256    178 /   208    237 /   229    277 /   292    337 /   464    538 /  1,033
+//     60,000   1,650     96 /   135    123 /   121    149 /   130    176 /   160    229 /   256    358 /    551
+//     30,000   2,062     89 /   208     99 /   195    126 /   130    136 /   146    162 /   219    266 /    448
+//   SDDMM           J = 64         J = 96         J = 128        J = 160        J = 256
+//    500,000  11,000    750 / 1,033  1,167 / 1,504  1,204 / 1,732  1,602 / 2,218  2,036 / 2,737
+//    500,000   5,500    594 /   636    901 /   935    942 / 1,099  1,225 / 1,329  1,581 / 1,675
+//    500,000   2,750    518 /   458    791 /   662    842 /   811  1,078 /   881  1,386 / 1,152
+//    250,000   4,400    232 /   298    318 /   409    354 /   467    453 /   573    590 /   713
+//    120,000   8,250    184 /   290    281 /   375    248 /   417    289 /   460    386 /   562
+//    120,000   3,300    183 /   228    222 /   263    225 /   291    258 /   302    314 /   349
+//    120,000   1,320     95 /   112    134 /   144    131 /   165    156 /   162    203 /   211
+//     88,000   6,050    138 /   182    165 /   238    172 /   278    215 /   253    274 /   309
+//     60,000   4,125    172 /   279    200 /   275    205 /   285    227 /   263    257 /   298
+//     60,000   1,650    103 /   148    116 /   150    119 /   154    138 /   145    154 /   159
+//     30,000   2,062    104 /   218    109 /   238    113 /   208    121 /   144    133 /   155
+// The rule takes the slower one where the two are within a few per cent; one row eight times as long as the others costs it
+// up to 28 % (120,000 rows, N = 128).
 __host__ __device__ inline float lds_cost(const LdsShape& s, const LdsList& list, const LdsArgs& args, int64_t K, int64_t N,
                                           uint32_t groups, uint32_t per_die)
 {
@@ -150,20 +161,26 @@ __host__ __device__ inline float lds_cost(const LdsShape& s, const LdsList& list
     if ((int64_t)(shares + 1) * list.count > args.ptr_room) return __builtin_inff();
     const uint32_t share_cols = ((uint32_t)K + shares - 1) / shares;
     const uint32_t windows = (share_cols + (uint32_t)s.window - 1) / (uint32_t)s.window;
-    const float in_window = s.per_col * (float)share_cols / (float)windows;  // entries of a row
+    const float in_window = lds_ratio(s.per_col * (float)share_cols, (float)windows);  // entries of a row
     const uint32_t rounds = ((args.dots ? 1 : s.tiles) * groups * per_die + args.workgroups - 1) / args.workgroups;
     const float tiles = (float)s.tiles, rows = (float)slots;
-    // Of a job: its windows on their way into LDS, a wavefront's passes over its slots, the sums added into C at the end.
-    // SDDMM passes once for every tile, and looking up and writing the entries is about half a pass more.
-    const float job = args.dots ? (float)windows * ((tiles + 0.45f) * (17600.0f + 815.0f * rows) + tiles * 106.0f * rows * in_window)
-                                : ((float)windows * (15800.0f + rows * (454.0f + 80.0f * in_window)) + 11000.0f * rows) *
-                                      (N % kLdsCols == 0 ? 0.97f : 1.14f);  // (a tile's rows of B begin amid cache lines)
+    // Of a job: its windows on their way into LDS (faster where B is small enough to meet in the L2s), a wavefront's passes
+    // over its slots, the sums added into C at the end.  SDDMM passes once for every tile, and looking up and writing the
+    // entries is about half a pass more.
+    const float tile = args.dots ? (tiles + 0.45f) * (14500.0f + 531.0f * rows) : 0.0f;
+    const float cols = lds_ratio((float)share_cols, (float)windows);  // of a window
+    float far = (float)K * (float)N * (1.0f / (8 << 20));             // B in 32 MiB, 1 at most
+    if (far > 1.0f) far = 1.0f;
+    const float job = args.dots ? (float)windows * (tile + tiles * (17.7f * cols + 97.5f * rows * in_window))
+                                : ((float)windows * (10700.0f + 4460.0f * far + rows * (124.0f + 359.0f * far + 74.5f * in_window)) +
+                                   9700.0f * rows) *
+                                      (N % kLdsCols == 0 ? 0.97f : 1.22f);  // (a tile's rows of B begin amid cache lines: 5 to 25 %)
     // what the longest row has in a window beyond the 32 entries that a slot takes at once, where its window is as narrow as
     // it gets: the fewer the rounds, the longer the others wait for it
-    const float share = (float)list.longest * (float)s.window / (float)K;
-    const float over = share > 32.0f && args.window == 0 ? (float)list.longest * (1.0f - 32.0f / share) * 32.0f / tiles : 0.0f;
+    const float share = lds_ratio((float)list.longest * (float)s.window, (float)K);
+    const float over = share > 32.0f && args.window == 0 ? lds_ratio((float)list.longest * (1.0f - lds_ratio(32.0f, share)) * 32.0f, tiles) : 0.0f;
     const float pointers = (args.dots ? 0.17f : 0.4f) * (float)list.count * (float)shares;
-    return (args.dots ? 20000.0f : 43000.0f) + (float)rounds * job + over + pointers;
+    return (args.dots ? 23500.0f : 60000.0f) + (float)rounds * job + over + pointers;
 }
 
 // Clocks of what the windows would not serve.  A few rows of it cost four times what their share of all entries would (the
@@ -181,7 +198,7 @@ __host__ __device__ inline float lds_cost(const LdsShape& s, const LdsList& list
 //           J = 256                       2,586 / 3,526   3,287 / 3,923  10,879 / 6,013
 __host__ __device__ inline float lds_apart_cost(const LdsShape& s, const LdsList& list, const LdsArgs& args)
 {
-    const float all = (float)list.apart / (float)(args.dies * args.workgroups) *
+    const float all = lds_ratio((float)list.apart, (float)(args.dies * args.workgroups)) *
                       (args.dots ? 280.0f + 460.0f * (float)s.tiles : 440.0f + 410.0f * (float)s.tiles);
     const float one = (float)list.worst * (args.dots ? 200.0f + 200.0f * (float)s.tiles : 600.0f);
     return all > one ? all : one;
@@ -198,23 +215,23 @@ __host__ __device__ inline float gather_cost(const LdsList& list, const LdsArgs&
         const float tiles = (float)((N + 255) / 256);
         const uint32_t owners = args.workgroups * kLdsWaves;
         const float rounds = (float)((list.count + owners - 1) / owners);
-        const float rows = rounds * entries / n;
+        const float rows = lds_ratio(rounds * entries, n);
         const float most = rows > (float)list.longest ? rows : (float)list.longest;
-        const float row = 270.0f + 0.28f * (float)N / tiles;  // of B
-        return tiles * (23000.0f + row * most * die_windows / windows + 1800.0f * rounds * windows / (float)args.dies);
+        const float row = 270.0f + lds_ratio(0.28f * (float)N, tiles);  // of B
+        return tiles * (23000.0f + lds_ratio(row * most * die_windows, windows) + lds_ratio(1800.0f * rounds * windows, (float)args.dies));
     }
     // wavefronts that claim pieces, sixteen to a workgroup: what the chip moves (columns filled up to 64 or 128), and what a
     // workgroup's pieces take one after the other
     const float columns = N <= 64 ? 64.0f : 128.0f;
-    const float bytes = entries * columns * 4.0f / (float)args.workgroups * die_windows / windows;
-    const float claims = n * die_windows / 16.0f / (7.0f * (float)args.workgroups);
-    const float piece = 4.0f * entries / (n * windows) * (claims > 1.0f ? claims : 1.0f);
+    const float bytes = lds_ratio(entries * columns * 4.0f * die_windows, (float)args.workgroups * windows);
+    const float claims = lds_ratio(n * die_windows, 112.0f * (float)args.workgroups);
+    const float piece = lds_ratio(4.0f * entries, n * windows) * (claims > 1.0f ? claims : 1.0f);
     const float pointers = (args.dots ? 0.17f : 0.4f) * n * windows;
     return args.dots ? 96000.0f + 0.0194f * bytes + piece * (70.0f + 60.6f * columns / 64.0f) + pointers
                      : 84000.0f + 0.0222f * bytes + piece * (38.5f + 52.3f * columns / 64.0f) + pointers;
 }
 
-constexpr uint32_t kLdsMore = 4, kLdsShares = kWave;  // layouts tried: the fewest groups of rows and up to three more, shares per die
+constexpr uint32_t kLdsMore = 4, kLdsShares = 32;  // layouts tried: the fewest groups of rows and up to three more, shares per die
 
 __host__ __device__ inline LdsPlan lds_layout(const LdsShape& s, const LdsList& list, const LdsArgs& args, int64_t K, int64_t N,
                                               uint32_t groups, uint32_t per_die, float cost)
@@ -233,19 +250,20 @@ __host__ __device__ inline LdsPlan lds_layout(const LdsShape& s, const LdsList& 
 }
 
 // How the list's rows are laid over the workgroups.  Their number is not known on the host: the workgroups of
-// panel_pointers_kernel each work it out (all lanes of a wavefront together, one number of shares each), one leaves it in the
-// header.
+// panel_pointers_kernel each work it out (all lanes of a wavefront together, two layouts each), one leaves it in the header.
 __device__ __forceinline__ LdsPlan lds_plan(const LdsList& list, const LdsArgs& args, int64_t K, int64_t N)
 {
     LdsPlan p;
     p.on = 0;
     if (list.count < args.min_rows) return p;
     const LdsShape s = lds_shape(list, args, K, N);
-    const uint32_t lane = threadIdx.x % kWave;
+    const uint32_t lane = threadIdx.x % kWave, shares = lane % kLdsShares;
     unsigned long long best = ~0ull;
-    for (uint32_t more = 0; more < kLdsMore; ++more) {
-        const float cost = lds_cost(s, list, args, K, N, s.least + more, lane + 1);
-        const unsigned long long key = (unsigned long long)__float_as_uint(cost) << 32 | more << 8 | lane;
+#pragma unroll
+    for (uint32_t half = 0; half < kLdsMore; half += kWave / kLdsShares) {
+        const uint32_t more = half + lane / kLdsShares;
+        const float cost = lds_cost(s, list, args, K, N, s.least + more, shares + 1);
+        const unsigned long long key = (unsigned long long)__float_as_uint(cost) << 32 | more << 8 | shares;
         if (key < best) best = key;
     }
 #pragma unroll

@@ -125,3 +125,44 @@ def test_lists_that_are_not_sorted():
     p = problem(9000, 1000, 128, 40, seed=3, shortest=30)
     spmm(p, 30, 154, "lds", max_long_rows=16384, points=[(1, "serial")])
     sddmm(problem(9000, 5000, 64, 40, seed=4, shortest=30), 30, 149, "lds", max_long_rows=16384)
+
+
+# captured once, replayed on columns in order and without: what the header of the workspace holds from the replay before
+# (among it the longest row and what windows in LDS would not serve) decides nothing
+@pytest.mark.parametrize("N,gathering", [(160, "owners"), (128, "claims")])
+def test_a_graph_replayed_on_other_columns(N, gathering):
+    p = problem(1300, 9000, N, 6000, seed=N)
+    order = p.colidx.copy(), p.vals.copy()
+    without_order(p, range(p.M))
+    orders = {"lds": order, gathering: (p.colidx, p.vals)}
+    C_ref, BND = full_reference(p)
+    X1 = wl.fill_values(np.random.default_rng(N), p.M * N, True).reshape(p.M, N)
+    X1d, dp = torch.from_numpy(X1).cuda(), DeviceProblem(p)
+    cfg = binding.make_config(1, "serial", "row_split", long_row_min=1500)
+    ws, C = dp.workspace_for(cfg), dp.new_output()
+    ws2 = torch.empty(binding.sgap_sddmm_csr_workspace_size(p.K, N), dtype=torch.uint8, device="cuda:0")
+    out = torch.empty(p.colidx.size, device="cuda:0")
+
+    def calls():
+        dp.launch_cfg(C, cfg, ws, stream=torch.cuda.current_stream())
+        binding.sgap_sddmm_csr_windows(p.M, p.K, N, dp.rowptr, dp.colidx, dp.vals, X1d, dp.B, out, 8, binding.STRATEGIES["parallel"],
+                                       1500, workspace=ws2, stream=torch.cuda.current_stream())
+
+    calls()  # eager, once per kernel
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        calls()
+    for wanted in ("lds", gathering, "lds", "lds", gathering):
+        colidx, vals = orders[wanted]
+        dp.colidx.copy_(torch.from_numpy(colidx))
+        dp.vals.copy_(torch.from_numpy(vals))
+        C.fill_(float("nan"))
+        out.fill_(float("nan"))
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert (form(ws), form(ws2)) == (wanted, wanted)
+        assert_close(C, C_ref, BND, exact=True, what=wanted)
+        ref, _ = oracle.sddmm_csr(p.M, p.K, N, p.rowptr, colidx, vals, X1, p.B, nthreads=8, bound=False)
+        assert np.array_equal(out.cpu().numpy().astype(np.float64), ref), wanted
