@@ -94,7 +94,9 @@ typedef enum {
  *       store.
  *     nnz-balanced schedule: lane = one stored entry ({<1 nnz, c col>, r},
  *       Section 6.2); the group performs a SEGMENTED reduction keyed by row
- *       (Fig. 1c), one writeback lane per run of equal rows.
+ *       (Fig. 1c), one writeback lane per run of equal rows.  At N <= 16 a
+ *       lane has four or eight consecutive entries and the group is the
+ *       wavefront: every group_size names the same launch.
  * SGAP_REDUCE_SERIAL: reduction parallelism 1.  Each lane walks group_size
  *   consecutive units by itself and flushes its register when the row changes
  *   ("conditional" reduction).

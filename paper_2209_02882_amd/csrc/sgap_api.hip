@@ -440,14 +440,17 @@ int spmm_impl(int64_t M, int64_t K, int64_t N, const int32_t* rowptr, const int3
         }
     } else {
         const int lc = pow2_ceil_capped(chunks, par ? 64 / group_size : 64);
-        const NnzPlan plan = par ? plan_nnz_parallel(group_size, lc, vec)
-                                 : plan_nnz_serial(group_size, lc, vec, nnz_hint, compute_units(), c.nnz_tile);
+        const bool narrow = par && N <= kNarrowColumns;
+        const NnzPlan plan = narrow ? plan_nnz_narrow(a)
+                             : par  ? plan_nnz_parallel(group_size, lc, vec)
+                                    : plan_nnz_serial(group_size, lc, vec, nnz_hint, compute_units(), c.nnz_tile);
         a.group = plan.share;
         a.log2_group = ilog2(plan.share);
         err = launch_nnz_zero_rows(a, vec, plan.merge_log2, s);
         if (err == hipSuccess)
-            err = par ? launch_nnz_parallel(a, lc, vec, compute_units(), nnz_hint, s)
-                      : launch_nnz_serial(a, lc, vec, plan, compute_units(), nnz_hint, s);
+            err = narrow ? launch_nnz_narrow(a, compute_units(), nnz_hint, s)
+                  : par  ? launch_nnz_parallel(a, lc, vec, plan, compute_units(), nnz_hint, s)
+                         : launch_nnz_serial(a, lc, vec, plan, compute_units(), nnz_hint, s);
     }
     if (ev0) {
         mark(ev1);

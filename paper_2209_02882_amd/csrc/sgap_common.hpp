@@ -12,6 +12,10 @@ namespace sgap {
 constexpr int kWave = 64;          // wavefront size on gfx950
 constexpr int kBlock = 256;        // threads per workgroup (4 waves)
 constexpr int kWavesPerBlock = kBlock / kWave;
+// Up to so many columns the nnz-balanced schedule's parallel strategy is sgap_nnz_narrow.hip.  Beyond, where a row of B takes
+// more than four lanes, the entries of a lane have not been measured.  R-MAT with 2^21 rows, N = 16, G = 16: 1,112 us with an
+// entry per lane, 614 with eight.
+constexpr int kNarrowColumns = 16;
 
 struct SpmmArgs {
     int64_t M, K, N;
@@ -230,6 +234,7 @@ struct NnzPlan {
 };
 NnzPlan plan_nnz_serial(int group, int lc, int vec, int64_t nnz_hint, int compute_units, int forced_tile);
 NnzPlan plan_nnz_parallel(int group, int lc, int vec);
+NnzPlan plan_nnz_narrow(const SpmmArgs& a);  // parallel, N <= kNarrowColumns
 // g = lanes per row of a whole-group reduction (1: no rows are shared), passes = passes of a group over its columns,
 // resident = workgroups that fit the chip at once for a persistent launch (0: a workgroup per item).
 RowSplitGrid plan_row_split_grid(int g, int passes, int64_t M, int64_t items, int xcds, int compute_units,
@@ -271,7 +276,10 @@ hipError_t launch_wave_rows(const SpmmArgs& a, int vec, int rows_per_wave, int x
 // 2^merge_log2 positions, and the rows without entries; merge_log2 = -1: all rows
 hipError_t launch_nnz_zero_rows(const SpmmArgs& a, int vec, int merge_log2, hipStream_t s);
 // compute_units sizes the persistent grid; nnz_hint (-1 = unknown) caps it.
-hipError_t launch_nnz_parallel(const SpmmArgs& a, int lc, int vec, int compute_units, int64_t nnz_hint, hipStream_t s);
+hipError_t launch_nnz_parallel(const SpmmArgs& a, int lc, int vec, const NnzPlan& plan, int compute_units,
+                               int64_t nnz_hint, hipStream_t s);
+// the same for N <= kNarrowColumns (sgap_nnz_narrow.hip)
+hipError_t launch_nnz_narrow(const SpmmArgs& a, int compute_units, int64_t nnz_hint, hipStream_t s);
 hipError_t launch_nnz_serial(const SpmmArgs& a, int lc, int vec, const NnzPlan& plan, int compute_units,
                              int64_t nnz_hint, hipStream_t s);
 // r = members per reducing sub-group (r = g: the whole group)

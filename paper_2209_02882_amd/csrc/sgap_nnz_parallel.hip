@@ -77,9 +77,9 @@ hipError_t launch_nnz_parallel_g2(const SpmmArgs&, int, int, int, int64_t, bool,
 hipError_t launch_nnz_parallel_g4_16(const SpmmArgs&, int, int, int, int64_t, bool, hipStream_t);
 hipError_t launch_nnz_parallel_g8_32_64(const SpmmArgs&, int, int, int, int64_t, bool, hipStream_t);
 
-hipError_t launch_nnz_parallel(const SpmmArgs& a, int lc, int vec, int compute_units, int64_t nnz_hint, hipStream_t s)
+hipError_t launch_nnz_parallel(const SpmmArgs& a, int lc, int vec, const NnzPlan& plan, int compute_units,
+                               int64_t nnz_hint, hipStream_t s)
 {
-    const NnzPlan plan = plan_nnz_parallel(a.group, lc, vec);
     lc = plan.lc;
     switch (a.group) {
         case 1: return launch_nnz_parallel_g1(a, lc, vec, compute_units, nnz_hint, plan.merge, s);

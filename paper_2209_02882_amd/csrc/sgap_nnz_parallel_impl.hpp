@@ -6,6 +6,8 @@
 // row of a position is found by searching rowptr, as in the paper's Listings 1
 // and 2, but only inside the tile's window of rows, which is kept in LDS.
 //
+// Rows of up to kNarrowColumns columns go to sgap_nnz_narrow.hip instead.
+//
 // This header holds the kernel templates and the per-group launcher; it is
 // included by the sgap_nnz_parallel_g*.hip translation units, each of which
 // instantiates the kernels of a few group sizes (the instances are split over
@@ -39,7 +41,7 @@ constexpr int kParWpt = kWindowCap / kBlock + 1;
 typedef int32_t native_i4 __attribute__((ext_vector_type(4), aligned(4)));
 // LDS merge through the hardware's fp32 atomic: the run heads of one row meet on
 // one address within a wavefront (measured against the compare-and-swap loop:
-// rmat N=4 G=16 0.47 vs 0.62 ms, powerlaw 0.135 vs 0.162 ms)
+// powerlaw 0.135 vs 0.162 ms)
 constexpr bool kParMergeCas = false;
 constexpr int kParDepth = 4;                   // steps issued together
 
@@ -295,7 +297,8 @@ struct Launch {
     template <int G, int LC, int VEC>
     void operator()() const
     {
-        if (off32) {
+        if constexpr (VEC != 4) return;  // N <= kNarrowColumns: sgap_nnz_narrow.hip
+        else if (off32) {
             if (merge) pick_columns<G, LC, VEC, true, true>(); else pick_columns<G, LC, VEC, true, false>();
         } else {
             if (merge) pick_columns<G, LC, VEC, false, true>(); else pick_columns<G, LC, VEC, false, false>();
