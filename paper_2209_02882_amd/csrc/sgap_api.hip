@@ -420,6 +420,9 @@ int spmm_impl(int64_t M, int64_t K, int64_t N, const int32_t* rowptr, const int3
         const bool wave_wanted = c.wave_rows == 1 ? N >= 48 : c.wave_rows == 0 && windows && N >= 192;
         const int wave_vec = wave_wanted && !par && reduce_size == 0 ? (N > 128 ? avec : N > 64 ? (avec < 2 ? avec : 2) : 1) : 0;
         const int wave_rows_count = group_size > 63 ? 63 : group_size;
+        // Neighbouring rows together, where the caller leaves the layout to the library and says how many entries there are.
+        const bool quads = !par && group_size <= 4 && vec == 4 && c.block_size == 0 && c.persistent == 0 && nnz_hint > 0 &&
+                           row_quads_apply(a, lc, avg_row, cus);
         if (reduce_size != 0) {
             // every row receives atomic adds
             err = launch_nnz_zero_rows(a, vec, -1, s);
@@ -432,6 +435,8 @@ int spmm_impl(int64_t M, int64_t K, int64_t N, const int32_t* rowptr, const int3
                                           window_bytes_of(c), c.window_kb > 0, workspace, long_rows_of(c), s);
         } else if (wave_vec > 0) {
             err = launch_wave_rows(a, wave_vec, wave_rows_count, xcds, nullptr, s);
+        } else if (quads) {
+            err = launch_row_quads(a, lc, (int)tile_cols, xcds, s);
         } else {
             // the parallel strategy interleaves its groups' rows; the serial strategy's lanes
             // own consecutive rows by definition

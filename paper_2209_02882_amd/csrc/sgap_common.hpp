@@ -252,6 +252,10 @@ hipError_t launch_row_split(const SpmmArgs& a, int g, int lc, int vec, int rows_
                             int tile_cols, int xcds, int compute_units, bool persistent, int block, int64_t nnz_hint,
                             double mean_row,
                             hipStream_t s);
+// serial strategy, four consecutive rows together (sgap_row_quads.hip); vec must be 4.  row_quads_apply: whether that is
+// the kernel for so many rows of mean_row stored entries
+bool row_quads_apply(const SpmmArgs& a, int lc, double mean_row, int compute_units);
+hipError_t launch_row_quads(const SpmmArgs& a, int lc, int tile_cols, int xcds, hipStream_t s);
 // the same with g lanes per row reducing in sub-groups of r < g lanes whose sums
 // are merged with atomics; C must have been zeroed (launch_nnz_zero_rows, -1)
 hipError_t launch_row_split_partial(const SpmmArgs& a, int g, int r, int lc, int vec, int rows_per_slot,

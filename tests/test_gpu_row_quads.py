@@ -1,0 +1,107 @@
+"""Row-split, serial strategy, four neighbouring rows together: rows, sharing and orders at which a quad is listed or goes row by
+row, widths at the edges of lanes and column tiles, planes dealt over the dies; exact on integer-valued inputs."""
+import functools
+
+import numpy as np
+import pytest
+
+import oracle
+from paper_2209_02882_amd import binding
+from paper_2209_02882_amd import workloads as wl
+
+from gpu_util import DeviceProblem
+
+pytestmark = pytest.mark.gpu
+ROWS = 82_003  # enough blocks of 64 rows on 256 compute units, and no multiple of four
+
+
+@functools.lru_cache
+def csr(kind):
+    """The rows of that kind, repeated with a period of 400 rows and shifted along."""
+    period = [rows_of(kind)(r) for r in range(400)]
+    columns = [period[r % 400] + 40 * (r // 400) for r in range(ROWS)]
+    rowptr = np.concatenate([[0], np.cumsum([c.size for c in columns])]).astype(np.int32)
+    return rowptr, np.concatenate(columns).astype(np.int32)
+
+
+def rows_of(kind):
+    rng = np.random.default_rng(7)
+    band = lambda r, n: r + np.arange(n)  # noqa: E731
+    some = [np.sort(rng.choice(900, n, replace=False)) for n in rng.integers(0, 41, 400)]
+    if kind == "band":
+        return lambda r: band(r, 20)
+    if kind == "31, 32 and 33 entries":
+        return lambda r: band(r, 31 + r // 8 % 3)
+    if kind == "as many records as there is room for, and one more":
+        return lambda r: np.sort(np.concatenate([np.arange(20 - r // 4 % 3), 900 + 11 * (r % 4) + np.arange(11 + r // 4 % 3)]))
+    if kind == "in the row before the last":  # columns that come and go
+        return lambda r: np.concatenate([band(r, 14), 600 + 30 * (r % 2) + np.arange(6)])
+    if kind == "descending and repeated":
+        return lambda r: band(r, 20)[::-1] if r % 8 < 4 and r % 3 == 0 else np.sort(np.concatenate([band(r, 16), band(r, 3)])) if r % 16 > 12 else band(r, 18)
+    if kind == "with empty rows":
+        return lambda r: band(r, 28 if r % 5 else 0) if r % 40 > 3 else band(0, 0)
+    return lambda r: some[r]  # without order
+
+
+KINDS = ["band", "31, 32 and 33 entries", "as many records as there is room for, and one more", "in the row before the last",
+         "descending and repeated", "with empty rows", "without order"]
+
+
+def check(p, points, **knobs):
+    ref, _ = oracle.spmm_csr(p.M, p.K, p.N, p.rowptr, p.colidx, p.vals, p.B, nthreads=8, bound=False)
+    dp = DeviceProblem(p)
+    for g in points:
+        cfg = binding.make_config(g, "serial", "row_split", **knobs)
+        assert np.array_equal(dp.run_cfg(cfg).cpu().numpy().astype(np.float64), ref), (g, knobs)
+
+
+@pytest.mark.parametrize("kind", KINDS)
+@pytest.mark.parametrize("N", [61, 64, 66, 130, 260])
+def test_rows_at_the_edges(N, kind):
+    rowptr, colidx = csr(kind)
+    rng, K = np.random.default_rng(N), int(colidx.max()) + 1
+    p = wl.SpmmProblem("quads", ROWS, K, N, rowptr, colidx, wl.fill_values(rng, colidx.size, True),
+                       wl.fill_values(rng, K * N, True).reshape(K, N))
+    check(p, (1, 4))
+    if N == 260:
+        check(p, (2,), tile_cols=256)  # 64 lanes to a row
+    if kind == "band":
+        check(p, (1,), xcd_remap=0)
+
+
+@pytest.mark.parametrize("N", [64, 100, 132])
+def test_planes_dealt_over_the_dies(N):
+    nx, ny, nz = 61, 103, 19  # reach 6,345 rows, the last planes are left over
+    x, y, z = (v.ravel() for v in np.meshgrid(np.arange(nx), np.arange(ny), np.arange(nz), indexing="ij"))
+    order = np.lexsort((x, y, z))
+    x, y, z = x[order], y[order], z[order]
+    columns, inside = [], []
+    for dz in (-1, 0, 1):
+        for dy in (-1, 0, 1):
+            for dx in (-1, 0, 1):
+                inside.append((x + dx >= 0) & (x + dx < nx) & (y + dy >= 0) & (y + dy < ny) & (z + dz >= 0) & (z + dz < nz))
+                columns.append(x + dx + nx * (y + dy + ny * (z + dz)))
+    inside, columns = np.stack(inside, 1), np.stack(columns, 1)
+    M = nx * ny * nz
+    rowptr = np.concatenate([[0], np.cumsum(inside.sum(1))]).astype(np.int32)
+    colidx = columns[inside].astype(np.int32)
+    rng = np.random.default_rng(N)
+    p = wl.SpmmProblem("planes", M, M, N, rowptr, colidx, wl.fill_values(rng, colidx.size, True),
+                       wl.fill_values(rng, M * N, True).reshape(M, N))
+    check(p, (1,))
+
+
+def test_what_is_not_finite_stays_in_its_rows():
+    N = 64
+    rowptr, colidx = csr("band")
+    rng, K = np.random.default_rng(3), int(colidx.max()) + 1
+    vals, B = wl.fill_values(rng, colidx.size, True), wl.fill_values(rng, K * N, True).reshape(K, N)
+    vals[vals == 0] = 1
+    B[70, 5], B[300, 60] = np.inf, np.nan
+    p = wl.SpmmProblem("quads", ROWS, K, N, rowptr, colidx, vals, B)
+    got = DeviceProblem(p).run_cfg(binding.make_config(1, "serial", "row_split")).cpu().numpy()
+    has = lambda c: np.add.reduceat(colidx == c, rowptr[:-1]) > 0  # noqa: E731
+    assert np.isinf(got[has(70), 5]).all() and np.isnan(got[has(300), 60]).all()
+    rest = np.ones(got.shape, bool)
+    rest[has(70), 5] = rest[has(300), 60] = False
+    assert np.isfinite(got[rest]).all()
