@@ -23,21 +23,18 @@
 // does not ascend, or too little to share.  Nothing is assumed of the matrix.
 #include "sgap_common.hpp"
 #include "sgap_gather.hpp"
+#include "sgap_quads.hpp"
 
 namespace sgap {
 
 namespace {
 
-constexpr int kQuad = 4;
-constexpr int kQuadRow = 32;      // rows of fewer entries are listed: there is kNoColumn behind every one
 constexpr int kQuadRecords = 64;  // records of a quad at most (27-point stencil: 54)
 constexpr int kQuadPlaces = 80;   // those, +0 up to a whole batch behind them, and in the last place what belongs to none
 constexpr int kQuadChunk = 160;   // entries staged at a time where rows go one by one
 constexpr int kQuadDepth = 6;     // rows of B in flight per lane
 constexpr int kPlainDepth = 8;    // the same where rows go one by one
 static_assert(kQuadRecords + kQuadDepth < kQuadPlaces, "a batch of +0 behind the records");
-constexpr int64_t kDealBytes = 4 << 20;  // an L2
-constexpr int32_t kNoColumn = 0x7fffffff;
 
 struct alignas(16) QuadLds {
     union {
@@ -50,58 +47,7 @@ struct alignas(16) QuadLds {
     int32_t row_col[kQuad][1 + kQuadRow];  // the rows' columns from place 1 on, kNoColumn behind them
 };
 
-// LDS is written and read by the lanes of one wavefront only, whose LDS instructions are carried out in order: what is
-// needed is that the compiler keeps them in order.
-__device__ __forceinline__ void wave_lds_order()
-{
-    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-}
-
 __device__ __forceinline__ bool finite(float x) { return (__float_as_uint(x) & 0x7f800000u) != 0x7f800000u; }
-
-// How many of a row's columns (ascending, kNoColumn behind them) are below c
-__device__ __forceinline__ int below(const int32_t* __restrict__ row, int32_t c)
-{
-    int lo = 0;
-#pragma unroll
-    for (int half = kQuadRow / 2; half > 0; half /= 2) lo += row[lo + half - 1] < c ? half : 0;
-    return lo;
-}
-
-// A row of a three-dimensional grid in its natural order wants three stretches of B a plane apart, and planes that no L2 holds come from memory three times
-// where a die goes through one run of rows.  There the planes are better dealt out: each die takes an eighth of every
-// plane, the same one, and finds the rows of B that the plane below has brought.  How far apart the planes are is read off
-// a row in the middle: half the distance of its outer columns.  It decides nothing but the order of the work.
-// Returns a die's rows of a plane, or 0: three planes of rows of B (b_row_bytes each) fit an L2, or the matrix has
-// fewer than eight.
-__device__ __forceinline__ uint32_t plane_share(const SpmmArgs& a, uint32_t dies, uint32_t b_row_bytes)
-{
-    const int32_t begin = a.rowptr[a.M / 2], end = a.rowptr[a.M / 2 + 1];
-    if (dies < 2 || end <= begin) return 0;
-    const int32_t first = a.colidx[begin], last = a.colidx[end - 1];
-    if (last <= first) return 0;
-    const uint32_t reach = (uint32_t)(last - first) / 2;
-    if ((int64_t)reach * 8 > a.M || (int64_t)reach * 3 * b_row_bytes <= kDealBytes) return 0;
-    return reach / dies;
-}
-
-// Which block of rows a die takes in its turn: those of one contiguous run for each die, or of its share of every plane.
-__device__ __forceinline__ uint32_t die_block(const SpmmArgs& a, uint32_t die, uint32_t turn, uint32_t blocks, uint32_t dies,
-                                              uint32_t block_rows, uint32_t b_row_bytes)
-{
-    const uint32_t per_die = (blocks + dies - 1) / dies;
-    const uint32_t share = (plane_share(a, dies, b_row_bytes) + block_rows / 2) / block_rows;
-    if (share < 2) return die * per_die + turn;
-    const uint32_t rounds = blocks / (share * dies);
-    const uint32_t round = turn / share;
-    if (round < rounds) return (round * dies + die) * share + turn % share;
-    const uint32_t rest = blocks - rounds * share * dies;  // dealt evenly: every die has per_die turns, or one without a block
-    const uint32_t each = (rest + dies - 1) / dies, at = turn - rounds * share;
-    return at < each ? rounds * share * dies + die * each + at : blocks;
-}
-
-typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 // U records from number q on: all U rows of B are requested before the first is consumed.  acc[j][i] is row i's sum in this
 // lane's column j: v_mfma_f32_4x4x1 multiplies, for every four lanes by themselves, the four rows' values (one per lane)
@@ -154,7 +100,8 @@ __global__ __launch_bounds__(kBlock) void row_quads_kernel(SpmmArgs a, TileSched
     const uint32_t per_die = (row_blocks + ts.xcds - 1) / ts.xcds;
     const uint32_t die = blockIdx.x % ts.xcds, turn = blockIdx.x / ts.xcds;
     const uint32_t col_tile = turn / per_die;
-    const uint32_t block = die_block(a, die, turn % per_die, row_blocks, ts.xcds, SLOTS * kQuad, LC * 16);
+    const uint32_t share = (plane_share(a, ts.xcds, LC * 16) + SLOTS * kQuad / 2) / (SLOTS * kQuad);
+    const uint32_t block = die_block(share, die, turn % per_die, row_blocks, ts.xcds);
     if (block >= row_blocks) return;  // the whole workgroup
     const int64_t row_first = ((int64_t)block * SLOTS + slot) * kQuad;
 

@@ -19,12 +19,13 @@
 // for the tile's first entry and an LDS window of rowptr for the rest (the
 // same pieces as the nnz-balanced SpMM kernels).  sddmm_tile_kernel has the
 // parallel strategy wherever four steps of its lanes cover a dense row,
-// sddmm_kernel has the rest.
+// sddmm_kernel has the rest.  Matrices whose neighbouring rows share columns go by four rows together, in the same launch.
 #include <type_traits>
 
 #include "sgap_common.hpp"
 #include "sgap_lane_ops.hpp"
 #include "sgap_nnz_common.hpp"
+#include "sgap_sddmm_quads.hpp"
 
 namespace sgap {
 
@@ -249,8 +250,17 @@ __host__ __device__ constexpr int x1_pitch(int columns, bool edge, int ept)
     return in_step(edge, ept) && columns % 64 == 0 ? columns + 32 : columns;
 }
 
+// quads: where rows turn out to share columns, the matrix is taken by four rows together (sgap_sddmm_quads.hpp), by all
+// workgroups of the grid; else by the first `workers` of them, tile by tile, as above.  resident: workgroups of a die at a time.
+// From 65 columns on: of 64, a 60 x 57 x 62 stencil takes 86 us tile by tile and 94 so.
+__host__ __device__ constexpr bool has_quads(int g, int s) { return s * g == 32 || s * g == 64; }  // 65 to 256 columns
+// Stored entries from which on a matrix is looked at for such rows: the look takes 2 us where it finds none.  40 x 41 x 42
+// points, 1.8 M entries: J = 100 59.9 -> 49.7 us, J = 72 55.2 -> 49.0, J = 256 141 -> 82, but J = 128, which the tiles have in
+// step, 55.0 -> 51.4 in groups of 8 and 59.4 -> 62.6 of 16; 60 x 57 x 62, 5.4 M, J = 128: 127 -> 121 and 134 -> 126; 31 x 30 x 33
+// points, 0.8 M: J = 100 35.6 -> 32.6, J = 128 27.2 -> 28.6.
+constexpr int64_t quads_from(bool step128) { return step128 ? 3000000 : 1500000; }
 template <int G, int S, bool EDGE, int EPT>
-__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) void sddmm_tile_kernel(SddmmArgs s, int x1_rows)
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(in_step(EDGE, EPT) ? 6 : 4))) void sddmm_tile_kernel(SddmmArgs s, int x1_rows, uint32_t workers, uint32_t resident, bool quads)
 {
     constexpr int VEC = 4;
     constexpr bool IN_STEP = in_step(EDGE, EPT);
@@ -286,9 +296,27 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
     const uint32_t row_bytes = (uint32_t)J * 4u;
     const int32_t M = (int32_t)a.M;
     const int32_t nnz = a.rowptr[a.M];
+    bool by_quads = false;
+    if constexpr (has_quads(G, S)) {
+        by_quads = quads && rows_share_columns(a, nnz, s_tile_row);
+        if (by_quads)
+            sddmm_quads(a, s.X1, s.out, DotColumns<S * G / 4, EDGE>(J), reinterpret_cast<QuadDots*>(s_x1)[wave], TILE, resident);
+    }
+    if (blockIdx.x >= workers) return;
     const int64_t tiles = ((int64_t)nnz + TILE - 1) / TILE;
-    const TileDeal deal(tiles, blockIdx.x, gridDim.x);
+    const TileDeal deal(tiles, blockIdx.x, workers);
     const int64_t my_tiles = deal.mine;
+    if constexpr (has_quads(G, S)) {
+        if (by_quads) {
+            for (int64_t j0 = 0; j0 < my_tiles; j0 += kTileRowBatch) {
+                find_tile_rows(a, deal, j0, TILE, s_tile_row);
+                const bool have = j0 + tid < my_tiles;
+                const int32_t tile_start = have ? (int32_t)(deal.tile(j0 + tid) * TILE) : 0;
+                tiles_of_long_quads(a, s.X1, s.out, DotColumns<S * G / 4, EDGE>(J), have, have ? s_tile_row[tid] : 0, tile_start, TILE);
+            }
+            return;
+        }
+    }
     if (my_tiles == 0) return;
     TileWalk ahead(deal);  // the tile that is fetched next
 
@@ -529,8 +557,17 @@ void launch_tile(const SddmmArgs& s, int compute_units, int64_t nnz_hint, hipStr
     constexpr int x1_rows = EPT * kX1LdsBytes / (S * G * 16);
     constexpr int x1_bytes = x1_rows * x1_pitch(S * G * 4, EDGE, EPT) * 4;
     static const int per_cu = resident_per_cu(sddmm_tile_kernel<G, S, EDGE, EPT>, x1_bytes);
-    const int grid = persistent_grid(per_cu, compute_units, nnz_hint, EPT * kBlock);
-    hipLaunchKernelGGL((sddmm_tile_kernel<G, S, EDGE, EPT>), dim3(grid), dim3(kBlock), x1_bytes, stream, s, x1_rows);
+    const uint32_t workers = (uint32_t)persistent_grid(per_cu, compute_units, nnz_hint, EPT * kBlock);
+    static_assert(!has_quads(G, S) || x1_bytes >= (int)sizeof(QuadDots) * kWavesPerBlock, "either is in the same place");
+    const uint32_t all = (uint32_t)(per_cu * compute_units), resident = all >= kQuadDies ? all / kQuadDies : 1;
+    bool quads = false;
+    if constexpr (has_quads(G, S)) {
+        const SpmmArgs& a = s.a;
+        quads = a.M > 1 && a.N > S * G * 2 && a.K * a.N * 4 <= 0xffffffffLL && nnz_hint >= quads_from(in_step(EDGE, EPT) && S * G == 32) &&
+                nnz_hint > kQuadMeanRow * a.M && nnz_hint < kQuadRow * a.M;
+    }
+    const uint32_t grid = quads && quad_workgroups(s.a.M, resident) > workers ? quad_workgroups(s.a.M, resident) : workers;
+    hipLaunchKernelGGL((sddmm_tile_kernel<G, S, EDGE, EPT>), dim3(grid), dim3(kBlock), x1_bytes, stream, s, x1_rows, workers, resident, quads);
 }
 
 // Steps of G*4 columns that cover J: 1, 2 or 4 pick sddmm_tile_kernel, 0 = more than 4.
