@@ -100,7 +100,7 @@ __global__ __launch_bounds__(kBlock) void row_quads_kernel(SpmmArgs a, TileSched
     const uint32_t per_die = (row_blocks + ts.xcds - 1) / ts.xcds;
     const uint32_t die = blockIdx.x % ts.xcds, turn = blockIdx.x / ts.xcds;
     const uint32_t col_tile = turn / per_die;
-    const uint32_t share = (plane_share(a, ts.xcds, LC * 16) + SLOTS * kQuad / 2) / (SLOTS * kQuad);
+    const uint32_t share = (plane_share(a, ts.xcds, (uint32_t)(a.N < ts.tile_cols ? a.N : ts.tile_cols) * 4u) + SLOTS * kQuad / 2) / (SLOTS * kQuad);
     const uint32_t block = die_block(share, die, turn % per_die, row_blocks, ts.xcds);
     if (block >= row_blocks) return;  // the whole workgroup
     const int64_t row_first = ((int64_t)block * SLOTS + slot) * kQuad;
@@ -150,15 +150,25 @@ __global__ __launch_bounds__(kBlock) void row_quads_kernel(SpmmArgs a, TileSched
                 if (q == 0) lds.row_col[i][0] = -1;
             }
         wave_lds_order();
-        // columns without order, told by the second row: nothing is listed (300,000 rows of 27 entries, N = 64: 299 us where
-        // they were, 294 so, 287 by the plain kernel; N = 128: 605, 587 and 593)
-        int seen = 0;
+        // columns without order, told by the second row and the first, or else (where a line of the grid ends between them) by
+        // the fourth and the third: nothing is listed (300,000 rows of 27 entries, N = 64: 299 us where they were, 294 so, 287
+        // by the plain kernel; N = 128: 605, 587 and 593; the second look: 75 x 75 x 30 points, N = 36 56.9 -> 49.1, by the plain
+        // kernel 49.6; 99 x 97 x 31, N = 56 88.9 -> 81.1, by that 88.9)
+        auto shares = [&](const int32_t* __restrict__ above, const int32_t (&row)[EPL], int32_t entries) {
+            int seen = 0;
 #pragma unroll
-        for (int u = 0; u < EPL; ++u) {
-            const int lo = below(lds.row_col[0] + 1, col[1][u]);
-            seen += __popc((uint32_t)slot_ballot(col[1][u] != kNoColumn && lds.row_col[0][1 + lo] == col[1][u]));
+            for (int u = 0; u < EPL; ++u) {
+                const int lo = below(above + 1, row[u]);
+                seen += __popc((uint32_t)slot_ballot(row[u] != kNoColumn && above[1 + lo] == row[u]));
+            }
+            return 4 * seen >= entries;
+        };
+        bool some_shared = shares(lds.row_col[0], col[1], p[2] - p[1]);
+        if (__ballot(listed && !some_shared) != 0) {
+            const bool others = shares(lds.row_col[2], col[3], p[4] - p[3]);
+            some_shared = some_shared || others;
         }
-        listed = listed && 4 * seen >= p[2] - p[1];
+        listed = listed && some_shared;
         if (__ballot(listed) != 0) {
             // (an empty place counts as a record of the quad's first column and of no row)
             int32_t some = kNoColumn;

@@ -38,13 +38,16 @@ def rows_of(kind):
         return lambda r: np.concatenate([band(r, 14), 600 + 30 * (r % 2) + np.arange(6)])
     if kind == "descending and repeated":
         return lambda r: band(r, 20)[::-1] if r % 8 < 4 and r % 3 == 0 else np.sort(np.concatenate([band(r, 16), band(r, 3)])) if r % 16 > 12 else band(r, 18)
+    if kind == "no column in common within the first two, or the last two":
+        return lambda r: np.concatenate([band(r, 18) + 500 * (r % 4 > (0, 2)[r // 4 % 2])])
     if kind == "with empty rows":
         return lambda r: band(r, 28 if r % 5 else 0) if r % 40 > 3 else band(0, 0)
     return lambda r: some[r]  # without order
 
 
 KINDS = ["band", "31, 32 and 33 entries", "as many records as there is room for, and one more", "in the row before the last",
-         "descending and repeated", "with empty rows", "without order"]
+         "descending and repeated",
+         "no column in common within the first two, or the last two", "with empty rows", "without order"]
 
 
 def check(p, points, **knobs):
@@ -69,7 +72,7 @@ def test_rows_at_the_edges(N, kind):
         check(p, (1,), xcd_remap=0)
 
 
-@pytest.mark.parametrize("N", [64, 100, 132])
+@pytest.mark.parametrize("N", [40, 64, 100, 132])  # 40: the rows as they are decide, not the lanes they take
 def test_planes_dealt_over_the_dies(N):
     nx, ny, nz = 61, 103, 19  # reach 6,345 rows, the last planes are left over
     x, y, z = (v.ravel() for v in np.meshgrid(np.arange(nx), np.arange(ny), np.arange(nz), indexing="ij"))
