@@ -422,7 +422,7 @@ int spmm_impl(int64_t M, int64_t K, int64_t N, const int32_t* rowptr, const int3
         const int wave_rows_count = group_size > 63 ? 63 : group_size;
         // Neighbouring rows together, where the caller leaves the layout to the library and says how many entries there are.
         const bool quads = !par && group_size <= 4 && vec == 4 && c.block_size == 0 && c.persistent == 0 && nnz_hint > 0 &&
-                           row_quads_apply(a, lc, avg_row, cus);
+                           row_quads_apply(a, lc, tile_cols, avg_row, cus);
         if (reduce_size != 0) {
             // every row receives atomic adds
             err = launch_nnz_zero_rows(a, vec, -1, s);

@@ -253,8 +253,8 @@ hipError_t launch_row_split(const SpmmArgs& a, int g, int lc, int vec, int rows_
                             double mean_row,
                             hipStream_t s);
 // serial strategy, four consecutive rows together (sgap_row_quads.hip); vec must be 4.  row_quads_apply: whether that is
-// the kernel for so many rows of mean_row stored entries
-bool row_quads_apply(const SpmmArgs& a, int lc, double mean_row, int compute_units);
+// the kernel for so many rows of mean_row stored entries and lc lanes per column tile
+bool row_quads_apply(const SpmmArgs& a, int lc, int64_t tile_cols, double mean_row, int compute_units);
 hipError_t launch_row_quads(const SpmmArgs& a, int lc, int tile_cols, int xcds, hipStream_t s);
 // the same with g lanes per row reducing in sub-groups of r < g lanes whose sums
 // are merged with atomics; C must have been zeroed (launch_nnz_zero_rows, -1)

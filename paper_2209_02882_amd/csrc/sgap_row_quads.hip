@@ -299,8 +299,10 @@ __global__ __launch_bounds__(kBlock) void row_quads_kernel(SpmmArgs a, TileSched
 // by the plain kernel, 213 so).  Enough blocks of rows for the chip, since a quad's rows are one after the other then: 312
 // blocks of 64 rows of 20 entries without order take 17 us and 12 by the plain kernel, 938 of 16 entries 31.1 and 30.9;
 // stencils gain from 844 blocks of 32 rows on (N = 128: 17.3 -> 14.2 us) and from 938 of 64 (19.1 -> 18.2).
-bool row_quads_apply(const SpmmArgs& a, int lc, double mean_row, int compute_units)
+// A column tile has to fit one pass of its lanes: the kernel makes no second one (row_split_kernel does).
+bool row_quads_apply(const SpmmArgs& a, int lc, int64_t tile_cols, double mean_row, int compute_units)
 {
+    if (tile_cols > (int64_t)lc * 4) return false;
     const int64_t blocks = a.M / ((int64_t)(kBlock / lc) * kQuad);
     return lc >= 16 && mean_row > 12.0 && mean_row <= (double)kQuadRow && blocks >= (int64_t)(lc >= 32 ? 3 : 5) * compute_units;
 }
@@ -308,6 +310,7 @@ bool row_quads_apply(const SpmmArgs& a, int lc, double mean_row, int compute_uni
 // lc = chunk lanes that hold a column tile in one pass (16, 32 or 64)
 hipError_t launch_row_quads(const SpmmArgs& a, int lc, int tile_cols, int xcds, hipStream_t s)
 {
+    if (tile_cols > lc * 4) return hipErrorInvalidValue;
     const int64_t rows = (int64_t)(kBlock / lc) * kQuad;
     TileSched ts;
     ts.row_blocks = (a.M + rows - 1) / rows;

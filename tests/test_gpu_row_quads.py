@@ -72,6 +72,16 @@ def test_rows_at_the_edges(N, kind):
         check(p, (1,), xcd_remap=0)
 
 
+@pytest.mark.parametrize("N,tile_cols", [(260, 260), (300, 300), (300, 1000), (520, 512), (520, 300), (600, 1000)])
+def test_column_tiles_wider_than_a_wavefront(N, tile_cols):
+    """64 lanes hold 256 columns: a tile of more takes several passes over its rows."""
+    rowptr, colidx = csr("band")
+    rng, K = np.random.default_rng(N), int(colidx.max()) + 1
+    p = wl.SpmmProblem("quads", ROWS, K, N, rowptr, colidx, wl.fill_values(rng, colidx.size, True),
+                       wl.fill_values(rng, K * N, True).reshape(K, N))
+    check(p, (1, 2, 4), tile_cols=tile_cols)
+
+
 @pytest.mark.parametrize("N", [40, 64, 100, 132])  # 40: the rows as they are decide, not the lanes they take
 def test_planes_dealt_over_the_dies(N):
     nx, ny, nz = 61, 103, 19  # reach 6,345 rows, the last planes are left over
