@@ -250,17 +250,23 @@ __host__ __device__ constexpr int x1_pitch(int columns, bool edge, int ept)
     return in_step(edge, ept) && columns % 64 == 0 ? columns + 32 : columns;
 }
 
-// quads: where rows turn out to share columns, the matrix is taken by four rows together (sgap_sddmm_quads.hpp), by all
+// QUADS: where rows turn out to share columns, the matrix is taken by four rows together (sgap_sddmm_quads.hpp), by all
 // workgroups of the grid; else by the first `workers` of them, tile by tile, as above.  resident: workgroups of a die at a time.
+// QUADS with IN_STEP: seven wavefronts per SIMD, as without QUADS, which takes 72 vector registers and 96 scalar ones.  The occupancy
+// that sizes the grid goes by the vector registers; of scalar ones a SIMD has 800, handed out in sixteens, and the trap handler
+// takes sixteen of each wavefront: with 100 six wavefronts were resident, and the persistent grid's last seventh ran in a second
+// round (tile by tile, J = 128, G = 16: 4.8 M entries without order 366 -> 385 us, 366 so; 6.5 M that share half of their columns with
+// the row above 161 -> 231, 162 so).  With six, and 76 vector registers, the stencil below takes 546 us by four rows together instead
+// of 553, but tile by tile everything takes 1 to 8 % more.
 // From 65 columns on: of 64, a 60 x 57 x 62 stencil takes 86 us tile by tile and 94 so.
-__host__ __device__ constexpr bool has_quads(int g, int s) { return s * g == 32 || s * g == 64; }  // 65 to 256 columns
+__host__ __device__ constexpr bool has_quads(int g, int s, int ept) { return ept == 1 && (s * g == 32 || s * g == 64); }  // 65 to 256 columns
 // Stored entries from which on a matrix is looked at for such rows: the look takes 2 us where it finds none.  40 x 41 x 42
 // points, 1.8 M entries: J = 100 59.9 -> 49.7 us, J = 72 55.2 -> 49.0, J = 256 141 -> 82, but J = 128, which the tiles have in
 // step, 55.0 -> 51.4 in groups of 8 and 59.4 -> 62.6 of 16; 60 x 57 x 62, 5.4 M, J = 128: 127 -> 121 and 134 -> 126; 31 x 30 x 33
 // points, 0.8 M: J = 100 35.6 -> 32.6, J = 128 27.2 -> 28.6.
 constexpr int64_t quads_from(bool step128) { return step128 ? 3000000 : 1500000; }
-template <int G, int S, bool EDGE, int EPT>
-__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(in_step(EDGE, EPT) ? 6 : 4))) void sddmm_tile_kernel(SddmmArgs s, int x1_rows, uint32_t workers, uint32_t resident, bool quads)
+template <int G, int S, bool EDGE, int EPT, bool QUADS>
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(QUADS && in_step(EDGE, EPT) ? 7 : 4))) void sddmm_tile_kernel(SddmmArgs s, int x1_rows, uint32_t workers, uint32_t resident)
 {
     constexpr int VEC = 4;
     constexpr bool IN_STEP = in_step(EDGE, EPT);
@@ -297,8 +303,8 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(in_step(
     const int32_t M = (int32_t)a.M;
     const int32_t nnz = a.rowptr[a.M];
     bool by_quads = false;
-    if constexpr (has_quads(G, S)) {
-        by_quads = quads && rows_share_columns(a, nnz, s_tile_row);
+    if constexpr (QUADS) {
+        by_quads = rows_share_columns(a, nnz, s_tile_row);
         if (by_quads)
             sddmm_quads(a, s.X1, s.out, DotColumns<S * G / 4, EDGE>(J), reinterpret_cast<QuadDots*>(s_x1)[wave], TILE, resident);
     }
@@ -306,7 +312,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(in_step(
     const int64_t tiles = ((int64_t)nnz + TILE - 1) / TILE;
     const TileDeal deal(tiles, blockIdx.x, workers);
     const int64_t my_tiles = deal.mine;
-    if constexpr (has_quads(G, S)) {
+    if constexpr (QUADS) {
         if (by_quads) {
             for (int64_t j0 = 0; j0 < my_tiles; j0 += kTileRowBatch) {
                 find_tile_rows(a, deal, j0, TILE, s_tile_row);
@@ -556,18 +562,22 @@ void launch_tile(const SddmmArgs& s, int compute_units, int64_t nnz_hint, hipStr
 {
     constexpr int x1_rows = EPT * kX1LdsBytes / (S * G * 16);
     constexpr int x1_bytes = x1_rows * x1_pitch(S * G * 4, EDGE, EPT) * 4;
-    static const int per_cu = resident_per_cu(sddmm_tile_kernel<G, S, EDGE, EPT>, x1_bytes);
-    const uint32_t workers = (uint32_t)persistent_grid(per_cu, compute_units, nnz_hint, EPT * kBlock);
-    static_assert(!has_quads(G, S) || x1_bytes >= (int)sizeof(QuadDots) * kWavesPerBlock, "either is in the same place");
-    const uint32_t all = (uint32_t)(per_cu * compute_units), resident = all >= kQuadDies ? all / kQuadDies : 1;
-    bool quads = false;
-    if constexpr (has_quads(G, S)) {
+    if constexpr (has_quads(G, S, EPT)) {
         const SpmmArgs& a = s.a;
-        quads = a.M > 1 && a.N > S * G * 2 && a.K * a.N * 4 <= 0xffffffffLL && nnz_hint >= quads_from(in_step(EDGE, EPT) && S * G == 32) &&
-                nnz_hint > kQuadMeanRow * a.M && nnz_hint < kQuadRow * a.M;
+        if (a.M > 1 && a.N > S * G * 2 && a.K * a.N * 4 <= 0xffffffffLL && nnz_hint >= quads_from(in_step(EDGE, EPT) && S * G == 32) &&
+            nnz_hint > kQuadMeanRow * a.M && nnz_hint < kQuadRow * a.M) {
+            static_assert(x1_bytes >= (int)sizeof(QuadDots) * kWavesPerBlock, "either is in the same place");
+            static const int per_cu = resident_per_cu(sddmm_tile_kernel<G, S, EDGE, EPT, true>, x1_bytes);
+            const uint32_t workers = (uint32_t)persistent_grid(per_cu, compute_units, nnz_hint, EPT * kBlock);
+            const uint32_t all = (uint32_t)(per_cu * compute_units), resident = all >= kQuadDies ? all / kQuadDies : 1;
+            const uint32_t grid = quad_workgroups(a.M, resident) > workers ? quad_workgroups(a.M, resident) : workers;
+            hipLaunchKernelGGL((sddmm_tile_kernel<G, S, EDGE, EPT, true>), dim3(grid), dim3(kBlock), x1_bytes, stream, s, x1_rows, workers, resident);
+            return;
+        }
     }
-    const uint32_t grid = quads && quad_workgroups(s.a.M, resident) > workers ? quad_workgroups(s.a.M, resident) : workers;
-    hipLaunchKernelGGL((sddmm_tile_kernel<G, S, EDGE, EPT>), dim3(grid), dim3(kBlock), x1_bytes, stream, s, x1_rows, workers, resident, quads);
+    static const int per_cu = resident_per_cu(sddmm_tile_kernel<G, S, EDGE, EPT, false>, x1_bytes);
+    const uint32_t grid = (uint32_t)persistent_grid(per_cu, compute_units, nnz_hint, EPT * kBlock);
+    hipLaunchKernelGGL((sddmm_tile_kernel<G, S, EDGE, EPT, false>), dim3(grid), dim3(kBlock), x1_bytes, stream, s, x1_rows, grid, 0u);
 }
 
 // Steps of G*4 columns that cover J: 1, 2 or 4 pick sddmm_tile_kernel, 0 = more than 4.
@@ -582,10 +592,10 @@ bool try_tile(const SddmmArgs& s, int64_t J, int compute_units, int64_t nnz_hint
     auto pick = [&](auto s_const) {
         constexpr int S = decltype(s_const)::value;
         const bool edge = J != S * G * 4;
-        if (J <= 64) {
+        if (S * G <= 16 || J <= 64) {
             if (edge) launch_tile<G, S, true, 2>(s, compute_units, nnz_hint, stream);
             else launch_tile<G, S, false, 2>(s, compute_units, nnz_hint, stream);
-        } else {
+        } else if constexpr (S * G > 16) {
             if (edge) launch_tile<G, S, true, 1>(s, compute_units, nnz_hint, stream);
             else launch_tile<G, S, false, 1>(s, compute_units, nnz_hint, stream);
         }

@@ -1,6 +1,7 @@
 """What the compiler gave the kernels of the built library, read from the code objects' own metadata: no kernel keeps
 vector registers in memory.  (A spill inside a loop over tiles costs more than the loads it stands beside, and a build
 says nothing about it.)  No GPU."""
+import re
 import struct
 
 import pytest
@@ -50,3 +51,14 @@ KNOWN = {f"sddmm_tile_kernelILi{g}ELi4ELb1ELi2E": 2 for g in (2, 4, 8, 16, 32)}
 def test_no_vector_register_is_spilled(kernels):
     spilled = {k[".name"]: k[".vgpr_spill_count"] for k in kernels if k[".vgpr_spill_count"] or k[".private_segment_fixed_size"]}
     assert not {name: n for name, n in spilled.items() if n > max([0] + [KNOWN[part] for part in KNOWN if part in name])}
+
+
+def test_scalar_registers_leave_the_wavefronts_that_a_persistent_grid_counts_on(kernels):
+    """sddmm_tile_kernel's grid is what the runtime says is resident at once, which goes by the vector registers (512 per lane of a
+    SIMD, in eights).  A SIMD has 800 scalar ones, in sixteens, and the trap handler takes sixteen of each wavefront."""
+    quads = [k for k in kernels if re.search(r"sddmm_tile_kernelILi\d+ELi\dELb0ELi1ELb1EE", k[".name"])]  # entries in step, looks for quads
+    assert len(quads) == 6
+    for k in quads:
+        by_vector = 512 // (-(-k[".vgpr_count"] // 8) * 8)
+        by_scalar = 800 // (-(-k[".sgpr_count"] // 16) * 16 + 16)
+        assert by_scalar >= by_vector, (k[".name"], k[".vgpr_count"], k[".sgpr_count"])
