@@ -85,6 +85,10 @@ int sgap_debug_group_seg_reduce(const float* in, const int32_t* span, float* out
  *     library expects of both (0: the one in LDS does not come into question).
  *     The device decides by the same functions; 32-bit word 19 of the
  *     workspace says what it decided.
+ *   sgap_debug_sddmm_quads: 1 if sgap_sddmm_csr with the parallel strategy
+ *     takes the matrix by four neighbouring rows together, 0 if entry by
+ *     entry, -1 on bad arguments (rowptr and colidx in host memory; the device
+ *     looks at the same rows of its own).
  */
 int64_t sgap_debug_tile_deal(int64_t tiles, int grid, int block, int64_t* out_tiles, int64_t capacity);
 int sgap_debug_plan_nnz_serial(int group_size, int lanes_per_row, int cols_per_lane, int64_t nnz_hint,
@@ -98,6 +102,8 @@ int sgap_debug_plan_windows(int sddmm, int64_t K, int64_t N, int64_t rows, int64
                             int64_t nnz, int64_t apart, int64_t worst, int window_kb, int max_long_rows,
                             int compute_units, int* in_lds, int* groups, int* shares, int* window,
                             double* lds_clocks, double* gather_clocks);
+int sgap_debug_sddmm_quads(int64_t M, int64_t K, int64_t J, int group_size, int64_t nnz_hint, const int32_t* rowptr,
+                           const int32_t* colidx);
 
 /*
  * Streaming kernels over n fp32 elements (16-byte aligned device buffers):

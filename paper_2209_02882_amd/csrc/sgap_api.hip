@@ -1043,6 +1043,17 @@ int sgap_debug_plan_windows(int sddmm, int64_t K, int64_t N, int64_t rows, int64
     return SGAP_OK;
 }
 
+int sgap_debug_sddmm_quads(int64_t M, int64_t K, int64_t J, int group_size, int64_t nnz_hint, const int32_t* rowptr,
+                           const int32_t* colidx)
+{
+    if (M < 0 || M > 2147483646LL || K < 0 || K > 2147483647LL || J < 0 || J > 2147483647LL || !is_pow2_group(group_size) ||
+        nnz_hint < -1 || nnz_hint > kMaxEntries || !rowptr || !colidx) {
+        fail(SGAP_ERR_INVALID_ARG, "bad matrix");
+        return -1;
+    }
+    return sgap::sddmm_by_quads(M, K, J, group_size, nnz_hint, rowptr, colidx) ? 1 : 0;
+}
+
 int64_t sgap_debug_finder_rows(int64_t M, int teams, int team, int64_t* out_rows, int64_t capacity)
 {
     if (M < 1 || M > 2147483646LL || teams < 1 || team < 0 || team >= teams || capacity < 0 ||

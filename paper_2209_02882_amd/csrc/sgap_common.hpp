@@ -256,6 +256,8 @@ hipError_t launch_row_split(const SpmmArgs& a, int g, int lc, int vec, int rows_
 // the kernel for so many rows of mean_row stored entries and lc lanes per column tile
 bool row_quads_apply(const SpmmArgs& a, int lc, int64_t tile_cols, double mean_row, int compute_units);
 hipError_t launch_row_quads(const SpmmArgs& a, int lc, int tile_cols, int xcds, hipStream_t s);
+// whether the parallel strategy of SDDMM takes a matrix in host memory by four rows together (g lanes per entry)
+bool sddmm_by_quads(int64_t M, int64_t K, int64_t J, int g, int64_t nnz_hint, const int32_t* rowptr, const int32_t* colidx);
 // the same with g lanes per row reducing in sub-groups of r < g lanes whose sums
 // are merged with atomics; C must have been zeroed (launch_nnz_zero_rows, -1)
 hipError_t launch_row_split_partial(const SpmmArgs& a, int g, int r, int lc, int vec, int rows_per_slot,

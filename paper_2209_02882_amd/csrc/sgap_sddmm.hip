@@ -265,6 +265,13 @@ __host__ __device__ constexpr bool has_quads(int g, int s, int ept) { return ept
 // step, 55.0 -> 51.4 in groups of 8 and 59.4 -> 62.6 of 16; 60 x 57 x 62, 5.4 M, J = 128: 127 -> 121 and 134 -> 126; 31 x 30 x 33
 // points, 0.8 M: J = 100 35.6 -> 32.6, J = 128 27.2 -> 28.6.
 constexpr int64_t quads_from(bool step128) { return step128 ? 3000000 : 1500000; }
+// Whether a call is launched so that it looks (chunks: of four columns, that the lanes and steps of an entry hold)
+constexpr bool looks_for_quads(int64_t M, int64_t K, int64_t J, int chunks, int64_t nnz_hint)
+{
+    return J > chunks * 2 && K * J * 4 <= 0xffffffffLL && nnz_hint >= quads_from(J == 128 && chunks == 32) &&
+           nnz_hint > kQuadMeanRow * M && nnz_hint < kQuadRow * M;
+}
+static_assert(1500000 / kQuadRow >= kLookRun, "so many entries come with enough rows to look at");
 template <int G, int S, bool EDGE, int EPT, bool QUADS>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(QUADS && in_step(EDGE, EPT) ? 7 : 4))) void sddmm_tile_kernel(SddmmArgs s, int x1_rows, uint32_t workers, uint32_t resident)
 {
@@ -304,9 +311,9 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(QUADS &&
     const int32_t nnz = a.rowptr[a.M];
     bool by_quads = false;
     if constexpr (QUADS) {
-        by_quads = rows_share_columns(a, nnz, s_tile_row);
+        by_quads = rows_share_columns(a, nnz, S * G > 32, s_tile_row);
         if (by_quads)
-            sddmm_quads(a, s.X1, s.out, DotColumns<S * G / 4, EDGE>(J), reinterpret_cast<QuadDots*>(s_x1)[wave], TILE, resident);
+            sddmm_quads(a, s.X1, s.out, DotColumns<S * G / 4, EDGE>(J), reinterpret_cast<QuadDots*>(s_x1)[__builtin_amdgcn_readfirstlane(wave)], TILE, resident);
     }
     if (blockIdx.x >= workers) return;
     const int64_t tiles = ((int64_t)nnz + TILE - 1) / TILE;
@@ -563,14 +570,12 @@ void launch_tile(const SddmmArgs& s, int compute_units, int64_t nnz_hint, hipStr
     constexpr int x1_rows = EPT * kX1LdsBytes / (S * G * 16);
     constexpr int x1_bytes = x1_rows * x1_pitch(S * G * 4, EDGE, EPT) * 4;
     if constexpr (has_quads(G, S, EPT)) {
-        const SpmmArgs& a = s.a;
-        if (a.M > 1 && a.N > S * G * 2 && a.K * a.N * 4 <= 0xffffffffLL && nnz_hint >= quads_from(in_step(EDGE, EPT) && S * G == 32) &&
-            nnz_hint > kQuadMeanRow * a.M && nnz_hint < kQuadRow * a.M) {
+        if (looks_for_quads(s.a.M, s.a.K, s.a.N, S * G, nnz_hint)) {
             static_assert(x1_bytes >= (int)sizeof(QuadDots) * kWavesPerBlock, "either is in the same place");
             static const int per_cu = resident_per_cu(sddmm_tile_kernel<G, S, EDGE, EPT, true>, x1_bytes);
             const uint32_t workers = (uint32_t)persistent_grid(per_cu, compute_units, nnz_hint, EPT * kBlock);
             const uint32_t all = (uint32_t)(per_cu * compute_units), resident = all >= kQuadDies ? all / kQuadDies : 1;
-            const uint32_t grid = quad_workgroups(a.M, resident) > workers ? quad_workgroups(a.M, resident) : workers;
+            const uint32_t grid = quad_workgroups(s.a.M, resident) > workers ? quad_workgroups(s.a.M, resident) : workers;
             hipLaunchKernelGGL((sddmm_tile_kernel<G, S, EDGE, EPT, true>), dim3(grid), dim3(kBlock), x1_bytes, stream, s, x1_rows, workers, resident);
             return;
         }
@@ -581,6 +586,12 @@ void launch_tile(const SddmmArgs& s, int compute_units, int64_t nnz_hint, hipStr
 }
 
 // Steps of G*4 columns that cover J: 1, 2 or 4 pick sddmm_tile_kernel, 0 = more than 4.
+constexpr int tile_steps(int64_t J, int g)
+{
+    const int64_t steps = (J + g * 4 - 1) / (g * 4);
+    return steps <= 2 ? (steps <= 1 ? 1 : 2) : steps <= 4 ? 4 : 0;
+}
+
 // Tile: the entries that all resident workgroups work on at a time decide whether neighbouring rows find each other's
 // rows of X2T in the die's L2: 256 entries for wide rows (stencil27, J = 128: 825 us, 512 entries 958, 1,024 entries
 // 1,038), twice that for rows of up to 64 columns, where the work per tile weighs more (57 x 60 x 62 stencil, J = 34:
@@ -588,7 +599,6 @@ void launch_tile(const SddmmArgs& s, int compute_units, int64_t nnz_hint, hipStr
 template <int G>
 bool try_tile(const SddmmArgs& s, int64_t J, int compute_units, int64_t nnz_hint, hipStream_t stream)
 {
-    const int64_t steps = (J + G * 4 - 1) / (G * 4);
     auto pick = [&](auto s_const) {
         constexpr int S = decltype(s_const)::value;
         const bool edge = J != S * G * 4;
@@ -600,11 +610,12 @@ bool try_tile(const SddmmArgs& s, int64_t J, int compute_units, int64_t nnz_hint
             else launch_tile<G, S, false, 1>(s, compute_units, nnz_hint, stream);
         }
     };
-    if (steps <= 1) pick(std::integral_constant<int, 1>{});
-    else if (steps <= 2) pick(std::integral_constant<int, 2>{});
-    else if (steps <= 4) pick(std::integral_constant<int, 4>{});
-    else return false;
-    return true;
+    switch (tile_steps(J, G)) {
+        case 1: pick(std::integral_constant<int, 1>{}); return true;
+        case 2: pick(std::integral_constant<int, 2>{}); return true;
+        case 4: pick(std::integral_constant<int, 4>{}); return true;
+        default: return false;
+    }
 }
 
 template <int G, int VEC, bool RAGGED>
@@ -682,6 +693,31 @@ hipError_t launch_sddmm(const SpmmArgs& a, const float* X1, float* out, int g, i
     }
     if (!ok) return hipErrorInvalidValue;
     return hipGetLastError();
+}
+
+// What the parallel strategy with g lanes per entry does with a matrix in host memory: rows_share_columns by a single thread.
+bool sddmm_by_quads(int64_t M, int64_t K, int64_t J, int g, int64_t nnz_hint, const int32_t* rowptr, const int32_t* colidx)
+{
+    const int chunks = tile_steps(J, g) * g;
+    if (J <= 64 || !(chunks == 32 || chunks == 64) || !looks_for_quads(M, K, J, chunks, nnz_hint)) return false;
+    int long_rows = 0, shared = 0, total = 0;
+    for (int i = 0; i < kLookRuns; ++i) {
+        const int32_t* p = rowptr + look_run((uint32_t)i, M);
+        for (int r = 0; r < kLookRun; ++r) long_rows += p[r + 1] - p[r] >= kQuadRow;
+        for (int n = 0; n < kLookPairs; ++n) {
+            const int32_t* row = p + look_at(n / 2, n % 2);
+            int32_t above[kQuadRow];
+            for (int q = 0; q < kQuadRow; ++q) above[q] = row[0] + q < row[1] ? colidx[row[0] + q] : kNoColumn;
+            for (int q = 0; q < kQuadRow && row[1] + q < row[2]; ++q) {
+                const int32_t c = colidx[row[1] + q];
+                int lo = 0;
+                for (int half = kQuadRow / 2; half > 0; half /= 2) lo += above[lo + half - 1] < c ? half : 0;
+                shared += above[lo] == c;
+                ++total;
+            }
+        }
+    }
+    return lengths_for_quads(M, rowptr[M], long_rows, chunks > 32) && columns_for_quads(shared, total, chunks > 32);
 }
 
 // The plain kernel (16-byte loads: J % 4 == 0, aligned operands) on the rows of at least from_len entries

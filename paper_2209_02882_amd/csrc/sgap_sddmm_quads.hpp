@@ -39,34 +39,56 @@ struct alignas(16) QuadDots {  // of a wavefront
     int32_t row_col[kQuad][1 + kQuadRow];     // the rows' columns from place 1 on, kNoColumn behind them
 };
 
-// Whether neighbouring rows share half of their columns, by sixteen of them spread over the matrix, and have more than a
-// dozen entries and less than kQuadRow in the mean.  Called by whole workgroups (counts: an integer for each wavefront, in
-// LDS); the same result everywhere.  It decides nothing but which way the products are formed.  The look costs a matrix that
-// does not pass two ways to memory (R-MAT of 2^16 rows, J = 100: 54.7 -> 56.8 us, 2^18 rows, J = 128: 263.6 -> 263.7) and the
-// grid's further workgroups (2^21 rows, J = 128: 2,873 -> 2,894); turning away rows of unlike length after the first spares 1 us
-// there, and costs 17 of 546 on the stencil above.
-__device__ __forceinline__ bool rows_share_columns(const SpmmArgs& a, int32_t nnz, int32_t* __restrict__ counts)
+// Whether a matrix is taken by four rows together is told by kLookRuns runs of kLookRun rows, spread over it (by multiples of the
+// golden section): by the lengths of all of them and, of kLookPairs rows of each run, whether the row above has their columns.  It
+// decides nothing but which way the products are formed.
+constexpr int kLookRuns = kWavesPerBlock, kLookRun = kWave - 1, kLookPairs = 4;  // (a lane for each row pointer of a run)
+__host__ __device__ constexpr int64_t look_run(uint32_t number, int64_t M)  // its first row; M >= kLookRun
 {
-    constexpr int PAIRS = 2;
-    const int lane = threadIdx.x % kWave, wave = threadIdx.x / kWave, q = lane % kQuadRow;
-    int32_t p[PAIRS][3], above[PAIRS], col[PAIRS];
+    return (int64_t)(((uint64_t)((number + 1u) * 0x9e3779b9u) * (uint32_t)(M - kLookRun + 1)) >> 32);
+}
+// More than a dozen entries and less than kQuadRow in the mean, and few rows of kQuadRow or more: such a row leaves its whole
+// quad to quad_entries.  400,000 rows of 27 neighbouring columns, one in 64, 32, 16 or 8 of 40, tile by tile and by four rows
+// together: J = 128, G = 8 253 / 216, 253 / 258, 261 / 317, 262 / 435 us; J = 72, G = 8 286 / 258, 290 / 313, 295 / 400, 302 / 534;
+// J = 200, G = 16 (wide) 689 / 437, 676 / 542, 673 / 704, 642 / 955.
+__host__ __device__ constexpr bool lengths_for_quads(int64_t M, int64_t nnz, int long_rows, bool wide)
+{
+    return nnz > kQuadMeanRow * M && nnz < kQuadRow * M && long_rows * (wide ? 20 : 42) <= kLookRuns * kLookRun;
+}
+// Of the rows' columns the row above has nine in sixteen, or half (wide).  268,800 rows that share 54 %, tile by tile and by four rows
+// together: J = 72 179 / 203 us, J = 128 161 / 172 (G = 8), 168 / 171 (G = 16), J = 200 524 / 335, J = 256 657 / 322; a 27-point
+// stencil shares two thirds but at the ends of its lines.
+__host__ __device__ constexpr bool columns_for_quads(int shared, int total, bool wide) { return wide ? 2 * shared >= total : 16 * shared >= 9 * total; }
+// The rows of a run whose columns are looked at, behind the first: no two pairs of them as far apart
+__host__ __device__ constexpr int look_at(int half, int i) { return half ? 29 + 23 * i : 11 * i; }
+
+// Called by whole workgroups (counts: an integer for each wavefront, in LDS); the same result everywhere.  A matrix that does not
+// pass costs the look one way to memory beside that of its last row pointer, or two where the lengths pass.
+__device__ __forceinline__ bool rows_share_columns(const SpmmArgs& a, int32_t nnz, bool wide, int32_t* __restrict__ counts)
+{
+    constexpr int MINE = kLookPairs / 2;  // rows whose columns half a wavefront looks at, of its first run
+    const int lane = threadIdx.x % kWave, wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave)), q = lane % kQuadRow;
+    int32_t p[kLookRuns];
 #pragma unroll
-    for (int i = 0; i < PAIRS; ++i) {
-        // (multiples of the golden section of 2^32: no two alike in a row of the grid, whatever its length)
-        const uint32_t at = (uint32_t)((wave * PAIRS + i) * 2 + lane / kQuadRow + 1) * 0x9e3779b9u;
-        const int64_t r = 1 + (int64_t)(((uint64_t)at * (uint32_t)(a.M - 1)) >> 32);
+    for (int i = 0; i < kLookRuns; ++i) p[i] = a.rowptr[look_run((uint32_t)(wave + i) % kLookRuns, a.M) + lane];
+    int long_rows = 0;
 #pragma unroll
-        for (int e = 0; e < 3; ++e) p[i][e] = a.rowptr[r - 1 + e];
+    for (int i = 0; i < kLookRuns; ++i) {
+        const int32_t next = __builtin_amdgcn_update_dpp(p[i], p[i], 0x130, 0xF, 0xF, false);  // wave_shl:1; the last lane keeps its own
+        long_rows += (int)__popcll(__ballot(next - p[i] >= kQuadRow));
     }
-    if ((int64_t)nnz <= kQuadMeanRow * a.M || (int64_t)nnz >= kQuadRow * a.M) return false;
+    if (!lengths_for_quads(a.M, nnz, long_rows, wide)) return false;
+    int32_t above[MINE], col[MINE];
 #pragma unroll
-    for (int i = 0; i < PAIRS; ++i) {
-        above[i] = p[i][0] + q < p[i][1] ? a.colidx[p[i][0] + q] : kNoColumn;
-        col[i] = p[i][1] + q < p[i][2] ? a.colidx[p[i][1] + q] : kNoColumn;
+    for (int i = 0; i < MINE; ++i) {
+        const int at = look_at(lane / kQuadRow, i);
+        const int32_t begin = __shfl(p[0], at), mid = __shfl(p[0], at + 1), end = __shfl(p[0], at + 2);
+        above[i] = begin + q < mid ? a.colidx[begin + q] : kNoColumn;
+        col[i] = mid + q < end ? a.colidx[mid + q] : kNoColumn;
     }
     int shared = 0, total = 0;
 #pragma unroll
-    for (int i = 0; i < PAIRS; ++i) {
+    for (int i = 0; i < MINE; ++i) {
         int lo = 0;
 #pragma unroll
         for (int half = kQuadRow / 2; half > 0; half /= 2) lo += __shfl(above[i], lo + half - 1, kQuadRow) < col[i] ? half : 0;
@@ -74,12 +96,12 @@ __device__ __forceinline__ bool rows_share_columns(const SpmmArgs& a, int32_t nn
         shared += (int)__popcll(__ballot(found && col[i] != kNoColumn));
         total += (int)__popcll(__ballot(col[i] != kNoColumn));
     }
-    if (lane == 0) counts[wave] = 2 * shared - total;
+    if (lane == 0) counts[wave] = shared << 16 | total;
     __syncthreads();
-    int over = 0;
+    int sum = 0;
 #pragma unroll
-    for (int w = 0; w < kWavesPerBlock; ++w) over += counts[w];
-    return over >= 0;
+    for (int w = 0; w < kWavesPerBlock; ++w) sum += counts[w];
+    return columns_for_quads(sum >> 16, sum & 0xffff, wide);
 }
 
 // Sum of v over the lanes 4, 8 and 12 further in each row of 16 lanes

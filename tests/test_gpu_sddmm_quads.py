@@ -7,6 +7,7 @@ import pytest
 import torch
 
 import oracle
+from paper_2209_02882_amd import binding
 from paper_2209_02882_amd import workloads as wl
 
 from gpu_util import DeviceProblem
@@ -19,8 +20,10 @@ def rows_of(kind):
     band = lambda r, n: r + np.arange(n)  # noqa: E731
     if kind == "band":
         return lambda r: band(r, 20)
-    if kind == "30, 31 and 32 entries":
-        return lambda r: band(r, 30 + r // 8 % 3)
+    if kind == "30, 31 and 32 entries":  # few of 32: not more than a matrix has that goes by quads
+        return lambda r: band(r, 32 if r in (1, 78, 207, 304, 396) else 30 + r // 8 % 2)
+    if kind == "31 to 33 entries, entry by entry":
+        return lambda r: band(r, 31 + r // 8 % 3 if r % 3 else 29)
     if kind == "in the row before the last":  # columns that come and go
         return lambda r: np.concatenate([band(r, 16), 600 + 30 * (r % 2) + np.arange(4)])
     if kind == "descending and repeated":
@@ -34,7 +37,7 @@ def rows_of(kind):
 
 
 KINDS = ["band", "30, 31 and 32 entries", "in the row before the last", "descending and repeated", "with empty rows",
-         "nothing in common in places", "long rows"]
+         "nothing in common in places", "long rows", "31 to 33 entries, entry by entry"]
 
 
 @functools.lru_cache
@@ -42,7 +45,8 @@ def csr(kind, rows=ROWS):
     """The rows of that kind, repeated with a period of 400 rows and shifted along."""
     period = [rows_of(kind)(r) for r in range(400)]
     columns = [period[r % 400] + 40 * (r // 400) for r in range(rows)]
-    if kind == "long rows":
+    if kind == "long rows":  # in every other period: not more than a matrix has that goes by quads
+        columns = [c if r // 400 % 2 else c[0] + np.arange(17) for r, c in enumerate(columns)]
         columns[-1] = np.arange(9_000)
     rowptr = np.concatenate([[0], np.cumsum([c.size for c in columns])]).astype(np.int32)
     assert (3_000_000 if rows == MORE_ROWS else 1_500_000) <= rowptr[-1] and 12 * rows < rowptr[-1] < 32 * rows
@@ -56,13 +60,18 @@ def problem(kind, J, rowptr, colidx):
     return p, wl.fill_values(rng, rows * J, True).reshape(rows, J)
 
 
+def by_quads(p, g):
+    return binding.load().sgap_debug_sddmm_quads(p.M, p.K, p.N, g, p.colidx.size, p.rowptr.ctypes.data, p.colidx.ctypes.data)
+
+
 @pytest.mark.parametrize("kind", KINDS)
 @pytest.mark.parametrize("J", [65, 101, 128, 129, 197, 256])
 def test_rows_at_the_edges(J, kind):
     p, X1 = problem(kind, J, *csr(kind, MORE_ROWS if J == 128 else ROWS))
     ref, _ = oracle.sddmm_csr(p.M, p.K, p.N, p.rowptr, p.colidx, p.vals, X1, p.B)
     dp, X1d = DeviceProblem(p), torch.from_numpy(X1).cuda()
-    for g in (8, 16, 32) if J <= 128 else (16, 32):
+    for g in (8, 16, 32) if J <= 128 else (16, 32, 64):
+        assert by_quads(p, g) == (kind != "31 to 33 entries, entry by entry")
         assert np.array_equal(dp.run_sddmm(X1d, g, "parallel").cpu().numpy().astype(np.float64), ref), g
 
 
