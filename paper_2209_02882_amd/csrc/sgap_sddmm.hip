@@ -258,20 +258,26 @@ __host__ __device__ constexpr int x1_pitch(int columns, bool edge, int ept)
 // round (tile by tile, J = 128, G = 16: 4.8 M entries without order 366 -> 385 us, 366 so; 6.5 M that share half of their columns with
 // the row above 161 -> 231, 162 so).  With six, and 76 vector registers, the stencil below takes 546 us by four rows together instead
 // of 553, but tile by tile everything takes 1 to 8 % more.
-// From 65 columns on: of 64, a 60 x 57 x 62 stencil takes 86 us tile by tile and 94 so.
-__host__ __device__ constexpr bool has_quads(int g, int s, int ept) { return ept == 1 && (s * g == 32 || s * g == 64); }  // 65 to 256 columns
+// From 72 columns on, and 136 where an entry has twice the lanes or steps: of 64, a 60 x 57 x 62 stencil takes 86 us tile by tile
+// and 94 so, and just above that a lane has four columns tile by tile, or five, and sums them no less exactly than CHAINS do here
+// (J = 65, G = 16 7.26e-8 and 7.34e-8).
+__host__ __device__ constexpr bool has_quads(int g, int s, int ept) { return ept == 1 && (s * g == 32 || s * g == 64); }  // up to 256 columns
 // Stored entries from which on a matrix is looked at for such rows: the look takes 2 us where it finds none.  40 x 41 x 42
 // points, 1.8 M entries: J = 100 59.9 -> 49.7 us, J = 72 55.2 -> 49.0, J = 256 141 -> 82, but J = 128, which the tiles have in
-// step, 55.0 -> 51.4 in groups of 8 and 59.4 -> 62.6 of 16; 60 x 57 x 62, 5.4 M, J = 128: 127 -> 121 and 134 -> 126; 31 x 30 x 33
+// step, 55.0 -> 51.4 in groups of 8 and 59.4 -> 62.6 of 16; 60 x 57 x 62, 5.5 M, J = 128: 123 -> 118 and 128 -> 115; 31 x 30 x 33
 // points, 0.8 M: J = 100 35.6 -> 32.6, J = 128 27.2 -> 28.6.
 constexpr int64_t quads_from(bool step128) { return step128 ? 3000000 : 1500000; }
 // Whether a call is launched so that it looks (chunks: of four columns, that the lanes and steps of an entry hold)
 constexpr bool looks_for_quads(int64_t M, int64_t K, int64_t J, int chunks, int64_t nnz_hint)
 {
-    return J > chunks * 2 && K * J * 4 <= 0xffffffffLL && nnz_hint >= quads_from(J == 128 && chunks == 32) &&
+    return J >= chunks * 2 + 8 && K * J * 4 <= 0xffffffffLL && nnz_hint >= quads_from(J == 128 && chunks == 32) &&
            nnz_hint > kQuadMeanRow * M && nnz_hint < kQuadRow * M;
 }
 static_assert(1500000 / kQuadRow >= kLookRun, "so many entries come with enough rows to look at");
+// Chains that four lanes' sixteen columns are summed in by four rows together: none longer than a lane has tile by tile, which
+// takes S steps of four columns, with EDGE more than half of them.
+__host__ __device__ constexpr int quad_chains(int s, bool edge) { return edge ? (s == 4 ? 2 : 4) : 4 / s; }
+
 template <int G, int S, bool EDGE, int EPT, bool QUADS>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(QUADS && in_step(EDGE, EPT) ? 7 : 4))) void sddmm_tile_kernel(SddmmArgs s, int x1_rows, uint32_t workers, uint32_t resident)
 {
@@ -313,7 +319,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(QUADS &&
     if constexpr (QUADS) {
         by_quads = rows_share_columns(a, nnz, S * G > 32, s_tile_row);
         if (by_quads)
-            sddmm_quads(a, s.X1, s.out, DotColumns<S * G / 4, EDGE>(J), reinterpret_cast<QuadDots*>(s_x1)[__builtin_amdgcn_readfirstlane(wave)], TILE, resident);
+            sddmm_quads(a, s.X1, s.out, DotColumns<S * G / 4, quad_chains(S, EDGE), EDGE>(J), reinterpret_cast<QuadDots*>(s_x1)[__builtin_amdgcn_readfirstlane(wave)], TILE, resident);
     }
     if (blockIdx.x >= workers) return;
     const int64_t tiles = ((int64_t)nnz + TILE - 1) / TILE;
@@ -325,7 +331,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(QUADS &&
                 find_tile_rows(a, deal, j0, TILE, s_tile_row);
                 const bool have = j0 + tid < my_tiles;
                 const int32_t tile_start = have ? (int32_t)(deal.tile(j0 + tid) * TILE) : 0;
-                tiles_of_long_quads(a, s.X1, s.out, DotColumns<S * G / 4, EDGE>(J), have, have ? s_tile_row[tid] : 0, tile_start, TILE);
+                tiles_of_long_quads(a, s.X1, s.out, DotColumns<S * G / 4, quad_chains(S, EDGE), EDGE>(J), have, have ? s_tile_row[tid] : 0, tile_start, TILE);
             }
             return;
         }

@@ -9,8 +9,8 @@
 // records those are kept that the pattern has.
 // No value of a row gets into another's products: infinities and NaN stay where they are.
 //
-// 27-point stencils, in the same grid as before (groups of 8; of 16 for J = 256): 1,000,000 rows, J = 128 676 -> 546 us, J = 100 890 -> 590; 212,040
-// rows, J = 128 127 -> 121, J = 100 171 -> 133, J = 72 151 -> 129, J = 200 402 -> 208, J = 256 436 -> 208.  Half of the gathers
+// 27-point stencils, tile by tile and so (groups of 8; of 16 from J = 200 on): 1,000,000 rows, J = 128 692 -> 553 us, J = 100 889 -> 581,
+// J = 256 2,272 -> 999; 212,040 rows, J = 128 123 -> 118, J = 100 170 -> 125, J = 72 152 -> 123, J = 200 402 -> 206, J = 256 436 -> 213.  Half of the gathers
 // are gone (L1 accesses 142 M at J = 128), and the time is no longer theirs alone: without any gather from beyond the L1 it is
 // 472 of 554 us, without products 185.  Vector instructions keep their units busy for 0.7 of the time (690 a quad beside 109
 // MFMA, of which 260 change places between lanes), X1 and the stored entries come from memory once.  What the steps gave:
@@ -186,9 +186,14 @@ __device__ __forceinline__ void transpose_fours(Vec<4> (&x)[4])
 // 16 / BL rows from end to end (lanes in the rows' order, which is what a load is quick with: with four rows in every four
 // lanes, as the products want them, every 16 bytes are a cache access of their own, 475 M of them and 889 us on the stencil
 // below).  Four loads make a batch of 64 / BL rows: lane group number p has rows 4 * p .. + 4 of it.
+// CHAINS: the sixteen columns of every four lanes are summed in so many chains (1, 2 or 4), none longer than what a lane of
+// sddmm_tile_kernel sums by itself, so that the error is no larger.  Relative error (2-norm) against 64 bits, uniform values,
+// J = 128: tile by tile 9.1e-8, 8.1e-8 and 7.7e-8 with groups of 8, 16 and 32, with one chain 9.1e-8 for all, so 9.1e-8, 8.1e-8 and
+// 7.7e-8; J = 72 7.9e-8, 7.4e-8 and 7.3e-8, 8.7e-8 for all, 7.7e-8, 7.3e-8 and 7.3e-8.  (Shorter chains of MFMA are quicker too:
+// stencil of 1,000,000 rows, J = 72 573 -> 559 us, J = 200 1,000 -> 970.)
 // EDGE: J is not BL * 16.  The last lane with columns begins where it ends with the row at the latest; what of a lane's four
 // columns is another lane's, or none, is zero.
-template <int BL, bool EDGE>
+template <int BL, int CHAINS, bool EDGE>
 struct DotColumns {
     static constexpr int ROWS = 64 / BL;  // of X2T, in a batch
     uint32_t row_bytes;
@@ -244,31 +249,39 @@ __device__ __forceinline__ int dot_number(int lane) { return lane / (4 * BL) * 4
 template <int BL>
 __device__ __forceinline__ bool dot_here(int lane) { return lane % 16 < (BL == 16 ? 4 : 8); }
 
-template <int BL, bool EDGE>
+template <int BL, int CHAINS, bool EDGE>
 __device__ __forceinline__ float quad_dots(const Vec<4> (&x1)[4], const uint32_t (&offset)[4], const float* __restrict__ X2T,
-                                           const DotColumns<BL, EDGE>& columns)
+                                           const DotColumns<BL, CHAINS, EDGE>& columns)
 {
     Vec<4> x2[4];
 #pragma unroll
     for (int m = 0; m < 4; ++m) x2[m] = columns.load_row(X2T, offset[m]);
     columns.own(x2);
     transpose_fours(x2);
-    f32x4 acc = {0.0f, 0.0f, 0.0f, 0.0f};
+    constexpr int EACH = 4 / CHAINS;
+    f32x4 part[CHAINS];
 #pragma unroll
-    for (int t = 0; t < 4; ++t)
+    for (int n = 0; n < CHAINS; ++n) {
+        part[n] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
-        for (int v = 0; v < 4; ++v) acc = __builtin_amdgcn_mfma_f32_4x4x1f32(x1[t].v[v], x2[t].v[v], acc, 0, 0, 0);
+        for (int t = n * EACH; t < (n + 1) * EACH; ++t)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) part[n] = __builtin_amdgcn_mfma_f32_4x4x1f32(x1[t].v[v], x2[t].v[v], part[n], 0, 0, 0);
+        if (n % 2 == 1) part[n - 1] += part[n];
+    }
+    f32x4 acc = part[0];
+    if constexpr (CHAINS == 4) acc += part[2];
     if constexpr (BL == 16) return sum_every_fourth(fold_rows(fold_halves(acc[0], acc[1]), fold_halves(acc[2], acc[3])));
     const float x = sum_every_fourth(fold_rows(acc[0], acc[1])), y = sum_every_fourth(fold_rows(acc[2], acc[3]));
     return threadIdx.x / 4 % 2 ? y : x;
 }
 
 // Stored entries [begin, end) of the quad's rows one by one
-template <int BL, bool EDGE>
+template <int BL, int CHAINS, bool EDGE>
 __device__ __forceinline__ void quad_entries(const SpmmArgs& a, const float* __restrict__ X1, float* __restrict__ out,
-                                             const DotColumns<BL, EDGE>& columns, int32_t row_first, int32_t begin, int32_t end)
+                                             const DotColumns<BL, CHAINS, EDGE>& columns, int32_t row_first, int32_t begin, int32_t end)
 {
-    constexpr int ROWS = DotColumns<BL, EDGE>::ROWS;
+    constexpr int ROWS = DotColumns<BL, CHAINS, EDGE>::ROWS;
     const int lane = threadIdx.x % kWave;
     const int32_t M = (int32_t)a.M;
     Vec<4> x1[4];
@@ -284,7 +297,7 @@ __device__ __forceinline__ void quad_entries(const SpmmArgs& a, const float* __r
                 const int32_t at = e + lane / (4 * BL) * 4 + m;
                 offset[m] = (uint32_t)load_stream(a.colidx + (at < to ? at : to - 1)) * columns.row_bytes;
             }
-            const float dot = quad_dots<BL, EDGE>(x1, offset, a.B, columns);
+            const float dot = quad_dots<BL, CHAINS, EDGE>(x1, offset, a.B, columns);
             const int32_t at = e + dot_number<BL>(lane);
             if (dot_row<BL>(lane) == i && dot_here<BL>(lane) && at < to)
                 __builtin_nontemporal_store(load_stream(a.vals + at) * dot, out + at);
@@ -294,9 +307,9 @@ __device__ __forceinline__ void quad_entries(const SpmmArgs& a, const float* __r
 
 // A tile's part of a quad of `tile` or more entries: the quad that the tile begins in (row: of the tile's first entry),
 // with what the tile in front has of it where it begins there.  Thread t brings tile number t of up to kTileRowBatch.
-template <int BL, bool EDGE>
+template <int BL, int CHAINS, bool EDGE>
 __device__ __forceinline__ void tiles_of_long_quads(const SpmmArgs& a, const float* __restrict__ X1, float* __restrict__ out,
-                                                    const DotColumns<BL, EDGE>& columns, bool have, int32_t row,
+                                                    const DotColumns<BL, CHAINS, EDGE>& columns, bool have, int32_t row,
                                                     int32_t tile_start, int32_t tile)
 {
     const int32_t M = (int32_t)a.M;
@@ -311,7 +324,7 @@ __device__ __forceinline__ void tiles_of_long_quads(const SpmmArgs& a, const flo
     }
     for (unsigned long long left = __ballot(end > begin); left != 0; left &= left - 1) {
         const int l = __ffsll((unsigned long long)left) - 1;
-        quad_entries<BL, EDGE>(a, X1, out, columns, __builtin_amdgcn_readlane(row_first, l),
+        quad_entries<BL, CHAINS, EDGE>(a, X1, out, columns, __builtin_amdgcn_readlane(row_first, l),
                                __builtin_amdgcn_readlane(begin, l), __builtin_amdgcn_readlane(end, l));
     }
 }
@@ -378,9 +391,9 @@ __device__ __forceinline__ int list_quad(QuadDots& lds, const int32_t (&col)[2],
 }
 
 // This workgroup's quads of less than `tile` entries
-template <int BL, bool EDGE>
+template <int BL, int CHAINS, bool EDGE>
 __device__ __forceinline__ void sddmm_quads(const SpmmArgs& a, const float* __restrict__ X1, float* __restrict__ out,
-                                            const DotColumns<BL, EDGE>& columns, QuadDots& lds, int32_t tile, uint32_t resident)
+                                            const DotColumns<BL, CHAINS, EDGE>& columns, QuadDots& lds, int32_t tile, uint32_t resident)
 {
     constexpr int PER_LANE = 2;  // entries of the quad per lane: number q of the rows half and 2 + half
     int lane = threadIdx.x % kWave;
@@ -469,7 +482,7 @@ __device__ __forceinline__ void sddmm_quads(const SpmmArgs& a, const float* __re
         if (e.total == 0) continue;
         if (!e.small) {
             const int32_t begin = __builtin_amdgcn_readlane(pointers, 0);
-            if (e.total < tile) quad_entries<BL, EDGE>(a, X1, out, columns, row_first, begin, begin + e.total);
+            if (e.total < tile) quad_entries<BL, CHAINS, EDGE>(a, X1, out, columns, row_first, begin, begin + e.total);
             continue;
         }
         Vec<4> x1[4];
@@ -520,11 +533,11 @@ __device__ __forceinline__ void sddmm_quads(const SpmmArgs& a, const float* __re
 
         columns.turn_quad(x1);
         const int row_mine = dot_row<BL>(lane), number_mine = dot_number<BL>(lane);
-        for (int at = 0; at < records; at += DotColumns<BL, EDGE>::ROWS) {
+        for (int at = 0; at < records; at += DotColumns<BL, CHAINS, EDGE>::ROWS) {
             const uint4 of = *reinterpret_cast<const uint4*>(&lds.offset[at + lane / (4 * BL) * 4]);
             const uint32_t offset[4] = {of.x, of.y, of.z, of.w};
             const uint32_t place = lds.place[at + number_mine] >> (8 * row_mine) & 0xffu;
-            const float dot = quad_dots<BL, EDGE>(x1, offset, a.B, columns);
+            const float dot = quad_dots<BL, CHAINS, EDGE>(x1, offset, a.B, columns);
             if (dot_here<BL>(lane) && place != kNoPlace) lds.out[row_mine][place] = dot;
         }
         wave_lds_order();
