@@ -12,6 +12,8 @@
 
 #include <stdint.h>
 
+#include "sgap.h"
+
 #ifdef __cplusplus
 extern "C" {
 #endif
@@ -85,6 +87,10 @@ int sgap_debug_group_seg_reduce(const float* in, const int32_t* span, float* out
  *     library expects of both (0: the one in LDS does not come into question).
  *     The device decides by the same functions; 32-bit word 19 of the
  *     workspace says what it decided.
+ *   sgap_debug_row_quads: 1 if the row-split schedule takes M rows of nnz_hint
+ *     stored entries by four neighbouring rows together, 0 if not, -1 on bad
+ *     arguments (config: a host sgap_config; long_row_min and wave_rows come
+ *     first where they apply).
  *   sgap_debug_sddmm_quads: 1 if sgap_sddmm_csr with the parallel strategy
  *     takes the matrix by four neighbouring rows together, 0 if entry by
  *     entry, -1 on bad arguments (rowptr and colidx in host memory; the device
@@ -102,6 +108,7 @@ int sgap_debug_plan_windows(int sddmm, int64_t K, int64_t N, int64_t rows, int64
                             int64_t nnz, int64_t apart, int64_t worst, int window_kb, int max_long_rows,
                             int compute_units, int* in_lds, int* groups, int* shares, int* window,
                             double* lds_clocks, double* gather_clocks);
+int sgap_debug_row_quads(int64_t M, int64_t N, int64_t nnz_hint, const sgap_config* config, int compute_units);
 int sgap_debug_sddmm_quads(int64_t M, int64_t K, int64_t J, int group_size, int64_t nnz_hint, const int32_t* rowptr,
                            const int32_t* colidx);
 

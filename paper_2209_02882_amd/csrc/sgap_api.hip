@@ -333,6 +333,35 @@ bool windows_apply(const sgap_config& c, int vec)
 int64_t window_bytes_of(const sgap_config& c) { return (int64_t)(c.window_kb > 0 ? c.window_kb : kAutoWindowKb) * 1024; }
 int64_t long_rows_of(const sgap_config& c) { return c.max_long_rows > 0 ? c.max_long_rows : kAutoLongRows; }
 
+// Column tile of the row-split schedule: how many columns of B/C one work item covers.
+int64_t row_split_tile(int64_t N, const sgap_config& c)
+{
+    const int vec = sgap::lane_columns(N);
+    int64_t tile_cols = c.tile_cols > 0 ? c.tile_cols : kAutoTileCols;
+    if (tile_cols > N) tile_cols = N;
+    return (tile_cols + vec - 1) / vec * vec;
+}
+
+// Lanes that hold it in one pass.  A row has the 64 lanes of a wavefront at most.  Columns come first: a group whose members
+// leave too few chunk lanes for the tile gives members up, so that a row is gathered in one pass with all its loads in flight (N =
+// 37, G = 16: one pass of 4 members x 16 chunk lanes in place of three of 16 x 4).  Not where the caller named
+// a reduction narrower than the group: the sub-groups are what is asked for then.
+int row_split_lanes(int64_t N, const sgap_config& c)
+{
+    const bool whole_group = c.reduce_size == 0 || c.reduce_size == c.group_size;
+    return pow2_ceil_capped(row_split_tile(N, c) / sgap::lane_columns(N), whole_group ? 64 : 64 / c.group_size);
+}
+
+// Four neighbouring rows together (sgap_row_quads.hip): where the caller leaves the layout to the library and says how many
+// entries there are.  Groups of more than four rows to a lane are left as the caller names them, whatever they cost (27-point
+// stencil of 212,040 rows, N = 128, G = 8 202 us, G = 4 147 and by quads 81).
+bool row_split_by_quads(int64_t M, int64_t N, const sgap_config& c, int64_t nnz_hint, int compute_units)
+{
+    return c.schedule == SGAP_SCHED_ROW_SPLIT && c.strategy == SGAP_REDUCE_SERIAL && c.group_size <= 4 && sgap::lane_columns(N) == 4 &&
+           c.block_size == 0 && c.persistent == 0 && nnz_hint > 0 &&
+           sgap::row_quads_apply(M, row_split_lanes(N, c), row_split_tile(N, c), (double)nnz_hint / (double)M, compute_units);
+}
+
 int spmm_impl(int64_t M, int64_t K, int64_t N, const int32_t* rowptr, const int32_t* colidx, const float* vals,
               const float* B, float* C, const sgap_config& c, int64_t nnz_hint, void* workspace,
               int64_t workspace_bytes, void* stream)
@@ -387,15 +416,8 @@ int spmm_impl(int64_t M, int64_t K, int64_t N, const int32_t* rowptr, const int3
         const int block = c.block_size > 0 ? c.block_size : kBlock;
         int g = par ? group_size : 1;  // members per row
         const double avg_row = nnz_hint > 0 ? (double)nnz_hint / (double)M : 16.0;
-        // Column tile: how many columns of B/C one work item covers.
-        int64_t tile_cols = c.tile_cols > 0 ? c.tile_cols : kAutoTileCols;
-        if (tile_cols > N) tile_cols = N;
-        tile_cols = (tile_cols + vec - 1) / vec * vec;
-        // A row has the 64 lanes of a wavefront at most.  Columns come first: a group whose members leave too few chunk
-        // lanes for the tile gives members up, so that a row is gathered in one pass with all its loads in flight (N =
-        // 37, G = 16: one pass of 4 members x 16 chunk lanes in place of three of 16 x 4).  Not where the caller named
-        // a reduction narrower than the group: the sub-groups are what is asked for then.
-        const int lc = pow2_ceil_capped(tile_cols / vec, reduce_size == 0 ? 64 : 64 / g);
+        const int64_t tile_cols = row_split_tile(N, c);
+        const int lc = row_split_lanes(N, c);
         if (reduce_size == 0 && g * lc > 64) g = 64 / lc;
         int rows_per_slot = par ? c.rows_per_group : group_size;
         if (rows_per_slot <= 0) {
@@ -420,9 +442,6 @@ int spmm_impl(int64_t M, int64_t K, int64_t N, const int32_t* rowptr, const int3
         const bool wave_wanted = c.wave_rows == 1 ? N >= 48 : c.wave_rows == 0 && windows && N >= 192;
         const int wave_vec = wave_wanted && !par && reduce_size == 0 ? (N > 128 ? avec : N > 64 ? (avec < 2 ? avec : 2) : 1) : 0;
         const int wave_rows_count = group_size > 63 ? 63 : group_size;
-        // Neighbouring rows together, where the caller leaves the layout to the library and says how many entries there are.
-        const bool quads = !par && group_size <= 4 && vec == 4 && c.block_size == 0 && c.persistent == 0 && nnz_hint > 0 &&
-                           row_quads_apply(a, lc, tile_cols, avg_row, cus);
         if (reduce_size != 0) {
             // every row receives atomic adds
             err = launch_nnz_zero_rows(a, vec, -1, s);
@@ -435,7 +454,7 @@ int spmm_impl(int64_t M, int64_t K, int64_t N, const int32_t* rowptr, const int3
                                           window_bytes_of(c), c.window_kb > 0, workspace, long_rows_of(c), s);
         } else if (wave_vec > 0) {
             err = launch_wave_rows(a, wave_vec, wave_rows_count, xcds, nullptr, s);
-        } else if (quads) {
+        } else if (row_split_by_quads(M, N, c, nnz_hint, cus)) {
             err = launch_row_quads(a, lc, (int)tile_cols, xcds, s);
         } else {
             // the parallel strategy interleaves its groups' rows; the serial strategy's lanes
@@ -1041,6 +1060,16 @@ int sgap_debug_plan_windows(int sddmm, int64_t K, int64_t N, int64_t rows, int64
     *lds_clocks = form.lds_clocks;
     *gather_clocks = form.gather_clocks;
     return SGAP_OK;
+}
+
+int sgap_debug_row_quads(int64_t M, int64_t N, int64_t nnz_hint, const sgap_config* config, int compute_units_)
+{
+    if (M < 1 || M > 2147483646LL || N < 1 || N > 2147483647LL || nnz_hint < -1 || nnz_hint > kMaxEntries || compute_units_ < 1 || !config) {
+        fail(SGAP_ERR_INVALID_ARG, "bad arguments");
+        return -1;
+    }
+    if (check_config(*config)) return -1;
+    return row_split_by_quads(M, N, *config, nnz_hint, compute_units_) ? 1 : 0;
 }
 
 int sgap_debug_sddmm_quads(int64_t M, int64_t K, int64_t J, int group_size, int64_t nnz_hint, const int32_t* rowptr,

@@ -254,7 +254,7 @@ hipError_t launch_row_split(const SpmmArgs& a, int g, int lc, int vec, int rows_
                             hipStream_t s);
 // serial strategy, four consecutive rows together (sgap_row_quads.hip); vec must be 4.  row_quads_apply: whether that is
 // the kernel for so many rows of mean_row stored entries and lc lanes per column tile
-bool row_quads_apply(const SpmmArgs& a, int lc, int64_t tile_cols, double mean_row, int compute_units);
+bool row_quads_apply(int64_t M, int lc, int64_t tile_cols, double mean_row, int compute_units);
 hipError_t launch_row_quads(const SpmmArgs& a, int lc, int tile_cols, int xcds, hipStream_t s);
 // whether the parallel strategy of SDDMM takes a matrix in host memory by four rows together (g lanes per entry)
 bool sddmm_by_quads(int64_t M, int64_t K, int64_t J, int g, int64_t nnz_hint, const int32_t* rowptr, const int32_t* colidx);

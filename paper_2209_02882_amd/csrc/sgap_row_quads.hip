@@ -10,17 +10,24 @@
 // twice: both entries go into one record, and a place behind it stays empty.)  Then every record costs one gather and four
 // v_mfma_f32_4x4x1: four rows' values times the four columns of each lane.
 //
-// 27-point stencil of 1,000,000 rows, N = 128: 593 -> 419 us (N = 64 288 -> 242, N = 256 1,218 -> 853; 90 x 40 x 95 points,
-// N = 128 179 -> 134).  By steps: listed in the order of opening, fp32 multiply-adds 499; on the matrix cores, which halves
+// 27-point stencil of 1,000,000 rows, N = 128: 588 -> 429 us (N = 64 287 -> 240, N = 256 1,217 -> 880; 212,040 rows, N = 128 112 ->
+// 81).  By steps: listed in the order of opening, fp32 multiply-adds 499; on the matrix cores, which halves
 // the vector instructions, 493; planes dealt over the dies (die_block) 450, L2 misses 19.9 M -> 10.9 M lines; in the order
 // of the columns, so that neighbouring quads ask for a line at the same time and the L1 answers one of them, 430, L1 misses
 // 56.0 M -> 44.7 M.  What is left is those: a compute unit's L1 has 256 lines to wait in, and 44.7 M of them at some 0.5 us
 // each take 0.36 ms.  More rows of B in flight (9, 12) or workgroups that go on to further rows with the next entries on
 // their way gain nothing (430 to 530 us).
 //
+// A wavefront lists its quads where all of their rows have fewer than kQuadRow entries and share columns.  The rows of the others,
+// and of quads that turn out not to be worth it, are taken one by one by all the workgroup's slots, with their entries in LDS: where
+// a slot took its own quad's rows it kept the others waiting, and read entry by entry.  us by row_split_kernel, that way and so: a
+// mesh of three unknowns a node and 7 to 11 neighbours, 300,000 rows, a third of them of 32 entries or more, N = 64 102, 187 and
+// 103, N = 128 175, 250 and 163; power law, 1,000,000 rows, N = 64 890, 1,170 and 810; rows of 27 neighbouring columns and one in
+// eight of 40, 400,000 rows, N = 128 227, 280 and 194.  Five wavefronts per SIMD: with four, as the compiler has it by itself, the
+// stencil takes 438 and the mesh 199 at N = 128, with six (and six rows of B in flight) 457 and 160.
+//
 // +0 times a finite element of B adds nothing; an infinity or a NaN would.  A quad with a sum that is not finite is
-// therefore done again row by row, as is, from the start, a quad with a row of kQuadRow entries or more, a row that
-// does not ascend, or too little to share.  Nothing is assumed of the matrix.
+// therefore done again row by row.  Nothing is assumed of the matrix.
 #include "sgap_common.hpp"
 #include "sgap_gather.hpp"
 #include "sgap_quads.hpp"
@@ -31,20 +38,20 @@ namespace {
 
 constexpr int kQuadRecords = 64;  // records of a quad at most (27-point stencil: 54)
 constexpr int kQuadPlaces = 80;   // those, +0 up to a whole batch behind them, and in the last place what belongs to none
-constexpr int kQuadChunk = 160;   // entries staged at a time where rows go one by one
+constexpr int kQuadChunk = 160;   // entries of a quad whose rows go one by one that are in LDS together
 constexpr int kQuadDepth = 6;     // rows of B in flight per lane
 constexpr int kPlainDepth = 8;    // the same where rows go one by one
 static_assert(kQuadRecords + kQuadDepth < kQuadPlaces, "a batch of +0 behind the records");
 
 struct alignas(16) QuadLds {
     union {
+        int32_t row_col[kQuad][1 + kQuadRow];  // the rows' columns from place 1 on, kNoColumn behind them
         struct {
             float val[kQuadPlaces][kQuad];
             int32_t col[kQuadPlaces];
         } rec;
-        StagedEntry staged[kQuadChunk];
+        StagedEntry staged[kQuadChunk];  // where rows go one by one
     };
-    int32_t row_col[kQuad][1 + kQuadRow];  // the rows' columns from place 1 on, kNoColumn behind them
 };
 
 __device__ __forceinline__ bool finite(float x) { return (__float_as_uint(x) & 0x7f800000u) != 0x7f800000u; }
@@ -83,12 +90,17 @@ __device__ __forceinline__ void quad_batch(f32x4 (&acc)[4], const QuadLds& lds, 
 }  // namespace
 
 template <int LC, bool OFF32>
-__global__ __launch_bounds__(kBlock) void row_quads_kernel(SpmmArgs a, TileSched ts)
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(5))) void row_quads_kernel(SpmmArgs a, TileSched ts)
 {
     constexpr int SLOTS = kBlock / LC;
     constexpr int EPL = LC < kQuadRow ? kQuadRow / LC : 1;  // entries of a row per lane
+    constexpr int EACH = (kQuadChunk + LC - 1) / LC;         // the same of kQuadChunk
+    constexpr int NEXT = EACH < 5 ? EACH : 5;                // entries per lane in flight to LDS where a row goes by itself,
+    constexpr int32_t CHUNK = NEXT * LC < kQuadChunk ? NEXT * LC : kQuadChunk;  // of a slot
     constexpr unsigned long long SLOT_MASK = LC == 64 ? ~0ull : (1ull << LC) - 1ull;
     __shared__ QuadLds s_lds[SLOTS];
+    __shared__ int32_t s_ptr[SLOTS][kQuad + 1];  // of the quads whose rows go one by one
+    __shared__ unsigned long long s_open[kWavesPerBlock], s_read[kWavesPerBlock];  // bit: lane, of such a quad; of one not in LDS
 
     const int slot = threadIdx.x / LC;
     const int t = threadIdx.x % LC;
@@ -120,12 +132,16 @@ __global__ __launch_bounds__(kBlock) void row_quads_kernel(SpmmArgs a, TileSched
 #pragma unroll
         for (int i = 0; i <= kQuad; ++i) p[i] = __shfl(mine, i, LC);
     }
-    bool listed = true;
-#pragma unroll
-    for (int i = 0; i < kQuad; ++i) listed = listed && p[i + 1] - p[i] < kQuadRow;
-    const bool staged = listed;  // in registers, and in LDS where the rows go one by one
-    int records = 0;
+    bool listed;
     {
+        bool shorts = true;
+#pragma unroll
+        for (int i = 0; i < kQuad; ++i) shorts = shorts && p[i + 1] - p[i] < kQuadRow;
+        listed = __ballot(!shorts) == 0;  // all quads of the wavefront, or none
+    }
+    const bool loaded = listed;  // into registers
+    int records = 0;
+    if (loaded) {
         int32_t col[kQuad][EPL];
         float val[kQuad][EPL];
 #pragma unroll
@@ -135,56 +151,57 @@ __global__ __launch_bounds__(kBlock) void row_quads_kernel(SpmmArgs a, TileSched
                 const int q = t + u * LC;
                 col[i][u] = kNoColumn;
                 val[i][u] = 0.0f;
-                if (staged && q < p[i + 1] - p[i]) {
+                if (q < p[i + 1] - p[i]) {
                     col[i][u] = load_stream(a.colidx + p[i] + q);
                     val[i][u] = load_stream(a.vals + p[i] + q);
                 }
             }
         // Nothing below is left out by a lane on its own: every lane of the wavefront comes by every ballot and shuffle.
+        auto put_columns = [&] {
 #pragma unroll
-        for (int i = 0; i < kQuad; ++i)
+            for (int i = 0; i < kQuad; ++i)
 #pragma unroll
-            for (int u = 0; u < EPL; ++u) {
-                const int q = t + u * LC;
-                if (q < kQuadRow) lds.row_col[i][1 + q] = col[i][u];
-                if (q == 0) lds.row_col[i][0] = -1;
-            }
-        wave_lds_order();
-        // columns without order, told by the second row and the first, or else (where a line of the grid ends between them) by
-        // the fourth and the third: nothing is listed (300,000 rows of 27 entries, N = 64: 299 us where they were, 294 so, 287
-        // by the plain kernel; N = 128: 605, 587 and 593; the second look: 75 x 75 x 30 points, N = 36 56.9 -> 49.1, by the plain
-        // kernel 49.6; 99 x 97 x 31, N = 56 88.9 -> 81.1, by that 88.9)
-        auto shares = [&](const int32_t* __restrict__ above, const int32_t (&row)[EPL], int32_t entries) {
+                for (int u = 0; u < EPL; ++u) {
+                    const int q = t + u * LC;
+                    if (q < kQuadRow) lds.row_col[i][1 + q] = col[i][u];
+                    if (q == 0) lds.row_col[i][0] = -1;
+                }
+            wave_lds_order();
+        };
+        // whether a row shares columns with the row above: half of them, at its own place or the next one above (16 lanes), or a
+        // quarter, wherever
+        auto shares = [&](int above) {
+            const int32_t (&row)[EPL] = col[above + 1];
             int seen = 0;
 #pragma unroll
             for (int u = 0; u < EPL; ++u) {
-                const int lo = below(above + 1, row[u]);
-                seen += __popc((uint32_t)slot_ballot(row[u] != kNoColumn && above[1 + lo] == row[u]));
+                bool found;
+                if constexpr (LC == 16) {
+                    const int32_t own = col[above][u];
+                    found = own == row[u] || __builtin_amdgcn_update_dpp(kNoColumn, own, 0x101, 0xF, 0xF, false) == row[u];  // row_shl:1
+                } else {
+                    const int32_t* __restrict__ columns = lds.row_col[above] + 1;
+                    found = columns[below(columns, row[u])] == row[u];
+                }
+                seen += __popc((uint32_t)slot_ballot(row[u] != kNoColumn && found));
             }
-            return 4 * seen >= entries;
+            if constexpr (LC == 16) return 2 * seen >= p[above + 2] - p[above + 1];
+            return 4 * seen >= p[above + 2] - p[above + 1] && p[kQuad] - p[0] - (kQuad - 1) * seen <= kQuadRecords;
         };
-        bool some_shared = shares(lds.row_col[0], col[1], p[2] - p[1]);
-        if (__ballot(listed && !some_shared) != 0) {
-            const bool others = shares(lds.row_col[2], col[3], p[4] - p[3]);
+        // columns without order, told by the second row and the first, or else (where a line of the grid ends between them) by
+        // the fourth and the third: nothing is listed (without the second look: 75 x 75 x 30 points, N = 36 56.9 us, 49.1 with it,
+        // 49.6 by row_split_kernel; 99 x 97 x 31, N = 56 88.9, 81.1 and 88.9)
+        if constexpr (LC > 16) put_columns();
+        bool some_shared = shares(0);
+        if (__ballot(!some_shared) != 0) {
+            const bool others = shares(2);
             some_shared = some_shared || others;
         }
-        listed = listed && some_shared;
-        if (__ballot(listed) != 0) {
-            // (an empty place counts as a record of the quad's first column and of no row)
-            int32_t some = kNoColumn;
-#pragma unroll
-            for (int i = kQuad - 1; i >= 0; --i) {
-                const int32_t first = __shfl(col[i][0], 0, LC);
-                some = first != kNoColumn ? first : some;
-            }
-#pragma unroll
-            for (int q = t; q < kQuadPlaces; q += LC) {
-                *reinterpret_cast<float4*>(lds.rec.val[q]) = float4{0.0f, 0.0f, 0.0f, 0.0f};
-                lds.rec.col[q] = some;
-            }
-            wave_lds_order();
-            int before[kQuad][EPL][kQuad];  // of row j, the columns below this one
-            uint32_t opens[kQuad];          // bit q: the row's entry q opens a record
+        listed = __ballot(!some_shared) == 0;
+        if (listed) {
+            if constexpr (LC == 16) put_columns();
+            uint32_t before[kQuad][EPL];  // byte j: of row j, the columns below this one
+            uint32_t opens[kQuad];        // bit q: the row's entry q opens a record
             bool descends = false;
 #pragma unroll
             for (int i = 0; i < kQuad; ++i) {
@@ -195,43 +212,70 @@ __global__ __launch_bounds__(kBlock) void row_quads_kernel(SpmmArgs a, TileSched
                     const int32_t c = col[i][u];
                     const bool have = c != kNoColumn;
                     descends = descends || (have && lds.row_col[i][q < kQuadRow ? q : 0] >= c);
+                    before[i][u] = 0;
+                    bool found = false;
 #pragma unroll
                     for (int j = 0; j < kQuad; ++j) {
                         const int32_t* __restrict__ row = lds.row_col[j] + 1;
-                        before[i][u][j] = j == i ? q : below(row, c);
+                        const int lower = j == i ? q : below(row, c);
+                        before[i][u] |= (uint32_t)lower << (8 * j);
+                        if (j == i - 1) found = have && row[lower] == c;
                     }
-                    const bool found = i > 0 && have && lds.row_col[i > 0 ? i - 1 : 0][1 + before[i][u][i > 0 ? i - 1 : 0]] == c;
                     const uint32_t here = (uint32_t)slot_ballot(have && !found);
                     opens[i] |= here << (u * LC % kQuadRow);
                 }
                 records += __popc(opens[i]);
             }
+            // (an empty place counts as a record of the quad's first column and of no row)
+            int32_t some = kNoColumn;
+#pragma unroll
+            for (int i = kQuad - 1; i >= 0; --i) {
+                const int32_t first = __shfl(col[i][0], 0, LC);
+                some = first != kNoColumn ? first : some;
+            }
+            wave_lds_order();  // the rows' columns have been read
+#pragma unroll
+            for (int q = t; q < kQuadPlaces; q += LC) {
+                *reinterpret_cast<float4*>(lds.rec.val[q]) = float4{0.0f, 0.0f, 0.0f, 0.0f};
+                lds.rec.col[q] = some;
+            }
+            wave_lds_order();
 #pragma unroll
             for (int i = 0; i < kQuad; ++i)
 #pragma unroll
                 for (int u = 0; u < EPL; ++u) {
                     int mine = 0;
 #pragma unroll
-                    for (int j = 0; j < kQuad; ++j) mine += __popc(opens[j] & ((1u << (before[i][u][j] & 31)) - 1u));
+                    for (int j = 0; j < kQuad; ++j) mine += __popc(__builtin_amdgcn_ubfe(opens[j], 0u, before[i][u] >> (8 * j) & 31u));
                     mine = col[i][u] != kNoColumn && mine < kQuadRecords ? mine : kQuadPlaces - 1;
                     lds.rec.col[mine] = col[i][u];
                     lds.rec.val[mine][i] = val[i][u];
                 }
             // worth it from a quarter shared on
-            listed = listed && slot_ballot(descends) == 0 && records <= kQuadRecords && 4 * records <= 3 * (p[kQuad] - p[0]);
+            listed = slot_ballot(descends) == 0 && records <= kQuadRecords && 4 * records <= 3 * (p[kQuad] - p[0]);
         }
         wave_lds_order();
-        if (staged && !listed) {
-            // row i's entries from kQuadRow * i on
+        if (!listed) {
 #pragma unroll
             for (int i = 0; i < kQuad; ++i)
 #pragma unroll
                 for (int u = 0; u < EPL; ++u)
-                    if (t + u * LC < kQuadRow) lds.staged[kQuadRow * i + t + u * LC] = StagedEntry{col[i][u], val[i][u]};
+                    if (t + u * LC < p[i + 1] - p[i]) lds.staged[p[i] - p[0] + t + u * LC] = StagedEntry{col[i][u], val[i][u]};
         }
-        wave_lds_order();
     }
-    const bool in_lds = staged && !listed;
+    const bool in_lds = !listed && p[kQuad] - p[0] <= kQuadChunk;  // the whole quad, one row after the other
+    if (in_lds && !loaded) {
+        StagedEntry e[EACH];
+#pragma unroll
+        for (int u = 0; u < EACH; ++u)
+            if (t + u * LC < p[kQuad] - p[0]) {
+                e[u].col = load_stream(a.colidx + p[0] + t + u * LC);
+                e[u].val = load_stream(a.vals + p[0] + t + u * LC);
+            }
+#pragma unroll
+        for (int u = 0; u < EACH; ++u)
+            if (t + u * LC < p[kQuad] - p[0]) lds.staged[t + u * LC] = e[u];
+    }
 
     bool done = false;
     if (__ballot(listed) != 0) {
@@ -266,45 +310,110 @@ __global__ __launch_bounds__(kBlock) void row_quads_kernel(SpmmArgs a, TileSched
             }
         }
     }
-    if (!done) {
-        for (int i = 0; i < kQuad && row_first + i < a.M; ++i) {
-            int32_t begin = p[0], end = p[1];
-            if (i == 1) { begin = p[1]; end = p[2]; }
-            if (i == 2) { begin = p[2]; end = p[3]; }
-            if (i == 3) { begin = p[3]; end = p[4]; }
-            Vec<4> acc;
-            acc.zero();
-            for (int32_t base = begin; base < end; base += kQuadChunk) {
-                const int32_t cnt = end - base < kQuadChunk ? end - base : kQuadChunk;
-                if (!in_lds) {
-                    wave_lds_order();
-                    for (int q = t; q < cnt; q += LC) {
-                        StagedEntry e;
-                        e.col = load_stream(a.colidx + base + q);
-                        e.val = load_stream(a.vals + base + q);
-                        lds.staged[q] = e;
-                    }
-                    wave_lds_order();
-                }
-                const uint32_t at = in_lds ? kQuadRow * i : 0;
-                if (k_ok) gather_fma<4, 1, kPlainDepth>(acc, lds.staged, at, at + (uint32_t)cnt, B);
+
+    // The rows of the quads that are left, a row to a slot, whichever slot's they are: first those whose entries are in LDS, then
+    // those that are read into it.
+    const int wave = threadIdx.x / kWave;
+    const unsigned long long open = __ballot(!done);
+    if (threadIdx.x % kWave == 0) s_open[wave] = open;
+    if (open != 0) {
+        const unsigned long long read = __ballot(!done && !in_lds);
+        if (threadIdx.x % kWave == 0) s_read[wave] = read;
+        if (t <= kQuad) s_ptr[slot][t] = t == 0 ? p[0] : t == 1 ? p[1] : t == 2 ? p[2] : t == 3 ? p[3] : p[4];
+    }
+    __syncthreads();
+    uint32_t here = 0, elsewhere = 0;  // bit: slot
+#pragma unroll
+    for (int w = 0; w < kWavesPerBlock; ++w) {
+        const unsigned long long all = s_open[w];
+        if (all == 0) continue;
+        const unsigned long long read = s_read[w];
+#pragma unroll
+        for (int l = 0; l < kWave / LC; ++l) {
+            here |= (uint32_t)((all & ~read) >> (l * LC) & 1) << (w * (kWave / LC) + l);
+            elsewhere |= (uint32_t)(read >> (l * LC) & 1) << (w * (kWave / LC) + l);
+        }
+    }
+    // number n of the rows of the slots in mask
+    auto row_number = [&](uint32_t mask, int n) {
+        for (int i = 0; i < n / kQuad; ++i) mask &= mask - 1;
+        return (__ffs(mask) - 1) * kQuad + n % kQuad;
+    };
+    auto store = [&](int row, const Vec<4>& sum) {
+        const int64_t r = (int64_t)block * (SLOTS * kQuad) + row;
+        if (k_ok && r < a.M) store_vec_stream<4>(a.C + r * a.N + k_lane, sum);
+    };
+    for (int n = slot; n < __popc(here) * kQuad; n += SLOTS) {
+        const int row = row_number(here, n);
+        const int32_t* __restrict__ ptr = s_ptr[row / kQuad];
+        const uint32_t at = (uint32_t)(ptr[row % kQuad] - ptr[0]);
+        Vec<4> acc;
+        acc.zero();
+        if (k_ok) gather_fma<4, 1, kPlainDepth>(acc, s_lds[row / kQuad].staged, at, (uint32_t)(ptr[row % kQuad + 1] - ptr[0]), B);
+        store(row, acc);
+    }
+    if (elsewhere == 0) return;
+    if (here != 0) __syncthreads();  // the rows in LDS are done with
+    const int rows = __popc(elsewhere) * kQuad;
+    StagedEntry next[NEXT];  // of a row, the next ones on their way while these are gathered for
+    int row = 0;
+    int32_t base = 0, end = 0;
+    auto fetch = [&] {
+#pragma unroll
+        for (int u = 0; u < NEXT; ++u)
+            if (t + u * LC < CHUNK && base + t + u * LC < end) {
+                next[u].col = load_stream(a.colidx + base + t + u * LC);
+                next[u].val = load_stream(a.vals + base + t + u * LC);
             }
-            if (k_ok) store_vec_stream<4>(a.C + (row_first + i) * a.N + k_lane, acc);
+    };
+    auto begin_row = [&](int n) {
+        row = row_number(elsewhere, n);
+        base = s_ptr[row / kQuad][row % kQuad];
+        end = s_ptr[row / kQuad][row % kQuad + 1];
+    };
+    Vec<4> acc;
+    acc.zero();
+    if (slot < rows) {
+        begin_row(slot);
+        fetch();
+    }
+    for (int n = slot; n < rows;) {
+        const int this_row = row;
+        const int32_t cnt = end - base < CHUNK ? end - base : CHUNK;
+        const bool last = end - base <= CHUNK;
+        wave_lds_order();
+#pragma unroll
+        for (int u = 0; u < NEXT; ++u)
+            if (t + u * LC < cnt) lds.staged[t + u * LC] = next[u];
+        wave_lds_order();
+        base += CHUNK;
+        if (last) {
+            n += SLOTS;
+            if (n < rows) begin_row(n);
+        }
+        if (n < rows) fetch();
+        if (k_ok) gather_fma<4, 1, kPlainDepth>(acc, lds.staged, 0, (uint32_t)cnt, B);
+        if (last) {
+            store(this_row, acc);
+            acc.zero();
         }
     }
 }
 
-// Rows of more than a dozen entries and of no more than kQuadRow in the mean, whose columns take 16 lanes or more: on those
-// nothing is lost where the quads turn out to share nothing (in the kernel, and 100,000 rows of 31 entries, N = 128: 215 us
-// by the plain kernel, 213 so).  Enough blocks of rows for the chip, since a quad's rows are one after the other then: 312
-// blocks of 64 rows of 20 entries without order take 17 us and 12 by the plain kernel, 938 of 16 entries 31.1 and 30.9;
-// stencils gain from 844 blocks of 32 rows on (N = 128: 17.3 -> 14.2 us) and from 938 of 64 (19.1 -> 18.2).
+// Rows of more than a dozen entries and of no more than kQuadRow in the mean, whose columns take 16 lanes or more, and enough blocks
+// of them for the chip, since a quad's rows are one after the other where it is not listed.  us by row_split_kernel and so, of
+// 27-point stencils, rows of 25 columns without order and the first mesh above: 27,000 rows, N = 128 17.0 / 13.7, 38.4 / 42.3 and
+// 18.4 / 21.0; 54,000 rows 31.7 / 26.3, 88.0 / 88.8 and 35.3 / 40.2; 110,000 rows 59.6 / 46.1, 196 / 195 and 67.5 / 63.8; in 16 lanes,
+// N = 64, 91,000 to 110,000 rows 30.0 / 31.0, 91.7 / 96.2 and 40.6 / 45.4; 140,000 rows 43.4 / 42.9, 121 / 123; 300,000 rows without order
+// 182 / 184.  What still loses by more than that in 16 lanes are grid points with a random part of the 125 around each, which share a little more
+// than half (268,800 rows, N = 40 81 / 85, N = 64 87 / 93; N = 128 152 / 126, and with a sixth of the rows of 32 entries or more
+// 175 / 171 to 204, by where the operands lie).
 // A column tile has to fit one pass of its lanes: the kernel makes no second one (row_split_kernel does).
-bool row_quads_apply(const SpmmArgs& a, int lc, int64_t tile_cols, double mean_row, int compute_units)
+bool row_quads_apply(int64_t M, int lc, int64_t tile_cols, double mean_row, int compute_units)
 {
     if (tile_cols > (int64_t)lc * 4) return false;
-    const int64_t blocks = a.M / ((int64_t)(kBlock / lc) * kQuad);
-    return lc >= 16 && mean_row > 12.0 && mean_row <= (double)kQuadRow && blocks >= (int64_t)(lc >= 32 ? 3 : 5) * compute_units;
+    const int64_t blocks = M / ((int64_t)(kBlock / lc) * kQuad);
+    return lc >= 16 && mean_row > 12.0 && mean_row <= (double)kQuadRow && blocks >= (int64_t)(lc >= 32 ? 5 : 8) * compute_units;
 }
 
 // lc = chunk lanes that hold a column tile in one pass (16, 32 or 64)

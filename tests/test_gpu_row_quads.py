@@ -1,9 +1,11 @@
 """Row-split, serial strategy, four neighbouring rows together: rows, sharing and orders at which a quad is listed or goes row by
 row, widths at the edges of lanes and column tiles, planes dealt over the dies; exact on integer-valued inputs."""
+import ctypes
 import functools
 
 import numpy as np
 import pytest
+import torch
 
 import oracle
 from paper_2209_02882_amd import binding
@@ -12,14 +14,14 @@ from paper_2209_02882_amd import workloads as wl
 from gpu_util import DeviceProblem
 
 pytestmark = pytest.mark.gpu
-ROWS = 82_003  # enough blocks of 64 rows on 256 compute units, and no multiple of four
+ROWS, MORE_ROWS = 82_003, 150_003  # no multiples of four; up to 64 columns want more blocks of them (check asserts that they are enough)
 
 
 @functools.lru_cache
-def csr(kind):
+def csr(kind, N=128):
     """The rows of that kind, repeated with a period of 400 rows and shifted along."""
     period = [rows_of(kind)(r) for r in range(400)]
-    columns = [period[r % 400] + 40 * (r // 400) for r in range(ROWS)]
+    columns = [period[r % 400] + 40 * (r // 400) for r in range(MORE_ROWS if N <= 64 else ROWS)]
     rowptr = np.concatenate([[0], np.cumsum([c.size for c in columns])]).astype(np.int32)
     return rowptr, np.concatenate(columns).astype(np.int32)
 
@@ -40,6 +42,9 @@ def rows_of(kind):
         return lambda r: band(r, 20)[::-1] if r % 8 < 4 and r % 3 == 0 else np.sort(np.concatenate([band(r, 16), band(r, 3)])) if r % 16 > 12 else band(r, 18)
     if kind == "no column in common within the first two, or the last two":
         return lambda r: np.concatenate([band(r, 18) + 500 * (r % 4 > (0, 2)[r // 4 % 2])])
+    if kind == "long rows":  # quads of 160 entries and one more, and of more than are read at a time; a wavefront's quads among them
+        long = {0: 100, 4: 101, 9: 79, 10: 80, 11: 81, 14: 160, 40: 161, 41: 0, 42: 0, 43: 0, 200: 41, 204: 700, 205: 321, 206: 33, 399: 160}
+        return lambda r: band(r, long.get(r, 20))
     if kind == "with empty rows":
         return lambda r: band(r, 28 if r % 5 else 0) if r % 40 > 3 else band(0, 0)
     return lambda r: some[r]  # without order
@@ -47,23 +52,25 @@ def rows_of(kind):
 
 KINDS = ["band", "31, 32 and 33 entries", "as many records as there is room for, and one more", "in the row before the last",
          "descending and repeated",
-         "no column in common within the first two, or the last two", "with empty rows", "without order"]
+         "no column in common within the first two, or the last two", "with empty rows", "without order", "long rows"]
 
 
-def check(p, points, **knobs):
+def check(p, points, quads=1, **knobs):
+    units = torch.cuda.get_device_properties(0).multi_processor_count
     ref, _ = oracle.spmm_csr(p.M, p.K, p.N, p.rowptr, p.colidx, p.vals, p.B, nthreads=8, bound=False)
     dp = DeviceProblem(p)
     for g in points:
         cfg = binding.make_config(g, "serial", "row_split", **knobs)
+        assert binding.load().sgap_debug_row_quads(p.M, p.N, p.colidx.size, ctypes.byref(cfg), units) == quads
         assert np.array_equal(dp.run_cfg(cfg).cpu().numpy().astype(np.float64), ref), (g, knobs)
 
 
 @pytest.mark.parametrize("kind", KINDS)
 @pytest.mark.parametrize("N", [61, 64, 66, 130, 260])
 def test_rows_at_the_edges(N, kind):
-    rowptr, colidx = csr(kind)
+    rowptr, colidx = csr(kind, N)
     rng, K = np.random.default_rng(N), int(colidx.max()) + 1
-    p = wl.SpmmProblem("quads", ROWS, K, N, rowptr, colidx, wl.fill_values(rng, colidx.size, True),
+    p = wl.SpmmProblem("quads", rowptr.size - 1, K, N, rowptr, colidx, wl.fill_values(rng, colidx.size, True),
                        wl.fill_values(rng, K * N, True).reshape(K, N))
     check(p, (1, 4))
     if N == 260:
@@ -79,12 +86,12 @@ def test_column_tiles_wider_than_a_wavefront(N, tile_cols):
     rng, K = np.random.default_rng(N), int(colidx.max()) + 1
     p = wl.SpmmProblem("quads", ROWS, K, N, rowptr, colidx, wl.fill_values(rng, colidx.size, True),
                        wl.fill_values(rng, K * N, True).reshape(K, N))
-    check(p, (1, 2, 4), tile_cols=tile_cols)
+    check(p, (1, 2, 4), quads=0, tile_cols=tile_cols)
 
 
 @pytest.mark.parametrize("N", [40, 64, 100, 132])  # 40: the rows as they are decide, not the lanes they take
 def test_planes_dealt_over_the_dies(N):
-    nx, ny, nz = 61, 103, 19  # reach 6,345 rows, the last planes are left over
+    nx, ny, nz = 61, 103, 19 if N > 64 else 23  # reach 6,345 rows, the last planes are left over
     x, y, z = (v.ravel() for v in np.meshgrid(np.arange(nx), np.arange(ny), np.arange(nz), indexing="ij"))
     order = np.lexsort((x, y, z))
     x, y, z = x[order], y[order], z[order]
@@ -106,12 +113,12 @@ def test_planes_dealt_over_the_dies(N):
 
 def test_what_is_not_finite_stays_in_its_rows():
     N = 64
-    rowptr, colidx = csr("band")
+    rowptr, colidx = csr("band", N)
     rng, K = np.random.default_rng(3), int(colidx.max()) + 1
     vals, B = wl.fill_values(rng, colidx.size, True), wl.fill_values(rng, K * N, True).reshape(K, N)
     vals[vals == 0] = 1
     B[70, 5], B[300, 60] = np.inf, np.nan
-    p = wl.SpmmProblem("quads", ROWS, K, N, rowptr, colidx, vals, B)
+    p = wl.SpmmProblem("quads", rowptr.size - 1, K, N, rowptr, colidx, vals, B)
     got = DeviceProblem(p).run_cfg(binding.make_config(1, "serial", "row_split")).cpu().numpy()
     has = lambda c: np.add.reduceat(colidx == c, rowptr[:-1]) > 0  # noqa: E731
     assert np.isinf(got[has(70), 5]).all() and np.isnan(got[has(300), 60]).all()
