@@ -339,26 +339,26 @@ struct Instance {
 };
 
 // Calls f with the instance for a problem: f(instance, positions per tile).
-template <int LC, int VEC, int E, typename F>
+template <int LC, int VEC, int E, bool RAGGED, typename F>
 auto with_form(const SpmmArgs& a, F&& f)
 {
     constexpr int TILE = kBlock / LC * E;
-    if (VEC > 1 && a.N % VEC != 0)
-        return offsets_fit_32(a) ? f(Instance<nnz_narrow_kernel<LC, VEC, E, true, (VEC > 1)>>{}, TILE)
-                                 : f(Instance<nnz_narrow_kernel<LC, VEC, E, false, (VEC > 1)>>{}, TILE);
-    return offsets_fit_32(a) ? f(Instance<nnz_narrow_kernel<LC, VEC, E, true, false>>{}, TILE)
-                             : f(Instance<nnz_narrow_kernel<LC, VEC, E, false, false>>{}, TILE);
+    return offsets_fit_32(a) ? f(Instance<nnz_narrow_kernel<LC, VEC, E, true, RAGGED>>{}, TILE)
+                             : f(Instance<nnz_narrow_kernel<LC, VEC, E, false, RAGGED>>{}, TILE);
 }
 
 template <typename F>
 auto with_kernel(const SpmmArgs& a, F&& f)
 {
     switch (a.N) {
-        case 1: return with_form<1, 1, 4>(a, f);
-        case 2: return with_form<1, 2, 4>(a, f);
-        case 3: return with_form<2, 2, 8>(a, f);
-        case 4: return with_form<1, 4, 4>(a, f);
-        default: return a.N <= 8 ? with_form<2, 4, 8>(a, f) : with_form<4, 4, 8>(a, f);
+        case 1: return with_form<1, 1, 4, false>(a, f);
+        case 2: return with_form<1, 2, 4, false>(a, f);
+        case 3: return with_form<2, 2, 8, true>(a, f);
+        case 4: return with_form<1, 4, 4, false>(a, f);
+        case 8: return with_form<2, 4, 8, false>(a, f);
+        case 5: case 6: case 7: return with_form<2, 4, 8, true>(a, f);
+        case 12: case 16: return with_form<4, 4, 8, false>(a, f);
+        default: return with_form<4, 4, 8, true>(a, f);
     }
 }
 
@@ -379,6 +379,7 @@ NnzPlan plan_nnz_narrow(const SpmmArgs& a)
 
 hipError_t launch_nnz_narrow(const SpmmArgs& a, int compute_units, int64_t nnz_hint, hipStream_t s)
 {
+    if (a.N < 1 || a.N > kNarrowColumns) return hipErrorInvalidValue;
     return with_kernel(a, [&](auto instance, int tile) {
         instance.launch(persistent_grid(instance.per_cu(), compute_units, nnz_hint, tile), a, s);
         return hipGetLastError();

@@ -297,7 +297,7 @@ struct Launch {
     template <int G, int LC, int VEC>
     void operator()() const
     {
-        if constexpr (VEC != 4) return;  // N <= kNarrowColumns: sgap_nnz_narrow.hip
+        if constexpr (VEC != 4) return;  // (launch_group turns them away)
         else if (off32) {
             if (merge) pick_columns<G, LC, VEC, true, true>(); else pick_columns<G, LC, VEC, true, false>();
         } else {
@@ -311,6 +311,7 @@ template <int G>
 inline hipError_t launch_group(const SpmmArgs& a, int lc, int vec, int compute_units, int64_t nnz_hint, bool merge,
                                hipStream_t s)
 {
+    if (vec != 4) return hipErrorInvalidValue;  // N <= kNarrowColumns: sgap_nnz_narrow.hip
     if (!dispatch_lc<G>(lc, vec, Launch{a, compute_units, nnz_hint, offsets_fit_32(a), merge, s}))
         return hipErrorInvalidValue;
     return hipGetLastError();
