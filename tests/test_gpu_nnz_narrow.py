@@ -2,6 +2,7 @@
 wavefront, of a round of row pointers and of a tile (512 and 1,024 entries); exact on integer-valued inputs."""
 import numpy as np
 import pytest
+import torch
 
 import oracle
 from paper_2209_02882_amd import binding
@@ -61,3 +62,20 @@ def test_what_is_not_finite_stays_in_its_row(N):
     with_4000 = np.add.reduceat(np.append(colidx == 4000, False), rowptr[:-1]).astype(bool) & (lengths > 0)
     assert np.isnan(got[with_4000]).all() and np.isinf(got[with_7 & ~with_4000]).all()
     assert np.isfinite(got[~with_7 & ~with_4000]).all()
+
+
+@pytest.mark.parametrize("N", [1, 2, 3, 4, 7, 8, 13, 16])
+def test_offsets_of_64_bits(N):
+    """Columns on both sides of 4 GiB of B."""
+    lengths = np.random.default_rng(N).integers(0, 60, 3000)
+    rng, k = np.random.default_rng(3), 6200
+    rowptr, colidx = wl.csr_from_lengths(rng, lengths, k)
+    vals, B = wl.fill_values(rng, colidx.size, True), wl.fill_values(rng, k * N, True).reshape(k, N)
+    ref, _ = oracle.spmm_csr(lengths.size, k, N, rowptr, colidx, vals, B, nthreads=8, bound=False)
+    first = 2**32 // (4 * N) - k // 2
+    wide = torch.zeros((first + k, N), device="cuda")
+    wide[first:] = torch.from_numpy(B)
+    C = torch.full((lengths.size, N), float("nan"), device="cuda")
+    rp, ci, va = (torch.from_numpy(x).cuda() for x in (rowptr, colidx + np.int32(first), vals))
+    binding.sgap_spmm_csr_cfg(lengths.size, first + k, N, rp, ci, va, wide, C, binding.make_config(8, "parallel", "nnz_balanced"))
+    assert np.array_equal(C.cpu().numpy().astype(np.float64), ref)

@@ -125,3 +125,22 @@ def test_what_is_not_finite_stays_in_its_rows():
     rest = np.ones(got.shape, bool)
     rest[has(70), 5] = rest[has(300), 60] = False
     assert np.isfinite(got[rest]).all()
+
+
+@pytest.mark.parametrize("N,tile_cols", [(64, 0), (61, 0), (128, 0), (256, 256)])  # 16, 32 and 64 lanes
+def test_offsets_of_64_bits(N, tile_cols):
+    """Columns on both sides of 4 GiB of B."""
+    rowptr, colidx = csr("long rows", N)
+    rng, k = np.random.default_rng(N), int(colidx.max()) + 1
+    vals, B = wl.fill_values(rng, colidx.size, True), wl.fill_values(rng, k * N, True).reshape(k, N)
+    ref, _ = oracle.spmm_csr(rowptr.size - 1, k, N, rowptr, colidx, vals, B, nthreads=8, bound=False)
+    first = 2**32 // (4 * N) - k // 2
+    wide = torch.zeros((first + k, N), device="cuda")
+    wide[first:] = torch.from_numpy(B)
+    C = torch.full((rowptr.size - 1, N), float("nan"), device="cuda")
+    rp, ci, va = (torch.from_numpy(x).cuda() for x in (rowptr, colidx + np.int32(first), vals))
+    cfg = binding.make_config(1, "serial", "row_split", tile_cols=tile_cols)
+    units = torch.cuda.get_device_properties(0).multi_processor_count
+    assert binding.load().sgap_debug_row_quads(rowptr.size - 1, N, colidx.size, ctypes.byref(cfg), units) == 1
+    binding.sgap_spmm_csr_cfg(rowptr.size - 1, first + k, N, rp, ci, va, wide, C, cfg)
+    assert np.array_equal(C.cpu().numpy().astype(np.float64), ref)
