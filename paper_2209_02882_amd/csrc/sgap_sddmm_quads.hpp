@@ -400,10 +400,11 @@ __device__ __forceinline__ void sddmm_quads(const SpmmArgs& a, const float* __re
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave));
     const int32_t M = (int32_t)a.M;
     const uint32_t die = blockIdx.x % kQuadDies, blocks = quad_blocks(a.M), per_die = quad_turns(a.M);
-    // (not worth the look at a row where X1 is small: 212,040 rows of 100 columns 133.3 us with it, 131.4 without; 1,000,000 of
-    // 128 529 and 547)
+    // (27-point stencils, G = 16, in one run of rows for each die and so: 1,000,000 rows, J = 256 1,022 and 991 us; 200 x 200 x 12
+    // points, J = 128 250 and 245, J = 256 569 and 484; 212,040 rows, J = 72 122.9 and 123.3, J = 256 204 and 201)
     uint32_t share = 0;
-    if (a.M * columns.row_bytes > 64 * kDealBytes) share = (plane_share(a, kQuadDies, columns.row_bytes) + kQuadBlock / 2) / kQuadBlock;
+    if (a.M * columns.row_bytes > kQuadDies * kDealBytes)  // (else a die's run of rows of X2T fits its L2)
+        share = (plane_share(a, kQuadDies, columns.row_bytes) + kQuadBlock / 2) / kQuadBlock;
 
     // first row of this wavefront's quad in a turn (M: none), and its row pointers, number l in lane l
     auto quad_of = [&](uint32_t turn) {

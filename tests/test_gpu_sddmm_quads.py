@@ -122,3 +122,23 @@ def test_no_less_exact_than_entry_by_entry(J):
             error.append(np.linalg.norm(out.cpu().numpy() - ref) / np.linalg.norm(ref))
         print(f"J={J} G={g} by quads {error[0]:.4g}, entry by entry {error[1]:.4g}", flush=True)
         assert error[0] <= 1.01 * error[1], g
+
+
+@pytest.mark.parametrize("J", [100, 128, 250, 256])
+def test_planes_dealt_over_the_dies(J):
+    """Each die takes its share of every plane; the last planes are left over."""
+    nx, ny, nz = 61, 103, 23
+    at = np.arange(nx * ny * nz)
+    x, y, z = at % nx, at // nx % ny, at // (nx * ny)
+    columns, inside = [], []
+    for dz in (-1, 0, 1):
+        for dy in (-1, 0, 1):
+            for dx in (-1, 0, 1):
+                inside.append((x + dx >= 0) & (x + dx < nx) & (y + dy >= 0) & (y + dy < ny) & (z + dz >= 0) & (z + dz < nz))
+                columns.append((at + dx + nx * (dy + ny * dz)).astype(np.int32))
+    inside, columns = np.stack(inside, 1), np.stack(columns, 1)
+    p, X1 = problem("planes", J, np.concatenate([[0], np.cumsum(inside.sum(1))]).astype(np.int32), columns[inside])
+    assert 3 * nx * ny * J * 4 > 4 << 20 and by_quads(p, 16) == 1
+    ref, _ = oracle.sddmm_csr(p.M, p.K, p.N, p.rowptr, p.colidx, p.vals, X1, p.B, nthreads=8, bound=False)
+    got = DeviceProblem(p).run_sddmm(torch.from_numpy(X1).cuda(), 16, "parallel").cpu().numpy()
+    assert np.array_equal(got.astype(np.float64), ref)
