@@ -101,7 +101,14 @@ typedef enum {
  *   consecutive units by itself and flushes its register when the row changes
  *   ("conditional" reduction).
  *     row-split schedule   : lane = group_size consecutive rows
- *       ({<g row, c col>, 1}, Section 6.1), plain stores.
+ *       ({<g row, c col>, 1}, Section 6.1), plain stores.  Where nnz_hint says
+ *       that rows have more than 12 and up to 32 entries in the mean, column
+ *       tiles have more than 32 and up to 256 columns and there are enough
+ *       rows for the chip (on 256 compute units 131,072 where a tile has up to
+ *       64 columns, 40,960 up to 128, 20,480 beyond), group sizes 1, 2 and 4
+ *       name the same launch: a lane has four consecutive rows, and a row of B
+ *       that several of them want is gathered once.  Setting block_size or
+ *       persistent (below) gives the launch row by row.
  *     nnz-balanced schedule: lane = group_size consecutive stored entries
  *       ({<g nnz, c col>, 1}, Section 6.1), or fewer where that many per lane
  *       are more than a tile has (a tile of 1,024 entries at N = 64 has 64 for
@@ -350,8 +357,16 @@ int sgap_spmm_csr_cfg_static(int64_t M, int64_t K, int64_t N,
  *             SGAP_REDUCE_PARALLEL: group_size lanes share a stored entry,
  *             split j between them and tree-sum; SGAP_REDUCE_SERIAL: every
  *             lane computes group_size consecutive stored entries by itself.
- *   nnz_hint  rowptr[M] if the host knows it, else -1 (sizes the grid; 0
- *             returns at once).
+ *             With the parallel strategy, J from 72 to 128 and groups of 8, 16
+ *             or 32 (J from 136 to 256: 16, 32 or 64), nnz_hint of 1,500,000
+ *             and more (3,000,000 at J = 128), 12 to 32 of them a row, and X2T
+ *             below 4 GiB, the device looks at a few rows; where neighbours
+ *             share enough columns, four rows are taken together and the
+ *             lanes of an entry are the library's (its chains of additions
+ *             are no longer than with group_size lanes).
+ *   nnz_hint  rowptr[M] if the host knows it, else -1 (sizes the grid and, as
+ *             above, chooses between launches of the same result; 0 returns at
+ *             once).
  * Every output has one writer: no atomics, results are reproducible run to
  * run.  Asynchronous on `stream`; ownership and errors as for sgap_spmm_csr.
  * J == 0 writes zeros.  colidx, vals and out_vals may be null only for a

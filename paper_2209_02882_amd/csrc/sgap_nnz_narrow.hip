@@ -19,6 +19,8 @@
 // come 200 MB of values and the zeroing pass.  us, R-MAT with 2^21 rows and 50 M entries, one entry per lane / E:
 //   N = 1 418 / 285   N = 2 359 / 315   N = 4 396 / 340   N = 8 646 / 455   N = 16 1,112 / 614;
 //   2^16 rows and 0.9 M entries: 18.5 / 11.0, 19.0 / 11.7, 20.0 / 12.7, 26.5 / 15.1, 34.5 / 18.2
+// Rows of one entry each lose, since every entry is then a store by itself, and neighbouring lanes' are E rows apart: 2,000,000 of
+// them, N = 1 37.1 / 41.5 (G = 64), N = 8 63.8 / 66.8 and N = 16 76.7 / 84.9 (G = 8); rows of three gain again.
 // E = 4 where one lane holds the columns (with eight N = 4 takes 357 us, N = 2 320, N = 1 286), 8 elsewhere (N = 8 with
 // four 440 us, but 16.1 on the small matrix).
 #include "sgap_common.hpp"
