@@ -357,13 +357,13 @@ int sgap_spmm_csr_cfg_static(int64_t M, int64_t K, int64_t N,
  *             SGAP_REDUCE_PARALLEL: group_size lanes share a stored entry,
  *             split j between them and tree-sum; SGAP_REDUCE_SERIAL: every
  *             lane computes group_size consecutive stored entries by itself.
- *             With the parallel strategy, J from 72 to 128 and groups of 8, 16
- *             or 32 (J from 136 to 256: 16, 32 or 64), nnz_hint of 1,500,000
- *             and more (3,000,000 at J = 128), 12 to 32 of them a row, and X2T
- *             below 4 GiB, the device looks at a few rows; where neighbours
- *             share enough columns, four rows are taken together and the
- *             lanes of an entry are the library's (its chains of additions
- *             are no longer than with group_size lanes).
+ *             With the parallel strategy, J from 68 to 128 and groups of 8 or
+ *             16 (from 72: or 32; J from 132 to 256: 16 or 32, from 136: or
+ *             64), nnz_hint of 1,500,000 and more (3,000,000 at J = 128), 12
+ *             to 32 of them a row, and X2T below 4 GiB, the device looks at a
+ *             few rows; where neighbours share enough columns, four rows are
+ *             taken together and the lanes of an entry are the library's (its
+ *             chains of additions are no longer than with group_size lanes).
  *   nnz_hint  rowptr[M] if the host knows it, else -1 (sizes the grid and, as
  *             above, chooses between launches of the same result; 0 returns at
  *             once).

@@ -258,9 +258,11 @@ __host__ __device__ constexpr int x1_pitch(int columns, bool edge, int ept)
 // round (tile by tile, J = 128, G = 16: 4.8 M entries without order 366 -> 385 us, 366 so; 6.5 M that share half of their columns with
 // the row above 161 -> 231, 162 so).  With six, and 76 vector registers, the stencil below takes 546 us by four rows together instead
 // of 553, but tile by tile everything takes 1 to 8 % more.
-// From 72 columns on, and 136 where an entry has twice the lanes or steps: of 64, a 60 x 57 x 62 stencil takes 86 us tile by tile
-// and 94 so, and just above that a lane has four columns tile by tile, or five, and sums them no less exactly than CHAINS do here
-// (J = 65, G = 16 7.26e-8 and 7.34e-8).
+// From 68 columns on, and 132 where an entry has twice the lanes or steps (of 64, a 60 x 57 x 62 stencil takes 86 us tile by tile and
+// 94 so); with one step from 72 and 136 on: just above 64 a lane has four columns tile by tile, or twice that, and sums them no
+// less exactly than CHAINS do here.  Relative error against 64 bits, tile by tile and so, and time on that stencil: G = 8, J = 65
+// 7.63e-8 / 7.69e-8 and 157 / 127 us, J = 68 7.75e-8 / 7.66e-8 and 158 / 129; G = 16, J = 67 7.30e-8 / 7.32e-8, J = 68 7.34e-8 / 7.32e-8,
+// 163 / 129 us; G = 32, one step, J = 68 7.29e-8 / 7.32e-8, J = 72 7.35e-8 / 7.35e-8; G = 64, J = 132 7.76e-8 / 7.78e-8.
 __host__ __device__ constexpr bool has_quads(int g, int s, int ept) { return ept == 1 && (s * g == 32 || s * g == 64); }  // up to 256 columns
 // Stored entries from which on a matrix is looked at for such rows: the look takes 2 us where it finds none.  40 x 41 x 42
 // points, 1.8 M entries: J = 100 59.9 -> 49.7 us, J = 72 55.2 -> 49.0, J = 256 141 -> 82, but J = 128, which the tiles have in
@@ -268,9 +270,9 @@ __host__ __device__ constexpr bool has_quads(int g, int s, int ept) { return ept
 // points, 0.8 M: J = 100 35.6 -> 32.6, J = 128 27.2 -> 28.6.
 constexpr int64_t quads_from(bool step128) { return step128 ? 3000000 : 1500000; }
 // Whether a call is launched so that it looks (chunks: of four columns, that the lanes and steps of an entry hold)
-constexpr bool looks_for_quads(int64_t M, int64_t K, int64_t J, int chunks, int64_t nnz_hint)
+constexpr bool looks_for_quads(int64_t M, int64_t K, int64_t J, int steps, int chunks, int64_t nnz_hint)
 {
-    return J >= chunks * 2 + 8 && K * J * 4 <= 0xffffffffLL && nnz_hint >= quads_from(J == 128 && chunks == 32) &&
+    return J >= chunks * 2 + (steps > 1 ? 4 : 8) && K * J * 4 <= 0xffffffffLL && nnz_hint >= quads_from(J == 128 && chunks == 32) &&
            nnz_hint > kQuadMeanRow * M && nnz_hint < kQuadRow * M;
 }
 static_assert(1500000 / kQuadRow >= kLookRun, "so many entries come with enough rows to look at");
@@ -576,7 +578,7 @@ void launch_tile(const SddmmArgs& s, int compute_units, int64_t nnz_hint, hipStr
     constexpr int x1_rows = EPT * kX1LdsBytes / (S * G * 16);
     constexpr int x1_bytes = x1_rows * x1_pitch(S * G * 4, EDGE, EPT) * 4;
     if constexpr (has_quads(G, S, EPT)) {
-        if (looks_for_quads(s.a.M, s.a.K, s.a.N, S * G, nnz_hint)) {
+        if (looks_for_quads(s.a.M, s.a.K, s.a.N, S, S * G, nnz_hint)) {
             static_assert(x1_bytes >= (int)sizeof(QuadDots) * kWavesPerBlock, "either is in the same place");
             static const int per_cu = resident_per_cu(sddmm_tile_kernel<G, S, EDGE, EPT, true>, x1_bytes);
             const uint32_t workers = (uint32_t)persistent_grid(per_cu, compute_units, nnz_hint, EPT * kBlock);
@@ -704,8 +706,8 @@ hipError_t launch_sddmm(const SpmmArgs& a, const float* X1, float* out, int g, i
 // What the parallel strategy with g lanes per entry does with a matrix in host memory: rows_share_columns by a single thread.
 bool sddmm_by_quads(int64_t M, int64_t K, int64_t J, int g, int64_t nnz_hint, const int32_t* rowptr, const int32_t* colidx)
 {
-    const int chunks = tile_steps(J, g) * g;
-    if (J <= 64 || !(chunks == 32 || chunks == 64) || !looks_for_quads(M, K, J, chunks, nnz_hint)) return false;
+    const int steps = tile_steps(J, g), chunks = steps * g;
+    if (J <= 64 || !(chunks == 32 || chunks == 64) || !looks_for_quads(M, K, J, steps, chunks, nnz_hint)) return false;
     int long_rows = 0, shared = 0, total = 0;
     for (int i = 0; i < kLookRuns; ++i) {
         const int32_t* p = rowptr + look_run((uint32_t)i, M);

@@ -65,13 +65,13 @@ def by_quads(p, g):
 
 
 @pytest.mark.parametrize("kind", KINDS)
-@pytest.mark.parametrize("J", [65, 73, 101, 128, 129, 137, 197, 256])
+@pytest.mark.parametrize("J", [65, 68, 73, 101, 128, 129, 132, 137, 197, 256])
 def test_rows_at_the_edges(J, kind):
     p, X1 = problem(kind, J, *csr(kind, MORE_ROWS if J == 128 else ROWS))
     ref, _ = oracle.sddmm_csr(p.M, p.K, p.N, p.rowptr, p.colidx, p.vals, X1, p.B)
     dp, X1d = DeviceProblem(p), torch.from_numpy(X1).cuda()
     for g in (8, 16, 32) if J <= 128 else (16, 32, 64):
-        assert by_quads(p, g) == (kind != "31 to 33 entries, entry by entry" and J not in (65, 129))
+        assert by_quads(p, g) == (kind != "31 to 33 entries, entry by entry" and J not in (65, 129) and (J, g) not in ((68, 32), (132, 64)))
         assert np.array_equal(dp.run_sddmm(X1d, g, "parallel").cpu().numpy().astype(np.float64), ref), g
 
 
@@ -81,6 +81,7 @@ def test_what_is_not_finite_stays_in_its_entries():
     p.vals[p.vals == 0] = 1
     p.B[70, 5], X1[300, 99] = np.inf, np.nan
     X1[:, 5] = 1
+    assert by_quads(p, 8) == 1
     got = DeviceProblem(p).run_sddmm(torch.from_numpy(X1).cuda(), 8, "parallel").cpu().numpy()
     row = np.repeat(np.arange(ROWS), np.diff(p.rowptr))
     assert np.isnan(got[row == 300]).all()
@@ -97,11 +98,12 @@ def test_small_products_are_kept():
     p.B[:, 7] = 2.0 ** -100
     X1[:] = 0
     X1[:, 7] = 2.0 ** -40
+    assert by_quads(p, 8) == 1
     got = DeviceProblem(p).run_sddmm(torch.from_numpy(X1).cuda(), 8, "parallel").cpu().numpy()
     assert (got == np.float32(2.0 ** -140)).all()
 
 
-@pytest.mark.parametrize("J", [72, 75, 100, 128, 136, 200, 256])
+@pytest.mark.parametrize("J", [68, 72, 75, 100, 128, 132, 136, 200, 256])
 def test_no_less_exact_than_entry_by_entry(J):
     """Relative error (2-norm) against 64 bits, by quads and where the count of entries that is passed lets nothing look for them.
     Over a million entries and more the ratio of two such errors of alike sums is one within a few thousandths."""
@@ -113,7 +115,7 @@ def test_no_less_exact_than_entry_by_entry(J):
     X1 = wl.fill_values(rng, rows * J, False).reshape(rows, J)
     ref, _ = oracle.sddmm_csr(p.M, p.K, p.N, p.rowptr, p.colidx, p.vals, X1, p.B, nthreads=8, bound=False)
     dp, X1d = DeviceProblem(p), torch.from_numpy(X1).cuda()
-    for g in (8, 16, 32) if J <= 128 else (16, 32, 64):
+    for g in [g for g in ((8, 16, 32) if J <= 128 else (16, 32, 64)) if (J, g) not in ((68, 32), (132, 64))]:
         assert by_quads(p, g) == 1
         error = []
         for hint in (colidx.size, 1):

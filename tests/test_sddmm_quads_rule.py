@@ -67,8 +67,8 @@ def test_calls_that_do_not_look():
     rowptr, colidx = bands(0)
     assert by_quads(rowptr, colidx, 100, 8, hint=-1) == 0  # nobody knows how many entries there are
     assert by_quads(rowptr, colidx, 100, 8, hint=1_499_999) == 0
-    assert by_quads(rowptr, colidx, 71, 8) == 0 and by_quads(rowptr, colidx, 72, 8) == 1  # narrow
-    assert by_quads(rowptr, colidx, 135, 16) == 0 and by_quads(rowptr, colidx, 136, 16) == 1
+    for g, least in ((8, 68), (16, 68), (32, 72), (16, 132), (32, 132), (64, 136)):  # narrow
+        assert by_quads(rowptr, colidx, least - 1, g) == 0 and by_quads(rowptr, colidx, least, g) == 1
     assert by_quads(rowptr, colidx, 100, 4) == 0 and by_quads(rowptr, colidx, 100, 64) == 0  # lanes and steps of an entry
     assert by_quads(rowptr, colidx, 128, 8, K=2**23) == 0 and by_quads(rowptr, colidx, 128, 8, K=2**23 - 1) == 1  # offsets of 32 bits
     assert by_quads(rowptr, colidx, 0, 8) == 0
