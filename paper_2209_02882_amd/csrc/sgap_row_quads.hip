@@ -10,7 +10,7 @@
 // twice: both entries go into one record, and a place behind it stays empty.)  Then every record costs one gather and four
 // v_mfma_f32_4x4x1: four rows' values times the four columns of each lane.
 //
-// 27-point stencil of 1,000,000 rows, N = 128: 588 -> 429 us (N = 64 287 -> 240, N = 256 1,217 -> 880; 212,040 rows, N = 128 112 ->
+// 27-point stencil of 1,000,000 rows, N = 128: 589 -> 418 us (N = 64 286 -> 238, N = 256 1,217 -> 849; 212,040 rows, N = 128 112 ->
 // 81).  By steps: listed in the order of opening, fp32 multiply-adds 499; on the matrix cores, which halves
 // the vector instructions, 493; planes dealt over the dies (die_block) 450, L2 misses 19.9 M -> 10.9 M lines; in the order
 // of the columns, so that neighbouring quads ask for a line at the same time and the L1 answers one of them, 430, L1 misses
@@ -23,8 +23,9 @@
 // a slot took its own quad's rows it kept the others waiting, and read entry by entry.  us by row_split_kernel, that way and so: a
 // mesh of three unknowns a node and 7 to 11 neighbours, 300,000 rows, a third of them of 32 entries or more, N = 64 102, 187 and
 // 103, N = 128 175, 250 and 163; power law, 1,000,000 rows, N = 64 890, 1,170 and 810; rows of 27 neighbouring columns and one in
-// eight of 40, 400,000 rows, N = 128 227, 280 and 194.  Five wavefronts per SIMD: with four, as the compiler has it by itself, the
-// stencil takes 438 and the mesh 199 at N = 128, with six (and six rows of B in flight) 457 and 160.
+// eight of 40, 400,000 rows, N = 128 227, 280 and 194.  Five wavefronts per SIMD: with four, as the compiler has it by itself in 16
+// lanes, the stencil takes 235 us at N = 40 and 245 at N = 64 (214 and 236 with five); with six (and six rows of B in flight) N = 128
+// took 457 against 428.
 //
 // +0 times a finite element of B adds nothing; an infinity or a NaN would.  A quad with a sum that is not finite is
 // therefore done again row by row.  Nothing is assumed of the matrix.
@@ -99,8 +100,8 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(5))) voi
     constexpr int32_t CHUNK = NEXT * LC < kQuadChunk ? NEXT * LC : kQuadChunk;  // of a slot
     constexpr unsigned long long SLOT_MASK = LC == 64 ? ~0ull : (1ull << LC) - 1ull;
     __shared__ QuadLds s_lds[SLOTS];
-    __shared__ int32_t s_ptr[SLOTS][kQuad + 1];  // of the quads whose rows go one by one
-    __shared__ unsigned long long s_open[kWavesPerBlock], s_read[kWavesPerBlock];  // bit: lane, of such a quad; of one not in LDS
+    __shared__ int32_t s_ptr[SLOTS][kQuad + 1];  // of the quads, for rows that go one by one
+    __shared__ unsigned long long s_open[kWavesPerBlock], s_read[kWavesPerBlock];  // bit: lane, of a quad that is open; and not in LDS
 
     const int slot = threadIdx.x / LC;
     const int t = threadIdx.x % LC;
@@ -277,6 +278,19 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(5))) voi
             if (t + u * LC < p[kQuad] - p[0]) lds.staged[t + u * LC] = e[u];
     }
 
+    // The workgroup's quads that go row by row, known before the gathers: where there are none nobody waits for anybody behind them
+    // (27-point stencil of 1,000,000 rows, with the meeting behind the gathers and so: N = 128 425 -> 416 us, N = 256 868 -> 848).
+    const int wave = threadIdx.x / kWave;
+    {
+        const unsigned long long open = __ballot(!listed), read = __ballot(!listed && !in_lds);
+        if (threadIdx.x % kWave == 0) {
+            s_open[wave] = open;
+            s_read[wave] = read;
+        }
+        if (t <= kQuad) s_ptr[slot][t] = t == 0 ? p[0] : t == 1 ? p[1] : t == 2 ? p[2] : t == 3 ? p[3] : p[4];
+    }
+    __syncthreads();
+
     bool done = false;
     if (__ballot(listed) != 0) {
         f32x4 acc[4];
@@ -311,29 +325,22 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(5))) voi
         }
     }
 
-    // The rows of the quads that are left, a row to a slot, whichever slot's they are: first those whose entries are in LDS, then
-    // those that are read into it.
-    const int wave = threadIdx.x / kWave;
-    const unsigned long long open = __ballot(!done);
-    if (threadIdx.x % kWave == 0) s_open[wave] = open;
-    if (open != 0) {
-        const unsigned long long read = __ballot(!done && !in_lds);
-        if (threadIdx.x % kWave == 0) s_read[wave] = read;
-        if (t <= kQuad) s_ptr[slot][t] = t == 0 ? p[0] : t == 1 ? p[1] : t == 2 ? p[2] : t == 3 ? p[3] : p[4];
-    }
-    __syncthreads();
-    uint32_t here = 0, elsewhere = 0;  // bit: slot
+    // Rows one by one, a row to a slot: those of quads that are open by all the workgroup's slots, whichever slot's they are, first those
+    // whose entries are in LDS, then those that are read into it; in between, by its own slots, a wavefront's that were not finite.
+    uint32_t here = 0, elsewhere = 0, again = 0;  // bit: slot
 #pragma unroll
     for (int w = 0; w < kWavesPerBlock; ++w) {
-        const unsigned long long all = s_open[w];
-        if (all == 0) continue;
-        const unsigned long long read = s_read[w];
+        const unsigned long long all = s_open[w], read = s_read[w];
 #pragma unroll
         for (int l = 0; l < kWave / LC; ++l) {
             here |= (uint32_t)((all & ~read) >> (l * LC) & 1) << (w * (kWave / LC) + l);
             elsewhere |= (uint32_t)(read >> (l * LC) & 1) << (w * (kWave / LC) + l);
         }
     }
+    const unsigned long long redo = __ballot(listed && !done);
+    if (redo == 0 && (here | elsewhere) == 0) return;
+#pragma unroll
+    for (int l = 0; l < kWave / LC; ++l) again |= (uint32_t)(redo >> (l * LC) & 1) << (wave * (kWave / LC) + l);
     // number n of the rows of the slots in mask
     auto row_number = [&](uint32_t mask, int n) {
         for (int i = 0; i < n / kQuad; ++i) mask &= mask - 1;
@@ -352,50 +359,54 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(5))) voi
         if (k_ok) gather_fma<4, 1, kPlainDepth>(acc, s_lds[row / kQuad].staged, at, (uint32_t)(ptr[row % kQuad + 1] - ptr[0]), B);
         store(row, acc);
     }
-    if (elsewhere == 0) return;
     if (here != 0) __syncthreads();  // the rows in LDS are done with
-    const int rows = __popc(elsewhere) * kQuad;
-    StagedEntry next[NEXT];  // of a row, the next ones on their way while these are gathered for
-    int row = 0;
-    int32_t base = 0, end = 0;
-    auto fetch = [&] {
+    for (int pass = 0; pass < 2; ++pass) {
+        const uint32_t mask = pass == 0 ? again : elsewhere;
+        const int first = pass == 0 ? slot % (kWave / LC) : slot, step = pass == 0 ? kWave / LC : SLOTS;
+        const int rows = __popc(mask) * kQuad;
+        if (rows == 0) continue;
+        StagedEntry next[NEXT];  // of a row, the next ones on their way while these are gathered for
+        int row = 0;
+        int32_t base = 0, end = 0;
+        auto fetch = [&] {
 #pragma unroll
-        for (int u = 0; u < NEXT; ++u)
-            if (t + u * LC < CHUNK && base + t + u * LC < end) {
-                next[u].col = load_stream(a.colidx + base + t + u * LC);
-                next[u].val = load_stream(a.vals + base + t + u * LC);
-            }
-    };
-    auto begin_row = [&](int n) {
-        row = row_number(elsewhere, n);
-        base = s_ptr[row / kQuad][row % kQuad];
-        end = s_ptr[row / kQuad][row % kQuad + 1];
-    };
-    Vec<4> acc;
-    acc.zero();
-    if (slot < rows) {
-        begin_row(slot);
-        fetch();
-    }
-    for (int n = slot; n < rows;) {
-        const int this_row = row;
-        const int32_t cnt = end - base < CHUNK ? end - base : CHUNK;
-        const bool last = end - base <= CHUNK;
-        wave_lds_order();
-#pragma unroll
-        for (int u = 0; u < NEXT; ++u)
-            if (t + u * LC < cnt) lds.staged[t + u * LC] = next[u];
-        wave_lds_order();
-        base += CHUNK;
-        if (last) {
-            n += SLOTS;
-            if (n < rows) begin_row(n);
+            for (int u = 0; u < NEXT; ++u)
+                if (t + u * LC < CHUNK && base + t + u * LC < end) {
+                    next[u].col = load_stream(a.colidx + base + t + u * LC);
+                    next[u].val = load_stream(a.vals + base + t + u * LC);
+                }
+        };
+        auto begin_row = [&](int n) {
+            row = row_number(mask, n);
+            base = s_ptr[row / kQuad][row % kQuad];
+            end = s_ptr[row / kQuad][row % kQuad + 1];
+        };
+        Vec<4> acc;
+        acc.zero();
+        if (first < rows) {
+            begin_row(first);
+            fetch();
         }
-        if (n < rows) fetch();
-        if (k_ok) gather_fma<4, 1, kPlainDepth>(acc, lds.staged, 0, (uint32_t)cnt, B);
-        if (last) {
-            store(this_row, acc);
-            acc.zero();
+        for (int n = first; n < rows;) {
+            const int this_row = row;
+            const int32_t cnt = end - base < CHUNK ? end - base : CHUNK;
+            const bool last = end - base <= CHUNK;
+            wave_lds_order();
+#pragma unroll
+            for (int u = 0; u < NEXT; ++u)
+                if (t + u * LC < cnt) lds.staged[t + u * LC] = next[u];
+            wave_lds_order();
+            base += CHUNK;
+            if (last) {
+                n += step;
+                if (n < rows) begin_row(n);
+            }
+            if (n < rows) fetch();
+            if (k_ok) gather_fma<4, 1, kPlainDepth>(acc, lds.staged, 0, (uint32_t)cnt, B);
+            if (last) {
+                store(this_row, acc);
+                acc.zero();
+            }
         }
     }
 }

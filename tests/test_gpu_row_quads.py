@@ -111,20 +111,27 @@ def test_planes_dealt_over_the_dies(N):
     check(p, (1,))
 
 
-def test_what_is_not_finite_stays_in_its_rows():
-    N = 64
-    rowptr, colidx = csr("band", N)
+@pytest.mark.parametrize("kind", ["band", "no column in common within the first two, or the last two", "31, 32 and 33 entries", "long rows"])
+@pytest.mark.parametrize("N,tile_cols", [(61, 0), (64, 0), (128, 0), (256, 256)])  # 16, 32 and 64 lanes
+def test_what_is_not_finite_stays_in_its_rows(N, tile_cols, kind):
+    """Listed quads that are done again beside quads whose rows go one by one, from LDS and from memory."""
+    rowptr, colidx = csr(kind, N)
     rng, K = np.random.default_rng(3), int(colidx.max()) + 1
     vals, B = wl.fill_values(rng, colidx.size, True), wl.fill_values(rng, K * N, True).reshape(K, N)
     vals[vals == 0] = 1
-    B[70, 5], B[300, 60] = np.inf, np.nan
+    ref, _ = oracle.spmm_csr(rowptr.size - 1, K, N, rowptr, colidx, vals, B, nthreads=8, bound=False)
+    infinite = np.concatenate([[70], np.arange(3_000, K, 157)])
+    B[infinite, 5], B[300, 60] = np.inf, np.nan
     p = wl.SpmmProblem("quads", rowptr.size - 1, K, N, rowptr, colidx, vals, B)
-    got = DeviceProblem(p).run_cfg(binding.make_config(1, "serial", "row_split")).cpu().numpy()
-    has = lambda c: np.add.reduceat(colidx == c, rowptr[:-1]) > 0  # noqa: E731
-    assert np.isinf(got[has(70), 5]).all() and np.isnan(got[has(300), 60]).all()
+    cfg = binding.make_config(1, "serial", "row_split", tile_cols=tile_cols)
+    units = torch.cuda.get_device_properties(0).multi_processor_count
+    assert binding.load().sgap_debug_row_quads(p.M, N, colidx.size, ctypes.byref(cfg), units) == 1
+    got = DeviceProblem(p).run_cfg(cfg).cpu().numpy()
+    has = lambda c: (np.diff(rowptr) > 0) & (np.add.reduceat(np.append(np.isin(colidx, c), False), rowptr[:-1]) > 0)  # noqa: E731
+    assert not np.isfinite(got[has(infinite), 5]).any() and np.isnan(got[has([300]), 60]).all()
     rest = np.ones(got.shape, bool)
-    rest[has(70), 5] = rest[has(300), 60] = False
-    assert np.isfinite(got[rest]).all()
+    rest[has(infinite), 5] = rest[has([300]), 60] = False
+    assert np.array_equal(got[rest].astype(np.float64), ref[rest])
 
 
 @pytest.mark.parametrize("N,tile_cols", [(64, 0), (61, 0), (128, 0), (256, 256)])  # 16, 32 and 64 lanes
