@@ -32,6 +32,8 @@ namespace {
 constexpr int kShareMin = 256;    // the shortest row that a whole workgroup takes together
 constexpr int kFinderRows = 64;   // a finder looks at no fewer rows (32 cost matrices without long rows: 10,000 rows of 16
                                   // entries, N = 32, G = 8 6.3 -> 6.7 us)
+constexpr int kFinderEntries = 2048;  // ... unless most rows are long, and then no more entries: 2,000 rows of 400, N = 37, G = 16 330 us by
+                                      // 32 finders, 31 by 400
 constexpr int kFindersPerCu = 8;  // as many workgroups as are resident
 constexpr int kTeamRows = 256;    // a team of two looks through no more rows: a look of its workgroups' threads
 constexpr int kTeamsPerCu = 4;    // no teams where there are more finders: they come in rounds then
@@ -69,7 +71,12 @@ RowSplitGrid plan_row_split_grid(int g, int passes, int64_t M, int64_t items, in
     const int32_t share_from = share_rows_from(g, passes);
     if (g > 1 && (nnz_hint < 0 || nnz_hint >= share_from)) {
         const int64_t most = (int64_t)kFindersPerCu * compute_units;
-        int64_t finders = (M + kFinderRows - 1) / kFinderRows < most ? (M + kFinderRows - 1) / kFinderRows : most;
+        // where most rows are long, as many rows as hold kFinderEntries
+        const double mean = (double)nnz_hint / (double)M;
+        int64_t rows = kFinderRows;
+        if (2.0 * mean >= (double)share_from && kFinderEntries / mean < (double)kFinderRows) rows = (int64_t)(kFinderEntries / mean);
+        if (rows < (int64_t)FinderDeal::kUnit) rows = FinderDeal::kUnit;
+        int64_t finders = (M + rows - 1) / rows < most ? (M + rows - 1) / rows : most;
         if (resident > 0 && finders > walkers) finders = walkers;
         const int64_t rows_each = (M + finders - 1) / finders;
         if (2 * rows_each <= kTeamRows && finders >= 2 && finders <= (int64_t)kTeamsPerCu * compute_units) p.log2_team = 1;

@@ -23,28 +23,41 @@ constexpr int kStageCap = 2048;  // (column, value) pairs per LDS chunk: 16 KB
 constexpr int kRowCap = 1024;    // rowptr entries kept in LDS per row block (+1)
 constexpr int kRowSplitMaxBlock = 512;  // threads per workgroup: 128, 256 or 512, chosen at launch
 
-// One row by the whole workgroup: lc chunk lanes (the power of two that covers the columns, at most a wavefront) and
-// block / lc members, each of which takes every (block / lc)-th stored entry with DEPTH rows of B in flight; members
-// of a wavefront are summed with shuffles, the wavefronts' sums through LDS in a fixed order, and the row has one
-// plain store as ever.  For the rows whose length would keep the one group that owns them busy long after the rest of
-// the chip is done (see plan_row_split_grid).  s_A and s_part may be the same memory.  Block-uniform; barriers inside.
+// One row by the whole workgroup: as many chunk lanes as the columns take (a wavefront's at most) and block / lanes members,
+// each of which takes every (block / lanes)-th stored entry with DEPTH rows of B in flight; the members' sums are added up
+// through LDS in a fixed order, and the row has one plain store as ever.  For the rows whose length would keep the one group
+// that owns them busy long after the rest of the chip is done (see plan_row_split_grid).  A round of loads is a round trip to
+// memory whatever is in it, so lanes that hold no columns cost in proportion: with the next power of two of chunk lanes, 16
+// members instead of 25 at N = 37, a row of 4,096 entries took 32 rounds instead of 21.  Power laws, four matrices each, us,
+// power of two / as many as the columns take: 50,021 rows, N = 37 40.2 to 62.4 / 35.2 to 50.3; 20,396 rows, N = 37 34.9 to
+// 40.6 / 29.0 to 33.9; 53,897 rows, N = 51 28.9 to 47.2 / 27.6 to 42.5; columns that fill a power of two within 2 %.
+// s_A and s_part may be the same memory.  Block-uniform; barriers inside.
+struct SharedLanes {
+    uint32_t lanes, members, member, chunk;  // member number `members` has no entries
+    __device__ __forceinline__ SharedLanes(int64_t chunks, int block)
+    {
+        lanes = chunks < kWave ? (uint32_t)chunks : (uint32_t)kWave;
+        // (divisions of numbers up to 512 by up to 64: exact)
+        const float per_lane = __builtin_amdgcn_rcpf((float)lanes);
+        members = (uint32_t)(((float)block + 0.5f) * per_lane);
+        member = (uint32_t)(((float)threadIdx.x + 0.5f) * per_lane);
+        chunk = threadIdx.x - member * lanes;
+    }
+};
+
 template <int VEC, bool OFF32, int DEPTH>
 __device__ __forceinline__ void shared_row(const SpmmArgs& a, int64_t row, uint32_t p_begin, uint32_t p_end,
-                                           int64_t k_begin, int64_t k_end, StagedEntry* __restrict__ s_A, int block)
+                                           const SharedLanes& l, StagedEntry* __restrict__ s_A, int block)
 {
     constexpr int D = DEPTH;
+    constexpr uint32_t PARTS = 8;  // of the members' sums, added up side by side
     const int64_t N = a.N;
-    int lc = 1;
-    while (lc < kWave && (int64_t)lc * VEC < k_end - k_begin) lc *= 2;
-    const uint32_t members = (uint32_t)(block / lc);
-    const uint32_t member = (uint32_t)threadIdx.x / lc;
-    const int chunk = threadIdx.x % lc;
-    const int lane = threadIdx.x % kWave;
-    const int wave = threadIdx.x / kWave;
-    float* s_part = reinterpret_cast<float*>(s_A);  // block/64 wavefronts x lc*VEC columns
-    for (int64_t k0 = k_begin; k0 < k_end; k0 += (int64_t)lc * VEC) {
+    const uint32_t lanes = l.lanes, members = l.members, member = l.member, chunk = l.chunk;
+    Vec<VEC>* const s_part = reinterpret_cast<Vec<VEC>*>(s_A);  // of each thread
+    static_assert(kRowSplitMaxBlock * sizeof(Vec<VEC>) <= kStageCap * sizeof(StagedEntry), "s_part");
+    for (int64_t k0 = 0; k0 < N; k0 += (int64_t)lanes * VEC) {
         const int64_t k = k0 + (int64_t)chunk * VEC;
-        const bool k_ok = k < k_end;
+        const bool k_ok = k < N && member < members;
         const int64_t first = k_ok ? lane_first_col<VEC>(k, N) : 0;
         const GlobalRows<VEC, OFF32> B(a.B, N, first);
         Vec<VEC> acc;
@@ -55,37 +68,56 @@ __device__ __forceinline__ void shared_row(const SpmmArgs& a, int64_t row, uint3
             stage_entries<8>(a.colidx + base, a.vals + base, cnt, s_A, block);
             __syncthreads();
             for (uint32_t q = member; k_ok && q < cnt; q += D * members) {
+                uint32_t at[D];
+                at[0] = q;
+#pragma unroll
+                for (int u = 1; u < D; ++u) at[u] = at[u - 1] + members;
                 StagedEntry e[D];
                 Vec<VEC> b[D];
 #pragma unroll
                 for (int u = 0; u < D; ++u) {
                     e[u].col = 0;
                     e[u].val = 0.0f;
-                    if (q + u * members < cnt) e[u] = s_A[q + u * members];
+                    if (at[u] < cnt) e[u] = s_A[at[u]];
                 }
 #pragma unroll
                 for (int u = 0; u < D; ++u) {
                     b[u].zero();
-                    if (q + u * members < cnt) b[u] = B.load(e[u].col);
+                    if (at[u] < cnt) b[u] = B.load(e[u].col);
                 }
 #pragma unroll
                 for (int u = 0; u < D; ++u) acc.fma(e[u].val, b[u]);
             }
         }
-        for (int d = kWave / 2; d >= lc; d /= 2) {
-#pragma unroll
-            for (int i = 0; i < VEC; ++i) acc.v[i] += __shfl_down(acc.v[i], d, kWave);
-        }
         __syncthreads();  // the last entries are consumed
-        if (lane < lc) {
+        uint32_t sums = PARTS < members ? PARTS : members;  // that the first member adds up, `lanes` places apart
+        if ((lanes & (lanes - 1)) == 0) {
+            // whole members in every wavefront: they hand their sums down
+            for (int d = kWave / 2; d >= (int)lanes; d /= 2) {
 #pragma unroll
-            for (int i = 0; i < VEC; ++i) s_part[(wave * lc + lane) * VEC + i] = acc.v[i];
+                for (int i = 0; i < VEC; ++i) acc.v[i] += __shfl_down(acc.v[i], d, kWave);
+            }
+            sums = (uint32_t)block / kWave;
+            if (threadIdx.x % kWave < lanes) s_part[threadIdx.x / kWave * lanes + chunk] = acc;
+        } else {
+            // member m of the first PARTS adds up those of m, m + PARTS, ...
+            s_part[threadIdx.x] = acc;
+            __syncthreads();
+            if (member < PARTS && member < members) {
+                for (uint32_t m = member + PARTS; m < members; m += PARTS) {
+                    const Vec<VEC> other = s_part[m * lanes + chunk];
+#pragma unroll
+                    for (int i = 0; i < VEC; ++i) acc.v[i] += other.v[i];
+                }
+                s_part[threadIdx.x] = acc;
+            }
         }
         __syncthreads();
-        if (wave == 0 && lane < lc && k_ok) {
-            for (int w = 1; w < block / kWave; ++w) {
+        if (member == 0 && k_ok) {
+            for (uint32_t m = 1; m < sums; ++m) {
+                const Vec<VEC> other = s_part[m * lanes + chunk];
 #pragma unroll
-                for (int i = 0; i < VEC; ++i) acc.v[i] += s_part[(w * lc + lane) * VEC + i];
+                for (int i = 0; i < VEC; ++i) acc.v[i] += other.v[i];
             }
             store_vec_stream<VEC>(a.C + row * N + first, acc);
         }
@@ -134,6 +166,7 @@ __global__ __launch_bounds__(kRowSplitMaxBlock) void row_split_kernel(SpmmArgs a
             const uint32_t mine = blockIdx.x & ((1u << plan.log2_team) - 1u);  // of the rows found, this one's turns
             const int lane = threadIdx.x % kWave, wave = threadIdx.x / kWave;
             const uint32_t last = plan.deal.first_place(team + 1, teams);
+            const SharedLanes lanes((N + VEC - 1) / VEC, block);
             for (uint32_t first = plan.deal.first_place(team, teams); first < last; first += kRowCap / UNIT) {
                 const uint32_t look = (last - first < kRowCap / UNIT ? last - first : kRowCap / UNIT) * UNIT;
                 uint32_t found = 0;  // the same in all members of the team, and in the same order
@@ -162,7 +195,7 @@ __global__ __launch_bounds__(kRowSplitMaxBlock) void row_split_kernel(SpmmArgs a
                 const int n = (int)((found + (1u << plan.log2_team) - 1u - mine) >> plan.log2_team);
                 for (int i = 0; i < n; ++i) {
                     const int32_t row = __builtin_amdgcn_readfirstlane(s_rp[i]);
-                    shared_row<VEC, OFF32, DEPTH>(a, row, (uint32_t)a.rowptr[row], (uint32_t)a.rowptr[row + 1], 0, N, s_A, block);
+                    shared_row<VEC, OFF32, DEPTH>(a, row, (uint32_t)a.rowptr[row], (uint32_t)a.rowptr[row + 1], lanes, s_A, block);
                 }
             }
             if ((int)blockIdx.x < plan.walk_from) return;

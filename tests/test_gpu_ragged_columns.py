@@ -57,3 +57,15 @@ def test_long_rows_found_in_large_matrices(M, block):
     for g in (2, 8, 32):
         got = dp.run_cfg(binding.make_config(g, "parallel", "row_split", block_size=block)).cpu().numpy()
         assert np.array_equal(got.astype(np.float64), ref), g
+
+
+# chunk lanes that divide neither a wavefront nor a workgroup (2, 3, 5, 13, 25 and 63 of them; 64 and a second pass)
+@pytest.mark.parametrize("N", [6, 9, 20, 52, 100, 252, 260])
+def test_shared_rows_on_any_number_of_lanes(N):
+    p, _ = problem(40, 7000, N, [256, 2049, 300, 4100, 0, 5] * 6 + [2047, 2048, 1, 383], seed=N)
+    ref, _ = oracle.spmm_csr(p.M, p.K, p.N, p.rowptr, p.colidx, p.vals, p.B, nthreads=8, bound=False)
+    dp = DeviceProblem(p)
+    for g in (2, 16):
+        for block in (0, 128, 512):
+            got = dp.run_cfg(binding.make_config(g, "parallel", "row_split", block_size=block)).cpu().numpy()
+            assert np.array_equal(got.astype(np.float64), ref), (g, block)

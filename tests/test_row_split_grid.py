@@ -81,3 +81,9 @@ def test_bad_arguments():
     assert lib.sgap_debug_plan_row_split(3, 1, 1, 1, 8, 256, -1, 0, x, x, x, x, x) == binding.SGAP_ERR_INVALID_ARG
     assert lib.sgap_debug_plan_row_split(8, 1, 1, 1, 8, 256, -2, 0, x, x, x, x, x) == binding.SGAP_ERR_INVALID_ARG
     assert lib.sgap_debug_plan_row_split(8, 1, 1, 1, 8, 256, -1, 0, x, x, x, x, None) == binding.SGAP_ERR_INVALID_ARG
+
+
+@pytest.mark.parametrize("M,mean,most_rows", [(100_000, 16, 64), (2000, 100, 64), (2000, 200, 12), (2000, 400, 6), (2000, 5000, 4)])
+def test_finders_look_at_fewer_rows_where_rows_are_long(M, mean, most_rows):
+    _, finders, _, _, _ = plan(4, 1, M, M, M * mean)
+    assert -(-M // finders) <= most_rows
