@@ -852,7 +852,7 @@ int sgap_mttkrp_csf_ex(int64_t I, int64_t K, int64_t L, int64_t J, const int32_t
             // the tuning knob counts the slices of a group of group_size members
             const int slots = 256 / (group_size * pow2_ceil_capped((J + vec - 1) / vec, 64 / group_size));
             const int slices = g_rows_per_slot > 0 ? slots * g_rows_per_slot : mttkrp_block_slices(I, nnz_hint, compute_units());
-            err = launch_mttkrp_fibers(m, slices, lc, vec, xcds, s);
+            err = launch_mttkrp_fibers(m, slices, vec, xcds, s);
         } else
             err = launch_mttkrp(m, group_size, lc, vec, xcds, s);
     }

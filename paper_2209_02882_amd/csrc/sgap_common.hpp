@@ -311,7 +311,7 @@ hipError_t launch_sddmm_rest(const SpmmArgs& a, const float* X1, float* out, int
 hipError_t launch_mttkrp(const MttkrpArgs& a, int rows_per_slot, int lc, int vec, int xcds, hipStream_t s);
 // Parallel strategy (sgap_mttkrp_fibers.hip): block_slices slices to a workgroup, by mttkrp_block_slices unless asked for.
 int mttkrp_block_slices(int64_t I, int64_t nnz_hint, int compute_units);
-hipError_t launch_mttkrp_fibers(const MttkrpArgs& a, int block_slices, int lc, int vec, int xcds, hipStream_t s);
+hipError_t launch_mttkrp_fibers(const MttkrpArgs& a, int block_slices, int vec, int xcds, hipStream_t s);
 hipError_t launch_debug_group_seg_reduce(const float* in, const int32_t* span, float* out, int g, int lc,
                                          hipStream_t s);
 // MTTKRP with the stored entries as the unit of work (sgap_mttkrp_nnz.hip): g = lanes per segment group

@@ -1,0 +1,178 @@
+// Short runs of stored entries (rows of A, fibers of a tensor) by teams of lanes that go each at its own pace.
+//
+// A workgroup copies consecutive runs into LDS; a team takes consecutive runs, cut where the entries are about even, up to
+// eight entries of one run at a time.  The next eight are the same run's or the next one's, whatever the other teams of the
+// wavefront are at: where they all take a run each and meet before the next (a loop over a run's entries inside one over
+// runs), they wait for the longest of eight at every turn.  The figures are beside the
+// kernel (sgap_mttkrp_fibers.hip).
+//   lanes of a team   as many as the columns take, four each: nothing is handed from lane to lane, so that a team may lie
+//                     anywhere in a workgroup
+#pragma once
+#include "sgap_common.hpp"
+#include "sgap_gather.hpp"
+
+namespace sgap {
+
+// Rows of a dense operand by number; `ok` = false reads as zeros, without a branch where byte offsets have 32 bits (an offset
+// past the end of a buffer descriptor is not fetched).
+template <int VEC, bool OFF32>
+struct MaskedRows {
+    __amdgpu_buffer_rsrc_t rows;
+    uint32_t row_bytes, k_bytes;
+    const float* base;
+    int64_t J;
+    __device__ __forceinline__ MaskedRows(const float* X, int64_t count, int64_t j, uint32_t k)
+        : rows(__builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(X), 0, (int)(uint32_t)(OFF32 ? count * j * 4 : 0), 0x00020000)),
+          row_bytes((uint32_t)(j * 4)), k_bytes(k * 4), base(X + k), J(j)
+    {
+    }
+    __device__ __forceinline__ Vec<VEC> load(int32_t row, bool ok) const
+    {
+        Vec<VEC> r;
+        if constexpr (OFF32) {
+            const uint32_t off = ok ? __umul24((uint32_t)row, row_bytes) + k_bytes : 0xfffffffcu;
+            if constexpr (VEC == 4) {
+                typedef uint32_t raw_u4 __attribute__((ext_vector_type(4)));
+                const raw_u4 t = __builtin_amdgcn_raw_buffer_load_b128(rows, (int)off, 0, 0);
+                r.v[0] = __uint_as_float(t.x); r.v[1] = __uint_as_float(t.y); r.v[2] = __uint_as_float(t.z); r.v[3] = __uint_as_float(t.w);
+            } else if constexpr (VEC == 2) {
+                typedef uint32_t raw_u2 __attribute__((ext_vector_type(2)));
+                const raw_u2 t = __builtin_amdgcn_raw_buffer_load_b64(rows, (int)off, 0, 0);
+                r.v[0] = __uint_as_float(t.x); r.v[1] = __uint_as_float(t.y);
+            } else {
+                r.v[0] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rows, (int)off, 0, 0));
+            }
+        } else {
+            r.zero();
+            if (ok) r = load_vec<VEC>(base + (int64_t)row * J);
+        }
+        return r;
+    }
+};
+
+// Where a thread stands: computed anew in every phase through an opaque copy of its number, because the compiler would
+// hoist what follows from it out of the loops over columns and pieces and hold it in registers throughout the walk.
+struct FlatPlace {
+    int tid, team, chunk;
+    __device__ __forceinline__ explicit FlatPlace(int lanes)
+    {
+        tid = threadIdx.x;
+        asm volatile("" : "+v"(tid));
+        team = (int)(((float)tid + 0.5f) * __builtin_amdgcn_rcpf((float)lanes));  // (below 256 by up to 64: exact)
+        chunk = tid - team * lanes;
+    }
+};
+
+constexpr int kFlatBatch = 8;
+
+// ENTRIES and RUNS: the most of a piece.
+template <int ENTRIES, int RUNS>
+struct FlatShared {
+    __attribute__((aligned(16))) StagedEntry entry[ENTRIES + kFlatBatch];  // (a batch reads past the last one)
+    int32_t ptr[RUNS + 1];      // first entries of the piece's runs
+    int32_t start[kBlock + 1];  // a team's first run
+};
+
+// The piece's entries [e0, e0 + cnt) on their way into LDS, four neighbours to a thread, all of them requested before the
+// first is put down.  The caller synchronises.
+template <int ENTRIES, typename SH>
+__device__ __forceinline__ void flat_stage(SH& s, const int32_t* __restrict__ idx, const float* __restrict__ vals, int32_t e0,
+                                           int32_t cnt, int tid)
+{
+    typedef int32_t native_i4 __attribute__((ext_vector_type(4), aligned(4)));
+    constexpr int U = (ENTRIES + kBlock * 4 - 1) / (kBlock * 4);
+    idx += e0;
+    vals += e0;
+    native_i4 c[U];
+    native_f4 v[U];
+    int32_t last_c = 0;
+    float last_v = 0.0f;
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        const int q = (u * kBlock + tid) * 4;
+        if (q + 4 <= cnt) {
+            c[u] = __builtin_nontemporal_load(reinterpret_cast<const native_i4*>(idx + q));
+            v[u] = __builtin_nontemporal_load(reinterpret_cast<const native_f4*>(vals + q));
+        }
+    }
+    const int rest = (cnt & ~3) + tid;  // the last one to three
+    if (rest < cnt) {
+        last_c = load_stream(idx + rest);
+        last_v = load_stream(vals + rest);
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        const int q = (u * kBlock + tid) * 4;
+        if (q + 4 <= cnt) {
+            s.entry[q] = {c[u].x, v[u].x};
+            s.entry[q + 1] = {c[u].y, v[u].y};
+            s.entry[q + 2] = {c[u].z, v[u].z};
+            s.entry[q + 3] = {c[u].w, v[u].w};
+        }
+    }
+    if (rest < cnt) s.entry[rest] = {last_c, last_v};
+}
+
+// Where the teams begin: with whole runs, at the first one that starts at or behind an even share of the entries.  The caller
+// synchronises.
+template <typename SH>
+__device__ __forceinline__ void flat_deal(SH& s, int32_t e0, int32_t cnt, int n, int teams, int tid)
+{
+    const float per_share = __builtin_amdgcn_rcpf((float)(cnt > teams ? (cnt + teams - 1) / teams : 1));
+    auto team_of = [&](int run) {  // (a division of numbers up to 4,096: exact)
+        const int t = (int)(((float)(s.ptr[run] - e0) + 0.5f) * per_share);
+        return t < teams ? t : teams - 1;
+    };
+#pragma unroll 1
+    for (int i = tid; i < n; i += kBlock) {
+        const int mine = team_of(i);
+#pragma unroll 1
+        for (int t = i == 0 ? 0 : team_of(i - 1) + 1; t <= mine; ++t) s.start[t] = i;
+        if (i == n - 1)
+#pragma unroll 1
+            for (int t = mine + 1; t <= teams; ++t) s.start[t] = n;
+    }
+}
+
+// The runs [run, last), run < last.  ahead(run, ok) is called before the last entries of a run are multiplied (ok; else before
+// others), done(run, sum) when they are.
+template <int VEC, bool OFF32, typename SH, typename AHEAD, typename DONE>
+__device__ __forceinline__ void flat_walk(const SH& s, int run, int last, int32_t e0, const MaskedRows<VEC, OFF32>& X, bool k_ok,
+                                          AHEAD&& ahead, DONE&& done)
+{
+    constexpr int D = kFlatBatch;
+    Vec<VEC> sum;
+    sum.zero();
+    int32_t q = s.ptr[run] - e0, end = s.ptr[run + 1] - e0;
+#pragma unroll 1
+    do {
+        StagedEntry e[D];
+        Vec<VEC> b[D];
+        const int32_t left = k_ok ? end - q : 0;
+#pragma unroll
+        for (int u = 0; u < D; ++u) e[u] = s.entry[q + u];
+#pragma unroll
+        for (int u = 0; u < D; ++u) {
+            b[u] = X.load(e[u].col, u < left);
+            if (u >= left) e[u].val = 0.0f;
+        }
+        const bool ends = end - q <= D;
+        ahead(run, ends);
+        const int now = run;
+        if (ends) {
+            ++run;
+            q = end;
+            end = s.ptr[run + 1 <= last ? run + 1 : last] - e0;
+        } else {
+            q += D;
+        }
+#pragma unroll
+        for (int u = 0; u < D; ++u) sum.fma(e[u].val, b[u]);
+        if (ends) {
+            done(now, sum);
+            sum.zero();
+        }
+    } while (run < last);
+}
+
+}  // namespace sgap

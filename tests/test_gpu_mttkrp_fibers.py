@@ -1,5 +1,5 @@
 """MTTKRP by blocks of slices (parallel strategy): pieces of a block, slices that go on in the next one, and fibers that a
-piece has no room for (3,584 entries, 512 fibers).  Exact on integer values."""
+piece has no room for (3,328 entries, 512 fibers).  Exact on integer values."""
 import numpy as np
 import pytest
 import torch
@@ -22,7 +22,7 @@ def tensor(I, K, L, J, fibers, entries, seed):
 
 CASES = {
     # the room of a piece, one less and one more, alone and between others; fibers without entries at both ends
-    "long_fibers": ([0, 1, 3, 0, 2, 5, 1, 1, 4], [0, 3583, 3584, 3585, 7168, 1, 7169, 0, 2, 10753, 0]),
+    "long_fibers": ([0, 1, 3, 0, 2, 5, 1, 1, 4], [0, 3327, 3328, 3329, 6656, 1, 6657, 0, 2, 9985, 0]),
     # a slice over many pieces, more than 512 fibers of an entry or none each, and short slices around it
     "many_fibers": ([1, 0, 2, 1700, 1, 0, 511, 512, 513, 3], [1, 0, 2]),
     # pieces that end with a slice, in the middle of one, and before a fiber that would not fit
