@@ -258,6 +258,10 @@ bool row_quads_apply(int64_t M, int lc, int64_t tile_cols, double mean_row, int 
 hipError_t launch_row_quads(const SpmmArgs& a, int lc, int tile_cols, int xcds, hipStream_t s);
 // whether the parallel strategy of SDDMM takes a matrix in host memory by four rows together (g lanes per entry)
 bool sddmm_by_quads(int64_t M, int64_t K, int64_t J, int g, int64_t nnz_hint, const int32_t* rowptr, const int32_t* colidx);
+// serial strategy, short rows (sgap_flat_rows.hip).  flat_rows_apply: whether that is the kernel for so many rows of
+// mean_row stored entries; never without a count of them
+bool flat_rows_apply(int64_t K, int64_t N, double mean_row, int64_t nnz_hint);
+hipError_t launch_flat_rows(const SpmmArgs& a, int vec, int xcds, int compute_units, int64_t nnz_hint, hipStream_t s);
 // the same with g lanes per row reducing in sub-groups of r < g lanes whose sums
 // are merged with atomics; C must have been zeroed (launch_nnz_zero_rows, -1)
 hipError_t launch_row_split_partial(const SpmmArgs& a, int g, int r, int lc, int vec, int rows_per_slot,

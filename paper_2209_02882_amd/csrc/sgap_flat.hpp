@@ -4,7 +4,7 @@
 // eight entries of one run at a time.  The next eight are the same run's or the next one's, whatever the other teams of the
 // wavefront are at: where they all take a run each and meet before the next (a loop over a run's entries inside one over
 // runs), they wait for the longest of eight at every turn.  The figures are beside the
-// kernel (sgap_mttkrp_fibers.hip).
+// kernels (sgap_flat_rows.hip, sgap_mttkrp_fibers.hip).
 //   lanes of a team   as many as the columns take, four each: nothing is handed from lane to lane, so that a team may lie
 //                     anywhere in a workgroup
 #pragma once

@@ -1,0 +1,168 @@
+// Row-split schedule, serial strategy, short rows: teams of lanes go through consecutive rows each at its own pace
+// (sgap_flat.hpp).  A workgroup owns a block of consecutive rows and takes them in pieces (one, as a rule); every row has one
+// owner and one plain store, and its entries are added up one after the other.
+//
+// Bound by the gathers from beyond the L2s where B is large (2,000,000 rows of 1 to 16 entries, N = 32, a B of 8.4 MB: 1.6 GB
+// at 7.5 TB/s), else by the address units.  us, a lane group per row that meets the others of its wavefront after each
+// (row_split_kernel) / this, rows of 1 to 16 entries: 2,000,000 rows, N = 32, B of 8.4 MB 217 / 214, of 2.6 MB 202 / 164;
+// N = 16, 4.2 MB 170 / 146; 160,000, N = 48 31.9 / 22.3; 225,000, N = 24 24.8 / 20.4; 115,000, N = 16, four rows to a lane
+// 17.2 / 10.2; 93,000, N = 16 9.9 / 9.4.  1,000,000 rows of 2 entries, N = 32 70.6 / 62.7.
+#include "sgap_common.hpp"
+#include "sgap_flat.hpp"
+#include "sgap_nnz_common.hpp"
+
+namespace sgap {
+
+constexpr int kFrEntries = 2560;   // entries of a piece at most: four workgroups' LDS, as many as the registers leave
+constexpr int kFrRows = 1024;      // rows of a piece at most
+constexpr int kFrResident = 4;     // workgroups of a compute unit
+constexpr int kFrMean = 1900;      // entries of a block in the mean at most
+constexpr int kFrTile = 32;        // columns of a tile: a cache line of each row of B
+
+template <int VEC, bool OFF32>
+__global__ __launch_bounds__(kBlock) void flat_rows_kernel(SpmmArgs a, int lanes, int block_rows, int64_t blocks, int64_t blocks_per_xcd,
+                                                           int xcds, int tile_cols)
+{
+    __shared__ FlatShared<kFrEntries, kFrRows> s;
+    __shared__ Vec<VEC> s_part[kBlock];
+    const int teams = kBlock / lanes;
+    // workgroup b runs on die b % xcds: every die gets one contiguous run of blocks, tile by tile
+    int64_t block = (int64_t)(blockIdx.x % xcds) * blocks_per_xcd + blockIdx.x / xcds;
+    const int64_t tiles = (a.N + tile_cols - 1) / tile_cols;
+    if (block >= blocks * tiles) return;  // the whole workgroup
+    const int64_t tile_first = block / blocks * tile_cols, tile_last = tile_first + tile_cols < a.N ? tile_first + tile_cols : a.N;
+    block %= blocks;
+    const int64_t row_first = block * block_rows;
+    const int64_t row_last = row_first + block_rows < a.M ? row_first + block_rows : a.M;
+
+    for (int64_t k0 = tile_first; k0 < tile_last; k0 += (int64_t)lanes * VEC) {
+        struct Columns {
+            bool ok;
+            uint32_t first;  // of the VEC columns this lane holds
+            __device__ __forceinline__ Columns(const FlatPlace& p, int64_t k0, int64_t N, int teams)
+            {
+                const uint32_t k = (uint32_t)k0 + p.chunk * VEC;  // N < 2^31
+                ok = k < (uint32_t)N && p.team < teams;
+                first = ok ? lane_first_col<VEC>(k, (uint32_t)N) : 0;
+            }
+        };
+        for (int64_t r0 = row_first; r0 < row_last;) {
+            int n = row_last - r0 < kFrRows ? (int)(row_last - r0) : kFrRows;
+            __syncthreads();  // the piece before is done with
+            {
+                const FlatPlace p(lanes);
+                for (int i = p.tid; i <= n; i += kBlock) s.ptr[i] = a.rowptr[r0 + i];
+            }
+            __syncthreads();
+            const int32_t e0 = __builtin_amdgcn_readfirstlane(s.ptr[0]);
+            if (s.ptr[n] - e0 > kFrEntries) {
+                const FlatPlace p(lanes);
+                int fit = 0;
+                for (int i = 0; i < n; i += kBlock) fit += __syncthreads_count(i + p.tid < n && s.ptr[i + p.tid + 1] - e0 <= kFrEntries);
+                n = fit;
+            }
+            n = __builtin_amdgcn_readfirstlane(n);
+            if (n == 0) {
+                // a row of more entries than there is room for: all teams together
+                const FlatPlace p(lanes);
+                const Columns c(p, k0, a.N, teams);
+                const MaskedRows<VEC, OFF32> B(a.B, a.K, a.N, c.first);
+                const int32_t e1 = __builtin_amdgcn_readfirstlane(s.ptr[1]);
+                Vec<VEC> t;
+                t.zero();
+                for (int32_t base = e0; base < e1; base += kFrEntries) {
+                    const int32_t cnt = e1 - base < kFrEntries ? e1 - base : kFrEntries;
+                    __syncthreads();
+                    flat_stage<kFrEntries>(s, a.colidx, a.vals, base, cnt, p.tid);
+                    __syncthreads();
+#pragma unroll 1
+                    for (int q = p.team; c.ok && q < cnt; q += teams) t.fma(s.entry[q].val, B.load(s.entry[q].col, true));
+                }
+                s_part[p.tid] = t;
+                __syncthreads();
+                if (p.team == 0 && c.ok) {
+#pragma unroll 1
+                    for (int m = 1; m < teams; ++m) {
+                        const Vec<VEC> other = s_part[m * lanes + p.chunk];
+#pragma unroll
+                        for (int i = 0; i < VEC; ++i) t.v[i] += other.v[i];
+                    }
+                    store_vec_stream<VEC>(a.C + r0 * a.N + c.first, t);
+                }
+                ++r0;
+                continue;
+            }
+            const int32_t cnt = __builtin_amdgcn_readfirstlane(s.ptr[n]) - e0;
+            {
+                const FlatPlace p(lanes);
+                flat_stage<kFrEntries>(s, a.colidx, a.vals, e0, cnt, p.tid);
+                flat_deal(s, e0, cnt, n, teams, p.tid);
+            }
+            __syncthreads();
+            {
+                const FlatPlace p(lanes);
+                const Columns c(p, k0, a.N, teams);
+                float* const C = a.C + r0 * a.N + c.first;
+                const uint32_t N = (uint32_t)a.N;
+                auto store = [&](uint32_t row, const Vec<VEC>& sum) { store_vec_stream<VEC>(C + (uint64_t)row * N, sum); };
+                const int first = c.ok ? s.start[p.team] : 0, last = c.ok ? s.start[p.team + 1] : 0;
+                if (first < last) {
+                    const MaskedRows<VEC, OFF32> B(a.B, a.K, a.N, c.first);
+                    flat_walk<VEC, OFF32>(s, first, last, e0, B, true, [](int, bool) {}, [&](int row, const Vec<VEC>& sum) { store((uint32_t)row, sum); });
+                }
+            }
+            r0 += n;
+        }
+    }
+}
+
+namespace {
+
+// Column tiles: where B is larger than a die's L2 and a tile of it is not much larger, dies with a tile each gather more out of
+// their L2s (items go tile by tile over the dies).  Not where rows of B begin amid cache lines.  us for the whole B / tiles of
+// 32 columns, 2,000,000 rows of 1 to 16 entries, N = 64, B of 5 MB 292 / 324, 6.4 MB 324 / 324, 8.4 MB 391 / 337, 16.8 MB
+// 545 / 441, 33.6 MB 632 / 610, 51 MB 663 / 671; 760,000 rows, N = 128, 10 MB 327 / 260, 33.6 MB 480 / 348; N = 96, 15 MB
+// 295 / 200.
+int64_t flat_tile(int64_t K, int64_t N)
+{
+    const bool tiles = N % kFrTile == 0 && N > kFrTile && K * N * 4 > (6 << 20) && K * kFrTile * 4 <= (14 << 20);
+    return tiles ? kFrTile : N;
+}
+
+}  // namespace
+
+// Fewer entries than kFlatMinEntries are a chain of loads that is longer here (60,000 rows of 8, N = 5 5.8 us, here 6.1; 10,000,
+// N = 32 4.2 and 5.1).  Rows of more entries leave few lanes idle there (300,000 of 24, N = 32 97.8, here 98.3).  Wide rows
+// of a large B, whole, are faster there: 2,000,000 rows of 1 to 16 entries, N = 64, B of 51 MB 643 and 663.
+bool flat_rows_apply(int64_t K, int64_t N, double mean_row, int64_t nnz_hint)
+{
+    constexpr int64_t kFlatMinEntries = 500'000;
+    constexpr double kFlatMean = 12.0;
+    return nnz_hint >= kFlatMinEntries && mean_row <= kFlatMean && (N <= 48 || flat_tile(K, N) < N || (N <= 64 && K * N * 4 <= (6 << 20)));
+}
+
+hipError_t launch_flat_rows(const SpmmArgs& a, int vec, int xcds, int compute_units, int64_t nnz_hint, hipStream_t s)
+{
+    const int64_t tile_cols = flat_tile(a.K, a.N);
+    const int64_t chunks = (tile_cols + vec - 1) / vec, tiles = (a.N + tile_cols - 1) / tile_cols;
+    const int lanes = chunks < kWave ? (int)chunks : kWave;
+    // blocks of even numbers of rows, as many as make whole rounds of the resident workgroups
+    const int64_t resident = (int64_t)kFrResident * compute_units;
+    const int64_t rounds = nnz_hint / (resident * kFrMean) + 1;
+    int64_t rows = (a.M + resident * rounds - 1) / (resident * rounds);
+    if (rows > kFrRows) rows = kFrRows;
+    const int64_t blocks = (a.M + rows - 1) / rows;
+    const int64_t blocks_per_xcd = (blocks * tiles + xcds - 1) / xcds;
+    if (blocks_per_xcd * xcds > 0x7ffffff0LL) return hipErrorInvalidValue;
+    auto go = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, dim3((unsigned)(blocks_per_xcd * xcds)), dim3(kBlock), 0, s, a, lanes, (int)rows, blocks, blocks_per_xcd, xcds,
+                           (int)tile_cols);
+    };
+    const bool off32 = offsets_fit_32(a);
+    if (vec == 4) { if (off32) go(flat_rows_kernel<4, true>); else go(flat_rows_kernel<4, false>); }
+    else if (vec == 2) { if (off32) go(flat_rows_kernel<2, true>); else go(flat_rows_kernel<2, false>); }
+    else { if (off32) go(flat_rows_kernel<1, true>); else go(flat_rows_kernel<1, false>); }
+    return hipGetLastError();
+}
+
+}  // namespace sgap
