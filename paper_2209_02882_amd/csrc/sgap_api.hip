@@ -472,9 +472,11 @@ int spmm_impl(int64_t M, int64_t K, int64_t N, const int32_t* rowptr, const int3
                                     : plan_nnz_serial(group_size, lc, vec, nnz_hint, compute_units(), c.nnz_tile);
         a.group = plan.share;
         a.log2_group = ilog2(plan.share);
-        err = launch_nnz_zero_rows(a, vec, plan.merge_log2, s);
+        const int flat_tile = par || c.nnz_tile != 0 ? 0 : nnz_flat_tile(N, group_size, (double)nnz_hint / (double)M, nnz_hint, compute_units());
+        err = launch_nnz_zero_rows(a, vec, flat_tile > 0 ? ilog2(flat_tile) : plan.merge_log2, s);
         if (err == hipSuccess)
-            err = narrow ? launch_nnz_narrow(a, compute_units(), nnz_hint, s)
+            err = flat_tile > 0 ? launch_nnz_flat(a, flat_tile, compute_units(), nnz_hint, s)
+                  : narrow ? launch_nnz_narrow(a, compute_units(), nnz_hint, s)
                   : par  ? launch_nnz_parallel(a, lc, vec, plan, compute_units(), nnz_hint, s)
                          : launch_nnz_serial(a, lc, vec, plan, compute_units(), nnz_hint, s);
     }

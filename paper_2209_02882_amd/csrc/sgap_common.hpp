@@ -290,6 +290,10 @@ hipError_t launch_nnz_parallel(const SpmmArgs& a, int lc, int vec, const NnzPlan
                                int64_t nnz_hint, hipStream_t s);
 // the same for N <= kNarrowColumns (sgap_nnz_narrow.hip)
 hipError_t launch_nnz_narrow(const SpmmArgs& a, int compute_units, int64_t nnz_hint, hipStream_t s);
+// the serial strategy by teams of lanes that go each at its own pace (sgap_nnz_flat.hip); nnz_flat_tile: the tile, 0 where
+// that is not the kernel
+int nnz_flat_tile(int64_t N, int group, double mean_row, int64_t nnz_hint, int compute_units);
+hipError_t launch_nnz_flat(const SpmmArgs& a, int tile, int compute_units, int64_t nnz_hint, hipStream_t s);
 hipError_t launch_nnz_serial(const SpmmArgs& a, int lc, int vec, const NnzPlan& plan, int compute_units,
                              int64_t nnz_hint, hipStream_t s);
 // r = members per reducing sub-group (r = g: the whole group)

@@ -4,7 +4,7 @@
 // eight entries of one run at a time.  The next eight are the same run's or the next one's, whatever the other teams of the
 // wavefront are at: where they all take a run each and meet before the next (a loop over a run's entries inside one over
 // runs), they wait for the longest of eight at every turn.  The figures are beside the
-// kernels (sgap_flat_rows.hip, sgap_mttkrp_fibers.hip).
+// kernels (sgap_flat_rows.hip, sgap_mttkrp_fibers.hip, sgap_nnz_flat.hip).
 //   lanes of a team   as many as the columns take, four each: nothing is handed from lane to lane, so that a team may lie
 //                     anywhere in a workgroup
 #pragma once
@@ -173,6 +173,23 @@ __device__ __forceinline__ void flat_walk(const SH& s, int run, int last, int32_
             sum.zero();
         }
     } while (run < last);
+}
+
+// What the teams from number `from` on have of a run that began in front of them, added to sum in order, up to the one where it
+// ends; whether it does.
+template <int VEC>
+__device__ __forceinline__ bool add_heads(Vec<VEC>& sum, const Vec<VEC>* __restrict__ head, const uint8_t* __restrict__ ended, int from,
+                                          int teams, int lanes, int chunk)
+{
+    bool done = false;
+#pragma unroll 1
+    for (int t = from; t < teams && !done; ++t) {
+        const Vec<VEC> other = head[t * lanes + chunk];
+#pragma unroll
+        for (int i = 0; i < VEC; ++i) sum.v[i] += other.v[i];
+        done = ended[t] != 0;
+    }
+    return done;
 }
 
 }  // namespace sgap

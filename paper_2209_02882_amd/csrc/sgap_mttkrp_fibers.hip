@@ -196,14 +196,7 @@ __global__ __launch_bounds__(kBlock) void mttkrp_fibers_kernel(MttkrpArgs a, int
                     slice = came_in;
                 }
                 if (!goes_on) continue;
-                bool ended = false;
-#pragma unroll 1
-                for (int t = round == 1 ? 0 : p.team + 1; t < teams && !ended; ++t) {
-                    const Vec<VEC> other = s_head[t * lanes + p.chunk];
-#pragma unroll
-                    for (int i = 0; i < VEC; ++i) sum.v[i] += other.v[i];
-                    ended = s_ended[t] != 0;
-                }
+                const bool ended = add_heads<VEC>(sum, s_head, s_ended, round == 1 ? 0 : p.team + 1, teams, lanes, p.chunk);
                 if (ended) store(slice, c, sum);
                 else s_carry[turn ^ 1][p.chunk] = sum;
             }

@@ -1,0 +1,247 @@
+// Nnz-balanced schedule, serial strategy, 16 to 128 columns: {<g nnz, c col>, 1} (Section 6.1) with a tile's entries dealt out to
+// teams of lanes that go through them each at its own pace (sgap_flat.hpp), whatever group_size says.
+//
+// A tile of stored entries comes into LDS with its rows that have entries.  A team takes consecutive entries, eight of one
+// row at a time; a row that begins and ends among them is stored plainly.  What a team has of a row that began in front of
+// it goes to LDS, where the team that has the row's beginning adds it up in order; the two rows that cross a tile's ends are
+// added into C with atomics (the merge rule of sgap_nnz_common.hpp with the tile as its block).  No LDS atomics, no slots.
+// The teams' shares are even in the turns that they take rather than in entries: a row counts kRowCost entries beside its own,
+// since its last turn is seldom full (R-MAT, 2^19 rows, N = 32: 158 us with shares of entries, 115 so).
+//
+// With fixed shares, batches of eight whatever the rows' ends, and a flush wherever one fell (nnz_serial_kernel, which serves
+// other widths), each entry cost a look at its row's end and row sums met in LDS slots by compare-and-swap.  Large R-MAT
+// matrices are bound by their 128-byte reads either way (2^21 rows, 50 M entries, N = 32: 6.2 TB/s).  us, before / now:
+//   power law, 65,536 rows, N = 64, G = 16 52.1 / 43.4; the same with N = 32 46.0 / 25.8; 300,000 rows, N = 64 198 / 190;
+//   10,000 rows, N = 85 19.7 / 14.6; 8,000 rows, N = 20 14.4 / 13.0; uniform, 60,000 rows of 32, N = 64, G = 8 103 / 65;
+//   R-MAT, 2^21 rows, 30 M edges, N = 32, G = 16 501 / 422, 50 M entries, G = 32 711 / 707; 2^19 rows, 8 M edges, N = 32 148 / 112,
+//   N = 16, G = 2 395 / 100; 2^17 rows, 2.5 M edges, N = 128 121 / 114
+#include "sgap_common.hpp"
+#include "sgap_flat.hpp"
+#include "sgap_nnz_common.hpp"
+
+namespace sgap {
+
+namespace {
+
+constexpr int kRowCost = 6;    // (with 3, 9 and 13 up to 4 % slower)
+constexpr int kNfTile = 1024;  // entries of a tile at most
+constexpr int kNfResident = 5;  // workgroups of a compute unit
+static_assert(kNfTile <= kWindowCap, "a row of the window for every entry of a tile");
+
+struct NnzFlatShared {
+    __attribute__((aligned(16))) StagedEntry entry[kNfTile + kFlatBatch];  // (a batch reads past the last one)
+    int32_t win[kWindowCap + 1];  // first positions of the tile's rows with entries
+    int32_t row[kWindowCap];      // ... and their numbers
+    Vec<4> head[kBlock];     // what a team has of a row that began in front of its entries
+    uint8_t ended[kBlock];   // whether that row ends there
+    float edge[2][4 * kWave];  // of the rows that cross the tile's ends: the one that comes in, the one that goes on
+    int32_t edge_row[2];     // -1: none
+    int32_t begin[kBlock + 1], begin_row[kBlock + 1];  // a team's first entry, and the window's row that holds it
+    int32_t scan[kWavesPerBlock];
+    int32_t tile_row[kTileRowBatch];
+};
+
+}  // namespace
+
+template <bool OFF32>
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(kNfResident)))
+void nnz_flat_kernel(SpmmArgs a, int lanes, int teams, int tile)
+{
+    __shared__ NnzFlatShared s;
+    const int32_t M = (int32_t)a.M;
+    const int32_t nnz = a.rowptr[a.M];
+    const TileDeal deal(((int64_t)nnz + tile - 1) / tile, blockIdx.x, gridDim.x);
+    if (deal.mine == 0) return;
+    TileWalk at(deal);
+    if (threadIdx.x < 2) s.edge_row[threadIdx.x] = -1;
+
+    const uint32_t N = (uint32_t)a.N;  // at most a wavefront's columns
+
+    const int mine = (int)deal.mine;
+    for (int j0 = 0; j0 < mine; j0 += kTileRowBatch) {
+        find_tile_rows(a, deal, j0, tile, s.tile_row);
+        const int j1 = j0 + kTileRowBatch < mine ? j0 + kTileRowBatch : mine;
+        for (int j = j0; j < j1; ++j) {
+            const int32_t tile_start = (int32_t)(at.tile() * tile);
+            at.next();
+            const int32_t cnt = nnz - tile_start < tile ? nnz - tile_start : tile;
+            const int32_t row_lb = s.tile_row[j - j0];
+            {
+                const FlatPlace p(lanes);
+                constexpr int WPT = kWindowCap / kBlock + 1;
+                int32_t win[WPT];
+#pragma unroll
+                for (int i = 0; i < WPT; ++i) {
+                    const int w = p.tid + i * kBlock;
+                    const int64_t r = (int64_t)row_lb + w;
+                    win[i] = w <= kWindowCap ? a.rowptr[r <= M ? r : M] : 0;
+                }
+                flat_stage<kNfTile>(s, a.colidx, a.vals, tile_start, cnt, p.tid);
+#pragma unroll
+                for (int i = 0; i < WPT; ++i)
+                    if (p.tid + i * kBlock <= kWindowCap) s.win[p.tid + i * kBlock] = win[i];
+            }
+            __syncthreads();
+            int32_t n;
+            if (s.win[kWindowCap] >= tile_start + cnt) {
+                n = compact_window(s.win, s.row, row_lb, tile_start + cnt, s.scan);
+            } else {
+                __syncthreads();  // everyone has read the plain window
+                n = load_compact_window(a, row_lb, tile_start + cnt, s.win, s.row, s.scan);
+            }
+            n = __builtin_amdgcn_readfirstlane(n);
+            // Where the teams begin: even shares of the turns that a team will take.  A row counts as kRowCost entries beside its own.
+            {
+                const FlatPlace p(lanes);
+                if (p.tid <= teams) {
+                    const int32_t x = (int32_t)((float)((cnt + kRowCost * n) * p.tid) * __builtin_amdgcn_rcpf((float)teams));
+                    int32_t lo = 0, hi = n - 1;
+                    auto first_of = [&](int32_t i) {
+                        const int32_t at = s.win[i] - tile_start;
+                        return at > 0 ? at : 0;
+                    };
+                    while (lo < hi) {
+                        const int32_t mid = (lo + hi + 1) / 2;
+                        if (first_of(mid) + kRowCost * mid <= x) lo = mid; else hi = mid - 1;
+                    }
+                    const int32_t first = first_of(lo), last = s.win[lo + 1] - tile_start < cnt ? s.win[lo + 1] - tile_start : cnt;
+                    int32_t q = x - kRowCost * (lo + 1);
+                    q = p.tid == 0 ? 0 : p.tid == teams ? cnt : q < first ? first : q;
+                    if (q >= last) {
+                        q = last;
+                        ++lo;
+                    }
+                    s.begin[p.tid] = q;
+                    s.begin_row[p.tid] = lo;
+                }
+            }
+            __syncthreads();
+
+            {
+                const FlatPlace p(lanes);
+                const uint32_t k = p.chunk * 4, first_col = lane_first_col<4>(k, N);
+                int32_t q = p.team < teams ? s.begin[p.team] : 0;
+                const int32_t end = p.team < teams ? s.begin[p.team + 1] : 0;  // of this team's entries
+                auto store = [&](int32_t row, const Vec<4>& sum) {
+                    store_vec_stream<4>(a.C + ((uint64_t)(uint32_t)row * N + first_col), sum);
+                };
+                Vec<4> sum;
+                sum.zero();
+                int wi = 0;
+                bool goes_on = false, head_ends = false;
+                if (q < end) {
+                    const MaskedRows<4, OFF32> B(a.B, a.K, a.N, first_col);
+                    wi = s.begin_row[p.team];
+                    bool whole = s.win[wi] - tile_start == q;  // the row begins with this team's entries
+                    int32_t row_end = s.win[wi + 1] - tile_start;
+#pragma unroll 1
+                    do {
+                        constexpr int D = kFlatBatch;
+                        StagedEntry e[D];
+                        Vec<4> b[D];
+                        const int32_t stop = row_end < end ? row_end : end;
+                        const int32_t left = stop - q;
+#pragma unroll
+                        for (int u = 0; u < D; ++u) e[u] = s.entry[q + u];
+#pragma unroll
+                        for (int u = 0; u < D; ++u) {
+                            b[u] = B.load(e[u].col, u < left);
+                            if (u >= left) e[u].val = 0.0f;
+                        }
+                        const bool ends = stop - q <= D;
+                        const bool row_done = ends && row_end <= end;
+                        const int now = wi;
+                        q = ends ? stop : q + D;
+                        if (row_done) {
+                            ++wi;
+                            row_end = s.win[wi + 1 <= n ? wi + 1 : n] - tile_start;
+                        }
+#pragma unroll
+                        for (int u = 0; u < D; ++u) sum.fma(e[u].val, b[u]);
+                        if (row_done) {
+                            if (whole) {
+                                store(s.row[now], sum);
+                            } else {
+                                s.head[p.tid] = sum;
+                                head_ends = true;
+                            }
+                            sum.zero();
+                            whole = true;
+                        } else if (ends) {
+                            if (whole) goes_on = true;
+                            else s.head[p.tid] = sum;
+                        }
+                    } while (q < end);
+                } else {
+                    s.head[p.tid] = sum;
+                }
+                if (p.team < teams && p.chunk == 0) s.ended[p.team] = head_ends ? 1 : 0;
+                if (p.tid < 2) s.edge_row[p.tid] = -1;
+                __syncthreads();
+                // a row that goes on is added up, in order, by the team that has its beginning; what came in from the tile in
+                // front by the first team
+#pragma unroll 1
+                for (int round = 0; round < 2; ++round) {
+                    if (round == 1) {
+                        goes_on = p.team == 0 && s.win[0] < tile_start;
+                        sum.zero();
+                        wi = 0;
+                    }
+                    if (!goes_on) continue;
+                    const bool ended = add_heads<4>(sum, s.head, s.ended, round == 1 ? 0 : p.team + 1, teams, lanes, p.chunk);
+                    if (round == 0 && ended) {
+                        store(s.row[wi], sum);
+                    } else {
+                        if (p.chunk == 0) s.edge_row[1 - round] = s.row[wi];
+                        from_last_columns<4>(sum, (int)(k - first_col));
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) s.edge[1 - round][p.chunk * 4 + i] = sum.v[i];
+                    }
+                }
+                __syncthreads();
+                // (an atomic instruction over consecutive words costs a quarter of one whose lanes are 16 bytes apart)
+                for (uint32_t i = p.tid; i < 2 * N; i += kBlock) {
+                    const uint32_t which = i >= N ? 1 : 0, col = i - which * N;
+                    const int32_t row = s.edge_row[which];
+                    if (row >= 0) unsafeAtomicAdd(a.C + ((uint64_t)(uint32_t)row * N + col), s.edge[which][col]);
+                }
+            }
+            // (the next tile's entries and window are put down behind what the walk and the sums have read; the edges' places are
+            // written again two barriers from here)
+        }
+    }
+}
+
+// The tile for a matrix, 0 where this is not the kernel.  Fewer columns leave a team with a lane or two (65,536 rows of a power
+// law, N = 8: 19.9 us by shares of entries, 24.0 here), with more a tile has too few teams (100,000 rows, N = 200 220 and
+// 219; R-MAT, 2^17 rows, N = 256 276 and 282).  A team has some 16 to 32 entries of a tile; 33 to 64 columns take the larger
+// tile where all of them fit the chip at once (power law, 65,536 rows, N = 64: 43.4 us with 1,030 tiles of 1,024 entries,
+// 45.7 with 512; 300,000 rows 200 and 192).  A small matrix has smaller tiles (10,000 rows, N = 44 16.6 us with 512 entries
+// and 17.3 with 1,024).  Where rows are long and the caller asks for shares of 64 entries nothing is left for this kernel to
+// gain (5,000 rows of 4,000, N = 16 179 us and 199, 40,000 of 300 118 and 121; shares of 16 145 and 122).
+int nnz_flat_tile(int64_t N, int group, double mean_row, int64_t nnz_hint, int compute_units)
+{
+    if (N < 16 || N > 128 || (N <= 32 && group > 32 && mean_row >= 200.0)) return 0;
+    int tile = N <= 32 ? kNfTile : N <= 64 ? kNfTile / 2 : kNfTile / 4;
+    if (nnz_hint < 0) return tile;
+    if (N > 32 && N <= 64 && nnz_hint > kNfTile * 3 * (int64_t)compute_units && nnz_hint <= kNfTile * kNfResident * (int64_t)compute_units)
+        tile = kNfTile;
+    const int least = N <= 32 ? kNfTile / 2 : kNfTile / 4;
+    while (tile > least && 2 * (nnz_hint / tile) < 5 * (int64_t)compute_units) tile /= 2;
+    return tile;
+}
+
+hipError_t launch_nnz_flat(const SpmmArgs& a, int tile, int compute_units, int64_t nnz_hint, hipStream_t s)
+{
+    const int lanes = (int)((a.N + 3) / 4);
+    auto go = [&](auto kernel, int& per_cu) {
+        if (per_cu == 0) per_cu = resident_per_cu(kernel, 0);
+        hipLaunchKernelGGL(kernel, dim3(persistent_grid(per_cu, compute_units, nnz_hint, tile)), dim3(kBlock), 0, s, a, lanes, kBlock / lanes, tile);
+    };
+    static int per_cu[2];  // resident workgroups of a compute unit, 0 = not asked yet
+    if (offsets_fit_32(a)) go(nnz_flat_kernel<true>, per_cu[0]);
+    else go(nnz_flat_kernel<false>, per_cu[1]);
+    return hipGetLastError();
+}
+
+}  // namespace sgap
