@@ -326,8 +326,11 @@ hipError_t launch_debug_group_seg_reduce(const float* in, const int32_t* span, f
 // (parallel) or entries per lane (serial); Y must hold zeros.
 hipError_t launch_mttkrp_nnz(const MttkrpArgs& a, int g, bool parallel, int lc, int vec, int compute_units,
                              int64_t nnz_hint, hipStream_t s);
-hipError_t launch_mttkrp_serial(const MttkrpArgs& a, int lc, int vec, int compute_units, int64_t nnz_hint,
-                                hipStream_t s);
+// its serial strategy: by teams of lanes at their own pace (sgap_mttkrp_fibers.hip), or, few entries of few columns
+// (sgap_mttkrp_serial.hip), by lanes with an even share each
+hipError_t launch_mttkrp_tiles(const MttkrpArgs& a, int vec, int compute_units, int64_t nnz_hint, hipStream_t s);
+bool mttkrp_serial_applies(int64_t J, int64_t nnz_hint);
+hipError_t launch_mttkrp_serial(const MttkrpArgs& a, int lc, int vec, int compute_units, int64_t nnz_hint, hipStream_t s);
 // Rows grouped by a coarse key (sgap_reorder.hip): the permutation and the permuted copy of the matrix.
 int64_t reorder_workspace_bytes(int64_t M);
 hipError_t launch_reorder_rows(int64_t M, int64_t K, const int32_t* rowptr, const int32_t* colidx, const float* vals,

@@ -113,37 +113,58 @@ __device__ __forceinline__ void flat_stage(SH& s, const int32_t* __restrict__ id
     if (rest < cnt) s.entry[rest] = {last_c, last_v};
 }
 
-// Where the teams begin: with whole runs, at the first one that starts at or behind an even share of the entries.  The caller
-// synchronises.
-template <typename SH>
+// Where the teams begin: with whole runs, at the first one that starts at or behind an even share of the entries; CUT: with the
+// even share itself where that lies in a run of more than kFlatCut entries, and s.start is made of flat_at().  The caller synchronises.
+// (A team may meet a fiber of any length: 20,000 slices of two fibers of 100 entries each, J = 32, 271 us by a lane group per
+// slice, 49 by teams that share the fibers.  Shorter ones stay whole: a cut costs a turn, and a head to add up.)
+constexpr int kFlatCut = 32;
+__device__ __forceinline__ int32_t flat_at(int run, int32_t pos) { return run | pos << 16; }
+
+template <bool CUT, typename SH>
 __device__ __forceinline__ void flat_deal(SH& s, int32_t e0, int32_t cnt, int n, int teams, int tid)
 {
-    const float per_share = __builtin_amdgcn_rcpf((float)(cnt > teams ? (cnt + teams - 1) / teams : 1));
+    const int32_t share = cnt > teams ? (cnt + teams - 1) / teams : 1;
+    const float per_share = __builtin_amdgcn_rcpf((float)share);
     auto team_of = [&](int run) {  // (a division of numbers up to 4,096: exact)
         const int t = (int)(((float)(s.ptr[run] - e0) + 0.5f) * per_share);
         return t < teams ? t : teams - 1;
     };
+    // the teams behind `from` up to `to` whose share begins behind the beginning of run i - 1, at the latest with run i
+    auto set = [&](int from, int to, int i) {
+        int32_t pos = 0, before = 0;
+        if constexpr (CUT) {
+            pos = s.ptr[i] - e0;
+            before = i > 0 ? s.ptr[i - 1] - e0 : 0;
+        }
+#pragma unroll 1
+        for (int t = from + 1; t <= to; ++t) {
+            if constexpr (!CUT) s.start[t] = i;
+            else if (pos - before > kFlatCut && t * share < pos) s.start[t] = flat_at(i - 1, t * share);
+            else s.start[t] = flat_at(i, pos);
+        }
+    };
 #pragma unroll 1
     for (int i = tid; i < n; i += kBlock) {
         const int mine = team_of(i);
-#pragma unroll 1
-        for (int t = i == 0 ? 0 : team_of(i - 1) + 1; t <= mine; ++t) s.start[t] = i;
-        if (i == n - 1)
-#pragma unroll 1
-            for (int t = mine + 1; t <= teams; ++t) s.start[t] = n;
+        set(i == 0 ? -1 : team_of(i - 1), mine, i);
+        if (i == n - 1) set(mine, teams, n);
     }
 }
 
-// The runs [run, last), run < last.  ahead(run, ok) is called before the last entries of a run are multiplied (ok; else before
-// others), done(run, sum) when they are.
+// The runs [run, last), run < last, from entry q (of run `run`) on up to entry `stop`.  ahead(run, ok) is called before the last
+// entries of a run are multiplied (ok; else before others), done(run, sum) when they are.
 template <int VEC, bool OFF32, typename SH, typename AHEAD, typename DONE>
-__device__ __forceinline__ void flat_walk(const SH& s, int run, int last, int32_t e0, const MaskedRows<VEC, OFF32>& X, bool k_ok,
-                                          AHEAD&& ahead, DONE&& done)
+__device__ __forceinline__ void flat_walk(const SH& s, int run, int last, int32_t q, int32_t stop, int32_t e0,
+                                          const MaskedRows<VEC, OFF32>& X, bool k_ok, AHEAD&& ahead, DONE&& done)
 {
     constexpr int D = kFlatBatch;
     Vec<VEC> sum;
     sum.zero();
-    int32_t q = s.ptr[run] - e0, end = s.ptr[run + 1] - e0;
+    auto end_of = [&](int r) {
+        const int32_t e = s.ptr[r + 1 <= last ? r + 1 : last] - e0;
+        return e < stop ? e : stop;
+    };
+    int32_t end = end_of(run);
 #pragma unroll 1
     do {
         StagedEntry e[D];
@@ -162,7 +183,7 @@ __device__ __forceinline__ void flat_walk(const SH& s, int run, int last, int32_
         if (ends) {
             ++run;
             q = end;
-            end = s.ptr[run + 1 <= last ? run + 1 : last] - e0;
+            end = end_of(run);
         } else {
             q += D;
         }
@@ -175,20 +196,71 @@ __device__ __forceinline__ void flat_walk(const SH& s, int run, int last, int32_
     } while (run < last);
 }
 
+// What teams have of runs that began in front of them.
+template <int VEC>
+struct FlatHeads {
+    static constexpr int kTeams = 8;  // to a batch
+    Vec<VEC> head[kBlock];
+    uint8_t ended[kBlock];            // whether the run ends there
+    // Batches of teams, summed by a team each: where all teams of a tile are at one run, the first of them otherwise waits for
+    // one LDS read after the other.  MTTKRP by tiles, 100,000 slices, one in a thousand of 2,000 to 20,000 fibers, us without /
+    // with: J = 4 185 / 115, J = 1 117 / 96; 15,510 slices, J = 16 31.5 / 29.
+    Vec<VEC> batch[kBlock / kTeams];
+    uint8_t batch_ended[kBlock / kTeams];
+};
+
+// The caller synchronises in front of it and behind it.
+template <int VEC>
+__device__ __forceinline__ void batch_heads(FlatHeads<VEC>& s, int teams, int lanes, const FlatPlace& p)
+{
+    constexpr int T = FlatHeads<VEC>::kTeams;
+    if (p.team < teams / T) {
+        Vec<VEC> sum;
+        sum.zero();
+        int any = 0;
+#pragma unroll
+        for (int j = 0; j < T; ++j) {
+            const int t = p.team * T + j;
+            any |= s.ended[t];
+            const Vec<VEC> other = s.head[t * lanes + p.chunk];
+#pragma unroll
+            for (int i = 0; i < VEC; ++i) sum.v[i] += other.v[i];
+        }
+        s.batch[p.team * lanes + p.chunk] = sum;
+        s.batch_ended[p.team] = any;
+    }
+}
+
 // What the teams from number `from` on have of a run that began in front of them, added to sum in order, up to the one where it
 // ends; whether it does.
-template <int VEC>
-__device__ __forceinline__ bool add_heads(Vec<VEC>& sum, const Vec<VEC>* __restrict__ head, const uint8_t* __restrict__ ended, int from,
-                                          int teams, int lanes, int chunk)
+template <int VEC, bool BATCHES>
+__device__ __forceinline__ bool add_heads(Vec<VEC>& sum, const FlatHeads<VEC>& s, int from, int teams, int lanes, int chunk)
 {
+    constexpr int T = FlatHeads<VEC>::kTeams;
+    int t = from;
     bool done = false;
+    auto single = [&](int until) {
 #pragma unroll 1
-    for (int t = from; t < teams && !done; ++t) {
-        const Vec<VEC> other = head[t * lanes + chunk];
+        for (; t < until && !done; ++t) {
+            const Vec<VEC> other = s.head[t * lanes + chunk];
 #pragma unroll
-        for (int i = 0; i < VEC; ++i) sum.v[i] += other.v[i];
-        done = ended[t] != 0;
+            for (int i = 0; i < VEC; ++i) sum.v[i] += other.v[i];
+            done = s.ended[t] != 0;
+        }
+    };
+    if constexpr (BATCHES) {
+        const int next = (from + T - 1) & ~(T - 1);
+        single(next < teams ? next : teams);
+#pragma unroll 1
+        for (bool all = !done; all && t + T <= teams;) {
+            const Vec<VEC> other = s.batch[t / T * lanes + chunk];
+            all = s.batch_ended[t / T] == 0;
+#pragma unroll
+            for (int i = 0; i < VEC; ++i) sum.v[i] += all ? other.v[i] : 0.0f;
+            t += all ? T : 0;
+        }
     }
+    single(teams);
     return done;
 }
 

@@ -96,7 +96,7 @@ __global__ __launch_bounds__(kBlock) void flat_rows_kernel(SpmmArgs a, int lanes
             {
                 const FlatPlace p(lanes);
                 flat_stage<kFrEntries>(s, a.colidx, a.vals, e0, cnt, p.tid);
-                flat_deal(s, e0, cnt, n, teams, p.tid);
+                flat_deal<false>(s, e0, cnt, n, teams, p.tid);
             }
             __syncthreads();
             {
@@ -108,7 +108,8 @@ __global__ __launch_bounds__(kBlock) void flat_rows_kernel(SpmmArgs a, int lanes
                 const int first = c.ok ? s.start[p.team] : 0, last = c.ok ? s.start[p.team + 1] : 0;
                 if (first < last) {
                     const MaskedRows<VEC, OFF32> B(a.B, a.K, a.N, c.first);
-                    flat_walk<VEC, OFF32>(s, first, last, e0, B, true, [](int, bool) {}, [&](int row, const Vec<VEC>& sum) { store((uint32_t)row, sum); });
+                    flat_walk<VEC, OFF32>(s, first, last, s.ptr[first] - e0, 0x7fffffff, e0, B, true, [](int, bool) {},
+                                          [&](int row, const Vec<VEC>& sum) { store((uint32_t)row, sum); });
                 }
             }
             r0 += n;

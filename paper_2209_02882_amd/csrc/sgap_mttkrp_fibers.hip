@@ -4,9 +4,10 @@
 // A workgroup owns a block of consecutive slices and works through their fibers in pieces (one piece, as a rule) whose
 // fibers and entries it brings into LDS with coalesced loads.  A team of lanes, four columns each, takes consecutive
 // fibers of a piece, cut where the entries are about even, and goes through them at its own pace (sgap_flat.hpp) with the
-// slice's sum in registers; it stores what begins and ends among them.  What a team has of a slice that began in front of it goes to LDS, where the team that has the
-// slice's beginning adds it up in order: one plain store per slice, no atomics, the same result every time.  A slice that
-// goes on in the next piece is carried over in LDS, and a fiber that a piece has no room for is the whole workgroup's.
+// slice's sum in registers; it stores what begins and ends among them.  What a team has of a slice that began in front of
+// it goes to LDS, where the team that has the slice's beginning adds it up in order: one plain store per slice, no atomics,
+// the same result every time.  A slice that goes on in the next piece is carried over in LDS, and a fiber that a piece has
+// no room for is the whole workgroup's.
 //
 // Bound by the gathers: of two factors of 8.4 MB 1.7 GB come from beyond the L2s, at 7.1 TB/s; small tensors by the chain
 // of loads that a block is (pointers, fibers, entries, then a team's rows of X2).  With a group of lanes per slice, members
@@ -14,7 +15,7 @@
 // longest of its wavefront's, and every slice ended in a tree sum.  us, group per slice / this, J = 32 unless said, slices x
 // fibers of a slice: 262,144 x 8 268 / 240, with factors of 256 KB 235 / 164; 227,077 x 4, J = 16 104 / 78; 133,470 x 6
 // 123 / 95; 43,825 x 7 62 to 76 / 41; 21,755 x 8 39 to 49 / 25; 15,510 x 6, J = 16 23 to 27 / 15; 100,000 x 8, J = 64
-// 254 / 230.
+// 254 / 230; fibers of 24 entries, 50,000 x 2 84 / 34; 100,000 x 4, one fiber in a hundred of 500 entries 609 / 84.
 #include "sgap_common.hpp"
 #include "sgap_flat.hpp"
 #include "sgap_nnz_common.hpp"
@@ -27,19 +28,31 @@ constexpr int kMfEntries = 3328;  // entries of a piece at most: four workgroups
 constexpr int kMfResident = 4;    // workgroups of a compute unit
 constexpr int kMfMean = 2600;     // entries of a block in the mean at most; 2,000 from kMfRounds rounds of blocks on
 constexpr int kMfRounds = 5;
+constexpr int kMfBatch = 64;      // tiles whose first fibers and slices are looked up at once
 constexpr int kMfBlock = 16;      // slices of a block where the caller does not say how many entries there are
 
-template <int VEC, bool OFF32>
-__global__ __launch_bounds__(kBlock) void mttkrp_fibers_kernel(MttkrpArgs a, int lanes, int block_slices,
-                                                               int64_t blocks, int64_t blocks_per_xcd, int xcds)
+namespace {
+
+template <int VEC>
+struct MfShared {
+    FlatShared<kMfEntries, kMfFibers> flat;  // its runs are fibers
+    int32_t fk[kMfFibers];
+    int32_t fp[kMfSlices + 1];  // first fibers of the slices at hand
+    FlatHeads<VEC> heads;       // of slices
+    Vec<VEC> carry[2][kWave];   // of the slice that goes on in the next piece
+};
+
+// The fibers [f_begin, f_end), slice number first_slice holding the first of them.
+// SHARED_SLICES: of them the entries [e_begin, e_end), kMfEntries at most; a slice may have some outside, its sum is added into
+// Y (which holds zeros), and slices without entries are left alone; cut_first, cut_last: the first fiber begins in front of
+// them, the last one goes on behind them.  Else the block's slices are whole, `slices` of them, their
+// pointers in fp, and every one is stored.
+template <int VEC, bool OFF32, bool SHARED_SLICES>
+__device__ __forceinline__ void mttkrp_block(const MttkrpArgs& a, MfShared<VEC>& sh, int lanes, int teams, int64_t first_slice,
+                                             int slices, int32_t f_begin, int32_t f_end, int32_t e_begin, int32_t e_end,
+                                             bool cut_first, bool cut_last)
 {
-    const int teams = kBlock / lanes;
-    __shared__ FlatShared<kMfEntries, kMfFibers> s;  // its runs are fibers
-    __shared__ int32_t s_fk[kMfFibers];
-    __shared__ int32_t s_fp[kMfSlices + 1];
-    __shared__ Vec<VEC> s_head[kBlock];    // what a team has of a slice that began in front of its fibers
-    __shared__ uint8_t s_ended[kBlock];    // whether that slice ends there
-    __shared__ Vec<VEC> s_carry[2][kWave];  // of the slice that goes on in the next piece
+    auto& s = sh.flat;
     struct Columns {
         bool ok;
         uint32_t first;  // of the VEC columns this lane holds
@@ -51,51 +64,73 @@ __global__ __launch_bounds__(kBlock) void mttkrp_fibers_kernel(MttkrpArgs a, int
         }
     };
 
-    // workgroup b runs on die b % xcds: every die gets one contiguous run of blocks
-    const int64_t block = (int64_t)(blockIdx.x % xcds) * blocks_per_xcd + blockIdx.x / xcds;
-    if (block >= blocks) return;  // the whole workgroup
-    const int64_t first_slice = block * block_slices;
-    const int slices = (int)(a.I - first_slice < block_slices ? a.I - first_slice : block_slices);
-    for (int i = threadIdx.x; i <= slices; i += kBlock) s_fp[i] = a.fptr[first_slice + i];
-    __syncthreads();
-    const int32_t f_begin = __builtin_amdgcn_readfirstlane(s_fp[0]);
-    const int32_t f_end = __builtin_amdgcn_readfirstlane(s_fp[slices]);
-
     for (int64_t k0 = 0; k0 < a.J; k0 += (int64_t)lanes * VEC) {
+        int64_t base = first_slice;  // number of the slice that fp begins with
         auto store = [&](int slice, const Columns& c, const Vec<VEC>& sum) {
-            if (c.ok) store_vec_stream<VEC>(a.Y + (first_slice + slice) * a.J + c.first, sum);
+            if (c.ok) store_vec_stream<VEC>(a.Y + (base + slice) * a.J + c.first, sum);
         };
-        {
+        // a sum that a slice outside has a part in
+        auto add = [&](int slice, const FlatPlace& p, const Columns& c, Vec<VEC> sum) {
+            const int64_t k = k0 + (int64_t)p.chunk * VEC;
+            from_last_columns<VEC>(sum, (int)(k - c.first));
+#pragma unroll
+            for (int i = 0; i < VEC; ++i)
+                if (c.ok && k + i < a.J) unsafeAtomicAdd(a.Y + (base + slice) * a.J + k + i, sum.v[i]);
+        };
+        if constexpr (!SHARED_SLICES) {
             const FlatPlace p(lanes);
             const Columns c(p, k0, a.J, teams);
             Vec<VEC> none;
             none.zero();
             for (int r = p.team; r < slices; r += teams)
-                if (s_fp[r] == s_fp[r + 1]) store(r, c, none);
+                if (sh.fp[r] == sh.fp[r + 1]) store(r, c, none);
         }
 
         int turn = 0;  // which of s_carry the piece takes over
         for (int32_t f0 = f_begin; f0 < f_end; turn ^= 1) {
+            auto next_piece = [&](int fibers) {
+                f0 += fibers;
+                if constexpr (SHARED_SLICES) {
+                    if (f0 >= f_end) return;
+                    base = sh.fp[slices] > f0 ? base + last_row_at_or_before(sh.fp, 0, slices - 1, f0)
+                                             : last_row_at_or_before(a.fptr, (int32_t)(base + slices), (int32_t)a.I - 1, f0);
+                }
+            };
             int32_t n = f_end - f0 < kMfFibers ? f_end - f0 : kMfFibers;  // fibers of the piece
             __syncthreads();  // the piece before is done with
             {
                 const FlatPlace p(lanes);
 #pragma unroll 2
                 for (int i = p.tid; i <= n; i += kBlock) {
-                    s.ptr[i] = a.eptr[f0 + i];
-                    if (i < n) s_fk[i] = a.fidx[f0 + i];
+                    int32_t e = a.eptr[f0 + i];
+                    if (SHARED_SLICES && e < e_begin) e = e_begin;
+                    if (SHARED_SLICES && e > e_end) e = e_end;
+                    s.ptr[i] = e;
+                    if (i < n) sh.fk[i] = a.fidx[f0 + i];
+                }
+                if constexpr (SHARED_SLICES) {
+                    slices = a.I - base < kMfSlices ? (int)(a.I - base) : kMfSlices;
+                    // (a slice that begins or ends with a fiber that is not all here does so outside)
+                    for (int i = p.tid; i <= slices; i += kBlock) {
+                        const int32_t f = a.fptr[base + i];
+                        sh.fp[i] = f + (cut_last && f == f_end ? 1 : 0) - (cut_first && f == f_begin ? 1 : 0);
+                    }
                 }
             }
             __syncthreads();
+            if constexpr (SHARED_SLICES) {
+                // the fibers of the slices at hand
+                if (sh.fp[slices] - f0 < n) n = sh.fp[slices] - f0;
+            }
             const int32_t e0 = __builtin_amdgcn_readfirstlane(s.ptr[0]);
-            if (s.ptr[n] - e0 > kMfEntries) {
+            if (!SHARED_SLICES && s.ptr[n] - e0 > kMfEntries) {
                 const FlatPlace p(lanes);
                 int fit = 0;
                 for (int i = 0; i < n; i += kBlock) fit += __syncthreads_count(i + p.tid < n && s.ptr[i + p.tid + 1] - e0 <= kMfEntries);
                 n = fit;
             }
             n = __builtin_amdgcn_readfirstlane(n);
-            if (n == 0) {
+            if (!SHARED_SLICES && n == 0) {
                 // a fiber of more entries than there is room for: all teams together
                 const FlatPlace p(lanes);
                 const Columns c(p, k0, a.J, teams);
@@ -111,26 +146,26 @@ __global__ __launch_bounds__(kBlock) void mttkrp_fibers_kernel(MttkrpArgs a, int
 #pragma unroll 1
                     for (int q = p.team; c.ok && q < cnt; q += teams) t.fma(s.entry[q].val, x2.load(s.entry[q].col, true));
                 }
-                s_head[p.tid] = t;
+                sh.heads.head[p.tid] = t;
                 __syncthreads();
                 if (p.team == 0) {
 #pragma unroll 1
                     for (int m = 1; m < teams; ++m) {
-                        const Vec<VEC> other = s_head[m * lanes + p.chunk];
+                        const Vec<VEC> other = sh.heads.head[m * lanes + p.chunk];
 #pragma unroll
                         for (int i = 0; i < VEC; ++i) t.v[i] += other.v[i];
                     }
-                    const int slice = last_row_at_or_before(s_fp, 0, slices - 1, f0);
-                    const Vec<VEC> x = x1.load(s_fk[0], c.ok);
+                    const int slice = last_row_at_or_before(sh.fp, 0, slices - 1, f0);
+                    const Vec<VEC> x = x1.load(sh.fk[0], c.ok);
                     Vec<VEC> sum;
                     sum.zero();
-                    if (s_fp[slice] < f0) sum = s_carry[turn][p.chunk];
+                    if (sh.fp[slice] < f0 && f0 > f_begin) sum = sh.carry[turn][p.chunk];
 #pragma unroll
                     for (int i = 0; i < VEC; ++i) sum.v[i] = __builtin_fmaf(x.v[i], t.v[i], sum.v[i]);
-                    if (s_fp[slice + 1] == f0 + 1) store(slice, c, sum);
-                    else s_carry[turn ^ 1][p.chunk] = sum;
+                    if (sh.fp[slice + 1] == f0 + 1) store(slice, c, sum);
+                    else sh.carry[turn ^ 1][p.chunk] = sum;
                 }
-                ++f0;
+                next_piece(1);
                 continue;
             }
 
@@ -139,7 +174,7 @@ __global__ __launch_bounds__(kBlock) void mttkrp_fibers_kernel(MttkrpArgs a, int
             {
                 const FlatPlace p(lanes);
                 flat_stage<kMfEntries>(s, a.eidx, a.vals, e0, cnt, p.tid);
-                flat_deal(s, e0, cnt, n, teams, p.tid);
+                flat_deal<true>(s, e0, cnt, n, teams, p.tid);
             }
             __syncthreads();
 
@@ -150,57 +185,136 @@ __global__ __launch_bounds__(kBlock) void mttkrp_fibers_kernel(MttkrpArgs a, int
             int slice = 0;
             bool goes_on = false;  // the slice that begins in this team's fibers goes on behind them
             {
-                const int first = p.team < teams ? s.start[p.team] : 0, last = p.team < teams ? s.start[p.team + 1] : 0;
+                const uint32_t from = p.team < teams ? s.start[p.team] : 0, to = p.team < teams ? s.start[p.team + 1] : 0;
+                const int first = from & 0xffff, finished = to & 0xffff;  // fibers before `finished` end here
+                const bool cut = (int)(to >> 16) > s.ptr[finished] - e0;
+                const int last = finished + (cut ? 1 : 0);
                 bool head_ends = false;
                 if (first < last) {
                     const MaskedRows<VEC, OFF32> x1(a.X1, a.K, a.J, c.first), x2(a.X2, a.L, a.J, c.first);
-                    slice = last_row_at_or_before(s_fp, 0, slices - 1, f0 + first);
-                    bool whole = s_fp[slice] == f0 + first;
-                    int32_t slice_end = s_fp[slice + 1] - f0;
+                    slice = last_row_at_or_before(sh.fp, 0, slices - 1, f0 + first);
+                    bool whole = sh.fp[slice] == f0 + first && (int)(from >> 16) == s.ptr[first] - e0;
+                    int32_t slice_end = sh.fp[slice + 1] - f0;
                     Vec<VEC> x;
                     flat_walk<VEC, OFF32>(
-                        s, first, last, e0, x2, c.ok, [&](int f, bool ends) { x = x1.load(s_fk[f], ends && c.ok); },
+                        s, first, last, from >> 16, to >> 16, e0, x2, c.ok, [&](int f, bool ends) { x = x1.load(sh.fk[f], ends && c.ok); },
                         [&](int f, const Vec<VEC>& t) {
 #pragma unroll
                             for (int i = 0; i < VEC; ++i) sum.v[i] = __builtin_fmaf(x.v[i], t.v[i], sum.v[i]);
-                            if (f + 1 != slice_end) return;
+                            if (f + 1 != slice_end || f >= finished) return;
                             if (whole) {
                                 store(slice, c, sum);
                             } else {
-                                s_head[p.tid] = sum;
+                                sh.heads.head[p.tid] = sum;
                                 head_ends = true;
                             }
                             sum.zero();
                             whole = true;
                             if (f + 1 < last) {
-                                do slice_end = s_fp[++slice + 1] - f0;
+                                do slice_end = sh.fp[++slice + 1] - f0;
                                 while (slice_end == f + 1);
                             }
                         });
-                    goes_on = last != slice_end && whole;
-                    if (last != slice_end && !whole) s_head[p.tid] = sum;
+                    const bool open = last != slice_end || cut;
+                    goes_on = open && whole;
+                    if (open && !whole) sh.heads.head[p.tid] = sum;
                 } else {
-                    s_head[p.tid] = sum;
+                    sh.heads.head[p.tid] = sum;
                 }
-                if (p.team < teams) s_ended[p.team] = head_ends ? 1 : 0;
+                if (p.team < teams) sh.heads.ended[p.team] = head_ends ? 1 : 0;
             }
             __syncthreads();
+            if constexpr (SHARED_SLICES) {
+                batch_heads(sh.heads, teams, lanes, p);
+                __syncthreads();
+            }
             // what goes on is added up by the team that has its beginning, what came in from the piece before by the first team
-            const int32_t came_in = f0 > f_begin ? last_row_at_or_before(s_fp, 0, slices - 1, f0) : 0;
-            const bool comes_in = f0 > f_begin && s_fp[came_in] < f0;
+            const bool look = SHARED_SLICES || f0 > f_begin;
+            const int32_t came_in = look ? last_row_at_or_before(sh.fp, 0, slices - 1, f0) : 0;
+            const bool comes_in = look && sh.fp[came_in] < f0;
 #pragma unroll 1
             for (int round = 0; round < 2; ++round) {
                 if (round == 1) {
                     goes_on = comes_in && p.team == 0;
-                    if (goes_on) sum = s_carry[turn][p.chunk];
+                    sum.zero();
+                    if (goes_on && f0 > f_begin) sum = sh.carry[turn][p.chunk];
                     slice = came_in;
                 }
                 if (!goes_on) continue;
-                const bool ended = add_heads<VEC>(sum, s_head, s_ended, round == 1 ? 0 : p.team + 1, teams, lanes, p.chunk);
-                if (ended) store(slice, c, sum);
-                else s_carry[turn ^ 1][p.chunk] = sum;
+                const bool ended = add_heads<VEC, SHARED_SLICES>(sum, sh.heads, round == 1 ? 0 : p.team + 1, teams, lanes, p.chunk);
+                if (SHARED_SLICES && (ended ? sh.fp[slice] < f_begin : f0 + n == f_end)) add(slice, p, c, sum);
+                else if (ended) store(slice, c, sum);
+                else sh.carry[turn ^ 1][p.chunk] = sum;
             }
-            f0 += n;
+            next_piece(n);
+        }
+    }
+}
+
+}  // namespace
+
+template <int VEC, bool OFF32>
+__global__ __launch_bounds__(kBlock) void mttkrp_fibers_kernel(MttkrpArgs a, int lanes, int block_slices,
+                                                               int64_t blocks, int64_t blocks_per_xcd, int xcds)
+{
+    __shared__ MfShared<VEC> s;
+    // workgroup b runs on die b % xcds: every die gets one contiguous run of blocks
+    const int64_t block = (int64_t)(blockIdx.x % xcds) * blocks_per_xcd + blockIdx.x / xcds;
+    if (block >= blocks) return;  // the whole workgroup
+    const int64_t first_slice = block * block_slices;
+    const int slices = (int)(a.I - first_slice < block_slices ? a.I - first_slice : block_slices);
+    for (int i = threadIdx.x; i <= slices; i += kBlock) s.fp[i] = a.fptr[first_slice + i];
+    __syncthreads();
+    const int32_t f_begin = __builtin_amdgcn_readfirstlane(s.fp[0]);
+    const int32_t f_end = __builtin_amdgcn_readfirstlane(s.fp[slices]);
+    mttkrp_block<VEC, OFF32, false>(a, s, lanes, kBlock / lanes, first_slice, slices, f_begin, f_end, 0, 0, false, false);
+}
+
+// Stored entries as the unit of work, serial strategy: {<g nnz, c col>, 1}, whatever group_size says.  A workgroup takes tiles of
+// entries, whose first and last fibers may go on outside, and works through them as through a block of slices; slices that go
+// on outside are merged with atomics.
+// Bound by the gathers too, where the factors do not fit an L2 (two of 8.4 MB: 5.3 TB/s).  With a lane to an even share of the
+// entries (sgap_mttkrp_serial.hip, the form before) the lanes of a wavefront met at every ending of a fiber, two steps of three.
+// us, even shares / this, one slice in a thousand of 2,000 to 20,000 fibers, the others of 4, J = 32 unless said: 262,144
+// slices 542 / 455; 76,491 173 / 133; 20,000 63 / 57; 5,000 34 / 29; 15,510, J = 16 41.5 / 29.5; 100,000, J = 64 1,283 / 1,020
+// and J = 256 2,490 / 1,775, J = 8 158 / 116, J = 4 161 / 116, J = 2 111 / 106, J = 1 95 / 96.  1,000 slices of two fibers of
+// 1,000 entries each 41.7 / 34.1.
+template <int VEC, bool OFF32>
+__global__ __launch_bounds__(kBlock) void mttkrp_tiles_kernel(MttkrpArgs a, int lanes, int tile)
+{
+    __shared__ MfShared<VEC> s;
+    __shared__ int32_t s_fiber[2 * kMfBatch], s_slice[kMfBatch];  // a tile's first and last fiber, the slice of the first
+    __shared__ uint8_t s_cut[2 * kMfBatch];
+    const int32_t F = a.fptr[a.I];
+    const int32_t E = F > 0 ? a.eptr[F] : 0;
+    const TileDeal deal(((int64_t)E + tile - 1) / tile, blockIdx.x, gridDim.x);
+    const int mine = (int)deal.mine;
+    for (int j0 = 0; j0 < mine; j0 += kMfBatch) {
+        const int batch = mine - j0 < kMfBatch ? mine - j0 : kMfBatch;
+        __syncthreads();  // the last ones are done with
+        // the fibers of the tiles' first and last entries
+        find_positions(a.eptr, F - 1, 2 * batch, [&](int j) {
+            const int64_t at = (deal.tile(j0 + j / 2) + j % 2) * tile;
+            return (int32_t)(at > E ? E : at) - j % 2;
+        }, s_fiber);
+        __syncthreads();
+        // (whether those are cut, on the way)
+        bool cut = false;
+        if ((int)threadIdx.x < 2 * batch) {
+            const int64_t at = (deal.tile(j0 + threadIdx.x / 2) + threadIdx.x % 2) * tile;
+            const int32_t e = a.eptr[s_fiber[threadIdx.x] + threadIdx.x % 2];
+            cut = threadIdx.x % 2 ? e > at : e < at;
+        }
+        find_positions(a.fptr, (int32_t)a.I - 1, batch, [&](int j) { return s_fiber[2 * j]; }, s_slice);
+        if ((int)threadIdx.x < 2 * batch) s_cut[threadIdx.x] = cut;
+        __syncthreads();
+        for (int j = 0; j < batch; ++j) {
+            const int32_t f_begin = __builtin_amdgcn_readfirstlane(s_fiber[2 * j]);
+            const int32_t f_end = __builtin_amdgcn_readfirstlane(s_fiber[2 * j + 1]) + 1;
+            const int32_t slice = __builtin_amdgcn_readfirstlane(s_slice[j]);
+            const int64_t at = deal.tile(j0 + j) * tile;
+            mttkrp_block<VEC, OFF32, true>(a, s, lanes, kBlock / lanes, slice, 0, f_begin, f_end, (int32_t)at,
+                                           (int32_t)(at + tile < E ? at + tile : E), s_cut[2 * j], s_cut[2 * j + 1]);
         }
     }
 }
@@ -219,6 +333,13 @@ int mttkrp_block_slices(int64_t I, int64_t nnz_hint, int compute_units)
     return slices < kMfSlices ? (int)slices : kMfSlices;
 }
 
+// every byte offset into X1 and X2 fits 32 bits and both factors of it fit 24 bits
+static bool mttkrp_off32(const MttkrpArgs& a)
+{
+    auto fits = [&](int64_t rows) { return rows <= (1 << 24) && a.J * 4 < (1 << 24) && rows * a.J * 4 <= 0xffffffffLL; };
+    return fits(a.K) && fits(a.L);
+}
+
 hipError_t launch_mttkrp_fibers(const MttkrpArgs& a, int block_slices, int vec, int xcds, hipStream_t s)
 {
     if (block_slices > kMfSlices) block_slices = kMfSlices;
@@ -230,12 +351,34 @@ hipError_t launch_mttkrp_fibers(const MttkrpArgs& a, int block_slices, int vec, 
     auto go = [&](auto kernel) {
         hipLaunchKernelGGL(kernel, dim3((unsigned)(blocks_per_xcd * xcds)), dim3(kBlock), 0, s, a, lanes, block_slices, blocks, blocks_per_xcd, xcds);
     };
-    // every byte offset into X1 and X2 fits 32 bits and both factors of it fit 24 bits
-    auto fits = [&](int64_t rows) { return rows <= (1 << 24) && a.J * 4 < (1 << 24) && rows * a.J * 4 <= 0xffffffffLL; };
-    const bool off32 = fits(a.K) && fits(a.L);
+    const bool off32 = mttkrp_off32(a);
     if (vec == 4) { if (off32) go(mttkrp_fibers_kernel<4, true>); else go(mttkrp_fibers_kernel<4, false>); }
     else if (vec == 2) { if (off32) go(mttkrp_fibers_kernel<2, true>); else go(mttkrp_fibers_kernel<2, false>); }
     else { if (off32) go(mttkrp_fibers_kernel<1, true>); else go(mttkrp_fibers_kernel<1, false>); }
+    return hipGetLastError();
+}
+
+hipError_t launch_mttkrp_tiles(const MttkrpArgs& a, int vec, int compute_units, int64_t nnz_hint, hipStream_t s)
+{
+    const int64_t chunks = (a.J + vec - 1) / vec, resident = (int64_t)kMfResident * compute_units;
+    const int lanes = chunks < kWave ? (int)chunks : kWave;
+    // Tiles that make whole rounds of the resident workgroups, 2,000 entries at most.  At least 1,024, although few entries
+    // would make more workgroups: each adds to the same few rows where slices are long (5,000 slices as above, J = 32: tiles
+    // of 512 34.6 us, of 1,024 29; 10,000 slices of 4 fibers 21.1 and 22.6).  1,536 with four lanes to a team or fewer (20,000
+    // slices as above, J = 4 44 and 37.6, J = 8 41.7 and 38; 5,000, J = 16 25 and 23).
+    int64_t tile = 2000;
+    if (nnz_hint > 0) {
+        const int64_t rounds = nnz_hint / (resident * 2000) + 1;
+        tile = (nnz_hint + resident * rounds - 1) / (resident * rounds);
+        const int least = lanes <= 4 ? 1536 : 1024;
+        if (tile < least) tile = least;
+    }
+    const int grid = persistent_grid(kMfResident, compute_units, nnz_hint, (int)tile);
+    auto go = [&](auto kernel) { hipLaunchKernelGGL(kernel, dim3(grid), dim3(kBlock), 0, s, a, lanes, (int)tile); };
+    const bool off32 = mttkrp_off32(a);
+    if (vec == 4) { if (off32) go(mttkrp_tiles_kernel<4, true>); else go(mttkrp_tiles_kernel<4, false>); }
+    else if (vec == 2) { if (off32) go(mttkrp_tiles_kernel<2, true>); else go(mttkrp_tiles_kernel<2, false>); }
+    else { if (off32) go(mttkrp_tiles_kernel<1, true>); else go(mttkrp_tiles_kernel<1, false>); }
     return hipGetLastError();
 }
 

@@ -9,7 +9,7 @@
 //             members of a group run a segmented sum keyed by fiber; the first lane of every fiber run
 //             multiplies by its chunk of the row of X1; a second segmented sum, keyed by slice, runs over
 //             those products (the other lanes pass +0); the first lane of every slice run adds into Y.
-// (The serial strategy has a kernel of its own: sgap_mttkrp_serial.hip.)
+// (The serial strategy has kernels of its own: sgap_mttkrp_fibers.hip and sgap_mttkrp_serial.hip.)
 // Lane layout as everywhere: thread = (slot*G + member)*LC + chunk.  Several groups may hold parts of one
 // slice, so sums are ADDED into Y (the "Atomics" output strategy of Section 6.2) and Y is set to zero
 // beforehand.  Where the accumulators fit (tile mode of the SpMM kernels' merge rule: one slot per aligned
@@ -249,7 +249,9 @@ struct LaunchMttkrpNnz {
 hipError_t launch_mttkrp_nnz(const MttkrpArgs& a, int g, bool parallel, int lc, int vec, int compute_units,
                              int64_t nnz_hint, hipStream_t s)
 {
-    if (!parallel) return launch_mttkrp_serial(a, lc, vec, compute_units, nnz_hint, s);
+    if (!parallel)
+        return mttkrp_serial_applies(a.J, nnz_hint) ? launch_mttkrp_serial(a, lc, vec, compute_units, nnz_hint, s)
+                                                    : launch_mttkrp_tiles(a, vec, compute_units, nnz_hint, s);
     const bool ok = dispatch_group(g, lc, vec, LaunchMttkrpNnz{a, g, compute_units, nnz_hint, s});
     if (!ok) return hipErrorInvalidValue;
     return hipGetLastError();

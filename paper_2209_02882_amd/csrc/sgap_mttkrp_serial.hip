@@ -1,4 +1,5 @@
-// MTTKRP on compressed sparse fibers with the stored entries as the unit of work, serial strategy: {<g nnz, c col>, 1}.
+// MTTKRP on compressed sparse fibers with the stored entries as the unit of work, serial strategy: {<g nnz, c col>, 1}, few
+// entries and few columns (where that ends: mttkrp_serial_applies; the rest is mttkrp_tiles_kernel's).
 //     t[f,:]  = sum over the entries (l, v) of fiber f of  v * X2[l,:]
 //     Y[i,:]  = sum over the fibers f of slice i of        X1[fidx[f],:] * t[f,:]
 // A lane walks g consecutive entries (g = the tile's entries over the workgroup's entry lanes, so that a tile is one walk
@@ -25,6 +26,7 @@
 
 namespace sgap {
 
+constexpr int kMsColumns = 8;
 constexpr int kMsEpt = 4;
 constexpr int kMsTile = kMsEpt * kBlock;
 constexpr int kMsBatch = 64;             // tiles whose first fibers and slices are looked up at once
@@ -324,7 +326,8 @@ struct LaunchSerial {
     void operator()() const
     {
         constexpr bool WIDE = VEC > 1;  // rows whose columns the lanes need not divide
-        if (!off32) go<LC, VEC, false, WIDE>();
+        if constexpr (LC * VEC > kMsColumns) return;
+        else if (!off32) go<LC, VEC, false, WIDE>();
         else if (WIDE && a.J % VEC != 0) go<LC, VEC, true, WIDE>();
         else go<LC, VEC, true, false>();
     }
@@ -332,10 +335,21 @@ struct LaunchSerial {
 
 }  // namespace
 
+// A tile here is one step through the loads less, and there is no more of it.  us, this / teams of lanes at their own pace
+// (slices of 4 fibers of 4.5 entries): J = 4, 1,000 slices 13.0 / 17.0, 10,000 16.3 / 18.1, 30,000 22.8 / 24, 60,000
+// 36.7 / 29.3; J = 8, 1,000 14.2 / 16.5, 10,000 17.2 / 18.0, 30,000 23.3 / 23.4; J = 16, 1,000 15.7 / 16, 10,000 20.1 / 20.1;
+// one slice in a thousand with 2,000 to 20,000 fibers: J = 4, 5,000 slices 20.8 / 21.5, 20,000 42.7 / 37.6; J = 1, 5,000
+// 14.6 / 17.4, 100,000 95 / 96.
+bool mttkrp_serial_applies(int64_t J, int64_t nnz_hint)
+{
+    return J <= kMsColumns && nnz_hint > 0 && nnz_hint < (J < 4 ? 2000000 / J : 500000);
+}
+
 hipError_t launch_mttkrp_serial(const MttkrpArgs& a, int lc, int vec, int compute_units, int64_t nnz_hint,
                                 hipStream_t s)
 {
     auto fits = [&](int64_t rows) { return rows <= (1 << 24) && a.J * 4 < (1 << 24) && rows * a.J * 4 <= 0xffffffffLL; };
+    if (a.J > kMsColumns) return hipErrorInvalidValue;
     if (!dispatch_lc<1>(lc, vec, LaunchSerial{a, compute_units, nnz_hint, fits(a.K) && fits(a.L), s}))
         return hipErrorInvalidValue;
     return hipGetLastError();

@@ -32,8 +32,7 @@ struct NnzFlatShared {
     __attribute__((aligned(16))) StagedEntry entry[kNfTile + kFlatBatch];  // (a batch reads past the last one)
     int32_t win[kWindowCap + 1];  // first positions of the tile's rows with entries
     int32_t row[kWindowCap];      // ... and their numbers
-    Vec<4> head[kBlock];     // what a team has of a row that began in front of its entries
-    uint8_t ended[kBlock];   // whether that row ends there
+    FlatHeads<4> heads;
     float edge[2][4 * kWave];  // of the rows that cross the tile's ends: the one that comes in, the one that goes on
     int32_t edge_row[2];     // -1: none
     int32_t begin[kBlock + 1], begin_row[kBlock + 1];  // a team's first entry, and the window's row that holds it
@@ -162,20 +161,20 @@ void nnz_flat_kernel(SpmmArgs a, int lanes, int teams, int tile)
                             if (whole) {
                                 store(s.row[now], sum);
                             } else {
-                                s.head[p.tid] = sum;
+                                s.heads.head[p.tid] = sum;
                                 head_ends = true;
                             }
                             sum.zero();
                             whole = true;
                         } else if (ends) {
                             if (whole) goes_on = true;
-                            else s.head[p.tid] = sum;
+                            else s.heads.head[p.tid] = sum;
                         }
                     } while (q < end);
                 } else {
-                    s.head[p.tid] = sum;
+                    s.heads.head[p.tid] = sum;
                 }
-                if (p.team < teams && p.chunk == 0) s.ended[p.team] = head_ends ? 1 : 0;
+                if (p.team < teams && p.chunk == 0) s.heads.ended[p.team] = head_ends ? 1 : 0;
                 if (p.tid < 2) s.edge_row[p.tid] = -1;
                 __syncthreads();
                 // a row that goes on is added up, in order, by the team that has its beginning; what came in from the tile in
@@ -188,7 +187,7 @@ void nnz_flat_kernel(SpmmArgs a, int lanes, int teams, int tile)
                         wi = 0;
                     }
                     if (!goes_on) continue;
-                    const bool ended = add_heads<4>(sum, s.head, s.ended, round == 1 ? 0 : p.team + 1, teams, lanes, p.chunk);
+                    const bool ended = add_heads<4, false>(sum, s.heads, round == 1 ? 0 : p.team + 1, teams, lanes, p.chunk);
                     if (round == 0 && ended) {
                         store(s.row[wi], sum);
                     } else {

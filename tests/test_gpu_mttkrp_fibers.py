@@ -28,6 +28,8 @@ CASES = {
     # pieces that end with a slice, in the middle of one, and before a fiber that would not fit
     "full_pieces": ([7, 7, 7, 14, 1, 0, 20, 9], [512]),
     "single": ([1], [1]),
+    # more slices without fibers than a piece of a tile keeps pointers of (256), in front, between and behind
+    "empty_slices": ([0] * 300 + [3, 0, 2] + [0] * 700 + [900] + [0] * 255 + [1] + [0] * 256 + [5, 4] + [0] * 300, [9, 1, 0, 30]),
 }
 
 
@@ -45,3 +47,8 @@ def test_pieces_of_a_block(name, J):
             Y.fill_(float("nan"))
             binding.sgap_mttkrp_csf_ex(t.I, t.K, t.L, t.J, *d, Y, g, binding.SGAP_REDUCE_PARALLEL, binding.SGAP_SCHED_ROW_SPLIT, nnz_hint=hint)
             assert np.array_equal(Y.cpu().numpy().astype(np.float64), ref), (hint, g)
+        # the same pieces from tiles of stored entries, of 1,024 to 2,000 each (few of few columns: shares of lanes), slices merged where they reach beyond one
+        print("  mttkrp tiles", name, J, hint, flush=True)
+        Y.fill_(float("nan"))
+        binding.sgap_mttkrp_csf_ex(t.I, t.K, t.L, t.J, *d, Y, 8, binding.SGAP_REDUCE_SERIAL, binding.SGAP_SCHED_NNZ_BALANCED, nnz_hint=hint)
+        assert np.array_equal(Y.cpu().numpy().astype(np.float64), ref), hint
