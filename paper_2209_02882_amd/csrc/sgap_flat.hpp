@@ -75,8 +75,8 @@ struct FlatShared {
 
 // The piece's entries [e0, e0 + cnt) on their way into LDS, four neighbours to a thread, all of them requested before the
 // first is put down.  The caller synchronises.
-template <int ENTRIES, typename SH>
-__device__ __forceinline__ void flat_stage(SH& s, const int32_t* __restrict__ idx, const float* __restrict__ vals, int32_t e0,
+template <int ENTRIES>
+__device__ __forceinline__ void flat_stage(StagedEntry* __restrict__ entry, const int32_t* __restrict__ idx, const float* __restrict__ vals, int32_t e0,
                                            int32_t cnt, int tid)
 {
     typedef int32_t native_i4 __attribute__((ext_vector_type(4), aligned(4)));
@@ -104,43 +104,54 @@ __device__ __forceinline__ void flat_stage(SH& s, const int32_t* __restrict__ id
     for (int u = 0; u < U; ++u) {
         const int q = (u * kBlock + tid) * 4;
         if (q + 4 <= cnt) {
-            s.entry[q] = {c[u].x, v[u].x};
-            s.entry[q + 1] = {c[u].y, v[u].y};
-            s.entry[q + 2] = {c[u].z, v[u].z};
-            s.entry[q + 3] = {c[u].w, v[u].w};
+            entry[q] = {c[u].x, v[u].x};
+            entry[q + 1] = {c[u].y, v[u].y};
+            entry[q + 2] = {c[u].z, v[u].z};
+            entry[q + 3] = {c[u].w, v[u].w};
         }
     }
-    if (rest < cnt) s.entry[rest] = {last_c, last_v};
+    if (rest < cnt) entry[rest] = {last_c, last_v};
 }
 
-// Where the teams begin: with whole runs, at the first one that starts at or behind an even share of the entries; CUT: with the
-// even share itself where that lies in a run of more than kFlatCut entries, and s.start is made of flat_at().  The caller synchronises.
-// (A team may meet a fiber of any length: 20,000 slices of two fibers of 100 entries each, J = 32, 271 us by a lane group per
+// Where the teams begin: with whole runs, at the first one that starts at or behind an even share of the work; CUT: inside a run
+// where that is one of more than kFlatCut entries, and s.start is made of flat_at().  The caller synchronises.
+// Work: a run costs a turn and what it does at its end, whatever it has, and kFlatRunCost entries more are about that.  us, even
+// shares of the entries / of this: TTM, 21,755 fibers of 1 to 16, N = 64 18.2 / 17.3, 76,491 slices of four, N = 48 62.0 / 59.7;
+// MTTKRP, 262,144 slices 241.0 / 238.4, 21,755 25.3 / 24.3; 100,000, J = 4, one in a thousand of 2,000 to 20,000 fibers 116 /
+// 109; 100,000 with one fiber in a hundred of 500 entries 84.8 / 73.9.  (3 entries: between the two.)
+// (A team may meet a run of any length: 20,000 slices of two fibers of 100 entries each, J = 32, 271 us by a lane group per
 // slice, 49 by teams that share the fibers.  Shorter ones stay whole: a cut costs a turn, and a head to add up.)
-constexpr int kFlatCut = 32;
+constexpr int32_t kFlatCut = 32;
+constexpr int32_t kFlatRunCost = 6;
 __device__ __forceinline__ int32_t flat_at(int run, int32_t pos) { return run | pos << 16; }
 
 template <bool CUT, typename SH>
 __device__ __forceinline__ void flat_deal(SH& s, int32_t e0, int32_t cnt, int n, int teams, int tid)
 {
-    const int32_t share = cnt > teams ? (cnt + teams - 1) / teams : 1;
+    const int32_t all = cnt + kFlatRunCost * n;
+    const int32_t share = all > teams ? (all + teams - 1) / teams : 1;
     const float per_share = __builtin_amdgcn_rcpf((float)share);
-    auto team_of = [&](int run) {  // (a division of numbers up to 4,096: exact)
-        const int t = (int)(((float)(s.ptr[run] - e0) + 0.5f) * per_share);
+    auto weight = [&](int run) { return s.ptr[run] - e0 + kFlatRunCost * run; };  // in front of it
+    auto team_of = [&](int run) {  // (a division of numbers up to 2^14, up to 256 times as large: exact)
+        const int t = (int)(((float)weight(run) + 0.5f) * per_share);
         return t < teams ? t : teams - 1;
     };
-    // the teams behind `from` up to `to` whose share begins behind the beginning of run i - 1, at the latest with run i
+    // the teams behind `from` up to `to`, whose share begins behind the beginning of run i - 1, at the latest with run i
     auto set = [&](int from, int to, int i) {
-        int32_t pos = 0, before = 0;
+        int32_t pos = 0, before = 0, front = 0;
         if constexpr (CUT) {
             pos = s.ptr[i] - e0;
             before = i > 0 ? s.ptr[i - 1] - e0 : 0;
+            front = before + kFlatRunCost * i;  // weight in front of the first entry of run i - 1
         }
 #pragma unroll 1
         for (int t = from + 1; t <= to; ++t) {
-            if constexpr (!CUT) s.start[t] = i;
-            else if (pos - before > kFlatCut && t * share < pos) s.start[t] = flat_at(i - 1, t * share);
-            else s.start[t] = flat_at(i, pos);
+            if constexpr (!CUT) {
+                s.start[t] = i;
+            } else {
+                const int32_t at = t * share > front ? t * share - front : 0;  // of run i - 1's entries
+                s.start[t] = pos - before > kFlatCut && before + at < pos ? flat_at(i - 1, before + at) : flat_at(i, pos);
+            }
         }
     };
 #pragma unroll 1

@@ -73,7 +73,7 @@ __global__ __launch_bounds__(kBlock) void flat_rows_kernel(SpmmArgs a, int lanes
                 for (int32_t base = e0; base < e1; base += kFrEntries) {
                     const int32_t cnt = e1 - base < kFrEntries ? e1 - base : kFrEntries;
                     __syncthreads();
-                    flat_stage<kFrEntries>(s, a.colidx, a.vals, base, cnt, p.tid);
+                    flat_stage<kFrEntries>(s.entry, a.colidx, a.vals, base, cnt, p.tid);
                     __syncthreads();
 #pragma unroll 1
                     for (int q = p.team; c.ok && q < cnt; q += teams) t.fma(s.entry[q].val, B.load(s.entry[q].col, true));
@@ -95,7 +95,7 @@ __global__ __launch_bounds__(kBlock) void flat_rows_kernel(SpmmArgs a, int lanes
             const int32_t cnt = __builtin_amdgcn_readfirstlane(s.ptr[n]) - e0;
             {
                 const FlatPlace p(lanes);
-                flat_stage<kFrEntries>(s, a.colidx, a.vals, e0, cnt, p.tid);
+                flat_stage<kFrEntries>(s.entry, a.colidx, a.vals, e0, cnt, p.tid);
                 flat_deal<false>(s, e0, cnt, n, teams, p.tid);
             }
             __syncthreads();

@@ -141,7 +141,7 @@ __device__ __forceinline__ void mttkrp_block(const MttkrpArgs& a, MfShared<VEC>&
                 for (int32_t base = e0; base < e1; base += kMfEntries) {
                     const int32_t cnt = e1 - base < kMfEntries ? e1 - base : kMfEntries;
                     __syncthreads();
-                    flat_stage<kMfEntries>(s, a.eidx, a.vals, base, cnt, p.tid);
+                    flat_stage<kMfEntries>(s.entry, a.eidx, a.vals, base, cnt, p.tid);
                     __syncthreads();
 #pragma unroll 1
                     for (int q = p.team; c.ok && q < cnt; q += teams) t.fma(s.entry[q].val, x2.load(s.entry[q].col, true));
@@ -173,7 +173,7 @@ __device__ __forceinline__ void mttkrp_block(const MttkrpArgs& a, MfShared<VEC>&
             const int32_t cnt = __builtin_amdgcn_readfirstlane(s.ptr[n]) - e0;
             {
                 const FlatPlace p(lanes);
-                flat_stage<kMfEntries>(s, a.eidx, a.vals, e0, cnt, p.tid);
+                flat_stage<kMfEntries>(s.entry, a.eidx, a.vals, e0, cnt, p.tid);
                 flat_deal<true>(s, e0, cnt, n, teams, p.tid);
             }
             __syncthreads();

@@ -75,7 +75,7 @@ void nnz_flat_kernel(SpmmArgs a, int lanes, int teams, int tile)
                     const int64_t r = (int64_t)row_lb + w;
                     win[i] = w <= kWindowCap ? a.rowptr[r <= M ? r : M] : 0;
                 }
-                flat_stage<kNfTile>(s, a.colidx, a.vals, tile_start, cnt, p.tid);
+                flat_stage<kNfTile>(s.entry, a.colidx, a.vals, tile_start, cnt, p.tid);
 #pragma unroll
                 for (int i = 0; i < WPT; ++i)
                     if (p.tid + i * kBlock <= kWindowCap) s.win[p.tid + i * kBlock] = win[i];
