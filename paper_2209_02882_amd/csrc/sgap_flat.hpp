@@ -21,9 +21,11 @@ struct MaskedRows {
     uint32_t row_bytes, k_bytes;
     const float* base;
     int64_t J;
-    __device__ __forceinline__ MaskedRows(const float* X, int64_t count, int64_t j, uint32_t k)
-        : rows(__builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(X), 0, (int)(uint32_t)(OFF32 ? count * j * 4 : 0), 0x00020000)),
-          row_bytes((uint32_t)(j * 4)), k_bytes(k * 4), base(X + k), J(j)
+    // (The descriptor reaches as far as 32-bit offsets of words do, not to the end of X: the number of X's rows would have to be
+    // held for it, and row_split_kernel, with no scalar registers left, lost a wavefront per SIMD to that.)
+    __device__ __forceinline__ MaskedRows(const float* X, int64_t j, uint32_t k)
+        : rows(__builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(X), 0, (int)0xfffffffcu, 0x00020000)), row_bytes((uint32_t)(j * 4)),
+          k_bytes(k * 4), base(X + k), J(j)
     {
     }
     __device__ __forceinline__ Vec<VEC> load(int32_t row, bool ok) const

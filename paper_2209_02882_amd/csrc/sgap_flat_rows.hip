@@ -66,7 +66,7 @@ __global__ __launch_bounds__(kBlock) void flat_rows_kernel(SpmmArgs a, int lanes
                 // a row of more entries than there is room for: all teams together
                 const FlatPlace p(lanes);
                 const Columns c(p, k0, a.N, teams);
-                const MaskedRows<VEC, OFF32> B(a.B, a.K, a.N, c.first);
+                const MaskedRows<VEC, OFF32> B(a.B, a.N, c.first);
                 const int32_t e1 = __builtin_amdgcn_readfirstlane(s.ptr[1]);
                 Vec<VEC> t;
                 t.zero();
@@ -107,7 +107,7 @@ __global__ __launch_bounds__(kBlock) void flat_rows_kernel(SpmmArgs a, int lanes
                 auto store = [&](uint32_t row, const Vec<VEC>& sum) { store_vec_stream<VEC>(C + (uint64_t)row * N, sum); };
                 const int first = c.ok ? s.start[p.team] : 0, last = c.ok ? s.start[p.team + 1] : 0;
                 if (first < last) {
-                    const MaskedRows<VEC, OFF32> B(a.B, a.K, a.N, c.first);
+                    const MaskedRows<VEC, OFF32> B(a.B, a.N, c.first);
                     flat_walk<VEC, OFF32>(s, first, last, s.ptr[first] - e0, 0x7fffffff, e0, B, true, [](int, bool) {},
                                           [&](int row, const Vec<VEC>& sum) { store((uint32_t)row, sum); });
                 }

@@ -134,7 +134,7 @@ __device__ __forceinline__ void mttkrp_block(const MttkrpArgs& a, MfShared<VEC>&
                 // a fiber of more entries than there is room for: all teams together
                 const FlatPlace p(lanes);
                 const Columns c(p, k0, a.J, teams);
-                const MaskedRows<VEC, OFF32> x1(a.X1, a.K, a.J, c.first), x2(a.X2, a.L, a.J, c.first);
+                const MaskedRows<VEC, OFF32> x1(a.X1, a.J, c.first), x2(a.X2, a.J, c.first);
                 const int32_t e1 = __builtin_amdgcn_readfirstlane(s.ptr[1]);
                 Vec<VEC> t;
                 t.zero();
@@ -191,7 +191,7 @@ __device__ __forceinline__ void mttkrp_block(const MttkrpArgs& a, MfShared<VEC>&
                 const int last = finished + (cut ? 1 : 0);
                 bool head_ends = false;
                 if (first < last) {
-                    const MaskedRows<VEC, OFF32> x1(a.X1, a.K, a.J, c.first), x2(a.X2, a.L, a.J, c.first);
+                    const MaskedRows<VEC, OFF32> x1(a.X1, a.J, c.first), x2(a.X2, a.J, c.first);
                     slice = last_row_at_or_before(sh.fp, 0, slices - 1, f0 + first);
                     bool whole = sh.fp[slice] == f0 + first && (int)(from >> 16) == s.ptr[first] - e0;
                     int32_t slice_end = sh.fp[slice + 1] - f0;

@@ -129,7 +129,7 @@ void nnz_flat_kernel(SpmmArgs a, int lanes, int teams, int tile)
                 int wi = 0;
                 bool goes_on = false, head_ends = false;
                 if (q < end) {
-                    const MaskedRows<4, OFF32> B(a.B, a.K, a.N, first_col);
+                    const MaskedRows<4, OFF32> B(a.B, a.N, first_col);
                     wi = s.begin_row[p.team];
                     bool whole = s.win[wi] - tile_start == q;  // the row begins with this team's entries
                     int32_t row_end = s.win[wi + 1] - tile_start;

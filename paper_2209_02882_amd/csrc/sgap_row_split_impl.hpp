@@ -3,6 +3,7 @@
 // stores; sgap_row_split_partial.hip: sub-groups merged with atomics).
 #pragma once
 #include "sgap_common.hpp"
+#include "sgap_flat.hpp"
 #include "sgap_gather.hpp"
 #include "sgap_lane_ops.hpp"
 
@@ -23,15 +24,7 @@ constexpr int kStageCap = 2048;  // (column, value) pairs per LDS chunk: 16 KB
 constexpr int kRowCap = 1024;    // rowptr entries kept in LDS per row block (+1)
 constexpr int kRowSplitMaxBlock = 512;  // threads per workgroup: 128, 256 or 512, chosen at launch
 
-// One row by the whole workgroup: as many chunk lanes as the columns take (a wavefront's at most) and block / lanes members,
-// each of which takes every (block / lanes)-th stored entry with DEPTH rows of B in flight; the members' sums are added up
-// through LDS in a fixed order, and the row has one plain store as ever.  For the rows whose length would keep the one group
-// that owns them busy long after the rest of the chip is done (see plan_row_split_grid).  A round of loads is a round trip to
-// memory whatever is in it, so lanes that hold no columns cost in proportion: with the next power of two of chunk lanes, 16
-// members instead of 25 at N = 37, a row of 4,096 entries took 32 rounds instead of 21.  Power laws, four matrices each, us,
-// power of two / as many as the columns take: 50,021 rows, N = 37 40.2 to 62.4 / 35.2 to 50.3; 20,396 rows, N = 37 34.9 to
-// 40.6 / 29.0 to 33.9; 53,897 rows, N = 51 28.9 to 47.2 / 27.6 to 42.5; columns that fill a power of two within 2 %.
-// s_A and s_part may be the same memory.  Block-uniform; barriers inside.
+// A thread's place among those that take a row together.
 struct SharedLanes {
     uint32_t lanes, members, member, chunk;  // member number `members` has no entries
     __device__ __forceinline__ SharedLanes(int64_t chunks, int block)
@@ -45,6 +38,17 @@ struct SharedLanes {
     }
 };
 
+// One row by the whole workgroup: as many chunk lanes as the columns take (a wavefront's at most) and block / lanes members,
+// each of which takes every (block / lanes)-th stored entry with DEPTH rows of B in flight; the members' sums are added up
+// through LDS in a fixed order, and the row has one plain store as ever.  For the rows whose length would keep the one group
+// that owns them busy long after the rest of the chip is done (see plan_row_split_grid).  A round of loads is a round trip to
+// memory whatever is in it, so lanes that hold no columns cost in proportion: with the next power of two of chunk lanes, 16
+// members instead of 25 at N = 37, a row of 4,096 entries took 32 rounds instead of 21.  Power laws, four matrices each, us,
+// power of two / as many as the columns take: 50,021 rows, N = 37 40.2 to 62.4 / 35.2 to 50.3; 20,396 rows, N = 37 34.9 to
+// 40.6 / 29.0 to 33.9; 53,897 rows, N = 51 28.9 to 47.2 / 27.6 to 42.5; columns that fill a power of two within 2 %.  Entries past
+// the end are masked loads (MaskedRows) of places that exist, not branches: 18,205 rows, N = 27 17.2 / 13.5; 10,000, N = 24
+// 13.6 / 9.6; 25,000, N = 48 31.4 / 24.7.
+// s_A and s_part may be the same memory.  Block-uniform; barriers inside.
 template <int VEC, bool OFF32, int DEPTH>
 __device__ __forceinline__ void shared_row(const SpmmArgs& a, int64_t row, uint32_t p_begin, uint32_t p_end,
                                            const SharedLanes& l, StagedEntry* __restrict__ s_A, int block)
@@ -59,7 +63,7 @@ __device__ __forceinline__ void shared_row(const SpmmArgs& a, int64_t row, uint3
         const int64_t k = k0 + (int64_t)chunk * VEC;
         const bool k_ok = k < N && member < members;
         const int64_t first = k_ok ? lane_first_col<VEC>(k, N) : 0;
-        const GlobalRows<VEC, OFF32> B(a.B, N, first);
+        const MaskedRows<VEC, OFF32> B(a.B, N, (uint32_t)first);
         Vec<VEC> acc;
         acc.zero();
         for (uint32_t base = p_begin; base < p_end; base += kStageCap) {
@@ -68,25 +72,19 @@ __device__ __forceinline__ void shared_row(const SpmmArgs& a, int64_t row, uint3
             stage_entries<8>(a.colidx + base, a.vals + base, cnt, s_A, block);
             __syncthreads();
             for (uint32_t q = member; k_ok && q < cnt; q += D * members) {
-                uint32_t at[D];
-                at[0] = q;
-#pragma unroll
-                for (int u = 1; u < D; ++u) at[u] = at[u - 1] + members;
-                StagedEntry e[D];
                 Vec<VEC> b[D];
 #pragma unroll
                 for (int u = 0; u < D; ++u) {
-                    e[u].col = 0;
-                    e[u].val = 0.0f;
-                    if (at[u] < cnt) e[u] = s_A[at[u]];
+                    const uint32_t at = q + u * members;
+                    b[u] = B.load(s_A[at < cnt ? at : q].col, at < cnt);
                 }
+                asm volatile("" ::: "memory");  // (the values are read meanwhile: registers)
 #pragma unroll
                 for (int u = 0; u < D; ++u) {
-                    b[u].zero();
-                    if (at[u] < cnt) b[u] = B.load(e[u].col);
+                    const uint32_t at = q + u * members;
+                    const float val = s_A[at < cnt ? at : q].val;
+                    acc.fma(at < cnt ? val : 0.0f, b[u]);
                 }
-#pragma unroll
-                for (int u = 0; u < D; ++u) acc.fma(e[u].val, b[u]);
             }
         }
         __syncthreads();  // the last entries are consumed
@@ -124,6 +122,52 @@ __device__ __forceinline__ void shared_row(const SpmmArgs& a, int64_t row, uint3
     }
 }
 
+// A finder's share of the rows (plan_row_split_grid): those of at least share_from entries and fewer than skip_from, one after the
+// other.  s_rp and s_mask: places for kRowCap rows and for a mask of every wavefront.
+template <int VEC, bool OFF32, int DEPTH>
+__device__ __forceinline__ void find_rows(const SpmmArgs& a, const RowSplitGrid& plan, int32_t skip_from, StagedEntry* __restrict__ s_A,
+                                          int32_t* __restrict__ s_rp, unsigned long long* __restrict__ s_mask, int block)
+{
+    const int64_t N = a.N;
+    constexpr uint32_t UNIT = FinderDeal::kUnit;
+    const uint32_t team = blockIdx.x >> plan.log2_team, teams = (uint32_t)plan.finders >> plan.log2_team;
+    const uint32_t mine = blockIdx.x & ((1u << plan.log2_team) - 1u);  // of the rows found, this one's turns
+    const int lane = threadIdx.x % kWave, wave = threadIdx.x / kWave;
+    const uint32_t last = plan.deal.first_place(team + 1, teams);
+    const SharedLanes lanes((N + VEC - 1) / VEC, block);
+    for (uint32_t first = plan.deal.first_place(team, teams); first < last; first += kRowCap / UNIT) {
+        const uint32_t look = (last - first < kRowCap / UNIT ? last - first : kRowCap / UNIT) * UNIT;
+        uint32_t found = 0;  // the same in all members of the team, and in the same order
+        for (uint32_t q0 = 0; q0 < look; q0 += block) {
+            const uint32_t q = q0 + threadIdx.x;
+            const int64_t r = plan.deal.row(first + q / UNIT, q % UNIT);
+            bool shared = q < look && r < a.M;
+            if (shared) {
+                const int32_t len = a.rowptr[r + 1] - a.rowptr[r];
+                shared = len >= plan.share_from;
+                shared = shared && len < skip_from;
+            }
+            const unsigned long long mask = __ballot(shared);
+            __syncthreads();  // the last rows found, or the last masks, are done with
+            if (lane == 0) s_mask[wave] = mask;
+            __syncthreads();
+            uint32_t rank = found + (uint32_t)__popcll(mask & ((1ull << lane) - 1ull));
+            for (int w = 0; w < block / kWave; ++w) {
+                const uint32_t c = (uint32_t)__popcll(s_mask[w]);
+                if (w < wave) rank += c;
+                found += c;
+            }
+            if (shared && (rank & ((1u << plan.log2_team) - 1u)) == mine) s_rp[rank >> plan.log2_team] = (int32_t)r;
+        }
+        __syncthreads();
+        const int n = (int)((found + (1u << plan.log2_team) - 1u - mine) >> plan.log2_team);
+        for (int i = 0; i < n; ++i) {
+            const int32_t row = __builtin_amdgcn_readfirstlane(s_rp[i]);
+            shared_row<VEC, OFF32, DEPTH>(a, row, (uint32_t)a.rowptr[row], (uint32_t)a.rowptr[row + 1], lanes, s_A, block);
+        }
+    }
+}
+
 // PARTIAL: the G members of a row reduce in sub-groups of `reduce_members`
 // (a power of two below G) and the first member of every sub-group adds its
 // sum to C with atomics; C must hold zeros before the launch.
@@ -132,12 +176,14 @@ __device__ __forceinline__ void shared_row(const SpmmArgs& a, int64_t row, uint3
 // the walk; the first `finders` workgroups of the grid look for them, a team of them in each share of the rows
 // (FinderDeal), and produce them in turn, one after the other with all their lanes (shared_row).  They start first, so that the longest rows are done while
 // the others are walked: a workgroup that came across one during its walk ended some 40 us behind the rest.
+// Registers: a row that a workgroup takes together wants more than six wavefronts per SIMD leave (10,000 rows, N = 16 9.6 us, with
+// five 8.4), a dozen columns or fewer rather the wavefronts (power law, 112,754 rows, N = 8 36.8, with five 40.1).
 // The workgroup size (the paper's blockSz, Section 7.2) is the launch's: SLOTS = blockDim.x / (G*LC)
 // groups work side by side on the rows of a row block.
 template <int G, int LC, int VEC, bool OFF32, bool PARTIAL, bool SKIP, int DEPTH>
-__global__ __launch_bounds__(kRowSplitMaxBlock) void row_split_kernel(SpmmArgs a, TileSched ts, int rows_per_slot,
-                                                                      int interleave, int reduce_members,
-                                                                      RowSplitGrid plan, RowSkip skip)
+__global__ __launch_bounds__(kRowSplitMaxBlock)
+__attribute__((amdgpu_waves_per_eu(2, G > 1 && !PARTIAL && VEC == 4 && LC > 2 ? 5 : 8)))
+void row_split_kernel(SpmmArgs a, TileSched ts, int rows_per_slot, int interleave, int reduce_members, RowSplitGrid plan, RowSkip skip)
 {
     __shared__ StagedEntry s_A[kStageCap];
     __shared__ int32_t s_rp[kRowCap + 1];
@@ -161,43 +207,7 @@ __global__ __launch_bounds__(kRowSplitMaxBlock) void row_split_kernel(SpmmArgs a
 
     if constexpr (SHARE) {
         if ((int)blockIdx.x < plan.finders) {
-            constexpr uint32_t UNIT = FinderDeal::kUnit;
-            const uint32_t team = blockIdx.x >> plan.log2_team, teams = (uint32_t)plan.finders >> plan.log2_team;
-            const uint32_t mine = blockIdx.x & ((1u << plan.log2_team) - 1u);  // of the rows found, this one's turns
-            const int lane = threadIdx.x % kWave, wave = threadIdx.x / kWave;
-            const uint32_t last = plan.deal.first_place(team + 1, teams);
-            const SharedLanes lanes((N + VEC - 1) / VEC, block);
-            for (uint32_t first = plan.deal.first_place(team, teams); first < last; first += kRowCap / UNIT) {
-                const uint32_t look = (last - first < kRowCap / UNIT ? last - first : kRowCap / UNIT) * UNIT;
-                uint32_t found = 0;  // the same in all members of the team, and in the same order
-                for (uint32_t q0 = 0; q0 < look; q0 += block) {
-                    const uint32_t q = q0 + threadIdx.x;
-                    const int64_t r = plan.deal.row(first + q / UNIT, q % UNIT);
-                    bool shared = q < look && r < a.M;
-                    if (shared) {
-                        const int32_t len = a.rowptr[r + 1] - a.rowptr[r];
-                        shared = len >= plan.share_from;
-                        if constexpr (SKIP) shared = shared && !(skip_on && len >= skip.min_len);
-                    }
-                    const unsigned long long mask = __ballot(shared);
-                    __syncthreads();  // the last rows found, or the last masks, are done with
-                    if (lane == 0) s_mask[wave] = mask;
-                    __syncthreads();
-                    uint32_t rank = found + (uint32_t)__popcll(mask & ((1ull << lane) - 1ull));
-                    for (int w = 0; w < block / kWave; ++w) {
-                        const uint32_t c = (uint32_t)__popcll(s_mask[w]);
-                        if (w < wave) rank += c;
-                        found += c;
-                    }
-                    if (shared && (rank & ((1u << plan.log2_team) - 1u)) == mine) s_rp[rank >> plan.log2_team] = (int32_t)r;
-                }
-                __syncthreads();
-                const int n = (int)((found + (1u << plan.log2_team) - 1u - mine) >> plan.log2_team);
-                for (int i = 0; i < n; ++i) {
-                    const int32_t row = __builtin_amdgcn_readfirstlane(s_rp[i]);
-                    shared_row<VEC, OFF32, DEPTH>(a, row, (uint32_t)a.rowptr[row], (uint32_t)a.rowptr[row + 1], lanes, s_A, block);
-                }
-            }
+            find_rows<VEC, OFF32, DEPTH>(a, plan, SKIP && skip_on ? skip.min_len : 0x7fffffff, s_A, s_rp, s_mask, block);
             if ((int)blockIdx.x < plan.walk_from) return;
         }
     }
