@@ -91,7 +91,11 @@ typedef enum {
  *       tile_cols admits more.  A row of at least 96*g entries (or fewer where
  *       a tile takes several passes, never below 256) is taken by a whole
  *       workgroup instead of holding one group up; it still has one plain
- *       store.
+ *       store.  At 12 to 64 columns and 300,000 entries or more (nnz_hint;
+ *       700,000 below 24 columns), 128 a row in the mean at most, and with the
+ *       layout left to the library, lanes share what a block of rows has evenly
+ *       instead: every group_size (from 16 on up to 16 columns) names the
+ *       same launch.
  *     nnz-balanced schedule: lane = one stored entry ({<1 nnz, c col>, r},
  *       Section 6.2); the group performs a SEGMENTED reduction keyed by row
  *       (Fig. 1c), one writeback lane per run of equal rows.  At N <= 16 a
@@ -108,11 +112,16 @@ typedef enum {
  *       64 columns, 40,960 up to 128, 20,480 beyond), group sizes 1, 2 and 4
  *       name the same launch: a lane has four consecutive rows, and a row of B
  *       that several of them want is gathered once.  Setting block_size or
- *       persistent (below) gives the launch row by row.
+ *       persistent (below) gives the launch row by row.  Where rows have 12
+ *       entries or fewer in the mean and 500,000 in all, every group_size
+ *       names the same launch (up to 48 columns; beyond, where B or a column
+ *       tile of it is small).
  *     nnz-balanced schedule: lane = group_size consecutive stored entries
  *       ({<g nnz, c col>, 1}, Section 6.1), or fewer where that many per lane
  *       are more than a tile has (a tile of 1,024 entries at N = 64 has 64 for
- *       each of 16 lanes; small matrices get smaller tiles).
+ *       each of 16 lanes; small matrices get smaller tiles).  At 16 to 128
+ *       columns, unless nnz_tile is set, the lanes of a tile share its rows and
+ *       entries evenly and every group_size names the same launch.
  *
  * In the nnz-balanced schedule a row whose stored entries all lie inside one
  * aligned block of positions (group_size positions, or a whole tile of about a
@@ -447,8 +456,9 @@ int sgap_ttm_csf(int64_t F, int64_t K, int64_t L,
  *   X1, X2    device, K x J and L x J row-major
  *   Y         device, I x J row-major; OVERWRITTEN
  *   group_size, strategy
- *             SGAP_REDUCE_PARALLEL: group_size lanes share a slice, split its
- *             fibers between them and tree-sum once per slice;
+ *             SGAP_REDUCE_PARALLEL: the lanes of a workgroup share the fibers
+ *             of a block of slices evenly, whatever group_size is, and add up
+ *             a slice's sums in a fixed order;
  *             SGAP_REDUCE_SERIAL: one lane (per column chunk) works through
  *             group_size consecutive slices by itself.
  * Slices are the unit of work (row-split schedule): every element of Y has
@@ -469,17 +479,18 @@ int sgap_mttkrp_csf(int64_t I, int64_t K, int64_t L, int64_t J,
  * The same operator with a choice of schedule (Section 6's two schedules
  * carried over to it):
  *   SGAP_SCHED_ROW_SPLIT     slices are the unit of work: exactly
- *                            sgap_mttkrp_csf (nnz_hint is not used)
+ *                            sgap_mttkrp_csf (parallel: nnz_hint
+ *                            sizes the blocks of slices)
  *   SGAP_SCHED_NNZ_BALANCED  stored entries are the unit of work, in tiles of
  *                            1,024, whatever slices and fibers they fall in (a
  *                            tensor with a few huge slices keeps the chip
  *                            busy).  parallel: G lanes hold G consecutive
  *                            entries and run two segmented sums, keyed by
  *                            fiber and then, over the fiber sums times their
- *                            rows of X1, by slice.  serial: a lane walks
- *                            consecutive entries, as many as divide a tile
- *                            evenly over the lanes whatever G is, and closes
- *                            slices into Y where they end.
+ *                            rows of X1, by slice.  serial: the lanes
+ *                            share a tile's (1,024 to 2,000 entries) fibers
+ *                            evenly, whatever G is, and close slices into Y
+ *                            where they end.
  *                            Y is set to zero first and every run's sum is
  *                            added with fp32 atomics: results agree from run
  *                            to run within rounding only.

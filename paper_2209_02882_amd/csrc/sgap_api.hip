@@ -455,7 +455,7 @@ int spmm_impl(int64_t M, int64_t K, int64_t N, const int32_t* rowptr, const int3
         } else if (wave_vec > 0) {
             err = launch_wave_rows(a, wave_vec, wave_rows_count, xcds, nullptr, s);
         } else if (par && c.block_size == 0 && c.persistent == 0 && c.tile_cols == 0 && c.rows_per_group == 0 &&
-                   flat_shared_rows_apply(K, N, avg_row, nnz_hint)) {
+                   flat_shared_rows_apply(K, N, g, avg_row, nnz_hint)) {
             err = launch_flat_shared_rows(a, xcds, cus, nnz_hint, s);
         } else if (row_split_by_quads(M, N, c, nnz_hint, cus)) {
             err = launch_row_quads(a, lc, (int)tile_cols, xcds, s);

@@ -258,8 +258,9 @@ bool row_quads_apply(int64_t M, int lc, int64_t tile_cols, double mean_row, int 
 hipError_t launch_row_quads(const SpmmArgs& a, int lc, int tile_cols, int xcds, hipStream_t s);
 // whether the parallel strategy of SDDMM takes a matrix in host memory by four rows together (g lanes per entry)
 bool sddmm_by_quads(int64_t M, int64_t K, int64_t J, int g, int64_t nnz_hint, const int32_t* rowptr, const int32_t* colidx);
-// parallel strategy, blocks of rows shared by teams of lanes (sgap_flat_shared.hip); never without a count of the entries
-bool flat_shared_rows_apply(int64_t K, int64_t N, double mean_row, int64_t nnz_hint);
+// parallel strategy, blocks of rows shared by teams of lanes (sgap_flat_shared.hip), where groups would have so many members;
+// never without a count of the entries
+bool flat_shared_rows_apply(int64_t K, int64_t N, int members, double mean_row, int64_t nnz_hint);
 hipError_t launch_flat_shared_rows(const SpmmArgs& a, int xcds, int compute_units, int64_t nnz_hint, hipStream_t s);
 // serial strategy, short rows (sgap_flat_rows.hip).  flat_rows_apply: whether that is the kernel for so many rows of
 // mean_row stored entries; never without a count of them

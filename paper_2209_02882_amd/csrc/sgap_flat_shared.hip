@@ -193,10 +193,13 @@ void flat_shared_rows_kernel(SpmmArgs a, int lanes, int block_rows, int64_t bloc
 // 20,000 9.0 / 7.2), few columns (50,000 rows, N = 8 17.5 / 24.3, N = 4 16.2 / 32), and where wide rows come from beyond
 // the L2s (500,000 rows of 16, N = 64 292 / 309; 200,000, N = 41, a B of 33 MB 129 / 128).  Long rows leave no members idle
 // (200,000 rows of 64, N = 32 118 / 107; 20,000 of 400 66 / 75).
-bool flat_shared_rows_apply(int64_t K, int64_t N, double mean_row, int64_t nnz_hint)
+// Groups of 8 and fewer have few idle members, and up to 16 columns that is enough (power law of 46,000 rows, N = 13, G = 8 17.5 /
+// 21.8, of 16 23 / 23; 130,000 32.6 / 36.6 and 53 / 50).
+bool flat_shared_rows_apply(int64_t K, int64_t N, int members, double mean_row, int64_t nnz_hint)
 {
     constexpr double kFsLongMean = 128.0;
     if (N < 12 || N > 64 || mean_row > kFsLongMean || (N > 40 && K * N * 4 > (32 << 20))) return false;
+    if (N <= 16 && members <= 8) return false;
     return nnz_hint >= (N < 24 ? 700'000 : 300'000);
 }
 

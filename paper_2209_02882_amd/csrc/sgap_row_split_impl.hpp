@@ -177,12 +177,13 @@ __device__ __forceinline__ void find_rows(const SpmmArgs& a, const RowSplitGrid&
 // (FinderDeal), and produce them in turn, one after the other with all their lanes (shared_row).  They start first, so that the longest rows are done while
 // the others are walked: a workgroup that came across one during its walk ended some 40 us behind the rest.
 // Registers: a row that a workgroup takes together wants more than six wavefronts per SIMD leave (10,000 rows, N = 16 9.6 us, with
-// five 8.4), a dozen columns or fewer rather the wavefronts (power law, 112,754 rows, N = 8 36.8, with five 40.1).
+// five 8.4); a dozen columns or fewer, and smaller groups, rather the wavefronts (power law, 112,754 rows, N = 8, G = 32 36.8,
+// with five 40.1; 130,000, N = 16, G = 8 31.7 and 34.1).
 // The workgroup size (the paper's blockSz, Section 7.2) is the launch's: SLOTS = blockDim.x / (G*LC)
 // groups work side by side on the rows of a row block.
 template <int G, int LC, int VEC, bool OFF32, bool PARTIAL, bool SKIP, int DEPTH>
 __global__ __launch_bounds__(kRowSplitMaxBlock)
-__attribute__((amdgpu_waves_per_eu(2, G > 1 && !PARTIAL && VEC == 4 && LC > 2 ? 5 : 8)))
+__attribute__((amdgpu_waves_per_eu(2, G > 1 && !PARTIAL && VEC == 4 && LC > 2 && G * LC == kWave ? 5 : 8)))
 void row_split_kernel(SpmmArgs a, TileSched ts, int rows_per_slot, int interleave, int reduce_members, RowSplitGrid plan, RowSkip skip)
 {
     __shared__ StagedEntry s_A[kStageCap];
