@@ -4,7 +4,7 @@
 //
 // Bound by the gathers from beyond the L2s where B is large (2,000,000 rows of 1 to 16 entries, N = 32, a B of 8.4 MB: 1.6 GB
 // at 7.5 TB/s), else by the address units.  us, a lane group per row that meets the others of its wavefront after each
-// (row_split_kernel) / this, rows of 1 to 16 entries: 2,000,000 rows, N = 32, B of 8.4 MB 217 / 214, of 2.6 MB 202 / 164;
+// (row_split_kernel) / this, rows of 1 to 16 entries: 2,000,000 rows, N = 32, B of 8.4 MB 217 / 212, of 2.6 MB 202 / 164;
 // N = 16, 4.2 MB 170 / 146; 160,000, N = 48 31.9 / 22.3; 225,000, N = 24 24.8 / 20.4; 115,000, N = 16, four rows to a lane
 // 17.2 / 10.2; 93,000, N = 16 9.9 / 9.4.  1,000,000 rows of 2 entries, N = 32 70.6 / 62.7.
 #include "sgap_common.hpp"

@@ -9,13 +9,13 @@
 // the same result every time.  A slice that goes on in the next piece is carried over in LDS, and a fiber that a piece has
 // no room for is the whole workgroup's.
 //
-// Bound by the gathers: of two factors of 8.4 MB 1.7 GB come from beyond the L2s, at 7.1 TB/s; small tensors by the chain
+// Bound by the gathers: of two factors of 8.4 MB 1.7 GB come from beyond the L2s, at 7.2 TB/s; small tensors by the chain
 // of loads that a block is (pointers, fibers, entries, then a team's rows of X2).  With a group of lanes per slice, members
 // m, m + G, ... of which took the slice's fibers (the form before), a third of the members had no fiber, each waited for the
 // longest of its wavefront's, and every slice ended in a tree sum.  us, group per slice / this, J = 32 unless said, slices x
-// fibers of a slice: 262,144 x 8 268 / 240, with factors of 256 KB 235 / 164; 227,077 x 4, J = 16 104 / 78; 133,470 x 6
+// fibers of a slice: 262,144 x 8 268 / 239, with factors of 256 KB 235 / 164; 227,077 x 4, J = 16 104 / 78; 133,470 x 6
 // 123 / 95; 43,825 x 7 62 to 76 / 41; 21,755 x 8 39 to 49 / 25; 15,510 x 6, J = 16 23 to 27 / 15; 100,000 x 8, J = 64
-// 254 / 230; fibers of 24 entries, 50,000 x 2 84 / 34; 100,000 x 4, one fiber in a hundred of 500 entries 609 / 84.
+// 254 / 230; fibers of 24 entries, 50,000 x 2 84 / 34; 100,000 x 4, one fiber in a hundred of 500 entries 609 / 74.
 #include "sgap_common.hpp"
 #include "sgap_flat.hpp"
 #include "sgap_nnz_common.hpp"

@@ -51,7 +51,8 @@ int32_t share_rows_from(int g, int passes)
 
 // Finders cost a look at every row pointer, so there are none where the caller's count of entries says that no row can
 // be long enough.  That count may be too small: the walk then takes every row, whatever its length (share_from).
-// Finders per compute unit, G = 8: the longest rows of a power law (4,096 entries) bind it otherwise.  65,536 rows,
+// Finders per compute unit, G = 8 (all measured before their loads were masked, and before flat_shared_rows_kernel took the
+// larger of these matrices): the longest rows of a power law (4,096 entries) bind it otherwise.  65,536 rows,
 // N = 37: 73 us without finders, 70.7 with one, 58.4 with two, 47.5 with four or eight; 114,150 rows, N = 34: 100.5
 // without, 100.4, 90.2 and 82.8 with one, two and four, 72.5 with eight (a stretch of rows for each; FinderDeal says
 // what dealing them out changed).  Where there are few finders two look through the same rows and take the long ones in

@@ -18,8 +18,9 @@ def lengths(kind, rng):
     if kind == "ragged":
         return rng.integers(0, 80, 20_001)
     if kind == "crowded":  # pieces that end inside rows, again and again
-        n = rng.integers(500, 768, 1500)
-        n[rng.integers(0, 1500, 40)] = [768, 767, 769, 1300, 2048] * 8
+        n = np.zeros(8000, np.int64)
+        n[::6] = rng.integers(500, 768, 1334)
+        n[6 * rng.integers(0, 1334, 40)] = [768, 767, 769, 1300, 2048] * 8
         return n
     if kind == "sparse":  # blocks of as many rows as there may be
         n = np.zeros(1_400_000, np.int64)
@@ -44,7 +45,7 @@ def test_shared_blocks_of_rows(kind, N):
     d = [torch.from_numpy(x).cuda() for x in (rowptr, colidx, vals, B)]
     C = torch.empty((M, N), device="cuda")
     for g in (2, 32):
-        for hint in (HINT, max(HINT, int(rowptr[-1])), 10**8):  # down to blocks of one row
+        for hint in (HINT, max(HINT, int(rowptr[-1])), 128 * M):  # down to blocks of few rows
             print("  rows", kind, N, g, hint, flush=True)
             C.fill_(float("nan"))
             binding.sgap_spmm_csr_ex(M, K, N, *d, C, g, binding.SGAP_REDUCE_PARALLEL, binding.SGAP_SCHED_ROW_SPLIT, nnz_hint=hint)
