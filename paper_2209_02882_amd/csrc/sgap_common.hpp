@@ -213,10 +213,17 @@ struct BRow {
     }
 };
 
-inline bool offsets_fit_32(const SpmmArgs& a)
+// Where the operands end whose rows are found by byte offsets of 32 bits.  The 32 bytes behind it are room for a load at
+// an offset that lies past every operand (MaskedRows).
+constexpr int64_t kOffsets32End = 0xffffffe0LL;
+
+// Both factors of a row's offset have 24 bits then.
+inline bool offsets_fit_32(int64_t rows, int64_t columns)
 {
-    return a.K <= (1 << 24) && a.N * 4 < (1 << 24) && a.K * a.N * 4 <= 0xffffffffLL;
+    return rows <= (1 << 24) && columns * 4 < (1 << 24) && rows * columns * 4 <= kOffsets32End;
 }
+
+inline bool offsets_fit_32(const SpmmArgs& a) { return offsets_fit_32(a.K, a.N); }
 
 // How an nnz-balanced kernel cuts the stored entries: tile = positions per LDS
 // tile, merge = tile mode of the merge rule, merge_log2 = log2 of the merge

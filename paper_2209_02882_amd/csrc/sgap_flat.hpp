@@ -14,17 +14,18 @@
 namespace sgap {
 
 // Rows of a dense operand by number; `ok` = false reads as zeros, without a branch where byte offsets have 32 bits (an offset
-// past the end of a buffer descriptor is not fetched).
+// past the end of a buffer descriptor is not fetched).  The masked offset is the descriptor's end, with room for a load of 16
+// bytes behind it: none of its words has an offset that wraps round to the operand's first ones.
 template <int VEC, bool OFF32>
 struct MaskedRows {
     __amdgpu_buffer_rsrc_t rows;
     uint32_t row_bytes, k_bytes;
     const float* base;
     int64_t J;
-    // (The descriptor reaches as far as 32-bit offsets of words do, not to the end of X: the number of X's rows would have to be
-    // held for it, and row_split_kernel, with no scalar registers left, lost a wavefront per SIMD to that.)
+    // (The descriptor reaches as far as byte offsets of 32 bits may (kOffsets32End), not to the end of X: the number of X's rows
+    // would have to be held for it, and row_split_kernel, with no scalar registers left, lost a wavefront per SIMD to that.)
     __device__ __forceinline__ MaskedRows(const float* X, int64_t j, uint32_t k)
-        : rows(__builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(X), 0, (int)0xfffffffcu, 0x00020000)), row_bytes((uint32_t)(j * 4)),
+        : rows(__builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(X), 0, (int)kOffsets32End, 0x00020000)), row_bytes((uint32_t)(j * 4)),
           k_bytes(k * 4), base(X + k), J(j)
     {
     }
@@ -32,7 +33,7 @@ struct MaskedRows {
     {
         Vec<VEC> r;
         if constexpr (OFF32) {
-            const uint32_t off = ok ? __umul24((uint32_t)row, row_bytes) + k_bytes : 0xfffffffcu;
+            const uint32_t off = ok ? __umul24((uint32_t)row, row_bytes) + k_bytes : (uint32_t)kOffsets32End;
             if constexpr (VEC == 4) {
                 typedef uint32_t raw_u4 __attribute__((ext_vector_type(4)));
                 const raw_u4 t = __builtin_amdgcn_raw_buffer_load_b128(rows, (int)off, 0, 0);

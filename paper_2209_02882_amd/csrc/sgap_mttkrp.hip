@@ -218,8 +218,7 @@ struct LaunchMttkrp {
 // rows_per_slot = consecutive slices of a lane, lc = chunk lanes, vec = columns per lane.
 hipError_t launch_mttkrp(const MttkrpArgs& a, int rows_per_slot, int lc, int vec, int xcds, hipStream_t s)
 {
-    // every byte offset into X2 fits 32 bits and both factors of it fit 24 bits
-    const bool off32 = a.L <= (1 << 24) && a.J * 4 < (1 << 24) && a.L * a.J * 4 <= 0xffffffffLL;
+    const bool off32 = offsets_fit_32(a.L, a.J);
     const int64_t rows_per_block = (int64_t)(kBlock / lc) * rows_per_slot;
     if ((a.I + rows_per_block - 1) / rows_per_block + xcds > 0x7ffffff0LL) return hipErrorInvalidValue;
     LaunchMttkrp f{a, rows_per_slot, xcds, off32, s};

@@ -333,13 +333,6 @@ int mttkrp_block_slices(int64_t I, int64_t nnz_hint, int compute_units)
     return slices < kMfSlices ? (int)slices : kMfSlices;
 }
 
-// every byte offset into X1 and X2 fits 32 bits and both factors of it fit 24 bits
-static bool mttkrp_off32(const MttkrpArgs& a)
-{
-    auto fits = [&](int64_t rows) { return rows <= (1 << 24) && a.J * 4 < (1 << 24) && rows * a.J * 4 <= 0xffffffffLL; };
-    return fits(a.K) && fits(a.L);
-}
-
 hipError_t launch_mttkrp_fibers(const MttkrpArgs& a, int block_slices, int vec, int xcds, hipStream_t s)
 {
     if (block_slices > kMfSlices) block_slices = kMfSlices;
@@ -351,7 +344,7 @@ hipError_t launch_mttkrp_fibers(const MttkrpArgs& a, int block_slices, int vec, 
     auto go = [&](auto kernel) {
         hipLaunchKernelGGL(kernel, dim3((unsigned)(blocks_per_xcd * xcds)), dim3(kBlock), 0, s, a, lanes, block_slices, blocks, blocks_per_xcd, xcds);
     };
-    const bool off32 = mttkrp_off32(a);
+    const bool off32 = offsets_fit_32(a.K, a.J) && offsets_fit_32(a.L, a.J);
     if (vec == 4) { if (off32) go(mttkrp_fibers_kernel<4, true>); else go(mttkrp_fibers_kernel<4, false>); }
     else if (vec == 2) { if (off32) go(mttkrp_fibers_kernel<2, true>); else go(mttkrp_fibers_kernel<2, false>); }
     else { if (off32) go(mttkrp_fibers_kernel<1, true>); else go(mttkrp_fibers_kernel<1, false>); }
@@ -375,7 +368,7 @@ hipError_t launch_mttkrp_tiles(const MttkrpArgs& a, int vec, int compute_units, 
     }
     const int grid = persistent_grid(kMfResident, compute_units, nnz_hint, (int)tile);
     auto go = [&](auto kernel) { hipLaunchKernelGGL(kernel, dim3(grid), dim3(kBlock), 0, s, a, lanes, (int)tile); };
-    const bool off32 = mttkrp_off32(a);
+    const bool off32 = offsets_fit_32(a.K, a.J) && offsets_fit_32(a.L, a.J);
     if (vec == 4) { if (off32) go(mttkrp_tiles_kernel<4, true>); else go(mttkrp_tiles_kernel<4, false>); }
     else if (vec == 2) { if (off32) go(mttkrp_tiles_kernel<2, true>); else go(mttkrp_tiles_kernel<2, false>); }
     else { if (off32) go(mttkrp_tiles_kernel<1, true>); else go(mttkrp_tiles_kernel<1, false>); }

@@ -348,9 +348,8 @@ bool mttkrp_serial_applies(int64_t J, int64_t nnz_hint)
 hipError_t launch_mttkrp_serial(const MttkrpArgs& a, int lc, int vec, int compute_units, int64_t nnz_hint,
                                 hipStream_t s)
 {
-    auto fits = [&](int64_t rows) { return rows <= (1 << 24) && a.J * 4 < (1 << 24) && rows * a.J * 4 <= 0xffffffffLL; };
     if (a.J > kMsColumns) return hipErrorInvalidValue;
-    if (!dispatch_lc<1>(lc, vec, LaunchSerial{a, compute_units, nnz_hint, fits(a.K) && fits(a.L), s}))
+    if (!dispatch_lc<1>(lc, vec, LaunchSerial{a, compute_units, nnz_hint, offsets_fit_32(a.K, a.J) && offsets_fit_32(a.L, a.J), s}))
         return hipErrorInvalidValue;
     return hipGetLastError();
 }
