@@ -117,7 +117,8 @@ __device__ __forceinline__ void flat_stage(StagedEntry* __restrict__ entry, cons
 }
 
 // Where the teams begin: with whole runs, at the first one that starts at or behind an even share of the work; CUT: inside a run
-// where that is one of more than kFlatCut entries, and s.start is made of flat_at().  The caller synchronises.
+// where that is one of more than kFlatCut entries, and s.start is made of flat_at().  The caller synchronises.  Whether this
+// thread cut a run.
 // Work: a run costs a turn and what it does at its end, whatever it has, and kFlatRunCost entries more are about that.  us, even
 // shares of the entries / of this: TTM, 21,755 fibers of 1 to 16, N = 64 18.2 / 17.3, 76,491 slices of four, N = 48 62.0 / 59.7;
 // MTTKRP, 262,144 slices 241.0 / 238.4, 21,755 25.3 / 24.3; 100,000, J = 4, one in a thousand of 2,000 to 20,000 fibers 116 /
@@ -129,7 +130,7 @@ constexpr int32_t kFlatRunCost = 6;
 __device__ __forceinline__ int32_t flat_at(int run, int32_t pos) { return run | pos << 16; }
 
 template <bool CUT, typename SH>
-__device__ __forceinline__ void flat_deal(SH& s, int32_t e0, int32_t cnt, int n, int teams, int tid)
+__device__ __forceinline__ bool flat_deal(SH& s, int32_t e0, int32_t cnt, int n, int teams, int tid)
 {
     const int32_t all = cnt + kFlatRunCost * n;
     const int32_t share = all > teams ? (all + teams - 1) / teams : 1;
@@ -139,6 +140,7 @@ __device__ __forceinline__ void flat_deal(SH& s, int32_t e0, int32_t cnt, int n,
         const int t = (int)(((float)weight(run) + 0.5f) * per_share);
         return t < teams ? t : teams - 1;
     };
+    bool cut = false;
     // the teams behind `from` up to `to`, whose share begins behind the beginning of run i - 1, at the latest with run i
     auto set = [&](int from, int to, int i) {
         int32_t pos = 0, before = 0, front = 0;
@@ -153,7 +155,9 @@ __device__ __forceinline__ void flat_deal(SH& s, int32_t e0, int32_t cnt, int n,
                 s.start[t] = i;
             } else {
                 const int32_t at = t * share > front ? t * share - front : 0;  // of run i - 1's entries
-                s.start[t] = pos - before > kFlatCut && before + at < pos ? flat_at(i - 1, before + at) : flat_at(i, pos);
+                const bool inside = pos - before > kFlatCut && before + at < pos;
+                s.start[t] = inside ? flat_at(i - 1, before + at) : flat_at(i, pos);
+                cut = cut || (inside && at > 0);
             }
         }
     };
@@ -163,16 +167,17 @@ __device__ __forceinline__ void flat_deal(SH& s, int32_t e0, int32_t cnt, int n,
         set(i == 0 ? -1 : team_of(i - 1), mine, i);
         if (i == n - 1) set(mine, teams, n);
     }
+    return cut;
 }
 
 // The runs [run, last), run < last, from entry q (of run `run`) on up to entry `stop`.  ahead(run, ok) is called before the last
-// entries of a run are multiplied (ok; else before others), done(run, sum) when they are.
+// entries of a run are multiplied (ok; else before others), done(run) when they are and are in sum, which is the last run's
+// afterwards.
 template <int VEC, bool OFF32, typename SH, typename AHEAD, typename DONE>
-__device__ __forceinline__ void flat_walk(const SH& s, int run, int last, int32_t q, int32_t stop, int32_t e0,
+__device__ __forceinline__ void flat_walk(const SH& s, Vec<VEC>& sum, int run, int last, int32_t q, int32_t stop, int32_t e0,
                                           const MaskedRows<VEC, OFF32>& X, bool k_ok, AHEAD&& ahead, DONE&& done)
 {
     constexpr int D = kFlatBatch;
-    Vec<VEC> sum;
     sum.zero();
     auto end_of = [&](int r) {
         const int32_t e = s.ptr[r + 1 <= last ? r + 1 : last] - e0;
@@ -204,8 +209,8 @@ __device__ __forceinline__ void flat_walk(const SH& s, int run, int last, int32_
 #pragma unroll
         for (int u = 0; u < D; ++u) sum.fma(e[u].val, b[u]);
         if (ends) {
-            done(now, sum);
-            sum.zero();
+            done(now);
+            if (run < last) sum.zero();
         }
     } while (run < last);
 }

@@ -108,8 +108,9 @@ __global__ __launch_bounds__(kBlock) void flat_rows_kernel(SpmmArgs a, int lanes
                 const int first = c.ok ? s.start[p.team] : 0, last = c.ok ? s.start[p.team + 1] : 0;
                 if (first < last) {
                     const MaskedRows<VEC, OFF32> B(a.B, a.N, c.first);
-                    flat_walk<VEC, OFF32>(s, first, last, s.ptr[first] - e0, 0x7fffffff, e0, B, true, [](int, bool) {},
-                                          [&](int row, const Vec<VEC>& sum) { store((uint32_t)row, sum); });
+                    Vec<VEC> sum;
+                    flat_walk<VEC, OFF32>(s, sum, first, last, s.ptr[first] - e0, 0x7fffffff, e0, B, true, [](int, bool) {},
+                                          [&](int row) { store((uint32_t)row, sum); });
                 }
             }
             r0 += n;

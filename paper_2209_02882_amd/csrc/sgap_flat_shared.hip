@@ -147,8 +147,9 @@ void flat_shared_rows_kernel(SpmmArgs a, int lanes, int block_rows, int64_t bloc
                 const MaskedRows<4, OFF32> B(a.B, a.N, c.first);
                 bool whole = (int)(from >> 16) == s.ptr[first] - e0 && !(first == 0 && comes_in);
                 const int ends = cut && finished == n ? n - 1 : finished;
-                flat_walk<4, OFF32>(s, first, last, from >> 16, to >> 16, e0, B, c.ok, [](int, bool) {},
-                                      [&](int row, const Vec<4>& sum) {
+                Vec<4> sum;
+                flat_walk<4, OFF32>(s, sum, first, last, from >> 16, to >> 16, e0, B, c.ok, [](int, bool) {},
+                                      [&](int row) {
                                           const bool is_end = row < ends;
                                           if (whole && is_end) {
                                               if (row != hole_row) store((uint32_t)row, sum);

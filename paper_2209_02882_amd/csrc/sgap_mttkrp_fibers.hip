@@ -40,6 +40,7 @@ struct MfShared {
     int32_t fp[kMfSlices + 1];  // first fibers of the slices at hand
     FlatHeads<VEC> heads;       // of slices
     Vec<VEC> carry[2][kWave];   // of the slice that goes on in the next piece
+    int32_t cut;                // whether several teams have a part of one fiber
 };
 
 // The fibers [f_begin, f_end), slice number first_slice holding the first of them.
@@ -100,6 +101,7 @@ __device__ __forceinline__ void mttkrp_block(const MttkrpArgs& a, MfShared<VEC>&
             __syncthreads();  // the piece before is done with
             {
                 const FlatPlace p(lanes);
+                if (p.tid == 0) sh.cut = 0;
 #pragma unroll 2
                 for (int i = p.tid; i <= n; i += kBlock) {
                     int32_t e = a.eptr[f0 + i];
@@ -174,56 +176,108 @@ __device__ __forceinline__ void mttkrp_block(const MttkrpArgs& a, MfShared<VEC>&
             {
                 const FlatPlace p(lanes);
                 flat_stage<kMfEntries>(s.entry, a.eidx, a.vals, e0, cnt, p.tid);
-                flat_deal<true>(s, e0, cnt, n, teams, p.tid);
+                if (flat_deal<true>(s, e0, cnt, n, teams, p.tid)) sh.cut = 1;
             }
             __syncthreads();
 
-            const FlatPlace p(lanes);
-            const Columns c(p, k0, a.J, teams);
-            Vec<VEC> sum;
+            // What a team has of the piece's fibers.  (Looked up again behind the walk, which has no registers left for it.)
+            struct Share {
+                int first, begun, finished, last;  // fibers from `begun` on begin here, those before `finished` end here
+                int32_t from, to;                  // entries
+                __device__ __forceinline__ Share(const FlatShared<kMfEntries, kMfFibers>& s, const FlatPlace& p, int teams, int32_t e0)
+                {
+                    first = begun = finished = last = from = to = 0;
+                    if (p.team >= teams) return;
+                    const uint32_t at = s.start[p.team], end = s.start[p.team + 1];
+                    begun = first = at & 0xffff;
+                    finished = last = end & 0xffff;
+                    from = at >> 16, to = end >> 16;
+                    begun += from > s.ptr[first] - e0 ? 1 : 0;
+                    last += to > s.ptr[finished] - e0 ? 1 : 0;
+                }
+                __device__ __forceinline__ bool open() const { return last > finished && finished >= begun; }  // the last one begins here and goes on behind
+            };
+            Vec<VEC> sum, head, t, x;  // of the slice at hand; of one that began in front; of the fiber; X1's row
             sum.zero();
+            head.zero();
             int slice = 0;
-            bool goes_on = false;  // the slice that begins in this team's fibers goes on behind them
+            int32_t slice_end = 0;
+            bool whole = false, head_ends = false;  // the slice at hand begins here; what is in head ends here
             {
-                const uint32_t from = p.team < teams ? s.start[p.team] : 0, to = p.team < teams ? s.start[p.team + 1] : 0;
-                const int first = from & 0xffff, finished = to & 0xffff;  // fibers before `finished` end here
-                const bool cut = (int)(to >> 16) > s.ptr[finished] - e0;
-                const int last = finished + (cut ? 1 : 0);
-                bool head_ends = false;
-                if (first < last) {
+                const FlatPlace p(lanes);
+                const Columns c(p, k0, a.J, teams);
+                const Share m(s, p, teams, e0);
+                if (m.first < m.last) {
                     const MaskedRows<VEC, OFF32> x1(a.X1, a.J, c.first), x2(a.X2, a.J, c.first);
-                    slice = last_row_at_or_before(sh.fp, 0, slices - 1, f0 + first);
-                    bool whole = sh.fp[slice] == f0 + first && (int)(from >> 16) == s.ptr[first] - e0;
-                    int32_t slice_end = sh.fp[slice + 1] - f0;
-                    Vec<VEC> x;
+                    slice = last_row_at_or_before(sh.fp, 0, slices - 1, f0 + m.first);
+                    whole = sh.fp[slice] == f0 + m.first && m.begun == m.first;
+                    slice_end = sh.fp[slice + 1] - f0;
                     flat_walk<VEC, OFF32>(
-                        s, first, last, from >> 16, to >> 16, e0, x2, c.ok, [&](int f, bool ends) { x = x1.load(sh.fk[f], ends && c.ok); },
-                        [&](int f, const Vec<VEC>& t) {
+                        s, t, m.first, m.last, m.from, m.to, e0, x2, c.ok, [&](int f, bool ends) { x = x1.load(sh.fk[f], ends && c.ok); },
+                        [&](int f) {
+                            if (!SHARED_SLICES && f < m.begun) {
+                                sh.heads.head[p.tid] = t;  // of a fiber that began in front
+                                sh.heads.ended[p.team] = f < m.finished ? 1 : 0;
+                            } else if (SHARED_SLICES || f < m.finished) {
 #pragma unroll
-                            for (int i = 0; i < VEC; ++i) sum.v[i] = __builtin_fmaf(x.v[i], t.v[i], sum.v[i]);
-                            if (f + 1 != slice_end || f >= finished) return;
+                                for (int i = 0; i < VEC; ++i) sum.v[i] = __builtin_fmaf(x.v[i], t.v[i], sum.v[i]);
+                            }
+                            if (f + 1 != slice_end || f == m.finished) return;
                             if (whole) {
                                 store(slice, c, sum);
-                            } else {
-                                sh.heads.head[p.tid] = sum;
+                            } else if (SHARED_SLICES || f >= m.begun) {  // (else the team that has the fiber's beginning closes the slice)
+                                head = sum;
                                 head_ends = true;
                             }
                             sum.zero();
                             whole = true;
-                            if (f + 1 < last) {
+                            if (f + 1 < m.last) {
                                 do slice_end = sh.fp[++slice + 1] - f0;
                                 while (slice_end == f + 1);
                             }
                         });
-                    const bool open = last != slice_end || cut;
-                    goes_on = open && whole;
-                    if (open && !whole) sh.heads.head[p.tid] = sum;
-                } else {
-                    sh.heads.head[p.tid] = sum;
                 }
-                if (p.team < teams) sh.heads.ended[p.team] = head_ends ? 1 : 0;
             }
+            const FlatPlace p(lanes);
+            const Columns c(p, k0, a.J, teams);
+            bool goes_on = false;  // the slice that begins in this team's fibers goes on behind them
+            const Share m(s, p, teams, e0);
+            const bool begins_late = !SHARED_SLICES && m.begun > m.first, open = !SHARED_SLICES && m.open();
+            // what the team has of the slice at hand, with all of its fibers in it
+            auto rest = [&](bool ends) {
+                if (!ends) {
+                    goes_on = whole;
+                    if (!whole) head = sum;
+                } else if (whole) {
+                    store(slice, c, sum);
+                } else {
+                    head = sum;
+                    head_ends = true;
+                }
+            };
+            if (!open && m.first < m.last && (m.last != slice_end || m.last > m.finished)) rest(false);
+            auto put_head = [&] {
+                sh.heads.head[p.tid] = head;
+                if (p.team < teams) sh.heads.ended[p.team] = head_ends ? 1 : 0;
+            };
+            if (!begins_late && !open) put_head();
             __syncthreads();
+            // A fiber that several teams share: its sum comes together before it is multiplied with its row of X1, as that of any
+            // other does (parts of it may be zero, cancel or leave the range where the sum does not, and an infinity in X1 is to
+            // meet the sum).  Not in a tile, which cuts fibers itself.
+            if (!SHARED_SLICES && sh.cut != 0) {
+                batch_heads(sh.heads, teams, lanes, p);
+                __syncthreads();
+                if (open) {
+                    add_heads<VEC, true>(t, sh.heads, p.team + 1, teams, lanes, p.chunk);
+#pragma unroll
+                    for (int i = 0; i < VEC; ++i) sum.v[i] = __builtin_fmaf(x.v[i], t.v[i], sum.v[i]);
+                    rest(m.last == slice_end);
+                }
+                __syncthreads();
+                if (begins_late || open) put_head();
+                __syncthreads();
+            }
             if constexpr (SHARED_SLICES) {
                 batch_heads(sh.heads, teams, lanes, p);
                 __syncthreads();
