@@ -170,9 +170,9 @@ __device__ __forceinline__ bool flat_deal(SH& s, int32_t e0, int32_t cnt, int n,
     return cut;
 }
 
-// The runs [run, last), run < last, from entry q (of run `run`) on up to entry `stop`.  ahead(run, ok) is called before the last
-// entries of a run are multiplied (ok; else before others), done(run) when they are and are in sum, which is the last run's
-// afterwards.
+// The runs [run, last), run < last, from entry q (of run `run`) on up to entry `stop`.  ahead(run, ok, any) is called before the last
+// entries of a run are multiplied (ok; else before others; any: there are such), done(run) when they are and are in sum, which is
+// the last run's afterwards.
 template <int VEC, bool OFF32, typename SH, typename AHEAD, typename DONE>
 __device__ __forceinline__ void flat_walk(const SH& s, Vec<VEC>& sum, int run, int last, int32_t q, int32_t stop, int32_t e0,
                                           const MaskedRows<VEC, OFF32>& X, bool k_ok, AHEAD&& ahead, DONE&& done)
@@ -197,7 +197,7 @@ __device__ __forceinline__ void flat_walk(const SH& s, Vec<VEC>& sum, int run, i
             if (u >= left) e[u].val = 0.0f;
         }
         const bool ends = end - q <= D;
-        ahead(run, ends);
+        ahead(run, ends, left > 0);
         const int now = run;
         if (ends) {
             ++run;

@@ -109,7 +109,7 @@ __global__ __launch_bounds__(kBlock) void flat_rows_kernel(SpmmArgs a, int lanes
                 if (first < last) {
                     const MaskedRows<VEC, OFF32> B(a.B, a.N, c.first);
                     Vec<VEC> sum;
-                    flat_walk<VEC, OFF32>(s, sum, first, last, s.ptr[first] - e0, 0x7fffffff, e0, B, true, [](int, bool) {},
+                    flat_walk<VEC, OFF32>(s, sum, first, last, s.ptr[first] - e0, 0x7fffffff, e0, B, true, [](int, bool, bool) {},
                                           [&](int row) { store((uint32_t)row, sum); });
                 }
             }

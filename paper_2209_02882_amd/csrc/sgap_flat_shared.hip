@@ -148,7 +148,7 @@ void flat_shared_rows_kernel(SpmmArgs a, int lanes, int block_rows, int64_t bloc
                 bool whole = (int)(from >> 16) == s.ptr[first] - e0 && !(first == 0 && comes_in);
                 const int ends = cut && finished == n ? n - 1 : finished;
                 Vec<4> sum;
-                flat_walk<4, OFF32>(s, sum, first, last, from >> 16, to >> 16, e0, B, c.ok, [](int, bool) {},
+                flat_walk<4, OFF32>(s, sum, first, last, from >> 16, to >> 16, e0, B, c.ok, [](int, bool, bool) {},
                                       [&](int row) {
                                           const bool is_end = row < ends;
                                           if (whole && is_end) {

@@ -213,7 +213,10 @@ __device__ __forceinline__ void mttkrp_block(const MttkrpArgs& a, MfShared<VEC>&
                     whole = sh.fp[slice] == f0 + m.first && m.begun == m.first;
                     slice_end = sh.fp[slice + 1] - f0;
                     flat_walk<VEC, OFF32>(
-                        s, t, m.first, m.last, m.from, m.to, e0, x2, c.ok, [&](int f, bool ends) { x = x1.load(sh.fk[f], ends && c.ok); },
+                        s, t, m.first, m.last, m.from, m.to, e0, x2, c.ok,
+                        // (a stored fiber without entries has no part in a tile, as with every other kernel whose unit of work is the
+                        // entry: whether the tile takes it up depends on where others end, and X1 may be infinite there)
+                        [&](int f, bool ends, bool any) { x = x1.load(sh.fk[f], ends && c.ok && (any || !SHARED_SLICES)); },
                         [&](int f) {
                             if (!SHARED_SLICES && f < m.begun) {
                                 sh.heads.head[p.tid] = t;  // of a fiber that began in front

@@ -71,3 +71,24 @@ def test_a_fiber_is_summed_whole_whatever_its_length(J):
                 binding.sgap_mttkrp_csf_ex(slices, 50, L, J, *d, Y, g, strategy, binding.SGAP_SCHED_ROW_SPLIT, nnz_hint=hint)
                 got = Y.cpu().numpy().astype(np.float64)
                 assert np.array_equal(got, np.broadcast_to(ref, got.shape), equal_nan=True), (strategy, g, hint)
+
+
+@pytest.mark.parametrize("J", [1, 3, 8, 20, 32, 70])
+def test_fibers_without_entries_have_no_part_where_entries_are_the_unit_of_work(J):
+    """X1 is not finite in the rows that only such fibers name.  They lie amid a tile, at its ends, and many in a row."""
+    rng = np.random.default_rng(J)
+    slices, K, L = 1200, 64, 500
+    fptr, fidx = wl.csr_from_lengths(rng, rng.integers(0, 25, slices), K)
+    eptr, eidx = wl.csr_from_lengths(rng, np.where(fidx % 2 == 0, 0, np.resize([1, 3, 1, 40, 2, 8], fidx.size)), L)
+    vals = wl.fill_values(rng, eidx.size, True)
+    X1, X2 = (wl.fill_values(rng, n * J, True).reshape(n, J) for n in (K, L))
+    X1[::2] = 0
+    ref, _ = oracle.mttkrp_csf(slices, K, L, J, fptr, fidx, eptr, eidx, vals, X1, X2)
+    X1[::4], X1[2::4] = np.inf, np.nan
+    d = [torch.from_numpy(x).cuda() for x in (fptr, fidx, eptr, eidx, vals, X1, X2)]
+    for strategy in binding.STRATEGIES.values():
+        for g in (1, 8, 64):
+            for hint in (-1, eidx.size, 10**9):
+                Y = torch.empty((slices, J), device="cuda")
+                binding.sgap_mttkrp_csf_ex(slices, K, L, J, *d, Y, g, strategy, binding.SGAP_SCHED_NNZ_BALANCED, nnz_hint=hint)
+                assert np.array_equal(Y.cpu().numpy().astype(np.float64), ref), (strategy, g, hint)
