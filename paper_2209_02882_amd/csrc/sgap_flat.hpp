@@ -11,6 +11,8 @@
 #include "sgap_common.hpp"
 #include "sgap_gather.hpp"
 
+#include <type_traits>
+
 namespace sgap {
 
 // Rows of a dense operand by number; `ok` = false reads as zeros, without a branch where byte offsets have 32 bits (an offset
@@ -170,15 +172,100 @@ __device__ __forceinline__ bool flat_deal(SH& s, int32_t e0, int32_t cnt, int n,
     return cut;
 }
 
+// The sum of a batch's products, four and four: one chain of additions as long as a team's share of a row had up to 1.7 times the
+// error of the groups' trees and of their members' and lanes' short chains.
+template <int VEC>
+__device__ __forceinline__ Vec<VEC> flat_dot(const StagedEntry (&e)[kFlatBatch], const Vec<VEC> (&b)[kFlatBatch])
+{
+    constexpr int H = kFlatBatch / 2;
+    Vec<VEC> sum;
+#pragma unroll
+    for (int i = 0; i < VEC; ++i) {
+        float low = e[0].val * b[0].v[i], high = e[H].val * b[H].v[i];
+#pragma unroll
+        for (int u = 1; u < H; ++u) {
+            low = __builtin_fmaf(e[u].val, b[u].v[i], low);
+            high = __builtin_fmaf(e[H + u].val, b[H + u].v[i], high);
+        }
+        sum.v[i] = low + high;
+    }
+    return sum;
+}
+
+// A sum in two chains that take turns: its error grows with the number of terms as that of two sums half as long.
+template <int VEC>
+struct FlatChains {
+    Vec<VEC> turn, other;
+    __device__ __forceinline__ void zero() { turn.zero(), other.zero(); }
+    __device__ __forceinline__ void add(const Vec<VEC>& term)
+    {
+        const Vec<VEC> last = turn;
+        turn = other;
+#pragma unroll
+        for (int i = 0; i < VEC; ++i) other.v[i] = last.v[i] + term.v[i];
+    }
+    __device__ __forceinline__ Vec<VEC> total() const
+    {
+        Vec<VEC> sum;
+#pragma unroll
+        for (int i = 0; i < VEC; ++i) sum.v[i] = turn.v[i] + other.v[i];
+        return sum;
+    }
+};
+
+template <int VEC>
+struct FlatChain {
+    Vec<VEC> sum;
+    __device__ __forceinline__ void zero() { sum.zero(); }
+    __device__ __forceinline__ void add(const Vec<VEC>& term)
+    {
+#pragma unroll
+        for (int i = 0; i < VEC; ++i) sum.v[i] += term.v[i];
+    }
+    __device__ __forceinline__ void add_product(const Vec<VEC>& x, const Vec<VEC>& t)
+    {
+#pragma unroll
+        for (int i = 0; i < VEC; ++i) sum.v[i] = __builtin_fmaf(x.v[i], t.v[i], sum.v[i]);
+    }
+    __device__ __forceinline__ Vec<VEC> total() const { return sum; }
+};
+
+// A sum of products in chains of four, whose sums are a chain.
+template <int VEC>
+struct FlatFours {
+    Vec<VEC> four, before;
+    int terms;
+    __device__ __forceinline__ void zero() { four.zero(), before.zero(), terms = 0; }
+    __device__ __forceinline__ void add_product(const Vec<VEC>& x, const Vec<VEC>& t)
+    {
+        const bool full = (++terms & 3) == 0;
+#pragma unroll
+        for (int i = 0; i < VEC; ++i) {
+            const float sum = __builtin_fmaf(x.v[i], t.v[i], four.v[i]);
+            before.v[i] += full ? sum : 0.0f;
+            four.v[i] = full ? 0.0f : sum;
+        }
+    }
+    __device__ __forceinline__ Vec<VEC> total() const
+    {
+        Vec<VEC> sum;
+#pragma unroll
+        for (int i = 0; i < VEC; ++i) sum.v[i] = before.v[i] + four.v[i];
+        return sum;
+    }
+};
+
 // The runs [run, last), run < last, from entry q (of run `run`) on up to entry `stop`.  ahead(run, ok, any) is called before the last
-// entries of a run are multiplied (ok; else before others; any: there are such), done(run) when they are and are in sum, which is
-// the last run's afterwards.
-template <int VEC, bool OFF32, typename SH, typename AHEAD, typename DONE>
-__device__ __forceinline__ void flat_walk(const SH& s, Vec<VEC>& sum, int run, int last, int32_t q, int32_t stop, int32_t e0,
-                                          const MaskedRows<VEC, OFF32>& X, bool k_ok, AHEAD&& ahead, DONE&& done)
+// entries of a run are multiplied (ok; else before others; any: there are such), done(run, sum) when they are and another
+// run follows; the last one's sum is returned (what a caller keeps of it then needs no registers meanwhile).
+// SUM: how the batches of a run are added up.
+template <int VEC, bool OFF32, typename SUM, typename SH, typename AHEAD, typename DONE>
+__device__ __forceinline__ Vec<VEC> flat_walk(const SH& s, int run, int last, int32_t q, int32_t stop, int32_t e0,
+                                              const MaskedRows<VEC, OFF32>& X, bool k_ok, AHEAD&& ahead, DONE&& done)
 {
     constexpr int D = kFlatBatch;
-    sum.zero();
+    SUM all;
+    all.zero();
     auto end_of = [&](int r) {
         const int32_t e = s.ptr[r + 1 <= last ? r + 1 : last] - e0;
         return e < stop ? e : stop;
@@ -206,13 +293,13 @@ __device__ __forceinline__ void flat_walk(const SH& s, Vec<VEC>& sum, int run, i
         } else {
             q += D;
         }
-#pragma unroll
-        for (int u = 0; u < D; ++u) sum.fma(e[u].val, b[u]);
-        if (ends) {
-            done(now);
-            if (run < last) sum.zero();
+        all.add(flat_dot<VEC>(e, b));
+        if (ends && run < last) {
+            done(now, all.total());
+            all.zero();
         }
     } while (run < last);
+    return all.total();
 }
 
 // What teams have of runs that began in front of them.
@@ -280,6 +367,28 @@ __device__ __forceinline__ bool add_heads(Vec<VEC>& sum, const FlatHeads<VEC>& s
         }
     }
     single(teams);
+    return done;
+}
+
+// The same with two chains that take turns, for what was a tree.
+template <int VEC, bool BATCHES>
+__device__ __forceinline__ bool add_heads_in_chains(Vec<VEC>& sum, const FlatHeads<VEC>& s, int from, int teams, int lanes, int chunk)
+{
+    constexpr int T = FlatHeads<VEC>::kTeams;
+    FlatChains<VEC> all;
+    all.zero();
+    all.add(sum);
+    int t = from;
+    bool done = false;
+#pragma unroll 1
+    while (t < teams && !done) {
+        const bool eight = BATCHES && t % T == 0 && t + T <= teams && s.batch_ended[t / T] == 0;
+        const Vec<VEC> other = eight ? s.batch[t / T * lanes + chunk] : s.head[t * lanes + chunk];
+        done = !eight && s.ended[t] != 0;
+        all.add(other);
+        t += eight ? T : 1;
+    }
+    sum = all.total();
     return done;
 }
 

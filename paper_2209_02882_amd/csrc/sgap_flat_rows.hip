@@ -1,6 +1,6 @@
 // Row-split schedule, serial strategy, short rows: teams of lanes go through consecutive rows each at its own pace
 // (sgap_flat.hpp).  A workgroup owns a block of consecutive rows and takes them in pieces (one, as a rule); every row has one
-// owner and one plain store, and its entries are added up one after the other.
+// owner and one plain store.
 //
 // Bound by the gathers from beyond the L2s where B is large (2,000,000 rows of 1 to 16 entries, N = 32, a B of 8.4 MB: 1.6 GB
 // at 7.5 TB/s), else by the address units.  us, a lane group per row that meets the others of its wavefront after each
@@ -104,13 +104,13 @@ __global__ __launch_bounds__(kBlock) void flat_rows_kernel(SpmmArgs a, int lanes
                 const Columns c(p, k0, a.N, teams);
                 float* const C = a.C + r0 * a.N + c.first;
                 const uint32_t N = (uint32_t)a.N;
-                auto store = [&](uint32_t row, const Vec<VEC>& sum) { store_vec_stream<VEC>(C + (uint64_t)row * N, sum); };
+                auto store = [&](int row, const Vec<VEC>& sum) { store_vec_stream<VEC>(C + (uint64_t)(uint32_t)row * N, sum); };
                 const int first = c.ok ? s.start[p.team] : 0, last = c.ok ? s.start[p.team + 1] : 0;
                 if (first < last) {
                     const MaskedRows<VEC, OFF32> B(a.B, a.N, c.first);
-                    Vec<VEC> sum;
-                    flat_walk<VEC, OFF32>(s, sum, first, last, s.ptr[first] - e0, 0x7fffffff, e0, B, true, [](int, bool, bool) {},
-                                          [&](int row) { store((uint32_t)row, sum); });
+                    const Vec<VEC> sum = flat_walk<VEC, OFF32, FlatChain<VEC>>(s, first, last, s.ptr[first] - e0, 0x7fffffff, e0, B, true,
+                                                                  [](int, bool, bool) {}, store);
+                    store(last - 1, sum);
                 }
             }
             r0 += n;

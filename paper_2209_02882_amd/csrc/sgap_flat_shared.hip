@@ -43,7 +43,7 @@ void flat_shared_rows_kernel(SpmmArgs a, int lanes, int block_rows, int64_t bloc
 {
     __shared__ FsShared sh;
     auto& s = sh.flat;
-    if ((int)blockIdx.x < plan.walk_from) {
+    if (__builtin_expect((int)blockIdx.x < plan.walk_from, 1)) {  // (said to come first: a register less is held meanwhile by the others)
         if ((int)blockIdx.x < plan.finders) find_rows<4, OFF32, kFsDepth>(a, plan, 0x7fffffff, s.entry, s.ptr, sh.mask, kBlock);
         return;
     }
@@ -134,9 +134,8 @@ void flat_shared_rows_kernel(SpmmArgs a, int lanes, int block_rows, int64_t bloc
         auto store = [&](uint32_t row, const Vec<4>& sum) {
             if (c.ok) store_vec_stream<4>(C + (uint64_t)row * (uint32_t)a.N, sum);
         };
-        Vec<4> open;
-        open.zero();
-        int open_row = -1;  // the row that begins among this team's entries and goes on behind them
+        Vec<4> sum;         // of the last row that this team has entries of
+        int open_row = -1;  // that row, where it begins among them and goes on behind them
         if (p.team < teams) {
             const uint32_t from = s.start[p.team], to = s.start[p.team + 1];
             const int first = from & 0xffff, finished = to & 0xffff;  // rows before `finished` end here
@@ -147,23 +146,24 @@ void flat_shared_rows_kernel(SpmmArgs a, int lanes, int block_rows, int64_t bloc
                 const MaskedRows<4, OFF32> B(a.B, a.N, c.first);
                 bool whole = (int)(from >> 16) == s.ptr[first] - e0 && !(first == 0 && comes_in);
                 const int ends = cut && finished == n ? n - 1 : finished;
-                Vec<4> sum;
-                flat_walk<4, OFF32>(s, sum, first, last, from >> 16, to >> 16, e0, B, c.ok, [](int, bool, bool) {},
-                                      [&](int row) {
-                                          const bool is_end = row < ends;
-                                          if (whole && is_end) {
-                                              if (row != hole_row) store((uint32_t)row, sum);
-                                          } else if (whole) {
-                                              open = sum;
-                                              open_row = row;
-                                          } else {
-                                              sh.heads.head[p.tid] = sum;
-                                              ended = is_end;
-                                          }
-                                          whole = true;
-                                      });
+                auto done = [&](int row, const Vec<4>& of_row) {
+                    const bool is_end = row < ends;
+                    if (whole && is_end) {
+                        if (row != hole_row) store((uint32_t)row, of_row);
+                    } else if (whole) {
+                        open_row = row;
+                    } else {
+                        sh.heads.head[p.tid] = of_row;
+                        ended = is_end;
+                    }
+                    whole = true;
+                };
+                sum = flat_walk<4, OFF32, FlatChains<4>>(s, first, last, from >> 16, to >> 16, e0, B, true, [](int, bool, bool) {}, done);
+                done(last - 1, sum);
             } else {
-                sh.heads.head[p.tid] = open;
+                float none = 0.0f;
+                asm volatile("" : "+v"(none));  // (four zeros would be held, or kept in memory, from the kernel's beginning on)
+                sh.heads.head[p.tid] = {{none, none, none, none}};
             }
             sh.heads.ended[p.team] = ended ? 1 : 0;
         }
@@ -175,12 +175,12 @@ void flat_shared_rows_kernel(SpmmArgs a, int lanes, int block_rows, int64_t bloc
             for (int round = 0; round < 2; ++round) {
                 if (round == 1) {
                     if (!comes_in || p.team != 0) continue;
-                    open = sh.carry[turn][p.chunk];
+                    sum = sh.carry[turn][p.chunk];
                     open_row = 0;
                 }
                 if (open_row < 0) continue;
-                if (add_heads<4, true>(open, sh.heads, round == 1 ? 0 : p.team + 1, teams, lanes, p.chunk)) store((uint32_t)open_row, open);
-                else sh.carry[turn ^ 1][p.chunk] = open;
+                if (add_heads_in_chains<4, true>(sum, sh.heads, round == 1 ? 0 : p.team + 1, teams, lanes, p.chunk)) store((uint32_t)open_row, sum);
+                else sh.carry[turn ^ 1][p.chunk] = sum;
             }
         }
         r0 += n - (cut ? 1 : 0);

@@ -198,7 +198,8 @@ __device__ __forceinline__ void mttkrp_block(const MttkrpArgs& a, MfShared<VEC>&
                 __device__ __forceinline__ bool open() const { return last > finished && finished >= begun; }  // the last one begins here and goes on behind
             };
             Vec<VEC> sum, head, t, x;  // of the slice at hand; of one that began in front; of the fiber; X1's row
-            sum.zero();
+            std::conditional_t<SHARED_SLICES, FlatChain<VEC>, FlatFours<VEC>> fibers;  // of the slice at hand, while it is walked through
+            fibers.zero();
             head.zero();
             int slice = 0;
             int32_t slice_end = 0;
@@ -212,35 +213,36 @@ __device__ __forceinline__ void mttkrp_block(const MttkrpArgs& a, MfShared<VEC>&
                     slice = last_row_at_or_before(sh.fp, 0, slices - 1, f0 + m.first);
                     whole = sh.fp[slice] == f0 + m.first && m.begun == m.first;
                     slice_end = sh.fp[slice + 1] - f0;
-                    flat_walk<VEC, OFF32>(
-                        s, t, m.first, m.last, m.from, m.to, e0, x2, c.ok,
-                        // (a stored fiber without entries has no part in a tile, as with every other kernel whose unit of work is the
-                        // entry: whether the tile takes it up depends on where others end, and X1 may be infinite there)
-                        [&](int f, bool ends, bool any) { x = x1.load(sh.fk[f], ends && c.ok && (any || !SHARED_SLICES)); },
-                        [&](int f) {
-                            if (!SHARED_SLICES && f < m.begun) {
-                                sh.heads.head[p.tid] = t;  // of a fiber that began in front
-                                sh.heads.ended[p.team] = f < m.finished ? 1 : 0;
-                            } else if (SHARED_SLICES || f < m.finished) {
-#pragma unroll
-                                for (int i = 0; i < VEC; ++i) sum.v[i] = __builtin_fmaf(x.v[i], t.v[i], sum.v[i]);
-                            }
-                            if (f + 1 != slice_end || f == m.finished) return;
-                            if (whole) {
-                                store(slice, c, sum);
-                            } else if (SHARED_SLICES || f >= m.begun) {  // (else the team that has the fiber's beginning closes the slice)
-                                head = sum;
-                                head_ends = true;
-                            }
-                            sum.zero();
-                            whole = true;
-                            if (f + 1 < m.last) {
-                                do slice_end = sh.fp[++slice + 1] - f0;
-                                while (slice_end == f + 1);
-                            }
-                        });
+                    auto done = [&](int f, const Vec<VEC>& of_fiber) {
+                        if (!SHARED_SLICES && f < m.begun) {
+                            sh.heads.head[p.tid] = of_fiber;  // of a fiber that began in front
+                            sh.heads.ended[p.team] = f < m.finished ? 1 : 0;
+                        } else if (SHARED_SLICES || f < m.finished) {
+                            fibers.add_product(x, of_fiber);
+                        }
+                        if (f + 1 != slice_end || f == m.finished) return;
+                        sum = fibers.total();
+                        if (whole) {
+                            store(slice, c, sum);
+                        } else if (SHARED_SLICES || f >= m.begun) {  // (else the team that has the fiber's beginning closes the slice)
+                            head = sum;
+                            head_ends = true;
+                        }
+                        fibers.zero();
+                        whole = true;
+                        if (f + 1 < m.last) {
+                            do slice_end = sh.fp[++slice + 1] - f0;
+                            while (slice_end == f + 1);
+                        }
+                    };
+                    // (a stored fiber without entries has no part in a tile, as with every other kernel whose unit of work is the
+                    // entry: whether the tile takes it up depends on where others end, and X1 may be infinite there)
+                    auto ahead = [&](int f, bool ends, bool any) { x = x1.load(sh.fk[f], ends && c.ok && (any || !SHARED_SLICES)); };
+                    t = flat_walk<VEC, OFF32, FlatChain<VEC>>(s, m.first, m.last, m.from, m.to, e0, x2, c.ok, ahead, done);
+                    done(m.last - 1, t);
                 }
             }
+            sum = fibers.total();
             const FlatPlace p(lanes);
             const Columns c(p, k0, a.J, teams);
             bool goes_on = false;  // the slice that begins in this team's fibers goes on behind them
@@ -272,7 +274,7 @@ __device__ __forceinline__ void mttkrp_block(const MttkrpArgs& a, MfShared<VEC>&
                 batch_heads(sh.heads, teams, lanes, p);
                 __syncthreads();
                 if (open) {
-                    add_heads<VEC, true>(t, sh.heads, p.team + 1, teams, lanes, p.chunk);
+                    add_heads_in_chains<VEC, true>(t, sh.heads, p.team + 1, teams, lanes, p.chunk);
 #pragma unroll
                     for (int i = 0; i < VEC; ++i) sum.v[i] = __builtin_fmaf(x.v[i], t.v[i], sum.v[i]);
                     rest(m.last == slice_end);
@@ -298,7 +300,10 @@ __device__ __forceinline__ void mttkrp_block(const MttkrpArgs& a, MfShared<VEC>&
                     slice = came_in;
                 }
                 if (!goes_on) continue;
-                const bool ended = add_heads<VEC, SHARED_SLICES>(sum, sh.heads, round == 1 ? 0 : p.team + 1, teams, lanes, p.chunk);
+                const int from = round == 1 ? 0 : p.team + 1;
+                bool ended;
+                if constexpr (SHARED_SLICES) ended = add_heads<VEC, true>(sum, sh.heads, from, teams, lanes, p.chunk);
+                else ended = add_heads_in_chains<VEC, false>(sum, sh.heads, from, teams, lanes, p.chunk);
                 if (SHARED_SLICES && (ended ? sh.fp[slice] < f_begin : f0 + n == f_end)) add(slice, p, c, sum);
                 else if (ended) store(slice, c, sum);
                 else sh.carry[turn ^ 1][p.chunk] = sum;

@@ -155,8 +155,9 @@ void nnz_flat_kernel(SpmmArgs a, int lanes, int teams, int tile)
                             ++wi;
                             row_end = s.win[wi + 1 <= n ? wi + 1 : n] - tile_start;
                         }
+                        const Vec<4> batch = flat_dot<4>(e, b);
 #pragma unroll
-                        for (int u = 0; u < D; ++u) sum.fma(e[u].val, b[u]);
+                        for (int i = 0; i < 4; ++i) sum.v[i] += batch.v[i];
                         if (row_done) {
                             if (whole) {
                                 store(s.row[now], sum);
