@@ -834,7 +834,6 @@ int sgap_mttkrp_csf_ex(int64_t I, int64_t K, int64_t L, int64_t J, const int32_t
 
     const int vec = lane_columns(J);
     const bool par = strategy == SGAP_REDUCE_PARALLEL;
-    const int lc = pow2_ceil_capped((J + vec - 1) / vec, 64);
     hipStream_t s = reinterpret_cast<hipStream_t>(stream);
     hipEvent_t ev0 = nullptr, ev1 = nullptr;
     auto mark = [&](hipEvent_t& ev) {
@@ -855,13 +854,17 @@ int sgap_mttkrp_csf_ex(int64_t I, int64_t K, int64_t L, int64_t J, const int32_t
     } else {
         const int xcds = g_xcd_remap == 0 ? 1 : kXcds;
         const MttkrpArgs m{I, K, L, J, fptr, fidx, eptr, eidx, vals, X1, X2, Y};
-        if (par) {
-            // the tuning knob counts the slices of a group of group_size members
-            const int slots = 256 / (group_size * pow2_ceil_capped((J + vec - 1) / vec, 64 / group_size));
-            const int slices = g_rows_per_slot > 0 ? slots * g_rows_per_slot : mttkrp_block_slices(I, nnz_hint, compute_units());
-            err = launch_mttkrp_fibers(m, slices, vec, xcds, s);
-        } else
-            err = launch_mttkrp(m, group_size, lc, vec, xcds, s);
+        if (par && g_rows_per_slot == 0 && mttkrp_fibers_apply(I, J, group_size, nnz_hint)) {
+            err = launch_mttkrp_fibers(m, vec, xcds, compute_units(), nnz_hint, s);
+        } else {
+            const int g = par ? group_size : 1;
+            const int lanes = pow2_ceil_capped((J + vec - 1) / vec, 64 / g);
+            // parallel: about 16 slices per workgroup, enough to pay for bringing a block's slice pointers,
+            // fibers and entries into LDS (more lose occupancy to the LDS copies); serial: group_size slices per lane
+            const int slots = 256 / (g * lanes);
+            const int rows_per_slot = !par ? group_size : g_rows_per_slot > 0 ? g_rows_per_slot : (slots >= 16 ? 1 : 16 / slots);
+            err = launch_mttkrp(m, g, rows_per_slot, par, lanes, vec, xcds, s);
+        }
     }
     if (ev0) {
         mark(ev1);

@@ -325,12 +325,13 @@ hipError_t launch_sddmm_panels(const SpmmArgs& a, const float* X1, float* out, i
 // there are more of those than skip.max_rows)
 hipError_t launch_sddmm_rest(const SpmmArgs& a, const float* X1, float* out, int g, int per_lane, int compute_units,
                              int64_t nnz_hint, const RowSkip& skip, int32_t from_len, hipStream_t stream);
-// MTTKRP on compressed sparse fibers with slices as the unit of work, lc chunk lanes of vec columns each.  Serial strategy:
-// rows_per_slot consecutive slices per lane.
-hipError_t launch_mttkrp(const MttkrpArgs& a, int rows_per_slot, int lc, int vec, int xcds, hipStream_t s);
-// Parallel strategy (sgap_mttkrp_fibers.hip): block_slices slices to a workgroup, by mttkrp_block_slices unless asked for.
-int mttkrp_block_slices(int64_t I, int64_t nnz_hint, int compute_units);
-hipError_t launch_mttkrp_fibers(const MttkrpArgs& a, int block_slices, int vec, int xcds, hipStream_t s);
+// MTTKRP on compressed sparse fibers with slices as the unit of work: g lanes per slice (1 for the serial strategy),
+// rows_per_slot slices per group (consecutive, or interleaved with the other groups' slices), lc chunk lanes of vec columns each.
+hipError_t launch_mttkrp(const MttkrpArgs& a, int g, int rows_per_slot, bool interleave, int lc, int vec, int xcds, hipStream_t s);
+// The parallel strategy by blocks of slices that teams of lanes share (sgap_mttkrp_fibers.hip), and whether that is the
+// kernel (nnz_hint: -1 where there is no count).
+bool mttkrp_fibers_apply(int64_t I, int64_t J, int group, int64_t nnz_hint);
+hipError_t launch_mttkrp_fibers(const MttkrpArgs& a, int vec, int xcds, int compute_units, int64_t nnz_hint, hipStream_t s);
 hipError_t launch_debug_group_seg_reduce(const float* in, const int32_t* span, float* out, int g, int lc,
                                          hipStream_t s);
 // MTTKRP with the stored entries as the unit of work (sgap_mttkrp_nnz.hip): g = lanes per segment group

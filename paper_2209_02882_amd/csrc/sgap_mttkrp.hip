@@ -8,11 +8,17 @@
 // Both are row-split reductions: a slice is produced by exactly one group, so
 // results are written with plain stores and empty slices are written as zeros.
 //
-// This is the serial strategy: one lane per slice and column chunk, `group_size`
-// consecutive slices per lane ({<g row, c col>, 1}, Section 6.1); the parallel
-// one is sgap_mttkrp_fibers.hip.
-// Lane layout:  thread = slot*LC + chunk over the workgroup; the LC chunk lanes
-// of a slot hold neighbouring column chunks of VEC columns.
+//   parallel  G lanes per slice ({<1/g row, c col>, r} with g = r = G, Section
+//             6.2): member m takes the slice's fibers m, m+G, ...; each member
+//             runs the first-level reduction of its fibers serially and adds
+//             X1[k,:] * t into its own accumulator; because the second level
+//             is linear in t the group tree-sums once per slice, and member 0
+//             stores.  (Where a slice's group has idle members, or waits
+//             for its longest: sgap_mttkrp_fibers.hip.)
+//   serial    one lane per slice and column chunk, `group_size` consecutive
+//             slices per lane ({<g row, c col>, 1}, Section 6.1).
+// Lane layout:  thread = (slot*G + member)*LC + chunk over the workgroup; the
+// LC chunk lanes of a member hold neighbouring column chunks of VEC columns.
 //
 // Compressed fibers put three dependent loads (slice pointer, fiber, entries)
 // before the first row of X2 can be asked for.  A workgroup therefore copies
@@ -23,6 +29,7 @@
 // from memory, fiber by fiber.
 #include "sgap_common.hpp"
 #include "sgap_gather.hpp"
+#include "sgap_lane_ops.hpp"
 
 namespace sgap {
 
@@ -44,29 +51,30 @@ __device__ __forceinline__ int32_t from_chunk_lane(int32_t v, int src)
     else return __shfl(v, src, LC);
 }
 
-// A slice, fibers f_begin <= f < f_end, with
+// One member's share of a slice, fibers f_begin + member, + G, ... < f_end, with
 // every level read from memory: the next fiber's (second index, entry range) is
 // asked for one fiber ahead, the fiber's row of X1 travels with its first
 // entries, and the LC chunk lanes load LC entries with one coalesced load and
 // hand the (index, value) pairs round through the LDS crossbar.
-template <int LC, int VEC, bool OFF32>
+template <int G, int LC, int VEC, bool OFF32>
 __device__ __forceinline__ void mttkrp_slice_direct(const MttkrpArgs& a, Vec<VEC>& acc, int32_t f_begin, int32_t f_end,
-                                                    int chunk, int64_t k, bool k_ok, const BRow<OFF32>& x2row)
+                                                    int member, int chunk, int64_t k, bool k_ok,
+                                                    const BRow<OFF32>& x2row)
 {
     constexpr int D = kMttkrpDepth;
-    int32_t f = f_begin;
+    int32_t f = f_begin + member;
     int32_t next_k = 0, next_begin = 0, next_end = 0;
     if (f < f_end) {
         next_k = a.fidx[f];
         next_begin = a.eptr[f];
         next_end = a.eptr[f + 1];
     }
-    for (; f < f_end; ++f) {
+    for (; f < f_end; f += G) {
         const int32_t fiber_k = next_k, e_begin = next_begin, e_end = next_end;
-        if (f + 1 < f_end) {
-            next_k = a.fidx[f + 1];
-            next_begin = a.eptr[f + 1];
-            next_end = a.eptr[f + 2];
+        if (f + G < f_end) {
+            next_k = a.fidx[f + G];
+            next_begin = a.eptr[f + G];
+            next_end = a.eptr[f + G + 1];
         }
         Vec<VEC> x1;
         x1.zero();
@@ -74,7 +82,7 @@ __device__ __forceinline__ void mttkrp_slice_direct(const MttkrpArgs& a, Vec<VEC
         Vec<VEC> t;
         t.zero();
         for (int32_t base = e_begin; base < e_end; base += LC) {
-            // the LC chunk lanes are all here: one entry each
+            // the LC chunk lanes of this member are all here: one entry each
             int32_t my_idx = 0, my_val = 0;
             if (base + chunk < e_end) {
                 my_idx = load_stream(a.eidx + base + chunk);
@@ -106,16 +114,18 @@ __device__ __forceinline__ void mttkrp_slice_direct(const MttkrpArgs& a, Vec<VEC
     }
 }
 
-template <int LC, int VEC, bool OFF32>
-__global__ __launch_bounds__(kBlock) void mttkrp_kernel(MttkrpArgs a, int rows_per_slot, int64_t row_blocks,
-                                                        int64_t blocks_per_xcd, int xcds)
+template <int G, int LC, int VEC, bool OFF32>
+__global__ __launch_bounds__(kBlock) void mttkrp_kernel(MttkrpArgs a, int rows_per_slot, int interleave,
+                                                        int64_t row_blocks, int64_t blocks_per_xcd, int xcds)
 {
     __shared__ StagedEntry s_A[kMtEntries];
     __shared__ int32_t s_fk[kMtFibers];
     __shared__ int32_t s_ep[kMtFibers + 1];
     __shared__ int32_t s_fp[kMtRows + 1];
-    constexpr int SLOTS = kBlock / LC;
-    const int slot = threadIdx.x / LC;
+    constexpr int SPAN = G * LC;
+    constexpr int SLOTS = kBlock / SPAN;
+    const int slot = threadIdx.x / SPAN;
+    const int member = (threadIdx.x / LC) % G;
     const int chunk = threadIdx.x % LC;
 
     // workgroup b runs on die b % xcds: every die gets one contiguous run of row blocks
@@ -162,13 +172,13 @@ __global__ __launch_bounds__(kBlock) void mttkrp_kernel(MttkrpArgs a, int rows_p
         const GlobalRows<VEC, OFF32> x2rows(a.X2, a.J, k_lane);
         for (int r = 0; r < rows_per_slot; ++r) {
             // the lanes of a slot share `row`, so whole slots leave together
-            const int64_t row = row_first + (int64_t)slot * rows_per_slot + r;
+            const int64_t row = row_first + (interleave ? slot + (int64_t)r * SLOTS : (int64_t)slot * rows_per_slot + r);
             if (row >= row_last) break;
             Vec<VEC> acc;
             acc.zero();
             if (staged) {
                 const int32_t f_end = s_fp[row - row_first + 1] - f0;
-                for (int32_t f = s_fp[row - row_first] - f0; f < f_end; ++f) {
+                for (int32_t f = s_fp[row - row_first] - f0 + member; f < f_end; f += G) {
                     // the fiber's row of X1 is in flight while its entries are multiplied out
                     Vec<VEC> x1, t;
                     x1.zero();
@@ -182,9 +192,13 @@ __global__ __launch_bounds__(kBlock) void mttkrp_kernel(MttkrpArgs a, int rows_p
                     for (int i = 0; i < VEC; ++i) acc.v[i] = __builtin_fmaf(x1.v[i], t.v[i], acc.v[i]);
                 }
             } else {
-                mttkrp_slice_direct<LC, VEC, OFF32>(a, acc, a.fptr[row], a.fptr[row + 1], chunk, k_lane, k_ok, x2row);
+                mttkrp_slice_direct<G, LC, VEC, OFF32>(a, acc, a.fptr[row], a.fptr[row + 1], member, chunk, k_lane, k_ok,
+                                                       x2row);
             }
-            if (k_ok) store_vec_stream<VEC>(a.Y + row * a.J + k_lane, acc);
+            // members without fibers contributed +0; the lanes of a slot meet here
+#pragma unroll
+            for (int i = 0; i < VEC; ++i) acc.v[i] = group_tree_sum<G, LC>(acc.v[i]);
+            if (member == 0 && k_ok) store_vec_stream<VEC>(a.Y + row * a.J + k_lane, acc);
         }
     }
 }
@@ -193,36 +207,38 @@ namespace {
 
 struct LaunchMttkrp {
     const MttkrpArgs& a;
-    int rows_per_slot, xcds;
+    int rows_per_slot, interleave, xcds;
     bool off32;
     hipStream_t s;
     template <int G, int LC, int VEC>
     void operator()() const
     {
-        constexpr int slots = kBlock / LC;
+        constexpr int slots = kBlock / (G * LC);
         const int64_t rows_per_block = (int64_t)slots * rows_per_slot;
         const int64_t row_blocks = (a.I + rows_per_block - 1) / rows_per_block;
         const int64_t blocks_per_xcd = (row_blocks + xcds - 1) / xcds;
         const unsigned grid = (unsigned)(blocks_per_xcd * xcds);
         if (off32)
-            hipLaunchKernelGGL((mttkrp_kernel<LC, VEC, true>), dim3(grid), dim3(kBlock), 0, s, a, rows_per_slot, row_blocks,
-                               blocks_per_xcd, xcds);
+            hipLaunchKernelGGL((mttkrp_kernel<G, LC, VEC, true>), dim3(grid), dim3(kBlock), 0, s, a, rows_per_slot,
+                               interleave, row_blocks, blocks_per_xcd, xcds);
         else
-            hipLaunchKernelGGL((mttkrp_kernel<LC, VEC, false>), dim3(grid), dim3(kBlock), 0, s, a, rows_per_slot, row_blocks,
-                               blocks_per_xcd, xcds);
+            hipLaunchKernelGGL((mttkrp_kernel<G, LC, VEC, false>), dim3(grid), dim3(kBlock), 0, s, a, rows_per_slot,
+                               interleave, row_blocks, blocks_per_xcd, xcds);
     }
 };
 
 }  // namespace
 
-// rows_per_slot = consecutive slices of a lane, lc = chunk lanes, vec = columns per lane.
-hipError_t launch_mttkrp(const MttkrpArgs& a, int rows_per_slot, int lc, int vec, int xcds, hipStream_t s)
+// g = lanes per slice (1 for the serial strategy), rows_per_slot = slices a
+// group works through (consecutive ones, or every slots-th slice of the block
+// when `interleave` is set), lc = chunk lanes, vec = columns per lane.
+hipError_t launch_mttkrp(const MttkrpArgs& a, int g, int rows_per_slot, bool interleave, int lc, int vec, int xcds, hipStream_t s)
 {
     const bool off32 = offsets_fit_32(a.L, a.J);
-    const int64_t rows_per_block = (int64_t)(kBlock / lc) * rows_per_slot;
+    const int64_t rows_per_block = (int64_t)(kBlock / (g * lc)) * rows_per_slot;
     if ((a.I + rows_per_block - 1) / rows_per_block + xcds > 0x7ffffff0LL) return hipErrorInvalidValue;
-    LaunchMttkrp f{a, rows_per_slot, xcds, off32, s};
-    if (!dispatch_lc<1>(lc, vec, f)) return hipErrorInvalidValue;
+    LaunchMttkrp f{a, rows_per_slot, interleave ? 1 : 0, xcds, off32, s};
+    if (!dispatch_group(g, lc, vec, f)) return hipErrorInvalidValue;
     return hipGetLastError();
 }
 

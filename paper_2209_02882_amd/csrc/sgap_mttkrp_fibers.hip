@@ -11,11 +11,10 @@
 //
 // Bound by the gathers: of two factors of 8.4 MB 1.7 GB come from beyond the L2s, at 7.2 TB/s; small tensors by the chain
 // of loads that a block is (pointers, fibers, entries, then a team's rows of X2).  With a group of lanes per slice, members
-// m, m + G, ... of which took the slice's fibers (the form before), a third of the members had no fiber, each waited for the
-// longest of its wavefront's, and every slice ended in a tree sum.  us, group per slice / this, J = 32 unless said, slices x
-// fibers of a slice: 262,144 x 8 268 / 239, with factors of 256 KB 235 / 164; 227,077 x 4, J = 16 104 / 78; 133,470 x 6
-// 123 / 95; 43,825 x 7 62 to 76 / 41; 21,755 x 8 39 to 49 / 25; 15,510 x 6, J = 16 23 to 27 / 15; 100,000 x 8, J = 64
-// 254 / 230; fibers of 24 entries, 50,000 x 2 84 / 34; 100,000 x 4, one fiber in a hundred of 500 entries 609 / 74.
+// m, m + G, ... of which take the slice's fibers (mttkrp_kernel), a third of the members have no fiber, each waits for the
+// longest of its wavefront's, and every slice ends in a tree sum.  us, group per slice (G = 8) / this, slices x fibers of a slice x
+// entries of a fiber in the mean: 262,144 x 8 x 8 J = 32 262 / 234, J = 16 196 / 160; 100,000 x 4 x 4 55.1 / 44.1, J = 64 98 / 80; 10,000 x 8 x 8 36.3 /
+// 19.5; 100,000 x 2 x 2 31.9 / 18.8; 20,000 x 20 x 4 70.6 / 45.6; 3,000 x 60 x 8 292 / 52.
 #include "sgap_common.hpp"
 #include "sgap_flat.hpp"
 #include "sgap_nnz_common.hpp"
@@ -385,7 +384,7 @@ __global__ __launch_bounds__(kBlock) void mttkrp_tiles_kernel(MttkrpArgs a, int 
 // 5 fibers, J = 24, takes 34.8 us in one round of 964 blocks and 43.1 in 1,286.  The larger a block the better, up to what
 // leaves few blocks in more than one piece; with many rounds those count more than the rounds (2,600 entries a block / 2,000:
 // 76,491 slices of 4 fibers, J = 32, two rounds 42.0 us / 46.2, 262,144 of 8, seven rounds or nine, 264 to 272 / 263).
-int mttkrp_block_slices(int64_t I, int64_t nnz_hint, int compute_units)
+static int mttkrp_block_slices(int64_t I, int64_t nnz_hint, int compute_units)
 {
     if (nnz_hint <= 0) return kMfBlock;
     const int64_t resident = (int64_t)kMfResident * compute_units;
@@ -395,9 +394,29 @@ int mttkrp_block_slices(int64_t I, int64_t nnz_hint, int compute_units)
     return slices < kMfSlices ? (int)slices : kMfSlices;
 }
 
-hipError_t launch_mttkrp_fibers(const MttkrpArgs& a, int block_slices, int vec, int xcds, hipStream_t s)
+// Where this is the kernel.  Teams of a lane or two share a slice that a group of lanes has by itself, and small tensors are over
+// when a block has been dealt out; without a count of the entries blocks are small.  The fewer columns, the longer the slices
+// have to be for the groups' idle and waiting members to cost more than that.  us, group per slice / this, G = 8 unless said,
+// slices x fibers of a slice x entries of a fiber in the mean:
+//   J = 100  100,000 x 1.2 x 8, G = 2 77 / 81, J = 64 44 / 42
+//   J = 64   100,000 x 2 x 2 52.2 / 31.1, no count 52.3 / 56.6; 1,000 x 4 x 4 18.6 / 8.8
+//   J = 32   30,000 x 2 x 2, G = 2 9.9 / 10.2; 1,000 x 4 x 4 10.5 / 10.2, J = 24 10.6 / 11.3; 10,000 x 4 x 4 13.4 / 11.1; no count, 100,000 x 2 x 2
+//            32.0 / 45.8
+//   J = 16   10,000 x 4 x 4 9.5 / 9.6; 100,000 x 2 x 2 22.0 / 14.3; 30,000 x 2 x 2, G = 2 7.2 / 8.9
+//   J = 8    100,000 x 4 x 4 28.9 / 29.4, G = 2 30.3 / 32.1; 20,000 x 20 x 4 62 / 40, G = 32 35.2 / 36.0; 10,000 x 8 x 8, G = 32 13.0 / 14.4
+//   J = 4    100,000 x 4 x 4 18.5 / 31.1; 20,000 x 20 x 4 59 / 51, G = 32 25 / 43; 3,000 x 60 x 8 284 / 64; 10,000 x 8 x 8, G = 32 9.6 / 19.0
+bool mttkrp_fibers_apply(int64_t I, int64_t J, int group, int64_t nnz_hint)
 {
-    if (block_slices > kMfSlices) block_slices = kMfSlices;
+    if (nnz_hint <= 0) return J >= 80;
+    if (J >= 48) return group > 2 || nnz_hint >= 12 * I;
+    if (J >= 20) return nnz_hint >= 150'000 || (J >= 32 && nnz_hint >= 12 * I);
+    if (J >= 12) return nnz_hint >= 300'000;
+    return nnz_hint >= 400'000 && nnz_hint / I >= 10 * group;
+}
+
+hipError_t launch_mttkrp_fibers(const MttkrpArgs& a, int vec, int xcds, int compute_units, int64_t nnz_hint, hipStream_t s)
+{
+    const int block_slices = mttkrp_block_slices(a.I, nnz_hint, compute_units);
     const int64_t blocks = (a.I + block_slices - 1) / block_slices;
     if (blocks + xcds > 0x7ffffff0LL) return hipErrorInvalidValue;
     const int64_t blocks_per_xcd = (blocks + xcds - 1) / xcds;

@@ -342,7 +342,7 @@ struct LaunchSerial {
 // 14.6 / 17.4, 100,000 95 / 96.
 bool mttkrp_serial_applies(int64_t J, int64_t nnz_hint)
 {
-    return J <= kMsColumns && nnz_hint > 0 && nnz_hint < (J < 4 ? 2000000 / J : 500000);
+    return J <= kMsColumns && nnz_hint > 0 && nnz_hint < (J < 4 ? 2000000 / J : J < 8 ? 700000 : 500000);
 }
 
 hipError_t launch_mttkrp_serial(const MttkrpArgs& a, int lc, int vec, int compute_units, int64_t nnz_hint,
