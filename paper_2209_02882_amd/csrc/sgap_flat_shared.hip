@@ -44,7 +44,8 @@ void flat_shared_rows_kernel(SpmmArgs a, int lanes, int block_rows, int64_t bloc
     __shared__ FsShared sh;
     auto& s = sh.flat;
     if (__builtin_expect((int)blockIdx.x < plan.walk_from, 1)) {  // (said to come first: a register less is held meanwhile by the others)
-        if ((int)blockIdx.x < plan.finders) find_rows<4, OFF32, kFsDepth>(a, plan, 0x7fffffff, s.entry, s.ptr, sh.mask, kBlock);
+        auto is_shared = [&](int64_t, int32_t len) { return len >= plan.share_from; };
+        if ((int)blockIdx.x < plan.finders) find_rows<4, OFF32, kFsDepth, true>(a, plan, is_shared, s.entry, s.ptr, sh.mask, kBlock);
         return;
     }
     const uint32_t wg = blockIdx.x - plan.walk_from;

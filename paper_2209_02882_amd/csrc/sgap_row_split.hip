@@ -33,7 +33,15 @@ constexpr int kShareMin = 256;    // the shortest row that a whole workgroup tak
 constexpr int kFinderRows = 64;   // a finder looks at no fewer rows (32 cost matrices without long rows: 10,000 rows of 16
                                   // entries, N = 32, G = 8 6.3 -> 6.7 us)
 constexpr int kFinderEntries = 2048;  // ... unless most rows are long, and then no more entries: 2,000 rows of 400, N = 37, G = 16 330 us by
-                                      // 32 finders, 31 by 400
+                                      // 32 finders, 31 by 400 (4,000 rows of 400, N = 32, G = 8, none of which is long enough: 15.1 by 64, 18.9 by 800)
+constexpr int kSmallShare = 512;  // where groups have four members, or several passes, ...
+constexpr int kFewRows = 8192;    // ... and so few rows, the half of that in the mean is enough (20,000 rows of 200, N = 8, G = 4 29 us, by 2,048 finders 38)
+// Few entries leave the chip to the rows that workgroups take together; with more the others want the wavefront per SIMD that
+// those rows' registers cost.  us, without / with: power laws, G = 8, 3,000 rows, N = 64 8.7 / 7.0; 10,000, N = 24 10.2 / 8.8, N = 64 16.8 / 12.7;
+// N = 100 31 / 25; 20,000, N = 64 31.3 / 20.9, N = 32 15.6 / 12.1, but N = 16, G = 16 10.0 / 10.7; 60,000 rows of 21, N = 32 22.1 / 25.6, N = 48 32.2 /
+// 34.9; 15,000 of 16, N = 40 8.8 / 9.2, N = 32 8.0 / 8.1; 5,000 of 16, N = 100 7.0 / 7.3; 1,024 of 10, N = 32 3.05 / 3.12.
+constexpr int64_t kDeepFewest = 30'000, kDeepMost = 330'000, kDeepMostNarrow = 200'000;  // entries; up to 16 columns
+constexpr int64_t kDeepColumns = 64;
 constexpr int kFindersPerCu = 8;  // as many workgroups as are resident
 constexpr int kTeamRows = 256;    // a team of two looks through no more rows: a look of its workgroups' threads
 constexpr int kTeamsPerCu = 4;    // no teams where there are more finders: they come in rounds then
@@ -72,10 +80,11 @@ RowSplitGrid plan_row_split_grid(int g, int passes, int64_t M, int64_t items, in
     const int32_t share_from = share_rows_from(g, passes);
     if (g > 1 && (nnz_hint < 0 || nnz_hint >= share_from)) {
         const int64_t most = (int64_t)kFindersPerCu * compute_units;
-        // where most rows are long, as many rows as hold kFinderEntries
+        // where most rows are long (few rows, small groups: where many are), as many rows as hold kFinderEntries
         const double mean = (double)nnz_hint / (double)M;
         int64_t rows = kFinderRows;
-        if (2.0 * mean >= (double)share_from && kFinderEntries / mean < (double)kFinderRows) rows = (int64_t)(kFinderEntries / mean);
+        const bool many = mean >= (double)share_from || (share_from <= kSmallShare && M <= kFewRows && 2.0 * mean >= (double)share_from);
+        if (many && kFinderEntries / mean < (double)kFinderRows) rows = (int64_t)(kFinderEntries / mean);
         if (rows < (int64_t)FinderDeal::kUnit) rows = FinderDeal::kUnit;
         int64_t finders = (M + rows - 1) / rows < most ? (M + rows - 1) / rows : most;
         if (resident > 0 && finders > walkers) finders = walkers;
@@ -103,6 +112,7 @@ hipError_t launch_row_split(const SpmmArgs& a, int g, int lc, int vec, int rows_
 {
     row_split_detail::Launch<false> f{a, rows_per_slot, interleave ? 1 : 0, tile_cols, xcds, compute_units,
                                       offsets_fit_32(a), persistent, 0, block, s, nnz_hint, mean_row <= kShortRowMean};
+    f.deep = a.N <= kDeepColumns && nnz_hint >= kDeepFewest && nnz_hint <= (a.N <= 16 ? kDeepMostNarrow : kDeepMost);
     if (!dispatch_group(g, lc, vec, f)) return hipErrorInvalidValue;
     return hipGetLastError();
 }

@@ -45,11 +45,11 @@ struct SharedLanes {
 // memory whatever is in it, so lanes that hold no columns cost in proportion: with the next power of two of chunk lanes, 16
 // members instead of 25 at N = 37, a row of 4,096 entries took 32 rounds instead of 21.  Power laws, four matrices each, us,
 // power of two / as many as the columns take: 50,021 rows, N = 37 40.2 to 62.4 / 35.2 to 50.3; 20,396 rows, N = 37 34.9 to
-// 40.6 / 29.0 to 33.9; 53,897 rows, N = 51 28.9 to 47.2 / 27.6 to 42.5; columns that fill a power of two within 2 %.  Entries past
-// the end are masked loads (MaskedRows) of places that exist, not branches: 18,205 rows, N = 27 17.2 / 13.5; 10,000, N = 24
-// 13.6 / 9.6; 25,000, N = 48 31.4 / 24.7.
+// 40.6 / 29.0 to 33.9; 53,897 rows, N = 51 28.9 to 47.2 / 27.6 to 42.5; columns that fill a power of two within 2 %.
+// MASKED: entries past the end are masked loads (MaskedRows) of places that exist, not branches (18,205 rows, N = 27 17.2 / 13.5;
+// 10,000, N = 24 13.6 / 9.6); where registers leave six wavefronts per SIMD branches are better (R-MAT, 65,536 rows, N = 64 106 / 112).
 // s_A and s_part may be the same memory.  Block-uniform; barriers inside.
-template <int VEC, bool OFF32, int DEPTH>
+template <int VEC, bool OFF32, int DEPTH, bool MASKED>
 __device__ __forceinline__ void shared_row(const SpmmArgs& a, int64_t row, uint32_t p_begin, uint32_t p_end,
                                            const SharedLanes& l, StagedEntry* __restrict__ s_A, int block)
 {
@@ -63,7 +63,7 @@ __device__ __forceinline__ void shared_row(const SpmmArgs& a, int64_t row, uint3
         const int64_t k = k0 + (int64_t)chunk * VEC;
         const bool k_ok = k < N && member < members;
         const int64_t first = k_ok ? lane_first_col<VEC>(k, N) : 0;
-        const MaskedRows<VEC, OFF32> B(a.B, N, (uint32_t)first);
+        const std::conditional_t<MASKED, MaskedRows<VEC, OFF32>, GlobalRows<VEC, OFF32>> B(a.B, N, (uint32_t)first);
         Vec<VEC> acc;
         acc.zero();
         for (uint32_t base = p_begin; base < p_end; base += kStageCap) {
@@ -73,17 +73,33 @@ __device__ __forceinline__ void shared_row(const SpmmArgs& a, int64_t row, uint3
             __syncthreads();
             for (uint32_t q = member; k_ok && q < cnt; q += D * members) {
                 Vec<VEC> b[D];
+                if constexpr (MASKED) {
 #pragma unroll
-                for (int u = 0; u < D; ++u) {
-                    const uint32_t at = q + u * members;
-                    b[u] = B.load(s_A[at < cnt ? at : q].col, at < cnt);
-                }
-                asm volatile("" ::: "memory");  // (the values are read meanwhile: registers)
+                    for (int u = 0; u < D; ++u) {
+                        const uint32_t at = q + u * members;
+                        b[u] = B.load(s_A[at < cnt ? at : q].col, at < cnt);
+                    }
+                    asm volatile("" ::: "memory");  // (the values are read meanwhile: registers)
 #pragma unroll
-                for (int u = 0; u < D; ++u) {
-                    const uint32_t at = q + u * members;
-                    const float val = s_A[at < cnt ? at : q].val;
-                    acc.fma(at < cnt ? val : 0.0f, b[u]);
+                    for (int u = 0; u < D; ++u) {
+                        const uint32_t at = q + u * members;
+                        const float val = s_A[at < cnt ? at : q].val;
+                        acc.fma(at < cnt ? val : 0.0f, b[u]);
+                    }
+                } else {
+                    StagedEntry e[D];
+#pragma unroll
+                    for (int u = 0; u < D; ++u) {
+                        e[u] = {0, 0.0f};
+                        if (q + u * members < cnt) e[u] = s_A[q + u * members];
+                    }
+#pragma unroll
+                    for (int u = 0; u < D; ++u) {
+                        b[u].zero();
+                        if (q + u * members < cnt) b[u] = B.load(e[u].col);
+                    }
+#pragma unroll
+                    for (int u = 0; u < D; ++u) acc.fma(e[u].val, b[u]);
                 }
             }
         }
@@ -122,10 +138,10 @@ __device__ __forceinline__ void shared_row(const SpmmArgs& a, int64_t row, uint3
     }
 }
 
-// A finder's share of the rows (plan_row_split_grid): those of at least share_from entries and fewer than skip_from, one after the
-// other.  s_rp and s_mask: places for kRowCap rows and for a mask of every wavefront.
-template <int VEC, bool OFF32, int DEPTH>
-__device__ __forceinline__ void find_rows(const SpmmArgs& a, const RowSplitGrid& plan, int32_t skip_from, StagedEntry* __restrict__ s_A,
+// A finder's share of the rows (plan_row_split_grid): those that is_shared(row, entries) says, one after the other.  s_rp and
+// s_mask: places for kRowCap rows and for a mask of every wavefront.
+template <int VEC, bool OFF32, int DEPTH, bool MASKED, typename SHARED>
+__device__ __forceinline__ void find_rows(const SpmmArgs& a, const RowSplitGrid& plan, SHARED&& is_shared, StagedEntry* __restrict__ s_A,
                                           int32_t* __restrict__ s_rp, unsigned long long* __restrict__ s_mask, int block)
 {
     const int64_t N = a.N;
@@ -142,11 +158,7 @@ __device__ __forceinline__ void find_rows(const SpmmArgs& a, const RowSplitGrid&
             const uint32_t q = q0 + threadIdx.x;
             const int64_t r = plan.deal.row(first + q / UNIT, q % UNIT);
             bool shared = q < look && r < a.M;
-            if (shared) {
-                const int32_t len = a.rowptr[r + 1] - a.rowptr[r];
-                shared = len >= plan.share_from;
-                shared = shared && len < skip_from;
-            }
+            if (shared) shared = is_shared(r, a.rowptr[r + 1] - a.rowptr[r]);
             const unsigned long long mask = __ballot(shared);
             __syncthreads();  // the last rows found, or the last masks, are done with
             if (lane == 0) s_mask[wave] = mask;
@@ -163,7 +175,7 @@ __device__ __forceinline__ void find_rows(const SpmmArgs& a, const RowSplitGrid&
         const int n = (int)((found + (1u << plan.log2_team) - 1u - mine) >> plan.log2_team);
         for (int i = 0; i < n; ++i) {
             const int32_t row = __builtin_amdgcn_readfirstlane(s_rp[i]);
-            shared_row<VEC, OFF32, DEPTH>(a, row, (uint32_t)a.rowptr[row], (uint32_t)a.rowptr[row + 1], lanes, s_A, block);
+            shared_row<VEC, OFF32, DEPTH, MASKED>(a, row, (uint32_t)a.rowptr[row], (uint32_t)a.rowptr[row + 1], lanes, s_A, block);
         }
     }
 }
@@ -176,14 +188,13 @@ __device__ __forceinline__ void find_rows(const SpmmArgs& a, const RowSplitGrid&
 // the walk; the first `finders` workgroups of the grid look for them, a team of them in each share of the rows
 // (FinderDeal), and produce them in turn, one after the other with all their lanes (shared_row).  They start first, so that the longest rows are done while
 // the others are walked: a workgroup that came across one during its walk ended some 40 us behind the rest.
-// Registers: a row that a workgroup takes together wants more than six wavefronts per SIMD leave (10,000 rows, N = 16 9.6 us, with
-// five 8.4); a dozen columns or fewer, and smaller groups, rather the wavefronts (power law, 112,754 rows, N = 8, G = 32 36.8,
-// with five 40.1; 130,000, N = 16, G = 8 31.7 and 34.1).
+// DEEP: the rows that a workgroup takes together have more loads in flight, with registers that leave five wavefronts per SIMD, one
+// less (launch_row_split).
 // The workgroup size (the paper's blockSz, Section 7.2) is the launch's: SLOTS = blockDim.x / (G*LC)
 // groups work side by side on the rows of a row block.
-template <int G, int LC, int VEC, bool OFF32, bool PARTIAL, bool SKIP, int DEPTH>
+template <int G, int LC, int VEC, bool OFF32, bool PARTIAL, bool SKIP, int DEPTH, bool DEEP>
 __global__ __launch_bounds__(kRowSplitMaxBlock)
-__attribute__((amdgpu_waves_per_eu(2, G > 1 && !PARTIAL && VEC == 4 && LC > 2 && G * LC == kWave ? 5 : 8)))
+__attribute__((amdgpu_waves_per_eu(2, DEEP ? 5 : 8)))
 void row_split_kernel(SpmmArgs a, TileSched ts, int rows_per_slot, int interleave, int reduce_members, RowSplitGrid plan, RowSkip skip)
 {
     __shared__ StagedEntry s_A[kStageCap];
@@ -208,7 +219,9 @@ void row_split_kernel(SpmmArgs a, TileSched ts, int rows_per_slot, int interleav
 
     if constexpr (SHARE) {
         if ((int)blockIdx.x < plan.finders) {
-            find_rows<VEC, OFF32, DEPTH>(a, plan, SKIP && skip_on ? skip.min_len : 0x7fffffff, s_A, s_rp, s_mask, block);
+            const int32_t skip_from = SKIP && skip_on ? skip.min_len : 0x7fffffff;
+            find_rows<VEC, OFF32, DEPTH, DEEP>(a, plan, [&](int64_t, int32_t len) { return len >= plan.share_from && len < skip_from; }, s_A, s_rp,
+                                         s_mask, block);
             if ((int)blockIdx.x < plan.walk_from) return;
         }
     }
@@ -351,6 +364,7 @@ struct Launch {
     int64_t nnz_hint;  // stored entries, -1 = unknown
     bool short_rows;  // rows of kShortRowMean entries or fewer in the mean
     RowSkip skip = {nullptr, 0, 0};
+    bool deep = false;  // the instance for rows that workgroups take together, where there is one
 
     // workgroups of this instance that one compute unit can hold at once
     template <typename K>
@@ -364,20 +378,23 @@ struct Launch {
     template <int G, int LC, int VEC>
     void operator()() const
     {
-        if constexpr (G > 1) go<G, LC, VEC, kDepthGroups>();
+        if constexpr (G > 1 && !PARTIAL && !SKIP && VEC == 4 && LC > 2 && G * LC == kWave) {
+            if (deep) go<G, LC, VEC, kDepthGroups, true>();
+            else go<G, LC, VEC, kDepthGroups>();
+        } else if constexpr (G > 1) go<G, LC, VEC, kDepthGroups>();
         else if constexpr (SKIP) go<G, LC, VEC, kDepthRows>();
         else if (short_rows) go<G, LC, VEC, kDepthShort>();
         else go<G, LC, VEC, kDepthRows>();
     }
 
-    template <int G, int LC, int VEC, int DEPTH>
+    template <int G, int LC, int VEC, int DEPTH, bool DEEP = false>
     void go() const
     {
         // a persistent grid must be resident all at once (asked of the runtime only for such launches)
         int resident = 0;
         if (persistent)
-            resident = compute_units * (off32 ? resident_per_cu(row_split_kernel<G, LC, VEC, true, PARTIAL, SKIP, DEPTH>, block)
-                                              : resident_per_cu(row_split_kernel<G, LC, VEC, false, PARTIAL, SKIP, DEPTH>, block));
+            resident = compute_units * (off32 ? resident_per_cu(row_split_kernel<G, LC, VEC, true, PARTIAL, SKIP, DEPTH, DEEP>, block)
+                                              : resident_per_cu(row_split_kernel<G, LC, VEC, false, PARTIAL, SKIP, DEPTH, DEEP>, block));
         const int slots = block / (G * LC);
         const int64_t rows_per_block = (int64_t)slots * rows_per_slot;
         TileSched ts;
@@ -392,10 +409,10 @@ struct Launch {
             plan_row_split_grid(PARTIAL ? 1 : G, passes, a.M, ts.items, xcds, compute_units, nnz_hint, resident);
         const uint32_t grid = plan.grid;
         if (off32)
-            hipLaunchKernelGGL((row_split_kernel<G, LC, VEC, true, PARTIAL, SKIP, DEPTH>), dim3(grid), dim3(block), 0, s, a,
+            hipLaunchKernelGGL((row_split_kernel<G, LC, VEC, true, PARTIAL, SKIP, DEPTH, DEEP>), dim3(grid), dim3(block), 0, s, a,
                                ts, rows_per_slot, interleave, reduce_members, plan, skip);
         else
-            hipLaunchKernelGGL((row_split_kernel<G, LC, VEC, false, PARTIAL, SKIP, DEPTH>), dim3(grid), dim3(block), 0, s, a,
+            hipLaunchKernelGGL((row_split_kernel<G, LC, VEC, false, PARTIAL, SKIP, DEPTH, DEEP>), dim3(grid), dim3(block), 0, s, a,
                                ts, rows_per_slot, interleave, reduce_members, plan, skip);
     }
 };
