@@ -70,6 +70,25 @@ struct FlatPlace {
 
 constexpr int kFlatBatch = 8;
 
+// Which block of rows a workgroup takes: workgroup b runs on die b % xcds, and a die gets `pieces` contiguous runs of blocks, spread
+// over the matrix (where long rows lie together, they are not all one die's).
+struct FlatBlocks {
+    int64_t blocks;
+    int32_t xcds, run;  // blocks of a run
+    FlatBlocks() = default;
+    FlatBlocks(int64_t blocks_, int xcds_, int pieces) : blocks(blocks_), xcds(xcds_), run((int32_t)((blocks_ + (int64_t)xcds_ * pieces - 1) / ((int64_t)xcds_ * pieces))) {}
+    int64_t grid() const
+    {
+        const int64_t round = (int64_t)xcds * run;
+        return (blocks + round - 1) / round * round;
+    }
+    __device__ __forceinline__ int64_t at(uint32_t wg) const  // `blocks` or more: none
+    {
+        const uint32_t turn = wg / (uint32_t)xcds;
+        return ((int64_t)(turn / (uint32_t)run) * xcds + wg % (uint32_t)xcds) * run + turn % (uint32_t)run;
+    }
+};
+
 // ENTRIES and RUNS: the most of a piece.
 template <int ENTRIES, int RUNS>
 struct FlatShared {

@@ -1,17 +1,21 @@
 // Row-split schedule, parallel strategy: a workgroup owns a block of consecutive rows, and teams of lanes share what it has
-// evenly (sgap_flat.hpp): whole rows a team each, a row of more than kFlatCut entries by several, whose sums are added up in
-// order.  One plain store per row, no atomics.  A row that goes on in the next piece of a block is carried over in LDS; rows
-// that are too long for that (768 entries) are left to the workgroups in front of the grid that look for them (find_rows), and
-// a piece goes on behind such a row.
+// evenly (sgap_flat.hpp): whole rows a team each, a row of more than kFlatCut entries by several, whose sums are added up in a
+// fixed order.  One plain store per row, no atomics.  A row that goes on in the next piece of a block is carried over in LDS; rows that
+// are too long for that (768 entries) are left to the workgroups in front of the grid that look for them (find_rows), and the other
+// rows of the piece close up.  Where long rows lie together a block of equal numbers of rows has many times the others' entries:
+// there the workgroups in front take rows of kFsHeavyRow entries and more too, and a die's blocks are spread over the matrix.
 //
 // Bound by the gathers from beyond the L2s where B is large, else by the chain of loads that a block is; power laws by their
 // longest rows, which a workgroup takes 20 us for (4,096 entries, N = 37).  With a group of lanes per row (row_split_kernel)
 // the groups of a wavefront meet at every row, and members without entries wait for those with most.  us, group per row
-// / this: uniform, 60,000 rows of 16, N = 16 19.2 / 10.3; 50,000 of 16, N = 32 19.9 / 12.3, N = 37 24.3 / 20.3; 60,000 of 8,
-// N = 32 20.7 / 10.6; of 12, N = 64 30.9 / 25.8; 500,000 of 16, N = 32, a B of 6.4 MB 131 / 75.  Power laws, mean 16, three
-// matrices each, in the mean: 50,000 rows, N = 16 22.6 / 20.9, N = 32 30.8 / 22.5; 120,000, N = 32 51 / 37, N = 64 71 / 65.
+// / this: uniform, 60,000 rows of 16, N = 13, G = 16 18.3 / 11.4, N = 32 21.7 / 14.1, N = 48 27.9 / 25.8; 40,000 of 8, N = 32
+// 15.4 / 8.9; 60,000 of 12, N = 64 29.7 / 24.8.  Power laws, mean 16: 50,000 rows, N = 24 30.3 / 27.8, N = 32 30.2 / 25.2, N = 37
+// 37.0 / 35.1, N = 48 37.1 / 34.1; 120,000, N = 32 50.5 / 46.8; 200,000, N = 32 77 / 68.  50,000 rows in order of their lengths,
+// N = 32 95 / 42 (254 with every row below 768 entries in its block); R-MAT, 65,536 rows, N = 16, G = 32 76 / 33 (164), N = 48 102 / 59
+// (164), 131,072, N = 32 124 / 84 (181).
 #include "sgap_common.hpp"
 #include "sgap_flat.hpp"
+#include "sgap_nnz_common.hpp"
 #include "sgap_row_split_impl.hpp"
 
 namespace sgap {
@@ -20,8 +24,11 @@ constexpr int kFsEntries = 2048;  // entries of a piece at most
 constexpr int kFsRows = 1024;     // rows of a block at most
 constexpr int kFsResident = 5;    // workgroups of a compute unit
 constexpr int kFsMean = 1200;     // entries of a block in the mean at most (800 and 1,800: up to 6 % slower)
+constexpr int kFsPieces = 8;      // runs of blocks of a die
 constexpr int kFsDepth = 12;      // rows of B in flight of a row that a workgroup takes together
 constexpr int kFsGroup = 8;       // plan_row_split_grid as for groups of so many: rows of 768 entries and more are looked for
+constexpr int kFsHeavy = 3072;    // entries of a block from which on ...
+constexpr int kFsHeavyRow = 96;   // ... rows of so many are looked for too
 
 namespace {
 
@@ -30,31 +37,74 @@ struct FsShared {
     FlatHeads<4> heads;      // of rows
     Vec<4> carry[2][kWave];  // of the row that goes on in the next piece
     unsigned long long mask[kWavesPerBlock];
-    int first_long, next_long;
+    unsigned long long left_out[kFsRows / kWave];  // rows of the piece that are a finder's
+    int32_t scan[kWavesPerBlock], gaps;
 };
 static_assert(kFsEntries >= kStageCap && kFsRows >= kRowCap, "find_rows has the same places");
+
+// Rows of so many entries and more are a finder's in a block of that many entries.
+__device__ __forceinline__ int32_t flat_shared_left_out(int32_t share_from, int32_t block_entries)
+{
+    return block_entries > kFsHeavy && kFsHeavyRow < share_from ? kFsHeavyRow : share_from;
+}
+
+// The pointers of a piece's n rows as if those that are left out had no entries and the first row began at e0; from 0 on.
+template <typename OUT>
+__device__ __forceinline__ void close_up(FsShared& sh, int n, int32_t e0, OUT&& is_left_out)
+{
+    constexpr int EACH = kFsRows / kBlock;  // consecutive rows to a thread
+    int32_t* const ptr = sh.flat.ptr;
+    const int lane = threadIdx.x % kWave, wave = threadIdx.x / kWave, first = threadIdx.x * EACH;
+    int32_t len[EACH], sum = 0;
+#pragma unroll
+    for (int j = 0; j < EACH; ++j) {
+        const int i = first + j;
+        const int32_t from = i == 0 || i >= n ? e0 : ptr[i];
+        len[j] = i < n && !is_left_out(i) ? ptr[i + 1] - from : 0;
+        sum += len[j];
+    }
+    int32_t before = sum;
+    for (int d = 1; d < kWave; d *= 2) {
+        const int32_t other = __shfl_up(before, d, kWave);
+        if (lane >= d) before += other;
+    }
+    if (lane == kWave - 1) sh.scan[wave] = before;
+    __syncthreads();  // everyone has read the pointers, too
+    before -= sum;
+    for (int w = 0; w < wave; ++w) before += sh.scan[w];
+#pragma unroll
+    for (int j = 0; j < EACH; ++j) {
+        if (first + j <= n) ptr[first + j] = before;
+        before += len[j];
+        if (first + j == n - 1) ptr[n] = before;
+    }
+    __syncthreads();
+}
 
 }  // namespace
 
 // N <= kWave * 4
 template <bool OFF32>
 __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(kFsResident)))
-void flat_shared_rows_kernel(SpmmArgs a, int lanes, int block_rows, int64_t blocks, int64_t blocks_per_xcd, int xcds, RowSplitGrid plan)
+void flat_shared_rows_kernel(SpmmArgs a, int lanes, int block_rows, FlatBlocks blocks, RowSplitGrid plan)
 {
     __shared__ FsShared sh;
     auto& s = sh.flat;
     if (__builtin_expect((int)blockIdx.x < plan.walk_from, 1)) {  // (said to come first: a register less is held meanwhile by the others)
-        auto is_shared = [&](int64_t, int32_t len) { return len >= plan.share_from; };
+        auto is_shared = [&](int64_t row, int32_t len) {
+            if (len < kFsHeavyRow || len >= plan.share_from) return len >= plan.share_from;
+            const int64_t first = (int64_t)((uint32_t)row / (uint32_t)block_rows) * block_rows;
+            const int64_t last = a.M - first < block_rows ? a.M : first + block_rows;
+            return len >= flat_shared_left_out(plan.share_from, a.rowptr[last] - a.rowptr[first]);
+        };
         if ((int)blockIdx.x < plan.finders) find_rows<4, OFF32, kFsDepth, true>(a, plan, is_shared, s.entry, s.ptr, sh.mask, kBlock);
         return;
     }
-    const uint32_t wg = blockIdx.x - plan.walk_from;
     const int teams = kBlock / lanes;
-    // workgroup b runs on die b % xcds: every die gets one contiguous run of blocks
-    const int64_t block = (int64_t)(wg % xcds) * blocks_per_xcd + wg / xcds;
-    if (block >= blocks) return;  // the whole workgroup
-    const int64_t row_first = block * block_rows;
-    const int rows = (int)(a.M - row_first < block_rows ? a.M - row_first : block_rows);
+    const int64_t block = blocks.at(blockIdx.x - plan.walk_from);
+    if (block >= blocks.blocks) return;  // the whole workgroup
+    const int32_t row_first = (int32_t)(block * block_rows);  // M < 2^31
+    const int rows = (int32_t)a.M - row_first < block_rows ? (int32_t)a.M - row_first : block_rows;
 
     struct Columns {
         bool ok;
@@ -66,6 +116,7 @@ void flat_shared_rows_kernel(SpmmArgs a, int lanes, int block_rows, int64_t bloc
             first = ok ? lane_first_col<4>(k, N) : 0;
         }
     };
+    int32_t left_out_from = 0;
     bool comes_in = false;  // row r0 began in the piece before
     int32_t e0 = 0;         // where the piece begins (comes_in)
     for (int r0 = 0, turn = 0; r0 < rows; turn ^= 1) {
@@ -74,32 +125,25 @@ void flat_shared_rows_kernel(SpmmArgs a, int lanes, int block_rows, int64_t bloc
         {
             const FlatPlace p(lanes);
             for (int i = p.tid; i <= n; i += kBlock) s.ptr[i] = a.rowptr[row_first + r0 + i];
-            if (p.tid == 0) sh.first_long = n;
+            if (p.tid == 0) sh.gaps = 0;
+            __syncthreads();
+            if (r0 == 0 && !comes_in) left_out_from = flat_shared_left_out(plan.share_from, __builtin_amdgcn_readfirstlane(s.ptr[n] - s.ptr[0]));  // the whole block
+            for (int i = p.tid; i - p.tid < n; i += kBlock) {
+                const bool out = i < n && s.ptr[i + 1] - s.ptr[i] >= left_out_from;
+                const unsigned long long mask = __ballot(out);
+                if (p.tid % kWave == 0) sh.left_out[i / kWave] = mask;
+                if (out) sh.gaps = 1;
+            }
         }
         __syncthreads();
-        {
-            const FlatPlace p(lanes);
-            for (int i = p.tid; i < n; i += kBlock)
-                if (s.ptr[i + 1] - s.ptr[i] >= plan.share_from) atomicMin(&sh.first_long, i);
-        }
-        __syncthreads();
-        int hole_row = __builtin_amdgcn_readfirstlane(sh.first_long);  // a finder's; the piece ends in front of another one
-        int32_t hole = 0, hole_at = 0;                                 // its entries, and where they were
-        if (hole_row < n) {
-            hole_at = __builtin_amdgcn_readfirstlane(s.ptr[hole_row]);
-            hole = __builtin_amdgcn_readfirstlane(s.ptr[hole_row + 1]) - hole_at;
-            if (threadIdx.x == 0) sh.next_long = n;
-            __syncthreads();
-            const FlatPlace p(lanes);
-            for (int i = p.tid; i < n; i += kBlock)
-                if (i > hole_row && s.ptr[i + 1] - s.ptr[i] >= plan.share_from) atomicMin(&sh.next_long, i);
-            __syncthreads();
-            n = __builtin_amdgcn_readfirstlane(sh.next_long);
-            for (int i = p.tid; i <= n; i += kBlock)
-                if (i > hole_row) s.ptr[i] -= hole;
-            __syncthreads();
-        }
+        const bool gaps = __builtin_amdgcn_readfirstlane(sh.gaps) != 0;  // rows of the piece are a finder's: the others close up in LDS
         if (!comes_in) e0 = __builtin_amdgcn_readfirstlane(s.ptr[0]);
+        auto is_left_out = [&](int row) { return (sh.left_out[row / kWave] >> (row % kWave) & 1) != 0; };
+        const int32_t came_from = e0;
+        if (gaps) {
+            close_up(sh, n, e0, is_left_out);
+            e0 = 0;
+        }
         bool cut = false;  // the last row goes on in the next piece
         int32_t end = __builtin_amdgcn_readfirstlane(s.ptr[n]);
         if (end - e0 > kFsEntries) {
@@ -111,7 +155,7 @@ void flat_shared_rows_kernel(SpmmArgs a, int lanes, int block_rows, int64_t bloc
             cut = end - e0 > kFsEntries;
             if (cut) end = e0 + kFsEntries;
         }
-        if (comes_in || cut) {
+        if ((comes_in && !gaps) || cut) {
             __syncthreads();
             if (threadIdx.x == 0) {
                 if (comes_in) s.ptr[0] = e0;
@@ -122,16 +166,32 @@ void flat_shared_rows_kernel(SpmmArgs a, int lanes, int block_rows, int64_t bloc
         const int32_t cnt = end - e0;
         {
             const FlatPlace p(lanes);
-            const int32_t front = hole > 0 && hole_at < end ? hole_at - e0 : cnt;
-            flat_stage<kFsEntries>(s.entry, a.colidx, a.vals, e0, front, p.tid);
-            if (front < cnt) flat_stage<kFsEntries>(s.entry + front, a.colidx, a.vals, e0 + front + hole, cnt - front, p.tid);
+            if (!gaps) {
+                flat_stage<kFsEntries>(s.entry, a.colidx, a.vals, e0, cnt, p.tid);
+            } else {
+                // entry by entry from where its row is
+                constexpr int U = 4;
+#pragma unroll 1
+                for (int q0 = p.tid; q0 < cnt; q0 += U * kBlock) {
+                    int32_t at[U];
+#pragma unroll
+                    for (int u = 0; u < U; ++u) {
+                        const int q = q0 + u * kBlock;
+                        const int row = last_row_at_or_before(s.ptr, 0, n - 1, q < cnt ? q : cnt - 1);
+                        at[u] = (row == 0 && comes_in ? came_from : a.rowptr[row_first + r0 + row]) + q - s.ptr[row];
+                    }
+#pragma unroll
+                    for (int u = 0; u < U; ++u)
+                        if (q0 + u * kBlock < cnt) s.entry[q0 + u * kBlock] = {load_stream(a.colidx + at[u]), load_stream(a.vals + at[u])};
+                }
+            }
             flat_deal<true>(s, e0, cnt, n, teams, p.tid);
         }
         __syncthreads();
 
         const FlatPlace p(lanes);
         const Columns c(p, (uint32_t)a.N, teams);
-        float* const C = a.C + (row_first + r0) * a.N + c.first;
+        float* const C = a.C + (int64_t)(row_first + r0) * a.N + c.first;
         auto store = [&](uint32_t row, const Vec<4>& sum) {
             if (c.ok) store_vec_stream<4>(C + (uint64_t)row * (uint32_t)a.N, sum);
         };
@@ -150,7 +210,7 @@ void flat_shared_rows_kernel(SpmmArgs a, int lanes, int block_rows, int64_t bloc
                 auto done = [&](int row, const Vec<4>& of_row) {
                     const bool is_end = row < ends;
                     if (whole && is_end) {
-                        if (row != hole_row) store((uint32_t)row, of_row);
+                        if (!gaps || !is_left_out(row)) store((uint32_t)row, of_row);
                     } else if (whole) {
                         open_row = row;
                     } else {
@@ -184,25 +244,31 @@ void flat_shared_rows_kernel(SpmmArgs a, int lanes, int block_rows, int64_t bloc
                 else sh.carry[turn ^ 1][p.chunk] = sum;
             }
         }
+        if (gaps && cut) {  // where the last row goes on: what it has here behind where it was
+            const int32_t begin = n == 1 && comes_in ? came_from : a.rowptr[row_first + r0 + n - 1];
+            end += __builtin_amdgcn_readfirstlane(begin - s.ptr[n - 1]);
+        }
         r0 += n - (cut ? 1 : 0);
-        e0 = end + (hole_at < end ? hole : 0);
+        e0 = end;
         comes_in = cut;
     }
 }
 
-// Where groups of lanes are the better ones: few entries (us, group per row / this: power laws of 10,000 rows, N = 16 8.8 /
-// 11.2, N = 24 11.3 / 12 to 18; 25,000 rows, N = 16 14.0 / 17.3, N = 48 24.7 / 24.7; uniform, 5,000 rows of 16, N = 32 5.3 / 6.1,
-// 20,000 9.0 / 7.2), few columns (50,000 rows, N = 8 17.5 / 24.3, N = 4 16.2 / 32), and where wide rows come from beyond
-// the L2s (500,000 rows of 16, N = 64 292 / 309; 200,000, N = 41, a B of 33 MB 129 / 128).  Long rows leave no members idle
-// (200,000 rows of 64, N = 32 118 / 107; 20,000 of 400 66 / 75).
-// Groups of 8 and fewer have few idle members, and up to 16 columns that is enough (power law of 46,000 rows, N = 13, G = 8 17.5 /
-// 21.8, of 16 23 / 23; 130,000 32.6 / 36.6 and 53 / 50).
+// Where groups of lanes are the better ones (us, group per row / this): few entries (power laws, 20,000 rows, N = 24, G = 8 15.1 / 16.8, N = 32
+// 15.8 / 18.1; 50,000, N = 12, G = 32 22.7 / 24.9, 120,000, N = 16 46 / 42; uniform, 5,000 rows of 16, N = 32 5.3 / 6.1), few
+// columns (50,000 rows, N = 8 17.5 / 24.3, N = 4 16.2 / 32), groups of few members, which have few idle ones (60,000 rows of 12, G = 4, N =
+// 32 12.8 / 15.6, N = 48, where a group's columns leave it no more anyway, 26.8 / 21.6; up to 16 columns groups of 8: 46,000 rows, N = 13
+// 17.5 / 21.8), longer rows (10,000 of 120, N = 32 14.5 / 15.8, N = 48 26.6 / 29.1; 30,000 of 1 to 63, N = 24 18.1 / 18.1, N = 64 30.2 /
+// 32.3; of 20, N = 32 21.8 / 16.6, N = 48 30.7 / 30.9), and wide rows from beyond the L2s (power laws, 120,000 rows, B of 18 MB, N = 37
+// 72.6 / 75.1, of 28 MB, N = 58 94 / 98; 50,000, N = 58 45.8 / 48.2).
 bool flat_shared_rows_apply(int64_t K, int64_t N, int members, double mean_row, int64_t nnz_hint)
 {
-    constexpr double kFsLongMean = 128.0;
-    if (N < 12 || N > 64 || mean_row > kFsLongMean || (N > 40 && K * N * 4 > (32 << 20))) return false;
-    if (N <= 16 && members <= 8) return false;
-    return nnz_hint >= (N < 24 ? 700'000 : 300'000);
+    constexpr double kRowMean = 20.0, kShortRowMean = 12.0;
+    if (N < 12 || N > 64 || mean_row > kRowMean) return false;
+    if (N < 24) return members > 8 && nnz_hint >= 1'000'000;
+    if (N <= 32 && members < 8) return false;
+    if (mean_row <= kShortRowMean) return nnz_hint >= 300'000 && (N <= 40 || K * N * 4 <= (32 << 20));
+    return N <= 32 ? nnz_hint >= 500'000 : N <= 48 && nnz_hint >= 300'000 && K * N * 4 <= (12 << 20);
 }
 
 hipError_t launch_flat_shared_rows(const SpmmArgs& a, int xcds, int compute_units, int64_t nnz_hint, hipStream_t s)
@@ -218,11 +284,11 @@ hipError_t launch_flat_shared_rows(const SpmmArgs& a, int xcds, int compute_unit
     const int64_t least = (int64_t)((lanes <= 8 ? 800.0 : 512.0) * (double)a.M / (double)nnz_hint);
     if (rows < least) rows = least;
     if (rows > kFsRows) rows = kFsRows;
-    const int64_t blocks = (a.M + rows - 1) / rows;
-    const int64_t blocks_per_xcd = (blocks + xcds - 1) / xcds;
-    const RowSplitGrid plan = plan_row_split_grid(kFsGroup, 1, a.M, blocks, xcds, compute_units, nnz_hint, 0);
+    const FlatBlocks blocks((a.M + rows - 1) / rows, xcds, kFsPieces);
+    const RowSplitGrid plan = plan_row_split_grid(kFsGroup, 1, a.M, blocks.grid(), xcds, compute_units, nnz_hint, 0);
+    if (plan.finders == 0) return hipErrorInvalidValue;  // (rows are left out for them)
     auto go = [&](auto kernel) {
-        hipLaunchKernelGGL(kernel, dim3(plan.grid), dim3(kBlock), 0, s, a, lanes, (int)rows, blocks, blocks_per_xcd, xcds, plan);
+        hipLaunchKernelGGL(kernel, dim3(plan.grid), dim3(kBlock), 0, s, a, lanes, (int)rows, blocks, plan);
     };
     if (offsets_fit_32(a)) go(flat_shared_rows_kernel<true>); else go(flat_shared_rows_kernel<false>);
     return hipGetLastError();
