@@ -459,7 +459,7 @@ int spmm_impl(int64_t M, int64_t K, int64_t N, const int32_t* rowptr, const int3
             err = launch_flat_shared_rows(a, xcds, cus, nnz_hint, s);
         } else if (row_split_by_quads(M, N, c, nnz_hint, cus)) {
             err = launch_row_quads(a, lc, (int)tile_cols, xcds, s);
-        } else if (!par && c.block_size == 0 && c.persistent == 0 && c.tile_cols == 0 && flat_rows_apply(K, N, avg_row, nnz_hint)) {
+        } else if (!par && c.block_size == 0 && c.persistent == 0 && c.tile_cols == 0 && flat_rows_apply(K, N, group_size, avg_row, nnz_hint)) {
             err = launch_flat_rows(a, vec, xcds, cus, nnz_hint, s);
         } else {
             // the parallel strategy interleaves its groups' rows; the serial strategy's lanes

@@ -270,8 +270,8 @@ bool sddmm_by_quads(int64_t M, int64_t K, int64_t J, int g, int64_t nnz_hint, co
 bool flat_shared_rows_apply(int64_t K, int64_t N, int members, double mean_row, int64_t nnz_hint);
 hipError_t launch_flat_shared_rows(const SpmmArgs& a, int xcds, int compute_units, int64_t nnz_hint, hipStream_t s);
 // serial strategy, short rows (sgap_flat_rows.hip).  flat_rows_apply: whether that is the kernel for so many rows of
-// mean_row stored entries; never without a count of them
-bool flat_rows_apply(int64_t K, int64_t N, double mean_row, int64_t nnz_hint);
+// mean_row stored entries, `group` to a lane; never without a count of them
+bool flat_rows_apply(int64_t K, int64_t N, int group, double mean_row, int64_t nnz_hint);
 hipError_t launch_flat_rows(const SpmmArgs& a, int vec, int xcds, int compute_units, int64_t nnz_hint, hipStream_t s);
 // the same with g lanes per row reducing in sub-groups of r < g lanes whose sums
 // are merged with atomics; C must have been zeroed (launch_nnz_zero_rows, -1)

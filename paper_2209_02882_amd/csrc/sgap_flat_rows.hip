@@ -4,9 +4,10 @@
 //
 // Bound by the gathers from beyond the L2s where B is large (2,000,000 rows of 1 to 16 entries, N = 32, a B of 8.4 MB: 1.6 GB
 // at 7.5 TB/s), else by the address units.  us, a lane group per row that meets the others of its wavefront after each
-// (row_split_kernel) / this, rows of 1 to 16 entries: 2,000,000 rows, N = 32, B of 8.4 MB 217 / 212, of 2.6 MB 202 / 164;
-// N = 16, 4.2 MB 170 / 146; 160,000, N = 48 31.9 / 22.3; 225,000, N = 24 24.8 / 20.4; 115,000, N = 16, four rows to a lane
-// 17.2 / 10.2; 93,000, N = 16 9.9 / 9.4.  1,000,000 rows of 2 entries, N = 32 70.6 / 62.7.
+// (row_split_kernel) / this: 2,000,000 rows of 1 to 15 entries, B of 65,536 rows, N = 32 228 / 200, N = 64 513 / 414; 250,000, N = 32
+// 32.9 / 31.1, N = 48 62.5 / 58.4, B of 20,000 rows 29.6 / 24.7 and 50.8 / 35.6; 700,000 of 1 to 11, N = 32, in order of their
+// lengths 83 / 64 (86 with a die's blocks in one run); 64,000, N = 16, four rows to a lane 17.4 / 8.3; 200,000 of 10 in the mean, N = 8, four
+// rows to a lane 45.7 / 22.3.
 #include "sgap_common.hpp"
 #include "sgap_flat.hpp"
 #include "sgap_nnz_common.hpp"
@@ -17,104 +18,101 @@ constexpr int kFrEntries = 2560;   // entries of a piece at most: four workgroup
 constexpr int kFrRows = 1024;      // rows of a piece at most
 constexpr int kFrResident = 4;     // workgroups of a compute unit
 constexpr int kFrMean = 1900;      // entries of a block in the mean at most
+constexpr int kFrPieces = 8;      // runs of blocks of a die, where the columns are not cut into tiles
 constexpr int kFrTile = 32;        // columns of a tile: a cache line of each row of B
 
 template <int VEC, bool OFF32>
-__global__ __launch_bounds__(kBlock) void flat_rows_kernel(SpmmArgs a, int lanes, int block_rows, int64_t blocks, int64_t blocks_per_xcd,
-                                                           int xcds, int tile_cols)
+__global__ __launch_bounds__(kBlock) void flat_rows_kernel(SpmmArgs a, int lanes, int block_rows, int64_t blocks, FlatBlocks items,
+                                                           int tile_cols)
 {
     __shared__ FlatShared<kFrEntries, kFrRows> s;
     __shared__ Vec<VEC> s_part[kBlock];
     const int teams = kBlock / lanes;
-    // workgroup b runs on die b % xcds: every die gets one contiguous run of blocks, tile by tile
-    int64_t block = (int64_t)(blockIdx.x % xcds) * blocks_per_xcd + blockIdx.x / xcds;
-    const int64_t tiles = (a.N + tile_cols - 1) / tile_cols;
-    if (block >= blocks * tiles) return;  // the whole workgroup
-    const int64_t tile_first = block / blocks * tile_cols, tile_last = tile_first + tile_cols < a.N ? tile_first + tile_cols : a.N;
+    int64_t block = items.at(blockIdx.x);  // tile by tile
+    if (block >= items.blocks) return;     // the whole workgroup
+    const int64_t tile_first = block / blocks * tile_cols;  // (a tile has no more columns than the lanes hold)
     block %= blocks;
     const int64_t row_first = block * block_rows;
     const int64_t row_last = row_first + block_rows < a.M ? row_first + block_rows : a.M;
 
-    for (int64_t k0 = tile_first; k0 < tile_last; k0 += (int64_t)lanes * VEC) {
-        struct Columns {
-            bool ok;
-            uint32_t first;  // of the VEC columns this lane holds
-            __device__ __forceinline__ Columns(const FlatPlace& p, int64_t k0, int64_t N, int teams)
-            {
-                const uint32_t k = (uint32_t)k0 + p.chunk * VEC;  // N < 2^31
-                ok = k < (uint32_t)N && p.team < teams;
-                first = ok ? lane_first_col<VEC>(k, (uint32_t)N) : 0;
-            }
-        };
-        for (int64_t r0 = row_first; r0 < row_last;) {
-            int n = row_last - r0 < kFrRows ? (int)(row_last - r0) : kFrRows;
-            __syncthreads();  // the piece before is done with
-            {
-                const FlatPlace p(lanes);
-                for (int i = p.tid; i <= n; i += kBlock) s.ptr[i] = a.rowptr[r0 + i];
-            }
-            __syncthreads();
-            const int32_t e0 = __builtin_amdgcn_readfirstlane(s.ptr[0]);
-            if (s.ptr[n] - e0 > kFrEntries) {
-                const FlatPlace p(lanes);
-                int fit = 0;
-                for (int i = 0; i < n; i += kBlock) fit += __syncthreads_count(i + p.tid < n && s.ptr[i + p.tid + 1] - e0 <= kFrEntries);
-                n = fit;
-            }
-            n = __builtin_amdgcn_readfirstlane(n);
-            if (n == 0) {
-                // a row of more entries than there is room for: all teams together
-                const FlatPlace p(lanes);
-                const Columns c(p, k0, a.N, teams);
-                const MaskedRows<VEC, OFF32> B(a.B, a.N, c.first);
-                const int32_t e1 = __builtin_amdgcn_readfirstlane(s.ptr[1]);
-                Vec<VEC> t;
-                t.zero();
-                for (int32_t base = e0; base < e1; base += kFrEntries) {
-                    const int32_t cnt = e1 - base < kFrEntries ? e1 - base : kFrEntries;
-                    __syncthreads();
-                    flat_stage<kFrEntries>(s.entry, a.colidx, a.vals, base, cnt, p.tid);
-                    __syncthreads();
-#pragma unroll 1
-                    for (int q = p.team; c.ok && q < cnt; q += teams) t.fma(s.entry[q].val, B.load(s.entry[q].col, true));
-                }
-                s_part[p.tid] = t;
-                __syncthreads();
-                if (p.team == 0 && c.ok) {
-#pragma unroll 1
-                    for (int m = 1; m < teams; ++m) {
-                        const Vec<VEC> other = s_part[m * lanes + p.chunk];
-#pragma unroll
-                        for (int i = 0; i < VEC; ++i) t.v[i] += other.v[i];
-                    }
-                    store_vec_stream<VEC>(a.C + r0 * a.N + c.first, t);
-                }
-                ++r0;
-                continue;
-            }
-            const int32_t cnt = __builtin_amdgcn_readfirstlane(s.ptr[n]) - e0;
-            {
-                const FlatPlace p(lanes);
-                flat_stage<kFrEntries>(s.entry, a.colidx, a.vals, e0, cnt, p.tid);
-                flat_deal<false>(s, e0, cnt, n, teams, p.tid);
-            }
-            __syncthreads();
-            {
-                const FlatPlace p(lanes);
-                const Columns c(p, k0, a.N, teams);
-                float* const C = a.C + r0 * a.N + c.first;
-                const uint32_t N = (uint32_t)a.N;
-                auto store = [&](int row, const Vec<VEC>& sum) { store_vec_stream<VEC>(C + (uint64_t)(uint32_t)row * N, sum); };
-                const int first = c.ok ? s.start[p.team] : 0, last = c.ok ? s.start[p.team + 1] : 0;
-                if (first < last) {
-                    const MaskedRows<VEC, OFF32> B(a.B, a.N, c.first);
-                    const Vec<VEC> sum = flat_walk<VEC, OFF32, FlatChain<VEC>>(s, first, last, s.ptr[first] - e0, 0x7fffffff, e0, B, true,
-                                                                  [](int, bool, bool) {}, store);
-                    store(last - 1, sum);
-                }
-            }
-            r0 += n;
+    struct Columns {
+        bool ok;
+        uint32_t first;  // of the VEC columns this lane holds
+        __device__ __forceinline__ Columns(const FlatPlace& p, int64_t tile_first, int64_t N, int teams)
+        {
+            const uint32_t k = (uint32_t)tile_first + p.chunk * VEC;  // N < 2^31
+            ok = k < (uint32_t)N && p.team < teams;
+            first = ok ? lane_first_col<VEC>(k, (uint32_t)N) : 0;
         }
+    };
+    for (int64_t r0 = row_first; r0 < row_last;) {
+        int n = row_last - r0 < kFrRows ? (int)(row_last - r0) : kFrRows;
+        __syncthreads();  // the piece before is done with
+        {
+            const FlatPlace p(lanes);
+            for (int i = p.tid; i <= n; i += kBlock) s.ptr[i] = a.rowptr[r0 + i];
+        }
+        __syncthreads();
+        const int32_t e0 = __builtin_amdgcn_readfirstlane(s.ptr[0]);
+        if (s.ptr[n] - e0 > kFrEntries) {
+            const FlatPlace p(lanes);
+            int fit = 0;
+            for (int i = 0; i < n; i += kBlock) fit += __syncthreads_count(i + p.tid < n && s.ptr[i + p.tid + 1] - e0 <= kFrEntries);
+            n = fit;
+        }
+        n = __builtin_amdgcn_readfirstlane(n);
+        if (n == 0) {
+            // a row of more entries than there is room for: all teams together
+            const FlatPlace p(lanes);
+            const Columns c(p, tile_first, a.N, teams);
+            const MaskedRows<VEC, OFF32> B(a.B, a.N, c.first);
+            const int32_t e1 = __builtin_amdgcn_readfirstlane(s.ptr[1]);
+            Vec<VEC> t;
+            t.zero();
+            for (int32_t base = e0; base < e1; base += kFrEntries) {
+                const int32_t cnt = e1 - base < kFrEntries ? e1 - base : kFrEntries;
+                __syncthreads();
+                flat_stage<kFrEntries>(s.entry, a.colidx, a.vals, base, cnt, p.tid);
+                __syncthreads();
+#pragma unroll 1
+                for (int q = p.team; c.ok && q < cnt; q += teams) t.fma(s.entry[q].val, B.load(s.entry[q].col, true));
+            }
+            s_part[p.tid] = t;
+            __syncthreads();
+            if (p.team == 0 && c.ok) {
+#pragma unroll 1
+                for (int m = 1; m < teams; ++m) {
+                    const Vec<VEC> other = s_part[m * lanes + p.chunk];
+#pragma unroll
+                    for (int i = 0; i < VEC; ++i) t.v[i] += other.v[i];
+                }
+                store_vec_stream<VEC>(a.C + r0 * a.N + c.first, t);
+            }
+            ++r0;
+            continue;
+        }
+        const int32_t cnt = __builtin_amdgcn_readfirstlane(s.ptr[n]) - e0;
+        {
+            const FlatPlace p(lanes);
+            flat_stage<kFrEntries>(s.entry, a.colidx, a.vals, e0, cnt, p.tid);
+            flat_deal<false>(s, e0, cnt, n, teams, p.tid);
+        }
+        __syncthreads();
+        {
+            const FlatPlace p(lanes);
+            const Columns c(p, tile_first, a.N, teams);
+            float* const C = a.C + r0 * a.N + c.first;
+            const uint32_t N = (uint32_t)a.N;
+            auto store = [&](int row, const Vec<VEC>& sum) { store_vec_stream<VEC>(C + (uint64_t)(uint32_t)row * N, sum); };
+            const int first = c.ok ? s.start[p.team] : 0, last = c.ok ? s.start[p.team + 1] : 0;
+            if (first < last) {
+                const MaskedRows<VEC, OFF32> B(a.B, a.N, c.first);
+                const Vec<VEC> sum = flat_walk<VEC, OFF32, FlatChain<VEC>>(s, first, last, s.ptr[first] - e0, 0x7fffffff, e0, B, true,
+                                                              [](int, bool, bool) {}, store);
+                store(last - 1, sum);
+            }
+        }
+        r0 += n;
     }
 }
 
@@ -133,32 +131,43 @@ int64_t flat_tile(int64_t K, int64_t N)
 
 }  // namespace
 
-// Fewer entries than kFlatMinEntries are a chain of loads that is longer here (60,000 rows of 8, N = 5 5.8 us, here 6.1; 10,000,
-// N = 32 4.2 and 5.1).  Rows of more entries leave few lanes idle there (300,000 of 24, N = 32 97.8, here 98.3).  Wide rows
-// of a large B, whole, are faster there: 2,000,000 rows of 1 to 16 entries, N = 64, B of 51 MB 643 and 663.
-bool flat_rows_apply(int64_t K, int64_t N, double mean_row, int64_t nnz_hint)
+// Where a lane group per row is the better one (us, that / this).  One row to a lane: up to 16 columns, which leave a team a lane or few
+// (760,000 rows of 8, N = 1 17.4 / 24.9; 200,000 of 1 to 19, N = 3 10.4 / 14.4, N = 16 16.6 / 18.6); rows that begin amid sectors of
+// 32 bytes (500,000 of 8, N = 28 68 / 74; 700,000 of 1 to 11 104.8 / 117.8, with N = 32 82.7 / 78.9); rows that fill a batch of eight and a little
+// of the next (60,000 of 9, N = 32 7.1 / 8.2; 200,000 of 10 21.5 / 23.5); a B from beyond the L2s that no tiles cut (500,000 of 8, N = 24, 6.3 MB
+// 55.0 / 57.0, N = 32, 8.4 MB 51.8 / 52.5, 250,000 of 1 to 15 32.9 / 31.1; 700,000 of 1 to 11, N = 24, 12.5 MB 89 / 92); few entries (64,000 of 1 to
+// 15, N = 32, two rows to a lane 10.7 / 11.2, N = 40 19 / 17); 24 and 32 columns of very short rows, where blocks of equal numbers of
+// rows may be uneven (300,000 of 3 in the mean, N = 32 31.8 / 21.7, in order of their lengths 31.6 / 36.2, N = 40 50 / 33 and 52.7 / 50.9).  More rows
+// to a lane are a longer chain there, and sooner lose: four, N = 16 as above, N = 8 45.7 / 22.3; two, N = 4 14 / 7.5 for 64,000 of 1 to 15,
+// but N = 1 20.5 / 25.2 for 760,000 of 8.
+bool flat_rows_apply(int64_t K, int64_t N, int group, double mean_row, int64_t nnz_hint)
 {
     constexpr int64_t kFlatMinEntries = 500'000;
-    constexpr double kFlatMean = 12.0;
-    return nnz_hint >= kFlatMinEntries && mean_row <= kFlatMean && (N <= 48 || flat_tile(K, N) < N || (N <= 64 && K * N * 4 <= (6 << 20)));
+    constexpr double kFlatMean = 12.0, kFlatWideMean = 8.75;
+    if (nnz_hint < kFlatMinEntries || mean_row > kFlatMean) return false;
+    const bool whole = K * N * 4 <= (N < 32 ? 5 << 20 : N <= 48 ? 13 << 20 : 6 << 20), tiles = flat_tile(K, N) < N;
+    if (group >= 8) return N <= 48 || tiles || (N <= 64 && whole);
+    if (N < 24) return (group >= 4 && N <= 16) || (group >= 2 && N <= 4 && nnz_hint < 2'000'000);
+    if (N < 40 && (nnz_hint < 750'000 || (group < 4 && mean_row < 5.0))) return false;
+    return N % 8 == 0 && mean_row <= kFlatWideMean && (tiles || (N <= 64 && whole));
 }
 
 hipError_t launch_flat_rows(const SpmmArgs& a, int vec, int xcds, int compute_units, int64_t nnz_hint, hipStream_t s)
 {
     const int64_t tile_cols = flat_tile(a.K, a.N);
     const int64_t chunks = (tile_cols + vec - 1) / vec, tiles = (a.N + tile_cols - 1) / tile_cols;
-    const int lanes = chunks < kWave ? (int)chunks : kWave;
+    if (chunks > kWave) return hipErrorInvalidValue;
+    const int lanes = (int)chunks;
     // blocks of even numbers of rows, as many as make whole rounds of the resident workgroups
     const int64_t resident = (int64_t)kFrResident * compute_units;
     const int64_t rounds = nnz_hint / (resident * kFrMean) + 1;
     int64_t rows = (a.M + resident * rounds - 1) / (resident * rounds);
     if (rows > kFrRows) rows = kFrRows;
     const int64_t blocks = (a.M + rows - 1) / rows;
-    const int64_t blocks_per_xcd = (blocks * tiles + xcds - 1) / xcds;
-    if (blocks_per_xcd * xcds > 0x7ffffff0LL) return hipErrorInvalidValue;
+    const FlatBlocks items(blocks * tiles, xcds, tiles > 1 ? 1 : kFrPieces);
+    if (items.grid() > 0x7ffffff0LL) return hipErrorInvalidValue;
     auto go = [&](auto kernel) {
-        hipLaunchKernelGGL(kernel, dim3((unsigned)(blocks_per_xcd * xcds)), dim3(kBlock), 0, s, a, lanes, (int)rows, blocks, blocks_per_xcd, xcds,
-                           (int)tile_cols);
+        hipLaunchKernelGGL(kernel, dim3((unsigned)items.grid()), dim3(kBlock), 0, s, a, lanes, (int)rows, blocks, items, (int)tile_cols);
     };
     const bool off32 = offsets_fit_32(a);
     if (vec == 4) { if (off32) go(flat_rows_kernel<4, true>); else go(flat_rows_kernel<4, false>); }
