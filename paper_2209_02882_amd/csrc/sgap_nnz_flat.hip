@@ -23,7 +23,7 @@ namespace sgap {
 
 namespace {
 
-constexpr int kRowCost = 6;    // (with 3, 9 and 13 up to 4 % slower)
+constexpr int kRowCost = kFlatRunCost;  // (with 3, 9 and 13 up to 4 % slower)
 constexpr int kNfTile = 1024;  // entries of a tile at most
 constexpr int kNfResident = 5;  // workgroups of a compute unit
 static_assert(kNfTile <= kWindowCap, "a row of the window for every entry of a tile");
@@ -212,18 +212,23 @@ void nnz_flat_kernel(SpmmArgs a, int lanes, int teams, int tile)
     }
 }
 
-// The tile for a matrix, 0 where this is not the kernel.  Fewer columns leave a team with a lane or two (65,536 rows of a power
-// law, N = 8: 19.9 us by shares of entries, 24.0 here), with more a tile has too few teams (100,000 rows, N = 200 220 and
-// 219; R-MAT, 2^17 rows, N = 256 276 and 282).  A team has some 16 to 32 entries of a tile; 33 to 64 columns take the larger
-// tile where all of them fit the chip at once (power law, 65,536 rows, N = 64: 43.4 us with 1,030 tiles of 1,024 entries,
-// 45.7 with 512; 300,000 rows 200 and 192).  A small matrix has smaller tiles (10,000 rows, N = 44 16.6 us with 512 entries
-// and 17.3 with 1,024).  Where rows are long and the caller asks for shares of 64 entries nothing is left for this kernel to
-// gain (5,000 rows of 4,000, N = 16 179 us and 199, 40,000 of 300 118 and 121; shares of 16 145 and 122).
+// The tile for a matrix, 0 where this is not the kernel (us, by shares of entries / here).  Fewer columns leave a team with a lane or
+// two (65,536 rows of a power law, N = 8: 19.9 / 24.0; 8,000, N = 16 11.8 / 13.8, N = 20 14.2 / 13.0), with more a tile has too few teams
+// (100,000 rows, N = 200 220 / 219; R-MAT, 2^17 rows, N = 256 276 / 282).  Where rows are long and the caller asks for shares of 64
+// entries nothing is left for this kernel to gain (5,000 rows of 4,000, N = 16 179 / 199; 10,000 of 200, N = 64 63.8 / 65.8; shares of 16,
+// 40,000 of 300, N = 16 145 / 122), nor where rows are short, many and wide, and shares are not (500,000 of 1 to 9, N = 64 96.6 / 101.9, shares
+// of 8 116 / 102; 60,000 22.6 / 20.8).
+// A team has some 16 to 32 entries of a tile; 33 to 64 columns take the larger tile where all of them fit the chip at once
+// (power law, 65,536 rows, N = 64: 43.4 us with 1,030 tiles of 1,024 entries, 45.7 with 512; 300,000 rows 200 and 192).  A small matrix
+// has smaller tiles (10,000 rows, N = 44 16.6 us with 512 entries and 17.3 with 1,024).
+// Power laws whose rows come in order of their lengths end in tiles of a row to an entry, a turn each: 40,000 rows, G = 16, N = 32 31.3 / 24.9,
+// but N = 64 34.1 / 41.5, N = 128 54.6 / 65.0; 150,000, N = 32 61 / 70, N = 64 97 / 115, N = 128 188 / 193.
 int nnz_flat_tile(int64_t N, int group, double mean_row, int64_t nnz_hint, int compute_units)
 {
-    if (N < 16 || N > 128 || (N <= 32 && group > 32 && mean_row >= 200.0)) return 0;
+    if (N < 16 || N > 128 || (N <= 64 && group > 32 && mean_row >= 200.0)) return 0;
     int tile = N <= 32 ? kNfTile : N <= 64 ? kNfTile / 2 : kNfTile / 4;
     if (nnz_hint < 0) return tile;
+    if ((N < 20 && nnz_hint < 250'000) || (N > 32 && group >= 16 && mean_row < 8.0 && nnz_hint >= 1'000'000)) return 0;
     if (N > 32 && N <= 64 && nnz_hint > kNfTile * 3 * (int64_t)compute_units && nnz_hint <= kNfTile * kNfResident * (int64_t)compute_units)
         tile = kNfTile;
     const int least = N <= 32 ? kNfTile / 2 : kNfTile / 4;
