@@ -91,6 +91,10 @@ int sgap_debug_group_seg_reduce(const float* in, const int32_t* span, float* out
  *     stored entries by four neighbouring rows together, 0 if not, -1 on bad
  *     arguments (config: a host sgap_config; long_row_min and wave_rows come
  *     first where they apply).
+ *   sgap_debug_spmm_teams, sgap_debug_mttkrp_teams: 1 if teams of lanes that go
+ *     each at its own pace take such a call, 0 if another kernel does, -1 on
+ *     bad arguments (config: a host sgap_config; long_row_min, wave_rows and,
+ *     for MTTKRP, SGAP_TUNE_ROWS_PER_GROUP come first where they apply).
  *   sgap_debug_sddmm_quads: 1 if sgap_sddmm_csr with the parallel strategy
  *     takes the matrix by four neighbouring rows together, 0 if entry by
  *     entry, -1 on bad arguments (rowptr and colidx in host memory; the device
@@ -109,6 +113,8 @@ int sgap_debug_plan_windows(int sddmm, int64_t K, int64_t N, int64_t rows, int64
                             int compute_units, int* in_lds, int* groups, int* shares, int* window,
                             double* lds_clocks, double* gather_clocks);
 int sgap_debug_row_quads(int64_t M, int64_t N, int64_t nnz_hint, const sgap_config* config, int compute_units);
+int sgap_debug_spmm_teams(int64_t M, int64_t K, int64_t N, int64_t nnz_hint, const sgap_config* config, int compute_units);
+int sgap_debug_mttkrp_teams(int64_t I, int64_t J, int group_size, int strategy, int schedule, int64_t nnz_hint);
 int sgap_debug_sddmm_quads(int64_t M, int64_t K, int64_t J, int group_size, int64_t nnz_hint, const int32_t* rowptr,
                            const int32_t* colidx);
 

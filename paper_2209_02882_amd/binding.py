@@ -74,6 +74,8 @@ EXPORTS = {
     "sgap_debug_plan_row_split": (_int, [_int, _int, _i64, _i64, _int, _int, _i64, _int, _p, _p, _p, _p, _p]),
     "sgap_debug_plan_windows": (_int, [_int] + [_i64] * 8 + [_int] * 3 + [_p] * 6),
     "sgap_debug_row_quads": (_int, [_i64, _i64, _i64, _p, _int]),
+    "sgap_debug_spmm_teams": (_int, [_i64, _i64, _i64, _i64, _p, _int]),
+    "sgap_debug_mttkrp_teams": (_int, [_i64, _i64, _int, _int, _int, _i64]),
     "sgap_debug_sddmm_quads": (_int, [_i64, _i64, _i64, _int, _i64, _p, _p]),
     "sgap_copy_f32": (_int, [_p, _p, _i64, _p]),
     "sgap_stream_f32": (_int, [_p, _p, _i64, _int, _p]),

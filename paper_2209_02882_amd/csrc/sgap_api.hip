@@ -362,6 +362,33 @@ bool row_split_by_quads(int64_t M, int64_t N, const sgap_config& c, int64_t nnz_
            sgap::row_quads_apply(M, row_split_lanes(N, c), row_split_tile(N, c), (double)nnz_hint / (double)M, compute_units);
 }
 
+// Members of a row's group: no more than a wavefront has beside the chunk lanes.
+int row_split_members(int64_t N, const sgap_config& c)
+{
+    if (c.strategy != SGAP_REDUCE_PARALLEL) return 1;
+    const int lc = row_split_lanes(N, c);
+    return c.group_size * lc > 64 ? 64 / lc : c.group_size;
+}
+
+// Teams of lanes that go each at its own pace (sgap_flat.hpp), where the caller leaves the layout to the library and says how many
+// entries there are.
+bool row_split_by_teams(int64_t M, int64_t K, int64_t N, const sgap_config& c, int64_t nnz_hint)
+{
+    if (c.schedule != SGAP_SCHED_ROW_SPLIT || c.block_size != 0 || c.persistent != 0 || c.tile_cols != 0 || nnz_hint <= 0) return false;
+    if (c.reduce_size != 0 && c.reduce_size != c.group_size) return false;  // (the sub-groups are what is asked for)
+    const double mean_row = (double)nnz_hint / (double)M;
+    if (c.strategy == SGAP_REDUCE_PARALLEL)
+        return c.rows_per_group == 0 && sgap::flat_shared_rows_apply(K, N, row_split_members(N, c), mean_row, nnz_hint);
+    return sgap::flat_rows_apply(K, N, c.group_size, mean_row, nnz_hint);
+}
+
+// The tile of the nnz-balanced schedule by such teams, 0 where they are not the kernel.
+int nnz_tile_by_teams(int64_t M, int64_t N, const sgap_config& c, int64_t nnz_hint, int compute_units)
+{
+    if (c.schedule != SGAP_SCHED_NNZ_BALANCED || c.strategy != SGAP_REDUCE_SERIAL || c.nnz_tile != 0) return 0;
+    return sgap::nnz_flat_tile(N, c.group_size, (double)nnz_hint / (double)M, nnz_hint, compute_units);
+}
+
 int spmm_impl(int64_t M, int64_t K, int64_t N, const int32_t* rowptr, const int32_t* colidx, const float* vals,
               const float* B, float* C, const sgap_config& c, int64_t nnz_hint, void* workspace,
               int64_t workspace_bytes, void* stream)
@@ -414,11 +441,10 @@ int spmm_impl(int64_t M, int64_t K, int64_t N, const int32_t* rowptr, const int3
         const int xcds = c.xcd_remap == 0 ? 1 : kXcds;
         const int cus = compute_units();
         const int block = c.block_size > 0 ? c.block_size : kBlock;
-        int g = par ? group_size : 1;  // members per row
         const double avg_row = nnz_hint > 0 ? (double)nnz_hint / (double)M : 16.0;
         const int64_t tile_cols = row_split_tile(N, c);
         const int lc = row_split_lanes(N, c);
-        if (reduce_size == 0 && g * lc > 64) g = 64 / lc;
+        const int g = reduce_size == 0 ? row_split_members(N, c) : group_size;  // members per row
         int rows_per_slot = par ? c.rows_per_group : group_size;
         if (rows_per_slot <= 0) {
             // rows a group works through per item: enough stored entries per
@@ -454,12 +480,11 @@ int spmm_impl(int64_t M, int64_t K, int64_t N, const int32_t* rowptr, const int3
                                           window_bytes_of(c), c.window_kb > 0, workspace, long_rows_of(c), s);
         } else if (wave_vec > 0) {
             err = launch_wave_rows(a, wave_vec, wave_rows_count, xcds, nullptr, s);
-        } else if (par && c.block_size == 0 && c.persistent == 0 && c.tile_cols == 0 && c.rows_per_group == 0 &&
-                   flat_shared_rows_apply(K, N, g, avg_row, nnz_hint)) {
+        } else if (par && row_split_by_teams(M, K, N, c, nnz_hint)) {
             err = launch_flat_shared_rows(a, xcds, cus, nnz_hint, s);
         } else if (row_split_by_quads(M, N, c, nnz_hint, cus)) {
             err = launch_row_quads(a, lc, (int)tile_cols, xcds, s);
-        } else if (!par && c.block_size == 0 && c.persistent == 0 && c.tile_cols == 0 && flat_rows_apply(K, N, group_size, avg_row, nnz_hint)) {
+        } else if (!par && row_split_by_teams(M, K, N, c, nnz_hint)) {
             err = launch_flat_rows(a, vec, xcds, cus, nnz_hint, s);
         } else {
             // the parallel strategy interleaves its groups' rows; the serial strategy's lanes
@@ -475,7 +500,7 @@ int spmm_impl(int64_t M, int64_t K, int64_t N, const int32_t* rowptr, const int3
                                     : plan_nnz_serial(group_size, lc, vec, nnz_hint, compute_units(), c.nnz_tile);
         a.group = plan.share;
         a.log2_group = ilog2(plan.share);
-        const int flat_tile = par || c.nnz_tile != 0 ? 0 : nnz_flat_tile(N, group_size, (double)nnz_hint / (double)M, nnz_hint, compute_units());
+        const int flat_tile = nnz_tile_by_teams(M, N, c, nnz_hint, compute_units());
         err = launch_nnz_zero_rows(a, vec, flat_tile > 0 ? ilog2(flat_tile) : plan.merge_log2, s);
         if (err == hipSuccess)
             err = flat_tile > 0 ? launch_nnz_flat(a, flat_tile, compute_units(), nnz_hint, s)
@@ -1083,6 +1108,28 @@ int sgap_debug_row_quads(int64_t M, int64_t N, int64_t nnz_hint, const sgap_conf
     }
     if (check_config(*config)) return -1;
     return row_split_by_quads(M, N, *config, nnz_hint, compute_units_) ? 1 : 0;
+}
+
+int sgap_debug_spmm_teams(int64_t M, int64_t K, int64_t N, int64_t nnz_hint, const sgap_config* config, int compute_units_)
+{
+    if (M < 1 || M > 2147483646LL || K < 0 || K > 2147483647LL || N < 1 || N > 2147483647LL || nnz_hint < -1 || nnz_hint > kMaxEntries ||
+        compute_units_ < 1 || !config) {
+        fail(SGAP_ERR_INVALID_ARG, "bad arguments");
+        return -1;
+    }
+    if (check_config(*config)) return -1;
+    if (row_split_by_quads(M, N, *config, nnz_hint, compute_units_)) return 0;
+    return row_split_by_teams(M, K, N, *config, nnz_hint) || nnz_tile_by_teams(M, N, *config, nnz_hint, compute_units_) > 0 ? 1 : 0;
+}
+
+int sgap_debug_mttkrp_teams(int64_t I, int64_t J, int group_size, int strategy, int schedule, int64_t nnz_hint)
+{
+    if (I < 1 || I > 2147483646LL || J < 1 || J > 2147483647LL || !is_pow2_group(group_size) || nnz_hint < -1 || nnz_hint > kMaxEntries) {
+        fail(SGAP_ERR_INVALID_ARG, "bad arguments");
+        return -1;
+    }
+    if (schedule == SGAP_SCHED_ROW_SPLIT) return strategy == SGAP_REDUCE_PARALLEL && sgap::mttkrp_fibers_apply(I, J, group_size, nnz_hint) ? 1 : 0;
+    return strategy == SGAP_REDUCE_SERIAL && !sgap::mttkrp_serial_applies(J, nnz_hint) ? 1 : 0;
 }
 
 int sgap_debug_sddmm_quads(int64_t M, int64_t K, int64_t J, int group_size, int64_t nnz_hint, const int32_t* rowptr,

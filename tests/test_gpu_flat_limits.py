@@ -1,5 +1,7 @@
 """Teams of lanes that go each at its own pace, in every kernel that has them: operands on both sides of 4 GiB, and values that
 are not finite in the first row of a dense operand, which entries that are left out of a load must not bring in."""
+import ctypes
+
 import numpy as np
 import pytest
 import torch
@@ -15,7 +17,11 @@ LONG = [768, 700, 4096, 33, 1500, 2561]
 SPMM = [  # the kernel, columns, (strategy, schedule, count of entries that the library is told)
     ("row-split serial, short rows", n, (binding.SGAP_REDUCE_SERIAL, binding.SGAP_SCHED_ROW_SPLIT, 500_000)) for n in (1, 3, 5, 24, 33)
 ] + [
-    ("row-split parallel, shared blocks", n, (binding.SGAP_REDUCE_PARALLEL, binding.SGAP_SCHED_ROW_SPLIT, 700_000)) for n in (13, 37, 40)
+    ("row-split parallel, shared blocks", n, (binding.SGAP_REDUCE_PARALLEL, binding.SGAP_SCHED_ROW_SPLIT, hint))
+    for n, hint in ((13, 1_000_000), (24, 500_000), (37, 500_000), (40, 500_000))
+] + [
+    ("row-split parallel, rows that a workgroup takes with fewer loads in flight", n, (binding.SGAP_REDUCE_PARALLEL, binding.SGAP_SCHED_ROW_SPLIT, 1_050_000))
+    for n in (24, 37)
 ] + [
     ("row-split parallel, rows that a workgroup takes", n, (binding.SGAP_REDUCE_PARALLEL, binding.SGAP_SCHED_ROW_SPLIT, 200_000))
     for n in (1, 3, 6, 37, 100)
@@ -49,6 +55,15 @@ def far(x):
 
 
 @pytest.mark.parametrize("kernel,n,point", SPMM)
+def test_spmm_teams_are_the_kernel(kernel, n, point):
+    strategy, schedule, hint = point
+    names = [{v: k for k, v in d.items()}[x] for d, x in ((binding.STRATEGIES, strategy), (binding.SCHEDULES, schedule))]
+    config = binding.make_config(16, *names)
+    for K in (COLS, 2**32 // (4 * n) + COLS // 2):
+        assert binding.load().sgap_debug_spmm_teams(ROWS, K, n, hint, ctypes.byref(config), 256) == (0 if "workgroup" in kernel else 1)
+
+
+@pytest.mark.parametrize("kernel,n,point", SPMM)
 def test_spmm_offsets_of_64_bits(kernel, n, point):
     rowptr, colidx, vals, B = matrix(n, n)
     ref, _ = oracle.spmm_csr(ROWS, COLS, n, rowptr, colidx, vals, B, nthreads=8, bound=False)
@@ -73,6 +88,7 @@ def test_spmm_first_row_not_finite(kernel, n, point):
 
 
 MTTKRP = [("slices", j, (binding.SGAP_REDUCE_PARALLEL, binding.SGAP_SCHED_ROW_SPLIT, None)) for j in (1, 3, 6, 32, 37)] + [
+    ("slices by teams", j, (binding.SGAP_REDUCE_PARALLEL, binding.SGAP_SCHED_ROW_SPLIT, 1_000_000)) for j in (1, 3, 6, 32, 37)] + [
     ("tiles", j, (binding.SGAP_REDUCE_SERIAL, binding.SGAP_SCHED_NNZ_BALANCED, -1)) for j in (1, 3, 6, 32, 37)] + [
     ("shares", j, (binding.SGAP_REDUCE_SERIAL, binding.SGAP_SCHED_NNZ_BALANCED, None)) for j in (1, 3, 6, 8)]
 SLICES, EXTENT = 2500, 4000
