@@ -32,7 +32,6 @@ constexpr int kMsTile = kMsEpt * kBlock;
 constexpr int kMsBatch = 64;             // tiles whose first fibers and slices are looked up at once
 constexpr int kMsFibers = kBlock - 1;    // fibers of a piece at most: a thread each, and a pointer more
 constexpr int kMsSlices = kBlock - 1;    // slices whose pointers a tile keeps (a fiber beyond them bisects the pointers)
-constexpr int kMsX1Bytes = 35 * 512;     // rows of X1 in LDS: 140 of 128 bytes (four workgroups per compute unit)
 constexpr uint16_t kMsEnds = 1 << 15;       // the slice ends with this entry
 constexpr uint16_t kMsFiberEnds = 1 << 14;  // the fiber does
 constexpr int kMsFiberMask = kMsFiberEnds - 1;
@@ -42,9 +41,9 @@ constexpr int kMsFiberMask = kMsFiberEnds - 1;
 __device__ __forceinline__ int ms_place(int q) { return q + (q >> 5); }
 
 template <int LC, int VEC, bool OFF32, bool RAGGED>
-__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) void mttkrp_serial_kernel(MttkrpArgs a,
-                                                                                                       int x1_rows)
+__global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) void mttkrp_serial_kernel(MttkrpArgs a)
 {
+    constexpr int x1_rows = kMsFibers;  // rows of X1 in LDS
     constexpr int ENTRY_LANES = kBlock / LC;
     constexpr int GROUP = kMsTile / ENTRY_LANES;  // entries of a lane's share
     constexpr int D = 4;  // gathered rows of X2 in flight per lane
@@ -151,17 +150,14 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
                 const int32_t top = s_fwin[x1_rows];
                 const int32_t end = top < tile_end ? top : tile_end;
                 // the rows of X1 (in the lanes' own layout)
-                auto stage_x1 = [&](int64_t k0) {
-                    for (int q = tid; q < x1_rows * LC; q += kBlock) {
-                        const int r = q / LC;
-                        const uint32_t k = (uint32_t)k0 + q % LC * VEC;
-                        if (s_fwin[r] >= end || k >= (uint32_t)a.J) continue;
-                        const Vec<VEC> x = load_vec<VEC>(a.X1 + (int64_t)s_k[r] * a.J + lane_first_col<VEC, RAGGED>(k, (uint32_t)a.J));
+                for (int q = tid; q < x1_rows * LC; q += kBlock) {
+                    const int r = q / LC;
+                    const uint32_t k = q % LC * VEC;
+                    if (s_fwin[r] >= end || k >= (uint32_t)a.J) continue;
+                    const Vec<VEC> x = load_vec<VEC>(a.X1 + (int64_t)s_k[r] * a.J + lane_first_col<VEC, RAGGED>(k, (uint32_t)a.J));
 #pragma unroll
-                        for (int v = 0; v < VEC; ++v) s_x1[q * VEC + v] = x.v[v];
-                    }
-                };
-                stage_x1(0);
+                    for (int v = 0; v < VEC; ++v) s_x1[q * VEC + v] = x.v[v];
+                }
                 // a thread per fiber: its slice, where its slice begins and ends
                 if (tid < x1_rows && s_fwin[tid] < end && s_fwin[tid + 1] > s_fwin[tid]) {
                     const int32_t f = f_lb + tid;
@@ -194,17 +190,12 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
                 }
                 __syncthreads();
 
-                for (int64_t k0 = 0; k0 < a.J; k0 += PITCH) {
-                    const uint32_t k = (uint32_t)k0 + chunk * VEC;  // J < 2^31
+                {
+                    const uint32_t k = chunk * VEC;
                     const bool k_ok = k < (uint32_t)a.J;
                     const uint32_t k_lane = k_ok ? lane_first_col<VEC, RAGGED>(k, (uint32_t)a.J) : 0;
                     const BRow<OFF32> X2row(a.X2, a.J, k_lane);
                     const float* __restrict__ my_x1 = s_x1 + chunk * VEC;
-                    if (k0 > 0) {
-                        __syncthreads();  // the previous pass is done with its columns
-                        stage_x1(k0);
-                        __syncthreads();
-                    }
                     // this lane's share, clipped to the piece
                     const int32_t blk = tile_start + entry_lane * GROUP;
                     const int32_t blk_begin = blk > base ? blk : base;
@@ -222,7 +213,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
                             if (ends && begin == run_begin) {
                                 store_vec_stream<VEC>(a.Y + (int64_t)row * a.J + k_lane, sum);
                             } else {
-                                from_last_columns<VEC, RAGGED>(sum, (int)((uint32_t)k0 + chunk * VEC - k_lane));
+                                from_last_columns<VEC, RAGGED>(sum, (int)(k - k_lane));
                                 merge_add<VEC, (LC >= 8)>(mb, begin < 0 ? mb.nslots - 1 : (begin - tile_start) / GROUP,
                                                           chunk * VEC, sum, chunk == 0 && run_begin == (begin < 0 ? base : begin),
                                                           row, begin < 0 || s_end[w] > end);
@@ -286,7 +277,7 @@ __global__ __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(4))) voi
                             }
                         }
                     }
-                    __syncthreads();  // all sums of this pass are in LDS
+                    __syncthreads();  // all sums are in LDS
                     merge_write_out<LC, VEC, RAGGED>(out, mb, k, k_ok);
                 }
                 __syncthreads();  // slots are clear again, the piece is consumed
@@ -315,18 +306,16 @@ struct LaunchSerial {
     void go() const
     {
         auto kernel = mttkrp_serial_kernel<LC, VEC, OFF32, RAGGED>;
-        constexpr int most = kMsX1Bytes / (LC * VEC * 4);
-        constexpr int x1_rows = most < kMsFibers ? most : kMsFibers;
-        constexpr int smem = x1_rows * LC * VEC * 4 + (kBlock / LC + 1) * (LC * VEC * 4 + 8);
+        constexpr int smem = kMsFibers * LC * VEC * 4 + (kBlock / LC + 1) * (LC * VEC * 4 + 8);
         static const int per_cu = resident_per_cu(kernel, smem);
         const int grid = persistent_grid(per_cu, compute_units, nnz_hint, kMsTile);
-        hipLaunchKernelGGL(kernel, dim3(grid), dim3(kBlock), smem, s, a, x1_rows);
+        hipLaunchKernelGGL(kernel, dim3(grid), dim3(kBlock), smem, s, a);
     }
     template <int G, int LC, int VEC>
     void operator()() const
     {
         constexpr bool WIDE = VEC > 1;  // rows whose columns the lanes need not divide
-        if constexpr (LC * VEC > kMsColumns) return;
+        if constexpr (LC * VEC > kMsColumns) return;  // (launch_mttkrp_serial asks for none)
         else if (!off32) go<LC, VEC, false, WIDE>();
         else if (WIDE && a.J % VEC != 0) go<LC, VEC, true, WIDE>();
         else go<LC, VEC, true, false>();
@@ -348,7 +337,7 @@ bool mttkrp_serial_applies(int64_t J, int64_t nnz_hint)
 hipError_t launch_mttkrp_serial(const MttkrpArgs& a, int lc, int vec, int compute_units, int64_t nnz_hint,
                                 hipStream_t s)
 {
-    if (a.J > kMsColumns) return hipErrorInvalidValue;
+    if (a.J > kMsColumns || lc * vec > kMsColumns) return hipErrorInvalidValue;
     if (!dispatch_lc<1>(lc, vec, LaunchSerial{a, compute_units, nnz_hint, offsets_fit_32(a.K, a.J) && offsets_fit_32(a.L, a.J), s}))
         return hipErrorInvalidValue;
     return hipGetLastError();
