@@ -194,20 +194,26 @@ __device__ __forceinline__ bool flat_deal(SH& s, int32_t e0, int32_t cnt, int n,
 // The sum of a batch's products, four and four: one chain of additions as long as a team's share of a row had up to 1.7 times the
 // error of the groups' trees and of their members' and lanes' short chains.
 template <int VEC>
-__device__ __forceinline__ Vec<VEC> flat_dot(const StagedEntry (&e)[kFlatBatch], const Vec<VEC> (&b)[kFlatBatch])
+__device__ __forceinline__ Vec<VEC> flat_dot_half(const StagedEntry* e, const Vec<VEC>* b)
 {
-    constexpr int H = kFlatBatch / 2;
     Vec<VEC> sum;
 #pragma unroll
     for (int i = 0; i < VEC; ++i) {
-        float low = e[0].val * b[0].v[i], high = e[H].val * b[H].v[i];
+        float t = e[0].val * b[0].v[i];
 #pragma unroll
-        for (int u = 1; u < H; ++u) {
-            low = __builtin_fmaf(e[u].val, b[u].v[i], low);
-            high = __builtin_fmaf(e[H + u].val, b[H + u].v[i], high);
-        }
-        sum.v[i] = low + high;
+        for (int u = 1; u < kFlatBatch / 2; ++u) t = __builtin_fmaf(e[u].val, b[u].v[i], t);
+        sum.v[i] = t;
     }
+    return sum;
+}
+
+template <int VEC>
+__device__ __forceinline__ Vec<VEC> flat_dot(const StagedEntry (&e)[kFlatBatch], const Vec<VEC> (&b)[kFlatBatch])
+{
+    Vec<VEC> sum = flat_dot_half<VEC>(e, b);
+    const Vec<VEC> high = flat_dot_half<VEC>(e + kFlatBatch / 2, b + kFlatBatch / 2);
+#pragma unroll
+    for (int i = 0; i < VEC; ++i) sum.v[i] += high.v[i];
     return sum;
 }
 

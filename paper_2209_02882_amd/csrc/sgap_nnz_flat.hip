@@ -2,19 +2,19 @@
 // teams of lanes that go through them each at its own pace (sgap_flat.hpp), whatever group_size says.
 //
 // A tile of stored entries comes into LDS with its rows that have entries.  A team takes consecutive entries, eight of one
-// row at a time; a row that begins and ends among them is stored plainly.  What a team has of a row that began in front of
-// it goes to LDS, where the team that has the row's beginning adds it up in order; the two rows that cross a tile's ends are
-// added into C with atomics (the merge rule of sgap_nnz_common.hpp with the tile as its block).  No LDS atomics, no slots.
+// row at a time, or the last four of one and the first four of the next; a row that begins and ends among them is stored
+// plainly.  What a team has of a row that began in front of it goes to LDS, where the team that has the row's beginning adds it
+// up in order; the two rows that cross a tile's ends are added into C with atomics (the merge rule of sgap_nnz_common.hpp with the
+// tile as its block).  No LDS atomics, no slots.
 // The teams' shares are even in the turns that they take rather than in entries: a row counts kRowCost entries beside its own,
 // since its last turn is seldom full (R-MAT, 2^19 rows, N = 32: 158 us with shares of entries, 115 so).
 //
 // With fixed shares, batches of eight whatever the rows' ends, and a flush wherever one fell (nnz_serial_kernel, which serves
 // other widths), each entry cost a look at its row's end and row sums met in LDS slots by compare-and-swap.  Large R-MAT
 // matrices are bound by their 128-byte reads either way (2^21 rows, 50 M entries, N = 32: 6.2 TB/s).  us, before / now:
-//   power law, 65,536 rows, N = 64, G = 16 52.1 / 43.4; the same with N = 32 46.0 / 25.8; 300,000 rows, N = 64 198 / 190;
-//   10,000 rows, N = 85 19.7 / 14.6; 8,000 rows, N = 20 14.4 / 13.0; uniform, 60,000 rows of 32, N = 64, G = 8 103 / 65;
-//   R-MAT, 2^21 rows, 30 M edges, N = 32, G = 16 501 / 422, 50 M entries, G = 32 711 / 707; 2^19 rows, 8 M edges, N = 32 148 / 112,
-//   N = 16, G = 2 395 / 100; 2^17 rows, 2.5 M edges, N = 128 121 / 114
+//   power law, 65,536 rows, N = 64, G = 16 52.2 / 43.9; the same with N = 32 45.9 / 23.7; 300,000 rows, N = 64 197 / 192;
+//   8,000 rows, N = 20 14.2 / 13.1; uniform, 60,000 rows of 32, N = 64, G = 8 101 / 65; R-MAT, G = 16, 2^19 rows, 8 M edges, N = 32
+//   156 / 112, N = 16 124 / 95; 2^17 rows, 1.9 M edges, N = 128 137 / 108; 2^21 rows, 50 M entries, N = 32, G = 32 747 / 717
 #include "sgap_common.hpp"
 #include "sgap_flat.hpp"
 #include "sgap_nnz_common.hpp"
@@ -133,31 +133,51 @@ void nnz_flat_kernel(SpmmArgs a, int lanes, int teams, int tile)
                     wi = s.begin_row[p.team];
                     bool whole = s.win[wi] - tile_start == q;  // the row begins with this team's entries
                     int32_t row_end = s.win[wi + 1] - tile_start;
+                    auto end_of = [&](int row) { return s.win[row + 1 <= n ? row + 1 : n] - tile_start; };
 #pragma unroll 1
                     do {
-                        constexpr int D = kFlatBatch;
+                        constexpr int D = kFlatBatch, H = D / 2;
                         StagedEntry e[D];
                         Vec<4> b[D];
                         const int32_t stop = row_end < end ? row_end : end;
                         const int32_t left = stop - q;
+                        const bool ends = left <= D, row_done = ends && row_end <= end;
+                        // Half a batch is enough for the row's last entries: the other half is the next row's.  (Rows of one to four entries
+                        // are a turn for two of them: power law of 40,000 rows, longest first, N = 64 40.2 us with a turn each, 33.2 so; 65,536 in
+                        // no order 43.8 / 44.8; 500,000 of 1 to 9 101.8 / 94.7; R-MAT, 2^15 rows 23 / 21.5.)
+                        const bool two = left <= H && row_end < end;
+                        const int32_t next_end = end_of(wi + 1), after_end = end_of(wi + 2);
+                        const int32_t at = two ? row_end : q + H;
+                        const int32_t left_there = (two ? (next_end < end ? next_end : end) : stop) - at;
 #pragma unroll
-                        for (int u = 0; u < D; ++u) e[u] = s.entry[q + u];
+                        for (int u = 0; u < H; ++u) {
+                            e[u] = s.entry[q + u];
+                            e[H + u] = s.entry[at + u];
+                        }
 #pragma unroll
-                        for (int u = 0; u < D; ++u) {
+                        for (int u = 0; u < H; ++u) {
                             b[u] = B.load(e[u].col, u < left);
                             if (u >= left) e[u].val = 0.0f;
                         }
-                        const bool ends = stop - q <= D;
-                        const bool row_done = ends && row_end <= end;
-                        const int now = wi;
-                        q = ends ? stop : q + D;
-                        if (row_done) {
-                            ++wi;
-                            row_end = s.win[wi + 1 <= n ? wi + 1 : n] - tile_start;
-                        }
-                        const Vec<4> batch = flat_dot<4>(e, b);
 #pragma unroll
-                        for (int i = 0; i < 4; ++i) sum.v[i] += batch.v[i];
+                        for (int u = 0; u < H; ++u) {
+                            b[H + u] = B.load(e[H + u].col, u < left_there);
+                            if (u >= left_there) e[H + u].val = 0.0f;
+                        }
+                        const int now = wi;
+                        const bool both_done = two && left_there <= H && next_end <= end;  // the next row too
+                        q = two ? at + (left_there < H ? left_there : H) : ends ? stop : q + D;
+                        if (row_done) {
+                            wi += both_done ? 2 : 1;
+                            row_end = both_done ? after_end : next_end;
+                        }
+                        const Vec<4> low = flat_dot_half<4>(e, b);
+                        Vec<4> high = flat_dot_half<4>(e + H, b + H);
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) {
+                            sum.v[i] += low.v[i] + (two ? 0.0f : high.v[i]);
+                            high.v[i] = two ? high.v[i] : 0.0f;
+                        }
                         if (row_done) {
                             if (whole) {
                                 store(s.row[now], sum);
@@ -165,9 +185,14 @@ void nnz_flat_kernel(SpmmArgs a, int lanes, int teams, int tile)
                                 s.heads.head[p.tid] = sum;
                                 head_ends = true;
                             }
-                            sum.zero();
+                            sum = high;
                             whole = true;
-                        } else if (ends) {
+                            if (both_done) {
+                                store(s.row[now + 1], sum);
+                                sum.zero();
+                            }
+                        }
+                        if (q >= end && !(two ? both_done : row_done)) {
                             if (whole) goes_on = true;
                             else s.heads.head[p.tid] = sum;
                         }
@@ -213,22 +238,21 @@ void nnz_flat_kernel(SpmmArgs a, int lanes, int teams, int tile)
 }
 
 // The tile for a matrix, 0 where this is not the kernel (us, by shares of entries / here).  Fewer columns leave a team with a lane or
-// two (65,536 rows of a power law, N = 8: 19.9 / 24.0; 8,000, N = 16 11.8 / 13.8, N = 20 14.2 / 13.0), with more a tile has too few teams
+// two (65,536 rows of a power law, N = 8: 19.9 / 24.0; 8,000, N = 16 11.9 / 13.9, N = 18 14.5 / 13.0), with more a tile has too few teams
 // (100,000 rows, N = 200 220 / 219; R-MAT, 2^17 rows, N = 256 276 / 282).  Where rows are long and the caller asks for shares of 64
 // entries nothing is left for this kernel to gain (5,000 rows of 4,000, N = 16 179 / 199; 10,000 of 200, N = 64 63.8 / 65.8; shares of 16,
-// 40,000 of 300, N = 16 145 / 122), nor where rows are short, many and wide, and shares are not (500,000 of 1 to 9, N = 64 96.6 / 101.9, shares
-// of 8 116 / 102; 60,000 22.6 / 20.8).
+// 40,000 of 300, N = 16 145 / 122).
 // A team has some 16 to 32 entries of a tile; 33 to 64 columns take the larger tile where all of them fit the chip at once
 // (power law, 65,536 rows, N = 64: 43.4 us with 1,030 tiles of 1,024 entries, 45.7 with 512; 300,000 rows 200 and 192).  A small matrix
 // has smaller tiles (10,000 rows, N = 44 16.6 us with 512 entries and 17.3 with 1,024).
-// Power laws whose rows come in order of their lengths end in tiles of a row to an entry, a turn each: 40,000 rows, G = 16, N = 32 31.3 / 24.9,
-// but N = 64 34.1 / 41.5, N = 128 54.6 / 65.0; 150,000, N = 32 61 / 70, N = 64 97 / 115, N = 128 188 / 193.
+// Power laws whose rows come in order of their lengths, the longest first, end in tiles of a row to an entry: 40,000 rows, G = 16, N = 32 31.3 /
+// 21.1, N = 64 34.1 / 33.2, N = 128 55 / 58; 150,000, N = 32 61 / 60, N = 48 93 / 103, N = 64 98 / 107, N = 128 188 / 189.
 int nnz_flat_tile(int64_t N, int group, double mean_row, int64_t nnz_hint, int compute_units)
 {
     if (N < 16 || N > 128 || (N <= 64 && group > 32 && mean_row >= 200.0)) return 0;
     int tile = N <= 32 ? kNfTile : N <= 64 ? kNfTile / 2 : kNfTile / 4;
     if (nnz_hint < 0) return tile;
-    if ((N < 20 && nnz_hint < 250'000) || (N > 32 && group >= 16 && mean_row < 8.0 && nnz_hint >= 1'000'000)) return 0;
+    if (N < 18 && nnz_hint < 250'000) return 0;
     if (N > 32 && N <= 64 && nnz_hint > kNfTile * 3 * (int64_t)compute_units && nnz_hint <= kNfTile * kNfResident * (int64_t)compute_units)
         tile = kNfTile;
     const int least = N <= 32 ? kNfTile / 2 : kNfTile / 4;

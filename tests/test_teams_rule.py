@@ -51,9 +51,8 @@ def test_row_split_serial(N, g, nnz, M, K, takes):
 
 
 @pytest.mark.parametrize("N,g,nnz,M,takes", [
-    (16, 16, 250_000, 20_000, 1), (16, 16, 249_999, 20_000, 0), (20, 16, 10_000, 1000, 1), (15, 16, 300_000, 20_000, 0), (128, 16, 300_000, 20_000, 1),
+    (17, 16, 250_000, 20_000, 1), (17, 16, 249_999, 20_000, 0), (18, 16, 10_000, 1000, 1), (15, 16, 300_000, 20_000, 0), (128, 16, 300_000, 20_000, 1),
     (129, 16, 300_000, 20_000, 0), (64, 64, 400_000, 2000, 0), (64, 32, 400_000, 2000, 1), (65, 64, 400_000, 2000, 1), (64, 64, 399_999, 2000, 1),
-    (33, 16, 1_000_000, 130_000, 0), (32, 16, 1_000_000, 130_000, 1), (33, 8, 1_000_000, 130_000, 1), (33, 16, 999_999, 130_000, 1), (33, 16, 1_040_000, 130_000, 1),
     (64, 16, -1, 20_000, 1),
 ])
 def test_nnz_balanced_serial(N, g, nnz, M, takes):
