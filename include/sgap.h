@@ -91,11 +91,16 @@ typedef enum {
  *       tile_cols admits more.  A row of at least 96*g entries (or fewer where
  *       a tile takes several passes, never below 256) is taken by a whole
  *       workgroup instead of holding one group up; it still has one plain
- *       store.  At 12 to 64 columns and 300,000 entries or more (nnz_hint;
- *       700,000 below 24 columns), 128 a row in the mean at most, and with the
- *       layout left to the library, lanes share what a block of rows has evenly
- *       instead: every group_size (from 16 on up to 16 columns) names the
- *       same launch.
+ *       store.  At 12 to 64 columns, with a count of entries (nnz_hint) and
+ *       the layout left to the library, lanes share what a block of rows has
+ *       evenly instead, and every group size that comes to it names the same
+ *       launch: up to 12 entries a row in the mean and 300,000 in all (above 40
+ *       columns a B of 32 MB at most); up to 20 a row and 500,000 up to 32
+ *       columns, 300,000 up to 48 with a B of 12 MB at most.  Groups of fewer
+ *       than 8 members (as g above) up to 32 columns, and of fewer than 16 or
+ *       with fewer than 1,000,000 entries below 24, keep the launch above.  A
+ *       row's entries are then added up in chains of four, whose sums are two
+ *       chains: no further from the exact sum than the tree is.
  *     nnz-balanced schedule: lane = one stored entry ({<1 nnz, c col>, r},
  *       Section 6.2); the group performs a SEGMENTED reduction keyed by row
  *       (Fig. 1c), one writeback lane per run of equal rows.  At N <= 16 a
@@ -112,16 +117,23 @@ typedef enum {
  *       64 columns, 40,960 up to 128, 20,480 beyond), group sizes 1, 2 and 4
  *       name the same launch: a lane has four consecutive rows, and a row of B
  *       that several of them want is gathered once.  Setting block_size or
- *       persistent (below) gives the launch row by row.  Where rows have 12
- *       entries or fewer in the mean and 500,000 in all, every group_size
- *       names the same launch (up to 48 columns; beyond, where B or a column
- *       tile of it is small).
+ *       persistent (below) gives the launch row by row.  Where nnz_hint says
+ *       that rows have 12 entries or fewer in the mean and 500,000 in all,
+ *       lanes share what a block of rows has evenly instead, whatever
+ *       group_size is among those that come to it: 8 and more up to 48
+ *       columns, 4 up to 16, 2 up to 4 (and 2,000,000 entries); the others,
+ *       and more columns, where the columns fill sectors of 32 bytes, B or a
+ *       column tile of it is small, and rows have 8.75 entries or fewer in the
+ *       mean (750,000 entries up to 32 columns).
  *     nnz-balanced schedule: lane = group_size consecutive stored entries
  *       ({<g nnz, c col>, 1}, Section 6.1), or fewer where that many per lane
  *       are more than a tile has (a tile of 1,024 entries at N = 64 has 64 for
  *       each of 16 lanes; small matrices get smaller tiles).  At 16 to 128
  *       columns, unless nnz_tile is set, the lanes of a tile share its rows and
- *       entries evenly and every group_size names the same launch.
+ *       entries evenly and every group_size names the same launch, but
+ *       group_size 64 up to 64 columns where rows have 200 entries or more in
+ *       the mean, and matrices of fewer than 250,000 entries at 16 and 17
+ *       columns, keep the lanes' own runs.
  *
  * In the nnz-balanced schedule a row whose stored entries all lie inside one
  * aligned block of positions (group_size positions, or a whole tile of about a
@@ -456,9 +468,12 @@ int sgap_ttm_csf(int64_t F, int64_t K, int64_t L,
  *   X1, X2    device, K x J and L x J row-major
  *   Y         device, I x J row-major; OVERWRITTEN
  *   group_size, strategy
- *             SGAP_REDUCE_PARALLEL: the lanes of a workgroup share the fibers
- *             of a block of slices evenly, whatever group_size is, and add up
- *             a slice's sums in a fixed order;
+ *             SGAP_REDUCE_PARALLEL: group_size lanes (per column chunk) share
+ *             the fibers of one slice and combine their sums in a tree; from 80
+ *             columns on (and, with a count of entries, where
+ *             sgap_mttkrp_csf_ex says) the lanes of a workgroup share the
+ *             fibers of a block of slices evenly, whatever group_size is, and
+ *             add up a slice's sums in a fixed order;
  *             SGAP_REDUCE_SERIAL: one lane (per column chunk) works through
  *             group_size consecutive slices by itself.
  * Slices are the unit of work (row-split schedule): every element of Y has
@@ -478,9 +493,14 @@ int sgap_mttkrp_csf(int64_t I, int64_t K, int64_t L, int64_t J,
 /*
  * The same operator with a choice of schedule (Section 6's two schedules
  * carried over to it):
- *   SGAP_SCHED_ROW_SPLIT     slices are the unit of work: exactly
- *                            sgap_mttkrp_csf (parallel: nnz_hint
- *                            sizes the blocks of slices)
+ *   SGAP_SCHED_ROW_SPLIT     slices are the unit of work, as
+ *                            sgap_mttkrp_csf.  parallel with nnz_hint: lanes
+ *                            share a block's fibers from 48 columns on
+ *                            (group sizes 1 and 2: with 12 entries a slice
+ *                            in the mean), from 20 on with 150,000 entries
+ *                            (or, from 32 on, 12 a slice), from 12 on with
+ *                            300,000, below with 400,000 and 10 * group_size
+ *                            a slice; nnz_hint sizes the blocks
  *   SGAP_SCHED_NNZ_BALANCED  stored entries are the unit of work, in tiles of
  *                            1,024, whatever slices and fibers they fall in (a
  *                            tensor with a few huge slices keeps the chip
@@ -490,7 +510,10 @@ int sgap_mttkrp_csf(int64_t I, int64_t K, int64_t L, int64_t J,
  *                            rows of X1, by slice.  serial: the lanes
  *                            share a tile's (1,024 to 2,000 entries) fibers
  *                            evenly, whatever G is, and close slices into Y
- *                            where they end.
+ *                            where they end (up to 8 columns and with fewer
+ *                            than 500,000 entries, 700,000 below 8, 2,000,000
+ *                            / J below 4, a lane has an even share of a tile's
+ *                            entries).
  *                            Y is set to zero first and every run's sum is
  *                            added with fp32 atomics: results agree from run
  *                            to run within rounding only.
@@ -599,7 +622,8 @@ int sgap_version(void);
  *                        serial strategy takes group_size rows by definition);
  *                        0 = automatic, from the mean row length.  Also the
  *                        slices per group of sgap_mttkrp_csf's parallel strategy
- *                        (automatic: about 16 slices per workgroup).
+ *                        (set: a group has a slice to itself whatever the
+ *                        columns; automatic: about 16 slices per workgroup).
  *   SGAP_TUNE_PERSISTENT 1: the row-split schedule launches only as many
  *                        workgroups as the chip holds at once and each loops
  *                        over work items; 0 (default): one workgroup per item.
