@@ -131,25 +131,21 @@ int64_t flat_tile(int64_t K, int64_t N)
 
 }  // namespace
 
-// Where a lane group per row is the better one (us, that / this).  One row to a lane: up to 16 columns, which leave a team a lane or few
-// (760,000 rows of 8, N = 1 17.4 / 24.9; 200,000 of 1 to 19, N = 3 10.4 / 14.4, N = 16 16.6 / 18.6); rows that begin amid sectors of
-// 32 bytes (500,000 of 8, N = 28 68 / 74; 700,000 of 1 to 11 104.8 / 117.8, with N = 32 82.7 / 78.9); rows that fill a batch of eight and a little
-// of the next (60,000 of 9, N = 32 7.1 / 8.2; 200,000 of 10 21.5 / 23.5); a B from beyond the L2s that no tiles cut (500,000 of 8, N = 24, 6.3 MB
-// 55.0 / 57.0, N = 32, 8.4 MB 51.8 / 52.5, 250,000 of 1 to 15 32.9 / 31.1; 700,000 of 1 to 11, N = 24, 12.5 MB 89 / 92); few entries (64,000 of 1 to
-// 15, N = 32, two rows to a lane 10.7 / 11.2, N = 40 19 / 17); 24 and 32 columns of very short rows, where blocks of equal numbers of
-// rows may be uneven (300,000 of 3 in the mean, N = 32 31.8 / 21.7, in order of their lengths 31.6 / 36.2, N = 40 50 / 33 and 52.7 / 50.9).  More rows
-// to a lane are a longer chain there, and sooner lose: four, N = 16 as above, N = 8 45.7 / 22.3; two, N = 4 14 / 7.5 for 64,000 of 1 to 15,
-// but N = 1 20.5 / 25.2 for 760,000 of 8.
+// Where a lane group per row is the better one (us, that / this): few entries, one row to a lane (331,000 and 16 to a row, N = 64 12.5 / 15.5;
+// 353,000, N = 20 7.5 / 7.4; 593,000 of 7 in the mean, N = 32 15.4 / 11.8); up to eleven columns, which leave a team a lane or few, one row to a
+// lane and not many entries (672,000, N = 2 6.7 / 10.6; 1.3 M, 3 to a row, N = 6 12.1 / 17.0; 5.5 M, N = 1 28.6 / 21.7, 1.9 M, N = 8 16.0 / 14.1; two
+// rows to a lane, 588,000, N = 4 7.5 / 8.3); wide rows of a B larger than an L2 that no tiles cut.  Rows that all fill a batch of eight and a
+// little of the next are the shape that teams take longer for (1.3 M rows of 9, N = 28 137 / 154, 727,000, N = 64, four rows to a lane 105 / 116;
+// 58,000, N = 24 8.3 / 9.2), and so are some matrices in order of their rows' lengths, of which blocks of equal numbers of rows have uneven shares
+// (121,000 rows of 9 in the mean, N = 32 23.5 / 38.7; but 624,000 entries, 10 to a row, N = 6 8.2 / 6.4).  Where rows have mixed
+// lengths the gain is larger, and the host cannot tell them apart (2.0 M entries, 10 to a row, N = 30 31.3 / 27.6; 665,000, N = 24 13.1 / 10.8; 521,000,
+// 3 to a row, N = 64 28.2 / 17.9; 679,000, 8 to a row, N = 40 19.5 / 15.0).
 bool flat_rows_apply(int64_t K, int64_t N, int group, double mean_row, int64_t nnz_hint)
 {
-    constexpr int64_t kFlatMinEntries = 500'000;
-    constexpr double kFlatMean = 12.0, kFlatWideMean = 8.75;
-    if (nnz_hint < kFlatMinEntries || mean_row > kFlatMean) return false;
-    const bool whole = K * N * 4 <= (N < 32 ? 5 << 20 : N <= 48 ? 13 << 20 : 6 << 20), tiles = flat_tile(K, N) < N;
-    if (group >= 8) return N <= 48 || tiles || (N <= 64 && whole);
-    if (N < 24) return (group >= 4 && N <= 16) || (group >= 2 && N <= 4 && nnz_hint < 2'000'000);
-    if (N < 40 && (nnz_hint < 750'000 || (group < 4 && mean_row < 5.0))) return false;
-    return N % 8 == 0 && mean_row <= kFlatWideMean && (tiles || (N <= 64 && whole));
+    constexpr int64_t kFlatMinEntries = 500'000, kFlatFewColumns = 1'400'000;
+    constexpr double kFlatMean = 12.0;
+    if (nnz_hint < kFlatMinEntries || mean_row > kFlatMean || (group < 2 && N < 12 && nnz_hint < kFlatFewColumns)) return false;
+    return N <= 48 || flat_tile(K, N) < N || (N <= 64 && K * N * 4 <= (6 << 20));
 }
 
 hipError_t launch_flat_rows(const SpmmArgs& a, int vec, int xcds, int compute_units, int64_t nnz_hint, hipStream_t s)

@@ -254,21 +254,19 @@ void flat_shared_rows_kernel(SpmmArgs a, int lanes, int block_rows, FlatBlocks b
     }
 }
 
-// Where groups of lanes are the better ones (us, group per row / this): few entries (power laws, 20,000 rows, N = 24, G = 8 15.1 / 16.8, N = 32
-// 15.8 / 18.1; 50,000, N = 12, G = 32 22.7 / 24.9, 120,000, N = 16 46 / 42; uniform, 5,000 rows of 16, N = 32 5.3 / 6.1), few
-// columns (50,000 rows, N = 8 17.5 / 24.3, N = 4 16.2 / 32), groups of few members, which have few idle ones (60,000 rows of 12, G = 4, N =
-// 32 12.8 / 15.6, N = 48, where a group's columns leave it no more anyway, 26.8 / 21.6; up to 16 columns groups of 8: 46,000 rows, N = 13
-// 17.5 / 21.8), longer rows (10,000 of 120, N = 32 14.5 / 15.8, N = 48 26.6 / 29.1; 30,000 of 1 to 63, N = 24 18.1 / 18.1, N = 64 30.2 /
-// 32.3; of 20, N = 32 21.8 / 16.6, N = 48 30.7 / 30.9), and wide rows from beyond the L2s (power laws, 120,000 rows, B of 18 MB, N = 37
-// 72.6 / 75.1, of 28 MB, N = 58 94 / 98; 50,000, N = 58 45.8 / 48.2).
+// Where groups of lanes are the better ones (us, group per row / this): few entries (ragged rows, 346,000 entries, 24 to a row, N = 37
+// 9.0 / 11.4; power laws, 159,000, N = 17 11.4 / 18.5, 590,000, N = 27 17.6 / 20.1, but 849,000, N = 31 37.6 / 34.5, 2.9 M, N = 23 60 / 47, N = 17
+// 73 / 59), fewer where rows are short, which leave most members idle (302,000 entries, 4 to a row, N = 60 26 / 21; 458,000, 12 to a row, N = 41
+// 13.9 / 10.9; groups of four have fewer idle ones: 604,000, 15 to a row, N = 31 13.8 / 15.3, 907,000, 13 to a row, N = 25 17.9 / 15.5); few columns
+// (50,000 rows, N = 8 17.5 / 24.3; 46,000, N = 13, G = 8 17.5 / 21.8; groups of 16: 2.1 M entries, N = 14 42.2 / 39.2); long rows (650,000 entries,
+// 37 to a row, N = 31 17.3 / 20.6, 1.8 M, 39 to a row, N = 55 58.0 / 59.7; 3.3 M, 34 to a row, N = 25, G = 4 36.9 / 36.8); wide rows of a B from
+// beyond the L2s (500,000 rows of 16, N = 64 292 / 309).
 bool flat_shared_rows_apply(int64_t K, int64_t N, int members, double mean_row, int64_t nnz_hint)
 {
-    constexpr double kRowMean = 20.0, kShortRowMean = 12.0;
-    if (N < 12 || N > 64 || mean_row > kRowMean) return false;
-    if (N < 24) return members > 8 && nnz_hint >= 1'000'000;
-    if (N <= 32 && members < 8) return false;
-    if (mean_row <= kShortRowMean) return nnz_hint >= 300'000 && (N <= 40 || K * N * 4 <= (32 << 20));
-    return N <= 32 ? nnz_hint >= 500'000 : N <= 48 && nnz_hint >= 300'000 && K * N * 4 <= (12 << 20);
+    constexpr double kRowMean = 35.0, kShortRowMean = 12.0;
+    if (N < 12 || N > 64 || mean_row > kRowMean || (N < 17 && members < 16) || (N > 40 && K * N * 4 > (32 << 20))) return false;
+    if (mean_row <= kShortRowMean && N >= 20 && (N > 32 || members >= 8) && nnz_hint >= 300'000) return true;
+    return nnz_hint >= (N < 24 ? 700'000 : 600'000);
 }
 
 hipError_t launch_flat_shared_rows(const SpmmArgs& a, int xcds, int compute_units, int64_t nnz_hint, hipStream_t s)

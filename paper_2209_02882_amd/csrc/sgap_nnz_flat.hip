@@ -11,7 +11,7 @@
 //
 // With fixed shares, batches of eight whatever the rows' ends, and a flush wherever one fell (nnz_serial_kernel, which serves
 // other widths), each entry cost a look at its row's end and row sums met in LDS slots by compare-and-swap.  Large R-MAT
-// matrices are bound by their 128-byte reads either way (2^21 rows, 50 M entries, N = 32: 6.2 TB/s).  us, before / now:
+// matrices are bound by their 128-byte reads either way (2^21 rows, 50 M entries, N = 32: 4.4 GB at 6.1 TB/s).  us, before / now:
 //   power law, 65,536 rows, N = 64, G = 16 52.2 / 43.9; the same with N = 32 45.9 / 23.7; 300,000 rows, N = 64 197 / 192;
 //   8,000 rows, N = 20 14.2 / 13.1; uniform, 60,000 rows of 32, N = 64, G = 8 101 / 65; R-MAT, G = 16, 2^19 rows, 8 M edges, N = 32
 //   156 / 112, N = 16 124 / 95; 2^17 rows, 1.9 M edges, N = 128 137 / 108; 2^21 rows, 50 M entries, N = 32, G = 32 747 / 717
@@ -238,7 +238,7 @@ void nnz_flat_kernel(SpmmArgs a, int lanes, int teams, int tile)
 }
 
 // The tile for a matrix, 0 where this is not the kernel (us, by shares of entries / here).  Fewer columns leave a team with a lane or
-// two (65,536 rows of a power law, N = 8: 19.9 / 24.0; 8,000, N = 16 11.9 / 13.9, N = 18 14.5 / 13.0), with more a tile has too few teams
+// two (65,536 rows of a power law, N = 8: 19.9 / 24.0; 8,000, N = 16 11.9 / 13.9, N = 17 14.3 / 13.2; 16,000, N = 16 13.7 / 14.9, 38,000 23.1 / 18.9; uniform rows gain there too, 18,000, N = 16 15.1 / 11.0), with more a tile has too few teams
 // (100,000 rows, N = 200 220 / 219; R-MAT, 2^17 rows, N = 256 276 / 282).  Where rows are long and the caller asks for shares of 64
 // entries nothing is left for this kernel to gain (5,000 rows of 4,000, N = 16 179 / 199; 10,000 of 200, N = 64 63.8 / 65.8; shares of 16,
 // 40,000 of 300, N = 16 145 / 122).
@@ -252,7 +252,7 @@ int nnz_flat_tile(int64_t N, int group, double mean_row, int64_t nnz_hint, int c
     if (N < 16 || N > 128 || (N <= 64 && group > 32 && mean_row >= 200.0)) return 0;
     int tile = N <= 32 ? kNfTile : N <= 64 ? kNfTile / 2 : kNfTile / 4;
     if (nnz_hint < 0) return tile;
-    if (N < 18 && nnz_hint < 250'000) return 0;
+    if (N < 17 && nnz_hint < 250'000) return 0;
     if (N > 32 && N <= 64 && nnz_hint > kNfTile * 3 * (int64_t)compute_units && nnz_hint <= kNfTile * kNfResident * (int64_t)compute_units)
         tile = kNfTile;
     const int least = N <= 32 ? kNfTile / 2 : kNfTile / 4;

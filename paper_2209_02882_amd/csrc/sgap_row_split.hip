@@ -37,10 +37,12 @@ constexpr int kFinderEntries = 2048;  // ... unless most rows are long, and then
 constexpr int kSmallShare = 512;  // where groups have four members, or several passes, ...
 constexpr int kFewRows = 8192;    // ... and so few rows, the half of that in the mean is enough (20,000 rows of 200, N = 8, G = 4 29 us, by 2,048 finders 38)
 // Few entries leave the chip to the rows that workgroups take together; with more the others want the wavefront per SIMD that
-// those rows' registers cost.  us, without / with: power laws, G = 8, 3,000 rows, N = 64 8.7 / 7.0; 10,000, N = 24 10.2 / 8.8, N = 64 16.8 / 12.7;
-// N = 100 31 / 25; 20,000, N = 64 31.3 / 20.9, N = 32 15.6 / 12.1, but N = 16, G = 16 10.0 / 10.7; 60,000 rows of 21, N = 32 22.1 / 25.6, N = 48 32.2 /
-// 34.9; 15,000 of 16, N = 40 8.8 / 9.2, N = 32 8.0 / 8.1; 5,000 of 16, N = 100 7.0 / 7.3; 1,024 of 10, N = 32 3.05 / 3.12.
-constexpr int64_t kDeepFewest = 30'000, kDeepMost = 330'000, kDeepMostNarrow = 200'000;  // entries; up to 16 columns
+// those rows' registers cost, and where B is small there is little to wait for.  us, without / with: power laws, 3,000 rows, N = 64 8.7 / 7.0;
+// 10,000, N = 64 16.8 / 12.7; 361,000 entries, N = 39, B of 14 MB 48 / 35; 464,000, N = 42, of 3.2 MB 26.7 / 19.2; 508,000, N = 51 38.2 / 31.7; 2.7 M, N = 19, of 3 MB
+// 56.7 / 60.4; uniform, 84,000 entries, N = 56 5.8 / 6.8, 571,000, N = 56, B of 0.2 MB 13.7 / 16.3; 1.2 M, N = 14 18.0 / 20.4; 40 to a row, 316,000
+// entries, B of 0.8 MB 8.2 / 8.7; 1,024 rows of 10, N = 32 3.05 / 3.12.
+constexpr int64_t kDeepFewest = 30'000, kDeepMost = 600'000, kDeepBytes = 1 << 20;  // entries; of B
+constexpr double kDeepMean = 22.0;
 constexpr int64_t kDeepColumns = 64;
 constexpr int kFindersPerCu = 8;  // as many workgroups as are resident
 constexpr int kTeamRows = 256;    // a team of two looks through no more rows: a look of its workgroups' threads
@@ -112,7 +114,7 @@ hipError_t launch_row_split(const SpmmArgs& a, int g, int lc, int vec, int rows_
 {
     row_split_detail::Launch<false> f{a, rows_per_slot, interleave ? 1 : 0, tile_cols, xcds, compute_units,
                                       offsets_fit_32(a), persistent, 0, block, s, nnz_hint, mean_row <= kShortRowMean};
-    f.deep = a.N <= kDeepColumns && nnz_hint >= kDeepFewest && nnz_hint <= (a.N <= 16 ? kDeepMostNarrow : kDeepMost);
+    f.deep = a.N <= kDeepColumns && nnz_hint >= kDeepFewest && nnz_hint <= kDeepMost && mean_row <= kDeepMean && a.K * a.N * 4 >= kDeepBytes;
     if (!dispatch_group(g, lc, vec, f)) return hipErrorInvalidValue;
     return hipGetLastError();
 }

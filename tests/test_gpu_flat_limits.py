@@ -20,11 +20,11 @@ SPMM = [  # the kernel, columns, (strategy, schedule, count of entries that the 
     ("row-split parallel, shared blocks", n, (binding.SGAP_REDUCE_PARALLEL, binding.SGAP_SCHED_ROW_SPLIT, hint))
     for n, hint in ((13, 1_000_000), (24, 500_000), (37, 500_000), (40, 500_000))
 ] + [
-    ("row-split parallel, rows that a workgroup takes with fewer loads in flight", n, (binding.SGAP_REDUCE_PARALLEL, binding.SGAP_SCHED_ROW_SPLIT, 1_050_000))
+    ("row-split parallel, rows that a workgroup takes with fewer loads in flight", n, (binding.SGAP_REDUCE_PARALLEL, binding.SGAP_SCHED_ROW_SPLIT, 1_800_000))
     for n in (24, 37)
 ] + [
     ("row-split parallel, rows that a workgroup takes", n, (binding.SGAP_REDUCE_PARALLEL, binding.SGAP_SCHED_ROW_SPLIT, 200_000))
-    for n in (1, 3, 6, 37, 100)
+    for n in (1, 3, 6, 37, 48, 100)
 ] + [
     ("nnz-balanced serial", n, (binding.SGAP_REDUCE_SERIAL, binding.SGAP_SCHED_NNZ_BALANCED, 700_000)) for n in (16, 37, 64, 125)
 ]

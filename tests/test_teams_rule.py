@@ -19,12 +19,12 @@ def mttkrp(I, J, nnz, g, strategy, schedule):
 
 
 @pytest.mark.parametrize("N,g,nnz,M,K,takes", [
-    (24, 8, 300_000, 30_000, 10_000, 1), (24, 8, 299_999, 30_000, 10_000, 0), (24, 8, 400_000, 30_000, 10_000, 0),  # 10 and 13.3 to a row
-    (24, 8, 500_000, 30_000, 10_000, 1), (32, 8, 600_000, 30_000, 10_000, 1), (32, 8, 600_001, 30_000, 10_000, 0),
-    (32, 4, 500_000, 30_000, 10_000, 0), (33, 4, 500_000, 30_000, 10_000, 1), (23, 16, 1_000_000, 60_000, 10_000, 0),
-    (16, 16, 1_000_000, 60_000, 10_000, 1), (16, 8, 1_000_000, 60_000, 10_000, 0), (12, 16, 999_999, 60_000, 10_000, 0), (11, 16, 1_000_000, 60_000, 10_000, 0),
-    (48, 8, 600_000, 40_000, 65_536, 1), (48, 8, 600_000, 40_000, 65_537, 0), (49, 8, 600_000, 40_000, 10_000, 0),
-    (64, 8, 400_000, 40_000, 131_072, 1), (64, 8, 400_000, 40_000, 131_073, 0), (65, 8, 400_000, 40_000, 10_000, 0),
+    (24, 8, 300_000, 25_000, 10_000, 1), (24, 8, 299_999, 30_000, 10_000, 0), (24, 8, 300_001, 25_000, 10_000, 0),  # 12 to a row
+    (24, 8, 600_000, 30_000, 10_000, 1), (24, 8, 599_999, 30_000, 10_000, 0), (64, 4, 600_000, 30_000, 10_000, 1), (23, 8, 700_000, 30_000, 10_000, 1),
+    (23, 8, 699_999, 30_000, 10_000, 0), (32, 4, 300_000, 30_000, 10_000, 0), (33, 4, 300_000, 30_000, 10_000, 1), (20, 8, 300_000, 30_000, 10_000, 1),
+    (19, 8, 300_000, 30_000, 10_000, 0), (17, 4, 700_000, 30_000, 10_000, 1), (16, 8, 700_000, 30_000, 10_000, 0), (16, 16, 700_000, 30_000, 10_000, 1),
+    (12, 16, 700_000, 30_000, 10_000, 1), (11, 16, 700_000, 30_000, 10_000, 0), (48, 8, 1_050_000, 30_000, 10_000, 1), (48, 8, 1_050_001, 30_000, 10_000, 0),
+    (64, 8, 600_000, 40_000, 131_072, 1), (64, 8, 600_000, 40_000, 131_073, 0), (40, 8, 600_000, 40_000, 300_000, 1), (65, 8, 600_000, 40_000, 10_000, 0),
 ])
 def test_row_split_parallel(N, g, nnz, M, K, takes):
     assert spmm(M, K, N, nnz, g, "parallel", ROW) == takes
@@ -35,12 +35,9 @@ def test_row_split_parallel(N, g, nnz, M, K, takes):
 
 @pytest.mark.parametrize("N,g,nnz,M,K,takes", [
     (4, 4, 500_000, 50_000, 100_000, 1), (4, 4, 499_999, 50_000, 100_000, 0), (4, 1, 500_000, 50_000, 100_000, 0), (4, 2, 500_000, 50_000, 100_000, 1),
-    (4, 2, 2_000_000, 200_000, 100_000, 0), (5, 2, 500_000, 50_000, 100_000, 0), (16, 4, 600_000, 50_000, 100_000, 1), (16, 4, 600_001, 50_000, 100_000, 0),
-    (17, 4, 500_000, 50_000, 100_000, 0), (17, 8, 500_000, 50_000, 100_000, 1), (32, 1, 750_000, 100_000, 10_000, 1), (32, 1, 749_999, 100_000, 10_000, 0),
-    (32, 1, 750_000, 200_000, 10_000, 0), (32, 4, 750_000, 200_000, 10_000, 1), (40, 1, 500_000, 200_000, 10_000, 1), (41, 1, 500_000, 100_000, 10_000, 0),
-    (32, 1, 875_000, 100_000, 10_000, 1), (32, 1, 875_001, 100_000, 10_000, 0), (32, 1, 800_000, 100_000, 106_496, 1), (32, 1, 800_000, 100_000, 106_497, 0),
-    (24, 1, 800_000, 100_000, 54_613, 1), (24, 1, 800_000, 100_000, 54_614, 0), (64, 1, 800_000, 100_000, 24_000, 1), (64, 1, 800_000, 100_000, 114_688, 1),
-    (64, 1, 800_000, 100_000, 114_689, 0), (128, 1, 800_000, 100_000, 20_000, 1), (128, 1, 800_000, 100_000, 10_000, 0),
+    (1, 1, 1_400_000, 200_000, 100_000, 1), (11, 1, 1_399_999, 200_000, 100_000, 0), (12, 1, 500_000, 50_000, 100_000, 1), (48, 1, 600_000, 50_000, 100_000, 1),
+    (48, 1, 600_001, 50_000, 100_000, 0), (49, 1, 800_000, 100_000, 32_000, 1), (64, 1, 800_000, 100_000, 24_000, 1), (64, 1, 800_000, 100_000, 114_688, 1),
+    (64, 1, 800_000, 100_000, 114_689, 0), (65, 1, 800_000, 100_000, 10_000, 0), (128, 1, 800_000, 100_000, 20_000, 1), (128, 1, 800_000, 100_000, 10_000, 0),
 ])
 def test_row_split_serial(N, g, nnz, M, K, takes):
     # (what four neighbouring rows together come first for has longer rows)
@@ -51,7 +48,7 @@ def test_row_split_serial(N, g, nnz, M, K, takes):
 
 
 @pytest.mark.parametrize("N,g,nnz,M,takes", [
-    (17, 16, 250_000, 20_000, 1), (17, 16, 249_999, 20_000, 0), (18, 16, 10_000, 1000, 1), (15, 16, 300_000, 20_000, 0), (128, 16, 300_000, 20_000, 1),
+    (16, 16, 250_000, 20_000, 1), (16, 16, 249_999, 20_000, 0), (17, 16, 10_000, 1000, 1), (15, 16, 300_000, 20_000, 0), (128, 16, 300_000, 20_000, 1),
     (129, 16, 300_000, 20_000, 0), (64, 64, 400_000, 2000, 0), (64, 32, 400_000, 2000, 1), (65, 64, 400_000, 2000, 1), (64, 64, 399_999, 2000, 1),
     (64, 16, -1, 20_000, 1),
 ])
