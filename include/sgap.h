@@ -94,13 +94,13 @@ typedef enum {
  *       store.  At 12 to 64 columns, with a count of entries (nnz_hint) and
  *       the layout left to the library, lanes share what a block of rows has
  *       evenly instead, and every group size that comes to it names the same
- *       launch: up to 12 entries a row in the mean and 300,000 in all (above 40
- *       columns a B of 32 MB at most); up to 20 a row and 500,000 up to 32
- *       columns, 300,000 up to 48 with a B of 12 MB at most.  Groups of fewer
- *       than 8 members (as g above) up to 32 columns, and of fewer than 16 or
- *       with fewer than 1,000,000 entries below 24, keep the launch above.  A
- *       row's entries are then added up in chains of four, whose sums are two
- *       chains: no further from the exact sum than the tree is.
+ *       launch: up to 35 entries a row in the mean and 600,000 in all (700,000
+ *       below 24 columns), or up to 12 a row and 300,000 in all from 20 columns
+ *       on (from 33 on for groups of fewer than 8 members, as g above); below 17
+ *       columns only groups of 16 members and more, above 40 only with a B of
+ *       32 MB at most.  A row's entries are then added up in chains of four,
+ *       whose sums are two chains: no further from the exact sum than the tree
+ *       is.
  *     nnz-balanced schedule: lane = one stored entry ({<1 nnz, c col>, r},
  *       Section 6.2); the group performs a SEGMENTED reduction keyed by row
  *       (Fig. 1c), one writeback lane per run of equal rows.  At N <= 16 a
@@ -120,11 +120,9 @@ typedef enum {
  *       persistent (below) gives the launch row by row.  Where nnz_hint says
  *       that rows have 12 entries or fewer in the mean and 500,000 in all,
  *       lanes share what a block of rows has evenly instead, whatever
- *       group_size is among those that come to it: 8 and more up to 48
- *       columns, 4 up to 16, 2 up to 4 (and 2,000,000 entries); the others,
- *       and more columns, where the columns fill sectors of 32 bytes, B or a
- *       column tile of it is small, and rows have 8.75 entries or fewer in the
- *       mean (750,000 entries up to 32 columns).
+ *       group_size is (from 2 on up to 11 columns with fewer than 1,400,000
+ *       entries); above 48 columns, where B (6 MB at 64 columns) or a column
+ *       tile of it is small.
  *     nnz-balanced schedule: lane = group_size consecutive stored entries
  *       ({<g nnz, c col>, 1}, Section 6.1), or fewer where that many per lane
  *       are more than a tile has (a tile of 1,024 entries at N = 64 has 64 for
@@ -132,8 +130,8 @@ typedef enum {
  *       columns, unless nnz_tile is set, the lanes of a tile share its rows and
  *       entries evenly and every group_size names the same launch, but
  *       group_size 64 up to 64 columns where rows have 200 entries or more in
- *       the mean, and matrices of fewer than 250,000 entries at 16 and 17
- *       columns, keep the lanes' own runs.
+ *       the mean, and matrices of fewer than 250,000 entries at 16 columns,
+ *       keep the lanes' own runs.
  *
  * In the nnz-balanced schedule a row whose stored entries all lie inside one
  * aligned block of positions (group_size positions, or a whole tile of about a
